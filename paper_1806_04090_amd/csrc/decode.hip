@@ -7,7 +7,7 @@
 // and the workgroups, which all start together, go through listing, products and stores in step.
 // The same kernel adds the update to what `out` holds instead of overwriting it (the parameter server's step,
 // params += alpha * average gradient), and takes messages in the folded form (weight inside U).
-// Entry-wise messages: zero fill, then one scatter launch per message in call order (bit-identical from run to run).
+// Entry-wise and l_q messages: one launch that searches the messages' ascending coordinates (decode_sparse).
 #include <algorithm>
 #include <cstring>
 #include <vector>
@@ -201,61 +201,151 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
         }
 }
 
-__global__ __launch_bounds__(256) void fill_zero(float* __restrict__ out, long long n)
-{
-    const long long stride = (long long)gridDim.x * 256;
-    const bool vec = (((size_t)out) & 15) == 0;
-    const long long n4 = vec ? n / 4 : 0;
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < n4; q += stride)
-        ((float4*)out)[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (long long i = n4 * 4 + (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) out[i] = 0.0f;
-}
+// ------------------------------------------------------------------------------------------------
+// Entry-wise and l_q messages.  The kept coordinates of a message ascend, so a workgroup that owns SPARSE_TILE
+// consecutive outputs finds its own part of every message by a search, adds the parts up in LDS in the order of
+// the messages and writes its outputs once: one launch for a fill and a scatter per message, and the outputs of
+// several messages are not read back.  Inside a message the coordinates are distinct, so plain LDS read-add-writes
+// with a barrier between messages give the same bits in every run.
+// Bound: HBM write of the outputs.  11.17 M outputs, one message of 111,740 pairs: 11.4 us (before: 8.6 us fill + 4.1 us
+// scatter + 3 us upload of the descriptor); 16 messages 34 us (8.6 + 16 x 4.1); 268 M outputs 228 us (187 + 110).
+// The descriptors travel in the kernel's arguments (SPARSE_MSGS of them: half a kilobyte), nothing is uploaded.
+// ------------------------------------------------------------------------------------------------
+constexpr int SPARSE_TILE = 4096;      // outputs per workgroup: 16 KB of LDS, eight workgroups per compute unit
+constexpr int SPARSE_RESIDENT = 2048;  // workgroups the chip holds at once
+constexpr int SPARSE_MSGS = 16;        // messages per launch
 
-struct EwDecMsg {
+struct SparseMsg {
     const long long* count;
     const unsigned int* idx;
-    const float* val;
+    const float* val;          // entry-wise: [capacity] values; l_q: [1] the magnitude
     long long capacity;
 };
 
-// One message per launch, in the order of the call: inside a message the kept coordinates are distinct, so plain
-// stores (first message, after the zero fill) and plain read-add-write (the others) give the same bits in every run.
-__global__ __launch_bounds__(256) void scatter_entrywise(const EwDecMsg* msgs, int which, float scale,
-                                                         float* __restrict__ out, long long n)
+struct SparseMsgs {
+    SparseMsg m[SPARSE_MSGS];
+    int n;
+};
+
+// First position in idx[0, kept) whose coordinate (masked) is not below `key`, by groups of G lanes of a wave, a search
+// of its own per group: every round of loads narrows the range G + 1 times.
+template <int G>
+__device__ inline long long lower_bound_group(const unsigned int* idx, long long kept, unsigned int mask, unsigned int key)
 {
-    const EwDecMsg m = msgs[which];
-    const long long kept = min(*m.count, m.capacity);
-    const long long stride = (long long)gridDim.x * 256;
-    for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < kept; k += stride) {
-        const unsigned int i = m.idx[k];
-        if ((long long)i >= n) continue;
-        const float v = scale * m.val[k];
-        out[i] = which == 0 ? v : out[i] + v;
+    const int lane = threadIdx.x & 63, glane = lane & (G - 1), shift = lane & ~(G - 1);
+    const unsigned long long members = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
+    auto below = [&](long long at, bool valid) {                 // how many of the group's probes are below
+        const bool b = valid && (idx[at] & mask) < key;
+        return __popcll((__ballot(b) >> shift) & members);
+    };
+    long long lo = 0, len = kept;
+    while (__any(len > G)) {                                     // (groups that are done repeat an empty round)
+        const bool active = len > G;
+        const long long step = (len + G) / (G + 1);              // G probes split the range into G + 1 pieces
+        const long long at = lo + (glane + 1) * step - 1;
+        const int c = below(at, active && at < lo + len);
+        if (active) {
+            lo += c * step;
+            len -= c * step;
+            if (c < G) len = min(step - 1, len);                 // (the probe at the end of the piece is not below)
+        }
     }
+    return lo + below(lo + glane, glane < len);
 }
 
-struct LqDecMsg {
-    const long long* count;
-    const unsigned int* idx;
-    const float* norm;
-    long long capacity;
-};
-
-// l_q messages (Section 4): a kept coordinate decodes to sign * |g|_q, the sign in bit 31 of its index.
-// One message per launch, like scatter_entrywise.
-__global__ __launch_bounds__(256) void scatter_lq(const LqDecMsg* msgs, int which, float scale, float* __restrict__ out,
-                                                  long long n)
+// A workgroup owns `run` consecutive tiles.  It searches for its part of every message once; from tile to tile it counts
+// how many of the pairs it had requested were used, and requests the next ones before it writes the tile.
+// G lanes look after one message: 64 for up to four messages, 16 for up to SPARSE_MSGS, so that the searches and the
+// loads of all messages are in flight together.
+// LQ (Section 4): a kept coordinate decodes to sign * |g|_q, the sign in bit 31 of its index.
+template <bool LQ, bool ACCUMULATE, int G>
+__global__ __launch_bounds__(256) void decode_sparse(SparseMsgs msgs, float scale, float* __restrict__ out, long long n, int run)
 {
-    const LqDecMsg m = msgs[which];
-    const long long kept = min(*m.count, m.capacity);
-    const float mag = scale * *m.norm;
-    const long long stride = (long long)gridDim.x * 256;
-    for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < kept; k += stride) {
-        const unsigned int word = m.idx[k];
-        const unsigned int i = word & 0x7FFFFFFFu;
-        if ((long long)i >= n) continue;
-        const float v = (word >> 31) ? -mag : mag;
-        out[i] = which == 0 ? v : out[i] + v;
+    constexpr int EPT = G == 64 ? 2 : 4;                         // pairs per lane requested at once
+    __shared__ __attribute__((aligned(16))) float tile[SPARSE_TILE];
+    __shared__ long long rest[256 / G];                          // where a message goes on behind those, or -1
+    const unsigned int mask = LQ ? 0x7FFFFFFFu : 0xFFFFFFFFu;
+    const int tid = threadIdx.x, group = tid / G, glane = tid % G;
+    const int shift = (tid & 63) & ~(G - 1);
+    const unsigned long long members = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
+    const long long first = (long long)blockIdx.x * run * SPARSE_TILE;
+    const long long last = min(n, first + (long long)run * SPARSE_TILE);
+
+    const bool mine = group < msgs.n;
+    const SparseMsg& m = msgs.m[mine ? group : 0];
+    const long long kept = mine ? min(*m.count, m.capacity) : 0;
+    const float mag = LQ ? scale * *m.val : 0.0f;
+    long long at = lower_bound_group<G>(m.idx, kept, mask, (unsigned int)first);     // first pair that is not in an earlier tile
+    unsigned int word[EPT];
+    float v[EPT];
+    auto request = [&]() {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const long long k = at + glane + G * e;
+            word[e] = k < kept ? m.idx[k] : 0u;
+            v[e] = LQ ? mag : k < kept ? scale * m.val[k] : 0.0f;
+        }
+    };
+    request();
+    for (long long i0 = first; i0 < last; i0 += SPARSE_TILE) {
+        const int here = (int)min((long long)SPARSE_TILE, n - i0);
+        if (ACCUMULATE) {
+            for (int k = tid; k < here; k += 256) tile[k] = out[i0 + k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < SPARSE_TILE / 1024; ++k) *(float4*)&tile[4 * (tid + 256 * k)] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        // which of the requested pairs lie in this tile (a prefix of them: the coordinates ascend)
+        bool in[EPT];
+        int used = 0;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const long long i = (long long)(word[e] & mask) - i0;
+            in[e] = at + glane + G * e < kept && i >= 0 && i < here;
+            used += __popcll((__ballot(in[e]) >> shift) & members);
+        }
+        if (glane == 0) rest[group] = used == G * EPT && at + used < kept ? at + used : -1;
+        for (int q = 0; q < msgs.n; ++q) {
+            __syncthreads();
+            auto put = [&](long long i, float x) { tile[i] = (q == 0 && !ACCUMULATE) ? x : tile[i] + x; };
+            if (group == q) {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e)
+                    if (in[e]) put((long long)(word[e] & mask) - i0, LQ && (word[e] >> 31) ? -v[e] : v[e]);
+            }
+            const long long from = rest[q];
+            if (from < 0) continue;
+            const SparseMsg& mq = msgs.m[q];
+            const long long kept_q = min(*mq.count, mq.capacity);
+            const float mag_q = LQ ? scale * *mq.val : 0.0f;
+            for (long long k = from + tid; k < kept_q; k += 256) {
+                const unsigned int w = mq.idx[k];
+                const long long i = (long long)(w & mask) - i0;
+                if (i >= here) break;                            // ascending: nothing of this tile behind it
+                if (i >= 0) put(i, LQ ? ((w >> 31) ? -mag_q : mag_q) : scale * mq.val[k]);
+            }
+        }
+        if (i0 + SPARSE_TILE < last) {
+            // (a message that filled its request is searched for again; the search is entered by whole waves)
+            const bool lost = used == G * EPT;
+            at += used;
+            if (__any(lost)) {
+                const long long found = lower_bound_group<G>(m.idx, kept, mask, (unsigned int)(i0 + SPARSE_TILE));
+                if (lost) at = found;
+            }
+            request();
+        }
+        __syncthreads();
+        float* const o = out + i0;
+        if (here == SPARSE_TILE && (((size_t)o) & 15) == 0) {
+#pragma unroll
+            for (int k = 0; k < SPARSE_TILE / 1024; ++k)
+                *(float4*)(o + 4 * (tid + 256 * k)) = *(const float4*)&tile[4 * (tid + 256 * k)];
+        } else {
+            for (int k = tid; k < here; k += 256) o[k] = tile[k];
+        }
+        // (the next tile's zeros are written by the thread that has just read the place, as float4 or one by one)
+        if (here < SPARSE_TILE || (((size_t)o) & 15) != 0 || ACCUMULATE) __syncthreads();
     }
 }
 
@@ -337,51 +427,46 @@ int decode_svd_batch(atomo_ctx* ctx, const atomo_svd_msg* msgs, const int32_t* f
     return ATOMO_OK;
 }
 
-int decode_entrywise(atomo_ctx* ctx, const atomo_ew_msg* msgs, int n_msgs, float scale, float* out,
-                     hipStream_t stream)
+namespace {
+
+// Messages SPARSE_MSGS at a time, in call order; the first launch overwrites the output, the others add to it.
+template <bool LQ, typename MSG>
+int decode_sparse_all(atomo_ctx* ctx, const MSG* msgs, int n_msgs, float scale, float* out, hipStream_t stream)
 {
     const int64_t n = msgs[0].n;
-    std::vector<EwDecMsg> hm(n_msgs);
-    for (int k = 0; k < n_msgs; ++k)
-        hm[k] = EwDecMsg{(const long long*)msgs[k].count, msgs[k].idx, msgs[k].val, (long long)msgs[k].capacity};
-    int rc = ensure_workspace(ctx, align_up(hm.size() * sizeof(EwDecMsg), 256));
-    if (rc != ATOMO_OK) return rc;
-    EwDecMsg* d_msgs = (EwDecMsg*)ctx->ws;
-    if ((rc = upload(ctx, d_msgs, hm.data(), hm.size() * sizeof(EwDecMsg), stream)) != ATOMO_OK) return rc;
-    const int fill_wgs = (int)std::min<int64_t>(2048, (n / 4 + 255) / 256 + 1);
-    {
-        ProfScope ps(ctx, ATOMO_K_EW_DECODE, stream);
-        fill_zero<<<fill_wgs, 256, 0, stream>>>(out, n);
-        for (int k = 0; k < n_msgs; ++k) {
-            const int sc_wgs = (int)std::min<int64_t>(1024, (msgs[k].capacity + 255) / 256);
-            scatter_entrywise<<<sc_wgs, 256, 0, stream>>>(d_msgs, k, scale, out, n);
+    // one tile per workgroup up to four times what is resident at once (16.8 M outputs: every workgroup starts with a
+    // search, but the chip is full); from there on runs of tiles, so that a search serves several
+    const int64_t tiles = (n + SPARSE_TILE - 1) / SPARSE_TILE;
+    const int run = (int)std::max<int64_t>(1, tiles / SPARSE_RESIDENT / 4);
+    const unsigned wgs = (unsigned)((tiles + run - 1) / run);
+    ProfScope ps(ctx, ATOMO_K_EW_DECODE, stream);
+    for (int first = 0; first < n_msgs; first += SPARSE_MSGS) {
+        SparseMsgs part = {};
+        part.n = std::min(SPARSE_MSGS, n_msgs - first);
+        for (int k = 0; k < part.n; ++k) {
+            const MSG& m = msgs[first + k];
+            if constexpr (LQ) part.m[k] = SparseMsg{(const long long*)m.count, m.idx, m.norm, (long long)m.capacity};
+            else part.m[k] = SparseMsg{(const long long*)m.count, m.idx, m.val, (long long)m.capacity};
         }
+        if (first > 0) decode_sparse<LQ, true, 16><<<wgs, 256, 0, stream>>>(part, scale, out, n, run);
+        else if (part.n > 4) decode_sparse<LQ, false, 16><<<wgs, 256, 0, stream>>>(part, scale, out, n, run);
+        else decode_sparse<LQ, false, 64><<<wgs, 256, 0, stream>>>(part, scale, out, n, run);
     }
     ATOMO_HIP(ctx, hipGetLastError());
     return ATOMO_OK;
 }
 
+}  // namespace
+
+int decode_entrywise(atomo_ctx* ctx, const atomo_ew_msg* msgs, int n_msgs, float scale, float* out,
+                     hipStream_t stream)
+{
+    return decode_sparse_all<false>(ctx, msgs, n_msgs, scale, out, stream);
+}
+
 int decode_lq(atomo_ctx* ctx, const atomo_lq_msg* msgs, int n_msgs, float scale, float* out, hipStream_t stream)
 {
-    const int64_t n = msgs[0].n;
-    std::vector<LqDecMsg> hm(n_msgs);
-    for (int k = 0; k < n_msgs; ++k)
-        hm[k] = LqDecMsg{(const long long*)msgs[k].count, msgs[k].idx, msgs[k].norm, (long long)msgs[k].capacity};
-    int rc = ensure_workspace(ctx, align_up(hm.size() * sizeof(LqDecMsg), 256));
-    if (rc != ATOMO_OK) return rc;
-    LqDecMsg* d_msgs = (LqDecMsg*)ctx->ws;
-    if ((rc = upload(ctx, d_msgs, hm.data(), hm.size() * sizeof(LqDecMsg), stream)) != ATOMO_OK) return rc;
-    const int fill_wgs = (int)std::min<int64_t>(2048, (n / 4 + 255) / 256 + 1);
-    {
-        ProfScope ps(ctx, ATOMO_K_EW_DECODE, stream);
-        fill_zero<<<fill_wgs, 256, 0, stream>>>(out, n);
-        for (int k = 0; k < n_msgs; ++k) {
-            const int sc_wgs = (int)std::min<int64_t>(1024, (msgs[k].capacity + 255) / 256);
-            scatter_lq<<<sc_wgs, 256, 0, stream>>>(d_msgs, k, scale, out, n);
-        }
-    }
-    ATOMO_HIP(ctx, hipGetLastError());
-    return ATOMO_OK;
+    return decode_sparse_all<true>(ctx, msgs, n_msgs, scale, out, stream);
 }
 
 }  // namespace atomo

@@ -1,0 +1,61 @@
+"""GPU parity of the one-launch decode of entry-wise and l_q messages (decode_sparse) at the sizes where it can go wrong:
+tile edges, a ragged last tile, unaligned outputs, tiles with more pairs than a group requests at once, runs of several
+tiles per workgroup, and more messages than one launch takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1806_04090_amd import binding
+from gpu_common import ctx, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def entrywise(rng, n, k):
+    idx = np.sort(rng.choice(n, size=k, replace=False)) if k < n else np.arange(n)
+    val = rng.standard_normal(k).astype(np.float32)
+    m = binding.alloc_entrywise_message(n, max(k, 1), "cuda")
+    m.count.fill_(k)
+    if k:
+        m.idx[:k] = dev(idx.astype(np.uint32).view(np.int32))
+        m.val[:k] = dev(val)
+    return m, {"idx": idx, "val": val.astype(np.float64)}
+
+
+@pytest.mark.parametrize("n,ks", [(1, [1]), (4095, [100]), (4096, [4096]), (4097, [1, 4097]), (8192, [0, 3, 0]),
+                                  (20_000, [20_000, 7, 6000]),          # every coordinate kept: beyond what is requested at once
+                                  (70_001, [700] * 5), (70_001, [60, 9000] * 8), (12_289, [50] * 37),
+                                  (20_000_003, [1500, 400_000])])       # several tiles per workgroup
+@pytest.mark.parametrize("offset", [0, 1])
+def test_entrywise_messages(n, ks, offset):
+    rng = np.random.default_rng(n + len(ks))
+    pairs = [entrywise(rng, n, k) for k in ks]
+    out = torch.full((n + 4,), 9.0, device="cuda")
+    binding.atomo_decode(ctx(), [m for m, _ in pairs], scale=0.5, out=out[offset:offset + n])
+    got = out.cpu().numpy()
+    want = np.zeros(n, dtype=np.float32)
+    for _, h in pairs:                                                  # the order of the call, in float32
+        want[h["idx"]] += np.float32(0.5) * h["val"].astype(np.float32)
+    assert np.array_equal(got[offset:offset + n], want)
+    assert (got[:offset] == 9).all() and (got[offset + n:] == 9).all()  # nothing beside the output is written
+    np.testing.assert_allclose(got[offset:offset + n], oracle.decode_entrywise([h for _, h in pairs], n, scale=0.5),
+                               rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("n,ks", [(4097, [3]), (9000, [9000, 10]), (70_001, [800] * 18)])
+def test_lq_messages(n, ks):
+    rng = np.random.default_rng(n)
+    msgs, want = [], np.zeros(n, dtype=np.float32)
+    for k in ks:
+        idx = np.sort(rng.choice(n, size=k, replace=False)).astype(np.uint32)
+        neg = rng.random(k) < 0.5
+        m = binding.alloc_lq_message(n, k, "cuda")
+        m.count.fill_(k)
+        m.idx[:] = dev((idx | (neg.astype(np.uint32) << 31)).view(np.int32))
+        norm = np.float32(rng.random() + 0.5)
+        m.norm.fill_(float(norm))
+        msgs.append(m)
+        want[idx] += np.where(neg, -1, 1).astype(np.float32) * (np.float32(0.25) * norm)
+    got = binding.atomo_decode(ctx(), msgs, scale=0.25).cpu().numpy()
+    assert np.array_equal(got, want)
