@@ -110,7 +110,14 @@ typedef struct atomo_lq_msg {
     float* norm;                     /* [1]  |g|_q                                                   */
 } atomo_lq_msg;
 
-/* Tuning knobs of the Jacobi SVD; pass NULL to the encoder for the defaults. */
+/* Options of the SVD encoder; pass NULL for the defaults.
+ *
+ * Matrices of 33 .. 640 vectors on the shorter side, with a budget s of at most 32 atoms, are first solved directly: the
+ * Gram matrix in double precision, its eigenvalues, and singular vectors of the kept atoms only.  The Jacobi iteration
+ * that the options below describe takes over for a matrix with singular values at or under twice the fp32 floor (3.8e-6 of the
+ * largest; gradients of low rank, other than through rows that are zero) or with kept atoms whose singular values
+ * agree to eight digits; for every other size and budget; and for every matrix of a call that sets stop_cosine,
+ * max_inner_sweeps, inner_reduction, full_period or block_order, or a max_sweeps under the default. */
 typedef struct atomo_svd_options {
     int32_t max_sweeps;              /* default 16 (0 = default).  Noise-dominated gradients take 8 to 10 sweeps   */
                                      /* (6 or 7 with 481 or more vectors on the shorter side, see block_order),    */
@@ -166,7 +173,10 @@ typedef struct atomo_svd_options {
                                      /* matrix confirm convergence on a Gram matrix formed afresh from the rotated */
                                      /* data, at a sweep boundary; the context also remembers after how many sweeps */
                                      /* the first of them asked for that, and a call enqueues those launches only  */
-                                     /* from k sweeps before: a matrix that is ready sooner sweeps on until then   */
+                                     /* from k sweeps before: a matrix that is ready sooner sweeps on until then.  */
+                                     /* A call whose predecessor had every matrix solved directly enqueues no      */
+                                     /* iteration: a matrix that would have needed it keeps the direct result and  */
+                                     /* is reported through ATOMO_ENOCONV; the call after it enqueues everything   */
 } atomo_svd_options;
 
 /* -------- context ------------------------------------------------------------------------------ */
@@ -195,7 +205,8 @@ int atomo_last_hip_error(const atomo_ctx* ctx);
  * atomo_encode_svd took into sweeps[0 .. n_mats) (HOST) and, if refreshes is not NULL, how many
  * times the full Gram matrix of the matrix was formed from the data (matrices of 33 .. 480 rows
  * iterate directly on the data: 0 below 225 rows, from there on the number of whole-matrix
- * convergence checks near the end).  n_mats must match that call; the counts stay readable until the
+ * convergence checks near the end).  A matrix that was solved directly counts as one sweep and two passes over
+ * the data (the Gram matrix, and the vectors of the longer side).  n_mats must match that call; the counts stay readable until the
  * next atomo_encode_svd on the context. */
 int atomo_svd_sweeps(atomo_ctx* ctx, void* stream, int32_t* sweeps /*host*/, int32_t* refreshes /*host, optional*/,
                      int n_mats);

@@ -249,7 +249,7 @@ class Context:
         _check(lib().atomo_reserve(self._h, nbytes), "atomo_reserve")
 
     KERNEL_CLASSES = ("svd_prepare", "svd_gram", "svd_eig", "svd_update", "svd_refresh", "svd_finalize", "decode_svd",
-                      "ew_hist", "ew_solve", "ew_sample", "ew_decode", "svd_thin")
+                      "ew_hist", "ew_solve", "ew_sample", "ew_decode", "svd_thin", "svd_direct")
 
     def measure_mfma_fp32(self) -> float:
         """TFLOP/s of a loop of fp32 matrix-core instructions on this GPU (blocks for about a millisecond)."""

@@ -22,13 +22,14 @@ enum { FLAG_CAPACITY = 0, FLAG_NOCONV = 1, FLAG_MAX_SWEEPS = 2, FLAG_EIG_VISITS 
 // What an SVD encode learnt about its own sweep counts, for the calls after it (atomo_svd_options.adaptive).
 struct SweepHint {
     int32_t* host = nullptr;     // pinned, device-visible: [0] most sweeps of a Gram-space matrix, [1] of a data-space one,
-                                 // [2] 1 once written
+                                 // [2] 1 once written, [3] see ask_from, [4] matrices that the direct encode left over
     int32_t* dev = nullptr;      // the same memory as the device addresses it
     hipEvent_t done = nullptr;   // recorded after the kernel that writes `host`
     bool pending = false;        // the event has not been seen complete yet
     uint64_t sig = 0;            // shapes of the call
     uint64_t seq = 0;            // order of the calls (0 = unused)
     int limit_gs = 0, limit_ds = 0;   // the sweep limits that call ran with
+    bool tried_direct = false, direct_only = false;   // the direct encode went first; and nothing was enqueued behind it
 };
 
 struct StageSlot {

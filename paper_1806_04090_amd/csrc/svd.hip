@@ -46,6 +46,7 @@
 #include <vector>
 
 #include "svd_common.h"
+#include "svd_direct.h"
 
 namespace atomo {
 
@@ -98,7 +99,10 @@ __global__ __launch_bounds__(256) void svd_reset(const SvdMat* mats, int n_mats,
     }
     const int t = blockIdx.x * 256 + threadIdx.x;
     const int j = t / ST_WORDS, w = t % ST_WORDS;
-    if (j < n_mats) mats[j].state[w] = (w == ST_FIRST) ? 1 : (w == ST_DMIN) ? 0x7f800000 : 0;
+    if (j >= n_mats || mats[j].skip) return;
+    // a matrix that the direct encode has settled is finished before the first tick
+    const bool settled = w == ST_DONE_AT && direct_done(mats[j]);
+    mats[j].state[w] = settled ? BEFORE_FIRST_TICK : (w == ST_FIRST) ? 1 : (w == ST_DMIN) ? 0x7f800000 : 0;
 }
 
 __global__ __launch_bounds__(256) void svd_absmax(const SvdMat* mats, const Work* work)
@@ -106,6 +110,7 @@ __global__ __launch_bounds__(256) void svd_absmax(const SvdMat* mats, const Work
     __shared__ float red[4];
     const Work wk = work[blockIdx.x];
     const SvdMat m = mats[wk.mat];
+    if (direct_done(m)) return;
     const int row0 = wk.a * BS;
     const int c = wk.b * 256 + threadIdx.x;
     float mx = 0.0f;
@@ -133,6 +138,7 @@ __global__ __launch_bounds__(256) void svd_prepare(const SvdMat* mats, const Wor
     __shared__ float part[4][BS];
     const Work wk = work[blockIdx.x];
     const SvdMat m = mats[wk.mat];
+    if (direct_done(m)) return;
     const int row0 = wk.a * BS;
     const int c = wk.b * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -167,7 +173,7 @@ __global__ __launch_bounds__(256) void svd_scale(const SvdMat* mats)
 {
     __shared__ float red[4];
     const SvdMat m = mats[blockIdx.x];
-    if (m.thin) return;
+    if (m.thin || direct_done(m)) return;
     const int pieces = (m.ldw + 255) / 256;
     float mx = 0.0f;
     for (int row = threadIdx.x; row < m.rows_alloc; row += 256) {
@@ -822,7 +828,7 @@ __global__ __launch_bounds__(256) void svd_norms(const SvdMat* mats, const Work*
     const SvdMat m = mats[wk.mat];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = wk.a * 4 + wave;
-    if (row >= m.rows_alloc) return;
+    if (row >= m.rows_alloc || direct_done(m)) return;
     // a Gram-space matrix ends on a refresh, whose Gram matrix has the squared norms of the final rows on its
     // diagonal (cref): svd_select takes its singular values from there
     if (m.gs) return;
@@ -855,6 +861,7 @@ __global__ __launch_bounds__(256) void svd_select(const SvdMat* mats, double s, 
     __shared__ int ipart[256];
 
     const SvdMat m = mats[blockIdx.x];
+    if (direct_done(m)) return;
     const int tid = threadIdx.x;
     const int r = m.r;
     int P = 1;
@@ -925,16 +932,20 @@ __global__ __launch_bounds__(256) void svd_select(const SvdMat* mats, double s, 
 }
 
 // Most sweeps any Gram-space matrix and any data-space matrix of the call took, and the fewest sweeps after which a
-// Gram-space matrix asked for a refresh (0: none did), into pinned host memory that the next calls read without
-// waiting (atomo_svd_options.adaptive).  One workgroup.
+// Gram-space matrix asked for a refresh (0: none did), and how many matrices the direct encode left to the iteration,
+// into pinned host memory that the next calls read without waiting (atomo_svd_options.adaptive).  One workgroup.
 __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
 {
     __shared__ int red[3][256];
+    __shared__ int open;
+    if (threadIdx.x == 0) open = 0;
+    __syncthreads();
     const int never = 1 << 30;
     int gs = 0, ds = 0, ask = never;
     for (int j = threadIdx.x; j < n_mats; j += 256) {
         const SvdMat& m = mats[j];
-        if (m.thin) continue;
+        if (m.accepted && *m.accepted == 0) atomicAdd(&open, 1);
+        if (m.thin || m.skip) continue;
         const int sw = m.report[0];
         if (m.gs) gs = max(gs, sw); else ds = max(ds, sw);
         if (m.gs) ask = min(ask, m.state[ST_FIRST_ASK] > 0 ? m.state[ST_FIRST_ASK] : never);
@@ -955,6 +966,7 @@ __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
         out[0] = red[0][0];
         out[1] = red[1][0];
         out[3] = red[2][0] == never ? 0 : red[2][0];
+        out[4] = open;
         out[2] = 1;
     }
 }
@@ -969,6 +981,7 @@ __global__ __launch_bounds__(256) void svd_pack(const SvdMat* mats, const Work* 
     }
     const Work wk = work[blockIdx.x];
     const SvdMat m = mats[wk.mat];
+    if (direct_done(m)) return;
     const int slot = wk.a;
     const int kept = min(*m.count, m.capacity);
     if (slot >= kept) return;
@@ -1005,6 +1018,9 @@ struct Plan {
     int max_R = 1;
     int max_R_ds[2] = {1, 1};        // largest R in each group of data-space matrices
     size_t rowgram_lds[2] = {0, 0};  // LDS bytes of a svd_rowgram workgroup: all rows of the group's tallest matrix
+    std::vector<int> direct_of;      // index of the matrix in direct.mats, -1: not tried
+    direct::DirectPlan direct;
+    direct::DirectMat* d_direct = nullptr;
     bool own_update = false;         // the two-sided update runs as launches of its own (see SPLIT_TWO_SIDED)
     size_t bytes = 0;
     SvdMat* d_mats = nullptr;        // device copies of `mats` and of the concatenated work lists
@@ -1014,7 +1030,7 @@ struct Plan {
         return prep.size() + rowgram[0].size() + rowgram[1].size() + fullgram.size() + tiles.size() + apply.size() +
                eig_gs.size() + eig_ds[0].size() + eig_ds[1].size() +
                twosided.size() + strips.size() + ds_full.size() + ds_tiles.size() + norms[0].size() + norms[1].size() + pack.size() + 2 * thin_chunks.size() + thin_list.size() +
-               gs_list.size();
+               gs_list.size() + direct.n_work();
     }
 };
 
@@ -1026,16 +1042,24 @@ struct Plan {
 constexpr size_t SPLIT_TWO_SIDED = 4096;
 
 // Lays the workspace out (base == nullptr: sizes only).
+// try_direct: the matrices of a size for it go through the direct encode first (plan.direct); direct_only: and are left
+// out of everything else.
 void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, float* sigma_out, float* p_out,
-                uint64_t stream_base, const uint64_t* stream_ids, void* base, Plan& plan)
+                uint64_t stream_base, const uint64_t* stream_ids, bool try_direct, bool direct_only, void* base, Plan& plan)
 {
     Carver carve(base);
     plan.mats.resize(n_mats);
     plan.d_mats = carve.take<SvdMat>(n_mats);
+    plan.direct_of.assign(n_mats, -1);
     size_t atom_off = 0;
     size_t update_tiles = 0;
     for (int j = 0; j < n_mats; ++j) {
         const int r = mats[j].rows < mats[j].cols ? mats[j].rows : mats[j].cols;
+        if (try_direct && direct::eligible(r)) {
+            plan.direct_of[j] = (int)plan.direct.mats.size();
+            plan.direct.mats.push_back(direct::DirectMat{});
+            if (direct_only) continue;
+        }
         const int nb = (r + BS - 1) / BS, nb2 = nb + (nb & 1);
         if (r > THIN_R && nb2 >= GS_MIN_BLOCKS) update_tiles += (size_t)(nb2 / 2) * (nb2 / 2 + nb2 * BS / PR);
     }
@@ -1049,6 +1073,8 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         m.r = m.transposed ? a.cols : a.rows;
         m.M = m.transposed ? a.rows : a.cols;
         m.thin = m.r <= THIN_R;
+        m.gs = 0;
+        m.state = nullptr;
         m.stream_id = stream_ids ? stream_ids[j] : stream_base + (uint64_t)j;
         m.G = a.data; m.ldg = a.ld;
         if (msgs) {
@@ -1061,6 +1087,21 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         m.sigma_out = sigma_out ? sigma_out + atom_off : nullptr;
         m.p_out = p_out ? p_out + atom_off : nullptr;
         atom_off += m.r;
+        m.accepted = nullptr;
+        m.skip = 0;
+        if (plan.direct_of[j] >= 0) {
+            direct::DirectMat& d = plan.direct.mats[plan.direct_of[j]];
+            d.G = m.G; d.ldg = m.ldg; d.rows = m.rows; d.cols = m.cols; d.transposed = m.transposed; d.r = m.r; d.M = m.M;
+            d.capacity = msgs ? m.capacity : m.r;
+            d.count = m.count; d.idx = m.idx; d.w = m.w; d.U = m.U; d.V = m.V;
+            d.sigma_out = m.sigma_out; d.p_out = m.p_out; d.stream_id = m.stream_id;
+            direct::plan_matrix(carve, d);
+            m.accepted = d.st + direct::DS_ACCEPT;
+            if (direct_only) {
+                m.skip = 1;
+                continue;
+            }
+        }
         if (m.thin) {
             // chunks of 1024 positions, larger only to keep a matrix under 128 chunks
             const int64_t per = ((int64_t)m.M + 128 * 1024 - 1) / (128 * 1024);
@@ -1201,6 +1242,8 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         std::stable_sort(list.begin(), list.end(), [&](const Work& a, const Work& b) {
             return plan.mats[a.mat].rows_alloc * (a.c >= 0 ? 2 : 1) > plan.mats[b.mat].rows_alloc * (b.c >= 0 ? 2 : 1);
         });
+    direct::plan_work(plan.direct);
+    plan.d_direct = carve.take<direct::DirectMat>(plan.direct.mats.size());
     plan.d_work = carve.take<Work>(plan.n_work());
     plan.bytes = carve.off;
 }
@@ -1214,7 +1257,7 @@ int svd_workspace_bytes(const atomo_mat* mats, int n_mats, size_t* bytes)
         if ((mats[j].rows < mats[j].cols ? mats[j].rows : mats[j].cols) > MAX_R) return ATOMO_EINVAL;
     }
     Plan plan;
-    build_plan(mats, n_mats, nullptr, nullptr, nullptr, 0, nullptr, nullptr, plan);
+    build_plan(mats, n_mats, nullptr, nullptr, nullptr, 0, nullptr, true, false, nullptr, plan);
     *bytes = plan.bytes;
     return ATOMO_OK;
 }
@@ -1236,6 +1279,16 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const int full_period = opt && opt->full_period > 0 ? opt->full_period : 12;
     const int cyclic = opt && opt->block_order == 1 ? 1 : 0;
     const int adaptive = opt ? opt->adaptive : 0;
+
+    // The direct encode (svd_direct.hip) goes first, and the Jacobi iteration takes the matrices that it does not settle.
+    // Not with a budget of many atoms (their vectors then cost more than the iteration), and not where the caller has
+    // chosen how the iteration runs or limits it below the default.
+    const bool try_direct = s <= direct::MAX_BUDGET &&
+                            !(opt && ((opt->max_sweeps > 0 && opt->max_sweeps < 16) || opt->stop_cosine > 0.0f ||
+                                      opt->max_inner_sweeps > 0 || opt->inner_reduction > 0.0f || opt->full_period > 0 ||
+                                      opt->block_order != 0));
+    // A training loop (`adaptive`) whose last finished call had every matrix settled directly enqueues no iteration.
+    bool direct_only = false;
 
     // Sweep limits of this call.  With `adaptive`, what the most recent finished call with the same shapes needed plus
     // the margin; a call that used up a reduced limit tells nothing about what was needed and is followed by a full one.
@@ -1269,7 +1322,8 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             }
             if (!h.pending && h.sig == sig && h.host[2] == 1 && (!best || h.seq > best->seq)) best = &h;
         }
-        if (best) {
+        if (best && try_direct && best->tried_direct && best->host[4] == 0) direct_only = true;
+        if (best && !best->direct_only) {
             const int g = best->host[0], d = best->host[1];
             if (!(g >= best->limit_gs && best->limit_gs < max_sweeps)) {
                 limit_gs = std::min(max_sweeps, std::max(1, g + adaptive));
@@ -1278,15 +1332,17 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             if (!(d >= best->limit_ds && best->limit_ds < max_sweeps)) limit_ds = std::min(max_sweeps, std::max(1, d + adaptive));
         }
         if (!hint->host) {
-            ATOMO_HIP(ctx, hipHostMalloc((void**)&hint->host, 4 * sizeof(int32_t), hipHostMallocDefault));
+            ATOMO_HIP(ctx, hipHostMalloc((void**)&hint->host, 8 * sizeof(int32_t), hipHostMallocDefault));
             ATOMO_HIP(ctx, hipHostGetDevicePointer((void**)&hint->dev, hint->host, 0));
             ATOMO_HIP(ctx, hipEventCreateWithFlags(&hint->done, hipEventDisableTiming));
         }
-        hint->host[0] = hint->host[1] = hint->host[2] = hint->host[3] = 0;
+        for (int k = 0; k < 8; ++k) hint->host[k] = 0;
         hint->sig = sig;
         hint->seq = ++ctx->hint_seq;
         hint->limit_gs = limit_gs;
         hint->limit_ds = limit_ds;
+        hint->tried_direct = try_direct;
+        hint->direct_only = direct_only;
     }
 
     if ((size_t)n_mats > ctx->report_cap) {                      // (hipFree waits for the device)
@@ -1299,7 +1355,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     }
     Plan sizing;
     const uint64_t* stream_ids = opt ? opt->stream_ids : nullptr;
-    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, nullptr, sizing);
+    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, nullptr, sizing);
     if (sizing.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL;   // (the work items address the workspace in 32 bits of 16-byte units)
     const bool tables_intact = ctx->svd_tables_intact;
     const void* const ws_before = ctx->ws;
@@ -1307,9 +1363,12 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     if (rc != ATOMO_OK) return rc;
 
     Plan plan;
-    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, ctx->ws, plan);
+    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, ctx->ws, plan);
     SvdMat* d_mats = plan.d_mats;
-    for (int j = 0; j < n_mats; ++j) plan.mats[j].report = ctx->d_report + 2 * j;
+    for (int j = 0; j < n_mats; ++j) {
+        plan.mats[j].report = ctx->d_report + 2 * j;
+        if (plan.direct_of[j] >= 0) plan.direct.mats[plan.direct_of[j]].report = plan.mats[j].report;
+    }
     ctx->report_n = (size_t)n_mats;
 
     std::vector<Work> all;
@@ -1337,27 +1396,74 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const Work* w_thin_direct = place(plan.thin_direct);
     const Work* w_thin_copied = place(plan.thin_copied);
     const Work* w_gs_list = place(plan.gs_list);
+    direct::DirectTables dt;
+    dt.mats = plan.d_direct;
+    dt.n_mats = (int)plan.direct.mats.size();
+    dt.gram = place(plan.direct.gram);
+    dt.tiles = place(plan.direct.tiles);
+    dt.tri = place(plan.direct.tri);
+    dt.eig = place(plan.direct.eig);
+    dt.vec = place(plan.direct.vec);
+    dt.lng = place(plan.direct.lng);
 
     // the tables go up unless the workspace still holds these very bytes (see atomo_ctx::svd_tables)
     {
-        const size_t mats_bytes = plan.mats.size() * sizeof(SvdMat), work_bytes = all.size() * sizeof(Work);
-        const bool same = tables_intact && ws_before == ctx->ws && ctx->svd_tables_stream == stream &&
-                          ctx->svd_tables.size() == mats_bytes + work_bytes &&
-                          memcmp(ctx->svd_tables.data(), plan.mats.data(), mats_bytes) == 0 &&
-                          memcmp(ctx->svd_tables.data() + mats_bytes, all.data(), work_bytes) == 0;
+        const struct { const void* host; void* dev; size_t bytes; } parts[3] = {
+            {plan.mats.data(), d_mats, plan.mats.size() * sizeof(SvdMat)},
+            {plan.direct.mats.data(), plan.d_direct, plan.direct.mats.size() * sizeof(direct::DirectMat)},
+            {all.data(), plan.d_work, all.size() * sizeof(Work)}};
+        size_t total = 0;
+        for (const auto& p : parts) total += p.bytes;
+        bool same = tables_intact && ws_before == ctx->ws && ctx->svd_tables_stream == stream && ctx->svd_tables.size() == total;
+        size_t at = 0;
+        for (const auto& p : parts) {
+            same = same && memcmp(ctx->svd_tables.data() + at, p.host, p.bytes) == 0;
+            at += p.bytes;
+        }
         if (!same) {
-            rc = upload(ctx, d_mats, plan.mats.data(), mats_bytes, stream);
-            if (rc != ATOMO_OK) return rc;
-            rc = upload(ctx, plan.d_work, all.data(), work_bytes, stream);
-            if (rc != ATOMO_OK) return rc;
-            ctx->svd_tables.resize(mats_bytes + work_bytes);
-            memcpy(ctx->svd_tables.data(), plan.mats.data(), mats_bytes);
-            memcpy(ctx->svd_tables.data() + mats_bytes, all.data(), work_bytes);
+            ctx->svd_tables.resize(total);
+            at = 0;
+            for (const auto& p : parts) {
+                if (p.bytes == 0) continue;
+                rc = upload(ctx, p.dev, p.host, p.bytes, stream);
+                if (rc != ATOMO_OK) return rc;
+                memcpy(ctx->svd_tables.data() + at, p.host, p.bytes);
+                at += p.bytes;
+            }
             ctx->svd_tables_stream = stream;
         }
     }
 
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
+    hipStream_t const caller = stream;
+    auto record_hint = [&]() -> int {
+        if (hint) {
+            ATOMO_HIP(ctx, hipEventRecord(hint->done, caller));
+            hint->pending = true;
+        }
+        ATOMO_HIP(ctx, hipGetLastError());
+        ctx->svd_tables_intact = true;                           // until anything asks for the workspace again
+        return ATOMO_OK;
+    };
+    const bool any_direct = !plan.direct.mats.empty();
+    bool iterate = false;                                        // does anything but the direct encode run?
+    for (int j = 0; j < n_mats; ++j) iterate = iterate || !plan.mats[j].skip;
+    // the hint comes from svd_pack, unless only thin matrices are left beside the direct ones
+    const bool hint_from_direct = direct_only && any_direct && plan.pack.empty();
+    // thin matrices beside direct ones: on a stream of their own from here to the end
+    const bool beside = hint_from_direct && iterate;
+    if (beside) {
+        rc = ensure_side_streams(ctx);
+        if (rc != ATOMO_OK) return rc;
+        ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
+        ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side2, ctx->ev_fork, 0));
+    }
+    if (any_direct) {
+        ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, stream);
+        direct::launch(plan.direct, dt, s, seed, direct_only, hint_from_direct && hint ? hint->dev : nullptr, ctx->d_flags, stream);
+    }
+    if (any_direct && !iterate) return record_hint();
+    if (beside) stream = ctx->side2;
     {
         ProfScope ps(ctx, ATOMO_K_SVD_PREPARE, stream);
         const int reset_wgs = (n_mats * ST_WORDS + 255) / 256;
@@ -1500,18 +1606,17 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     {
         ProfScope ps(ctx, ATOMO_K_SVD_FINALIZE, stream);
         svd_select<<<(unsigned)n_mats, 256, 0, stream>>>(d_mats, s, (unsigned long long)seed, ctx->d_flags);
-        const unsigned pack_wgs = grid(plan.pack) + (hint ? 1u : 0u);     // the hint rides behind the pack items
+        const bool hint_here = hint && !hint_from_direct;
+        const unsigned pack_wgs = grid(plan.pack) + (hint_here ? 1u : 0u);     // the hint rides behind the pack items
         if (pack_wgs > 0)
-            svd_pack<<<pack_wgs, 256, 0, stream>>>(d_mats, w_pack, (int)plan.pack.size(), n_mats, hint ? hint->dev : nullptr);
+            svd_pack<<<pack_wgs, 256, 0, stream>>>(d_mats, w_pack, (int)plan.pack.size(), n_mats, hint_here ? hint->dev : nullptr);
         if (have_thin) launch_thin_pack(d_mats, w_thin_chunks, (int)plan.thin_chunks.size(), stream);
     }
-    if (hint) {
-        ATOMO_HIP(ctx, hipEventRecord(hint->done, stream));
-        hint->pending = true;
+    if (beside) {
+        ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join, stream));
+        ATOMO_HIP(ctx, hipStreamWaitEvent(caller, ctx->ev_join, 0));
     }
-    ATOMO_HIP(ctx, hipGetLastError());
-    ctx->svd_tables_intact = true;                               // until anything asks for the workspace again
-    return ATOMO_OK;
+    return record_hint();
 }
 
 int svd_sweeps(atomo_ctx* ctx, hipStream_t stream, int32_t* sweeps, int32_t* refreshes, int n_mats)

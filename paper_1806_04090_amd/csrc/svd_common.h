@@ -50,6 +50,7 @@ enum {
 };
 
 enum { MODE_NEED_REFRESH = 0, MODE_SWEEPS = 1, MODE_DONE = 2 };
+constexpr int BEFORE_FIRST_TICK = -2;   // ST_DONE_AT of a matrix that has nothing to iterate (the first launch is tick -1)
 
 // Rows whose squared norm is below ZERO_REL * (largest squared row norm of the matrix) are rounding
 // residue of the fp32 updates (about 32 ulp of the dominant rows): their directions carry no
@@ -136,6 +137,9 @@ struct SvdMat {
     int tchunk;              // positions per work item (a multiple of 256)
     float* B;                // M x r, position-major: the rotated data
     int* report;             // [2] sweeps and refreshes of this matrix, written when the message is made
+    // matrices that svd_direct.hip has tried first
+    int skip;                // 1: the direct encode alone, no Jacobi launches were enqueued (all pointers below r, M unset)
+    const int* accepted;     // nonzero word: the message is in place already (null: the matrix was not tried)
     const float* X;          // the data before the first rotation, position-major with row stride r: G itself, or its copy in B
     // Gram-space matrices: the pairing of the ticks, tables indexed by tick mod 3
     int* sched;              // [3][npairs][2]: the two blocks (smaller first) of every pair
@@ -199,6 +203,9 @@ __device__ inline void write_pair_desc(const SvdMat& m, int t, int k, int bi, in
     d[PD_K1] = wi >> 1; d[PD_S1] = wi & 1; d[PD_X0] = xi0; d[PD_X1] = xi1;
     d[PD_K2] = wj >> 1; d[PD_S2] = wj & 1; d[PD_Y0] = xj0; d[PD_Y1] = xj1;
 }
+
+// true if the matrix has its message from the direct encode
+__device__ inline bool direct_done(const SvdMat& m) { return m.skip || (m.accepted && *m.accepted != 0); }
 
 // exponent e such that absmax * 2^-e lies in [1, 2); 0 for an all-zero matrix
 __device__ inline int scale_exponent(const SvdMat& m)

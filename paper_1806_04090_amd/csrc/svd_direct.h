@@ -1,0 +1,80 @@
+// Direct Spectral-ATOMO encode (svd_direct.hip): descriptors and launches shared with the host side in svd.hip.
+#pragma once
+
+#include "svd_common.h"
+
+namespace atomo {
+namespace direct {
+
+constexpr int MAX_R = 640;           // vectors on the shorter side that the reduction holds in registers
+constexpr int TILE = 64;
+constexpr double MAX_BUDGET = 32.0;  // above this many expected atoms the vectors cost more than the Jacobi iteration
+
+// State words of a matrix (device, int32).
+enum {
+    DS_ACCEPT = 0,       // 1: the message is in place and the Jacobi iteration leaves the matrix alone
+    DS_EXP = 1,          // the Gram matrix was multiplied by 2^-DS_EXP (even) before the reduction
+    DS_FAIL = 2,         // 1: a wait of the reduction hit its bound
+    DS_ZERO_ROWS = 3,    // rows of A that are exactly zero
+    DS_WORDS = 8
+};
+
+struct DirectMat {
+    const float* G;
+    long long ldg;
+    int rows, cols, transposed, r, M;
+    int nt, pad;                     // N = 64 nt >= r: the Gram matrix with `pad` zero rows and columns in front
+    int cls;                         // CLS_*: how the reduction splits the matrix
+    int nchunks, kchunk;             // the columns of A in the Gram product: nchunks partial sums of kchunk each
+    int capacity;
+    double* part;                    // [nchunks][nt (nt + 1) / 2][64 * 64] partial Gram tiles
+    double* C;                       // [N][N] Gram matrix, both triangles
+    double* refl;                    // [N][N] row k: the Householder vector of step k (entries from 64 (k / 64) on)
+    double* tau;                     // [N]
+    double* dg;                      // [N] diagonal of the tridiagonal matrix, scaled
+    double* od;                      // [N] off-diagonal: od[k] couples k and k + 1
+    double* od2;                     // [N] its square, kept above OD2_MIN
+    double* fact;                    // [N / 16][16][16] triangular factors of the blocks of 16 reflectors
+    double* lam;                     // [r] eigenvalues, descending, scaled
+    double* u;                       // [capacity][r] kept vectors of the shorter side
+    unsigned long long* xch;         // exchange slots of the reduction, see tri_group
+    int* xid;                        // [64] which die every workgroup of the matrix's group runs on, plus one
+    int* st;                         // [DS_WORDS]
+    int* count;
+    int* idx;
+    float* w;
+    float* U;
+    float* V;
+    float* sigma_out;                // may be null
+    float* p_out;                    // may be null
+    float* inv;                      // [capacity] 1 / sigma of the kept atom
+    unsigned long long stream_id;
+    int* report;                     // [2] sweeps (1: solved directly) and passes over the data
+};
+
+struct DirectPlan {
+    std::vector<DirectMat> mats;
+    std::vector<svd::Work> gram, tiles, tri, eig, vec, lng;
+    int eig_lanes = 64;              // lanes per eigenvalue in the search
+    size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
+    int max_nt = 1;
+    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
+};
+
+// Lays out one matrix (base of `carve` null: sizes only) and appends its work; false if the matrix is not for this path.
+bool eligible(int r);
+void plan_matrix(Carver& carve, DirectMat& m);
+void plan_work(DirectPlan& plan);
+
+struct DirectTables {
+    const DirectMat* mats;
+    int n_mats;
+    const svd::Work *gram, *tiles, *tri, *eig, *vec, *lng;
+};
+// finish: the call enqueues nothing else for these matrices, so those that were not accepted are reported; hint_out
+// (may be null): where the counts for the next calls go.
+void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int finish, int* hint_out, int* d_flags,
+            hipStream_t stream);
+
+}  // namespace direct
+}  // namespace atomo

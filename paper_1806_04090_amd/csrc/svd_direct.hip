@@ -1,0 +1,1284 @@
+// Spectral-ATOMO encode without an iteration over the data: Gram matrix in double precision, Householder reduction to
+// tridiagonal form, all eigenvalues by multisection with Sturm counts, eigenvectors of the kept atoms only.
+//
+// A message holds about s atoms of r, but its probabilities need every singular value.  A Jacobi iteration computes all
+// r singular pairs to get there.  Here the r x r matrix C = A A^T (A: the r vectors of the shorter side) is formed once,
+// C = H T H^T with T tridiagonal, sigma_i = sqrt(lambda_i(T)), and after the Bernoulli draw only the kept atoms get an
+// eigenvector of T, its image under H, and one product with the data for the other side.
+//
+// Precision.  Squaring loses half of the digits, so everything between the data and sigma is in double precision:
+// products of two floats are exact there, lambda has an absolute error of about 1e-15 lambda_1, and sigma one of
+// 1e-10 sigma_1 at the fp32 floor 2e-6 sigma_1 of the encoder.  A matrix with singular values at or under that floor
+// (rank-deficient gradients), or with two kept atoms whose eigenvalues the search cannot tell apart, is left to the
+// Jacobi iteration: DS_ACCEPT stays 0.
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+#include "svd_direct.h"
+
+namespace atomo {
+namespace direct {
+
+using svd::Work;
+typedef unsigned long long u64;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+namespace {
+
+enum { CLS_64 = 0, CLS_128, CLS_256, CLS_512, CLS_640, CLS_COUNT };
+// columns / 64, workgroups of the group
+constexpr int CLS_CHUNKS[CLS_COUNT] = {1, 2, 4, 8, 10};
+constexpr int CLS_WGS[CLS_COUNT] = {1, 1, 16, 16, 32};
+
+constexpr double OD2_MIN = 7.7e-34;          // 2^-110: keeps the Sturm recurrence going where T splits
+constexpr double FLOOR_REL = 1.4551915e-11;  // 2^-36: four times the squared fp32 floor of the encoder (ZERO_REL)
+constexpr int LAM_BITS = 27;                 // the search ends at this relative precision of lambda
+constexpr u64 LAM_MIN_BITS = 0x3CD0000000000000ull;   // 2^-50: anything below is zero (lambda_1 >= 2^-12 in this scale)
+constexpr u64 LAM_MAX_BITS = 0x3FF0000000000000ull;   // 1.0: the trace is below it
+constexpr int LAM_STEP_BITS = 52 - LAM_BITS;
+
+// ------------------------------------------------------------------------------------------------
+// wave helpers (64 lanes, no LDS)
+// ------------------------------------------------------------------------------------------------
+__device__ inline unsigned lo32(double x) { return (unsigned)__double_as_longlong(x); }
+__device__ inline unsigned hi32(double x) { return (unsigned)(__double_as_longlong(x) >> 32); }
+__device__ inline double mk64(unsigned lo, unsigned hi) { return __longlong_as_double((long long)(((u64)hi << 32) | lo)); }
+
+template <int CTRL>
+__device__ inline double dpp(double x)
+{
+    const unsigned a = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo32(x), CTRL, 0xf, 0xf, true);
+    const unsigned b = (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi32(x), CTRL, 0xf, 0xf, true);
+    return mk64(a, b);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
+
+// lanes 0..31 of the result: a of the lane plus a of lane + 32; lanes 32..63: b of both
+__device__ inline double fold32(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
+    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
+}
+// the same between neighbouring rows of 16 lanes (even rows: a, odd rows: b)
+__device__ inline double fold16(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
+    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
+}
+__device__ inline double fold8(double a, double b, int lane)
+{
+    const bool up = lane & 8;
+    const double keep = up ? b : a, give = up ? a : b;
+    return keep + dpp<DPP_ROR8>(give);
+}
+__device__ inline double sum8(double x)      // over the 8 lanes of a group, in every lane
+{
+    x += dpp<DPP_XOR1>(x);
+    x += dpp<DPP_XOR2>(x);
+    x += dpp<DPP_HALF_MIRROR>(x);
+    return x;
+}
+// sum over the 64 lanes, the same bits in every lane
+__device__ inline double wave_sum(double x)
+{
+    x = sum8(x);
+    x += dpp<DPP_MIRROR>(x);
+    x = fold16(x, x);
+    return fold32(x, x);
+}
+// K <= 8 sums over the 64 lanes at once: lane l receives sum number (l >> 5 & 1) | (l >> 4 & 1) << 1 | (l >> 3 & 1) << 2
+template <int K>
+__device__ inline double wave_sums(const double (&v)[K], int lane)
+{
+    constexpr int K1 = (K + 1) / 2, K2 = (K1 + 1) / 2;
+    double a[K1], b[K2];
+#pragma unroll
+    for (int i = 0; i < K1; ++i) a[i] = fold32(v[2 * i], 2 * i + 1 < K ? v[2 * i + 1] : v[2 * i]);
+#pragma unroll
+    for (int i = 0; i < K2; ++i) b[i] = fold16(a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i]);
+    return sum8(fold8(b[0], K2 > 1 ? b[1] : b[0], lane));
+}
+__device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2; }
+
+__device__ inline double lane_value(double x, int lane)
+{
+    return mk64((unsigned)__builtin_amdgcn_readlane((int)lo32(x), lane), (unsigned)__builtin_amdgcn_readlane((int)hi32(x), lane));
+}
+
+// ------------------------------------------------------------------------------------------------
+// Gram matrix: partial sums of one 64 x 64 tile over one chunk of columns of A
+// ------------------------------------------------------------------------------------------------
+constexpr int GK = 32;           // columns staged per step
+constexpr int GLD = GK + 4;      // row stride in LDS: 16 rows x 4 consecutive columns hit 64 different banks
+
+// One row of A per lane group: loads the 64 x 32 piece (rows row0.., columns c0..) into registers / LDS.
+// Rows before the padding and columns past c_end are zero.
+struct GramLoader {
+    const float* G;
+    long long ldg;
+    int transposed, r;
+    __device__ inline void fetch(float (&v)[8], int row0, int c0, int c_end, int tid) const
+    {
+        if (!transposed) {
+            // thread: row tid / 4, eight columns from 8 (tid mod 4)
+            const int row = row0 + (tid >> 2), c = c0 + 8 * (tid & 3);
+            const float* g = G + (long long)row * ldg + c;
+            if (row >= 0 && c + 8 <= c_end && ((((size_t)g) & 15) == 0)) {
+                *(float4*)&v[0] = *(const float4*)g;
+                *(float4*)&v[4] = *(const float4*)(g + 4);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = row >= 0 && c + k < c_end ? g[k] : 0.0f;
+            }
+        } else {
+            // thread: row tid mod 64, columns tid / 64 + 4 k
+            const int row = row0 + (tid & 63), c = c0 + (tid >> 6);
+            const float* g = G + (long long)c * ldg + row;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = row >= 0 && c + 4 * k < c_end ? g[(long long)(4 * k) * ldg] : 0.0f;
+        }
+    }
+    __device__ inline void store(const float (&v)[8], float (*t)[GLD], int tid) const
+    {
+        if (!transposed) {
+            float* p = &t[tid >> 2][8 * (tid & 3)];
+            *(float4*)p = make_float4(v[0], v[1], v[2], v[3]);
+            *(float4*)(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) t[tid & 63][(tid >> 6) + 4 * k] = v[k];
+        }
+    }
+};
+
+// Bound: the double-precision matrix cores (2 x 64 cycles of v_mfma_f64_16x16x4 per 16 columns, sub-tile and wave; the
+// operand of four instructions is one 16-byte LDS read per lane).  A wave owns a 32 x 32 quarter of the tile.
+__global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const Work* work)
+{
+    __shared__ float ta[64][GLD], tb[64][GLD];
+    const Work wk = work[blockIdx.x];
+    const DirectMat& m = mats[wk.mat];
+    const int ti = wk.a, tj = wk.b, chunk = wk.c;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
+    const int qi = (wave >> 1) * 32, qj = (wave & 1) * 32;
+    const GramLoader ld{m.G, m.ldg, m.transposed, m.r};
+    const int rowa = ti * TILE - m.pad, rowb = tj * TILE - m.pad;
+    const int c0 = chunk * m.kchunk, c1 = min(m.M, c0 + m.kchunk);
+    const bool same = ti == tj;
+    doublex4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    float va[8], vb[8];
+    ld.fetch(va, rowa, c0, c1, tid);
+    if (!same) ld.fetch(vb, rowb, c0, c1, tid);
+    for (int c = c0; c < c1; c += GK) {
+        __syncthreads();
+        ld.store(va, ta, tid);
+        if (!same) ld.store(vb, tb, tid);
+        __syncthreads();
+        if (c + GK < c1) {
+            ld.fetch(va, rowa, c + GK, c1, tid);
+            if (!same) ld.fetch(vb, rowb, c + GK, c1, tid);
+        }
+        float (*tbb)[GLD] = same ? ta : tb;
+#pragma unroll
+        for (int h = 0; h < GK / 16; ++h) {
+            float4 a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i] = *(const float4*)&ta[qi + 16 * i + l16][16 * h + 4 * q];
+                b[i] = *(const float4*)&tbb[qj + 16 * i + l16][16 * h + 4 * q];
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const float ax = x == 0 ? a[i].x : x == 1 ? a[i].y : x == 2 ? a[i].z : a[i].w;
+                        const float bx = x == 0 ? b[j].x : x == 1 ? b[j].y : x == 2 ? b[j].z : b[j].w;
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ax, (double)bx, acc[i][j], 0, 0, 0);
+                    }
+        }
+    }
+    const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
+    double* out = m.part + ((size_t)chunk * ntiles + tile) * (TILE * TILE);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) out[(qi + 16 * i + 4 * v + q) * TILE + qj + 16 * j + l16] = acc[i][j][v];
+}
+
+// Adds the partial tiles up in the order of the columns and writes both triangles; the first tile's workgroup also clears
+// what the reduction needs cleared.
+__global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, const Work* work)
+{
+    __shared__ double t[TILE][TILE + 1];
+    const Work wk = work[blockIdx.x];
+    const DirectMat& m = mats[wk.mat];
+    const int ti = wk.a, tj = wk.b, tid = threadIdx.x, N = m.nt * TILE;
+    const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
+    const double* in = m.part + (size_t)tile * (TILE * TILE);
+    double sum[16];
+#pragma unroll
+    for (int p = 0; p < 16; ++p) sum[p] = 0.0;
+    for (int c = 0; c < m.nchunks; ++c) {
+#pragma unroll
+        for (int p = 0; p < 16; ++p) sum[p] += in[(size_t)c * ntiles * (TILE * TILE) + tid + 256 * p];
+    }
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+        const int i = (tid >> 6) + 4 * p, j = tid & 63;
+        m.C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
+        t[i][j] = sum[p];
+    }
+    if (ti != tj) {
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const int i = (tid >> 6) + 4 * p, j = tid & 63;
+            m.C[(size_t)(tj * TILE + i) * N + ti * TILE + j] = t[j][i];
+        }
+    }
+    if (ti == 0 && tj == 0) {
+        if (tid < DS_WORDS) m.st[tid] = 0;
+        if (tid < 64) m.xid[tid] = 0;
+        for (int i = tid; i < 4 * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Householder reduction C = H T H^T
+// ------------------------------------------------------------------------------------------------
+// Step k: x = column k of the current matrix, v the Householder vector that maps x[k + 1 ..] to a multiple of the first
+// unit vector, p = A v, w = tau p - (tau^2 / 2)(v^T p) v, A <- A - v w^T - w v^T.
+struct Step {
+    double tau, beta, v0;
+};
+__device__ inline Step householder(double alpha, double sig2)
+{
+    Step s;
+    if (!(sig2 > 0.0)) {
+        s.tau = 0.0;
+        s.beta = alpha;
+        s.v0 = 0.0;
+    } else {
+        s.beta = -copysign(sqrt(fma(alpha, alpha, sig2)), alpha);
+        s.v0 = alpha - s.beta;
+        s.tau = -1.0 / (s.beta * s.v0);
+    }
+    return s;
+}
+
+// What every wave works out for itself before the first step: the scale of the matrix (a power of four that brings the
+// trace under 1) and how many of its rows are zero.
+template <int C>
+__device__ inline double scale_of(const DirectMat& m, int off, int lane, int& expo, int& zero_rows)
+{
+    const int N = m.nt * TILE;
+    double tr = 0.0;
+    int zeros = 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int i = lane + 64 * c - off;
+        const double d = i >= 0 ? m.C[(size_t)i * N + i] : 0.0;
+        tr += d;
+        zeros += __popcll(__ballot(i >= m.pad && d == 0.0));
+    }
+    tr = wave_sum(tr);
+    int e = 0;
+    if (tr > 0.0 && tr <= 1.7976931348623157e308) (void)frexp(tr, &e);
+    e += e & 1;
+    expo = e;
+    zero_rows = zeros;
+    return ldexp(1.0, -e);
+}
+
+// Groups of 16 or 32 workgroups (matrices of more than 128 rows): every wave owns R rows of the matrix in registers (lane l:
+// columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all waves
+// the same bits; one exchange per step: every wave publishes the entries of p of its rows, the owner of row k + 1
+// that row (column k + 1 of the matrix before the step), and every wave reads all of both.
+// An entry is one 8-byte store whose two lowest mantissa bits carry the step number mod 4: a reader knows from the value
+// that it is the one of this step, no flag and no second round trip.  Two slots by step parity: a wave that publishes
+// step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more.
+// The workgroups of a group sit on one die (blockIdx mod 8), whose L2 the exchange goes through: 0.77 us per step among 64
+// waves, against 5 us through memory; they check that with the die's number, and store through to memory if it is not so.
+// Bound: the chain of steps.  512 rows on 64 waves: TRI_MEASURED
+template <int C, int R, int QW>
+struct Tri {
+    static constexpr int CN = 64 * C, W = 64 * QW;
+    double a[R][C];
+    double x[C];
+    const DirectMat* m;
+    u64* slots;
+    int lane, w, wl, q, off, N, k_first;
+    bool local;
+
+    __device__ inline void put(u64* p, u64 v) const
+    {
+        if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // steps k of [64 P, 64 (P + 1)): chunks of columns before P are finished
+    template <int P>
+    __device__ inline bool phase(int& k)
+    {
+        constexpr int T0 = P / QW;                               // row slots before T0 are finished
+        constexpr int PN = P + 1 < C ? P + 1 : P;
+        const int k_end = P + 1 < C ? 64 * (P + 1) : CN - 2;
+        for (; k < k_end; ++k) {
+            const int k1 = k + 1, l1 = k1 & 63;
+            const bool next_chunk = P + 1 < C && l1 == 0;        // row k + 1 is the first of chunk P + 1
+            const double alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
+            double sq = 0.0;
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                const double y = lane + 64 * c > k1 ? x[c] : 0.0;
+                sq = fma(y, y, sq);
+            }
+            const Step s = householder(alpha, wave_sum(sq));
+            double v[C];
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                const int i = lane + 64 * c;
+                v[c] = i > k1 ? (s.tau != 0.0 ? x[c] : 0.0) : i == k1 ? s.v0 : 0.0;
+            }
+            if (w == (k & (W - 1))) {                            // one wave keeps the step for the way back
+                const int kk = k - off;
+#pragma unroll
+                for (int c = P; c < C; ++c) m->refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
+                const double dk = lane_value(x[P], k & 63);
+                if (lane == 0) {
+                    m->tau[kk] = s.tau;
+                    m->dg[kk] = dk;
+                    m->od[kk] = s.beta;
+                    m->od2[kk] = fmax(s.beta * s.beta, OD2_MIN);
+                }
+            }
+            const unsigned step = (unsigned)(k - k_first + 1);   // (from 1: the cleared slots carry tag 0)
+            const u64 tag = step & 3;
+            u64* slot_p = slots + (step & 1) * (2 * CN);
+            u64* slot_c = slot_p + CN;
+            // column k + 1 of the matrix, from the wave that owns that row
+            if (wl == l1) {
+                if (!next_chunk) {
+                    if (q == P % QW) {
+#pragma unroll
+                        for (int c = P; c < C; ++c) put(slot_c + lane + 64 * c, ((u64)__double_as_longlong(a[P / QW][c]) & ~3ull) | tag);
+                    }
+                } else if (q == PN % QW) {
+#pragma unroll
+                    for (int c = P; c < C; ++c) put(slot_c + lane + 64 * c, ((u64)__double_as_longlong(a[PN / QW][c]) & ~3ull) | tag);
+                }
+            }
+            {
+                double part[R - T0];
+#pragma unroll
+                for (int t = T0; t < R; ++t) {
+                    double sum = a[t][P] * v[P];
+#pragma unroll
+                    for (int c = P + 1; c < C; ++c) sum = fma(a[t][c], v[c], sum);
+                    part[t - T0] = sum;
+                }
+                const double p = wave_sums<R - T0>(part, lane);
+                const int t = T0 + sum_slot(lane);
+                if ((lane & 7) == 0 && t < R) put(slot_p + w + W * t, ((u64)__double_as_longlong(p) & ~3ull) | tag);
+            }
+            u64 pu[C], cu[C];
+            int spins = 0;
+            while (true) {
+                bool ok = true;
+#pragma unroll
+                for (int c = P; c < C; ++c) {
+                    pu[c] = __hip_atomic_load(slot_p + lane + 64 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cu[c] = __hip_atomic_load(slot_c + lane + 64 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int c = P; c < C; ++c) ok = ok && (pu[c] & 3) == tag && (cu[c] & 3) == tag;
+                if (__all(ok)) break;
+                if (++spins > SPIN_STEP) return false;
+            }
+            double p[C], gamma = 0.0;
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                p[c] = __longlong_as_double((long long)(pu[c] & ~3ull));
+                if (c == P || c == PN) p[c] = lane + 64 * c > k ? p[c] : 0.0;
+                gamma = fma(v[c], p[c], gamma);
+            }
+            gamma = wave_sum(gamma) * (0.5 * s.tau * s.tau);
+            double wv[C];
+#pragma unroll
+            for (int c = P; c < C; ++c) wv[c] = fma(-gamma, v[c], s.tau * p[c]);
+            const double wk1 = lane_value(next_chunk ? wv[PN] : wv[P], l1);
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                const double cc = __longlong_as_double((long long)(cu[c] & ~3ull));
+                x[c] = fma(-wv[c], s.v0, fma(-v[c], wk1, cc));
+            }
+#pragma unroll
+            for (int t = T0; t < R; ++t) {
+                double vr, wr;
+                if constexpr (QW == 1) {
+                    vr = lane_value(v[t], wl);
+                    wr = lane_value(wv[t], wl);
+                } else {
+                    vr = wr = 0.0;
+                    if (q == 0) {
+                        if constexpr (2 * (T0 < R ? 1 : 1) > 0) {
+                            if (2 * t >= P) { vr = lane_value(v[2 * t >= P ? 2 * t : P], wl); wr = lane_value(wv[2 * t >= P ? 2 * t : P], wl); }
+                        }
+                    } else {
+                        vr = lane_value(v[2 * t + 1], wl);
+                        wr = lane_value(wv[2 * t + 1], wl);
+                    }
+                }
+#pragma unroll
+                for (int c = P; c < C; ++c) a[t][c] = fma(-wr, v[c], fma(-vr, wv[c], a[t][c]));
+            }
+        }
+        return true;
+    }
+
+    template <int P>
+    __device__ inline bool phases(int& k)
+    {
+        if (!phase<P>(k)) return false;
+        if constexpr (P + 1 < C) return phases<P + 1>(k);
+        return true;
+    }
+
+    static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
+    static constexpr long long SPIN_START = 200000000ll;         // 2 s of the 100 MHz clock for all workgroups to have started
+
+    // false: a wait hit its bound
+    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs)
+    {
+        m = &mm;
+        lane = threadIdx.x & 63;
+        w = member * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        wl = w & 63;
+        q = w >> 6;
+        N = mm.nt * TILE;
+        off = CN - N;
+        slots = mm.xch;
+        // which die: every workgroup says so, all wait for all
+        const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u) + 1;
+        if (threadIdx.x == 0) __hip_atomic_store(mm.xid + member, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int expo, zeros;
+        const double scale = scale_of<C>(mm, off, lane, expo, zeros);
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            const int i = w + W * t - off;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int j = lane + 64 * c - off;
+                a[t][c] = i >= 0 && j >= 0 ? scale * mm.C[(size_t)i * N + j] : 0.0;
+            }
+        }
+        int k = off + mm.pad;
+        k_first = k;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int j = lane + 64 * c - off;
+            x[c] = j >= 0 ? scale * mm.C[(size_t)mm.pad * N + j] : 0.0;
+        }
+        {
+            const long long t0 = wall_clock64();
+            while (true) {
+                const int id = lane < n_wgs ? __hip_atomic_load(mm.xid + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcc;
+                if (__all(id != 0)) {
+                    local = __all(id == xcc);
+                    break;
+                }
+                if (wall_clock64() - t0 > SPIN_START) return false;
+                __builtin_amdgcn_s_sleep(4);
+            }
+        }
+        if (!phases<0>(k)) return false;
+        // what is left: the last 2 x 2 block
+        if (w == 0) {
+            const double d = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63);
+            if (lane == 0) {
+                mm.dg[N - 2] = d;
+                mm.od[N - 2] = e;
+                mm.od2[N - 2] = fmax(e * e, OD2_MIN);
+                mm.tau[N - 2] = 0.0;
+                mm.st[DS_EXP] = expo;
+                mm.st[DS_ZERO_ROWS] = zeros;
+            }
+        }
+        if (wl == 63 && q == (C - 1) % QW) {
+            const double d = lane_value(a[R - 1][C - 1], 63);
+            if (lane == 0) mm.dg[N - 1] = d;
+        }
+        return true;
+    }
+};
+
+// Up to 128 rows: one workgroup, no exchange through memory.  Lane l holds rows l (and l + 64), wave w the columns w, w + 4, ..;
+// the products of the four waves are added up through LDS, one barrier per step.
+template <int C>
+__device__ inline void tri_small(const DirectMat& m)
+{
+    constexpr int CN = 64 * C, NC = 16 * C;                      // columns per wave
+    __shared__ double part[2][4][CN], col[2][CN];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int N = m.nt * TILE, off = CN - N;
+    int expo, zeros;
+    const double scale = scale_of<C>(m, off, lane, expo, zeros);
+    double a[NC][C], x[C];
+#pragma unroll
+    for (int t = 0; t < NC; ++t) {
+        const int j = w + 4 * t - off;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = lane + 64 * c - off;
+            a[t][c] = i >= 0 && j >= 0 ? scale * m.C[(size_t)j * N + i] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int j = lane + 64 * c - off;
+        x[c] = j >= 0 ? scale * m.C[(size_t)m.pad * N + j] : 0.0;
+    }
+    for (int k = off + m.pad; k < CN - 2; ++k) {
+        const int k1 = k + 1, l1 = k1 & 63, c1 = k1 >> 6;
+        const double alpha = lane_value(C > 1 && c1 ? x[C - 1] : x[0], l1);
+        double sq = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double y = lane + 64 * c > k1 ? x[c] : 0.0;
+            sq = fma(y, y, sq);
+        }
+        const Step s = householder(alpha, wave_sum(sq));
+        double v[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = lane + 64 * c;
+            v[c] = i > k1 ? (s.tau != 0.0 ? x[c] : 0.0) : i == k1 ? s.v0 : 0.0;
+        }
+        if (w == (k & 3)) {
+            const int kk = k - off;
+            const double dk = lane_value(C > 1 && k >= 64 ? x[C - 1] : x[0], k & 63);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (lane + 64 * c >= off) m.refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
+            if (lane == 0) {
+                m.tau[kk] = s.tau;
+                m.dg[kk] = dk;
+                m.od[kk] = s.beta;
+                m.od2[kk] = fmax(s.beta * s.beta, OD2_MIN);
+            }
+        }
+        double vj[NC], sum[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) sum[c] = 0.0;
+#pragma unroll
+        for (int t = 0; t < NC; ++t) {
+            vj[t] = lane_value(v[t / 16], w + 4 * (t & 15));
+#pragma unroll
+            for (int c = 0; c < C; ++c) sum[c] = fma(a[t][c], vj[t], sum[c]);
+        }
+        double(*pt)[CN] = part[k & 1];
+        double* cl = col[k & 1];
+#pragma unroll
+        for (int c = 0; c < C; ++c) pt[w][lane + 64 * c] = sum[c];
+        if (lane == l1) {
+#pragma unroll
+            for (int t = 0; t < NC; ++t) cl[w + 4 * t] = C > 1 && c1 ? a[t][C - 1] : a[t][0];
+        }
+        __syncthreads();
+        double p[C], gamma = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = lane + 64 * c;
+            p[c] = (pt[0][i] + pt[1][i]) + (pt[2][i] + pt[3][i]);
+            p[c] = i > k ? p[c] : 0.0;
+            gamma = fma(v[c], p[c], gamma);
+        }
+        gamma = wave_sum(gamma) * (0.5 * s.tau * s.tau);
+        double wv[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) wv[c] = fma(-gamma, v[c], s.tau * p[c]);
+        const double wk1 = lane_value(C > 1 && c1 ? wv[C - 1] : wv[0], l1);
+#pragma unroll
+        for (int c = 0; c < C; ++c) x[c] = fma(-wv[c], s.v0, fma(-v[c], wk1, cl[lane + 64 * c]));
+#pragma unroll
+        for (int t = 0; t < NC; ++t) {
+            const double wj = lane_value(wv[t / 16], w + 4 * (t & 15));
+#pragma unroll
+            for (int c = 0; c < C; ++c) a[t][c] = fma(-wj, v[c], fma(-vj[t], wv[c], a[t][c]));
+        }
+    }
+    if (w == 3) {                                                // (the wave of the last column)
+        const double d2 = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63), d1 = lane_value(a[NC - 1][C - 1], 63);
+        if (lane == 0) {
+            m.dg[N - 2] = d2;
+            m.dg[N - 1] = d1;
+            m.od[N - 2] = e;
+            m.od2[N - 2] = fmax(e * e, OD2_MIN);
+            m.tau[N - 2] = 0.0;
+            m.st[DS_EXP] = expo;
+            m.st[DS_ZERO_ROWS] = zeros;
+        }
+    }
+}
+
+// work: matrix (below 0: nothing), member of the group, workgroups of the group.
+__global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work)
+{
+    const Work wk = work[blockIdx.x];
+    if (wk.mat < 0) return;
+    const DirectMat& m = mats[wk.mat];
+    bool ok = true;
+    switch (m.cls) {
+        case CLS_64: tri_small<1>(m); break;
+        case CLS_128: tri_small<2>(m); break;
+        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b); } break;
+        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b); } break;
+        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b); } break;
+    }
+    if (!ok && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Blocks of reflectors
+// ------------------------------------------------------------------------------------------------
+constexpr int VMAX = MAX_R;
+constexpr int RB = 16;           // reflectors per block of the way back through H
+
+// H = H_0 H_1 .. in blocks of 16 reflectors, each I - V F V^T with V the 16 vectors and F upper triangular: column i of F is
+// -tau_i F (V^T v_i) above the diagonal and tau_i on it.  One workgroup per block: the 16 x 16 products V^T V on the
+// matrix cores (every wave a quarter of the columns), then the columns of F one after the other.
+__device__ inline void block_factor(const DirectMat& m, int b)
+{
+    __shared__ double gram[4][RB][RB + 1], f[RB][RB + 1], tau[RB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
+    const int N = m.nt * TILE, k0 = b * RB, k = k0 + l16;
+    const bool live = k >= m.pad && k < N - 2;
+    const double* row = m.refl + (size_t)k * N;
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int c = (k0 & ~63) + 16 * wave; c < N; c += 64) {
+        double2 v[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+        if (live) {
+            v[0] = *(const double2*)(row + c + 4 * q);
+            v[1] = *(const double2*)(row + c + 4 * q + 2);
+        }
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[0].x, v[0].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[0].y, v[0].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[1].x, v[1].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[1].y, v[1].y, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gram[wave][4 * v + q][l16] = acc[v];
+    if (tid < RB) tau[tid] = live ? m.tau[k] : 0.0;
+    f[tid >> 4][tid & 15] = 0.0;
+    __syncthreads();
+    gram[0][tid >> 4][tid & 15] = (gram[0][tid >> 4][tid & 15] + gram[1][tid >> 4][tid & 15]) +
+                                  (gram[2][tid >> 4][tid & 15] + gram[3][tid >> 4][tid & 15]);
+    __syncthreads();
+    if (tid < 64) {                                              // one wave: LDS operations in program order
+        for (int i = 0; i < RB; ++i) {
+            if (lane < i) {
+                double sum = 0.0;
+                for (int j = lane; j < i; ++j) sum = fma(f[lane][j], gram[0][j][i], sum);
+                f[lane][i] = -tau[i] * sum;
+            } else if (lane == i) {
+                f[i][i] = tau[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+    __syncthreads();
+    m.fact[(size_t)b * (RB * RB) + tid] = f[tid >> 4][tid & 15];
+}
+
+// ------------------------------------------------------------------------------------------------
+// Eigenvalues of T
+// ------------------------------------------------------------------------------------------------
+// How many eigenvalues of T lie below z: sign changes of the characteristic polynomials of the leading blocks,
+// p_{i+1} = (d_i - z) p_i - e_{i-1}^2 p_{i-1} (no division; rescaled by a power of two every eight steps, the squared
+// off-diagonals are kept above 2^-110 so that eight steps stay inside the range).  T comes through scalar loads.
+typedef const double __attribute__((address_space(4)))* scalar_ptr;   // read through the scalar cache, never written here
+
+__device__ inline int sturm_count(scalar_ptr dg, scalar_ptr od2, int n, double z)
+{
+    double p0 = 0.0, p1 = 1.0;
+    int count = 0, i = 0;
+    unsigned signs = 0;
+    // the entries of the next eight steps are on their way while these eight run
+    double dn[8], en[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        dn[u] = dg[u];                                           // (n > 32)
+        en[u] = u > 0 ? od2[u - 1] : 0.0;
+    }
+    for (; i + 8 <= n; i += 8) {
+        double d[8], e2[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            d[u] = dn[u];
+            e2[u] = en[u];
+        }
+        const int next = i + 16 <= n ? i + 8 : i;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            dn[u] = dg[next + u];
+            en[u] = od2[next + u - (next > 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double p2 = fma(d[u] - z, p1, -(e2[u] * p0));
+            p0 = p1;
+            p1 = p2;
+            signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+        }
+        count += __popc((signs ^ (signs >> 1)) & 0xffu);
+        const int e = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+        p0 = __builtin_amdgcn_ldexp(p0, -e);
+        p1 = __builtin_amdgcn_ldexp(p1, -e);
+    }
+    for (; i < n; ++i) {
+        const double p2 = fma(dg[i] - z, p1, -(od2[i - 1] * p0));
+        count += (hi32(p2) ^ hi32(p1)) >> 31;
+        p0 = p1;
+        p1 = p2;
+    }
+    return count;
+}
+
+__device__ inline double bits_double(u64 b) { return __longlong_as_double((long long)b); }
+
+// Eigenvalue number i (descending) in [2^-50, 1), searched on the bit pattern of the double, in cells of 2^25 patterns
+// (LAM_BITS relative bits): a first pass at 256 points for all eigenvalues of the workgroup, then `lanes` points per
+// eigenvalue and pass.  The cell that is found does not depend on how many points a pass has.
+// Work: matrix, first eigenvalue; 256 / lanes eigenvalues per workgroup.  Behind the n_eig of these: matrix, block of
+// reflectors (block_factor: wanted by the next kernels, and this one leaves the room).
+__device__ inline double cell_start(u64 cell) { return bits_double(LAM_MIN_BITS + (cell << LAM_STEP_BITS)); }
+
+__global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats, const Work* work, int n_eig, int lanes)
+{
+    if ((int)blockIdx.x >= n_eig) {
+        const Work wb = work[blockIdx.x];
+        block_factor(mats[wb.mat], wb.a);
+        return;
+    }
+    __shared__ int below[256];
+    constexpr u64 CELLS = (LAM_MAX_BITS - LAM_MIN_BITS) >> LAM_STEP_BITS, SPAN = CELLS / 256;
+    const Work wk = work[blockIdx.x];
+    const DirectMat& m = mats[wk.mat];
+    const int tid = threadIdx.x, lane = tid & 63, n = m.r;
+    const scalar_ptr dg = (scalar_ptr)(u64)(m.dg + m.pad), od2 = (scalar_ptr)(u64)(m.od2 + m.pad);
+    below[tid] = sturm_count(dg, od2, n, cell_start(SPAN * tid));
+    __syncthreads();
+    const int l = tid & (lanes - 1), base = lane & ~(lanes - 1);
+    const int i = min(wk.a + tid / lanes, n - 1);                // (a group past the end repeats the last one)
+    const int asc = n - 1 - i;
+    // last point with at most asc eigenvalues below it
+    int lo = 0, hi = 256;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (below[mid] <= asc) lo = mid; else hi = mid;
+    }
+    const bool zero = below[0] > asc;
+    u64 g0 = SPAN * lo, g1 = zero ? g0 : g0 + SPAN;
+    const u64 group = lanes == 64 ? ~0ull : ((1ull << lanes) - 1) << base;
+    while (!__all(g1 - g0 <= 1)) {
+        const u64 width = g1 - g0;
+        const u64 z = g0 + width * (unsigned)(l + 1) / (unsigned)(lanes + 1);
+        const int k = __popcll(__ballot(sturm_count(dg, od2, n, cell_start(z)) <= asc) & group);
+        const u64 z_lo = __shfl(z, base + max(k - 1, 0)), z_hi = __shfl(z, base + min(k, lanes - 1));
+        if (k > 0) g0 = z_lo;
+        if (k < lanes) g1 = z_hi;
+    }
+    if (l == 0) m.lam[i] = zero ? 0.0 : bits_double(LAM_MIN_BITS + (g0 << LAM_STEP_BITS) + (1ull << (LAM_STEP_BITS - 1)));
+}
+
+// ------------------------------------------------------------------------------------------------
+// Probabilities, draw, message header; one workgroup per matrix
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, double s, u64 seed, int* flags)
+{
+    __shared__ float key[MAX_R];
+    __shared__ Alg1Scratch sc;
+    __shared__ int ipart[256];
+    __shared__ int close;
+    const DirectMat& m = mats[blockIdx.x];
+    const int tid = threadIdx.x, r = m.r;
+    const double l0 = m.lam[0];
+    const int half = m.st[DS_EXP] / 2, zeros = m.st[DS_ZERO_ROWS];
+    const double floor = (double)svd::ZERO_REL * l0;
+    for (int i = tid; i < r; i += 256) {
+        const double l = m.lam[i];
+        key[i] = l > floor ? (float)ldexp(sqrt(l), half) : 0.0f;
+    }
+    if (tid == 0) close = 0;
+    __syncthreads();
+    const int ns = block_algorithm1(key, r, s, sc);
+    const double tail_ns = sc.tail_ns;
+    const int per = (r + 255) / 256;
+    const int lo = min(r, tid * per), hi = min(r, lo + per);
+    int kept_local = 0;
+    bool kept_before = false;
+    for (int i = lo; i < hi; ++i) {
+        const float p = alg1_probability(key[i], i, ns, s, tail_ns);
+        const u32x4 rnd = philox4x32_10((u64)(i >> 2), m.stream_id, seed);
+        const uint32_t word = (i & 3) == 0 ? rnd.x : (i & 3) == 1 ? rnd.y : (i & 3) == 2 ? rnd.z : rnd.w;
+        if (m.sigma_out) m.sigma_out[i] = key[i];
+        if (m.p_out) m.p_out[i] = p;
+        const bool kept = u01(word) < p;
+        kept_local += kept;
+        // two kept neighbours that the search left inside one interval: their vectors are not separated
+        if (kept) {
+            if (i == lo && i > 0) {
+                const float pb = alg1_probability(key[i - 1], i - 1, ns, s, tail_ns);
+                const u32x4 rb = philox4x32_10((u64)((i - 1) >> 2), m.stream_id, seed);
+                const int x = (i - 1) & 3;
+                kept_before = u01(x == 0 ? rb.x : x == 1 ? rb.y : x == 2 ? rb.z : rb.w) < pb;
+            }
+            if (kept_before && i > 0 && m.lam[i - 1] - m.lam[i] <= m.lam[i] * (4.0 / (double)(1 << LAM_BITS))) close = 1;
+        }
+        kept_before = kept;
+    }
+    ipart[tid] = kept_local;
+    __syncthreads();
+    const int owners = (r + per - 1) / per;
+    int pos = 0;
+    for (int t = 0; t < min(tid, owners); ++t) pos += ipart[t];
+    if (tid == 0) {
+        m.report[0] = 1;
+        m.report[1] = 2;
+        // all of the spectrum above the floor, but for rows of A that are zero themselves; a matrix of zeros has no atoms
+        const bool resolved = zeros >= r || (zeros < r && m.lam[r - 1 - zeros] > FLOOR_REL * l0);
+        m.st[DS_ACCEPT] = resolved && !close && m.st[DS_FAIL] == 0;
+        atomicMax(&flags[FLAG_MAX_SWEEPS], 1);
+    }
+    if (tid == 255) {
+        const int total = pos + kept_local;
+        *m.count = total;
+        if (total > m.capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
+    }
+    for (int i = lo; i < hi; ++i) {
+        const float p = alg1_probability(key[i], i, ns, s, tail_ns);
+        const u32x4 rnd = philox4x32_10((u64)(i >> 2), m.stream_id, seed);
+        const uint32_t word = (i & 3) == 0 ? rnd.x : (i & 3) == 1 ? rnd.y : (i & 3) == 2 ? rnd.z : rnd.w;
+        if (u01(word) < p) {
+            if (pos < m.capacity) {
+                const float weight = key[i] / p;
+                m.idx[pos] = i;
+                if (m.w) m.w[pos] = weight;
+                m.inv[pos] = weight;
+            }
+            ++pos;
+        }
+    }
+}
+
+// Vectors of the shorter side
+// ------------------------------------------------------------------------------------------------
+// One workgroup of 64 nt threads (or more: the largest matrix of the call) per kept atom.
+//
+// First the eigenvector of T for the eigenvalue next to lam, by a twisted factorisation (wave 0): pivots from the top
+// (lane 0) and from the bottom (lane 1) as quotients of the characteristic polynomials of the leading and of the trailing
+// blocks, twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and a second round
+// starts from there.  Then its image under H, a block of 16 reflectors at a time: thread i owns entry i of the vector
+// and column i of V.  Bound: latency, two chains of n steps per round and N / 16 blocks with one barrier each.
+// Work: matrix, slot.
+__global__ __launch_bounds__(MAX_R) void direct_vectors(const DirectMat* mats, const Work* work)
+{
+    __shared__ double2 de[2][VMAX + 8];      // per direction: diagonal and the squared coupling to the step before
+    __shared__ double P[2][VMAX + 8], B[2][VMAX / 8 + 1], e[VMAX], X[VMAX], part[2][VMAX / 64][RB], red[VMAX / 64];
+    __shared__ double s_res;
+    const Work wk = work[blockIdx.x];
+    const DirectMat& m = mats[wk.mat];
+    const int slot = wk.a, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = m.r, nw = blockDim.x >> 6;
+    if (slot >= min(*m.count, m.capacity)) return;
+    const int N = m.nt * TILE;
+    // the first block of the way back, on its way from here on
+    int b = (N - 3) / RB;
+    const int col = tid;
+    double vn[RB];
+    auto fetch = [&](int blk) {
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            const int k = blk * RB + j;
+            vn[j] = col < N && col >= (k & ~63) && k >= m.pad && k < N - 2 ? m.refl[(size_t)k * N + col] : 0.0;
+        }
+    };
+    fetch(b);
+    for (int i = tid; i < n; i += blockDim.x) {
+        const double d = m.dg[m.pad + i], o = i + 1 < n ? m.od[m.pad + i] : 0.0;
+        e[i] = o;
+        de[0][i].x = d;
+        de[1][n - 1 - i].x = d;
+        de[0][i + 1].y = o * o;
+        de[1][n - 1 - i].y = o * o;
+    }
+    if (tid == 0) de[0][0].y = 0.0;
+    if (tid < 16) de[tid >> 3][n + (tid & 7)].x = 0.0;           // (steps past the end, up to a multiple of eight)
+    if (tid < 14) de[tid / 7][n + 1 + tid % 7].y = 0.0;
+    if (tid == 0) de[1][n].y = 0.0;
+    __syncthreads();
+    double y = 0.0;
+    if (wave == 0) {
+        double lam = m.lam[m.idx[slot]], norm2 = 1.0, res = 0.0;
+        const double good = 1e-14 * m.lam[0];
+        const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
+        for (int round = 0; round < 3; ++round) {
+            if (lane < 2) {
+                double p0 = 0.0, p1 = 1.0;
+                double* out = P[lane];
+                const double2* in = de[lane];
+                out[0] = 1.0;
+                double2 next[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) next[u] = in[u];
+                for (int i = 0; i < n; i += 8) {
+                    double2 now[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) now[u] = next[u];
+                    const int at = i + 8 < n ? i + 8 : i;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) next[u] = in[at + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const double p2 = fma(now[u].x - lam, p1, -(now[u].y * p0));
+                        p0 = p1;
+                        p1 = p2;
+                        if (u < 7) out[i + u + 1] = p1;
+                    }
+                    const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+                    p0 = __builtin_amdgcn_ldexp(p0, -ex);
+                    p1 = __builtin_amdgcn_ldexp(p1, -ex);
+                    B[lane][i >> 3] = p0;
+                    out[i + 8] = p1;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet
+            auto pivots = [&](int i, double& top, double& bot) {
+                const int j = n - 1 - i;
+                top = P[0][i + 1] / ((i & 7) == 7 ? B[0][i >> 3] : P[0][i]);
+                bot = P[1][j + 1] / ((j & 7) == 7 ? B[1][j >> 3] : P[1][j]);
+                return top + bot - (de[0][i].x - lam);
+            };
+            double best = 1e300, gamma = 0.0;
+            int at = 0;
+            for (int i = i0; i < i1; ++i) {
+                double top, bot;
+                const double g = pivots(i, top, bot);
+                if (fabs(g) < best) { best = fabs(g); gamma = g; at = i; }
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ob = __shfl_xor(best, o), og = __shfl_xor(gamma, o);
+                const int oa = __shfl_xor(at, o);
+                if (ob < best || (ob == best && oa < at)) { best = ob; gamma = og; at = oa; }
+            }
+            // entries from the twist outwards: products of -e_i / top_i downwards and of -e_{i-1} / bottom_i upwards,
+            // per lane over its own entries, then over the lanes
+            double up = 1.0, down = 1.0;
+            for (int i = i0; i < i1; ++i) {
+                double top, bot;
+                (void)pivots(i, top, bot);
+                const double f = i < at ? -e[i] / top : i > at ? -e[i - 1] / bot : 1.0;
+                X[i] = f;
+                if (i < at) down *= f; else up *= f;
+            }
+            double up_before = up, down_after = down;
+            for (int o = 1; o < 64; o <<= 1) {
+                const double u = __shfl_up(up_before, o), d = __shfl_down(down_after, o);
+                if (lane >= o) up_before *= u;
+                if (lane + o < 64) down_after *= d;
+            }
+            up_before = __shfl_up(up_before, 1);
+            down_after = __shfl_down(down_after, 1);
+            if (lane == 0) up_before = 1.0;
+            if (lane == 63) down_after = 1.0;
+            double sq = 0.0, run = up_before;
+            for (int i = max(i0, at); i < i1; ++i) {
+                run *= X[i];
+                X[i] = run;
+                sq = fma(run, run, sq);
+            }
+            run = down_after;
+            for (int i = min(i1, at) - 1; i >= i0; --i) {
+                run *= X[i];
+                X[i] = run;
+                sq = fma(run, run, sq);
+            }
+            norm2 = wave_sum(sq);
+            res = fabs(gamma) / sqrt(norm2);                     // |T x - lam x| / |x|
+            if (res <= good) break;
+            if (round < 2) lam += gamma / norm2;
+        }
+        // (the eigenvalue was not separated from its neighbour, or the factorisation broke down)
+        if (lane == 0) s_res = res <= 100.0 * good ? 1.0 / sqrt(norm2) : -1.0;
+    }
+    __syncthreads();
+    const double scale = s_res;
+    if (tid == 0 && !(scale > 0.0)) m.st[DS_ACCEPT] = 0;
+    if (col >= m.pad && col < N) y = X[col - m.pad] * scale;
+    // back through H
+    for (; b >= m.pad / RB; --b) {
+        double v[RB], f[RB], prod[RB];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            v[j] = vn[j];
+            prod[j] = v[j] * y;
+        }
+#pragma unroll
+        for (int j = 0; j < RB; ++j) f[j] = m.fact[(size_t)b * (RB * RB) + (lane & 15) * RB + j];
+        if (b > m.pad / RB) fetch(b - 1);
+        const double lo = wave_sums<8>((const double(&)[8])prod[0], lane), hi = wave_sums<8>((const double(&)[8])prod[8], lane);
+        double(*pt)[RB] = part[b & 1];
+        if ((lane & 7) == 0) {
+            pt[wave][sum_slot(lane)] = lo;
+            pt[wave][8 + sum_slot(lane)] = hi;
+        }
+        __syncthreads();
+        double sum = 0.0;
+        for (int w = 0; w < nw; ++w) sum += pt[w][lane & 15];    // lane j: the product of vector j with y
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < RB; ++j) t = fma(f[j], lane_value(sum, j), t);
+#pragma unroll
+        for (int j = 0; j < RB; ++j) y = fma(-v[j], lane_value(t, j), y);
+    }
+    {
+        const double sq = wave_sum(y * y);
+        if (lane == 0) red[wave] = sq;
+    }
+    __syncthreads();
+    double sq = 0.0;
+    for (int w = 0; w < nw; ++w) sq += red[w];
+    y /= sqrt(sq);
+    const float fold = m.w || m.transposed ? 1.0f : m.inv[slot];  // folded message: the weight goes into U
+    float* out = m.transposed ? m.V + (size_t)slot * m.cols : m.U + (size_t)slot * m.rows;
+    if (col >= m.pad && col < N) {
+        m.u[(size_t)slot * n + col - m.pad] = y;
+        out[col - m.pad] = (float)y * fold;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Vectors of the longer side: A^T u / sigma, four kept atoms per pass over the data
+// ------------------------------------------------------------------------------------------------
+constexpr int LONG_COLS = 128;   // positions of the long side per workgroup
+constexpr int LONG_GROUP = 4;
+
+// Bound: one read of the data (4 atoms at a time).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
+// positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The last workgroup reports.
+__global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_items, int n_mats, int finish,
+                                                   int* hint_out, int* flags)
+{
+    __shared__ double us[LONG_GROUP][MAX_R];
+    __shared__ double red[8][LONG_GROUP][LONG_COLS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if ((int)blockIdx.x >= n_items) {
+        __shared__ int left;
+        if (tid == 0) left = 0;
+        __syncthreads();
+        int open = 0;
+        for (int j = tid; j < n_mats; j += 512) open += mats[j].st[DS_ACCEPT] == 0;
+        if (open) atomicAdd(&left, open);
+        __syncthreads();
+        if (tid == 0 && finish) {
+            if (left) atomicMax(&flags[FLAG_NOCONV], 1);
+            if (hint_out) {
+                hint_out[0] = hint_out[1] = 1;
+                hint_out[3] = 0;
+                hint_out[4] = left;
+                hint_out[2] = 1;
+            }
+        }
+        return;
+    }
+    const Work wk = work[blockIdx.x];
+    const DirectMat& m = mats[wk.mat];
+    const int kept = min(*m.count, m.capacity), r = m.r, p0 = wk.a * LONG_COLS;
+    float* out = m.transposed ? m.U : m.V;
+    for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
+        const int ns = min(LONG_GROUP, kept - s0);
+        __syncthreads();
+        for (int i = tid; i < LONG_GROUP * r; i += 512) {
+            const int k = i / r, x = i - k * r;
+            us[k][x] = k < ns ? m.u[(size_t)(s0 + k) * r + x] : 0.0;
+        }
+        __syncthreads();
+        if (!m.transposed) {
+            double acc[LONG_GROUP][2];
+#pragma unroll
+            for (int k = 0; k < LONG_GROUP; ++k) acc[k][0] = acc[k][1] = 0.0;
+            const int ca = min(p0 + lane, m.M - 1), cb = min(p0 + 64 + lane, m.M - 1);
+            for (int i0 = wave; i0 < r; i0 += 8 * 8) {
+                float ga[8], gb[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = min(i0 + 8 * u, r - 1);
+                    ga[u] = m.G[(long long)i * m.ldg + ca];
+                    gb[u] = m.G[(long long)i * m.ldg + cb];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = i0 + 8 * u;
+                    if (i < r) {
+#pragma unroll
+                        for (int k = 0; k < LONG_GROUP; ++k) {
+                            acc[k][0] = fma((double)ga[u], us[k][i], acc[k][0]);
+                            acc[k][1] = fma((double)gb[u], us[k][i], acc[k][1]);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < LONG_GROUP; ++k) {
+                red[wave][k][lane] = acc[k][0];
+                red[wave][k][64 + lane] = acc[k][1];
+            }
+        } else {
+            // positions wave, wave + 8, ..: eight at a time, the lanes along the vector
+            for (int h = 0; h < LONG_COLS / 64; ++h) {
+                for (int k = 0; k < ns; ++k) {
+                    double acc[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+                    for (int i = lane; i < r; i += 64) {
+                        const double uu = us[k][i];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const int p = min(p0 + 64 * h + wave + 8 * u, m.M - 1);
+                            acc[u] = fma((double)m.G[(long long)p * m.ldg + i], uu, acc[u]);
+                        }
+                    }
+                    const double sum = wave_sums<8>(acc, lane);
+                    if ((lane & 7) == 0) red[0][k][64 * h + wave + 8 * sum_slot(lane)] = sum;
+                }
+            }
+        }
+        __syncthreads();
+        const int k = tid / LONG_COLS, p = tid % LONG_COLS;
+        if (k < ns && p0 + p < m.M) {
+            double sum = red[0][k][p];
+            if (!m.transposed) {
+#pragma unroll
+                for (int q = 1; q < 8; ++q) sum += red[q][k][p];
+            }
+            const int i = m.idx[s0 + k];
+            const double sigma = ldexp(sqrt(m.lam[i]), m.st[DS_EXP] / 2);
+            const float fold = m.w || !m.transposed ? 1.0f : m.inv[s0 + k];
+            out[(size_t)(s0 + k) * m.M + p0 + p] = (float)(sum / sigma) * fold;
+        }
+    }
+}
+
+int class_of(int r)
+{
+    int c = 0;
+    while (64 * CLS_CHUNKS[c] < r) ++c;
+    return c;
+}
+
+}  // namespace
+
+bool eligible(int r) { return r > svd::THIN_R && r <= MAX_R; }
+
+void plan_matrix(Carver& carve, DirectMat& m)
+{
+    m.nt = (m.r + TILE - 1) / TILE;
+    m.pad = m.nt * TILE - m.r;
+    m.cls = class_of(m.r);
+    const int ntiles = m.nt * (m.nt + 1) / 2;
+    // About 160 work items of the Gram product per matrix, none under 128 columns, at most 64 partial sums; from the shape
+    // alone, so that the sums do not depend on what else is in the call.
+    const int want = std::max(1, std::min({160 / ntiles, m.M / 128, 64}));
+    m.kchunk = (int)align_up((size_t)(m.M + want - 1) / want, GK);
+    m.nchunks = (m.M + m.kchunk - 1) / m.kchunk;
+    const size_t N = (size_t)m.nt * TILE;
+    m.part = carve.take<double>((size_t)m.nchunks * ntiles * TILE * TILE);
+    m.C = carve.take<double>(N * N);
+    m.refl = carve.take<double>(N * N);
+    m.tau = carve.take<double>(N);
+    m.dg = carve.take<double>(N);
+    m.od = carve.take<double>(N);
+    m.od2 = carve.take<double>(N);
+    m.fact = carve.take<double>(N * RB);
+    m.lam = carve.take<double>(m.r);
+    m.u = carve.take<double>((size_t)m.capacity * m.r);
+    m.xch = carve.take<u64>((size_t)4 * 64 * CLS_CHUNKS[m.cls]);
+    m.xid = carve.take<int>(64);
+    m.st = carve.take<int>(DS_WORDS);
+    m.inv = carve.take<float>(m.capacity);
+}
+
+void plan_work(DirectPlan& plan)
+{
+    size_t eigenvalues = 0;
+    for (const DirectMat& m : plan.mats) eigenvalues += (size_t)m.r;
+    // points per eigenvalue and pass of the search: as many as fill the chip about once (1024 waves)
+    plan.eig_lanes = 64;
+    while (plan.eig_lanes > 4 && eigenvalues * plan.eig_lanes > 1536 * 64) plan.eig_lanes /= 2;
+    std::vector<Work> factors;
+    std::vector<int> order(plan.mats.size());
+    for (size_t j = 0; j < order.size(); ++j) order[j] = (int)j;
+    for (int j : order) {
+        const DirectMat& m = plan.mats[j];
+        for (int ti = 0; ti < m.nt; ++ti)
+            for (int tj = ti; tj < m.nt; ++tj) {
+                plan.tiles.push_back(Work{j, ti, tj, 0});
+                for (int c = 0; c < m.nchunks; ++c) plan.gram.push_back(Work{j, ti, tj, c});
+            }
+        for (int i = 0; i < m.r; i += 256 / plan.eig_lanes) plan.eig.push_back(Work{j, i, 0, 0});
+        for (int b = m.pad / RB; b <= (m.nt * TILE - 3) / RB; ++b) factors.push_back(Work{j, b, 0, 0});
+        plan.max_nt = std::max(plan.max_nt, m.nt);
+        for (int k = 0; k < m.capacity; ++k) plan.vec.push_back(Work{j, k, 0, 0});
+        for (int p = 0; p < (m.M + LONG_COLS - 1) / LONG_COLS; ++p) plan.lng.push_back(Work{j, p, 0, 0});
+    }
+    plan.n_eig = plan.eig.size();
+    plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
+    // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].r > plan.mats[b].r; });
+    std::vector<Work> die[8];
+    long long load[8] = {0};
+    for (int j : order) {
+        const DirectMat& m = plan.mats[j];
+        const int wgs = CLS_WGS[m.cls];
+        int best = 0;
+        for (int x = 1; x < 8; ++x)
+            if (load[x] < load[best]) best = x;
+        for (int g = 0; g < wgs; ++g) die[best].push_back(Work{j, g, wgs, 0});
+        load[best] += (long long)m.r * wgs;
+    }
+    size_t most = 0;
+    for (const auto& l : die) most = std::max(most, l.size());
+    plan.tri.assign(8 * most, Work{-1, 0, 0, 0});
+    for (int x = 0; x < 8; ++x)
+        for (size_t k = 0; k < die[x].size(); ++k) plan.tri[8 * k + x] = die[x][k];
+}
+
+void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int finish, int* hint_out, int* d_flags,
+            hipStream_t stream)
+{
+    auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
+    direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
+    direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
+    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri);
+    direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
+    direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
+    direct_vectors<<<grid(plan.vec), 64u * (unsigned)plan.max_nt, 0, stream>>>(t.mats, t.vec);
+    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, (int)plan.lng.size(), t.n_mats, finish, hint_out, d_flags);
+}
+
+}  // namespace direct
+}  // namespace atomo

@@ -1,0 +1,127 @@
+"""GPU parity of the direct encode (Gram matrix, tridiagonal form, eigenvectors of the kept atoms): the edges of its size
+classes and tiles against the fp64 oracle, and the cases that it leaves to the Jacobi iteration."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1806_04090_amd import binding, inputs
+from gpu_common import ctx, dev, check_svd_message_against_matrix
+from test_gpu_svd import encode, full_parity
+
+pytestmark = pytest.mark.gpu
+
+DIRECT = (1, 2)                                                  # sweeps and passes over the data that it reports
+
+
+def route(n=1):
+    return list(zip(ctx().svd_sweeps(n), ctx().svd_refreshes(n)))
+
+
+@pytest.mark.parametrize("shape", [(33, 33), (40, 63), (64, 1300), (65, 70), (127, 128), (128, 129), (129, 131), (192, 257),
+                                   (255, 256), (256, 300), (257, 258), (448, 449), (511, 512), (512, 513), (513, 520),
+                                   (576, 577), (577, 600), (639, 641), (640, 640)])
+@pytest.mark.parametrize("tall", [False, True])
+def test_sizes_around_the_tiles(shape, tall):
+    rng = np.random.default_rng(shape[0] * 1009 + shape[1])
+    m, n = shape[::-1] if tall else shape
+    # (a square of noise has one singular value near zero: let it stay above the floor)
+    G = inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5, 0.25, 0.1], 0.01)
+    msgs, per, status, sweeps = encode([G], 3.0, 5, stream_base=3, capacity=min(shape))
+    assert status == 0
+    if abs(m - n) > 8:
+        assert route() == [DIRECT]
+    full_parity(G, 3.0, 5, 3, msgs[0], *per[0])
+
+
+def test_strided_folded_and_mixed_with_other_sizes_in_one_call():
+    rng = np.random.default_rng(3)
+    shapes = [(64, 27), (96, 200), (650, 660), (300, 140), (512, 700)]
+    host = [inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.4, 0.2], 0.01) for m, n in shapes]
+    mats = []
+    for g in host:
+        wide = torch.zeros(g.shape[0], g.shape[1] + 3, device="cuda")
+        wide[:, 1:-2] = dev(g)
+        mats.append(wide[:, 1:-2])                               # rows that start anywhere, an odd stride
+    total = sum(min(s) for s in shapes)
+    sigma, p = torch.zeros(total, device="cuda"), torch.zeros(total, device="cuda")
+    plain = binding.atomo_encode_svd(ctx(), mats, 3.0, 9, 40, sigma_out=sigma, p_out=p)
+    assert ctx().status()[0] == 0
+    kinds = route(len(shapes))
+    assert [k == DIRECT for k in kinds[1:]] == [True, False, True, True]
+    folded = [binding.alloc_svd_message(m, n, binding.default_capacity(3.0, min(m, n)), "cuda", folded=True) for m, n in shapes]
+    binding.atomo_encode_svd(ctx(), mats, 3.0, 9, 40, msgs=folded)
+    assert ctx().status()[0] == 0
+    a = binding.atomo_decode_svd_batch(ctx(), [[m] for m in plain])
+    b = binding.atomo_decode_svd_batch(ctx(), [[m] for m in folded])
+    at = 0
+    for j, g in enumerate(host):
+        r = min(g.shape)
+        full_parity(g, 3.0, 9, 40 + j, plain[j], sigma[at:at + r].cpu().numpy(), p[at:at + r].cpu().numpy())
+        at += r
+        assert torch.linalg.norm(a[j] - b[j]) <= 1e-5 * torch.linalg.norm(a[j])
+
+
+@pytest.mark.parametrize("shape", [(100, 300), (300, 400), (600, 620)])
+def test_left_to_the_iteration(shape):
+    # rank below the shorter side, kept atoms with equal singular values, an explicit option, a budget of many atoms
+    rng = np.random.default_rng(shape[0])
+    m, n = shape
+    low = (rng.standard_normal((m, m // 2)) @ rng.standard_normal((m // 2, n))).astype(np.float32)
+    q, _ = np.linalg.qr(rng.standard_normal((n, m)))
+    equal = np.zeros((m, n), dtype=np.float32)
+    equal[:, :m] = np.eye(m, dtype=np.float32)                   # every singular value is 1
+    for G, kw, s in ((low, {}, 3.0), (equal, {}, 32.0), (q.T.astype(np.float32), dict(block_order=1), 3.0),
+                     (q.T.astype(np.float32), {}, 40.0)):
+        msgs, per, status, _ = encode([G], s, 2, capacity=m, **kw)
+        assert status == 0 and route() != [DIRECT]
+        check_svd_message_against_matrix(G.astype(np.float64), msgs[0].to_host(), *per[0])
+
+
+@pytest.mark.parametrize("shape", [(120, 300), (500, 400)])
+def test_rows_of_zeros_and_a_matrix_of_zeros_are_solved_directly(shape):
+    # filters that got no gradient: as many singular values are exactly zero
+    rng = np.random.default_rng(shape[1])
+    G = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.5], 0.02)
+    dead = rng.choice(min(shape), 17, replace=False)
+    if shape[0] < shape[1]:
+        G[dead] = 0
+    else:
+        G[:, dead] = 0
+    msgs, per, status, _ = encode([G, np.zeros(shape, dtype=np.float32)], 3.0, 4, capacity=16)
+    assert status == 0 and route(2) == [DIRECT, DIRECT]
+    assert (per[0][0][-17:] == 0).all() and (per[0][1][-17:] == 0).all() and (per[0][0][:-17] > 0).all()
+    full_parity(G, 3.0, 4, 0, msgs[0], *per[0])
+    assert (per[1][0] == 0).all() and msgs[1].to_host()["count"] == 0
+
+
+def test_many_matrices_in_one_call_give_the_bits_of_calls_of_their_own():
+    # more groups than run at once, another number of points per eigenvalue
+    shapes = [(512, 520)] * 40 + [(96, 130)] * 40 + [(530, 600)] * 3
+    host = [inputs.low_rank_plus_noise(np.random.default_rng(j % 2), m, n, [1.0, 0.3], 0.02) for j, (m, n) in enumerate(shapes)]
+    mats = [dev(g) for g in host]
+    ids = [7 + j % 2 for j in range(len(shapes))]
+    many = binding.atomo_encode_svd(ctx(), mats, 3.0, 1, 0, stream_ids=ids)
+    assert ctx().status()[0] == 0
+    for j in (0, 1, 39, 40, 79, 80, 82):
+        one = binding.atomo_encode_svd(ctx(), [mats[j]], 3.0, 1, ids[j])[0].to_host()
+        got = many[j].to_host()
+        assert got["count"] == one["count"] and all(np.array_equal(got[k], one[k]) for k in ("idx", "w", "U", "V")), j
+    assert ctx().status()[0] == 0
+
+
+def test_a_training_loop_enqueues_the_direct_encode_alone_until_it_falls_short():
+    shape = (200, 260)
+    rng = np.random.default_rng(0)
+    easy = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.5], 0.02)
+    low = (rng.standard_normal((shape[0], 50)) @ rng.standard_normal((50, shape[1]))).astype(np.float32)
+    want = encode([easy], 3.0, 9)[0][0].to_host()
+    for _ in range(3):
+        msgs, per, status, _ = encode([easy], 3.0, 9, adaptive=1)
+        got = msgs[0].to_host()
+        assert status == 0 and all(np.array_equal(got[k], want[k]) for k in ("idx", "w", "U", "V"))
+    msgs, per, status, _ = encode([low], 3.0, 9, adaptive=1)
+    assert status == binding.ATOMO_ENOCONV
+    check_svd_message_against_matrix(low.astype(np.float64), msgs[0].to_host(), *per[0])
+    msgs, per, status, _ = encode([low], 3.0, 9, adaptive=1)
+    assert status == 0 and route() != [DIRECT]
