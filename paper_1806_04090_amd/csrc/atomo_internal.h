@@ -60,6 +60,7 @@ struct atomo_ctx {
     atomo::SweepHint hints[4];
     int hint_next = 0;
     uint64_t hint_seq = 0;
+    bool direct_lds = false;       // direct::allow_lds has been called for this context's device
     size_t rowgram_lds = 0;        // dynamic LDS that svd_rowgram has been allowed on this context's device
     // Descriptor tables of the last SVD encode (at the start of the workspace) and of the last SVD decode (in a block
     // of their own): a training loop passes the same layer set and buffers step after step, so a call whose tables

@@ -1459,6 +1459,10 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side2, ctx->ev_fork, 0));
     }
     if (any_direct) {
+        if (!ctx->direct_lds) {
+            ATOMO_HIP(ctx, direct::allow_lds());
+            ctx->direct_lds = true;
+        }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, stream);
         direct::launch(plan.direct, dt, s, seed, direct_only, hint_from_direct && hint ? hint->dev : nullptr, ctx->d_flags, stream);
     }

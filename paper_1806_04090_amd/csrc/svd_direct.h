@@ -31,9 +31,9 @@ struct DirectMat {
     double* C;                       // [N][N] Gram matrix, both triangles
     double* refl;                    // [N][N] row k: the Householder vector of step k (entries from 64 (k / 64) on)
     double* tau;                     // [N]
-    double* dg;                      // [N] diagonal of the tridiagonal matrix, scaled
-    double* od;                      // [N] off-diagonal: od[k] couples k and k + 1
-    double* od2;                     // [N] its square, kept above OD2_MIN
+    double2* td;                     // [N] tridiagonal matrix, scaled: squared coupling to the entry before (kept above
+                                     //   OD2_MIN), diagonal; (0, 2) in the padding
+    double* od;                      // [N] couplings: od[k] between k and k + 1
     double* fact;                    // [N / 16][16][16] triangular factors of the blocks of 16 reflectors
     double* lam;                     // [r] eigenvalues, descending, scaled
     double* u;                       // [capacity][r] kept vectors of the shorter side
@@ -61,6 +61,8 @@ struct DirectPlan {
     size_t n_work() const { return gram.size() + tiles.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
 };
 
+// Lets the kernels have more LDS than a launch gets by default; once per device.
+hipError_t allow_lds();
 // Lays out one matrix (base of `carve` null: sizes only) and appends its work; false if the matrix is not for this path.
 bool eligible(int r);
 void plan_matrix(Carver& carve, DirectMat& m);

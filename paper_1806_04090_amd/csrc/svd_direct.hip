@@ -22,7 +22,9 @@ namespace direct {
 
 using svd::Work;
 typedef unsigned long long u64;
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+using svd::floatx4;
 
 namespace {
 
@@ -38,6 +40,13 @@ constexpr u64 LAM_MIN_BITS = 0x3CD0000000000000ull;   // 2^-50: anything below i
 constexpr u64 LAM_MAX_BITS = 0x3FF0000000000000ull;   // 1.0: the trace is below it
 constexpr int LAM_STEP_BITS = 52 - LAM_BITS;
 
+// A pointer out of a descriptor as one into global memory: the compiler cannot know that, and a load through a generic
+// pointer waits for the LDS as well.
+template <typename T>
+using Global = T __attribute__((address_space(1)))*;
+template <typename T>
+__device__ inline Global<T> global(T* p) { return (Global<T>)p; }
+
 // ------------------------------------------------------------------------------------------------
 // wave helpers (64 lanes, no LDS)
 // ------------------------------------------------------------------------------------------------
@@ -48,8 +57,8 @@ __device__ inline double mk64(unsigned lo, unsigned hi) { return __longlong_as_d
 template <int CTRL>
 __device__ inline double dpp(double x)
 {
-    const unsigned a = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo32(x), CTRL, 0xf, 0xf, true);
-    const unsigned b = (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi32(x), CTRL, 0xf, 0xf, true);
+    const unsigned a = (unsigned)__builtin_amdgcn_mov_dpp((int)lo32(x), CTRL, 0xf, 0xf, true);
+    const unsigned b = (unsigned)__builtin_amdgcn_mov_dpp((int)hi32(x), CTRL, 0xf, 0xf, true);
     return mk64(a, b);
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
@@ -108,6 +117,27 @@ __device__ inline double lane_value(double x, int lane)
     return mk64((unsigned)__builtin_amdgcn_readlane((int)lo32(x), lane), (unsigned)__builtin_amdgcn_readlane((int)hi32(x), lane));
 }
 
+// Square root and reciprocal of a positive normal number, to the last bits: the hardware's estimates, then Goldschmidt's and
+// Newton's iterations (no scaling, no special cases: half the latency of sqrt() and of a division in a serial chain).
+__device__ inline double root(double x)
+{
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = 0.5 * r;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = fma(-h, g, 0.5);
+        g = fma(g, e, g);
+        h = fma(h, e, h);
+    }
+    return fma(fma(-g, g, x), h, g);
+}
+__device__ inline double reciprocal(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Gram matrix: partial sums of one 64 x 64 tile over one chunk of columns of A
 // ------------------------------------------------------------------------------------------------
@@ -117,7 +147,7 @@ constexpr int GLD = GK + 4;      // row stride in LDS: 16 rows x 4 consecutive c
 // One row of A per lane group: loads the 64 x 32 piece (rows row0.., columns c0..) into registers / LDS.
 // Rows before the padding and columns past c_end are zero.
 struct GramLoader {
-    const float* G;
+    Global<const float> G;
     long long ldg;
     int transposed, r;
     __device__ inline void fetch(float (&v)[8], int row0, int c0, int c_end, int tid) const
@@ -125,10 +155,14 @@ struct GramLoader {
         if (!transposed) {
             // thread: row tid / 4, eight columns from 8 (tid mod 4)
             const int row = row0 + (tid >> 2), c = c0 + 8 * (tid & 3);
-            const float* g = G + (long long)row * ldg + c;
+            const Global<const float> g = G + (long long)row * ldg + c;
             if (row >= 0 && c + 8 <= c_end && ((((size_t)g) & 15) == 0)) {
-                *(float4*)&v[0] = *(const float4*)g;
-                *(float4*)&v[4] = *(const float4*)(g + 4);
+                const floatx4 x = *(Global<const floatx4>)g, y = *(Global<const floatx4>)(g + 4);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v[k] = x[k];
+                    v[4 + k] = y[k];
+                }
             } else {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] = row >= 0 && c + k < c_end ? g[k] : 0.0f;
@@ -136,7 +170,7 @@ struct GramLoader {
         } else {
             // thread: row tid mod 64, columns tid / 64 + 4 k
             const int row = row0 + (tid & 63), c = c0 + (tid >> 6);
-            const float* g = G + (long long)c * ldg + row;
+            const Global<const float> g = G + (long long)c * ldg + row;
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = row >= 0 && c + 4 * k < c_end ? g[(long long)(4 * k) * ldg] : 0.0f;
         }
@@ -164,7 +198,7 @@ __global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const 
     const int ti = wk.a, tj = wk.b, chunk = wk.c;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
     const int qi = (wave >> 1) * 32, qj = (wave & 1) * 32;
-    const GramLoader ld{m.G, m.ldg, m.transposed, m.r};
+    const GramLoader ld{global(m.G), m.ldg, m.transposed, m.r};
     const int rowa = ti * TILE - m.pad, rowb = tj * TILE - m.pad;
     const int c0 = chunk * m.kchunk, c1 = min(m.M, c0 + m.kchunk);
     const bool same = ti == tj;
@@ -207,7 +241,7 @@ __global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const 
         }
     }
     const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
-    double* out = m.part + ((size_t)chunk * ntiles + tile) * (TILE * TILE);
+    const Global<double> out = global(m.part) + ((size_t)chunk * ntiles + tile) * (TILE * TILE);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -225,7 +259,8 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
     const DirectMat& m = mats[wk.mat];
     const int ti = wk.a, tj = wk.b, tid = threadIdx.x, N = m.nt * TILE;
     const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
-    const double* in = m.part + (size_t)tile * (TILE * TILE);
+    const Global<const double> in = global((const double*)m.part) + (size_t)tile * (TILE * TILE);
+    const Global<double> C = global(m.C);
     double sum[16];
 #pragma unroll
     for (int p = 0; p < 16; ++p) sum[p] = 0.0;
@@ -236,7 +271,7 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
 #pragma unroll
     for (int p = 0; p < 16; ++p) {
         const int i = (tid >> 6) + 4 * p, j = tid & 63;
-        m.C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
+        C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
         t[i][j] = sum[p];
     }
     if (ti != tj) {
@@ -244,13 +279,18 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             const int i = (tid >> 6) + 4 * p, j = tid & 63;
-            m.C[(size_t)(tj * TILE + i) * N + ti * TILE + j] = t[j][i];
+            C[(size_t)(tj * TILE + i) * N + ti * TILE + j] = t[j][i];
         }
     }
     if (ti == 0 && tj == 0) {
         if (tid < DS_WORDS) m.st[tid] = 0;
         if (tid < 64) m.xid[tid] = 0;
         for (int i = tid; i < 4 * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
+        if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
+        if (tid == m.pad) m.td[tid].x = 0.0;
+        // rows of the reflectors' blocks that are no step
+        for (int i = tid; i < (m.pad & 15) * N; i += 256) m.refl[(size_t)(m.pad & ~15) * N + i] = 0.0;
+        for (int i = tid; i < 2 * N; i += 256) m.refl[(size_t)(N - 2) * N + i] = 0.0;
     }
 }
 
@@ -259,23 +299,30 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
 // ------------------------------------------------------------------------------------------------
 // Step k: x = column k of the current matrix, v the Householder vector that maps x[k + 1 ..] to a multiple of the first
 // unit vector, p = A v, w = tau p - (tau^2 / 2)(v^T p) v, A <- A - v w^T - w v^T.
-struct Step {
-    double tau, beta, v0;
-};
-__device__ inline Step householder(double alpha, double sig2)
+// beta, the entry that remains, and v_{k+1} = alpha - beta; tau = 2 / v^T v.  (A column of zeros: the floor under the
+// root makes v a multiple of the first unit vector and the step a change of sign.  The trace is about 1.)
+__device__ inline void householder(double alpha, double sig2, double& beta, double& v0)
 {
-    Step s;
-    if (!(sig2 > 0.0)) {
-        s.tau = 0.0;
-        s.beta = alpha;
-        s.v0 = 0.0;
-    } else {
-        s.beta = -copysign(sqrt(fma(alpha, alpha, sig2)), alpha);
-        s.v0 = alpha - s.beta;
-        s.tau = -1.0 / (s.beta * s.v0);
-    }
-    return s;
+    beta = -copysign(root(fma(alpha, alpha, fmax(sig2, 1e-280))), alpha);
+    v0 = alpha - beta;
 }
+__device__ inline double householder_tau(double sig2, double v0) { return 2.0 * reciprocal(fma(v0, v0, sig2)); }
+
+// Where the steps are kept.
+struct StepStore {
+    Global<double> refl, tau, td, od;
+    int N;
+    __device__ inline StepStore(const DirectMat& m)
+        : refl(global(m.refl)), tau(global(m.tau)), td(global((double*)m.td)), od(global(m.od)), N(m.nt * TILE) {}
+    // entry k of the tridiagonal matrix and its coupling to entry k + 1
+    __device__ inline void put(int k, double t, double d, double beta) const
+    {
+        tau[k] = t;
+        td[2 * k + 1] = d;
+        od[k] = beta;
+        td[2 * k + 2] = fmax(beta * beta, OD2_MIN);
+    }
+};
 
 // What every wave works out for itself before the first step: the scale of the matrix (a power of four that brings the
 // trace under 1) and how many of its rows are zero.
@@ -288,7 +335,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int i = lane + 64 * c - off;
-        const double d = i >= 0 ? m.C[(size_t)i * N + i] : 0.0;
+        const double d = i >= 0 ? global(m.C)[(size_t)i * N + i] : 0.0;
         tr += d;
         zeros += __popcll(__ballot(i >= m.pad && d == 0.0));
     }
@@ -304,7 +351,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // Groups of 16 or 32 workgroups (matrices of more than 128 rows): every wave owns R rows of the matrix in registers (lane l:
 // columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all waves
 // the same bits; one exchange per step: every wave publishes the entries of p of its rows, the owner of row k + 1
-// that row (column k + 1 of the matrix before the step), and every wave reads all of both.
+// that row (column k + 1 of the matrix before the step), and every workgroup reads all of both, a quarter per wave.
 // An entry is one 8-byte store whose two lowest mantissa bits carry the step number mod 4: a reader knows from the value
 // that it is the one of this step, no flag and no second round trip.  Two slots by step parity: a wave that publishes
 // step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more.
@@ -313,23 +360,59 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // Bound: the chain of steps.  512 rows on 64 waves: TRI_MEASURED
 template <int C, int R, int QW>
 struct Tri {
-    static constexpr int CN = 64 * C, W = 64 * QW;
+    static constexpr int CN = 64 * C, W = 64 * QW, OWN = (C + 3) / 4;
     double a[R][C];
-    double x[C];
-    const DirectMat* m;
-    u64* slots;
-    int lane, w, wl, q, off, N, k_first;
+    double x[C], v[C], wv[C];        // column k; the last step's vectors, which the rows have still to be updated with
+    Global<u64> slots;
+    double2 (*shared)[CN];           // [2][CN] by step parity: p and column k + 1
+    int lane, wave, w, wl, q, off, k_first, spin_limit;
     bool local;
 
-    __device__ inline void put(u64* p, u64 v) const
+    template <bool LOCAL>
+    static __device__ inline void put(Global<u64> p, double value, u64 tag)
     {
-        if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u64 x = ((u64)__double_as_longlong(value) & ~3ull) | tag;
+        if (LOCAL) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // column k + 1 of the matrix, in row slot T of this wave
+    template <int P, int T>
+    __device__ inline void put_row(Global<u64> slot, u64 tag) const
+    {
+        if (local) {
+#pragma unroll
+            for (int c = P; c < C; ++c) put<true>(slot + lane + 64 * c, a[T][c], tag);
+        } else {
+#pragma unroll
+            for (int c = P; c < C; ++c) put<false>(slot + lane + 64 * c, a[T][c], tag);
+        }
+    }
+    // entry of row slot t of a vector whose chunks before P are finished (0 there)
+    template <int P, int T>
+    __device__ inline double own(const double (&vec)[C]) const
+    {
+        if constexpr (QW == 1) {
+            return lane_value(vec[T], wl);
+        } else {
+            constexpr int c0 = 2 * T >= P ? 2 * T : 2 * T + 1;
+            if (q == 0) return 2 * T >= P ? lane_value(vec[c0], wl) : 0.0;
+            return lane_value(vec[2 * T + 1], wl);
+        }
+    }
+    template <int P, int T>
+    __device__ inline void update()
+    {
+        if constexpr (T < R) {
+            const double vr = own<P, T>(v), wr = own<P, T>(wv);
+#pragma unroll
+            for (int c = P; c < C; ++c) a[T][c] = fma(-wr, v[c], fma(-vr, wv[c], a[T][c]));
+            update<P, T + 1>();
+        }
     }
 
     // steps k of [64 P, 64 (P + 1)): chunks of columns before P are finished
     template <int P>
-    __device__ inline bool phase(int& k)
+    __device__ inline void phase(int& k, const StepStore& store)
     {
         constexpr int T0 = P / QW;                               // row slots before T0 are finished
         constexpr int PN = P + 1 < C ? P + 1 : P;
@@ -337,46 +420,31 @@ struct Tri {
         for (; k < k_end; ++k) {
             const int k1 = k + 1, l1 = k1 & 63;
             const bool next_chunk = P + 1 < C && l1 == 0;        // row k + 1 is the first of chunk P + 1
-            const double alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
             double sq = 0.0;
 #pragma unroll
             for (int c = P; c < C; ++c) {
-                const double y = lane + 64 * c > k1 ? x[c] : 0.0;
+                const double y = c > PN || lane + 64 * c > k1 ? x[c] : 0.0;
                 sq = fma(y, y, sq);
             }
-            const Step s = householder(alpha, wave_sum(sq));
-            double v[C];
+            const double sig2 = wave_sum(sq), alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
+            update<P, T0>();                                     // (fills the latency of the sum and of the root)
+            double beta, v0;
+            householder(alpha, sig2, beta, v0);
 #pragma unroll
             for (int c = P; c < C; ++c) {
                 const int i = lane + 64 * c;
-                v[c] = i > k1 ? (s.tau != 0.0 ? x[c] : 0.0) : i == k1 ? s.v0 : 0.0;
-            }
-            if (w == (k & (W - 1))) {                            // one wave keeps the step for the way back
-                const int kk = k - off;
-#pragma unroll
-                for (int c = P; c < C; ++c) m->refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
-                const double dk = lane_value(x[P], k & 63);
-                if (lane == 0) {
-                    m->tau[kk] = s.tau;
-                    m->dg[kk] = dk;
-                    m->od[kk] = s.beta;
-                    m->od2[kk] = fmax(s.beta * s.beta, OD2_MIN);
-                }
+                v[c] = c > PN || i > k1 ? x[c] : i == k1 ? v0 : 0.0;
             }
             const unsigned step = (unsigned)(k - k_first + 1);   // (from 1: the cleared slots carry tag 0)
             const u64 tag = step & 3;
-            u64* slot_p = slots + (step & 1) * (2 * CN);
-            u64* slot_c = slot_p + CN;
+            const Global<u64> slot_p = slots + (step & 1) * (2 * CN);
+            const Global<u64> slot_c = slot_p + CN;
             // column k + 1 of the matrix, from the wave that owns that row
             if (wl == l1) {
                 if (!next_chunk) {
-                    if (q == P % QW) {
-#pragma unroll
-                        for (int c = P; c < C; ++c) put(slot_c + lane + 64 * c, ((u64)__double_as_longlong(a[P / QW][c]) & ~3ull) | tag);
-                    }
+                    if (q == P % QW) put_row<P, P / QW>(slot_c, tag);
                 } else if (q == PN % QW) {
-#pragma unroll
-                    for (int c = P; c < C; ++c) put(slot_c + lane + 64 * c, ((u64)__double_as_longlong(a[PN / QW][c]) & ~3ull) | tag);
+                    put_row<P, PN / QW>(slot_c, tag);
                 }
             }
             {
@@ -390,88 +458,96 @@ struct Tri {
                 }
                 const double p = wave_sums<R - T0>(part, lane);
                 const int t = T0 + sum_slot(lane);
-                if ((lane & 7) == 0 && t < R) put(slot_p + w + W * t, ((u64)__double_as_longlong(p) & ~3ull) | tag);
+                if ((lane & 7) == 0 && t < R) {
+                    if (local) put<true>(slot_p + w + W * t, p, tag);
+                    else put<false>(slot_p + w + W * t, p, tag);
+                }
             }
-            u64 pu[C], cu[C];
+            const double tau = householder_tau(sig2, v0);
+            if (w == (k & (W - 1))) {                            // one wave keeps the step for the way back
+                const int kk = k - off;
+                const Global<double> row = store.refl + (size_t)kk * store.N + lane - off;
+#pragma unroll
+                for (int c = P; c < C; ++c) row[64 * c] = v[c];
+                // (chunks are read in pairs: the finished half of one has to hold zeros)
+                if constexpr (P > 0) {
+                    if ((P - (off >> 6)) & 1) row[64 * (P - 1)] = 0.0;
+                }
+                const double dk = lane_value(x[P], k & 63);
+                if (lane == 0) store.put(kk, tau, dk, beta);
+            }
+            // this wave's chunks of p and of the column (one of a finished chunk: any other), then the workgroup's
+            constexpr int J0 = P / 4;
+            int at[OWN - J0];
+            u64 pu[OWN - J0], cu[OWN - J0];
+#pragma unroll
+            for (int j = J0; j < OWN; ++j) at[j - J0] = lane + 64 * min(max(wave + 4 * j, P), C - 1);
             int spins = 0;
             while (true) {
-                bool ok = true;
 #pragma unroll
-                for (int c = P; c < C; ++c) {
-                    pu[c] = __hip_atomic_load(slot_p + lane + 64 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    cu[c] = __hip_atomic_load(slot_c + lane + 64 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int j = 0; j < OWN - J0; ++j) {
+                    pu[j] = __hip_atomic_load(slot_p + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    cu[j] = __hip_atomic_load(slot_c + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
+                unsigned other = 0;
 #pragma unroll
-                for (int c = P; c < C; ++c) ok = ok && (pu[c] & 3) == tag && (cu[c] & 3) == tag;
-                if (__all(ok)) break;
-                if (++spins > SPIN_STEP) return false;
+                for (int j = 0; j < OWN - J0; ++j) other |= ((unsigned)pu[j] ^ (unsigned)tag) | ((unsigned)cu[j] ^ (unsigned)tag);
+                if (__all((other & 3u) == 0u)) break;
+                if (++spins > spin_limit) {                      // (once: the steps after it wait for nothing)
+                    spin_limit = 0;
+                    break;
+                }
             }
+            double2* sh = shared[step & 1];
+#pragma unroll
+            for (int j = 0; j < OWN - J0; ++j)
+                sh[at[j]] = make_double2(__longlong_as_double((long long)(pu[j] & ~3ull)),
+                                         __longlong_as_double((long long)(cu[j] & ~3ull)));
+            __syncthreads();
             double p[C], gamma = 0.0;
 #pragma unroll
             for (int c = P; c < C; ++c) {
-                p[c] = __longlong_as_double((long long)(pu[c] & ~3ull));
-                if (c == P || c == PN) p[c] = lane + 64 * c > k ? p[c] : 0.0;
+                const double2 pc = sh[lane + 64 * c];
+                p[c] = c <= PN && lane + 64 * c <= k ? 0.0 : pc.x;
+                x[c] = pc.y;
                 gamma = fma(v[c], p[c], gamma);
             }
-            gamma = wave_sum(gamma) * (0.5 * s.tau * s.tau);
-            double wv[C];
+            gamma = wave_sum(gamma) * tau * (0.5 * tau);
 #pragma unroll
-            for (int c = P; c < C; ++c) wv[c] = fma(-gamma, v[c], s.tau * p[c]);
+            for (int c = P; c < C; ++c) wv[c] = fma(-gamma, v[c], tau * p[c]);
             const double wk1 = lane_value(next_chunk ? wv[PN] : wv[P], l1);
 #pragma unroll
-            for (int c = P; c < C; ++c) {
-                const double cc = __longlong_as_double((long long)(cu[c] & ~3ull));
-                x[c] = fma(-wv[c], s.v0, fma(-v[c], wk1, cc));
-            }
-#pragma unroll
-            for (int t = T0; t < R; ++t) {
-                double vr, wr;
-                if constexpr (QW == 1) {
-                    vr = lane_value(v[t], wl);
-                    wr = lane_value(wv[t], wl);
-                } else {
-                    vr = wr = 0.0;
-                    if (q == 0) {
-                        if constexpr (2 * (T0 < R ? 1 : 1) > 0) {
-                            if (2 * t >= P) { vr = lane_value(v[2 * t >= P ? 2 * t : P], wl); wr = lane_value(wv[2 * t >= P ? 2 * t : P], wl); }
-                        }
-                    } else {
-                        vr = lane_value(v[2 * t + 1], wl);
-                        wr = lane_value(wv[2 * t + 1], wl);
-                    }
-                }
-#pragma unroll
-                for (int c = P; c < C; ++c) a[t][c] = fma(-wr, v[c], fma(-vr, wv[c], a[t][c]));
-            }
+            for (int c = P; c < C; ++c) x[c] = fma(-wv[c], v0, fma(-v[c], wk1, x[c]));
         }
-        return true;
     }
 
     template <int P>
-    __device__ inline bool phases(int& k)
+    __device__ inline void phases(int& k, const StepStore& store)
     {
-        if (!phase<P>(k)) return false;
-        if constexpr (P + 1 < C) return phases<P + 1>(k);
-        return true;
+        phase<P>(k, store);
+        if constexpr (P + 1 < C) phases<P + 1>(k, store);
     }
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
     static constexpr long long SPIN_START = 200000000ll;         // 2 s of the 100 MHz clock for all workgroups to have started
 
     // false: a wait hit its bound
-    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs)
+    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs, double2* lds)
     {
-        m = &mm;
+        const StepStore store(mm);
+        const int N = store.N;
+        spin_limit = SPIN_STEP;
+        shared = (double2(*)[CN])lds;
         lane = threadIdx.x & 63;
-        w = member * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        w = member * 4 + wave;
         wl = w & 63;
         q = w >> 6;
-        N = mm.nt * TILE;
         off = CN - N;
-        slots = mm.xch;
+        slots = global(mm.xch);
         // which die: every workgroup says so, all wait for all
         const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u) + 1;
-        if (threadIdx.x == 0) __hip_atomic_store(mm.xid + member, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) __hip_atomic_store(global(mm.xid) + member, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int expo, zeros;
         const double scale = scale_of<C>(mm, off, lane, expo, zeros);
 #pragma unroll
@@ -480,7 +556,7 @@ struct Tri {
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const int j = lane + 64 * c - off;
-                a[t][c] = i >= 0 && j >= 0 ? scale * mm.C[(size_t)i * N + j] : 0.0;
+                a[t][c] = i >= 0 && j >= 0 ? scale * global(mm.C)[(size_t)i * N + j] : 0.0;
             }
         }
         int k = off + mm.pad;
@@ -488,12 +564,13 @@ struct Tri {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int j = lane + 64 * c - off;
-            x[c] = j >= 0 ? scale * mm.C[(size_t)mm.pad * N + j] : 0.0;
+            x[c] = j >= 0 ? scale * global(mm.C)[(size_t)mm.pad * N + j] : 0.0;
+            v[c] = wv[c] = 0.0;
         }
         {
             const long long t0 = wall_clock64();
             while (true) {
-                const int id = lane < n_wgs ? __hip_atomic_load(mm.xid + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcc;
+                const int id = lane < n_wgs ? __hip_atomic_load(global(mm.xid) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcc;
                 if (__all(id != 0)) {
                     local = __all(id == xcc);
                     break;
@@ -502,36 +579,37 @@ struct Tri {
                 __builtin_amdgcn_s_sleep(4);
             }
         }
-        if (!phases<0>(k)) return false;
+        phases<0>(k, store);
+        update<C - 1, R - 1>();
         // what is left: the last 2 x 2 block
         if (w == 0) {
             const double d = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63);
             if (lane == 0) {
-                mm.dg[N - 2] = d;
-                mm.od[N - 2] = e;
-                mm.od2[N - 2] = fmax(e * e, OD2_MIN);
-                mm.tau[N - 2] = 0.0;
+                store.put(N - 2, 0.0, d, e);
                 mm.st[DS_EXP] = expo;
                 mm.st[DS_ZERO_ROWS] = zeros;
             }
         }
         if (wl == 63 && q == (C - 1) % QW) {
             const double d = lane_value(a[R - 1][C - 1], 63);
-            if (lane == 0) mm.dg[N - 1] = d;
+            if (lane == 0) store.td[2 * N - 1] = d;
         }
-        return true;
+        return spin_limit != 0;
     }
 };
 
 // Up to 128 rows: one workgroup, no exchange through memory.  Lane l holds rows l (and l + 64), wave w the columns w, w + 4, ..;
 // the products of the four waves are added up through LDS, one barrier per step.
 template <int C>
-__device__ inline void tri_small(const DirectMat& m)
+__device__ inline void tri_small(const DirectMat& m, double* lds)
 {
     constexpr int CN = 64 * C, NC = 16 * C;                      // columns per wave
-    __shared__ double part[2][4][CN], col[2][CN];
+    static_assert(10 * CN <= 4 * MAX_R, "the workgroup's LDS");
+    double(*part)[4][CN] = (double(*)[4][CN])lds;                // [2][4][CN] by step parity
+    double(*col)[CN] = (double(*)[CN])(lds + 8 * CN);            // [2][CN]
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = m.nt * TILE, off = CN - N;
+    const StepStore store(m);
+    const int N = store.N, off = CN - N;
     int expo, zeros;
     const double scale = scale_of<C>(m, off, lane, expo, zeros);
     double a[NC][C], x[C];
@@ -541,13 +619,13 @@ __device__ inline void tri_small(const DirectMat& m)
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int i = lane + 64 * c - off;
-            a[t][c] = i >= 0 && j >= 0 ? scale * m.C[(size_t)j * N + i] : 0.0;
+            a[t][c] = i >= 0 && j >= 0 ? scale * global(m.C)[(size_t)j * N + i] : 0.0;
         }
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const int j = lane + 64 * c - off;
-        x[c] = j >= 0 ? scale * m.C[(size_t)m.pad * N + j] : 0.0;
+        x[c] = j >= 0 ? scale * global(m.C)[(size_t)m.pad * N + j] : 0.0;
     }
     for (int k = off + m.pad; k < CN - 2; ++k) {
         const int k1 = k + 1, l1 = k1 & 63, c1 = k1 >> 6;
@@ -558,25 +636,23 @@ __device__ inline void tri_small(const DirectMat& m)
             const double y = lane + 64 * c > k1 ? x[c] : 0.0;
             sq = fma(y, y, sq);
         }
-        const Step s = householder(alpha, wave_sum(sq));
+        double beta, v0;
+        const double sig2 = wave_sum(sq);
+        householder(alpha, sig2, beta, v0);
         double v[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int i = lane + 64 * c;
-            v[c] = i > k1 ? (s.tau != 0.0 ? x[c] : 0.0) : i == k1 ? s.v0 : 0.0;
+            v[c] = i > k1 ? x[c] : i == k1 ? v0 : 0.0;
         }
+        const double tau = householder_tau(sig2, v0);
         if (w == (k & 3)) {
             const int kk = k - off;
             const double dk = lane_value(C > 1 && k >= 64 ? x[C - 1] : x[0], k & 63);
 #pragma unroll
             for (int c = 0; c < C; ++c)
-                if (lane + 64 * c >= off) m.refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
-            if (lane == 0) {
-                m.tau[kk] = s.tau;
-                m.dg[kk] = dk;
-                m.od[kk] = s.beta;
-                m.od2[kk] = fmax(s.beta * s.beta, OD2_MIN);
-            }
+                if (lane + 64 * c >= off) store.refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
+            if (lane == 0) store.put(kk, tau, dk, beta);
         }
         double vj[NC], sum[C];
 #pragma unroll
@@ -604,13 +680,13 @@ __device__ inline void tri_small(const DirectMat& m)
             p[c] = i > k ? p[c] : 0.0;
             gamma = fma(v[c], p[c], gamma);
         }
-        gamma = wave_sum(gamma) * (0.5 * s.tau * s.tau);
+        gamma = wave_sum(gamma) * tau * (0.5 * tau);
         double wv[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) wv[c] = fma(-gamma, v[c], s.tau * p[c]);
+        for (int c = 0; c < C; ++c) wv[c] = fma(-gamma, v[c], tau * p[c]);
         const double wk1 = lane_value(C > 1 && c1 ? wv[C - 1] : wv[0], l1);
 #pragma unroll
-        for (int c = 0; c < C; ++c) x[c] = fma(-wv[c], s.v0, fma(-v[c], wk1, cl[lane + 64 * c]));
+        for (int c = 0; c < C; ++c) x[c] = fma(-wv[c], v0, fma(-v[c], wk1, cl[lane + 64 * c]));
 #pragma unroll
         for (int t = 0; t < NC; ++t) {
             const double wj = lane_value(wv[t / 16], w + 4 * (t & 15));
@@ -621,11 +697,8 @@ __device__ inline void tri_small(const DirectMat& m)
     if (w == 3) {                                                // (the wave of the last column)
         const double d2 = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63), d1 = lane_value(a[NC - 1][C - 1], 63);
         if (lane == 0) {
-            m.dg[N - 2] = d2;
-            m.dg[N - 1] = d1;
-            m.od[N - 2] = e;
-            m.od2[N - 2] = fmax(e * e, OD2_MIN);
-            m.tau[N - 2] = 0.0;
+            store.put(N - 2, 0.0, d2, e);
+            store.td[2 * N - 1] = d1;
             m.st[DS_EXP] = expo;
             m.st[DS_ZERO_ROWS] = zeros;
         }
@@ -635,16 +708,17 @@ __device__ inline void tri_small(const DirectMat& m)
 // work: matrix (below 0: nothing), member of the group, workgroups of the group.
 __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work)
 {
+    __shared__ double2 lds[2 * MAX_R];
     const Work wk = work[blockIdx.x];
     if (wk.mat < 0) return;
     const DirectMat& m = mats[wk.mat];
     bool ok = true;
     switch (m.cls) {
-        case CLS_64: tri_small<1>(m); break;
-        case CLS_128: tri_small<2>(m); break;
-        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b); } break;
-        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b); } break;
-        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b); } break;
+        case CLS_64: tri_small<1>(m, (double*)lds); break;
+        case CLS_128: tri_small<2>(m, (double*)lds); break;
+        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b, lds); } break;
+        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b, lds); } break;
+        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b, lds); } break;
     }
     if (!ok && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
 }
@@ -664,13 +738,13 @@ __device__ inline void block_factor(const DirectMat& m, int b)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
     const int N = m.nt * TILE, k0 = b * RB, k = k0 + l16;
     const bool live = k >= m.pad && k < N - 2;
-    const double* row = m.refl + (size_t)k * N;
+    const Global<const double> row = global((const double*)m.refl) + (size_t)k * N;
     doublex4 acc = {0.0, 0.0, 0.0, 0.0};
     for (int c = (k0 & ~63) + 16 * wave; c < N; c += 64) {
-        double2 v[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+        doublex2 v[2] = {doublex2{0.0, 0.0}, doublex2{0.0, 0.0}};
         if (live) {
-            v[0] = *(const double2*)(row + c + 4 * q);
-            v[1] = *(const double2*)(row + c + 4 * q + 2);
+            v[0] = *(Global<const doublex2>)(row + c + 4 * q);
+            v[1] = *(Global<const doublex2>)(row + c + 4 * q + 2);
         }
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[0].x, v[0].x, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[0].y, v[0].y, acc, 0, 0, 0);
@@ -680,24 +754,21 @@ __device__ inline void block_factor(const DirectMat& m, int b)
 #pragma unroll
     for (int v = 0; v < 4; ++v) gram[wave][4 * v + q][l16] = acc[v];
     if (tid < RB) tau[tid] = live ? m.tau[k] : 0.0;
-    f[tid >> 4][tid & 15] = 0.0;
     __syncthreads();
     gram[0][tid >> 4][tid & 15] = (gram[0][tid >> 4][tid & 15] + gram[1][tid >> 4][tid & 15]) +
                                   (gram[2][tid >> 4][tid & 15] + gram[3][tid >> 4][tid & 15]);
     __syncthreads();
-    if (tid < 64) {                                              // one wave: LDS operations in program order
+    if (tid < RB) {                                              // thread r: row r of F
+        double row_f[RB];
+#pragma unroll
         for (int i = 0; i < RB; ++i) {
-            if (lane < i) {
-                double sum = 0.0;
-                for (int j = lane; j < i; ++j) sum = fma(f[lane][j], gram[0][j][i], sum);
-                f[lane][i] = -tau[i] * sum;
-            } else if (lane == i) {
-                f[i][i] = tau[i];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            double sum = 0.0;
+#pragma unroll
+            for (int j = 0; j < i; ++j) sum = fma(row_f[j], gram[0][j][i], sum);
+            row_f[i] = tid == i ? tau[i] : tid < i ? -tau[i] * sum : 0.0;
         }
+#pragma unroll
+        for (int i = 0; i < RB; ++i) f[tid][i] = row_f[i];
     }
     __syncthreads();
     m.fact[(size_t)b * (RB * RB) + tid] = f[tid >> 4][tid & 15];
@@ -708,51 +779,36 @@ __device__ inline void block_factor(const DirectMat& m, int b)
 // ------------------------------------------------------------------------------------------------
 // How many eigenvalues of T lie below z: sign changes of the characteristic polynomials of the leading blocks,
 // p_{i+1} = (d_i - z) p_i - e_{i-1}^2 p_{i-1} (no division; rescaled by a power of two every eight steps, the squared
-// off-diagonals are kept above 2^-110 so that eight steps stay inside the range).  T comes through scalar loads.
-typedef const double __attribute__((address_space(4)))* scalar_ptr;   // read through the scalar cache, never written here
+// off-diagonals are kept above 2^-110 so that eight steps stay inside the range).  T comes through scalar loads, four
+// entries (e_{i-1}^2, d_i) at a time; the padding in front, (0, 2), leaves the sign as it is.  Four instructions per step.
+typedef unsigned uintx16 __attribute__((ext_vector_type(16)));
+typedef const uintx16 __attribute__((address_space(4)))* scalar_ptr;   // read through the scalar cache, never written here
 
-__device__ inline int sturm_count(scalar_ptr dg, scalar_ptr od2, int n, double z)
+__device__ inline int sturm_count(scalar_ptr t, int n, double z)
 {
     double p0 = 0.0, p1 = 1.0;
-    int count = 0, i = 0;
+    int count = 0;
     unsigned signs = 0;
-    // the entries of the next eight steps are on their way while these eight run
-    double dn[8], en[8];
+    for (int i = 0; i < n; i += 16) {
+        uintx16 e[4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        dn[u] = dg[u];                                           // (n > 32)
-        en[u] = u > 0 ? od2[u - 1] : 0.0;
-    }
-    for (; i + 8 <= n; i += 8) {
-        double d[8], e2[8];
+        for (int u = 0; u < 4; ++u) e[u] = t[i / 4 + u];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            d[u] = dn[u];
-            e2[u] = en[u];
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uintx16& w = e[2 * h + u / 4];
+                const int x = 4 * (u & 3);
+                const double p2 = fma(mk64(w[x + 2], w[x + 3]) - z, p1, -(mk64(w[x], w[x + 1]) * p0));
+                p0 = p1;
+                p1 = p2;
+                signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+            }
+            const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+            p0 = __builtin_amdgcn_ldexp(p0, -ex);
+            p1 = __builtin_amdgcn_ldexp(p1, -ex);
         }
-        const int next = i + 16 <= n ? i + 8 : i;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            dn[u] = dg[next + u];
-            en[u] = od2[next + u - (next > 0)];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double p2 = fma(d[u] - z, p1, -(e2[u] * p0));
-            p0 = p1;
-            p1 = p2;
-            signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
-        }
-        count += __popc((signs ^ (signs >> 1)) & 0xffu);
-        const int e = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-        p0 = __builtin_amdgcn_ldexp(p0, -e);
-        p1 = __builtin_amdgcn_ldexp(p1, -e);
-    }
-    for (; i < n; ++i) {
-        const double p2 = fma(dg[i] - z, p1, -(od2[i - 1] * p0));
-        count += (hi32(p2) ^ hi32(p1)) >> 31;
-        p0 = p1;
-        p1 = p2;
+        count += __popc((signs ^ (signs >> 1)) & 0xffffu);
     }
     return count;
 }
@@ -778,8 +834,9 @@ __global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats,
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
     const int tid = threadIdx.x, lane = tid & 63, n = m.r;
-    const scalar_ptr dg = (scalar_ptr)(u64)(m.dg + m.pad), od2 = (scalar_ptr)(u64)(m.od2 + m.pad);
-    below[tid] = sturm_count(dg, od2, n, cell_start(SPAN * tid));
+    const int first = m.pad & ~15, n_pad = m.nt * TILE - first;
+    const scalar_ptr t = (scalar_ptr)(u64)(m.td + first);
+    below[tid] = sturm_count(t, n_pad, cell_start(SPAN * tid));
     __syncthreads();
     const int l = tid & (lanes - 1), base = lane & ~(lanes - 1);
     const int i = min(wk.a + tid / lanes, n - 1);                // (a group past the end repeats the last one)
@@ -794,9 +851,9 @@ __global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats,
     u64 g0 = SPAN * lo, g1 = zero ? g0 : g0 + SPAN;
     const u64 group = lanes == 64 ? ~0ull : ((1ull << lanes) - 1) << base;
     while (!__all(g1 - g0 <= 1)) {
-        const u64 width = g1 - g0;
-        const u64 z = g0 + width * (unsigned)(l + 1) / (unsigned)(lanes + 1);
-        const int k = __popcll(__ballot(sturm_count(dg, od2, n, cell_start(z)) <= asc) & group);
+        const u64 z = g0 + (g1 - g0) * (unsigned)(l + 1) / (unsigned)(lanes + 1);
+        // points with at most asc eigenvalues below
+        const int k = __popcll(__ballot(sturm_count(t, n_pad, cell_start(z)) <= asc) & group);
         const u64 z_lo = __shfl(z, base + max(k - 1, 0)), z_hi = __shfl(z, base + min(k, lanes - 1));
         if (k > 0) g0 = z_lo;
         if (k < lanes) g1 = z_hi;
@@ -886,100 +943,123 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
 
 // Vectors of the shorter side
 // ------------------------------------------------------------------------------------------------
-// One workgroup of 64 nt threads (or more: the largest matrix of the call) per kept atom.
+// One workgroup of 32 nt threads (a whole number of waves; of the largest matrix of the call) per kept atom.
 //
-// First the eigenvector of T for the eigenvalue next to lam, by a twisted factorisation (wave 0): pivots from the top
-// (lane 0) and from the bottom (lane 1) as quotients of the characteristic polynomials of the leading and of the trailing
-// blocks, twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and a second round
-// starts from there.  Then its image under H, a block of 16 reflectors at a time: thread i owns entry i of the vector
-// and column i of V.  Bound: latency, two chains of n steps per round and N / 16 blocks with one barrier each.
+// First the eigenvector of T for the eigenvalue next to lam, by a twisted factorisation: pivots from the top (wave 0) and
+// from the bottom (wave 1) as quotients of the characteristic polynomials of the leading and of the trailing blocks,
+// twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and a second round starts
+// from there.  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
+// vector and those columns of V.  Bound: latency, two chains of n steps and then N / 16 blocks with one barrier each, whose V comes
+// from memory: two blocks are on their way while one is worked on (64 KB each at 512 rows: with one, a block took 4 us), the
+// factors of all blocks are in LDS before the first.
 // Work: matrix, slot.
-__global__ __launch_bounds__(MAX_R) void direct_vectors(const DirectMat* mats, const Work* work)
+constexpr int VEC_THREADS = VMAX / 2;
+constexpr int FLD = RB + 1;      // row stride of a factor in LDS
+constexpr int VEC_LDS = VMAX * FLD * (int)sizeof(double);
+
+__global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat* mats, const Work* work)
 {
-    __shared__ double2 de[2][VMAX + 8];      // per direction: diagonal and the squared coupling to the step before
-    __shared__ double P[2][VMAX + 8], B[2][VMAX / 8 + 1], e[VMAX], X[VMAX], part[2][VMAX / 64][RB], red[VMAX / 64];
-    __shared__ double s_res;
+    // characteristic polynomials of the leading blocks ([0], in units of index + 1) and of the trailing ones ([1]), every
+    // pair of neighbours in one scale except where `B` holds the first of the pair in the scale of the second
+    extern __shared__ double fact[];
+    __shared__ double2 T[2][VMAX + 8];       // T from the top, padding in front, and from the bottom, padding behind
+    __shared__ double P[2][VMAX + 17], B[2][VMAX / 8 + 2], X[VMAX], part[2][VEC_THREADS / 64][RB], red[VEC_THREADS / 64];
+    __shared__ double s_scale;
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
-    const int slot = wk.a, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = m.r, nw = blockDim.x >> 6;
+    const int slot = wk.a, tid = threadIdx.x, lane = tid & 63, n = m.r, nthr = blockDim.x, nw = nthr >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (slot >= min(*m.count, m.capacity)) return;
-    const int N = m.nt * TILE;
-    // the first block of the way back, on its way from here on
-    int b = (N - 3) / RB;
-    const int col = tid;
-    double vn[RB];
-    auto fetch = [&](int blk) {
-#pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const int k = blk * RB + j;
-            vn[j] = col < N && col >= (k & ~63) && k >= m.pad && k < N - 2 ? m.refl[(size_t)k * N + col] : 0.0;
+    const int N = m.nt * TILE, pad = m.pad;
+    {
+        const Global<const doublex2> in = (Global<const doublex2>)global((const double*)m.fact);
+        for (int i = tid; i < N * RB / 2; i += nthr) {
+            const doublex2 x = in[i];
+            fact[i / 8 * FLD + 2 * (i & 7)] = x.x;
+            fact[i / 8 * FLD + 2 * (i & 7) + 1] = x.y;
         }
-    };
-    fetch(b);
-    for (int i = tid; i < n; i += blockDim.x) {
-        const double d = m.dg[m.pad + i], o = i + 1 < n ? m.od[m.pad + i] : 0.0;
-        e[i] = o;
-        de[0][i].x = d;
-        de[1][n - 1 - i].x = d;
-        de[0][i + 1].y = o * o;
-        de[1][n - 1 - i].y = o * o;
     }
-    if (tid == 0) de[0][0].y = 0.0;
-    if (tid < 16) de[tid >> 3][n + (tid & 7)].x = 0.0;           // (steps past the end, up to a multiple of eight)
-    if (tid < 14) de[tid / 7][n + 1 + tid % 7].y = 0.0;
-    if (tid == 0) de[1][n].y = 0.0;
+    double lam = m.lam[m.idx[slot]];
+    const double good = 1e-14 * m.lam[0];
+    // what wave 0 needs of T: its lane's entries
+    constexpr int PER = VMAX / 64;
+    const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
+    double d[PER], e_up[PER], e_dn[PER];                         // diagonal, coupling to the entry before, to the one after
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = i0 + u;
+        const bool in = wave == 0 && i < i1;
+        d[u] = in ? global((const double*)m.td)[2 * (pad + i) + 1] : 0.0;
+        e_up[u] = in && i > 0 ? global((const double*)m.od)[pad + i - 1] : 0.0;
+        e_dn[u] = in && i + 1 < n ? global((const double*)m.od)[pad + i] : 0.0;
+    }
+    const int first = pad & ~15, n_pad = N - first;
+    for (int i = tid; i < n_pad; i += nthr) {
+        const doublex2 t = ((Global<const doublex2>)global((const double*)m.td))[first + i];
+        T[0][i] = make_double2(t.x, t.y);
+        T[1][n_pad - 1 - i].y = t.y;
+        T[1][n_pad - i].x = t.x;                                 // (the coupling to the entry before comes a step later)
+    }
+    if (tid < 8) {
+        T[0][n_pad + tid] = make_double2(0.0, 2.0);
+        if (tid > 0) T[1][n_pad + tid].x = 0.0;
+        T[1][n_pad + tid].y = 2.0;
+    }
+    if (tid == 0) T[1][0].x = 0.0;
     __syncthreads();
-    double y = 0.0;
-    if (wave == 0) {
-        double lam = m.lam[m.idx[slot]], norm2 = 1.0, res = 0.0;
-        const double good = 1e-14 * m.lam[0];
-        const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
-        for (int round = 0; round < 3; ++round) {
-            if (lane < 2) {
-                double p0 = 0.0, p1 = 1.0;
-                double* out = P[lane];
-                const double2* in = de[lane];
-                out[0] = 1.0;
-                double2 next[8];
+    for (int round = 0; round < 3; ++round) {
+        if (wave < 2 || nw == 1) {
+            // wave 0 the leading blocks, wave 1 the trailing ones (a workgroup of one wave: both)
+            for (int dir = nw == 1 ? 0 : wave; dir < (nw == 1 ? 2 : wave + 1); ++dir) {
+                const double2* t = T[dir];
+                double* out = P[dir];
+                double* bound = B[dir];
+                if (lane == 0) {
+                    double p0 = 0.0, p1 = 1.0;
+                    out[0] = 1.0;
+                    double2 next[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) next[u] = in[u];
-                for (int i = 0; i < n; i += 8) {
-                    double2 now[8];
+                    for (int u = 0; u < 8; ++u) next[u] = t[u];
+                    for (int i = 0; i < n_pad; i += 8) {
+                        double2 now[8];
+                        double step[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) now[u] = next[u];
-                    const int at = i + 8 < n ? i + 8 : i;
+                        for (int u = 0; u < 8; ++u) now[u] = next[u];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) next[u] = in[at + u];
+                        for (int u = 0; u < 8; ++u) next[u] = t[i + 8 + u];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double p2 = fma(now[u].x - lam, p1, -(now[u].y * p0));
-                        p0 = p1;
-                        p1 = p2;
-                        if (u < 7) out[i + u + 1] = p1;
+                        for (int u = 0; u < 8; ++u) {
+                            step[u] = fma(now[u].y - lam, p1, -(now[u].x * p0));
+                            p0 = p1;
+                            p1 = step[u];
+                        }
+                        const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+                        p0 = __builtin_amdgcn_ldexp(p0, -ex);
+                        p1 = __builtin_amdgcn_ldexp(p1, -ex);
+                        step[7] = p1;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) out[i + 1 + u] = step[u];
+                        bound[i >> 3] = p0;
                     }
-                    const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-                    p0 = __builtin_amdgcn_ldexp(p0, -ex);
-                    p1 = __builtin_amdgcn_ldexp(p1, -ex);
-                    B[lane][i >> 3] = p0;
-                    out[i + 8] = p1;
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet
-            auto pivots = [&](int i, double& top, double& bot) {
-                const int j = n - 1 - i;
-                top = P[0][i + 1] / ((i & 7) == 7 ? B[0][i >> 3] : P[0][i]);
-                bot = P[1][j + 1] / ((j & 7) == 7 ? B[1][j >> 3] : P[1][j]);
-                return top + bot - (de[0][i].x - lam);
-            };
-            double best = 1e300, gamma = 0.0;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet with the smallest pivot
+            double top[PER], bot[PER], best = 1e300, gamma = 0.0;
             int at = 0;
-            for (int i = i0; i < i1; ++i) {
-                double top, bot;
-                const double g = pivots(i, top, bot);
-                if (fabs(g) < best) { best = fabs(g); gamma = g; at = i; }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = i0 + u;
+                top[u] = bot[u] = 1.0;
+                if (i < i1) {
+                    const int s = pad - first + i, j = n - 1 - i;    // steps that made them
+                    top[u] = P[0][s + 1] * reciprocal((s & 7) == 7 ? B[0][s >> 3] : P[0][s]);
+                    bot[u] = P[1][j + 1] * reciprocal((j & 7) == 7 ? B[1][j >> 3] : P[1][j]);
+                    const double g = top[u] + bot[u] - (d[u] - lam);
+                    if (fabs(g) < best) { best = fabs(g); gamma = g; at = i; }
+                }
             }
             for (int o = 32; o > 0; o >>= 1) {
                 const double ob = __shfl_xor(best, o), og = __shfl_xor(gamma, o);
@@ -988,59 +1068,83 @@ __global__ __launch_bounds__(MAX_R) void direct_vectors(const DirectMat* mats, c
             }
             // entries from the twist outwards: products of -e_i / top_i downwards and of -e_{i-1} / bottom_i upwards,
             // per lane over its own entries, then over the lanes
-            double up = 1.0, down = 1.0;
-            for (int i = i0; i < i1; ++i) {
-                double top, bot;
-                (void)pivots(i, top, bot);
-                const double f = i < at ? -e[i] / top : i > at ? -e[i - 1] / bot : 1.0;
-                X[i] = f;
-                if (i < at) down *= f; else up *= f;
+            double f[PER], up = 1.0, down = 1.0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = i0 + u;
+                f[u] = 1.0;
+                if (i < i1) {
+                    f[u] = i < at ? -e_dn[u] * reciprocal(top[u]) : i > at ? -e_up[u] * reciprocal(bot[u]) : 1.0;
+                    if (i < at) down *= f[u]; else up *= f[u];
+                }
             }
             double up_before = up, down_after = down;
             for (int o = 1; o < 64; o <<= 1) {
-                const double u = __shfl_up(up_before, o), d = __shfl_down(down_after, o);
-                if (lane >= o) up_before *= u;
-                if (lane + o < 64) down_after *= d;
+                const double x = __shfl_up(up_before, o), y = __shfl_down(down_after, o);
+                if (lane >= o) up_before *= x;
+                if (lane + o < 64) down_after *= y;
             }
             up_before = __shfl_up(up_before, 1);
             down_after = __shfl_down(down_after, 1);
             if (lane == 0) up_before = 1.0;
             if (lane == 63) down_after = 1.0;
             double sq = 0.0, run = up_before;
-            for (int i = max(i0, at); i < i1; ++i) {
-                run *= X[i];
-                X[i] = run;
-                sq = fma(run, run, sq);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = i0 + u;
+                if (i < i1 && i >= at) {
+                    run *= f[u];
+                    X[i] = run;
+                    sq = fma(run, run, sq);
+                }
             }
             run = down_after;
-            for (int i = min(i1, at) - 1; i >= i0; --i) {
-                run *= X[i];
-                X[i] = run;
-                sq = fma(run, run, sq);
+#pragma unroll
+            for (int u = PER - 1; u >= 0; --u) {
+                const int i = i0 + u;
+                if (i < i1 && i < at) {
+                    run *= f[u];
+                    X[i] = run;
+                    sq = fma(run, run, sq);
+                }
             }
-            norm2 = wave_sum(sq);
-            res = fabs(gamma) / sqrt(norm2);                     // |T x - lam x| / |x|
-            if (res <= good) break;
-            if (round < 2) lam += gamma / norm2;
+            const double norm2 = wave_sum(sq), res = fabs(gamma) / sqrt(norm2);    // |T x - lam x| / |x|
+            lam += gamma / norm2;                                // Rayleigh quotient
+            // over: the residual is small enough, or it never will be (the eigenvalue was not separated from its
+            // neighbour, or the factorisation broke down)
+            if (lane == 0) {
+                red[0] = lam;
+                s_scale = res <= good || (round == 2 && res <= 100.0 * good) ? 1.0 / sqrt(norm2) : round == 2 ? -1.0 : 0.0;
+            }
         }
-        // (the eigenvalue was not separated from its neighbour, or the factorisation broke down)
-        if (lane == 0) s_res = res <= 100.0 * good ? 1.0 / sqrt(norm2) : -1.0;
+        __syncthreads();
+        lam = red[0];
+        if (s_scale != 0.0) break;
+        __syncthreads();
     }
-    __syncthreads();
-    const double scale = s_res;
-    if (tid == 0 && !(scale > 0.0)) m.st[DS_ACCEPT] = 0;
-    if (col >= m.pad && col < N) y = X[col - m.pad] * scale;
     // back through H
-    for (; b >= m.pad / RB; --b) {
-        double v[RB], f[RB], prod[RB];
+    const int c0 = 2 * tid;                                      // this thread's entries: c0, c0 + 1
+    struct Block { doublex2 v[RB]; };
+    auto fetch = [&](int blk, Block& at) {
+        if (2 * wave + 1 >= blk * RB / 64) {                     // (uniform: the wave's 128 columns are not all finished)
+            const Global<const double> row = global((const double*)m.refl) + (size_t)max(blk, 0) * RB * N + min(c0, N - 2);
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            v[j] = vn[j];
-            prod[j] = v[j] * y;
+            for (int j = 0; j < RB; ++j) at.v[j] = *(Global<const doublex2>)(row + (size_t)j * N);
+        } else {
+#pragma unroll
+            for (int j = 0; j < RB; ++j) at.v[j] = doublex2{0.0, 0.0};
         }
+    };
+    const double scale = s_scale;
+    if (tid == 0 && !(scale > 0.0)) m.st[DS_ACCEPT] = 0;
+    double y0 = c0 >= pad && c0 < N ? X[c0 - pad] * scale : 0.0;
+    double y1 = c0 + 1 >= pad && c0 < N ? X[c0 + 1 - pad] * scale : 0.0;
+    const int last = (N - 3) / RB, first_block = pad / RB;
+    auto apply = [&](int b, const Block& at) {
+        double prod[RB];
+        const double* f = fact + (size_t)b * (RB * FLD) + (lane & 15) * FLD;
 #pragma unroll
-        for (int j = 0; j < RB; ++j) f[j] = m.fact[(size_t)b * (RB * RB) + (lane & 15) * RB + j];
-        if (b > m.pad / RB) fetch(b - 1);
+        for (int j = 0; j < RB; ++j) prod[j] = fma(at.v[j].x, y0, at.v[j].y * y1);
         const double lo = wave_sums<8>((const double(&)[8])prod[0], lane), hi = wave_sums<8>((const double(&)[8])prod[8], lane);
         double(*pt)[RB] = part[b & 1];
         if ((lane & 7) == 0) {
@@ -1048,27 +1152,54 @@ __global__ __launch_bounds__(MAX_R) void direct_vectors(const DirectMat* mats, c
             pt[wave][8 + sum_slot(lane)] = hi;
         }
         __syncthreads();
-        double sum = 0.0;
-        for (int w = 0; w < nw; ++w) sum += pt[w][lane & 15];    // lane j: the product of vector j with y
+        double sum = 0.0;                                        // lane j: the product of vector j with y
+#pragma unroll
+        for (int w = 0; w < VEC_THREADS / 64; ++w) sum += w < nw ? pt[w][lane & 15] : 0.0;
         double t = 0.0;
 #pragma unroll
         for (int j = 0; j < RB; ++j) t = fma(f[j], lane_value(sum, j), t);
 #pragma unroll
-        for (int j = 0; j < RB; ++j) y = fma(-v[j], lane_value(t, j), y);
+        for (int j = 0; j < RB; ++j) {
+            const double tj = lane_value(t, j);
+            y0 = fma(-at.v[j].x, tj, y0);
+            y1 = fma(-at.v[j].y, tj, y1);
+        }
+        if (c0 >= N) y0 = y1 = 0.0;
+    };
+    {
+        Block a, c, e;
+        fetch(last, a);
+        fetch(last - 1, c);
+        for (int b = last;;) {
+            fetch(b - 2, e);
+            apply(b, a);
+            if (--b < first_block) break;
+            fetch(b - 2, a);
+            apply(b, c);
+            if (--b < first_block) break;
+            fetch(b - 2, c);
+            apply(b, e);
+            if (--b < first_block) break;
+        }
     }
     {
-        const double sq = wave_sum(y * y);
+        const double sq = wave_sum(fma(y0, y0, y1 * y1));
         if (lane == 0) red[wave] = sq;
     }
     __syncthreads();
     double sq = 0.0;
     for (int w = 0; w < nw; ++w) sq += red[w];
-    y /= sqrt(sq);
+    const double inv = 1.0 / sqrt(sq);
     const float fold = m.w || m.transposed ? 1.0f : m.inv[slot];  // folded message: the weight goes into U
-    float* out = m.transposed ? m.V + (size_t)slot * m.cols : m.U + (size_t)slot * m.rows;
-    if (col >= m.pad && col < N) {
-        m.u[(size_t)slot * n + col - m.pad] = y;
-        out[col - m.pad] = (float)y * fold;
+    const Global<float> out = global(m.transposed ? m.V + (size_t)slot * m.cols : m.U + (size_t)slot * m.rows);
+    const Global<double> keep = global(m.u) + (size_t)slot * n;
+    if (c0 >= pad && c0 < N) {
+        keep[c0 - pad] = y0 * inv;
+        out[c0 - pad] = (float)(y0 * inv) * fold;
+    }
+    if (c0 + 1 >= pad && c0 < N) {
+        keep[c0 + 1 - pad] = y1 * inv;
+        out[c0 + 1 - pad] = (float)(y1 * inv) * fold;
     }
 }
 
@@ -1108,13 +1239,14 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
     const int kept = min(*m.count, m.capacity), r = m.r, p0 = wk.a * LONG_COLS;
-    float* out = m.transposed ? m.U : m.V;
+    const Global<const float> G = global(m.G);
+    const Global<float> out = global(m.transposed ? m.U : m.V);
     for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
         const int ns = min(LONG_GROUP, kept - s0);
         __syncthreads();
         for (int i = tid; i < LONG_GROUP * r; i += 512) {
             const int k = i / r, x = i - k * r;
-            us[k][x] = k < ns ? m.u[(size_t)(s0 + k) * r + x] : 0.0;
+            us[k][x] = k < ns ? global(m.u)[(size_t)(s0 + k) * r + x] : 0.0;
         }
         __syncthreads();
         if (!m.transposed) {
@@ -1127,8 +1259,8 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int i = min(i0 + 8 * u, r - 1);
-                    ga[u] = m.G[(long long)i * m.ldg + ca];
-                    gb[u] = m.G[(long long)i * m.ldg + cb];
+                    ga[u] = G[(long long)i * m.ldg + ca];
+                    gb[u] = G[(long long)i * m.ldg + cb];
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
@@ -1159,7 +1291,7 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
 #pragma unroll
                         for (int u = 0; u < 8; ++u) {
                             const int p = min(p0 + 64 * h + wave + 8 * u, m.M - 1);
-                            acc[u] = fma((double)m.G[(long long)p * m.ldg + i], uu, acc[u]);
+                            acc[u] = fma((double)G[(long long)p * m.ldg + i], uu, acc[u]);
                         }
                     }
                     const double sum = wave_sums<8>(acc, lane);
@@ -1192,6 +1324,11 @@ int class_of(int r)
 
 }  // namespace
 
+hipError_t allow_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(direct_vectors), hipFuncAttributeMaxDynamicSharedMemorySize, VEC_LDS);
+}
+
 bool eligible(int r) { return r > svd::THIN_R && r <= MAX_R; }
 
 void plan_matrix(Carver& carve, DirectMat& m)
@@ -1200,9 +1337,9 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.pad = m.nt * TILE - m.r;
     m.cls = class_of(m.r);
     const int ntiles = m.nt * (m.nt + 1) / 2;
-    // About 160 work items of the Gram product per matrix, none under 128 columns, at most 64 partial sums; from the shape
+    // About 320 work items of the Gram product per matrix, none under 128 columns, at most 64 partial sums; from the shape
     // alone, so that the sums do not depend on what else is in the call.
-    const int want = std::max(1, std::min({160 / ntiles, m.M / 128, 64}));
+    const int want = std::max(1, std::min({320 / ntiles, m.M / 128, 64}));
     m.kchunk = (int)align_up((size_t)(m.M + want - 1) / want, GK);
     m.nchunks = (m.M + m.kchunk - 1) / m.kchunk;
     const size_t N = (size_t)m.nt * TILE;
@@ -1210,9 +1347,8 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.C = carve.take<double>(N * N);
     m.refl = carve.take<double>(N * N);
     m.tau = carve.take<double>(N);
-    m.dg = carve.take<double>(N);
+    m.td = carve.take<double2>(N);
     m.od = carve.take<double>(N);
-    m.od2 = carve.take<double>(N);
     m.fact = carve.take<double>(N * RB);
     m.lam = carve.take<double>(m.r);
     m.u = carve.take<double>((size_t)m.capacity * m.r);
@@ -1226,9 +1362,10 @@ void plan_work(DirectPlan& plan)
 {
     size_t eigenvalues = 0;
     for (const DirectMat& m : plan.mats) eigenvalues += (size_t)m.r;
-    // points per eigenvalue and pass of the search: as many as fill the chip about once (1024 waves)
+    // lanes per eigenvalue in the search: as many as one wave on every SIMD has (the search is bound by instruction issue:
+    // with a few more than that, on some SIMDs two waves, it took twice as long)
     plan.eig_lanes = 64;
-    while (plan.eig_lanes > 4 && eigenvalues * plan.eig_lanes > 1536 * 64) plan.eig_lanes /= 2;
+    while (plan.eig_lanes > 4 && eigenvalues * plan.eig_lanes > 1024 * 64) plan.eig_lanes /= 2;
     std::vector<Work> factors;
     std::vector<int> order(plan.mats.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = (int)j;
@@ -1245,6 +1382,9 @@ void plan_work(DirectPlan& plan)
         for (int k = 0; k < m.capacity; ++k) plan.vec.push_back(Work{j, k, 0, 0});
         for (int p = 0; p < (m.M + LONG_COLS - 1) / LONG_COLS; ++p) plan.lng.push_back(Work{j, p, 0, 0});
     }
+    // the longest products first: the last workgroups to start set when the launch ends
+    std::stable_sort(plan.gram.begin(), plan.gram.end(),
+                     [&](const Work& a, const Work& b) { return plan.mats[a.mat].kchunk > plan.mats[b.mat].kchunk; });
     plan.n_eig = plan.eig.size();
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
     // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
@@ -1276,7 +1416,8 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
-    direct_vectors<<<grid(plan.vec), 64u * (unsigned)plan.max_nt, 0, stream>>>(t.mats, t.vec);
+    const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
+    direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
     direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, (int)plan.lng.size(), t.n_mats, finish, hint_out, d_flags);
 }
 
