@@ -26,9 +26,10 @@
  *    staging buffers owned by the context: a call that needs a buffer whose
  *    previous copy (eight uploads ago) has not been executed yet waits for
  *    that copy, and for nothing else.  The SVD encoder and the SVD decoder
- *    skip the upload when a call, on the same stream, describes exactly the
- *    buffers of the call before it (a training loop): the tables hold
- *    addresses and sizes, never data, and the device still has them.
+ *    each keep the four sets of tables used last on the device, and skip the
+ *    upload when a call, on the same stream, describes exactly the buffers of
+ *    one of them (a training loop, or one that takes a few sets of buffers in
+ *    turn): the tables hold addresses and sizes, never data.
  *  - The caller owns every input, output and message buffer.  Inputs are never
  *    modified.  The context owns a device workspace that grows on demand
  *    (growing it allocates, which synchronises the device; atomo_reserve

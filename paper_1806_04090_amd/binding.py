@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes as C
 import math
 import os
+import struct
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
@@ -75,16 +76,15 @@ def lib() -> C.CDLL:
         L.atomo_last_hip_error.argtypes = [vp]
         L.atomo_strerror.argtypes = [C.c_int]
         L.atomo_strerror.restype = C.c_char_p
-        L.atomo_probabilities.argtypes = [vp, vp, C.POINTER(C.c_int64), C.c_int, C.c_double, vp, vp]
-        L.atomo_encode_svd.argtypes = [vp, C.POINTER(atomo_mat), C.c_int, C.c_double, C.c_uint64, C.c_uint64,
-                                       C.POINTER(atomo_svd_options), C.POINTER(atomo_svd_msg), vp, vp, vp]
+        L.atomo_probabilities.argtypes = [vp, vp, vp, C.c_int, C.c_double, vp, vp]
+        L.atomo_encode_svd.argtypes = [vp, vp, C.c_int, C.c_double, C.c_uint64, C.c_uint64,
+                                       C.POINTER(atomo_svd_options), vp, vp, vp, vp]
         L.atomo_encode_entrywise.argtypes = [vp, vp, C.c_double, C.c_uint64, C.c_uint64, C.POINTER(atomo_ew_msg),
                                              vp, vp]
         L.atomo_encode_entrywise_noalloc.argtypes = L.atomo_encode_entrywise.argtypes
         L.atomo_encode_lq.argtypes = [vp, vp, C.c_double, C.c_uint64, C.c_uint64, C.POINTER(atomo_lq_msg), vp, vp]
         L.atomo_decode.argtypes = [vp, C.c_int, vp, C.c_int, C.c_float, vp, C.c_int64, vp]
-        L.atomo_decode_svd_batch.argtypes = [vp, C.POINTER(atomo_svd_msg), C.POINTER(C.c_int32), C.c_int, C.c_float,
-                                             C.POINTER(vp), C.POINTER(C.c_int64), vp]
+        L.atomo_decode_svd_batch.argtypes = [vp, vp, vp, C.c_int, C.c_float, vp, vp, vp]
         L.atomo_apply_svd_batch.argtypes = L.atomo_decode_svd_batch.argtypes
         L.atomo_svd_sweeps.argtypes = [vp, vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_int]
         L.atomo_last_counters.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
@@ -110,8 +110,43 @@ def _check(status: int, what: str):
 
 
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    st = torch.cuda.current_stream() if stream is None else stream
-    return int(st.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream)
+
+
+# How calls of many descriptors are marshalled: the array goes down as one bytes object, put together from the packed
+# descriptors that the messages keep (an array of ctypes structures costs half a microsecond per element).
+_MAT_FORMAT = "iiqQ"
+assert struct.calcsize(_MAT_FORMAT) == C.sizeof(atomo_mat)
+
+
+def _packed(msgs) -> bytes:
+    """The C descriptors of SVD messages, one after the other."""
+    try:
+        return b"".join([m._packed for m in msgs])
+    except AttributeError:
+        return b"".join([m.pack() for m in msgs])
+
+
+def _packed_groups(groups):
+    """The same for groups of messages, and the int32 bounds of the groups."""
+    first, end = [0], 0
+    for grp in groups:
+        end += len(grp)
+        first.append(end)
+    try:
+        blob = b"".join([m._packed for grp in groups for m in grp])
+    except AttributeError:
+        blob = _packed([m for grp in groups for m in grp])
+    return blob, struct.pack("%di" % len(first), *first)
+
+
+def _packed_outs(groups, outs):
+    """Pointers and row strides of the outputs of groups of messages."""
+    n = len(outs)
+    ptrs = struct.pack("%dQ" % n, *[o.data_ptr() for o in outs])
+    return ptrs, struct.pack("%dq" % n, *[o.stride(0) if grp[0].rows > 1 else grp[0].cols for o, grp in zip(outs, groups)])
 
 
 def _f32_cuda(t: torch.Tensor, what: str) -> torch.Tensor:
@@ -143,6 +178,12 @@ class SvdMessage:
             self.__dict__["_c"] = c
         return c
 
+    def pack(self) -> bytes:
+        """The bytes of the C descriptor, kept as `_packed`."""
+        b = bytes(self.c_struct())
+        self.__dict__["_packed"] = b
+        return b
+
     def to_host(self) -> dict:
         k = min(int(self.count.item()), self.capacity)
         return {"count": int(self.count.item()), "idx": self.idx[:k].cpu().numpy(),
@@ -159,7 +200,12 @@ class EntrywiseMessage:
     val: torch.Tensor     # float32 [capacity]
 
     def c_struct(self) -> atomo_ew_msg:
-        return atomo_ew_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.val.data_ptr())
+        """The C descriptor, built once (the buffers of a message are not replaced after allocation)."""
+        c = self.__dict__.get("_c")
+        if c is None:
+            c = atomo_ew_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.val.data_ptr())
+            self.__dict__["_c"] = c
+        return c
 
     def to_host(self) -> dict:
         k = min(int(self.count.item()), self.capacity)
@@ -177,7 +223,12 @@ class LqMessage:
     norm: torch.Tensor    # float32 [1]
 
     def c_struct(self) -> atomo_lq_msg:
-        return atomo_lq_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.norm.data_ptr())
+        """The C descriptor, built once (the buffers of a message are not replaced after allocation)."""
+        c = self.__dict__.get("_c")
+        if c is None:
+            c = atomo_lq_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.norm.data_ptr())
+            self.__dict__["_c"] = c
+        return c
 
     def to_host(self) -> dict:
         k = min(int(self.count.item()), self.capacity)
@@ -302,7 +353,7 @@ def atomo_probabilities(ctx: Context, lam: torch.Tensor, offsets: Sequence[int],
     """Algorithm 1 on each segment lam[offsets[k]:offsets[k+1]]; returns p (same order as lam)."""
     lam = _f32_cuda(lam, "lam").contiguous()
     p = torch.empty_like(lam) if out is None else _f32_cuda(out, "out")
-    offs = (C.c_int64 * len(offsets))(*[int(o) for o in offsets])
+    offs = struct.pack("%dq" % len(offsets), *[int(o) for o in offsets])
     _check(lib().atomo_probabilities(ctx._h, lam.data_ptr(), offs, len(offsets) - 1, float(s), p.data_ptr(),
                                      _stream_handle(stream)), "atomo_probabilities")
     return p
@@ -319,15 +370,19 @@ def atomo_encode_svd(ctx: Context, mats: Sequence[torch.Tensor], s: float, seed:
     block_order: 0 = block pairs by weight (default), 1 = the fixed tournament, for the matrices that iterate in Gram space.
     adaptive: k > 0 enqueues only the sweeps that earlier calls with the same shapes needed, plus k (see atomo.h)."""
     n = len(mats)
-    c_mats = (atomo_mat * n)()
+    fields = []
     for j, g in enumerate(mats):
-        _f32_cuda(g, f"mats[{j}]")
-        if g.dim() != 2 or g.stride(1) != 1:
+        if not (isinstance(g, torch.Tensor) and g.is_cuda and g.dtype is torch.float32):
+            _f32_cuda(g, f"mats[{j}]")                           # (raises)
+        shape, stride = g.shape, g.stride()
+        if len(shape) != 2 or stride[1] != 1:
             raise ValueError("each gradient must be a 2-D tensor with unit column stride")
-        c_mats[j] = atomo_mat(g.shape[0], g.shape[1], g.stride(0) if g.shape[0] > 1 else g.shape[1], g.data_ptr())
+        rows, cols = shape
+        fields += (rows, cols, stride[0] if rows > 1 else cols, g.data_ptr())
+    c_mats = struct.pack(_MAT_FORMAT * n, *fields)
     if msgs is None:
         msgs = [alloc_svd_message(g.shape[0], g.shape[1], default_capacity(s, min(g.shape)), g.device) for g in mats]
-    c_msgs = (atomo_svd_msg * n)(*[m.c_struct() for m in msgs])
+    c_msgs = _packed(msgs)
     opt = None
     if (max_sweeps is not None or stop_cosine is not None or max_inner_sweeps or inner_reduction or full_period
             or block_order or stream_ids is not None or adaptive):
@@ -407,8 +462,8 @@ def atomo_decode(ctx: Context, msgs, scale: float = 1.0, out: Optional[torch.Ten
         if out is None:
             out = torch.empty(first.rows, first.cols, dtype=torch.float32, device=first.U.device)
         _f32_cuda(out, "out")
-        c_msgs = (atomo_svd_msg * len(msgs))(*[m.c_struct() for m in msgs])
-        _check(lib().atomo_decode(ctx._h, ATOMO_KIND_SVD, C.cast(c_msgs, C.c_void_p), len(msgs), float(scale),
+        c_msgs = _packed(msgs)
+        _check(lib().atomo_decode(ctx._h, ATOMO_KIND_SVD, c_msgs, len(msgs), float(scale),
                                   out.data_ptr(), out.stride(0) if out.shape[0] > 1 else out.shape[1],
                                   _stream_handle(stream)), "atomo_decode")
         return out
@@ -432,16 +487,10 @@ def atomo_decode(ctx: Context, msgs, scale: float = 1.0, out: Optional[torch.Ten
 def atomo_decode_svd_batch(ctx: Context, groups: Sequence[Sequence[SvdMessage]], scale: float = 1.0,
                            outs: Optional[List[torch.Tensor]] = None, stream=None) -> List[torch.Tensor]:
     """One launch for a whole layer set: groups[o] are the messages summed into outs[o]."""
-    flat = [m for grp in groups for m in grp]
-    first = [0]
-    for grp in groups:
-        first.append(first[-1] + len(grp))
     if outs is None:
         outs = [torch.empty(grp[0].rows, grp[0].cols, dtype=torch.float32, device=grp[0].U.device) for grp in groups]
-    c_msgs = (atomo_svd_msg * len(flat))(*[m.c_struct() for m in flat])
-    c_first = (C.c_int32 * len(first))(*first)
-    c_outs = (C.c_void_p * len(outs))(*[o.data_ptr() for o in outs])
-    c_lds = (C.c_int64 * len(outs))(*[o.stride(0) if o.shape[0] > 1 else o.shape[1] for o in outs])
+    c_msgs, c_first = _packed_groups(groups)
+    c_outs, c_lds = _packed_outs(groups, outs)
     _check(lib().atomo_decode_svd_batch(ctx._h, c_msgs, c_first, len(outs), float(scale), c_outs, c_lds,
                                         _stream_handle(stream)), "atomo_decode_svd_batch")
     return outs
@@ -450,17 +499,11 @@ def atomo_decode_svd_batch(ctx: Context, groups: Sequence[Sequence[SvdMessage]],
 def atomo_apply_svd_batch(ctx: Context, groups: Sequence[Sequence[SvdMessage]], alpha: float,
                           params: List[torch.Tensor], stream=None) -> List[torch.Tensor]:
     """params[o] += alpha * (sum of the decoded messages of groups[o]), in place, one launch for the layer set."""
-    flat = [m for grp in groups for m in grp]
-    first = [0]
-    for grp in groups:
-        first.append(first[-1] + len(grp))
     for p, grp in zip(params, groups):
         if p.dtype != torch.float32 or tuple(p.shape) != (grp[0].rows, grp[0].cols) or p.stride(1) != 1:
             raise ValueError("params must be float32 rows x cols tensors with unit column stride")
-    c_msgs = (atomo_svd_msg * len(flat))(*[m.c_struct() for m in flat])
-    c_first = (C.c_int32 * len(first))(*first)
-    c_params = (C.c_void_p * len(params))(*[p.data_ptr() for p in params])
-    c_lds = (C.c_int64 * len(params))(*[p.stride(0) if p.shape[0] > 1 else p.shape[1] for p in params])
+    c_msgs, c_first = _packed_groups(groups)
+    c_params, c_lds = _packed_outs(groups, params)
     _check(lib().atomo_apply_svd_batch(ctx._h, c_msgs, c_first, len(params), float(alpha), c_params, c_lds,
                                        _stream_handle(stream)), "atomo_apply_svd_batch")
     return params

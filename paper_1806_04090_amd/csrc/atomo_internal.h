@@ -32,6 +32,21 @@ struct SweepHint {
     bool tried_direct = false, direct_only = false;   // the direct encode went first; and nothing was enqueued behind it
 };
 
+// Descriptor tables that the device holds, with what they were made from.  They hold addresses, sizes and stream ids, never
+// data, so a call whose tables come out byte for byte like one of these uploads nothing.  Four of them: a program that
+// goes through a few sets of buffers in turn (one per worker, double buffering) finds each where it left it.
+struct TableSlot {
+    void* dev = nullptr;
+    size_t cap = 0;
+    std::vector<char> host;
+    hipStream_t stream = nullptr;
+    uint64_t used = 0;
+};
+struct TableCache {
+    TableSlot slot[4];
+    uint64_t clock = 0;
+};
+
 struct StageSlot {
     void* host = nullptr;        // pinned
     size_t bytes = 0;
@@ -62,18 +77,10 @@ struct atomo_ctx {
     uint64_t hint_seq = 0;
     bool direct_lds = false;       // direct::allow_lds has been called for this context's device
     size_t rowgram_lds = 0;        // dynamic LDS that svd_rowgram has been allowed on this context's device
-    // Descriptor tables of the last SVD encode (at the start of the workspace) and of the last SVD decode (in a block
-    // of their own): a training loop passes the same layer set and buffers step after step, so a call whose tables
-    // come out byte for byte the same, on the same stream, with the device copy untouched since, uploads nothing.
-    std::vector<char> svd_tables;        // host copy of what the workspace holds
-    bool svd_tables_intact = false;      // nothing has asked for the workspace since they were uploaded
-    hipStream_t svd_tables_stream = nullptr;
-    void* dec_tables_dev = nullptr;
-    size_t dec_tables_cap = 0;
-    std::vector<char> dec_tables;        // host copy of what dec_tables_dev holds
-    hipStream_t dec_tables_stream = nullptr;
-    hipStream_t side = nullptr, side2 = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_join2 = nullptr;
+    atomo::TableCache svd_tables, dec_tables;    // of the SVD encoder and of the SVD decoder
+    std::vector<char> table_scratch;     // where a call puts its tables together
+    hipStream_t side = nullptr, side2 = nullptr, side_thin = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_join2 = nullptr, ev_join_thin = nullptr;
     // optional event bracketing of kernel launches (atomo_profile_*)
     bool profiling = false;
     std::vector<hipEvent_t> ev_pool;     // pairs: [2k] start, [2k+1] stop
@@ -92,16 +99,19 @@ namespace atomo {
         }                                                      \
     } while (0)
 
-// Grows the workspace to at least `bytes` (contents are not preserved).  Every user of the workspace asks for it here
-// first, so this is also where the SVD encoder's tables stop counting as intact.
+// Grows the workspace to at least `bytes` (contents are not preserved).
 int ensure_workspace(atomo_ctx* ctx, size_t bytes);
 
-// Creates ctx->side, ctx->side2 and the fork/join events if they do not exist yet.
+// Creates the context's side streams and the fork/join events if they do not exist yet.
 int ensure_side_streams(atomo_ctx* ctx);
 
 // Copies `bytes` of host data to device address `dst` on `stream` through a pinned staging slot,
 // so the caller's host buffer may be reused as soon as this returns.
 int upload(atomo_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t stream);
+
+// Where on the device `tables` are (uploaded on `stream`, in place of the set that has not been used for longest, if no
+// set of the cache is the same).
+int resident_tables(atomo_ctx* ctx, TableCache& cache, const std::vector<char>& tables, hipStream_t stream, void** dev);
 
 // Brackets the launches issued during its lifetime with two events when profiling is on.
 struct ProfScope {

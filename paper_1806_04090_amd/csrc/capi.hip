@@ -10,7 +10,6 @@ namespace atomo {
 
 int ensure_workspace(atomo_ctx* ctx, size_t bytes)
 {
-    ctx->svd_tables_intact = false;
     if (bytes <= ctx->ws_bytes) return ATOMO_OK;
     // Growing frees the old block; hipFree waits for the device, so no kernel still uses it.
     if (ctx->ws) {
@@ -33,7 +32,8 @@ int ensure_side_streams(atomo_ctx* ctx)
 {
     if (!ctx->side) ATOMO_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
     if (!ctx->side2) ATOMO_HIP(ctx, hipStreamCreateWithFlags(&ctx->side2, hipStreamNonBlocking));
-    hipEvent_t* events[] = {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_join2};
+    if (!ctx->side_thin) ATOMO_HIP(ctx, hipStreamCreateWithFlags(&ctx->side_thin, hipStreamNonBlocking));
+    hipEvent_t* events[] = {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_join2, &ctx->ev_join_thin};
     for (hipEvent_t* e : events)
         if (!*e) ATOMO_HIP(ctx, hipEventCreateWithFlags(e, hipEventDisableTiming));
     return ATOMO_OK;
@@ -65,6 +65,38 @@ int upload(atomo_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t
     ATOMO_HIP(ctx, hipMemcpyAsync(dst, slot.host, bytes, hipMemcpyHostToDevice, stream));
     ATOMO_HIP(ctx, hipEventRecord(slot.ev, stream));
     slot.pending = true;
+    return ATOMO_OK;
+}
+
+int resident_tables(atomo_ctx* ctx, TableCache& cache, const std::vector<char>& tables, hipStream_t stream, void** dev)
+{
+    TableSlot* oldest = &cache.slot[0];
+    for (TableSlot& t : cache.slot) {
+        if (t.stream == stream && t.host.size() == tables.size() && t.used > 0 &&
+            memcmp(t.host.data(), tables.data(), tables.size()) == 0) {
+            t.used = ++cache.clock;
+            *dev = t.dev;
+            return ATOMO_OK;
+        }
+        if (t.used < oldest->used) oldest = &t;
+    }
+    TableSlot& t = *oldest;
+    t.used = 0;                                                  // (an upload that fails leaves nothing to match)
+    if (t.cap < tables.size()) {
+        // (hipFree waits for the device, so no kernel still reads the old block)
+        if (t.dev) ATOMO_HIP(ctx, hipFree(t.dev));
+        t.dev = nullptr;
+        t.cap = 0;
+        const size_t want = align_up(tables.size() + tables.size() / 2, (size_t)1 << 14);
+        if (hipMalloc(&t.dev, want) != hipSuccess) return ATOMO_ENOMEM;
+        t.cap = want;
+    }
+    const int rc = upload(ctx, t.dev, tables.data(), tables.size(), stream);
+    if (rc != ATOMO_OK) return rc;
+    t.host = tables;
+    t.stream = stream;
+    t.used = ++cache.clock;
+    *dev = t.dev;
     return ATOMO_OK;
 }
 
@@ -139,12 +171,15 @@ int atomo_destroy(atomo_ctx* ctx)
         if (h.host) (void)hipHostFree(h.host);
     }
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
-    for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join, ctx->ev_join2})
+    for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join, ctx->ev_join2, ctx->ev_join_thin})
         if (e) (void)hipEventDestroy(e);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
     if (ctx->side2) (void)hipStreamDestroy(ctx->side2);
+    if (ctx->side_thin) (void)hipStreamDestroy(ctx->side_thin);
     if (ctx->ws) (void)hipFree(ctx->ws);
-    if (ctx->dec_tables_dev) (void)hipFree(ctx->dec_tables_dev);
+    for (TableCache* cache : {&ctx->svd_tables, &ctx->dec_tables})
+        for (TableSlot& t : cache->slot)
+            if (t.dev) (void)hipFree(t.dev);
     if (ctx->ew_state) (void)hipFree(ctx->ew_state);
     if (ctx->d_report) (void)hipFree(ctx->d_report);
     if (ctx->d_flags) (void)hipFree(ctx->d_flags);

@@ -47,6 +47,7 @@
 
 #include "svd_common.h"
 #include "svd_direct.h"
+#include "svd_thin.h"
 
 namespace atomo {
 
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(256) void svd_scale(const SvdMat* mats)
 {
     __shared__ float red[4];
     const SvdMat m = mats[blockIdx.x];
-    if (m.thin || direct_done(m)) return;
+    if (direct_done(m)) return;
     const int pieces = (m.ldw + 255) / 256;
     float mx = 0.0f;
     for (int row = threadIdx.x; row < m.rows_alloc; row += 256) {
@@ -945,7 +946,7 @@ __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
     for (int j = threadIdx.x; j < n_mats; j += 256) {
         const SvdMat& m = mats[j];
         if (m.accepted && *m.accepted == 0) atomicAdd(&open, 1);
-        if (m.thin || m.skip) continue;
+        if (m.skip) continue;
         const int sw = m.report[0];
         if (m.gs) gs = max(gs, sw); else ds = max(ds, sw);
         if (m.gs) ask = min(ask, m.state[ST_FIRST_ASK] > 0 ? m.state[ST_FIRST_ASK] : never);
@@ -1011,26 +1012,23 @@ struct Plan {
     std::vector<Work> norms[2];                    // four rows of a data-space matrix per item: the final row norms
     std::vector<Work> ds_full, ds_tiles;           // data-space matrices that check their whole Gram matrix (DS_VERIFY)
     std::vector<int> ds_periods;                   // their distinct R
-    std::vector<Work> thin_chunks, thin_list;      // thin matrices: (matrix, chunk of positions); (matrix)
-    std::vector<Work> thin_direct, thin_copied;    // the chunks again, split by whether G is used in place
     std::vector<Work> gs_list;                     // the Gram-space matrices
     std::vector<int> gs_periods;     // distinct R of the Gram-space matrices
     int max_R = 1;
     int max_R_ds[2] = {1, 1};        // largest R in each group of data-space matrices
     size_t rowgram_lds[2] = {0, 0};  // LDS bytes of a svd_rowgram workgroup: all rows of the group's tallest matrix
+    std::vector<int> thin_of;        // which matrix every thin.mats entry is
     std::vector<int> direct_of;      // index of the matrix in direct.mats, -1: not tried
     direct::DirectPlan direct;
-    direct::DirectMat* d_direct = nullptr;
+    thin::ThinPlan thin;             // the matrices of at most THIN_R vectors
     bool own_update = false;         // the two-sided update runs as launches of its own (see SPLIT_TWO_SIDED)
     size_t bytes = 0;
-    SvdMat* d_mats = nullptr;        // device copies of `mats` and of the concatenated work lists
-    Work* d_work = nullptr;
     size_t n_work() const
     {
         return prep.size() + rowgram[0].size() + rowgram[1].size() + fullgram.size() + tiles.size() + apply.size() +
                eig_gs.size() + eig_ds[0].size() + eig_ds[1].size() +
-               twosided.size() + strips.size() + ds_full.size() + ds_tiles.size() + norms[0].size() + norms[1].size() + pack.size() + 2 * thin_chunks.size() + thin_list.size() +
-               gs_list.size() + direct.n_work();
+               twosided.size() + strips.size() + ds_full.size() + ds_tiles.size() + norms[0].size() + norms[1].size() + pack.size() +
+               gs_list.size() + direct.n_work() + thin.n_work();
     }
 };
 
@@ -1048,8 +1046,8 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
                 uint64_t stream_base, const uint64_t* stream_ids, bool try_direct, bool direct_only, void* base, Plan& plan)
 {
     Carver carve(base);
+    carve.take<char>(256);
     plan.mats.resize(n_mats);
-    plan.d_mats = carve.take<SvdMat>(n_mats);
     plan.direct_of.assign(n_mats, -1);
     size_t atom_off = 0;
     size_t update_tiles = 0;
@@ -1072,7 +1070,6 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         m.transposed = a.rows > a.cols;
         m.r = m.transposed ? a.cols : a.rows;
         m.M = m.transposed ? a.rows : a.cols;
-        m.thin = m.r <= THIN_R;
         m.gs = 0;
         m.state = nullptr;
         m.stream_id = stream_ids ? stream_ids[j] : stream_base + (uint64_t)j;
@@ -1102,33 +1099,18 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
                 continue;
             }
         }
-        if (m.thin) {
-            // chunks of 1024 positions, larger only to keep a matrix under 128 chunks
-            const int64_t per = ((int64_t)m.M + 128 * 1024 - 1) / (128 * 1024);
-            m.tchunk = m.M <= 1024 ? (int)align_up(m.M, 256) : (int)(1024 * per);
-            m.nchg = (m.M + m.tchunk - 1) / m.tchunk;
-            m.Mp = m.M; m.ldw = 0; m.nb2 = 0; m.rows_alloc = THIN_R; m.R = 1; m.npairs = 0; m.nchu = 0; m.gs = 0;
-            m.ntiles = 0; m.ldc = 0;
-            m.W0 = nullptr; m.W1 = nullptr; m.CT = nullptr; m.CT2 = nullptr; m.cref = nullptr; m.cref0 = nullptr; m.rowsq = nullptr;
-            m.sched = nullptr; m.where = nullptr; m.bw = nullptr; m.dd = nullptr; m.idle = nullptr;
-            m.gram = carve.take<float>((size_t)m.nchg * THIN_R * THIN_R);
-            m.Q = carve.take<float>(2 * THIN_R * THIN_R);
-            m.B = carve.take<float>((size_t)m.M * m.r);
-            m.state = carve.take<int>(ST_WORDS);
-            m.sig_raw = carve.take<float>(THIN_R);
-            m.src_row = carve.take<int>(m.capacity);
-            m.src_inv = carve.take<float>(m.capacity);
-            m.src_fold = carve.take<float>(m.capacity);
-            const bool direct = m.transposed && m.ldg == m.r;
-            m.X = direct ? m.G : m.B;
-            for (int c = 0; c < m.nchg; ++c) {
-                plan.thin_chunks.push_back(Work{j, c, 0, 0});
-                (direct ? plan.thin_direct : plan.thin_copied).push_back(Work{j, c, 0, 0});
-            }
-            plan.thin_list.push_back(Work{j, 0, 0, 0});
+        if (m.r <= THIN_R) {
+            m.skip = 1;
+            plan.thin.mats.push_back(thin::ThinMat{});
+            thin::ThinMat& t = plan.thin.mats.back();
+            t.G = m.G; t.ldg = m.ldg; t.rows = m.rows; t.cols = m.cols; t.tall = m.transposed; t.r = m.r; t.M = m.M;
+            t.capacity = m.capacity;
+            t.count = m.count; t.idx = m.idx; t.w = m.w; t.U = m.U; t.V = m.V;
+            t.sigma_out = m.sigma_out; t.p_out = m.p_out; t.stream_id = m.stream_id;
+            plan.thin_of.push_back(j);
+            thin::plan_matrix(carve, t);
             continue;
         }
-        m.tchunk = 0; m.B = nullptr; m.X = nullptr;
         m.Mp = (int)align_up(m.M, 64);
         m.ldw = m.Mp + (int)align_up(m.r, 64);
         const int nb = (m.r + BS - 1) / BS;
@@ -1184,7 +1166,7 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         for (int b = 0; b < m.nb2; ++b)
             for (int c = 0; c < (m.ldw + 255) / 256; ++c) plan.prep.push_back(Work{j, b, c, 0});
         for (int k = 0; k < m.npairs; ++k) {
-            // (offsets from the matrices' descriptors, which are the first thing in the workspace)
+            // (the first 256 bytes of the workspace are left out, so that an offset of 0 means none)
             if (m.gs)
                 plan.eig_gs.push_back(Work{j, k, (int)(unsigned)(state_off / HOT_UNIT),
                                            (int)(unsigned)((pdesc_off + (size_t)k * 3 * PD_WORDS * sizeof(int)) / HOT_UNIT)});
@@ -1243,8 +1225,7 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
             return plan.mats[a.mat].rows_alloc * (a.c >= 0 ? 2 : 1) > plan.mats[b.mat].rows_alloc * (b.c >= 0 ? 2 : 1);
         });
     direct::plan_work(plan.direct);
-    plan.d_direct = carve.take<direct::DirectMat>(plan.direct.mats.size());
-    plan.d_work = carve.take<Work>(plan.n_work());
+    thin::plan_work(plan.thin);
     plan.bytes = carve.off;
 }
 
@@ -1353,121 +1334,116 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         if (hipMalloc((void**)&ctx->d_report, want * 2 * sizeof(int32_t)) != hipSuccess) return ATOMO_ENOMEM;
         ctx->report_cap = want;
     }
-    Plan sizing;
     const uint64_t* stream_ids = opt ? opt->stream_ids : nullptr;
-    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, nullptr, sizing);
-    if (sizing.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL;   // (the work items address the workspace in 32 bits of 16-byte units)
-    const bool tables_intact = ctx->svd_tables_intact;
-    const void* const ws_before = ctx->ws;
-    int rc = ensure_workspace(ctx, sizing.bytes);
-    if (rc != ATOMO_OK) return rc;
-
     Plan plan;
-    build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, ctx->ws, plan);
-    SvdMat* d_mats = plan.d_mats;
+    int rc;
+    // (laid out in the workspace there is, and again if it turns out too small)
+    for (;;) {
+        plan = Plan();
+        build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, ctx->ws, plan);
+        if (plan.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL; // (the work items address the workspace in 32 bits of 16-byte units)
+        if (ctx->ws && plan.bytes <= ctx->ws_bytes) break;
+        if ((rc = ensure_workspace(ctx, plan.bytes)) != ATOMO_OK) return rc;
+    }
     for (int j = 0; j < n_mats; ++j) {
         plan.mats[j].report = ctx->d_report + 2 * j;
         if (plan.direct_of[j] >= 0) plan.direct.mats[plan.direct_of[j]].report = plan.mats[j].report;
     }
+    for (size_t t = 0; t < plan.thin_of.size(); ++t) plan.thin.mats[t].report = plan.mats[plan.thin_of[t]].report;
     ctx->report_n = (size_t)n_mats;
 
-    std::vector<Work> all;
-    all.reserve(plan.n_work());
-    auto place = [&](const std::vector<Work>& list) {
-        const Work* at = plan.d_work + all.size();
-        all.insert(all.end(), list.begin(), list.end());
-        return at;
+    // the tables: matrices, those of the direct encode, the thin ones, work lists
+    const size_t at_direct = align_up(plan.mats.size() * sizeof(SvdMat), 256);
+    const size_t at_thin = align_up(at_direct + plan.direct.mats.size() * sizeof(direct::DirectMat), 256);
+    const size_t at_work = align_up(at_thin + plan.thin.mats.size() * sizeof(thin::ThinMat), 256);
+    std::vector<char>& tables = ctx->table_scratch;
+    tables.assign(at_work + plan.n_work() * sizeof(Work), 0);
+    memcpy(tables.data(), plan.mats.data(), plan.mats.size() * sizeof(SvdMat));
+    memcpy(tables.data() + at_direct, plan.direct.mats.data(), plan.direct.mats.size() * sizeof(direct::DirectMat));
+    memcpy(tables.data() + at_thin, plan.thin.mats.data(), plan.thin.mats.size() * sizeof(thin::ThinMat));
+    struct Placed { const Work** where; size_t at; };
+    std::vector<Placed> placed;
+    size_t n_placed = 0;
+    auto place = [&](const std::vector<Work>& list, const Work*& where) {
+        placed.push_back(Placed{&where, n_placed});
+        memcpy(tables.data() + at_work + n_placed * sizeof(Work), list.data(), list.size() * sizeof(Work));
+        n_placed += list.size();
     };
-    const Work* w_prep = place(plan.prep);
-    const Work* w_rowgram[2] = {place(plan.rowgram[0]), place(plan.rowgram[1])};
-    const Work* w_fullgram = place(plan.fullgram);
-    const Work* w_tiles = place(plan.tiles);
-    const Work* w_apply = place(plan.apply);
-    const Work* w_eig_gs = place(plan.eig_gs);
-    const Work* w_eig_ds[2] = {place(plan.eig_ds[0]), place(plan.eig_ds[1])};
-    const Work* w_twosided = place(plan.twosided);
-    const Work* w_strips = place(plan.strips);
-    const Work* w_ds_full = place(plan.ds_full);
-    const Work* w_ds_tiles = place(plan.ds_tiles);
-    const Work* w_norms[2] = {place(plan.norms[0]), place(plan.norms[1])};
-    const Work* w_pack = place(plan.pack);
-    const Work* w_thin_chunks = place(plan.thin_chunks);
-    const Work* w_thin_list = place(plan.thin_list);
-    const Work* w_thin_direct = place(plan.thin_direct);
-    const Work* w_thin_copied = place(plan.thin_copied);
-    const Work* w_gs_list = place(plan.gs_list);
+    const Work *w_prep, *w_rowgram[2], *w_fullgram, *w_tiles, *w_apply, *w_eig_gs, *w_eig_ds[2], *w_twosided, *w_strips, *w_ds_full,
+        *w_ds_tiles, *w_norms[2], *w_pack, *w_gs_list, *w_thin_gram, *w_thin_long;
     direct::DirectTables dt;
-    dt.mats = plan.d_direct;
-    dt.n_mats = (int)plan.direct.mats.size();
-    dt.gram = place(plan.direct.gram);
-    dt.tiles = place(plan.direct.tiles);
-    dt.tri = place(plan.direct.tri);
-    dt.eig = place(plan.direct.eig);
-    dt.vec = place(plan.direct.vec);
-    dt.lng = place(plan.direct.lng);
-
-    // the tables go up unless the workspace still holds these very bytes (see atomo_ctx::svd_tables)
-    {
-        const struct { const void* host; void* dev; size_t bytes; } parts[3] = {
-            {plan.mats.data(), d_mats, plan.mats.size() * sizeof(SvdMat)},
-            {plan.direct.mats.data(), plan.d_direct, plan.direct.mats.size() * sizeof(direct::DirectMat)},
-            {all.data(), plan.d_work, all.size() * sizeof(Work)}};
-        size_t total = 0;
-        for (const auto& p : parts) total += p.bytes;
-        bool same = tables_intact && ws_before == ctx->ws && ctx->svd_tables_stream == stream && ctx->svd_tables.size() == total;
-        size_t at = 0;
-        for (const auto& p : parts) {
-            same = same && memcmp(ctx->svd_tables.data() + at, p.host, p.bytes) == 0;
-            at += p.bytes;
-        }
-        if (!same) {
-            ctx->svd_tables.resize(total);
-            at = 0;
-            for (const auto& p : parts) {
-                if (p.bytes == 0) continue;
-                rc = upload(ctx, p.dev, p.host, p.bytes, stream);
-                if (rc != ATOMO_OK) return rc;
-                memcpy(ctx->svd_tables.data() + at, p.host, p.bytes);
-                at += p.bytes;
-            }
-            ctx->svd_tables_stream = stream;
-        }
+    place(plan.prep, w_prep);
+    for (int g = 0; g < 2; ++g) {
+        place(plan.rowgram[g], w_rowgram[g]);
+        place(plan.eig_ds[g], w_eig_ds[g]);
+        place(plan.norms[g], w_norms[g]);
     }
+    place(plan.fullgram, w_fullgram);
+    place(plan.tiles, w_tiles);
+    place(plan.apply, w_apply);
+    place(plan.eig_gs, w_eig_gs);
+    place(plan.twosided, w_twosided);
+    place(plan.strips, w_strips);
+    place(plan.ds_full, w_ds_full);
+    place(plan.ds_tiles, w_ds_tiles);
+    place(plan.pack, w_pack);
+    place(plan.thin.gram, w_thin_gram);
+    place(plan.thin.lng, w_thin_long);
+    place(plan.gs_list, w_gs_list);
+    place(plan.direct.gram, dt.gram);
+    place(plan.direct.tiles, dt.tiles);
+    place(plan.direct.tri, dt.tri);
+    place(plan.direct.eig, dt.eig);
+    place(plan.direct.vec, dt.vec);
+    place(plan.direct.lng, dt.lng);
+    void* d_tables = nullptr;
+    if ((rc = resident_tables(ctx, ctx->svd_tables, tables, stream, &d_tables)) != ATOMO_OK) return rc;
+    const SvdMat* d_mats = (const SvdMat*)d_tables;
+    dt.mats = (const direct::DirectMat*)((char*)d_tables + at_direct);
+    dt.n_mats = (int)plan.direct.mats.size();
+    for (const Placed& x : placed) *x.where = (const Work*)((char*)d_tables + at_work) + x.at;
 
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
-    hipStream_t const caller = stream;
     auto record_hint = [&]() -> int {
         if (hint) {
-            ATOMO_HIP(ctx, hipEventRecord(hint->done, caller));
+            ATOMO_HIP(ctx, hipEventRecord(hint->done, stream));
             hint->pending = true;
         }
         ATOMO_HIP(ctx, hipGetLastError());
-        ctx->svd_tables_intact = true;                           // until anything asks for the workspace again
         return ATOMO_OK;
     };
     const bool any_direct = !plan.direct.mats.empty();
-    bool iterate = false;                                        // does anything but the direct encode run?
+    bool iterate = false;                                        // is anything enqueued for the Jacobi iteration?
     for (int j = 0; j < n_mats; ++j) iterate = iterate || !plan.mats[j].skip;
-    // the hint comes from svd_pack, unless only thin matrices are left beside the direct ones
-    const bool hint_from_direct = direct_only && any_direct && plan.pack.empty();
-    // thin matrices beside direct ones: on a stream of their own from here to the end
-    const bool beside = hint_from_direct && iterate;
-    if (beside) {
-        rc = ensure_side_streams(ctx);
-        if (rc != ATOMO_OK) return rc;
-        ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
-        ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side2, ctx->ev_fork, 0));
+    // thin matrices: beside all others on a stream of their own, from the caller's point in time
+    const bool any_thin = !plan.thin.mats.empty();
+    const bool beside = any_thin && (any_direct || iterate);
+    if (any_thin) {
+        hipStream_t s_thin = stream;
+        if (beside) {
+            if ((rc = ensure_side_streams(ctx)) != ATOMO_OK) return rc;
+            ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
+            ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side_thin, ctx->ev_fork, 0));
+            s_thin = ctx->side_thin;
+        }
+        ProfScope ps(ctx, ATOMO_K_SVD_THIN, s_thin);
+        thin::launch(plan.thin, (const thin::ThinMat*)((char*)d_tables + at_thin), w_thin_gram, w_thin_long, s, seed, ctx->d_flags,
+                     s_thin);
+        if (beside) ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join_thin, s_thin));
     }
+    // the hint comes from svd_pack, or from the direct encode if nothing iterates
     if (any_direct) {
         if (!ctx->direct_lds) {
             ATOMO_HIP(ctx, direct::allow_lds());
             ctx->direct_lds = true;
         }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, stream);
-        direct::launch(plan.direct, dt, s, seed, direct_only, hint_from_direct && hint ? hint->dev : nullptr, ctx->d_flags, stream);
+        direct::launch(plan.direct, dt, s, seed, direct_only, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, stream);
     }
-    if (any_direct && !iterate) return record_hint();
-    if (beside) stream = ctx->side2;
+    if (!iterate) {
+        if (beside) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join_thin, 0));
+        return record_hint();
+    }
     {
         ProfScope ps(ctx, ATOMO_K_SVD_PREPARE, stream);
         const int reset_wgs = (n_mats * ST_WORDS + 255) / 256;
@@ -1486,10 +1462,9 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     // two buffers: the update of tick t-1 reads the C of parity t-1 and writes parity t, while svd_eig of tick
     // t forms its own 64x64 block from the C of parity t-1 and the rotations of tick t-1, which are
     // double-buffered by tick parity as well.
-    // Thin matrices go in front of the small ones when there are Gram-space matrices to overlap with.
     const bool have_ds[2] = {!plan.rowgram[0].empty(), !plan.rowgram[1].empty()};
-    const bool have_gs = !plan.twosided.empty(), have_thin = !plan.thin_list.empty();
-    const bool use_side[2] = {have_ds[0], have_ds[1] || (have_thin && have_gs)};
+    const bool have_gs = !plan.twosided.empty();
+    const bool use_side[2] = {have_ds[0], have_ds[1]};
     const int n_two = (int)plan.twosided.size();
     if (use_side[0] || use_side[1]) {
         rc = ensure_side_streams(ctx);
@@ -1497,19 +1472,6 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
         if (use_side[0]) ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
         if (use_side[1]) ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side2, ctx->ev_fork, 0));
-    }
-    if (have_thin) {
-        hipStream_t s_thin = have_gs ? ctx->side2 : stream;
-        // a pass over the data does the work of many sweeps of the blocked iteration: one rotating pass per eight
-        // sweeps of the limit, and the pass that confirms (no input tried, however graded or rank-deficient, has
-        // needed more than two rotating passes)
-        const int passes = std::max(2, std::min(THIN_PASSES, 1 + (max_sweeps + 7) / 8));
-        ProfScope ps(ctx, ATOMO_K_SVD_THIN, s_thin);
-        launch_thin_absmax(d_mats, w_thin_direct, (int)plan.thin_direct.size(), w_thin_copied, (int)plan.thin_copied.size(),
-                           s_thin);
-        for (int pass = 0; pass < passes; ++pass)
-            launch_thin_pass(d_mats, w_thin_chunks, (int)plan.thin_chunks.size(), w_thin_list, (int)plan.thin_list.size(),
-                             pass, passes - 1, stop_cosine, ctx->d_flags, s_thin);
     }
     if (have_ds[0] || have_ds[1]) {
         hipStream_t s_ds[2] = {ctx->side, ctx->side2};
@@ -1536,7 +1498,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
                 if (!have_ds[g] || tick >= ds_ticks[g]) continue;
                 if (tick >= 0) {
                     ProfScope ps(ctx, ATOMO_K_SVD_EIG, s_ds[g]);
-                    launch_svd_eig(d_mats, w_eig_ds[g], (int)plan.eig_ds[g].size(), nullptr, 0, nullptr, 0, 0, tick, limit_ds, 0,
+                    launch_svd_eig(d_mats, ctx->ws, w_eig_ds[g], (int)plan.eig_ds[g].size(), nullptr, 0, nullptr, 0, 0, tick, limit_ds, 0,
                                    stop_cosine, max_inner_ds, inner_reduction_ds, full_period, 0, ctx->d_flags, s_ds[g]);
                 }
                 {
@@ -1574,7 +1536,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
                 }
                 {
                     ProfScope ps(ctx, ATOMO_K_SVD_EIG, stream);
-                    launch_svd_eig(d_mats, w_eig_gs, (int)plan.eig_gs.size(), w_twosided, own_launch ? 0 : n_two, w_gs_list,
+                    launch_svd_eig(d_mats, ctx->ws, w_eig_gs, (int)plan.eig_gs.size(), w_twosided, own_launch ? 0 : n_two, w_gs_list,
                                    (int)plan.gs_list.size(), cyclic, tick, limit_gs, ask_from, stop_cosine, max_inner,
                                    inner_reduction, full_period, 0, ctx->d_flags, stream);
                 }
@@ -1594,7 +1556,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
                 }
                 {
                     ProfScope ps(ctx, ATOMO_K_SVD_EIG, stream);
-                    launch_svd_eig(d_mats, w_eig_gs, (int)plan.eig_gs.size(), nullptr, 0, nullptr, 0, 0, tick, limit_gs,
+                    launch_svd_eig(d_mats, ctx->ws, w_eig_gs, (int)plan.eig_gs.size(), nullptr, 0, nullptr, 0, 0, tick, limit_gs,
                                    ask_from, stop_cosine, max_inner, inner_reduction, full_period, 1, ctx->d_flags, stream);
                 }
             }
@@ -1610,16 +1572,11 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     {
         ProfScope ps(ctx, ATOMO_K_SVD_FINALIZE, stream);
         svd_select<<<(unsigned)n_mats, 256, 0, stream>>>(d_mats, s, (unsigned long long)seed, ctx->d_flags);
-        const bool hint_here = hint && !hint_from_direct;
-        const unsigned pack_wgs = grid(plan.pack) + (hint_here ? 1u : 0u);     // the hint rides behind the pack items
+        const unsigned pack_wgs = grid(plan.pack) + (hint ? 1u : 0u);     // the hint rides behind the pack items
         if (pack_wgs > 0)
-            svd_pack<<<pack_wgs, 256, 0, stream>>>(d_mats, w_pack, (int)plan.pack.size(), n_mats, hint_here ? hint->dev : nullptr);
-        if (have_thin) launch_thin_pack(d_mats, w_thin_chunks, (int)plan.thin_chunks.size(), stream);
+            svd_pack<<<pack_wgs, 256, 0, stream>>>(d_mats, w_pack, (int)plan.pack.size(), n_mats, hint ? hint->dev : nullptr);
     }
-    if (beside) {
-        ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join, stream));
-        ATOMO_HIP(ctx, hipStreamWaitEvent(caller, ctx->ev_join, 0));
-    }
+    if (beside) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join_thin, 0));
     return record_hint();
 }
 

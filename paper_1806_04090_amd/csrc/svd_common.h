@@ -15,7 +15,6 @@ constexpr int QSZ = PR * PR;
 constexpr int MAX_R = ALG1_MAX;
 constexpr int GS_MIN_BLOCKS = 16; // matrices with at least this many row blocks iterate in Gram space
 constexpr int THIN_R = 32;        // matrices with at most this many vectors on the shorter side take the thin path (svd_thin.hip)
-constexpr int THIN_PASSES = 8;    // at most this many passes over the data for a thin matrix
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -132,15 +131,10 @@ struct SvdMat {
     float* src_inv;          // [capacity] what the long vector of the kept atom is multiplied by: 1 / its norm
     float* src_fold;         // [capacity] what the short vector is multiplied by: 1
                              //   (a folded message, w == null, has the weight sigma / p in the factor of its U side)
-    // thin matrices (r <= THIN_R): Q = [V | rotation of the next pass], 32 x 32 each; gram = [nchg][32 x 32]
-    int thin;
-    int tchunk;              // positions per work item (a multiple of 256)
-    float* B;                // M x r, position-major: the rotated data
     int* report;             // [2] sweeps and refreshes of this matrix, written when the message is made
     // matrices that svd_direct.hip has tried first
-    int skip;                // 1: the direct encode alone, no Jacobi launches were enqueued (all pointers below r, M unset)
+    int skip;                // 1: not for the iteration (the direct encode alone, or a thin matrix): nothing else is set
     const int* accepted;     // nonzero word: the message is in place already (null: the matrix was not tried)
-    const float* X;          // the data before the first rotation, position-major with row stride r: G itself, or its copy in B
     // Gram-space matrices: the pairing of the ticks, tables indexed by tick mod 3
     int* sched;              // [3][npairs][2]: the two blocks (smaller first) of every pair
     int* pdesc;              // [npairs][3][PD_WORDS]: what a pair problem needs to know about its pair, see PD_*
@@ -158,7 +152,7 @@ struct Work { int mat, a, b, c; };
 enum { PD_BI = 0, PD_BJ, PD_K1, PD_S1, PD_X0, PD_X1, PD_K2, PD_S2, PD_Y0, PD_Y1, PD_WORDS = 12 };
 
 // The work item of a Gram-space pair problem carries where the matrix's state words and the pair's descriptors are,
-// as offsets from the descriptor table of the matrices in units of 16 bytes (b and c; 0 for data-space matrices), so
+// as offsets from the start of the workspace in units of 16 bytes (b and c; c is 0 for data-space matrices), so
 // that they are read beside the matrix's descriptor, not after it.
 constexpr size_t HOT_UNIT = 16;
 
@@ -372,27 +366,17 @@ __device__ inline void twosided_tile(const SvdMat* mats, const Work* work, int i
     }
 }
 
-// Enqueues svd_eig for one tick (defined in svd_eig.hip): n_items pair problems, plus, when n_two > 0, the
+// Enqueues svd_eig for one tick (defined in svd_eig.hip; hot_base: the workspace, see HOT_UNIT): n_items pair problems, plus, when n_two > 0, the
 // two-sided update of tick - 1 over the n_two tiles of d_two_work.  fresh_only selects, among the Gram-space
 // matrices, those whose Gram matrix was formed in this very tick (1) or all the others (0).
 // With n_plan > 0 the launch also plans the pairing of tick + 1 for the Gram-space matrices of d_plan_work (one
 // workgroup each): by block weight, or, with cyclic != 0, the fixed tournament.
 // ask_from: a Gram-space matrix does not ask for a refresh before it has completed that many sweeps (the host enqueues
 // no refresh launches at the sweep boundaries before; the sweep limit overrides it).
-void launch_svd_eig(const SvdMat* d_mats, const Work* d_work, int n_items, const Work* d_two_work, int n_two,
+void launch_svd_eig(const SvdMat* d_mats, const void* hot_base, const Work* d_work, int n_items, const Work* d_two_work, int n_two,
                     const Work* d_plan_work, int n_plan, int cyclic, int tick, int max_sweeps, int ask_from,
                     float stop_cosine, int max_inner, float inner_reduction, int full_period, int fresh_only,
                     int* d_flags, hipStream_t stream);
-
-// Thin matrices (defined in svd_thin.hip).  d_chunks lists (matrix, chunk of positions), d_list the thin matrices.
-// d_direct: chunks of the matrices used in place (largest |entry| only); d_copied: chunks of those copied into B first.
-void launch_thin_absmax(const SvdMat* d_mats, const Work* d_direct, int n_direct, const Work* d_copied, int n_copied,
-                        hipStream_t stream);
-// One pass over the data (rotate, Gram matrix) followed by the r x r problem of every thin matrix.
-void launch_thin_pass(const SvdMat* d_mats, const Work* d_chunks, int n_chunks, const Work* d_list, int n_list, int pass,
-                      int last_pass, float stop_cosine, int* d_flags, hipStream_t stream);
-// After svd_select: the kept atoms' vectors into the message.
-void launch_thin_pack(const SvdMat* d_mats, const Work* d_chunks, int n_chunks, hipStream_t stream);
 
 }  // namespace svd
 }  // namespace atomo

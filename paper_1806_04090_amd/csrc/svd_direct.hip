@@ -15,15 +15,13 @@
 #include <cmath>
 #include <vector>
 
+#include "svd_device.h"
 #include "svd_direct.h"
 
 namespace atomo {
 namespace direct {
 
 using svd::Work;
-typedef unsigned long long u64;
-typedef double doublex2 __attribute__((ext_vector_type(2)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 using svd::floatx4;
 
 namespace {
@@ -40,20 +38,9 @@ constexpr u64 LAM_MIN_BITS = 0x3CD0000000000000ull;   // 2^-50: anything below i
 constexpr u64 LAM_MAX_BITS = 0x3FF0000000000000ull;   // 1.0: the trace is below it
 constexpr int LAM_STEP_BITS = 52 - LAM_BITS;
 
-// A pointer out of a descriptor as one into global memory: the compiler cannot know that, and a load through a generic
-// pointer waits for the LDS as well.
-template <typename T>
-using Global = T __attribute__((address_space(1)))*;
-template <typename T>
-__device__ inline Global<T> global(T* p) { return (Global<T>)p; }
-
 // ------------------------------------------------------------------------------------------------
 // wave helpers (64 lanes, no LDS)
 // ------------------------------------------------------------------------------------------------
-__device__ inline unsigned lo32(double x) { return (unsigned)__double_as_longlong(x); }
-__device__ inline unsigned hi32(double x) { return (unsigned)(__double_as_longlong(x) >> 32); }
-__device__ inline double mk64(unsigned lo, unsigned hi) { return __longlong_as_double((long long)(((u64)hi << 32) | lo)); }
-
 template <int CTRL>
 __device__ inline double dpp(double x)
 {
@@ -115,27 +102,6 @@ __device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 &
 __device__ inline double lane_value(double x, int lane)
 {
     return mk64((unsigned)__builtin_amdgcn_readlane((int)lo32(x), lane), (unsigned)__builtin_amdgcn_readlane((int)hi32(x), lane));
-}
-
-// Square root and reciprocal of a positive normal number, to the last bits: the hardware's estimates, then Goldschmidt's and
-// Newton's iterations (no scaling, no special cases: half the latency of sqrt() and of a division in a serial chain).
-__device__ inline double root(double x)
-{
-    const double r = __builtin_amdgcn_rsq(x);
-    double g = x * r, h = 0.5 * r;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const double e = fma(-h, g, 0.5);
-        g = fma(g, e, g);
-        h = fma(h, e, h);
-    }
-    return fma(fma(-g, g, x), h, g);
-}
-__device__ inline double reciprocal(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1369,6 +1335,8 @@ void plan_work(DirectPlan& plan)
     std::vector<Work> factors;
     std::vector<int> order(plan.mats.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = (int)j;
+    // the longest products first: the last workgroups to start set when the launch ends
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].kchunk > plan.mats[b].kchunk; });
     for (int j : order) {
         const DirectMat& m = plan.mats[j];
         for (int ti = 0; ti < m.nt; ++ti)
@@ -1382,9 +1350,6 @@ void plan_work(DirectPlan& plan)
         for (int k = 0; k < m.capacity; ++k) plan.vec.push_back(Work{j, k, 0, 0});
         for (int p = 0; p < (m.M + LONG_COLS - 1) / LONG_COLS; ++p) plan.lng.push_back(Work{j, p, 0, 0});
     }
-    // the longest products first: the last workgroups to start set when the launch ends
-    std::stable_sort(plan.gram.begin(), plan.gram.end(),
-                     [&](const Work& a, const Work& b) { return plan.mats[a.mat].kchunk > plan.mats[b.mat].kchunk; });
     plan.n_eig = plan.eig.size();
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
     // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.

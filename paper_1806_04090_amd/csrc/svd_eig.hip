@@ -241,7 +241,7 @@ __device__ inline void plan_next_tick(const SvdMat& m, int tick, int cyclic, flo
 // previous tick's two-sided update (one tile per group of four waves, staged in the LDS arrays a pair problem
 // would use).  The update writes the C of this tick's parity; the pair problems read the C of the previous
 // parity and bring their own 64x64 block up to date themselves (step 1 below), so the two do not meet.
-__global__ __launch_bounds__(NT) void svd_eig(const SvdMat* mats, const Work* work, int n_eig, const Work* two_work,
+__global__ __launch_bounds__(NT) void svd_eig(const SvdMat* mats, const char* hot_base, const Work* work, int n_eig, const Work* two_work,
                                               int n_two, const Work* plan_work, int cyclic, int step, int max_sweeps, int ask_from,
                                               float stop_cosine, int max_inner, float inner_reduction, int full_period,
                                               int fresh_only, int* flags)
@@ -280,8 +280,8 @@ __global__ __launch_bounds__(NT) void svd_eig(const SvdMat* mats, const Work* wo
     for (int i = 0; i <= PD_Y1; ++i) pdw[i] = 0;
     int st_done = 0, st_mode = 0;
     if (wk.c) {
-        const int* hot = (const int*)((const char*)mats + (size_t)(unsigned)wk.b * HOT_UNIT);
-        const int* pd = (const int*)((const char*)mats + (size_t)(unsigned)wk.c * HOT_UNIT) + (step % 3) * PD_WORDS;
+        const int* hot = (const int*)(hot_base + (size_t)(unsigned)wk.b * HOT_UNIT);
+        const int* pd = (const int*)(hot_base + (size_t)(unsigned)wk.c * HOT_UNIT) + (step % 3) * PD_WORDS;
         st_done = hot[ST_DONE_AT]; st_mode = hot[ST_MODE]; st_fresh = hot[ST_FRESH_AT];
 #pragma unroll
         for (int i = 0; i <= PD_Y1; ++i) pdw[i] = pd[i];
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(NT) void svd_eig(const SvdMat* mats, const Work* wo
 }  // namespace
 
 
-void launch_svd_eig(const SvdMat* d_mats, const Work* d_work, int n_items, const Work* d_two_work, int n_two,
+void launch_svd_eig(const SvdMat* d_mats, const void* hot_base, const Work* d_work, int n_items, const Work* d_two_work, int n_two,
                     const Work* d_plan_work, int n_plan, int cyclic, int step, int max_sweeps, int ask_from,
                     float stop_cosine, int max_inner, float inner_reduction, int full_period, int fresh_only,
                     int* d_flags, hipStream_t stream)
@@ -874,7 +874,7 @@ void launch_svd_eig(const SvdMat* d_mats, const Work* d_work, int n_items, const
     // the launch, unused dynamic LDS keeps them apart: a pair problem is a latency chain and runs slower
     // when it shares its SIMDs.
     const size_t pad = n_items <= 200 ? 20 * 1024 : 0;
-    svd_eig<<<grid, NT, pad, stream>>>(d_mats, d_work, n_items, d_two_work, n_two, d_plan_work, cyclic, step, max_sweeps,
+    svd_eig<<<grid, NT, pad, stream>>>(d_mats, (const char*)hot_base, d_work, n_items, d_two_work, n_two, d_plan_work, cyclic, step, max_sweeps,
                                      ask_from, stop_cosine, max_inner, inner_reduction, full_period, fresh_only, d_flags);
 }
 

@@ -1,480 +1,432 @@
-// Spectral-ATOMO (Section 5), matrices whose shorter side has at most 32 vectors ("thin": the
-// [x*y/2, 2*k*k] reshape of Section 6 gives 18 columns for every 3x3 convolution, 2 for 1x1).
+// Spectral-ATOMO encode of thin matrices: at most 32 vectors on the shorter side, any number of positions on the longer one
+// (a convolution gradient [x, y, k, k] in the reshape [x y / 2, 2 k k] of Section 6 has 18 columns).
 //
-// The r <= 32 vectors x_c (columns of a tall G, rows of a wide one) have M entries ("positions").
-// The whole Jacobi problem is one r x r eigenproblem, so a pass over the data is
-//     thin_gram : B <- B * Q  (32 positions x r per wave and step, fp32 MFMA), written back in place, and in the
-//                 same pass the partial Gram matrices  C = B^T B  of 1024-position chunks (MFMA, the 16 result
-//                 registers of the first product are the operands of the second as they are)
-//     thin_eig  : one workgroup per matrix: sums the partials, tests the cosines |C_ij| / sqrt(C_ii C_jj)
-//                 measured on the data; if they are not below the threshold, diagonalises C by two-sided
-//                 Jacobi (in LDS, to convergence) -> Q for the next pass, V <- V * Q
-// Pass 0 reads G and only forms C (Q = I); pass 1 reads G and writes B = 2^-e G Q; later passes update B in
-// place.  (A G that is not position-major and contiguous - vectors along rows, or padded rows - is first copied
-// into B in that layout, thin_prepare, and the passes read the copy.)  Because every Q after the first is close to the identity, small columns are updated with small
-// relative error, which an accumulated V applied to G could not give in fp32.  Two or three passes are the
-// rule.  The kept atoms are then gathered from B (thin_pack); the short vectors are columns of V.
-#include <cfloat>
-#include <cmath>
+// Three launches and two passes over the data:
+//     thin_gram  : partial r x r Gram matrices of runs of positions, in double precision on the matrix cores
+//     thin_solve : one workgroup per matrix sums them, diagonalises the sum (two-sided Jacobi, all in LDS), takes the
+//                  singular values, runs Algorithm 1, draws the mask and writes the message but for the long vectors
+//     thin_long  : the long vectors of the kept atoms, A^T u / sigma
+// Products of two floats are exact in double precision: lambda has an absolute error of about 1e-15 lambda_1, and Jacobi's
+// vectors are orthogonal to rounding whatever the spectrum looks like.
+#include <algorithm>
+#include <vector>
 
-#include "svd_common.h"
+#include "svd_device.h"
+#include "svd_thin.h"
 
 namespace atomo {
-namespace svd {
+namespace thin {
+
+using svd::Work;
 
 namespace {
 
-constexpr int XLD = THIN_R + 1;         // LDS row stride of a staged block (32 positions x 32 vectors)
-constexpr int TNT = 512;                // threads of the streaming kernels
-constexpr int TWAVES = TNT / 64;
-constexpr int TSZ = THIN_R * THIN_R;
+constexpr int GRAM_WAVES = 8;
+constexpr int GRAM_CHUNK = 128 * GRAM_WAVES;   // positions per workgroup: eight rounds of 16 per wave
+constexpr int MAX_CHUNKS = 128;
+constexpr int PART = 3 * 256;                  // doubles of a partial Gram matrix
 
-// Where lane `lane` starts in a block of 32 positions x r vectors stored position-major, and how it moves on
-// when it advances by 64 elements.
-struct Cursor {
-    int pos, c, dq, dr;
-};
-
-__device__ inline Cursor cursor_for(int lane, int r)
+// Bound: one read of the data; the matrix cores have three 16 x 16 x 4 products per four positions (one up to 16 vectors).
+// 11.16 M elements of 18 columns: THIN_GRAM_MEASURED
+__global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats, const Work* work)
 {
-    Cursor cu;
-    cu.pos = lane / r;
-    cu.c = lane % r;
-    cu.dq = 64 / r;
-    cu.dr = 64 % r;
-    return cu;
-}
-
-__device__ inline void advance(Cursor& cu, int r)
-{
-    cu.c += cu.dr;
-    cu.pos += cu.dq;
-    if (cu.c >= r) {
-        cu.c -= r;
-        ++cu.pos;
-    }
-}
-
-// One block = positions k0 .. k0 + 31 of a position-major source with row stride r: one contiguous run of 32 r
-// floats; positions beyond M read as zero.
-__device__ inline void load_block(float (&vals)[16], const float* __restrict__ src, int r, int M, int k0, int lane)
-{
-    const float* base = src + (long long)k0 * r;
-    const int valid = min(32, M - k0) * r;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) vals[i] = lane + 64 * i < valid ? base[lane + 64 * i] : 0.0f;
-}
-
-// The same elements into the wave's LDS block xs[position][vector], multiplied by `factor`.
-__device__ inline void stage_block(float* xs, const float (&vals)[16], float factor, int r, Cursor cu)
-{
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        if (cu.pos < 32) xs[cu.pos * XLD + cu.c] = vals[i] * factor;
-        advance(cu, r);
-    }
-}
-
-struct Source {
-    const float* p;
-    float factor;
-};
-
-// Before the first rotation has been applied the data are X (G itself where G already is position-major and
-// contiguous, else its copy in B), scaled by 2^-e on the fly; afterwards B.
-__device__ inline Source source_of(const SvdMat& m, bool unrotated)
-{
-    Source s;
-    const float* const x = m.X;
-    const float* const b = m.B;
-    s.p = unrotated ? x : b;
-    s.factor = unrotated ? ldexpf(1.0f, -scale_exponent(m)) : 1.0f;
-    return s;
-}
-
-__device__ inline void publish_absmax(const SvdMat& m, float mx, float* red)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_down(mx, o));
-    if (lane == 0) red[wave] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < TWAVES; ++w) mx = fmaxf(mx, red[w]);
-        if (mx > 0.0f && mx <= FLT_MAX) atomicMax((unsigned int*)&m.state[ST_ABSMAX], __float_as_uint(mx));
-    }
-}
-
-// Largest |entry| of one chunk of a matrix that is used in place.
-__global__ __launch_bounds__(TNT) void thin_absmax(const SvdMat* mats, const Work* work)
-{
-    __shared__ float red[TWAVES];
+    __shared__ double red[GRAM_WAVES / 2][PART];
     const Work wk = work[blockIdx.x];
-    const SvdMat m = mats[wk.mat];
-    const long long lo = (long long)wk.a * m.tchunk * m.r;
-    const long long hi = min((long long)m.M, (long long)(wk.a + 1) * m.tchunk) * m.r;
-    float mx = 0.0f;
-    const float* x = m.X + lo;
-    const long long len = hi - lo;
-    long long done = 0;
-    if ((((size_t)x) & 15) == 0) {                                  // 16-byte loads, four in flight per thread
-        const float4* x4 = (const float4*)x;
-        const long long n4 = len / 4;
-        for (long long q = threadIdx.x; q < n4; q += 4 * TNT) {
-            float4 v[4];
+    const ThinMat& m = mats[wk.mat];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
+    const int r = m.r, p_end = min(m.M, (wk.a + 1) * m.chunk);
+    const bool two = r > 16;
+    // entry (vector i, position p) at i * by_vec + p * by_pos; a lane holds vectors l16 and 16 + l16 (clamped: zeroed below)
+    const long long by_vec = m.tall ? 1 : m.ldg, by_pos = m.tall ? m.ldg : 1;
+    const Global<const float> g0 = global(m.G) + (long long)min(l16, r - 1) * by_vec;
+    const Global<const float> g1 = global(m.G) + (long long)min(16 + l16, r - 1) * by_vec;
+    const float m0 = l16 < r ? 1.0f : 0.0f, m1 = 16 + l16 < r ? 1.0f : 0.0f;
+    doublex4 acc[3] = {doublex4{0, 0, 0, 0}, doublex4{0, 0, 0, 0}, doublex4{0, 0, 0, 0}};
+    // the four positions p0 + 4 q + s of a round, one per instruction; the next round's are on their way meanwhile
+    struct Round { float a[4], b[4]; };
+    auto fetch = [&](int p0, Round& x) {
+        const int p = p0 + 4 * q;
+        const Global<const float> h0 = g0 + p * by_pos, h1 = g1 + p * by_pos;
+        if (p0 + 16 <= p_end) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = q + u * TNT < n4 ? x4[q + u * TNT] : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int s = 0; s < 4; ++s) x.a[s] = h0[s * by_pos];
+            if (two) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v[u].x), fabsf(v[u].y))), fmaxf(fabsf(v[u].z), fabsf(v[u].w)));
-        }
-        done = n4 * 4;
-    }
-    for (long long e = done + threadIdx.x; e < len; e += TNT) mx = fmaxf(mx, fabsf(x[e]));
-    publish_absmax(m, mx, red);
-}
-
-// Matrices that are not position-major and contiguous (vectors along rows, or padded rows): copy into B.
-__global__ __launch_bounds__(TNT) void thin_prepare(const SvdMat* mats, const Work* work)
-{
-    __shared__ float red[TWAVES];
-    const Work wk = work[blockIdx.x];
-    const SvdMat m = mats[wk.mat];
-    const int r = m.r;
-    const long long lo = (long long)wk.a * m.tchunk * r;
-    const long long hi = min((long long)m.M, (long long)(wk.a + 1) * m.tchunk) * r;
-    float mx = 0.0f;
-    for (long long e = lo + threadIdx.x; e < hi; e += TNT) {
-        const long long k = e / r;
-        const int c = (int)(e - k * r);
-        const float v = m.transposed ? m.G[k * m.ldg + c] : m.G[c * m.ldg + k];
-        m.B[e] = v;
-        mx = fmaxf(mx, fabsf(v));
-    }
-    publish_absmax(m, mx, red);
-}
-
-// One chunk of positions of one matrix: B <- B * Q (pass >= 1) and the chunk's part of C = B^T B.
-//   fp32 MFMA 32x32x2: A operand lane l = A[i = l % 32][k = l / 32], B operand lane l = B[k = l / 32][j = l % 32],
-//   result register v of lane l = D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
-// For B^T B both operands of one instruction are the same register: lane l supplies entry (position of
-// half l / 32, vector l % 32) of two positions, and which two positions an instruction takes does not matter
-// for the sum.  Result register v of the first product holds exactly such a pair (positions 8 (v / 4) + v % 4
-// and that + 4).
-template <bool MATVEC>
-__global__ __launch_bounds__(TNT, 4) void thin_gram(const SvdMat* mats, const Work* work, int pass)
-{
-    __shared__ float xs_all[TWAVES][THIN_R * XLD];
-    __shared__ float qs[THIN_R * XLD];                              // the rotation, zero outside r x r
-    const Work wk = work[blockIdx.x];
-    const SvdMat m = mats[wk.mat];
-    if (m.state[ST_MODE] == MODE_DONE) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    float* xs = xs_all[wave];
-    const int r = m.r, M = m.M;
-    const Source s = source_of(m, pass <= 1);
-    const Cursor cu = cursor_for(lane, r);
-    for (int e = lane; e < THIN_R * XLD; e += 64) xs[e] = 0.0f;     // vectors r .. 31 stay zero
-    if (MATVEC)
-        for (int e = tid; e < TSZ; e += TNT) qs[(e >> 5) * XLD + (e & 31)] = m.Q[TSZ + e];
-    floatx16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-
-    const int nit = m.tchunk / (32 * TWAVES);
-    const int kbase = wk.a * m.tchunk;
-    float vals[16];
-    load_block(vals, s.p, r, M, kbase + 32 * wave, lane);
-    for (int it = 0; it < nit; ++it) {
-        const int k0 = kbase + 32 * (it * TWAVES + wave);
-        stage_block(xs, vals, s.factor, r, cu);
-        __syncthreads();
-        if (it + 1 < nit) load_block(vals, s.p, r, M, k0 + 32 * TWAVES, lane);
-        if (!MATVEC) {
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                const float a = xs[(2 * t + h) * XLD + l32];
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, a, acc, 0, 0, 0);
+                for (int s = 0; s < 4; ++s) x.b[s] = h1[s * by_pos];
             }
         } else {
-            floatx16 d;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) d[v] = 0.0f;
-#pragma unroll
-            for (int t = 0; t < 16; ++t)
-                if (2 * t < r)
-                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[l32 * XLD + 2 * t + h], qs[(2 * t + h) * XLD + l32], d, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(d[v], d[v], acc, 0, 0, 0);
-            __syncthreads();
-#pragma unroll
-            for (int v = 0; v < 16; ++v) xs[(8 * (v >> 2) + 4 * h + (v & 3)) * XLD + l32] = d[v];
-            __syncthreads();
-            Cursor w = cu;
-            float* out = m.B + (long long)k0 * r;
-            const int valid = min(32, M - k0) * r;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (lane + 64 * i < valid) out[lane + 64 * i] = xs[w.pos * XLD + w.c];
-                advance(w, r);
+            for (int s = 0; s < 4; ++s) {
+                const long long at = min(p + s, m.M - 1) * by_pos;
+                x.a[s] = p + s < p_end ? g0[at] : 0.0f;
+                x.b[s] = two && p + s < p_end ? g1[at] : 0.0f;
             }
         }
+    };
+    auto add = [&](const Round& x) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double u = m0 != 0.0f ? (double)x.a[s] : 0.0;
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, u, acc[0], 0, 0, 0);
+            if (two) {
+                const double v = m1 != 0.0f ? (double)x.b[s] : 0.0;
+                acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, v, acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc[2], 0, 0, 0);
+            }
+        }
+    };
+    constexpr int STEP = 16 * GRAM_WAVES;
+    Round x, y;
+    int p0 = wk.a * m.chunk + 16 * wave;
+    if (p0 < p_end) fetch(p0, x);
+    for (; p0 < p_end; p0 += 2 * STEP) {
+        if (p0 + STEP < p_end) fetch(p0 + STEP, y);
+        add(x);
+        if (p0 + STEP >= p_end) break;
+        if (p0 + 2 * STEP < p_end) fetch(p0 + 2 * STEP, x);
+        add(y);
+    }
+    // the waves' sums in a fixed order: the upper half of them hands its own over, then all add up
+    auto at = [&](int t, int v) { return t * 256 + (4 * v + q) * 16 + l16; };
+    const int tiles = two ? 3 : 1;
+    if (wave >= GRAM_WAVES / 2) {
+        for (int t = 0; t < tiles; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave - GRAM_WAVES / 2][at(t, v)] = acc[t][v];
+    }
+    __syncthreads();
+    if (wave < GRAM_WAVES / 2) {
+        for (int t = 0; t < tiles; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][at(t, v)] += acc[t][v];
+    }
+    __syncthreads();
+    const Global<double> out = global(m.part) + (size_t)wk.a * PART;
+    for (int e = tid; e < 256 * tiles; e += 64 * GRAM_WAVES) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < GRAM_WAVES / 2; ++w) sum += red[w][e];
+        out[e] = sum;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+constexpr int ST = 512;                        // threads of a workgroup of thin_solve
+constexpr int LD = THIN_R + 1;
+constexpr int MAX_SWEEPS = 15;
+
+// 1 / sqrt(x) of a positive normal number: the hardware's estimate and two of Newton's steps.
+__device__ inline double inverse_root(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return y;
+}
+
+// Jacobi rotation of the pair with diagonal entries a, b and off-diagonal g: columns (x, y) become (c x - s y, s x + c y),
+// rows likewise.  With h = (b - a) / 2 the angle has cos 2 phi = |h| / sqrt(h^2 + g^2) and s has the sign of h g; the
+// identity for g = 0.
+__device__ inline void rotation(double a, double b, double g, double& c, double& s)
+{
+    const double h = 0.5 * (b - a), hh = fma(h, h, g * g);
+    const bool none = !(hh > 1e-300);
+    const double inv = inverse_root(none ? 1.0 : hh);
+    const double cc = none ? 1.0 : fma(0.5 * fabs(h), inv, 0.5), ic = inverse_root(cc);
+    c = cc * ic;
+    s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
+}
+
+// Bound: latency, one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other,
+// threads 0 .. 255 one 2 x 2 block each; threads 256 .. 511 rotate the vectors in place, two pairs of entries each.  A wave works
+// out all rotations of the round in its first 16 lanes and hands them around inside.
+__global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
+{
+    __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];
+    __shared__ int unfinished[2];
+    __shared__ double lam[THIN_R];
+    __shared__ int rank_of[THIN_R];
+    const ThinMat& m = mats[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = m.r;
+    // C in both triangles: sums over the chunks
+    const bool two = r > 16;
+    for (int e0 = tid; e0 < (two ? PART : 256); e0 += ST) {
+        const Global<const double> in = global((const double*)m.part) + e0;
+        double sum = 0.0;
+        int c = 0;
+        for (; c + 32 <= m.nchunks; c += 32) {
+            double x[32];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) x[u] = in[(size_t)(c + u) * PART];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) sum += x[u];
+        }
+        for (; c + 4 <= m.nchunks; c += 4) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = in[(size_t)(c + u) * PART];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum += x[u];
+        }
+        for (; c < m.nchunks; ++c) sum += in[(size_t)c * PART];
+        const int t = e0 >> 8, e = e0 & 255, i = (e >> 4) + (t == 2 ? 16 : 0), j = (e & 15) + (t > 0 ? 16 : 0);
+        // (a square tile holds both triangles, equal to the last bit: the products commute)
+        A[0][i * LD + j] = sum;
+        if (t == 1) A[0][j * LD + i] = sum;
+    }
+    for (int e = tid; e < THIN_R * THIN_R; e += ST) V[(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+    if (tid < 2) unfinished[tid] = 0;
+    __syncthreads();
+    // tournament over n = r rounded up to even (an entry past r is a row of zeros and never rotates)
+    const int n = (r + 1) & ~1, half = n >> 1, n1 = n - 1;
+    double trace = 0.0;
+    for (int i = 0; i < r; ++i) trace += A[0][i * LD + i];
+    if (r & 1) {                                                 // the row and column of zeros
+        __syncthreads();
+        if (tid < n) A[0][r * LD + tid] = A[0][tid * LD + r] = 0.0;
         __syncthreads();
     }
-    // the eight waves' sums, added in a fixed order
-    float* cs = &xs_all[0][0];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) cs[wave * TSZ + (8 * (v >> 2) + 4 * h + (v & 3)) * THIN_R + l32] = acc[v];
-    __syncthreads();
-    for (int e = tid; e < TSZ; e += TNT) {
-        float sum = 0.0f;
-#pragma unroll
-        for (int w = 0; w < TWAVES; ++w) sum += cs[w * TSZ + e];
-        m.gram[(size_t)wk.a * TSZ + e] = sum;
+    const int ka = (tid & 255) >> 4, kb = tid & 15;
+    const double floor = 1e-13 * trace;
+    // round t pairs n1 with t and t + k with t - k (mod n1); a thread holds pairs ka and kb and moves them on by one per round
+    auto first_of = [&](int k, int& p, int& q) {
+        k = min(k, half - 1);
+        p = k == 0 ? n1 : k;
+        q = k == 0 ? 0 : n1 - k;
+    };
+    auto move_on = [&](int k, int& p, int& q) {
+        if (k != 0) p = p + 1 == n1 ? 0 : p + 1;
+        q = q + 1 == n1 ? 0 : q + 1;
+    };
+    auto at = [](int i) { return (i << 5) + i; };                // i * LD
+    static_assert(LD == 33, "row offsets by shift and add");
+    const int row_v = at(ka);
+    int pa, qa, pb, qb;
+    first_of(ka, pa, qa);
+    first_of(kb, pb, qb);
+    int cur = 0, sweeps = 0;
+    bool open = n > 1 && trace > 0.0;
+    while (open && sweeps < MAX_SWEEPS) {
+        bool turned = false;
+        for (int round = 0; round < n1; ++round) {
+            const double* old = A[cur];
+            double* now = A[cur ^ 1];
+            // everything that will be needed, on its way before the rotations
+            const int ra = at(pa), sa_ = at(qa), rb = at(pb), sb_ = at(qb);
+            const double dp = old[rb + pb], dq = old[sb_ + qb], g = old[rb + qb];
+            double b00 = 0.0, b01 = 0.0, b10 = 0.0, b11 = 0.0;
+            if (tid < 256) {
+                b00 = old[ra + pb];
+                b01 = old[ra + qb];
+                b10 = old[sa_ + pb];
+                b11 = old[sa_ + qb];
+            } else {
+                b00 = V[row_v + pb];                           // rows ka and ka + 16, pair kb
+                b01 = V[row_v + qb];
+                b10 = V[row_v + 16 * LD + pb];
+                b11 = V[row_v + 16 * LD + qb];
+            }
+            double cb, sb;
+            rotation(dp, dq, g, cb, sb);
+            // the sweep is the last one if all cosines it met were small (what it leaves is then their square), rows at the
+            // rounding of the largest aside
+            turned = turned || (g * g > 1e-12 * dp * dq && fmin(dp, dq) > floor);
+            const double c00 = cb * b00 - sb * b01, c01 = sb * b00 + cb * b01;
+            const double c10 = cb * b10 - sb * b11, c11 = sb * b10 + cb * b11;
+            if (tid < 256) {
+                const double ca = __shfl(cb, ka), sa = __shfl(sb, ka);      // (lane k holds pair k)
+                if (ka < half && kb < half) {
+                    const bool diagonal = ka == kb;
+                    now[ra + pb] = ca * c00 - sa * c10;
+                    now[ra + qb] = diagonal ? 0.0 : ca * c01 - sa * c11;
+                    now[sa_ + pb] = diagonal ? 0.0 : sa * c00 + ca * c10;
+                    now[sa_ + qb] = sa * c01 + ca * c11;
+                }
+            } else if (kb < half) {
+                V[row_v + pb] = c00;
+                V[row_v + qb] = c01;
+                V[row_v + 16 * LD + pb] = c10;
+                V[row_v + 16 * LD + qb] = c11;
+            }
+            move_on(ka, pa, qa);
+            move_on(kb, pb, qb);
+            __syncthreads();
+            cur ^= 1;
+        }
+        if (turned) unfinished[sweeps & 1] = 1;
+        __syncthreads();
+        open = unfinished[sweeps & 1] != 0;
+        ++sweeps;
+        if (tid == 0) unfinished[sweeps & 1] = 0;                // (written again only after the barriers of the next sweep)
     }
-}
-
-constexpr int ENT = 1024;               // threads of thin_eig: one per entry of a 32 x 32 matrix
-
-__device__ inline float block_max(float x, float* red, int tid)
-{
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+    if (tid < r) lam[tid] = A[cur][tid * LD + tid];
+    if (tid < THIN_R) rank_of[tid] = 0;                          // (not all of them are written if lam is not a number)
     __syncthreads();
-    if ((tid & 63) == 0) red[tid >> 6] = x;
+    if (tid < r) {
+        int before = 0;
+        const double mine = lam[tid];
+        for (int j = 0; j < r; ++j) before += lam[j] > mine || (lam[j] == mine && j < tid);
+        rank_of[before] = tid;
+    }
     __syncthreads();
-    float mx = red[0];
-    for (int w = 1; w < ENT / 64; ++w) mx = fmaxf(mx, red[w]);
-    return mx;
-}
-
-// One workgroup per thin matrix, after thin_gram of the same pass.
-__global__ __launch_bounds__(ENT) void thin_eig(const SvdMat* mats, const Work* work, int pass, int last_pass,
-                                                float stop_cosine, int* flags)
-{
-    __shared__ float A[THIN_R * XLD], Qs[THIN_R * XLD], T1[THIN_R * XLD], T2[THIN_R * XLD];
-    __shared__ float red[ENT / 64];
-    __shared__ unsigned short sched[(THIN_R - 1) * (THIN_R / 2)];   // column pair of (step, k): p | q << 8
-    __shared__ float2 rot[THIN_R / 2];                              // (cos, sin) of the step's rotations
-    const SvdMat m = mats[work[blockIdx.x].mat];
-    if (m.state[ST_MODE] == MODE_DONE) return;
-    const int tid = threadIdx.x, ei = tid >> 5, ej = tid & 31;      // this thread's entry of a 32 x 32 matrix
-    const int r = m.r, n = r + (r & 1);
-
-    // C = sum of the chunks' partial Gram matrices, in chunk order
-    {
-        // four interleaved running sums (chunks 0, 4, 8, ... in the first, and so on), added at the end: a fixed
-        // order, and a shorter dependent chain than one sum
-        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-        for (int ch0 = 0; ch0 < m.nchg; ch0 += 32) {
-            float part[32];
-#pragma unroll
-            for (int u = 0; u < 32; ++u) part[u] = ch0 + u < m.nchg ? m.gram[(size_t)(ch0 + u) * TSZ + tid] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 32; u += 4) {
-                s0 += part[u];
-                s1 += part[u + 1];
-                s2 += part[u + 2];
-                s3 += part[u + 3];
+    // one wave: sigma, Algorithm 1 (the first index whose probability stays under 1, see block_algorithm1), the draw
+    if (wave == 0) {
+        const double l0 = lam[rank_of[0]];
+        const int src = lane < r ? rank_of[lane] : 0;
+        const double l = lam[src];
+        const bool real = lane < r && l > (double)svd::ZERO_REL * l0;
+        const float sigma = real ? (float)sqrt(l) : 0.0f;
+        double tail = 0.0;                                       // sum of the sigmas from this one on, smallest first
+        for (int j = r - 1; j >= 0; --j) {
+            const float sj = __shfl(sigma, j);
+            if (j >= lane) tail += (double)sj;
+        }
+        const u64 under = __ballot(lane < r && (double)sigma * (s - (double)lane) <= tail);
+        const int ns = under ? __ffsll((unsigned long long)under) - 1 : r;
+        const double tail_ns = ns < r ? __shfl(tail, ns) : 0.0;
+        const float p = lane < r ? alg1_probability(sigma, lane, ns, s, tail_ns) : 0.0f;
+        const u32x4 rnd = philox4x32_10((u64)(lane >> 2), m.stream_id, seed);
+        const uint32_t word = (lane & 3) == 0 ? rnd.x : (lane & 3) == 1 ? rnd.y : (lane & 3) == 2 ? rnd.z : rnd.w;
+        const bool kept = lane < r && u01(word) < p;
+        const u64 mask = __ballot(kept);
+        const int pos = __popcll(mask & ((1ull << lane) - 1));
+        if (lane < r) {
+            if (m.sigma_out) m.sigma_out[lane] = sigma;
+            if (m.p_out) m.p_out[lane] = p;
+        }
+        if (lane == 0) {
+            *m.count = __popcll(mask);
+            m.report[0] = 1;
+            m.report[1] = 2;
+            atomicMax(&flags[FLAG_MAX_SWEEPS], 1);
+            if (__popcll(mask) > m.capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
+            if (open && !(trace != trace)) atomicMax(&flags[FLAG_NOCONV], 1);
+        }
+        if (kept && pos < m.capacity) {
+            const float weight = sigma / p;
+            m.idx[pos] = lane;
+            if (m.w) m.w[pos] = weight;
+            const double fold = m.w ? 1.0 : (double)weight;      // folded message: the weight goes into U
+            float* out = m.tall ? m.V + (size_t)pos * r : m.U + (size_t)pos * r;
+            const double inv = reciprocal(sqrt(l));
+            for (int i = 0; i < r; ++i) {
+                const double x = V[i * LD + src];
+                global(out)[i] = (float)(m.tall ? x : x * fold);
+                global(m.u)[pos * r + i] = x * inv * (m.tall ? fold : 1.0);
             }
         }
-        const float sum = (s0 + s1) + (s2 + s3);
-        A[ei * XLD + ej] = sum;
-        Qs[ei * XLD + ej] = ei == ej ? 1.0f : 0.0f;
-        if (tid < (n - 1) * (THIN_R / 2)) {
-            int p = 0, q = 1;
-            if ((tid & 15) < n / 2) pair_blocks(n, tid >> 4, tid & 15, p, q);
-            sched[tid] = (unsigned short)(p | (q << 8));
-        }
     }
-    __syncthreads();
-    float scale = 0.0f;
-    for (int i = 0; i < r; ++i) scale = fmaxf(scale, A[i * XLD + i]);
-    const float floor_sq = ZERO_REL * scale;                       // squared norms at or below this are rounding residue
-    float worst = 0.0f;
-    if (ei < ej && ej < r) {
-        const float di = A[ei * XLD + ei], dj = A[ej * XLD + ej];
-        if (di > floor_sq && dj > floor_sq) worst = fabsf(A[ei * XLD + ej]) * rsqrtf(di * dj);
-    }
-    worst = block_max(worst, red, tid);
-    const bool done = worst < stop_cosine;
-    if (done || pass == last_pass) {
-        const int e = scale_exponent(m);
-        if (tid < r) m.sig_raw[tid] = ldexpf(sqrtf(fmaxf(A[tid * XLD + tid], 0.0f)), e);
-        if (pass == 0) m.Q[tid] = (ei == ej && ei < r) ? 1.0f : 0.0f;
-        if (tid == 0) {
-            m.state[ST_MODE] = MODE_DONE;
-            m.state[ST_EXP] = e;
-            atomicMax(&flags[FLAG_MAX_SWEEPS], pass);
-            if (!done) atomicMax(&flags[FLAG_NOCONV], 1);
-        }
-        return;
-    }
-
-    // Two-sided Jacobi on the symmetric C (C <- J^T C J, Q <- Q J), round-robin pairing: n / 2 disjoint rotations
-    // per step.  The cosine of a rotation is the cosine of the two data columns, the quantity the pass over the
-    // data tests.  A step is two phases: thread k < n / 2 works out rotation k from C_pp, C_qq, C_pq; then one
-    // thread per 2 x 2 block (rows of pair ka, columns of pair kb) applies both rotations to its block, and one
-    // thread per (row, pair) rotates two entries of Q.  Every entry has one owner, which reads it before the
-    // phase barrier and writes it after, so the update is in place.
-    {
-        const int n2 = n / 2;
-        const bool blk = tid < n2 * n2;                             // owner of a 2 x 2 block of C
-        const int ka = blk ? tid / n2 : 0, kb = blk ? tid % n2 : 0;
-        const int t2 = tid - 256;
-        const bool qit = t2 >= 0 && t2 < n * n2;                    // owner of two entries of a row of Q
-        const int qi = qit ? t2 / n2 : 0, qk = qit ? t2 % n2 : 0;
-        float sweep_worst = 0.0f;
-        for (int sweep = 0; sweep < 10; ++sweep) {
-            for (int step = 0; step < n - 1; ++step) {
-                const unsigned short* sc = sched + step * (THIN_R / 2);
-                float b00 = 0.0f, b01 = 0.0f, b10 = 0.0f, b11 = 0.0f, q0 = 0.0f, q1 = 0.0f;
-                int pa = 0, qa = 0, pb = 0, qb = 0;
-                if (blk) {
-                    const int ea = sc[ka], eb = sc[kb];
-                    pa = ea & 255; qa = ea >> 8; pb = eb & 255; qb = eb >> 8;
-                    b00 = A[pa * XLD + pb]; b01 = A[pa * XLD + qb];
-                    b10 = A[qa * XLD + pb]; b11 = A[qa * XLD + qb];
-                } else if (qit) {
-                    const int eb = sc[qk];
-                    pb = eb & 255; qb = eb >> 8;
-                    q0 = Qs[qi * XLD + pb]; q1 = Qs[qi * XLD + qb];
-                }
-                if (tid < n2) {
-                    // here ka = 0, kb = tid: pb, qb are this rotation's columns
-                    const float cpp = A[pb * XLD + pb], cqq = A[qb * XLD + qb], cpq = A[pb * XLD + qb];
-                    bool rotate = cpp > floor_sq && cqq > floor_sq;
-                    float cosv = 0.0f;
-                    if (rotate) cosv = fabsf(cpq) * __builtin_amdgcn_rsqf(cpp * cqq);
-                    rotate = rotate && cosv > 1.0e-7f;
-                    // an error of a few ulp in the angle only changes which rotation is applied; (c, sn) stays a
-                    // rotation to rounding because sn = c t with c = 1 / sqrt(1 + t^2)
-                    float c = 1.0f, sn = 0.0f;
-                    if (rotate) {
-                        sweep_worst = fmaxf(sweep_worst, cosv);
-                        const float zeta = (cqq - cpp) * __builtin_amdgcn_rcpf(2.0f * cpq);
-                        const float t = copysignf(1.0f, zeta) *
-                                        __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.0f)));
-                        c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.0f));
-                        sn = c * t;
-                    }
-                    rot[tid] = make_float2(c, sn);
-                }
-                __syncthreads();
-                if (blk) {
-                    const float2 ra = rot[ka], rb = rot[kb];
-                    // columns: [x, y] <- [c x - s y, s x + c y] with the rotation of pair kb
-                    const float c00 = rb.x * b00 - rb.y * b01, c01 = rb.y * b00 + rb.x * b01;
-                    const float c10 = rb.x * b10 - rb.y * b11, c11 = rb.y * b10 + rb.x * b11;
-                    // rows, with the rotation of pair ka
-                    A[pa * XLD + pb] = ra.x * c00 - ra.y * c10;
-                    A[pa * XLD + qb] = ra.x * c01 - ra.y * c11;
-                    A[qa * XLD + pb] = ra.y * c00 + ra.x * c10;
-                    A[qa * XLD + qb] = ra.y * c01 + ra.x * c11;
-                } else if (qit) {
-                    const float2 rb = rot[qk];
-                    Qs[qi * XLD + pb] = rb.x * q0 - rb.y * q1;
-                    Qs[qi * XLD + qb] = rb.y * q0 + rb.x * q1;
-                }
-                __syncthreads();
-            }
-            // Jacobi converges quadratically: after a sweep whose largest cosine was below 1e-3 the columns are
-            // orthogonal to about 1e-6, which the next pass over the data then measures
-            const float w = block_max(sweep_worst, red, tid);
-            sweep_worst = 0.0f;
-            if (w < 1.0e-3f) break;
-        }
-    }
-    __syncthreads();
-
-    // one Newton-Schulz step keeps Q orthogonal to rounding:  Q <- Q (1.5 I - 0.5 Q^T Q)
-    {
-        float sum = 0.0f;
-        for (int x = 0; x < THIN_R; ++x) sum = fmaf(Qs[x * XLD + ei], Qs[x * XLD + ej], sum);
-        T1[ei * XLD + ej] = (ei == ej ? 1.5f : 0.0f) - 0.5f * sum;
-        A[ei * XLD + ej] = pass == 0 ? (ei == ej ? 1.0f : 0.0f) : m.Q[tid];      // V so far
-    }
-    __syncthreads();
-    {
-        float sum = 0.0f;
-        for (int x = 0; x < THIN_R; ++x) sum = fmaf(Qs[ei * XLD + x], T1[x * XLD + ej], sum);
-        T2[ei * XLD + ej] = (ei < r && ej < r) ? sum : 0.0f;
-    }
-    __syncthreads();
-    {
-        float sum = 0.0f;
-        for (int x = 0; x < THIN_R; ++x) sum = fmaf(A[ei * XLD + x], T2[x * XLD + ej], sum);
-        m.Q[tid] = (ei < r && ej < r) ? sum : 0.0f;                // V <- V Q
-        m.Q[TSZ + tid] = T2[ei * XLD + ej];                        // the rotation of the next pass
-    }
-    if (tid == 0) m.state[ST_SWEEPS] = pass + 1;
 }
 
-// Kept atoms of one chunk: the long vector of slot s is column src_row[s] of the data divided by its norm.
-__global__ __launch_bounds__(TNT) void thin_pack(const SvdMat* mats, const Work* work)
+// ------------------------------------------------------------------------------------------------
+constexpr int LONG_POS = 1024;                 // positions per workgroup
+constexpr int LONG_GROUP = 4;
+
+// Bound: one read of the data, four kept atoms per pass.  A thread owns one position of 256 at a time.  The r entries of a
+// position of a tall matrix lie side by side: they come through LDS, so that the loads are coalesced; those of a wide matrix come
+// from r coalesced rows.
+__global__ __launch_bounds__(256) void thin_long(const ThinMat* mats, const Work* work)
 {
-    __shared__ float xs_all[TWAVES][THIN_R * XLD];
-    __shared__ int col_of[THIN_R];
-    __shared__ float inv_of[THIN_R], fold_of[THIN_R];
+    __shared__ double us[LONG_GROUP][THIN_R];
+    __shared__ float xs[256 * (THIN_R + 1)];
     const Work wk = work[blockIdx.x];
-    const SvdMat m = mats[wk.mat];
-    const int kept = min(*m.count, m.capacity);
-    if (kept <= 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    float* xs = xs_all[wave];
-    const int r = m.r, M = m.M;
-    const Source s = source_of(m, m.state[ST_SWEEPS] == 0);
-    const Cursor cu = cursor_for(lane, r);
-    if (tid < kept) {
-        col_of[tid] = m.src_row[tid];
-        inv_of[tid] = m.src_inv[tid];
-        fold_of[tid] = m.src_fold[tid];
-    }
-    float* const mu = m.U;
-    float* const mv = m.V;
-    float* long_out = m.transposed ? mu : mv;
-    float* short_out = m.transposed ? mv : mu;
-    const int nit = m.tchunk / (32 * TWAVES);
-    for (int it = 0; it < nit; ++it) {
-        const int k0 = wk.a * m.tchunk + 32 * (it * TWAVES + wave);
-        float vals[16];
-        load_block(vals, s.p, r, M, k0, lane);
+    const ThinMat& m = mats[wk.mat];
+    const int kept = min(*m.count, m.capacity), r = m.r, tid = threadIdx.x;
+    const bool tall = m.tall;
+    const Global<const float> G = global(m.G);
+    const Global<float> out = global(tall ? m.U : m.V);
+    const int ls = r | 1;                                        // stride of a position in LDS
+    const int by_r = ((1 << 20) + r - 1) / r;
+    const bool dense = m.ldg == r;
+    for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
+        const int ns = min(LONG_GROUP, kept - s0);
         __syncthreads();
-        stage_block(xs, vals, s.factor, r, cu);
-        __syncthreads();
-        const int kk = k0 + l32;
-        if (kk < M)
-            for (int slot = h; slot < kept; slot += 2)
-                long_out[(size_t)slot * M + kk] = xs[l32 * XLD + col_of[slot]] * inv_of[slot];
-    }
-    if (wk.a == 0) {
-        __syncthreads();
-        for (int e = tid; e < kept * r; e += TNT) {
-            const int slot = e / r, c = e % r;
-            short_out[(size_t)slot * r + c] = m.Q[c * THIN_R + col_of[slot]] * fold_of[slot];
+        if (tid < LONG_GROUP * THIN_R) {
+            const int k = tid / THIN_R, i = tid % THIN_R;
+            us[k][i] = k < ns && i < r ? global(m.u)[(s0 + k) * r + i] : 0.0;
+        }
+        for (int h = 0; h < LONG_POS / 256; ++h) {
+            const int first = wk.a * LONG_POS + 256 * h, here = min(256, m.M - first);
+            if (here <= 0) break;
+            __syncthreads();
+            double acc[LONG_GROUP] = {0.0, 0.0, 0.0, 0.0};
+            if (tall) {
+                const Global<const float> block = G + (long long)first * m.ldg;
+                // element e of the block of `here` positions: position e / r (by a multiplication that is exact below 2^13),
+                // entry e mod r; eight loads in flight
+                const int total = here * r;
+                for (int e0 = tid; e0 < total; e0 += 8 * 256) {
+                    float x[8];
+                    int to[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int e = min(e0 + 256 * u, total - 1), p = (e * by_r) >> 20;
+                        to[u] = p * ls + (e - p * r);
+                        x[u] = block[dense ? (long long)e : (long long)p * m.ldg + (e - p * r)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) xs[to[u]] = x[u];
+                }
+                __syncthreads();
+                const float* mine = xs + min(tid, here - 1) * ls;
+                for (int i = 0; i < r; ++i) {
+                    const double d = (double)mine[i];
+#pragma unroll
+                    for (int k = 0; k < LONG_GROUP; ++k) acc[k] = fma(d, us[k][i], acc[k]);
+                }
+            } else {
+                const Global<const float> g = G + first + min(tid, here - 1);
+                __syncthreads();
+                for (int i0 = 0; i0 < r; i0 += 8) {
+                    float x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = g[min(i0 + u, r - 1) * m.ldg];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const double d = i0 + u < r ? (double)x[u] : 0.0;
+#pragma unroll
+                        for (int k = 0; k < LONG_GROUP; ++k) acc[k] = fma(d, us[k][min(i0 + u, THIN_R - 1)], acc[k]);
+                    }
+                }
+            }
+            if (tid < here) {
+#pragma unroll
+                for (int k = 0; k < LONG_GROUP; ++k)
+                    if (k < ns) out[(size_t)(s0 + k) * m.M + first + tid] = (float)acc[k];
+            }
         }
     }
 }
 
 }  // namespace
 
-void launch_thin_absmax(const SvdMat* d_mats, const Work* d_direct, int n_direct, const Work* d_copied, int n_copied,
-                        hipStream_t stream)
+void plan_matrix(Carver& carve, ThinMat& m)
 {
-    if (n_direct > 0) thin_absmax<<<(unsigned)n_direct, TNT, 0, stream>>>(d_mats, d_direct);
-    if (n_copied > 0) thin_prepare<<<(unsigned)n_copied, TNT, 0, stream>>>(d_mats, d_copied);
+    // chunks of 2048 positions, larger only to keep a matrix under 128 of them; from the shape alone, so that the sums do not
+    // depend on what else is in the call
+    const long long runs = ((long long)m.M + GRAM_CHUNK - 1) / GRAM_CHUNK;
+    m.chunk = (int)(GRAM_CHUNK * ((runs + MAX_CHUNKS - 1) / MAX_CHUNKS));
+    m.nchunks = (int)(((long long)m.M + m.chunk - 1) / m.chunk);
+    m.part = carve.take<double>((size_t)m.nchunks * PART);
+    m.u = carve.take<double>((size_t)m.r * m.r);
 }
 
-void launch_thin_pass(const SvdMat* d_mats, const Work* d_chunks, int n_chunks, const Work* d_list, int n_list, int pass,
-                      int last_pass, float stop_cosine, int* d_flags, hipStream_t stream)
+void plan_work(ThinPlan& plan)
 {
-    if (pass == 0) thin_gram<false><<<(unsigned)n_chunks, TNT, 0, stream>>>(d_mats, d_chunks, pass);
-    else thin_gram<true><<<(unsigned)n_chunks, TNT, 0, stream>>>(d_mats, d_chunks, pass);
-    thin_eig<<<(unsigned)n_list, ENT, 0, stream>>>(d_mats, d_list, pass, last_pass, stop_cosine, d_flags);
+    for (size_t j = 0; j < plan.mats.size(); ++j) {
+        const ThinMat& m = plan.mats[j];
+        for (int c = 0; c < m.nchunks; ++c) plan.gram.push_back(Work{(int)j, c, 0, 0});
+        for (int c = 0; c < (m.M + LONG_POS - 1) / LONG_POS; ++c) plan.lng.push_back(Work{(int)j, c, 0, 0});
+    }
 }
 
-void launch_thin_pack(const SvdMat* d_mats, const Work* d_chunks, int n_chunks, hipStream_t stream)
+void launch(const ThinPlan& plan, const ThinMat* d_mats, const Work* gram, const Work* lng, double s, uint64_t seed, int* d_flags,
+            hipStream_t stream)
 {
-    thin_pack<<<(unsigned)n_chunks, TNT, 0, stream>>>(d_mats, d_chunks);
+    thin_gram<<<(unsigned)plan.gram.size(), 64 * GRAM_WAVES, 0, stream>>>(d_mats, gram);
+    thin_solve<<<(unsigned)plan.mats.size(), ST, 0, stream>>>(d_mats, s, (u64)seed, d_flags);
+    thin_long<<<(unsigned)plan.lng.size(), 256, 0, stream>>>(d_mats, lng);
 }
 
-}  // namespace svd
+}  // namespace thin
 }  // namespace atomo
