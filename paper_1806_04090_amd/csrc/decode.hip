@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "atomo_internal.h"
+#include "svd_device.h"
 
 namespace atomo {
 
@@ -40,6 +41,7 @@ constexpr int TR = 64, TC = 256;
 constexpr int TALL_ROWS = 256;     // rows per workgroup for outputs of at most 32 columns
 constexpr int ATOMS_MAX = 512;     // atoms listed in LDS at a time
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // out tile (64 x 256) = sum over messages and kept atoms of (scale w_k u_k) v_k^T as a rank-K update on the
@@ -68,9 +70,9 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
     constexpr int US = UROWS + 32, VS = VCOLS + 32;              // LDS strides: odd and even atoms on different banks
     constexpr int NU = (KP * UROWS / 4 + 255) / 256;             // 16-byte loads per thread and piece, u and v
     constexpr int NV = (KP * VCOLS / 4 + 255) / 256;
-    __shared__ const float* up[ATOMS_MAX];
-    __shared__ const float* vp[ATOMS_MAX];
-    __shared__ const float* wp[ATOMS_MAX];                       // the atom's weight (nullptr: folded into u)
+    __shared__ Global<const float> up[ATOMS_MAX];
+    __shared__ Global<const float> vp[ATOMS_MAX];
+    __shared__ Global<const float> wp[ATOMS_MAX];                // the atom's weight (nullptr: folded into u)
     __shared__ int kept_of[ATOMS_MAX];
     __shared__ int total_sh;
     __shared__ __attribute__((aligned(16))) float Us[KP * US];
@@ -90,12 +92,30 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[rb][cb][v] = 0.0f;
 
+    // this lane's corner; element v of block (rb, cb): row below(rb, v) under it, column 32 cb to its right
+    const int row0 = tile_r0 + row_off + 4 * h, col0 = tile_c0 + col_off + l32;
+    auto below = [](int rb, int v) { return rb * 32 + 8 * (v >> 2) + (v & 3); };
+    // the tile as it is, on its way from here on: 36.9 -> 28.1 us for the update of 9.75 M parameters from 8 messages (a load
+    // behind each store of the end waits for it)
+    floatx16 old[2][NCB];
+    if constexpr (ACCUMULATE) {
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) {
+                const Global<const float> in = global((const float*)o.out) + min(col0 + cb * 32, o.cols - 1);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) old[rb][cb][v] = in[(long long)min(row0 + below(rb, v), o.rows - 1) * o.ld];
+            }
+    }
+
     // four consecutive elements of an atom's row, zero beyond `limit`; one 16-byte load where the address allows
-    auto load4 = [](const float* base, int at, int limit) {
+    auto load4 = [](Global<const float> base, int at, int limit) {
         float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        const float* p = base + at;
+        const Global<const float> p = base + at;
         if (at + 3 < limit && (((size_t)p) & 15) == 0) {
-            x = *(const float4*)p;
+            const floatx4 y = *(Global<const floatx4>)p;
+            x = make_float4(y[0], y[1], y[2], y[3]);
         } else {
             if (at < limit) x.x = p[0];
             if (at + 1 < limit) x.y = p[1];
@@ -112,7 +132,7 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
             const int f = tid + 256 * e, atom = f / (UROWS / 4), part = f % (UROWS / 4);
             ru[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (atom < KP && k0 + atom < total) {
-                const float* w = wp[k0 + atom];
+                const Global<const float> w = wp[k0 + atom];
                 const float wgt = w ? scale * *w : scale;
                 const float4 x = load4(up[k0 + atom], tile_r0 + 4 * part, o.rows);
                 ru[e] = make_float4(wgt * x.x, wgt * x.y, wgt * x.z, wgt * x.w);
@@ -141,7 +161,7 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
     for (int first = o.first; first < o.last; first += batch) {
         const int nm = min(batch, o.last - first);
         __syncthreads();                                         // the previous list is spent
-        for (int q = tid; q < nm; q += 256) kept_of[q] = min(*msgs[first + q].count, msgs[first + q].capacity);
+        for (int q = tid; q < nm; q += 256) kept_of[q] = min(*global(msgs[first + q].count), msgs[first + q].capacity);
         __syncthreads();
         // several messages: everything fits the list by the host's choice of `batch` (one run); a message of its
         // own: runs of ATOMS_MAX atoms, `run` = first atom of the run
@@ -154,9 +174,9 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
                 const DecMsg m = msgs[first + q];
                 const int kept = max(0, min(kept_of[q] - run, ATOMS_MAX - at));
                 for (int k = 0; k < kept; ++k) {
-                    up[at + k] = m.U + (size_t)(run + k) * o.rows;
-                    vp[at + k] = m.V + (size_t)(run + k) * o.cols;
-                    wp[at + k] = m.w ? m.w + run + k : nullptr;    // folded messages carry the weight in U
+                    up[at + k] = global(m.U) + (size_t)(run + k) * o.rows;
+                    vp[at + k] = global(m.V) + (size_t)(run + k) * o.cols;
+                    wp[at + k] = m.w ? global(m.w) + run + k : nullptr;    // folded messages carry the weight in U
                 }
                 if (q == nm - 1) total_sh = at + kept;
             }
@@ -184,21 +204,15 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
             }
         }
     }
-    const int r0 = tile_r0 + row_off, c0 = tile_c0 + col_off;
+    const Global<float> corner = global(o.out) + (long long)row0 * o.ld + col0;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-            const int col = c0 + cb * 32 + l32;
+        for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = r0 + rb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (row < o.rows && col < o.cols) {
-                    float* dst = o.out + (size_t)row * o.ld + col;
-                    *dst = ACCUMULATE ? *dst + acc[rb][cb][v] : acc[rb][cb][v];
-                }
-            }
-        }
+            for (int v = 0; v < 16; ++v)
+                if (row0 + below(rb, v) < o.rows && col0 + cb * 32 < o.cols)
+                    corner[below(rb, v) * o.ld + cb * 32] = ACCUMULATE ? old[rb][cb][v] + acc[rb][cb][v] : acc[rb][cb][v];
 }
 
 // ------------------------------------------------------------------------------------------------
