@@ -16,11 +16,11 @@
 // skipped on the device.
 //
 // Sampling and packing.  Coordinate i is kept iff u_i < p_i (Philox stream, float32 compare) and is
-// stored as (i, g_i / p_i) in ascending i.  The encoder reads the gradient twice ("the two-read encoder"
-// below): once for the level-0 histogram, once to draw every uniform and settle it against the bracket
-// that level 0 leaves for p_i; the few draws that fall inside the bracket wait for the exact water level.
-// The l_q encoder (Section 4), whose probabilities need only a norm, uses the plain form: a counting pass
-// per 4096-element chunk, a scan of the chunk counts, and a writing pass that reads the keep bits.
+// stored as (i, g_i / p_i) in ascending i.  The encoder reads the gradient twice: once for the level-0 histogram, once to
+// draw every uniform against the bracket that level 0 leaves for p_i.  Whatever may be kept is written down in that pass as
+// a record (value and offset), and all that follows reads the records, a hundredth of the gradient: the third level of the
+// search, the settling of the few draws inside the bracket, the message.  The l_q encoder (Section 4), whose probabilities
+// need only a norm, draws against the exact p and has nothing to settle.
 #include <cmath>
 #include <vector>
 
@@ -34,7 +34,6 @@ namespace {
 constexpr int L0_BITS = 11, L1_BITS = 10, L2_BITS = 10;
 constexpr int NBUCKET = 1 << L0_BITS;        // the largest level
 constexpr int HIST_WGS = 1024;
-constexpr int CHUNK = 4096;                  // elements per sampling workgroup (256 threads x 4 float4)
 
 // What a level leaves behind: either the final answer or the path to continue on.
 struct SolveOut {
@@ -45,6 +44,7 @@ struct SolveOut {
     unsigned long long n_s;       // done: number of capped elements
     double tail;                  // done: sum of the uncapped magnitudes
     double lo, hi;                // level 0: the edges of the chosen bucket; the water level lies in [lo, hi]
+    unsigned int count;           // elements in the chosen bucket
 };
 
 struct EwState {
@@ -160,14 +160,14 @@ __global__ __launch_bounds__(LEVEL == 0 ? 1024 : 256) void ew_hist(const float* 
 // to `out` (LDS or global, visible to the workgroup after the call's last barrier).
 // T threads (256 or 1024); COHERENT: the histogram was written by other workgroups of the running kernel (atomics), so it
 // is read with device-scope atomic loads instead of plain ones.
-// scratch: LDS, (2 T + 1) x 8 bytes.
+// scratch: LDS, (2 T / 64 + 1) x 8 bytes.
 template <int LEVEL, int T = 256, bool COHERENT = false>
 __device__ inline void solve_level(const EwState* st, double s, unsigned int prefix, unsigned long long n_above0,
                                    double sum_below0, SolveOut* out, unsigned long long* scratch)
 {
     unsigned long long* cpart = scratch;
-    double* spart = (double*)(scratch + T);
-    int& best = *(int*)(scratch + 2 * T);
+    double* spart = (double*)(scratch + T / 64);
+    int& best = *(int*)(scratch + 2 * (T / 64));
     constexpr int NB = LEVEL == 0 ? (1 << L0_BITS) : (1 << L1_BITS);
     constexpr int SHIFT = LEVEL == 0 ? 20 : LEVEL == 1 ? 10 : 0;
     constexpr int PER = NB / T;
@@ -200,21 +200,31 @@ __device__ inline void solve_level(const EwState* st, double s, unsigned int pre
         s_mine += sum_r[e];
     }
     __syncthreads();                                             // (the scratch may still be read from a previous call)
-    cpart[tid] = c_mine;
-    spart[tid] = s_mine;
+    // suffix scan of the counts and prefix scan of the sums over the threads: in the wave by shuffles, then over the waves
+    const int lane = tid & 63, wave = tid >> 6;
+    unsigned long long c_scan = c_mine;
+    double s_scan = s_mine;
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long cv = __shfl_down(c_scan, off);
+        const double sv = __shfl_up(s_scan, off);
+        if (lane + off < 64) c_scan += cv;
+        if (lane >= off) s_scan += sv;
+    }
+    if (lane == 0) cpart[wave] = c_scan;
+    if (lane == 63) spart[wave] = s_scan;
     if (tid == 0) best = 0;
     __syncthreads();
-    // suffix scan of the counts and prefix scan of the sums over the 256 threads (log-step, in LDS)
-    for (int off = 1; off < T; off <<= 1) {
-        const unsigned long long cv = tid + off < T ? cpart[tid + off] : 0ull;
-        const double sv = tid >= off ? spart[tid - off] : 0.0;
-        __syncthreads();
-        cpart[tid] += cv;
-        spart[tid] += sv;
-        __syncthreads();
+    unsigned long long c_after = c_scan - c_mine;                // count in buckets owned by later threads
+    double s_before = __shfl_up(s_scan, 1);                      // sum in buckets owned by earlier threads
+    if (lane == 0) s_before = 0.0;
+    {
+        double earlier = 0.0;
+        for (int w = 0; w < T / 64; ++w) {
+            if (w > wave) c_after += cpart[w];
+            if (w < wave) earlier += spart[w];
+        }
+        s_before += earlier;
     }
-    const unsigned long long c_after = tid < T - 1 ? cpart[tid + 1] : 0ull; // count in buckets owned by later threads
-    const double s_before = tid > 0 ? spart[tid - 1] : 0.0;                 // sum in buckets owned by earlier threads
 
     // h at the lower edge of bucket b:  lo_b * (s - #{elements in buckets >= b}) - sum(buckets < b)
     {
@@ -262,6 +272,7 @@ __device__ inline void solve_level(const EwState* st, double s, unsigned int pre
             done = true;
         }
         out->done = done ? 1 : 0;
+        out->count = c;
         out->n_s = n_s;
         out->tail = tail;
         out->n_above = n_above;
@@ -295,7 +306,7 @@ template <int LEVEL>
 __global__ __launch_bounds__(256) void ew_solve(EwState* st, double s)
 {
     __shared__ SolveOut out;
-    __shared__ unsigned long long scratch[2 * 256 + 1];
+    __shared__ unsigned long long scratch[2 * 4 + 1];
     unsigned int prefix = 0u;
     unsigned long long n_above = 0ull;
     double sum_below = 0.0;
@@ -395,171 +406,152 @@ __device__ inline float4 load4(const float* g, long long q, long long n, bool ve
     return x;
 }
 
-// Kept coordinates per chunk, and their keep bits.  Wave w of a chunk owns float4 [w*256, (w+1)*256) of the
-// chunk, in four iterations of 64 lanes: order inside a chunk is (wave, iteration, lane, component) =
-// ascending index.  keep[((chunk*4 + wave)*4 + iteration)*4 + component] holds one bit per lane, so that the
-// writer neither draws the random numbers again nor reads the gradient outside the kept coordinates.
-__global__ __launch_bounds__(256) void ew_count(const float* __restrict__ g, long long n, const EwState* st,
-                                                unsigned long long stream_id, unsigned long long seed,
-                                                unsigned int* __restrict__ chunk_count,
-                                                unsigned long long* __restrict__ keep)
+// ---- records ------------------------------------------------------------------------------------------
+// A wave owns a segment of the gradient: `steps` float4 per lane, one after the other (step, lane, component = ascending
+// index).  The coordinates of the segment that are, or may be, kept are written to the segment's slots in that order: a
+// 2-byte word (offset in the segment, and one flag above it) and, for the entry-wise encoder, the 4-byte value.
+// The slots are sized for about six times the density of a 1 % message; a segment that holds more is marked and drawn again
+// from the gradient wherever its records would be read (same draws, same result), so any distribution is encoded.
+constexpr int STEP = 256;                    // elements of a wave per step
+constexpr int STEP_BYTES = 288;              // slots per step: 48 entry-wise records, 144 of l_q
+constexpr unsigned int OVER = 0x80000000u;   // segment with more candidates than slots
+constexpr unsigned int FLAG_BIT = 0x1000u;   // entry-wise: kept for sure; l_q: negative
+constexpr unsigned int DROPPED = 0x2000u;    // entry-wise: settled, not kept
+constexpr int MAX_GROUP = 64;
+constexpr unsigned int DIRECT_MAX = 65536;
+
+struct Segments {
+    unsigned int* count;          // [n_seg] records of a segment; in a group with an OVER among them: kept coordinates | OVER
+    unsigned int* group_kept;     // [n_groups] kept coordinates of a group of per_group segments
+    unsigned char* slots;
+    long long n_seg, n_groups;
+    int slot_bytes;               // per segment
+    int per_group;
+};
+
+// Entry-wise records: values first, then the words.
+struct Slots {
+    float* val;
+    unsigned short* word;
+    int capacity;
+};
+
+__device__ inline Slots ew_slots(const Segments& sg, long long seg)
 {
-    __shared__ unsigned int wsum[4];
-    const double ratio = st->ratio;
+    unsigned char* p = sg.slots + seg * sg.slot_bytes;
+    const int cap = sg.slot_bytes / 6 & ~1;
+    return Slots{(float*)p, (unsigned short*)(p + 4 * cap), cap};
+}
+
+__device__ inline Slots lq_slots(const Segments& sg, long long seg)
+{
+    return Slots{nullptr, (unsigned short*)(sg.slots + seg * sg.slot_bytes), sg.slot_bytes / 2};
+}
+
+// The records of a group, read by a workgroup as one list: before[k] are those ahead of the group's segment k.
+struct Group {
+    unsigned int before[MAX_GROUP + 1];
+    int over;                     // a segment is OVER: none of the group's records is used
+};
+
+// All threads call; the group is complete behind the caller's next barrier.
+__device__ inline void load_group(const Segments& sg, long long group, Group& gr)
+{
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
+    const long long first = group * sg.per_group;
+    const unsigned int c = lane < sg.per_group && first + lane < sg.n_seg ? sg.count[first + lane] : 0u;
+    unsigned int v = c & ~OVER;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int w = __shfl_up(v, o);
+        if (lane >= o) v += w;
+    }
+    gr.before[lane + 1] = v;
+    const unsigned long long over = __ballot((c & OVER) != 0u);
+    if (lane == 0) { gr.before[0] = 0u; gr.over = over != 0ull; }
+}
+
+// Segment of the group that holds record t
+__device__ inline int segment_of(const Group& gr, int per_group, unsigned int t)
+{
+    int k = 0;
+    for (int half = per_group >> 1; half > 0; half >>= 1)
+        if (gr.before[k + half] <= t) k += half;
+    return k;
+}
+
+// ballots[e]: lanes with component e in the list.  Position of this lane's first listed component, and how many there are.
+__device__ inline unsigned int listed_before(const unsigned long long (&ballots)[4])
+{
+    unsigned int r = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        r = __builtin_amdgcn_mbcnt_hi((unsigned int)(ballots[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)ballots[e], r));
+    return r;
+}
+__device__ inline unsigned int listed_total(const unsigned long long (&ballots)[4])
+{
+    return (unsigned int)(__popcll(ballots[0]) + __popcll(ballots[1]) + __popcll(ballots[2]) + __popcll(ballots[3]));
+}
+
+// Calls visit(position, offset in the segment, value, p) for every kept coordinate of a segment, drawn from the gradient
+// with the exact ratio; returns their number.  All lanes of the wave call.
+template <int STEPS, typename VISIT>
+__device__ inline unsigned int draw_segment(const float* __restrict__ g, long long n, long long seg,
+                                            unsigned long long stream_id, unsigned long long seed, double ratio, VISIT visit)
+{
     const bool vec = (((size_t)g) & 15) == 0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long q0 = (long long)blockIdx.x * (CHUNK / 4) + wave * 256;
-    unsigned long long* kw = keep + ((long long)blockIdx.x * 4 + wave) * 16;
-    unsigned int kept = 0;                                   // wave-uniform
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const long long q = q0 + j * 64 + lane;
-        unsigned int bits = 0;
+    const int lane = threadIdx.x & 63;
+    unsigned int fill = 0u;                                      // wave-uniform
+    for (int j = 0; j < STEPS; ++j) {
+        const long long q = (seg * STEPS + j) * 64 + lane;
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), p = x;
+        unsigned int bits = 0u;
         if (q * 4 < n) {
-            float4 p;
-            bits = draw4(load4(g, q, n, vec), q, stream_id, seed, ratio, p);
+            x = load4(g, q, n, vec);
+            bits = draw4(x, q, stream_id, seed, ratio, p);
         }
-        unsigned long long mine = 0ull;
+        unsigned long long ballots[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const unsigned long long ballot = __ballot((bits >> c) & 1u);
-            kept += __popcll(ballot);
-            if (lane == c) mine = ballot;
-        }
-        if (lane < 4) kw[j * 4 + lane] = mine;
+        for (int e = 0; e < 4; ++e) ballots[e] = __ballot((bits >> e) & 1u);
+        unsigned int pos = fill + listed_before(ballots);
+        const float xs[4] = {x.x, x.y, x.z, x.w}, ps[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((bits >> e) & 1u) visit(pos++, (unsigned int)(j * STEP + lane * 4 + e), xs[e], ps[e]);
+        fill += listed_total(ballots);
     }
-    if (lane == 0) wsum[wave] = kept;
-    __syncthreads();
-    if (threadIdx.x == 0) chunk_count[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    return fill;
 }
 
-// Exclusive scan of the chunk counts (single workgroup).
-__global__ __launch_bounds__(256) void ew_scan(const unsigned int* __restrict__ chunk_count, long long n_chunks,
-                                               unsigned long long* __restrict__ chunk_base, EwState* st,
-                                               long long* count_out, long long capacity, int* flags)
-{
-    __shared__ unsigned long long part[256];
-    const int tid = threadIdx.x;
-    const long long per = (n_chunks + 255) / 256;
-    const long long lo = min(n_chunks, tid * per), hi = min(n_chunks, lo + per);
-    unsigned long long mine = 0ull;
-    for (long long c = lo; c < hi; ++c) mine += chunk_count[c];
-    part[tid] = mine;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const unsigned long long v = tid >= off ? part[tid - off] : 0ull;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    unsigned long long base = tid > 0 ? part[tid - 1] : 0ull;
-    for (long long c = lo; c < hi; ++c) {
-        chunk_base[c] = base;
-        base += chunk_count[c];
-    }
-    if (tid == 255) {
-        st->total_kept = base;
-        *count_out = (long long)base;
-        if ((long long)base > capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
-    }
-}
-
-// Writes the kept coordinates of one chunk in ascending order.  The keep bits give every kept coordinate
-// its rank inside the chunk; the coordinates are first listed in LDS by rank, then thread t takes the t-th
-// one, so the gradient is read and the message written in one batch of loads and coalesced stores.
-__global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, const EwState* st,
-                                                const unsigned long long* __restrict__ keep,
-                                                const unsigned long long* __restrict__ chunk_base, long long capacity,
-                                                unsigned int* __restrict__ idx, float* __restrict__ val /* null: signs in idx */)
-{
-    __shared__ unsigned int wsum[4];
-    __shared__ unsigned short local[CHUNK];    // coordinate offsets inside the chunk, by rank
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned long long* kw = keep + ((long long)blockIdx.x * 4 + wave) * 16;
-    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-
-    unsigned int bits[4], before[4];           // keep bits; kept coordinates of this wave ahead of this lane's float4
-    unsigned int running = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        unsigned int ahead = 0, all = 0;
-        bits[j] = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const unsigned long long ballot = kw[j * 4 + c];
-            bits[j] |= (unsigned int)((ballot >> lane) & 1ull) << c;
-            ahead += __popcll(ballot & lt_mask);
-            all += __popcll(ballot);
-        }
-        before[j] = running + ahead;
-        running += all;
-    }
-    if (lane == 0) wsum[wave] = running;
-    __syncthreads();
-    unsigned int wave_base = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        if (w < wave) wave_base += wsum[w];
-        total += wsum[w];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        unsigned int pos = wave_base + before[j];
-        const unsigned int off = (unsigned int)(wave * 256 + j * 64 + lane) * 4u;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if ((bits[j] >> c) & 1u) local[pos++] = (unsigned short)(off + c);
-    }
-    __syncthreads();
-    const double ratio = st->ratio;
-    const unsigned long long base = chunk_base[blockIdx.x];
-    const long long i0 = (long long)blockIdx.x * CHUNK;
-    for (unsigned int t = threadIdx.x; t < total; t += 256) {
-        const unsigned long long pos = base + t;
-        if ((long long)pos < capacity) {
-            const long long i = i0 + local[t];
-            const float x = g[i];
-            if (val) {
-                idx[pos] = (unsigned int)i;
-                val[pos] = x / ew_probability(x, ratio);
-            } else {                                             // l_q message: the sign rides in bit 31
-                idx[pos] = (unsigned int)i | (x < 0.0f ? 0x80000000u : 0u);
-            }
-        }
-    }
-}
-
-// ---- the two-read encoder -----------------------------------------------------------------------------
-// After the level-0 histogram the water level tau = tail / (s - n_s) is known to lie inside one bucket [lo, hi] of the
-// float bit pattern (12.5 % wide), so p_i = min(1, |g_i| / tau) is bracketed for every element, and because rounding
-// is monotone,  fl(|g_i| / hi) <= p_i <= fl(|g_i| / lo)  holds for the float32 p_i that the final ratio will give.
-// The second pass over g therefore draws every element's uniform once and settles it at once wherever the bracket
-// allows: kept for sure if u < p_lo, dropped for sure if u >= p_hi.  What lies between (about 0.12 s elements) is
-// marked undecided and settled by ew_settle once the remaining levels have fixed tau exactly.  The same pass forms
-// the level-1 histogram of the elements inside the chosen bucket, so g is read twice in all unless a third level
-// is needed.
-
-constexpr int SUPER = 256;                   // chunks per entry of the coarse count table
-
-// Second pass, one chunk per workgroup; the level-0 result is read from st->lvl[0] (the launch before left it there).
-// Layout of the keep / undecided bits: see ew_count.
-__global__ __launch_bounds__(256) void ew_pass_b(const float* __restrict__ g, long long n, long long n_chunks, EwState* st,
-                                                 double s, unsigned long long stream_id, unsigned long long seed,
-                                                 unsigned int* __restrict__ chunk_count,
-                                                 unsigned long long* __restrict__ keep,
-                                                 unsigned long long* __restrict__ und)
+// Second pass of the entry-wise encoder over the gradient; the level-0 result is read from st->lvl[0] (the launch before
+// left it there).
+// After level 0 the water level tau = tail / (s - n_s) is known to lie inside one bucket [lo, hi] of the float bit pattern
+// (12.5 % wide), so p_i = min(1, |g_i| / tau) is bracketed for every element, and because rounding is monotone,
+// fl(|g_i| / hi) <= p_i <= fl(|g_i| / lo)  holds for the float32 p_i that the final ratio will give.  An element is dropped
+// here if u >= p_hi, marked as kept for sure if u < p_lo; what lies between (about 0.12 s elements) is settled by ew_settle
+// once the remaining levels have fixed tau exactly.  Every element of the chosen bucket has p_hi >= 1 and so a record: level
+// 1 is histogrammed here and level 2 from the records.
+// Bound by the Philox rounds (18 wide multiplications per four elements): everything per element that can be left to the
+// candidates, one element in fifty, is left to them.  2^28 elements, 1 % kept: 264 us, where drawing, keep bits, and gathering
+// the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us (now: 264,
+// 22 for level 2, 21 to settle, 19 to write).
+template <int STEPS>
+__global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long long n, EwState* st, double s,
+                                               unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int l1cnt[1 << L1_BITS];
     __shared__ unsigned long long l1sig[1 << L1_BITS];
-    __shared__ unsigned int wsum[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const long long seg = (long long)blockIdx.x * 4 + (tid >> 6);
     const SolveOut so = st->lvl[0];
     const bool done = so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
-    // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio): with
-    // r_lo <= ratio (1 - 2^-22) and r_hi >= ratio (1 + 2^-22),  fl32(|g| r_lo) (1 - 2^-22) <= p <= fl32(|g| r_hi) (1 + 2^-22)
-    // (each rounding moves a value by at most 2^-24 of itself).  A bracket that is a little wide only sends a few more
-    // coordinates to ew_settle, which decides with the exact formula.
+    // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
+    // uniform (an integer below 2^24): with r_lo <= ratio (1 - 2^-22) and r_hi >= ratio (1 + 2^-22),
+    // fl32(|g| r_lo) (1 - 2^-22) <= p <= fl32(|g| r_hi) (each rounding moves a value by at most 2^-24 of itself; where
+    // |g| r_hi 2^24 underflows, p is zero).  A bracket that is a little wide only sends a few more coordinates to ew_settle,
+    // which decides with the exact formula.
     double ratio_lo, ratio_hi;
     if (done) {
         ratio_lo = ratio_hi = final_ratio(s, so.n_s, so.tail);
@@ -567,73 +559,85 @@ __global__ __launch_bounds__(256) void ew_pass_b(const float* __restrict__ g, lo
         ratio_lo = so.hi < inf ? 1.0 / so.hi : 0.0;              // 1 / hi <= ratio <= 1 / lo
         ratio_hi = so.lo > 0.0 ? 1.0 / so.lo : inf;
     }
-    const float down = 1.0f - 2.384185791015625e-07f, up = 1.0f + 2.384185791015625e-07f;    // 1 -+ 2^-22
-    // (1 - 2^-21): covers its own rounding; a ratio beyond the float range is bounded from below by the largest float
-    const float r_lo = ratio_lo < 3.0e38 ? (float)(ratio_lo * (1.0 - 4.76837158203125e-07)) : 3.0e38f;
-    const float r_hi = ratio_hi < 3.0e38 ? (float)(ratio_hi * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
-    const unsigned int bucket = so.prefix;
-    if (!done) {
+    const double down = 1.0 - 4.76837158203125e-07, up = 1.0 + 4.76837158203125e-07;     // 1 -+ 2^-21, of the ratios
+    // a ratio beyond the float range is bounded from below by the largest float and from above by infinity
+    const float r_lo = ratio_lo < 1.0e31 ? (float)(ratio_lo * 16777216.0 * down) : 3.0e38f;
+    const float r_hi = ratio_hi < 1.0e31 ? (float)(ratio_hi * 16777216.0 * up) : __int_as_float(0x7f800000);
+    const bool zeros = !(ratio_hi < 1.0e31);                     // 0 * infinity: zeros are taken out by hand
+    const unsigned int bucket = done ? 0xFFFFFFFFu : so.prefix;
+    // Few elements in the bucket: straight into the global histogram, where they hardly ever meet.  Many: through LDS.
+    const bool through_lds = !done && so.count > DIRECT_MAX;
+    if (through_lds) {
         for (int b = tid; b < (1 << L1_BITS); b += 256) { l1cnt[b] = 0u; l1sig[b] = 0ull; }
         __syncthreads();
     }
 
-    const bool vec = (((size_t)g) & 15) == 0;
-    {
-        const long long c = blockIdx.x;
-        const long long q0 = c * (CHUNK / 4) + wave * 256;
-        unsigned long long* kw = keep + (c * 4 + wave) * 16;
-        unsigned long long* uw = und + (c * 4 + wave) * 16;
-        unsigned int kept = 0;                                   // wave-uniform
+    if (seg < sg.n_seg) {
+        const bool vec = (((size_t)g) & 15) == 0;
+        const Slots sl = ew_slots(sg, seg);
+        unsigned int fill = 0u;                                  // wave-uniform
+        for (int j0 = 0; j0 < STEPS; j0 += 4) {
+            float4 xv[4];
+            const long long q0 = (seg * STEPS + j0) * 64 + lane;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long long q = q0 + j * 64 + lane;
-            unsigned int sure = 0, open = 0;
-            if (q * 4 < n) {
-                const float4 x = load4(g, q, n, vec);
-                const u32x4 rnd = philox4x32_10((unsigned long long)q, stream_id, seed);
-                const float xs[4] = {x.x, x.y, x.z, x.w};
-                const float us[4] = {u01(rnd.x), u01(rnd.y), u01(rnd.z), u01(rnd.w)};
+            for (int u = 0; u < 4; ++u) xv[u] = load4(g, q0 + u * 64, n, vec);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float a = fabsf(xs[e]);
-                    // (a = 0: both are 0, never kept.  The floor 2^-24 under p_hi keeps the draw u = 0 undecided for
-                    // an element whose bound underflows.)
-                    const float p_lo = a > 0.0f ? fminf(1.0f, a * r_lo) * down : 0.0f;
-                    const float p_hi = a > 0.0f ? fmaxf(fminf(1.0f, a * r_hi * up), 5.9604644775390625e-08f) : 0.0f;
-                    if (us[e] < p_lo) sure |= 1u << e;
-                    else if (us[e] < p_hi) open |= 1u << e;
-                    if (!done) {
-                        const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
-                        if ((key >> 20) == bucket && (q * 4 + e) < n) {
-                            atomicAdd(&l1cnt[(key >> 10) & ((1 << L1_BITS) - 1)], 1u);
-                            atomicAdd(&l1sig[(key >> 10) & ((1 << L1_BITS) - 1)], (unsigned long long)significand(key));
+            for (int u = 0; u < 4; ++u) {
+                const u32x4 rnd = philox4x32_10((unsigned long long)(unsigned int)(q0 + u * 64), stream_id, seed);
+                const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+                const float us[4] = {(float)(rnd.x >> 8), (float)(rnd.y >> 8), (float)(rnd.z >> 8), (float)(rnd.w >> 8)};
+                bool in[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) in[e] = !(us[e] >= fabsf(xs[e]) * r_hi);     // (a NaN is a candidate)
+                if (zeros) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) in[e] = in[e] && xs[e] != 0.0f;
+                }
+                unsigned long long ballots[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
+                if (ballots[0] | ballots[1] | ballots[2] | ballots[3]) {
+                    unsigned int pos = fill + listed_before(ballots);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (in[e]) {
+                            const bool sure = us[e] < fminf(16777216.0f, fabsf(xs[e]) * r_lo) * (1.0f - 2.384185791015625e-07f);
+                            if (pos < (unsigned int)sl.capacity) {
+                                sl.val[pos] = xs[e];
+                                sl.word[pos] = (unsigned short)(((j0 + u) * STEP + lane * 4 + e) | (sure ? FLAG_BIT : 0u));
+                            }
+                            ++pos;
+                            const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
+                            if ((key >> 20) == bucket) {
+                                const unsigned int b = (key >> 10) & ((1 << L1_BITS) - 1);
+                                if (through_lds) {
+                                    atomicAdd(&l1cnt[b], 1u);
+                                    atomicAdd(&l1sig[b], (unsigned long long)significand(key));
+                                } else {
+                                    atomicAdd(&st->cnt[1][b], 1u);
+                                    atomicAdd(&st->sig[1][b], (unsigned long long)significand(key));
+                                }
+                            }
                         }
                     }
+                    fill += listed_total(ballots);
                 }
             }
-            unsigned long long mine = 0ull, mine_open = 0ull;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned long long ballot = __ballot((sure >> e) & 1u);
-                const unsigned long long ballot_open = __ballot((open >> e) & 1u);
-                kept += __popcll(ballot);
-                if (lane == e) { mine = ballot; mine_open = ballot_open; }
-            }
-            if (lane < 4) { kw[j * 4 + lane] = mine; uw[j * 4 + lane] = mine_open; }
         }
-        if (lane == 0) wsum[wave] = kept;
-        __syncthreads();
-        if (tid == 0) chunk_count[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        if (lane == 0) sg.count[seg] = fill <= (unsigned int)sl.capacity ? fill : OVER;
     }
     if (done) {
         if (blockIdx.x == 0 && tid == 0) st->lvl[1].done = 1;    // nothing left for the levels below
         return;
     }
-    for (int b = tid; b < (1 << L1_BITS); b += 256) {
-        const unsigned int cnt = l1cnt[b];
-        if (cnt) {
-            atomicAdd(&st->cnt[1][b], cnt);
-            atomicAdd(&st->sig[1][b], l1sig[b]);
+    if (through_lds) {
+        __syncthreads();
+        for (int b = tid; b < (1 << L1_BITS); b += 256) {
+            const unsigned int cnt = l1cnt[b];
+            if (cnt) {
+                atomicAdd(&st->cnt[1][b], cnt);
+                atomicAdd(&st->sig[1][b], l1sig[b]);
+            }
         }
     }
     // the last workgroup to finish solves level 1 from the merged histogram
@@ -643,169 +647,185 @@ __global__ __launch_bounds__(256) void ew_pass_b(const float* __restrict__ g, lo
     if (tid == 0) publish(st, 1, out, s);
 }
 
-// Level-2 histogram of the elements on the path that level 1 chose (nothing to do if level 1 settled everything, the
-// usual case); its last workgroup solves level 2.
-__global__ __launch_bounds__(256) void ew_hist2_solve2(const float* __restrict__ g, long long n, EwState* st, double s)
+// Level-2 histogram of the elements on the path that level 1 chose, from the records (nothing to do if level 1 settled
+// everything); its last workgroup solves level 2.
+template <int STEPS>
+__global__ __launch_bounds__(256) void ew_level2(const float* __restrict__ g, long long n, EwState* st, double s, Segments sg)
 {
-    __shared__ unsigned long long acc[1 << L2_BITS];
+    __shared__ unsigned int cnt[1 << L2_BITS];
+    __shared__ unsigned long long sig[1 << L2_BITS];
+    __shared__ Group gr;
     __shared__ SolveOut out;
     const SolveOut in = st->lvl[1];
     if (in.done) return;
-    hist_body<2, 256>(g, n, st, acc, in.prefix);
+    const int tid = threadIdx.x;
+    for (int b = tid; b < (1 << L2_BITS); b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
+    auto visit = [&](float x) {
+        const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
+        if ((key >> L2_BITS) == in.prefix) {
+            atomicAdd(&cnt[key & ((1 << L2_BITS) - 1)], 1u);
+            atomicAdd(&sig[key & ((1 << L2_BITS) - 1)], (unsigned long long)significand(key));
+        }
+    };
+    for (long long group = blockIdx.x; group < sg.n_groups; group += gridDim.x) {
+        load_group(sg, group, gr);
+        __syncthreads();
+        if (gr.over) {
+            const long long i0 = group * sg.per_group * STEPS * STEP;
+            const long long i1 = min(n, i0 + (long long)sg.per_group * STEPS * STEP);
+            for (long long i = i0 + tid; i < i1; i += 256) visit(g[i]);
+        } else {
+            for (unsigned int t = tid; t < gr.before[MAX_GROUP]; t += 256) {
+                const int k = segment_of(gr, sg.per_group, t);
+                visit(ew_slots(sg, group * sg.per_group + k).val[t - gr.before[k]]);
+            }
+        }
+        __syncthreads();
+    }
+    for (int b = tid; b < (1 << L2_BITS); b += 256) {
+        if (cnt[b]) {
+            atomicAdd(&st->cnt[2][b], cnt[b]);
+            atomicAdd(&st->sig[2][b], sig[b]);
+        }
+    }
     if (!last_workgroup(st->ticket[2])) return;
-    solve_level<2, 256, true>(st, s, in.prefix, in.n_above, in.sum_below, &out, acc);
-    if (threadIdx.x == 0) publish(st, 2, out, s);
+    solve_level<2, 256, true>(st, s, in.prefix, in.n_above, in.sum_below, &out, sig);
+    if (tid == 0) publish(st, 2, out, s);
 }
 
-// Settles the undecided coordinates of one chunk with the final ratio (the draws are repeated for the float4s that
-// hold one), completes the chunk's keep bits and count, and adds the count to the coarse table.  Also leaves the
-// three histograms zeroed for the next call (their last reader has run).
+// Settles the records of a group of segments with the final ratio: the draw of an open one is repeated, and what is not kept
+// is marked.  Leaves the kept count of the group.
+template <int STEPS>
 __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, const EwState* st,
-                                                 unsigned long long stream_id, unsigned long long seed,
-                                                 unsigned int* __restrict__ chunk_count,
-                                                 unsigned long long* __restrict__ keep,
-                                                 const unsigned long long* __restrict__ und)
+                                                 unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int wsum[4];
+    __shared__ Group gr;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const double ratio = st->ratio;                              // final since the last solve
-    const bool vec = (((size_t)g) & 15) == 0;
-    const long long c = blockIdx.x;
-    const long long q0 = c * (CHUNK / 4) + wave * 256;
-    unsigned long long* kw = keep + (c * 4 + wave) * 16;
-    const unsigned long long* uw = und + (c * 4 + wave) * 16;
-    unsigned int added = 0;                                      // wave-uniform
-    const unsigned long long word = lane < 16 ? uw[lane] : 0ull;
-    if (__ballot(word != 0ull)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            unsigned int open = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned long long w = __shfl(word, j * 4 + e);
-                open |= (unsigned int)((w >> lane) & 1ull) << e;
+    const long long first = (long long)blockIdx.x * sg.per_group;
+    load_group(sg, blockIdx.x, gr);
+    __syncthreads();
+    unsigned int kept = 0u;                                      // wave-uniform
+    if (gr.over) {
+        for (int k = wave; k < sg.per_group && first + k < sg.n_seg; k += 4) {
+            const unsigned int c = draw_segment<STEPS>(g, n, first + k, stream_id, seed, ratio,
+                                                       [](unsigned int, unsigned int, float, float) {});
+            if (lane == 0) sg.count[first + k] = c | OVER;
+            kept += c;
+        }
+    } else {
+        for (unsigned int t0 = 0; t0 < gr.before[MAX_GROUP]; t0 += 256) {
+            const unsigned int t = t0 + tid;
+            bool keep = false;
+            if (t < gr.before[MAX_GROUP]) {
+                const int k = segment_of(gr, sg.per_group, t);
+                const Slots sl = ew_slots(sg, first + k);
+                const unsigned int r = t - gr.before[k], word = sl.word[r];
+                const float x = sl.val[r];
+                keep = (word & FLAG_BIT) != 0u;
+                if (!keep) {
+                    const unsigned int off = word & (FLAG_BIT - 1);
+                    const u32x4 rnd = philox4x32_10((unsigned long long)((first + k) * STEPS * 64 + (off >> 2)), stream_id, seed);
+                    const unsigned int bits = (off & 2) ? ((off & 1) ? rnd.w : rnd.z) : ((off & 1) ? rnd.y : rnd.x);
+                    keep = u01(bits) < ew_probability(x, ratio);
+                    if (!keep) sl.word[r] = (unsigned short)(word | DROPPED);
+                }
             }
-            if (__ballot(open != 0u) == 0ull) continue;          // (uniform)
-            const long long q = q0 + j * 64 + lane;
-            unsigned int now = 0;
-            if (open) {
-                float4 p;
-                now = draw4(load4(g, q, n, vec), q, stream_id, seed, ratio, p) & open;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned long long ballot = __ballot((now >> e) & 1u);
-                added += __popcll(ballot);
-                if (lane == e && ballot) kw[j * 4 + e] |= ballot;
-            }
+            kept += (unsigned int)__popcll(__ballot(keep));
         }
     }
-    if (lane == 0) wsum[wave] = added;
+    if (lane == 0) wsum[wave] = kept;
     __syncthreads();
-    const unsigned int more = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-    if (tid == 0 && more) chunk_count[c] += more;
+    if (tid == 0) sg.group_kept[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-// Sums of the chunk counts per group of SUPER chunks, for gradients so long that a workgroup of ew_write2 could not
-// add up all the counts before its own (one workgroup per group).
-__global__ __launch_bounds__(256) void ew_super(const unsigned int* __restrict__ chunk_count, long long n_chunks,
-                                                unsigned long long* __restrict__ super_count)
+// The message from the settled records, one group of segments per workgroup, which adds up the counts of all groups before
+// its own by itself.  The last group also reports the total.
+// LQ: every record is kept, and the message's words are index and sign (bit 31) alone.
+template <int STEPS, bool LQ>
+__global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, long long n, EwState* st,
+                                                unsigned long long stream_id, unsigned long long seed, Segments sg,
+                                                long long capacity, unsigned int* __restrict__ idx, float* __restrict__ val,
+                                                long long* count_out, int* flags)
 {
-    __shared__ unsigned long long part[4];
-    const long long i = (long long)blockIdx.x * SUPER + threadIdx.x;
-    unsigned long long v = i < n_chunks ? chunk_count[i] : 0u;
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) super_count[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-
-// ew_write with the chunk's offset summed up by the workgroup itself: the counts of all chunks before it (for very
-// long gradients: the coarse table up to the chunk's group of SUPER chunks, then the counts inside the group).  The
-// last chunk also reports the total.  Leaves the three histograms zeroed for the next call.
-__global__ __launch_bounds__(256) void ew_write2(const float* __restrict__ g, EwState* st,
-                                                 const unsigned long long* __restrict__ keep,
-                                                 const unsigned int* __restrict__ chunk_count,
-                                                 const unsigned long long* __restrict__ super_count /* null: add up chunk_count */,
-                                                 long long capacity,
-                                                 unsigned int* __restrict__ idx, float* __restrict__ val /* null: signs in idx */,
-                                                 long long* count_out, int* flags)
-{
-    __shared__ unsigned int wsum[4];
     __shared__ unsigned long long bsum[4];
-    __shared__ unsigned short local[CHUNK];    // coordinate offsets inside the chunk, by rank
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned long long* kw = keep + ((long long)blockIdx.x * 4 + wave) * 16;
-    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-
-    // offset of the chunk in the message
-    unsigned long long part = 0ull;
-    {
-        const long long sup = super_count ? (long long)blockIdx.x / SUPER : 0;
-        for (long long i = threadIdx.x; i < sup; i += 256) part += super_count[i];
-        for (long long i = sup * SUPER + threadIdx.x; i < (long long)blockIdx.x; i += 256) part += chunk_count[i];
-        for (int o = 32; o > 0; o >>= 1) part += __shfl_down(part, o);
-    }
-
-    unsigned int bits[4], before[4];           // keep bits; kept coordinates of this wave ahead of this lane's float4
-    unsigned int running = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        unsigned int ahead = 0, all = 0;
-        bits[j] = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const unsigned long long ballot = kw[j * 4 + c];
-            bits[j] |= (unsigned int)((ballot >> lane) & 1ull) << c;
-            ahead += __popcll(ballot & lt_mask);
-            all += __popcll(ballot);
-        }
-        before[j] = running + ahead;
-        running += all;
-    }
-    if (lane == 0) { wsum[wave] = running; bsum[wave] = part; }
-    __syncthreads();
-    unsigned int wave_base = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        if (w < wave) wave_base += wsum[w];
-        total += wsum[w];
-    }
-    const unsigned long long base = bsum[0] + bsum[1] + bsum[2] + bsum[3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        unsigned int pos = wave_base + before[j];
-        const unsigned int off = (unsigned int)(wave * 256 + j * 64 + lane) * 4u;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if ((bits[j] >> c) & 1u) local[pos++] = (unsigned short)(off + c);
-    }
-    __syncthreads();
+    __shared__ unsigned int wsum[2][4];
+    __shared__ Group gr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const double ratio = st->ratio;
-    const long long i0 = (long long)blockIdx.x * CHUNK;
-    for (unsigned int t = threadIdx.x; t < total; t += 256) {
-        const unsigned long long pos = base + t;
+    const long long first = (long long)blockIdx.x * sg.per_group;
+    unsigned long long part = 0ull;
+    for (long long i = tid; i < (long long)blockIdx.x; i += 256) part += sg.group_kept[i];
+    load_group(sg, blockIdx.x, gr);
+    for (int o = 32; o > 0; o >>= 1) part += __shfl_down(part, o);
+    if (lane == 0) bsum[wave] = part;
+    __syncthreads();
+    unsigned long long base = bsum[0] + bsum[1] + bsum[2] + bsum[3];
+    auto put = [&](unsigned long long pos, unsigned int i, float x, float p) {
         if ((long long)pos < capacity) {
-            const long long i = i0 + local[t];
-            const float x = g[i];
-            if (val) {
-                idx[pos] = (unsigned int)i;
-                val[pos] = x / ew_probability(x, ratio);
-            } else {                                             // l_q message: the sign rides in bit 31
-                idx[pos] = (unsigned int)i | (x < 0.0f ? 0x80000000u : 0u);
+            if (LQ) {
+                idx[pos] = i | (x < 0.0f ? 0x80000000u : 0u);
+            } else {
+                idx[pos] = i;
+                val[pos] = x / p;
             }
         }
+    };
+    if (gr.over) {
+        for (int k = wave; k < sg.per_group && first + k < sg.n_seg; k += 4) {
+            const unsigned long long pos0 = base + gr.before[k];
+            const unsigned int i0 = (unsigned int)((first + k) * STEPS * STEP);
+            draw_segment<STEPS>(g, n, first + k, stream_id, seed, ratio,
+                                [&](unsigned int pos, unsigned int off, float x, float p) { put(pos0 + pos, i0 + off, x, p); });
+        }
+        base += gr.before[MAX_GROUP];
+    } else {
+        for (unsigned int t0 = 0; t0 < gr.before[MAX_GROUP]; t0 += 256) {
+            const unsigned int t = t0 + tid;
+            bool keep = false;
+            float x = 0.0f;
+            unsigned int i = 0u;
+            if (t < gr.before[MAX_GROUP]) {
+                const int k = segment_of(gr, sg.per_group, t);
+                const unsigned int r = t - gr.before[k];
+                const Slots sl = LQ ? lq_slots(sg, first + k) : ew_slots(sg, first + k);
+                const unsigned int word = sl.word[r];
+                x = LQ ? (word & FLAG_BIT ? -1.0f : 1.0f) : sl.val[r];
+                keep = LQ || !(word & DROPPED);
+                i = (unsigned int)((first + k) * STEPS * STEP) + (word & (FLAG_BIT - 1));
+            }
+            if (LQ) {
+                if (keep) put(base + t, i, x, 1.0f);
+            } else {
+                const unsigned long long ballot = __ballot(keep);
+                unsigned int (&ws)[4] = wsum[(t0 >> 8) & 1];
+                if (lane == 0) ws[wave] = (unsigned int)__popcll(ballot);
+                __syncthreads();
+                unsigned int ahead = __builtin_amdgcn_mbcnt_hi((unsigned int)(ballot >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((unsigned int)ballot, 0u));
+                unsigned int all = 0u;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    if (w < wave) ahead += ws[w];
+                    all += ws[w];
+                }
+                if (keep) put(base + ahead, i, x, ew_probability(x, ratio));
+                base += all;
+            }
+        }
+        if (LQ) base += gr.before[MAX_GROUP];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        const unsigned long long all = base + total;
-        st->total_kept = all;
-        *count_out = (long long)all;
-        if ((long long)all > capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        st->total_kept = base;
+        *count_out = (long long)base;
+        if ((long long)base > capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
     }
-    // the histograms have had their last reader: zero again for the next call
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < 3 * NBUCKET; i += (long long)gridDim.x * 256) {
-        (&st->cnt[0][0])[i] = 0u;
-        (&st->sig[0][0])[i] = 0ull;
+    if (!LQ) {   // the histograms have had their last reader: zero again for the next call
+        for (long long i = (long long)blockIdx.x * 256 + tid; i < 3 * NBUCKET; i += (long long)gridDim.x * 256) {
+            (&st->cnt[0][0])[i] = 0u;
+            (&st->sig[0][0])[i] = 0ull;
+        }
     }
 }
 
@@ -904,29 +924,62 @@ __global__ __launch_bounds__(256) void lq_norm_final(const double* __restrict__ 
     }
 }
 
+// The l_q encoder's pass over the gradient behind the norm: draws against the exact p, one group of segments per workgroup.
+template <int STEPS>
+__global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long long n, const EwState* st,
+                                               unsigned long long stream_id, unsigned long long seed, Segments sg)
+{
+    __shared__ unsigned int wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const double ratio = st->ratio;
+    const int mine = sg.per_group / 4;
+    const long long seg0 = (long long)blockIdx.x * sg.per_group + wave * mine;
+    unsigned int total = 0u;                                     // wave-uniform
+    for (long long seg = seg0; seg < min(seg0 + mine, sg.n_seg); ++seg) {
+        const Slots sl = lq_slots(sg, seg);
+        const unsigned int kept = draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio,
+            [&](unsigned int pos, unsigned int off, float x, float) {
+                if (pos < (unsigned int)sl.capacity) sl.word[pos] = (unsigned short)(off | (x < 0.0f ? FLAG_BIT : 0u));
+            });
+        if (lane == 0) sg.count[seg] = kept | (kept > (unsigned int)sl.capacity ? OVER : 0u);
+        total += kept;
+    }
+    if (lane == 0) wsum[wave] = total;
+    __syncthreads();
+    if (tid == 0) sg.group_kept[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+}
+
 struct EwLayout {
     EwState* st;
-    unsigned int* chunk_count;
-    unsigned long long* chunk_base;
-    unsigned long long* keep;     // [n_chunks][64] keep bits, see ew_count
-    unsigned long long* und;      // [n_chunks][64] coordinates the second pass could not settle, same layout
-    unsigned long long* super_count;   // [ceil(n_chunks / SUPER)] kept coordinates per group of SUPER chunks
     double* lq_partial;           // [LQ_WGS] per-workgroup parts of |g|_q
+    Segments sg;
+    int steps;                    // float4 steps per segment
     size_t bytes;
 };
 
-EwLayout ew_layout(void* base, int64_t n)
+// limit: bytes that may be used, 0 for no limit (the records take what is left; a segment that finds too few slots is drawn
+// again, see "records").
+EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
 {
     Carver carve(base);
     EwLayout l;
-    const size_t n_chunks = (size_t)((n + CHUNK - 1) / CHUNK);
+    // Short segments until there are enough of them to fill the chip several times over (8192 waves run at once), then
+    // long ones: a segment costs its counts and a chain of loads in every later kernel whatever its length.
+    l.steps = n < (1ll << 25) ? 4 : 16;
+    const int64_t seg = (int64_t)l.steps * STEP;
+    l.sg.n_seg = (n + seg - 1) / seg;
+    // A workgroup that writes the message adds up the counts of all groups before its own: about a thousand at most.
+    l.sg.per_group = 4;
+    while (l.sg.per_group < MAX_GROUP && (l.sg.n_seg + l.sg.per_group - 1) / l.sg.per_group > 1024) l.sg.per_group *= 2;
+    l.sg.n_groups = (l.sg.n_seg + l.sg.per_group - 1) / l.sg.per_group;
     l.st = carve.take<EwState>(1);
-    l.chunk_count = carve.take<unsigned int>(n_chunks);
-    l.chunk_base = carve.take<unsigned long long>(n_chunks);
-    l.keep = carve.take<unsigned long long>(n_chunks * 64);
-    l.und = carve.take<unsigned long long>(n_chunks * 64);
-    l.super_count = carve.take<unsigned long long>((n_chunks + SUPER - 1) / SUPER);
     l.lq_partial = carve.take<double>(LQ_WGS);
+    l.sg.count = carve.take<unsigned int>((size_t)l.sg.n_seg);
+    l.sg.group_kept = carve.take<unsigned int>((size_t)l.sg.n_groups);
+    size_t step_bytes = STEP_BYTES;
+    if (limit) step_bytes = std::min<size_t>(step_bytes, (limit - carve.off - 256) / ((size_t)l.sg.n_seg * l.steps) & ~(size_t)7);
+    l.sg.slot_bytes = (int)(step_bytes * l.steps);
+    l.sg.slots = carve.take<unsigned char>((size_t)l.sg.n_seg * l.sg.slot_bytes);
     l.bytes = carve.off;
     return l;
 }
@@ -959,28 +1012,32 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
                              const atomo_ew_msg* msg, float* p_out, const EwLayout& l, bool clear_first, hipStream_t stream)
 {
     const int64_t n = msg->n;
-    const long long n_chunks = (n + CHUNK - 1) / CHUNK;
-    const int n_super = (int)((n_chunks + SUPER - 1) / SUPER);
-    // No workgroup of the level-0 pass may visit 2^16 elements or more (field widths of its packed histogram word).
+    const Segments& sg = l.sg;
+    // No workgroup may visit 2^16 elements or more (field widths of the packed histogram word).
     const int64_t floor_wgs = (n + 49151) / 49152;
-    const int wgs = (int)std::max<int64_t>(std::min<int64_t>(HIST_WGS, (n + 1023) / 1024), floor_wgs);
     const int wgs0 = (int)std::max<int64_t>(std::min<int64_t>(256, (n + 4095) / 4096), floor_wgs);
+    const int wgs2 = (int)std::min<int64_t>(HIST_WGS, sg.n_groups);
+    const unsigned quads = (unsigned)((sg.n_seg + 3) / 4), groups = (unsigned)sg.n_groups;
+    const bool long_seg = l.steps == 16;
     if (clear_first) { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(l.st); }
     { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist0_solve0<<<wgs0, 1024, 0, stream>>>(g, n, l.st, s); }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
-        ew_pass_b<<<(unsigned)n_chunks, 256, 0, stream>>>(g, n, n_chunks, l.st, s, stream_id, seed, l.chunk_count, l.keep,
-                                                          l.und);
+        if (long_seg) ew_draw<16><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
+        else ew_draw<4><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
     }
-    { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist2_solve2<<<wgs, 256, 0, stream>>>(g, n, l.st, s); }
+    {
+        ProfScope ps(ctx, ATOMO_K_EW_HIST, stream);
+        if (long_seg) ew_level2<16><<<wgs2, 256, 0, stream>>>(g, n, l.st, s, sg);
+        else ew_level2<4><<<wgs2, 256, 0, stream>>>(g, n, l.st, s, sg);
+    }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
-        ew_settle<<<(unsigned)n_chunks, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.chunk_count, l.keep, l.und);
-        const bool coarse = n_chunks > 16384;                    // (above 2^26 elements)
-        if (coarse) ew_super<<<(unsigned)n_super, 256, 0, stream>>>(l.chunk_count, n_chunks, l.super_count);
-        ew_write2<<<(unsigned)n_chunks, 256, 0, stream>>>(g, l.st, l.keep, l.chunk_count, coarse ? l.super_count : nullptr,
-                                                          (long long)msg->capacity, msg->idx, msg->val,
-                                                          (long long*)msg->count, ctx->d_flags);
+        if (long_seg) ew_settle<16><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg);
+        else ew_settle<4><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg);
+        const auto write = long_seg ? ew_write<16, false> : ew_write<4, false>;
+        write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg, (long long)msg->capacity, msg->idx, msg->val,
+                                          (long long*)msg->count, ctx->d_flags);
         if (p_out) ew_write_p<<<(int)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(g, n, l.st, p_out);
     }
     ATOMO_HIP(ctx, hipGetLastError());
@@ -1013,7 +1070,6 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
     int rc = ensure_workspace(ctx, entrywise_workspace_bytes(n));
     if (rc != ATOMO_OK) return rc;
     const EwLayout l = ew_layout(ctx->ws, n);
-    const long long n_chunks = (n + CHUNK - 1) / CHUNK;
     const int mode = std::isinf(q) ? LQ_MAX : q == 2.0 ? LQ_TWO : q == 1.0 ? LQ_ONE : LQ_POW;
     const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
     {
@@ -1023,11 +1079,13 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
     { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); lq_norm_final<<<1, 256, 0, stream>>>(l.lq_partial, wgs, mode, q, l.st, msg->norm); }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
-        ew_count<<<(unsigned)n_chunks, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.chunk_count, l.keep);
-        ew_scan<<<1, 256, 0, stream>>>(l.chunk_count, n_chunks, l.chunk_base, l.st, (long long*)msg->count,
-                                       (long long)msg->capacity, ctx->d_flags);
-        ew_write<<<(unsigned)n_chunks, 256, 0, stream>>>(g, l.st, l.keep, l.chunk_base, (long long)msg->capacity,
-                                                         msg->idx, nullptr);
+        const unsigned groups = (unsigned)l.sg.n_groups;
+        const bool long_seg = l.steps == 16;
+        if (long_seg) lq_draw<16><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg);
+        else lq_draw<4><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg);
+        const auto write = long_seg ? ew_write<16, true> : ew_write<4, true>;
+        write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg, (long long)msg->capacity, msg->idx, nullptr,
+                                          (long long*)msg->count, ctx->d_flags);
         if (p_out) ew_write_p<<<(int)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(g, n, l.st, p_out);
     }
     ATOMO_HIP(ctx, hipGetLastError());
@@ -1072,7 +1130,7 @@ int probabilities(atomo_ctx* ctx, const float* lambda, const int64_t* offsets, i
 
 // ---------------------------------------------------------------------------------------------------------
 // atomo_encode_entrywise_noalloc: the entry-wise encoder for callers that cannot allocate (see include/atomo.h).
-// Its scratch memory (the state of the water-level search, per-chunk counts, offsets and keep bits) is the
+// Its scratch memory (the state of the water-level search, counts and records) is the
 // file-scope device array below instead of the context's growable workspace.  Every GPU the library runs on
 // holds its own copy of the array, at its own address, until the process ends; the address on a device is
 // looked up once, with that device current (atomo_create does it, so that no call made later has to).
@@ -1098,7 +1156,7 @@ int entrywise_noalloc_setup(atomo_ctx* ctx)
     const int dev = ctx->device;
     if (dev < 0 || dev >= NOALLOC_MAX_DEVICES) return ATOMO_EINVAL;
     if (__atomic_load_n(&scratch_ptr[dev], __ATOMIC_ACQUIRE)) return ATOMO_OK;
-    if (ew_layout(nullptr, NOALLOC_MAX_N).bytes > NOALLOC_SCRATCH_BYTES) return ATOMO_EINVAL;   // (a build-time fact)
+    if (ew_layout(nullptr, NOALLOC_MAX_N, NOALLOC_SCRATCH_BYTES).bytes > NOALLOC_SCRATCH_BYTES) return ATOMO_EINVAL;   // (a build-time fact)
     void* ptr = nullptr;
     ATOMO_HIP(ctx, hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch)));
     if (!ptr) return ATOMO_EHIP;
@@ -1125,7 +1183,7 @@ extern "C" int atomo_encode_entrywise_noalloc(atomo_ctx* ctx, const float* g, do
         ctx->profiling = false;
         void* base = __atomic_load_n(&scratch_ptr[ctx->device], __ATOMIC_ACQUIRE);
         // (the array keeps what the previous call left: the histograms are cleared first, by a kernel)
-        rc = enqueue_encode_entrywise(ctx, g, s, seed, stream_id, msg, p_out, ew_layout(base, msg->n), true, (hipStream_t)stream);
+        rc = enqueue_encode_entrywise(ctx, g, s, seed, stream_id, msg, p_out, ew_layout(base, msg->n, NOALLOC_SCRATCH_BYTES), true, (hipStream_t)stream);
         ctx->profiling = profiling;
     }
     if (prev >= 0 && prev != ctx->device) (void)hipSetDevice(prev);

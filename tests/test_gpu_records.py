@@ -1,0 +1,59 @@
+"""GPU parity of the entry-wise and l_q encoders where their records run out or their lengths change: densely kept stretches,
+equal magnitudes, a water level in the middle of a narrow band, gradients of zeros, and the sizes on both sides of each rule."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1806_04090_amd import binding
+from gpu_common import ctx, dev
+from test_gpu_entrywise import parity
+from test_gpu_lq import parity as lq_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def make(kind, n):
+    rng = np.random.default_rng(n)
+    g = (1e-3 * rng.standard_normal(n)).astype(np.float32)
+    if kind == "stretch":                        # whole segments kept with p = 1 among sparse ones, not at their edges
+        lo = n // 3 + 5
+        g[lo:lo + 3000] = 1.0 + rng.random(g[lo:lo + 3000].size).astype(np.float32)
+        return g, n / 100 + 3000
+    if kind == "equal":                          # one magnitude: every element in the chosen bucket
+        return np.where(rng.random(n) < 0.5, -0.25, 0.25).astype(np.float32), n * 0.75
+    if kind == "band":                           # the level lies inside a band narrower than a bucket
+        return (1.0 + 0.02 * rng.random(n)).astype(np.float32), n * 0.995
+    if kind == "zeros":                          # fewer non-zeros than the budget: nothing is left uncapped
+        g[rng.random(n) < 0.9] = 0
+        return g, float(n)
+    return g, n / 100
+
+
+@pytest.mark.parametrize("kind", ["plain", "stretch", "equal", "band", "zeros"])
+@pytest.mark.parametrize("n", [1023, 16_384, 16_385, 70_001, 4_194_305])
+def test_entrywise_records(kind, n):
+    g, s = make(kind, n)
+    parity(g, s, 11, n)
+
+
+@pytest.mark.parametrize("kind", ["plain", "stretch", "equal"])
+@pytest.mark.parametrize("n", [1023, 16_385, 70_001])
+def test_lq_records(kind, n):
+    g, _ = make(kind, n)
+    lq_parity(g, float("inf"), 3, n)
+
+
+@pytest.mark.parametrize("n", [(1 << 25) - 3, 1 << 25, (1 << 25) + 4099])
+def test_long_segments(n):
+    """The rule that picks the segments' length changes nothing in the message: dense and sparse stretches, both encoders."""
+    g, s = make("stretch", n)
+    msg = binding.atomo_encode_entrywise(ctx(), dev(g), s, 1, 2)
+    ref = oracle.encode_entrywise(g, s, 1, 2)
+    h = msg.to_host()
+    assert ctx().status()[0] == 0
+    assert len(np.setxor1d(ref["idx"], h["idx"])) <= 2 and np.all(np.diff(h["idx"].astype(np.int64)) > 0)
+    if np.array_equal(ref["idx"], h["idx"]):
+        np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6)
+    m = binding.atomo_encode_lq(ctx(), dev(g), float("inf"), 1, 2).to_host()
+    want = oracle.encode_lq(g, float("inf"), 1, 2)
+    assert ctx().status()[0] == 0 and len(np.setxor1d(want["idx"], m["idx"])) <= 2
