@@ -77,7 +77,7 @@ struct atomo_ctx {
     uint64_t hint_seq = 0;
     bool direct_lds = false;       // direct::allow_lds has been called for this context's device
     size_t rowgram_lds = 0;        // dynamic LDS that svd_rowgram has been allowed on this context's device
-    atomo::TableCache svd_tables, dec_tables;    // of the SVD encoder and of the SVD decoder
+    atomo::TableCache svd_tables, dec_tables, prob_tables;   // of the SVD encoder, the SVD decoder and atomo_probabilities
     std::vector<char> table_scratch;     // where a call puts its tables together
     hipStream_t side = nullptr, side2 = nullptr, side_thin = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_join2 = nullptr, ev_join_thin = nullptr;

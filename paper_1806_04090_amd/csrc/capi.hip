@@ -177,7 +177,7 @@ int atomo_destroy(atomo_ctx* ctx)
     if (ctx->side2) (void)hipStreamDestroy(ctx->side2);
     if (ctx->side_thin) (void)hipStreamDestroy(ctx->side_thin);
     if (ctx->ws) (void)hipFree(ctx->ws);
-    for (TableCache* cache : {&ctx->svd_tables, &ctx->dec_tables})
+    for (TableCache* cache : {&ctx->svd_tables, &ctx->dec_tables, &ctx->prob_tables})
         for (TableSlot& t : cache->slot)
             if (t.dev) (void)hipFree(t.dev);
     if (ctx->ew_state) (void)hipFree(ctx->ew_state);

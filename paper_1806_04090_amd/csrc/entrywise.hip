@@ -25,7 +25,6 @@
 #include <vector>
 
 #include "atomo_internal.h"
-#include "block_algorithm1.h"
 
 namespace atomo {
 
@@ -52,12 +51,11 @@ struct EwState {
     unsigned long long sig[3][NBUCKET];
     SolveOut lvl[3];              // what each level found (written by one kernel, read by the kernels after it);
                                   // lvl[k].done also when an earlier level already settled everything
-    unsigned int ticket[3][65];   // per pass: workgroups that have finished (the last one solves the level); zero between calls
+    unsigned int ticket[65];      // workgroups of a pass that have finished (the last one solves level 0); zero between calls
     unsigned long long n_s;       // final: number of capped elements
     double tail;                  // final: sum of the uncapped magnitudes
     double budget;                // final: s - n_s
     double ratio;                 // final: budget / tail, +inf if tail == 0
-    unsigned long long total_kept;
 };
 
 
@@ -73,21 +71,32 @@ __device__ inline unsigned int significand(unsigned int key)
     return e ? (mant | 0x800000u) : mant;
 }
 
+// Histograms: level 2 is cleared by the pass that forms level 1, levels 0 and 1 by the last kernel of a call (their readers
+// have run by then).
+__device__ inline void clear_level(EwState* st, int level)
+{
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < NBUCKET; i += gridDim.x * 256) {
+        st->cnt[level][i] = 0u;
+        st->sig[level][i] = 0ull;
+    }
+}
+
 __global__ __launch_bounds__(256) void ew_clear(EwState* st)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < 3 * NBUCKET) { (&st->cnt[0][0])[i] = 0u; (&st->sig[0][0])[i] = 0ull; }
     if (i == 0) {
-        for (int k = 0; k < 3 * 65; ++k) (&st->ticket[0][0])[k] = 0u;
+        for (int k = 0; k < 65; ++k) st->ticket[k] = 0u;
         for (int k = 0; k < 3; ++k) { st->lvl[k].done = 0; st->lvl[k].prefix = 0u; st->lvl[k].n_above = 0ull; st->lvl[k].sum_below = 0.0; }
-        st->n_s = 0ull; st->tail = 0.0; st->budget = 0.0; st->ratio = 0.0; st->total_kept = 0ull;
+        st->n_s = 0ull; st->tail = 0.0; st->budget = 0.0; st->ratio = 0.0;
     }
 }
 
-// Level-LEVEL histogram of the elements on the path `prefix`, by the TPB threads of a workgroup (all call):
+// Level-LEVEL histogram of the elements on the path `prefix`, by the TPB threads of workgroup `self` of `members` (all call):
 // accumulated in the LDS array acc (COPIES x NB packed words), then added to the global histogram.
 template <int LEVEL, int TPB>
-__device__ inline void hist_body(const float* __restrict__ g, long long n, EwState* st, unsigned long long* acc, unsigned int prefix)
+__device__ inline void hist_body(const float* __restrict__ g, long long n, EwState* st, unsigned long long* acc, unsigned int prefix,
+                                 unsigned int self, unsigned int members)
 {
     // Level 0 sees every element and most of them fall into a few dozen buckets: four copies of the
     // histogram (one per lane mod 4) keep lanes of a wave from queueing on the same LDS word.
@@ -113,9 +122,9 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
 
     const bool vec = (((size_t)g) & 15) == 0;
     const long long n4 = vec ? n / 4 : 0;
-    const long long stride = (long long)gridDim.x * TPB;
+    const long long stride = (long long)members * TPB;
     // four loads in flight per thread: one at a time, the pass is a chain of memory latencies
-    for (long long q0 = (long long)blockIdx.x * TPB + threadIdx.x; q0 < n4; q0 += 4 * stride) {
+    for (long long q0 = (long long)self * TPB + threadIdx.x; q0 < n4; q0 += 4 * stride) {
         float4 x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -127,7 +136,7 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
             if (q0 + u * stride < n4) { visit(x[u].x); visit(x[u].y); visit(x[u].z); visit(x[u].w); }
         }
     }
-    for (long long i = n4 * 4 + (long long)blockIdx.x * TPB + threadIdx.x; i < n; i += stride) visit(g[i]);
+    for (long long i = n4 * 4 + (long long)self * TPB + threadIdx.x; i < n; i += stride) visit(g[i]);
     __syncthreads();
     for (int b = threadIdx.x; b < NB; b += TPB) {
         unsigned int c = 0u;
@@ -145,27 +154,43 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
     }
 }
 
-// Histogram of one level.  Elements are visited as float4 where the pointer allows.
-template <int LEVEL>
-__global__ __launch_bounds__(LEVEL == 0 ? 1024 : 256) void ew_hist(const float* __restrict__ g, long long n, EwState* st)
+// Inclusive prefix sums over the lanes of a wave by DPP moves (a shuffle through LDS takes about ten times as long):
+// doubling inside the rows of 16 lanes, then the last lane of a row into the rows behind it.
+template <int CTRL, int ROWS>
+__device__ inline unsigned int dpp_moved(unsigned int v)
 {
-    constexpr int TPB = LEVEL == 0 ? 1024 : 256;
-    __shared__ unsigned long long acc[(LEVEL == 0 ? 4 : 1) * (LEVEL == 0 ? (1 << L0_BITS) : (1 << L1_BITS))];
-    if (LEVEL > 0 && st->lvl[LEVEL > 0 ? LEVEL - 1 : 0].done) return;
-    hist_body<LEVEL, TPB>(g, n, st, acc, LEVEL == 0 ? 0u : st->lvl[LEVEL > 0 ? LEVEL - 1 : 0].prefix);
+    return (unsigned int)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
+template <int CTRL, int ROWS>
+__device__ inline double dpp_moved(double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned int lo = dpp_moved<CTRL, ROWS>((unsigned int)u), hi = dpp_moved<CTRL, ROWS>((unsigned int)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <typename V>
+__device__ inline V wave_prefix(V v)
+{
+    v += dpp_moved<0x111, 0xF>(v);                               // row_shr:1, 2, 4, 8
+    v += dpp_moved<0x112, 0xF>(v);
+    v += dpp_moved<0x114, 0xF>(v);
+    v += dpp_moved<0x118, 0xF>(v);
+    v += dpp_moved<0x142, 0xA>(v);                               // row_bcast:15 into rows 1 and 3
+    v += dpp_moved<0x143, 0xC>(v);                               // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// The value of the lane before; 0 in lane 0.
+__device__ inline double lane_before(double v) { return dpp_moved<0x138, 0xF>(v); }           // wave_shr:1
 
 // One level of the search, by the T threads of a workgroup (all must call).
-// Reads the level's histogram from st, and the path chosen so far from `in` (level 0: nothing).  The result goes
-// to `out` (LDS or global, visible to the workgroup after the call's last barrier).
-// T threads (256 or 1024); COHERENT: the histogram was written by other workgroups of the running kernel (atomics), so it
-// is read with device-scope atomic loads instead of plain ones.
+// read(b, cnt, sig) gives a bucket of the level's histogram; `prefix`, n_above0 and sum_below0 are the path chosen so far
+// (level 0: nothing).  The result goes to `out` (LDS or global, visible to the workgroup after the call's last barrier).
 // scratch: LDS, (2 T / 64 + 1) x 8 bytes.
-template <int LEVEL, int T = 256, bool COHERENT = false>
-__device__ inline void solve_level(const EwState* st, double s, unsigned int prefix, unsigned long long n_above0,
-                                   double sum_below0, SolveOut* out, unsigned long long* scratch)
+template <int LEVEL, int T, typename READ>
+__device__ inline void solve_hist(READ read, double s, unsigned int prefix, unsigned long long n_above0, double sum_below0,
+                                  SolveOut* out, unsigned long long* scratch)
 {
-    unsigned long long* cpart = scratch;
+    unsigned int* cpart = (unsigned int*)scratch;
     double* spart = (double*)(scratch + T / 64);
     int& best = *(int*)(scratch + 2 * (T / 64));
     constexpr int NB = LEVEL == 0 ? (1 << L0_BITS) : (1 << L1_BITS);
@@ -183,52 +208,44 @@ __device__ inline void solve_level(const EwState* st, double s, unsigned int pre
     // this thread's PER consecutive buckets stay in registers
     unsigned int cnt_r[PER];
     double sum_r[PER];
-    unsigned long long c_mine = 0ull;
+    unsigned int c_mine = 0u;                                    // (n < 2^32: every count fits)
     double s_mine = 0.0;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         const int b = tid * PER + e;
-        if (COHERENT) {                                          // (both loads in flight at once)
-            cnt_r[e] = __hip_atomic_load(&st->cnt[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned long long sg = __hip_atomic_load(&st->sig[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sum_r[e] = cnt_r[e] ? sig_value(sg, bucket_exp(b)) : 0.0;
-        } else {
-            cnt_r[e] = st->cnt[LEVEL][b];
-            sum_r[e] = cnt_r[e] ? sig_value(st->sig[LEVEL][b], bucket_exp(b)) : 0.0;    // (most buckets are empty)
-        }
+        unsigned long long sg;
+        read(b, cnt_r[e], sg);
+        sum_r[e] = sig_value(sg, bucket_exp(b));
         c_mine += cnt_r[e];
         s_mine += sum_r[e];
     }
     __syncthreads();                                             // (the scratch may still be read from a previous call)
-    // suffix scan of the counts and prefix scan of the sums over the threads: in the wave by shuffles, then over the waves
+    // prefix sums over the threads: in the wave, then over the waves
     const int lane = tid & 63, wave = tid >> 6;
-    unsigned long long c_scan = c_mine;
-    double s_scan = s_mine;
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long cv = __shfl_down(c_scan, off);
-        const double sv = __shfl_up(s_scan, off);
-        if (lane + off < 64) c_scan += cv;
-        if (lane >= off) s_scan += sv;
+    const unsigned int c_scan = wave_prefix(c_mine);
+    const double s_scan = wave_prefix(s_mine);
+    if (lane == 63) {
+        cpart[wave] = c_scan;
+        spart[wave] = s_scan;
     }
-    if (lane == 0) cpart[wave] = c_scan;
-    if (lane == 63) spart[wave] = s_scan;
     if (tid == 0) best = 0;
     __syncthreads();
-    unsigned long long c_after = c_scan - c_mine;                // count in buckets owned by later threads
-    double s_before = __shfl_up(s_scan, 1);                      // sum in buckets owned by earlier threads
-    if (lane == 0) s_before = 0.0;
-    {
-        double earlier = 0.0;
-        for (int w = 0; w < T / 64; ++w) {
-            if (w > wave) c_after += cpart[w];
-            if (w < wave) earlier += spart[w];
-        }
-        s_before += earlier;
+    unsigned int c_before = c_scan - c_mine, c_all = 0u;         // counts in buckets owned by earlier threads, by all
+    double s_before = lane_before(s_scan), earlier = 0.0;        // sum in buckets owned by earlier threads
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) {
+        const unsigned int c = cpart[w];
+        const double d = spart[w];
+        c_all += c;
+        c_before += w < wave ? c : 0u;
+        earlier += w < wave ? d : 0.0;
     }
+    s_before += earlier;
+    const unsigned int c_after = c_all - c_before - c_mine;      // counts in buckets owned by later threads
 
     // h at the lower edge of bucket b:  lo_b * (s - #{elements in buckets >= b}) - sum(buckets < b)
     {
-        unsigned long long at_or_above = c_after + c_mine;
+        unsigned int at_or_above = c_after + c_mine;
         double below = s_before;
         int mine_best = -1;
 #pragma unroll
@@ -239,12 +256,15 @@ __device__ inline void solve_level(const EwState* st, double s, unsigned int pre
             at_or_above -= cnt_r[e];
             below += sum_r[e];
         }
-        if (mine_best >= 0) atomicMax(&best, mine_best);
+        // h is monotone: the highest lane of a wave that has one holds the wave's last bucket (64 lanes' atomics on one word
+        // would be performed one after the other)
+        const unsigned long long have = __ballot(mine_best >= 0);
+        if (have && lane == 63 - __builtin_clzll(have)) atomicMax(&best, mine_best);
     }
     __syncthreads();
     const int bs = best;
     if (tid == bs / PER) {                      // the owner of the chosen bucket finishes from its registers
-        unsigned long long above = c_after;
+        unsigned int above = c_after;
         double below = s_before;
         unsigned int c = 0;
         double bucket_sum = 0.0;
@@ -284,6 +304,28 @@ __device__ inline void solve_level(const EwState* st, double s, unsigned int pre
     __syncthreads();
 }
 
+// The same from a histogram in st->cnt / st->sig that other workgroups of the running kernel wrote (atomics): device-scope
+// atomic loads instead of plain ones.
+template <int LEVEL, int T>
+__device__ inline void solve_level(const EwState* st, double s, unsigned int prefix, unsigned long long n_above0,
+                                   double sum_below0, SolveOut* out, unsigned long long* scratch)
+{
+    solve_hist<LEVEL, T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+        cnt = __hip_atomic_load(&st->cnt[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sig = __hip_atomic_load(&st->sig[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }, s, prefix, n_above0, sum_below0, out, scratch);
+}
+
+// The same from a histogram that an earlier kernel wrote.
+template <int LEVEL, int T>
+__device__ inline void solve_written(const EwState* st, double s, const SolveOut& in, SolveOut* out, unsigned long long* scratch)
+{
+    solve_hist<LEVEL, T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+        cnt = st->cnt[LEVEL][b];
+        sig = st->sig[LEVEL][b];
+    }, s, in.prefix, in.n_above, in.sum_below, out, scratch);
+}
+
 // (s - n_s) / tail, or +inf when nothing is left uncapped
 __device__ inline double final_ratio(double s, unsigned long long n_s, double tail)
 {
@@ -302,45 +344,50 @@ __device__ inline void publish(EwState* st, int level, const SolveOut& r, double
     }
 }
 
-template <int LEVEL>
-__global__ __launch_bounds__(256) void ew_solve(EwState* st, double s)
+// Levels 1 and 2 are solved at the head of the kernel behind the one that wrote the histogram, by each of its workgroups for
+// itself: about two microseconds of loads from L2 and scans, where a last workgroup behind a ticket costs the writing kernel
+// five to seven (2728 workgroups).  All 256 threads call; out in LDS.
+
+// At the head of the pass that histograms level 2: true if there is something to do for it, with the path in *out.
+__device__ inline bool enter_level2(EwState* st, double s, SolveOut* out, unsigned long long* scratch)
 {
-    __shared__ SolveOut out;
-    __shared__ unsigned long long scratch[2 * 4 + 1];
-    unsigned int prefix = 0u;
-    unsigned long long n_above = 0ull;
-    double sum_below = 0.0;
-    if (LEVEL > 0) {
-        const SolveOut& in = st->lvl[LEVEL > 0 ? LEVEL - 1 : 0];
-        if (in.done) {                                           // settled earlier: hand the mark on
-            if (threadIdx.x == 0) st->lvl[LEVEL].done = 1;
-            return;
-        }
-        prefix = in.prefix; n_above = in.n_above; sum_below = in.sum_below;
-    }
-    solve_level<LEVEL>(st, s, prefix, n_above, sum_below, &out, scratch);
-    if (threadIdx.x == 0) publish(st, LEVEL, out, s);
+    const SolveOut in = st->lvl[0];
+    if (in.done) return false;
+    solve_written<1, 256>(st, s, in, out, scratch);
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish(st, 1, *out, s);
+    return !out->done;
 }
 
-// True in every thread of the workgroup that finishes last among the launch's workgroups (all threads of every
+// Behind it: the final ratio.
+__device__ inline double enter_final(EwState* st, double s, SolveOut* out, unsigned long long* scratch)
+{
+    if (st->lvl[0].done) return st->ratio;
+    const SolveOut in = st->lvl[1];
+    if (in.done) return st->ratio;
+    solve_written<2, 256>(st, s, in, out, scratch);
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish(st, 2, *out, s);
+    return final_ratio(s, out->n_s, out->tail);
+}
+
+// True in every thread of the workgroup that finishes last among `members` workgroups numbered from 0 (all threads of every
 // workgroup call, at their very end).  The last workgroup may then read what the others added to the global
 // histograms, with device-scope atomic loads: every wave first waits until its own atomics have been performed
 // (s_waitcnt vmcnt(0): on gfx9 stores and atomics count in vmcnt, and a workgroup barrier alone does not wait for memory
 // operations in flight), and device-scope atomics are performed where every compute unit sees them, so no cache
 // maintenance is involved.  Nobody waits for anybody: the others simply leave.
 // Tickets in two levels (thousands of atomic adds on one address are performed one after the other, about ten
-// nanoseconds each): a workgroup counts on word blockIdx.x mod 64, the last one of a word counts on word 64.
+// nanoseconds each): a workgroup counts on word `self` mod 64, the last one of a word counts on word 64.
 // ticket: [65] words, zero on entry and zero again when the last workgroup returns.
-__device__ inline bool last_workgroup(unsigned int* ticket)
+__device__ inline bool last_workgroup(unsigned int* ticket, unsigned int self, unsigned int members)
 {
     __shared__ int last_sh;
     __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0), other counters untouched
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned int slots = min(64u, gridDim.x), slot = blockIdx.x % slots;
-        const unsigned int members = (gridDim.x - slot + slots - 1) / slots;
+        const unsigned int slots = min(64u, members), slot = self % slots;
+        const unsigned int here = (members - slot + slots - 1) / slots;
         int last = 0;
-        if (__hip_atomic_fetch_add(&ticket[slot], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1)
+        if (__hip_atomic_fetch_add(&ticket[slot], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == here - 1)
             last = __hip_atomic_fetch_add(&ticket[64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slots - 1;
         last_sh = last;
     }
@@ -356,9 +403,9 @@ __global__ __launch_bounds__(1024) void ew_hist0_solve0(const float* __restrict_
 {
     __shared__ unsigned long long acc[4 * NBUCKET];
     __shared__ SolveOut out;
-    hist_body<0, 1024>(g, n, st, acc, 0u);
-    if (!last_workgroup(st->ticket[0])) return;
-    solve_level<0, 1024, true>(st, s, 0u, 0ull, 0.0, &out, acc);            // (acc is spent: scratch)
+    hist_body<0, 1024>(g, n, st, acc, 0u, blockIdx.x, gridDim.x);
+    if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
+    solve_level<0, 1024>(st, s, 0u, 0ull, 0.0, &out, acc);            // (acc is spent: scratch)
     if (threadIdx.x == 0) publish(st, 0, out, s);
 }
 
@@ -371,27 +418,25 @@ __device__ inline float ew_probability(float x, double ratio)
     return fminf(1.0f, (float)((double)a * ratio));
 }
 
-// p for a large segment of atomo_probabilities
-__global__ __launch_bounds__(256) void ew_write_p(const float* __restrict__ lam, long long n, const EwState* st,
-                                                  float* __restrict__ p)
+// p of every element with the final ratio, by a grid of 256-thread workgroups
+__device__ inline void write_p(const float* lam, long long n, double ratio, float* p)
 {
-    const double ratio = st->ratio;
     const long long stride = (long long)gridDim.x * 256;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
-        p[i] = ew_probability(lam[i], ratio);
+    long long done = 0;
+    if (((((size_t)lam) | ((size_t)p)) & 15) == 0) {
+        for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < n / 4; q += stride) {
+            const float4 x = ((const float4*)lam)[q];
+            ((float4*)p)[q] = make_float4(ew_probability(x.x, ratio), ew_probability(x.y, ratio), ew_probability(x.z, ratio),
+                                          ew_probability(x.w, ratio));
+        }
+        done = n / 4 * 4;
+    }
+    for (long long i = done + (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) p[i] = ew_probability(lam[i], ratio);
 }
 
-// Draws for the four coordinates 4q .. 4q+3 (one Philox block).  Returns the keep bits.
-__device__ inline unsigned int draw4(const float4 x, long long q, unsigned long long stream_id, unsigned long long seed,
-                                     double ratio, float4& p)
+__global__ __launch_bounds__(256) void ew_write_p(const float* lam, long long n, const EwState* st, float* p)
 {
-    const u32x4 rnd = philox4x32_10((unsigned long long)q, stream_id, seed);
-    p.x = ew_probability(x.x, ratio);
-    p.y = ew_probability(x.y, ratio);
-    p.z = ew_probability(x.z, ratio);
-    p.w = ew_probability(x.w, ratio);
-    return (u01(rnd.x) < p.x ? 1u : 0u) | (u01(rnd.y) < p.y ? 2u : 0u) | (u01(rnd.z) < p.z ? 4u : 0u) |
-           (u01(rnd.w) < p.w ? 8u : 0u);
+    write_p(lam, n, st->ratio, p);
 }
 
 __device__ inline float4 load4(const float* g, long long q, long long n, bool vec)
@@ -494,6 +539,36 @@ __device__ inline unsigned int listed_total(const unsigned long long (&ballots)[
     return (unsigned int)(__popcll(ballots[0]) + __popcll(ballots[1]) + __popcll(ballots[2]) + __popcll(ballots[3]));
 }
 
+// r with  p <= fl32(|x| r) 2^-24  for the p = fl32(|x| ratio) of any x but 0 (the product may be NaN there); see ew_draw
+__device__ inline float upper_ratio(double ratio)
+{
+    return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
+}
+__device__ inline unsigned int candidate_bits(const bool (&in)[4])
+{
+    return (in[0] ? 1u : 0u) | (in[1] ? 2u : 0u) | (in[2] ? 4u : 0u) | (in[3] ? 8u : 0u);
+}
+// v[e] by selects (an index would send the array through memory)
+__device__ inline float pick(const float (&v)[4], int e)
+{
+    const float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+    const float low = (e & 1) ? v1 : v0, high = (e & 1) ? v3 : v2;
+    return (e & 2) ? high : low;
+}
+// Four steps' float4s of a wave, from float4 q0 + lane on.  `whole`: aligned and all inside the gradient (wave-uniform).
+__device__ inline void load_steps(const float* __restrict__ g, long long q0, long long n, bool whole, bool vec, float4 (&x)[4])
+{
+    const int lane = threadIdx.x & 63;
+    if (whole) {
+        const float4* p = (const float4*)g + q0 + lane;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = p[u * 64];
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = load4(g, q0 + u * 64 + lane, n, vec);
+    }
+}
+
 // Calls visit(position, offset in the segment, value, p) for every kept coordinate of a segment, drawn from the gradient
 // with the exact ratio; returns their number.  All lanes of the wave call.
 template <int STEPS, typename VISIT>
@@ -502,24 +577,43 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
 {
     const bool vec = (((size_t)g) & 15) == 0;
     const int lane = threadIdx.x & 63;
+    // u >= p is decided in single precision wherever p (1 + 2^-21) leaves no doubt; the rest gets the exact p
+    const float r_hi = ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
+    const bool whole = vec && (seg + 1) * STEPS * STEP <= n;
     unsigned int fill = 0u;                                      // wave-uniform
-    for (int j = 0; j < STEPS; ++j) {
-        const long long q = (seg * STEPS + j) * 64 + lane;
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), p = x;
-        unsigned int bits = 0u;
-        if (q * 4 < n) {
-            x = load4(g, q, n, vec);
-            bits = draw4(x, q, stream_id, seed, ratio, p);
+    for (int j0 = 0; j0 < STEPS; j0 += 4) {
+        float4 xv[4];
+        const long long q0 = (seg * STEPS + j0) * 64;
+        load_steps(g, q0, n, whole, vec, xv);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
+            const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+            const unsigned int rs[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+            bool in[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) in[e] = !((float)(rs[e] >> 8) >= fabsf(xs[e]) * r_hi);
+            if (__ballot(in[0] || in[1] || in[2] || in[3]) == 0ull) continue;
+            float ps[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ps[e] = ew_probability(xs[e], ratio);
+                in[e] = in[e] && u01(rs[e]) < ps[e];
+            }
+            unsigned long long ballots[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
+            unsigned int pos = fill + listed_before(ballots);
+            unsigned int left = candidate_bits(in);
+            while (__ballot(left != 0u)) {
+                if (left) {
+                    const int e = __builtin_ctz(left);
+                    left &= left - 1;
+                    visit(pos++, (unsigned int)((j0 + u) * STEP + lane * 4 + e), pick(xs, e), pick(ps, e));
+                }
+            }
+            fill += listed_total(ballots);
         }
-        unsigned long long ballots[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ballots[e] = __ballot((bits >> e) & 1u);
-        unsigned int pos = fill + listed_before(ballots);
-        const float xs[4] = {x.x, x.y, x.z, x.w}, ps[4] = {p.x, p.y, p.z, p.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if ((bits >> e) & 1u) visit(pos++, (unsigned int)(j * STEP + lane * 4 + e), xs[e], ps[e]);
-        fill += listed_total(ballots);
     }
     return fill;
 }
@@ -532,10 +626,11 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
 // here if u >= p_hi, marked as kept for sure if u < p_lo; what lies between (about 0.12 s elements) is settled by ew_settle
 // once the remaining levels have fixed tau exactly.  Every element of the chosen bucket has p_hi >= 1 and so a record: level
 // 1 is histogrammed here and level 2 from the records.
-// Bound by the Philox rounds (18 wide multiplications per four elements): everything per element that can be left to the
-// candidates, one element in fifty, is left to them.  2^28 elements, 1 % kept: 264 us, where drawing, keep bits, and gathering
-// the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us (now: 264,
-// 22 for level 2, 21 to settle, 19 to write).
+// Bound by the Philox rounds (17 or 18 wide multiplications per four elements): everything per element that can be left to
+// the candidates, one element in fifty, is left to them, and a lane takes one candidate per turn, because four predicated
+// blocks, one per component, were a third of the pass.  2^28 elements, 1 % kept: 230 us, where drawing, keep bits, and
+// gathering the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us
+// (now 17 for level 2, 24 to settle, 20 to write).
 template <int STEPS>
 __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long long n, EwState* st, double s,
                                                unsigned long long stream_id, unsigned long long seed, Segments sg)
@@ -543,8 +638,12 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     __shared__ unsigned int l1cnt[1 << L1_BITS];
     __shared__ unsigned long long l1sig[1 << L1_BITS];
     const int tid = threadIdx.x, lane = tid & 63;
-    const long long seg = (long long)blockIdx.x * 4 + (tid >> 6);
+    const long long seg = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool vec = (((size_t)g) & 15) == 0, whole = vec && (seg + 1) * STEPS * STEP <= n;
+    float4 xv[4];                                                // (in flight while the search's result arrives)
+    load_steps(g, seg * STEPS * 64, n, whole, vec, xv);
     const SolveOut so = st->lvl[0];
+    clear_level(st, 2);
     const bool done = so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
@@ -559,10 +658,10 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
         ratio_lo = so.hi < inf ? 1.0 / so.hi : 0.0;              // 1 / hi <= ratio <= 1 / lo
         ratio_hi = so.lo > 0.0 ? 1.0 / so.lo : inf;
     }
-    const double down = 1.0 - 4.76837158203125e-07, up = 1.0 + 4.76837158203125e-07;     // 1 -+ 2^-21, of the ratios
+    const double down = 1.0 - 4.76837158203125e-07;              // 1 - 2^-21
     // a ratio beyond the float range is bounded from below by the largest float and from above by infinity
     const float r_lo = ratio_lo < 1.0e31 ? (float)(ratio_lo * 16777216.0 * down) : 3.0e38f;
-    const float r_hi = ratio_hi < 1.0e31 ? (float)(ratio_hi * 16777216.0 * up) : __int_as_float(0x7f800000);
+    const float r_hi = upper_ratio(ratio_hi);
     const bool zeros = !(ratio_hi < 1.0e31);                     // 0 * infinity: zeros are taken out by hand
     const unsigned int bucket = done ? 0xFFFFFFFFu : so.prefix;
     // Few elements in the bucket: straight into the global histogram, where they hardly ever meet.  Many: through LDS.
@@ -573,17 +672,14 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     }
 
     if (seg < sg.n_seg) {
-        const bool vec = (((size_t)g) & 15) == 0;
         const Slots sl = ew_slots(sg, seg);
         unsigned int fill = 0u;                                  // wave-uniform
         for (int j0 = 0; j0 < STEPS; j0 += 4) {
-            float4 xv[4];
-            const long long q0 = (seg * STEPS + j0) * 64 + lane;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) xv[u] = load4(g, q0 + u * 64, n, vec);
+            const long long q0 = (seg * STEPS + j0) * 64;
+            if (j0 > 0) load_steps(g, q0, n, whole, vec, xv);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const u32x4 rnd = philox4x32_10((unsigned long long)(unsigned int)(q0 + u * 64), stream_id, seed);
+                const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
                 const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
                 const float us[4] = {(float)(rnd.x >> 8), (float)(rnd.y >> 8), (float)(rnd.z >> 8), (float)(rnd.w >> 8)};
                 bool in[4];
@@ -597,17 +693,21 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
                 if (ballots[0] | ballots[1] | ballots[2] | ballots[3]) {
+                    // one candidate per lane and turn: a lane seldom has a second one
                     unsigned int pos = fill + listed_before(ballots);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (in[e]) {
-                            const bool sure = us[e] < fminf(16777216.0f, fabsf(xs[e]) * r_lo) * (1.0f - 2.384185791015625e-07f);
+                    unsigned int left = candidate_bits(in);
+                    do {
+                        if (left) {
+                            const int e = __builtin_ctz(left);
+                            left &= left - 1;
+                            const float x = pick(xs, e), uf = pick(us, e);
+                            const bool sure = uf < fminf(16777216.0f, fabsf(x) * r_lo) * (1.0f - 2.384185791015625e-07f);
                             if (pos < (unsigned int)sl.capacity) {
-                                sl.val[pos] = xs[e];
+                                sl.val[pos] = x;
                                 sl.word[pos] = (unsigned short)(((j0 + u) * STEP + lane * 4 + e) | (sure ? FLAG_BIT : 0u));
                             }
                             ++pos;
-                            const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
+                            const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
                             if ((key >> 20) == bucket) {
                                 const unsigned int b = (key >> 10) & ((1 << L1_BITS) - 1);
                                 if (through_lds) {
@@ -619,16 +719,12 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                                 }
                             }
                         }
-                    }
+                    } while (__ballot(left != 0u));
                     fill += listed_total(ballots);
                 }
             }
         }
         if (lane == 0) sg.count[seg] = fill <= (unsigned int)sl.capacity ? fill : OVER;
-    }
-    if (done) {
-        if (blockIdx.x == 0 && tid == 0) st->lvl[1].done = 1;    // nothing left for the levels below
-        return;
     }
     if (through_lds) {
         __syncthreads();
@@ -640,15 +736,10 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
             }
         }
     }
-    // the last workgroup to finish solves level 1 from the merged histogram
-    if (!last_workgroup(st->ticket[1])) return;
-    __shared__ SolveOut out;
-    solve_level<1, 256, true>(st, s, so.prefix, so.n_above, so.sum_below, &out, l1sig);     // (l1sig is spent: scratch)
-    if (tid == 0) publish(st, 1, out, s);
 }
 
-// Level-2 histogram of the elements on the path that level 1 chose, from the records (nothing to do if level 1 settled
-// everything); its last workgroup solves level 2.
+// Solves level 1; level-2 histogram of the elements on the path that it chose, from the records (nothing to do if level 1
+// settled everything).
 template <int STEPS>
 __global__ __launch_bounds__(256) void ew_level2(const float* __restrict__ g, long long n, EwState* st, double s, Segments sg)
 {
@@ -656,13 +747,14 @@ __global__ __launch_bounds__(256) void ew_level2(const float* __restrict__ g, lo
     __shared__ unsigned long long sig[1 << L2_BITS];
     __shared__ Group gr;
     __shared__ SolveOut out;
-    const SolveOut in = st->lvl[1];
-    if (in.done) return;
+    __shared__ unsigned long long scratch[2 * 4 + 1];
+    if (!enter_level2(st, s, &out, scratch)) return;
+    const unsigned int prefix = out.prefix;
     const int tid = threadIdx.x;
     for (int b = tid; b < (1 << L2_BITS); b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
     auto visit = [&](float x) {
         const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
-        if ((key >> L2_BITS) == in.prefix) {
+        if ((key >> L2_BITS) == prefix) {
             atomicAdd(&cnt[key & ((1 << L2_BITS) - 1)], 1u);
             atomicAdd(&sig[key & ((1 << L2_BITS) - 1)], (unsigned long long)significand(key));
         }
@@ -688,21 +780,20 @@ __global__ __launch_bounds__(256) void ew_level2(const float* __restrict__ g, lo
             atomicAdd(&st->sig[2][b], sig[b]);
         }
     }
-    if (!last_workgroup(st->ticket[2])) return;
-    solve_level<2, 256, true>(st, s, in.prefix, in.n_above, in.sum_below, &out, sig);
-    if (tid == 0) publish(st, 2, out, s);
 }
 
 // Settles the records of a group of segments with the final ratio: the draw of an open one is repeated, and what is not kept
 // is marked.  Leaves the kept count of the group.
 template <int STEPS>
-__global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, const EwState* st,
+__global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, EwState* st, double s,
                                                  unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int wsum[4];
     __shared__ Group gr;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double ratio = st->ratio;                              // final since the last solve
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ SolveOut out;
+    __shared__ unsigned long long scratch[2 * 4 + 1];
+    const double ratio = enter_final(st, s, &out, scratch);
     const long long first = (long long)blockIdx.x * sg.per_group;
     load_group(sg, blockIdx.x, gr);
     __syncthreads();
@@ -737,7 +828,12 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     }
     if (lane == 0) wsum[wave] = kept;
     __syncthreads();
-    if (tid == 0) sg.group_kept[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (tid == 0) {
+        unsigned int all = 0u;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) all += wsum[w];
+        sg.group_kept[blockIdx.x] = all;
+    }
 }
 
 // The message from the settled records, one group of segments per workgroup, which adds up the counts of all groups before
@@ -752,7 +848,7 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
     __shared__ unsigned long long bsum[4];
     __shared__ unsigned int wsum[2][4];
     __shared__ Group gr;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double ratio = st->ratio;
     const long long first = (long long)blockIdx.x * sg.per_group;
     unsigned long long part = 0ull;
@@ -761,7 +857,9 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
     for (int o = 32; o > 0; o >>= 1) part += __shfl_down(part, o);
     if (lane == 0) bsum[wave] = part;
     __syncthreads();
-    unsigned long long base = bsum[0] + bsum[1] + bsum[2] + bsum[3];
+    unsigned long long base = 0ull;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) base += bsum[w];
     auto put = [&](unsigned long long pos, unsigned int i, float x, float p) {
         if ((long long)pos < capacity) {
             if (LQ) {
@@ -817,62 +915,306 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
         if (LQ) base += gr.before[MAX_GROUP];
     }
     if (blockIdx.x == gridDim.x - 1 && tid == 0) {
-        st->total_kept = base;
         *count_out = (long long)base;
         if ((long long)base > capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
     }
-    if (!LQ) {   // the histograms have had their last reader: zero again for the next call
-        for (long long i = (long long)blockIdx.x * 256 + tid; i < 3 * NBUCKET; i += (long long)gridDim.x * 256) {
-            (&st->cnt[0][0])[i] = 0u;
-            (&st->sig[0][0])[i] = 0ull;
+    if (!LQ) {
+        clear_level(st, 0);
+        clear_level(st, 1);
+    }
+}
+
+// ---- one workgroup for everything ----------------------------------------------------------------------
+// Up to LOCAL_MAX elements are held in the registers of one workgroup: the three levels of the search run in LDS one behind
+// the other, without a launch, a ticket or a global atomic between them.  9610 elements: 9.6 us in all (load 0.6, level 0 3.9,
+// draws and message 4.2), where five launches took 22.  The draws of one compute unit grow with n: from about 2^15 elements
+// on the launches are the cheaper way.
+constexpr int LOCAL_T = 1024, LOCAL_PER = 16, LOCAL_MAX = LOCAL_T * LOCAL_PER;
+
+struct LocalScratch {
+    unsigned long long hist[4 * NBUCKET];        // packed as in hist_body; four copies at level 0
+    unsigned long long solve[2 * (LOCAL_T / 64) + 1];
+    SolveOut out;
+};
+
+// n_s and tail of the n elements; thread t holds element e * LOCAL_T + t as `key[e]` (bit pattern of the magnitude, ~0 where
+// there is none), e < per.  All LOCAL_T threads call; the result is in sc.out for all of them.
+__device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], int per, double s, LocalScratch& sc)
+{
+    const int tid = threadIdx.x;
+    auto clear = [&](int words) {
+        for (int b = tid; b < words; b += LOCAL_T) sc.hist[b] = 0ull;
+        __syncthreads();
+    };
+    auto add = [&](unsigned int b, unsigned int k) {
+        atomicAdd(&sc.hist[b], (1ull << 40) | (unsigned long long)significand(k));
+    };
+    const unsigned int copies = per > 2 ? 4u : 1u, copy = (tid & (copies - 1)) * NBUCKET;
+    clear((int)copies * NBUCKET);
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        if (e < per && key[e] != ~0u) add(copy + (key[e] >> 20), key[e]);
+    __syncthreads();
+    solve_hist<0, LOCAL_T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+        const unsigned long long w = sc.hist[b];
+        cnt = (unsigned int)(w >> 40);
+        sig = w & ((1ull << 40) - 1);
+        if (copies > 1u) {
+#pragma unroll
+            for (int c = 1; c < 4; ++c) {
+                const unsigned long long v = sc.hist[c * NBUCKET + b];
+                cnt += (unsigned int)(v >> 40);
+                sig += v & ((1ull << 40) - 1);
+            }
+        }
+    }, s, 0u, 0ull, 0.0, &sc.out, sc.solve);
+    auto read = [&](int b, unsigned int& cnt, unsigned long long& sig) {
+        cnt = (unsigned int)(sc.hist[b] >> 40);
+        sig = sc.hist[b] & ((1ull << 40) - 1);
+    };
+    if (sc.out.done) return;
+    SolveOut in = sc.out;
+    clear(1 << L1_BITS);
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        if (e < per && (key[e] >> 20) == in.prefix) add((key[e] >> 10) & ((1 << L1_BITS) - 1), key[e]);
+    __syncthreads();
+    solve_hist<1, LOCAL_T>(read, s, in.prefix, in.n_above, in.sum_below, &sc.out, sc.solve);
+    if (sc.out.done) return;
+    in = sc.out;
+    clear(1 << L2_BITS);
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        if (e < per && (key[e] >> 10) == in.prefix) add(key[e] & ((1 << L2_BITS) - 1), key[e]);
+    __syncthreads();
+    solve_hist<2, LOCAL_T>(read, s, in.prefix, in.n_above, in.sum_below, &sc.out, sc.solve);
+}
+
+__device__ inline unsigned int magnitude(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+
+// Draws and writes the message of a gradient that the workgroup holds: component e of thread t's float4 j is element
+// ((j * LOCAL_T + t) * 4 + e).
+template <bool LQ>
+__device__ inline void local_message(const float (&x)[LOCAL_PER], int n, double ratio, unsigned long long stream_id,
+                                     unsigned long long seed, long long capacity, unsigned int* idx, float* val, float* p_out,
+                                     long long* count_out, int* flags)
+{
+    constexpr int W = LOCAL_T / 64;
+    __shared__ unsigned int counts[LOCAL_PER / 4 * W + 1];       // kept, then kept before
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float r_hi = upper_ratio(ratio);                       // (see draw_segment)
+    unsigned int bits = 0u, before[LOCAL_PER / 4];
+#pragma unroll
+    for (int j = 0; j < LOCAL_PER / 4; ++j) {
+        before[j] = 0u;
+        if (j * LOCAL_T * 4 < n) {
+            const int q = j * LOCAL_T + tid;
+            unsigned long long ballots[4];
+            const u32x4 rnd = philox4x32_10((unsigned long long)q, stream_id, seed);
+            const unsigned int rs[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+            bool in[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) in[e] = !((float)(rs[e] >> 8) >= fabsf(x[j * 4 + e]) * r_hi);
+            if (p_out || __ballot(in[0] || in[1] || in[2] || in[3])) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float p = ew_probability(x[j * 4 + e], ratio);
+                    in[e] = in[e] && u01(rs[e]) < p;
+                    if (p_out && q * 4 + e < n) p_out[q * 4 + e] = p;
+                }
+            }
+            bits |= candidate_bits(in) << (4 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
+            before[j] = listed_before(ballots);
+            if (lane == 0) counts[j * W + wave] = listed_total(ballots);
+        } else if (lane == 0) {
+            counts[j * W + wave] = 0u;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        static_assert(LOCAL_PER / 4 * W == 64, "one count per lane");
+        const unsigned int mine = counts[lane];
+        unsigned int v = mine;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int w = __shfl_up(v, o);
+            if (lane >= o) v += w;
+        }
+        counts[lane] = v - mine;
+        if (lane == 63) {
+            *count_out = (long long)v;
+            if ((long long)v > capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < LOCAL_PER / 4; ++j) {
+        unsigned int pos = counts[j * W + wave] + before[j], left = (bits >> (4 * j)) & 15u;
+        const float xs[4] = {x[j * 4], x[j * 4 + 1], x[j * 4 + 2], x[j * 4 + 3]};
+        while (__ballot(left != 0u)) {
+            if (left) {
+                const int e = __builtin_ctz(left);
+                left &= left - 1;
+                if ((long long)pos < capacity) {
+                    const float xe = pick(xs, e);
+                    const unsigned int k = (unsigned int)((j * LOCAL_T + tid) * 4 + e);
+                    if (LQ) {
+                        idx[pos] = k | (xe < 0.0f ? 0x80000000u : 0u);
+                    } else {
+                        idx[pos] = k;
+                        val[pos] = xe / ew_probability(xe, ratio);
+                    }
+                }
+                ++pos;
+            }
         }
     }
 }
 
-// Small segments of atomo_probabilities: sort-based Algorithm 1, one workgroup per segment.
-struct SmallSeg { long long begin; int n; int pad; };
-
-__global__ __launch_bounds__(256) void prob_small(const float* __restrict__ lam, const SmallSeg* segs, double s,
-                                                  float* __restrict__ p)
+__device__ inline void local_load(const float* __restrict__ g, int n, float (&x)[LOCAL_PER])
 {
-    __shared__ float key[ALG1_MAX];
-    __shared__ int src[ALG1_MAX];
-    __shared__ Alg1Scratch sc;
-    const SmallSeg seg = segs[blockIdx.x];
-    const int n = seg.n, tid = threadIdx.x;
-    if (n <= 0) return;
-    int P = 1;
-    while (P < n) P <<= 1;
-    for (int i = tid; i < P; i += 256) {
-        key[i] = i < n ? fabsf(lam[seg.begin + i]) : -1.0f;
-        src[i] = i;
+    const bool vec = (((size_t)g) & 15) == 0;
+#pragma unroll
+    for (int j = 0; j < LOCAL_PER / 4; ++j) {
+        const float4 v = load4(g, j * LOCAL_T + (int)threadIdx.x, n, vec);
+        x[j * 4] = v.x; x[j * 4 + 1] = v.y; x[j * 4 + 2] = v.z; x[j * 4 + 3] = v.w;
     }
-    __syncthreads();
-    block_sort_desc(key, src, P);
-    const int ns = block_algorithm1(key, n, s, sc);
-    const double tail_ns = sc.tail_ns;
-    for (int i = tid; i < n; i += 256) p[seg.begin + src[i]] = alg1_probability(key[i], i, ns, s, tail_ns);
+}
+
+// The whole entry-wise encoder for n <= LOCAL_MAX.
+__global__ __launch_bounds__(LOCAL_T) void ew_encode_local(const float* __restrict__ g, int n, double s, unsigned long long stream_id,
+                                                           unsigned long long seed, long long capacity,
+                                                           unsigned int* __restrict__ idx, float* __restrict__ val, float* p_out,
+                                                           long long* count_out, int* flags)
+{
+    __shared__ LocalScratch sc;
+    float x[LOCAL_PER];
+    local_load(g, n, x);
+    unsigned int key[LOCAL_PER];
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        key[e] = ((e / 4) * LOCAL_T + (int)threadIdx.x) * 4 + e % 4 < n ? magnitude(x[e]) : ~0u;
+    local_water_level(key, (n + LOCAL_T * 4 - 1) / (LOCAL_T * 4) * 4, s, sc);
+    local_message<false>(x, n, final_ratio(s, sc.out.n_s, sc.out.tail), stream_id, seed, capacity, idx, val, p_out, count_out, flags);
+}
+
+// ---- atomo_probabilities --------------------------------------------------------------------------------
+struct LocalSeg { long long begin; int n; int pad; };
+
+// First launch: one workgroup per segment of up to LOCAL_MAX elements, start to end, and beside them, on workgroups of their
+// own, level 0 of the first longer segment (n_long elements from `lambda_long` on; 0: none).
+__global__ __launch_bounds__(LOCAL_T) void prob_first(const float* lam, const LocalSeg* segs, int n_local, double s, float* p,
+                                                      const float* lambda_long, long long n_long, EwState* st)
+{
+    __shared__ LocalScratch sc;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= n_local) {
+        const unsigned int self = blockIdx.x - n_local, members = gridDim.x - n_local;
+        hist_body<0, LOCAL_T>(lambda_long, n_long, st, sc.hist, 0u, self, members);
+        if (!last_workgroup(st->ticket, self, members)) return;
+        solve_level<0, LOCAL_T>(st, s, 0u, 0ull, 0.0, &sc.out, sc.solve);
+        if (tid == 0) publish(st, 0, sc.out, s);
+        return;
+    }
+    const LocalSeg seg = segs[blockIdx.x];
+    const int per = (seg.n + LOCAL_T - 1) / LOCAL_T;
+    float x[LOCAL_PER];
+    unsigned int key[LOCAL_PER];
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e) {
+        const int i = e * LOCAL_T + tid;
+        x[e] = i < seg.n ? lam[seg.begin + i] : 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e) key[e] = e * LOCAL_T + tid < seg.n ? magnitude(x[e]) : ~0u;
+    local_water_level(key, per, s, sc);
+    const double ratio = final_ratio(s, sc.out.n_s, sc.out.tail);
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        if (e * LOCAL_T + tid < seg.n) p[seg.begin + e * LOCAL_T + tid] = ew_probability(x[e], ratio);
+}
+
+// Histograms of levels 1 and 2 of a longer segment, nothing to do where an earlier level settled everything.
+template <int LEVEL>
+__global__ __launch_bounds__(256) void ew_hist(const float* x, long long n, EwState* st, double s)
+{
+    __shared__ unsigned long long acc[1 << L1_BITS];
+    __shared__ SolveOut out;
+    unsigned int prefix;
+    if (LEVEL == 1) {
+        clear_level(st, 2);
+        const SolveOut in = st->lvl[0];
+        if (in.done) return;
+        prefix = in.prefix;
+    } else {
+        if (!enter_level2(st, s, &out, acc)) return;
+        prefix = out.prefix;
+        __syncthreads();
+    }
+    hist_body<LEVEL, 256>(x, n, st, acc, prefix, blockIdx.x, gridDim.x);
+}
+
+// Solves level 2 and writes the probabilities.
+__global__ __launch_bounds__(256) void prob_last(const float* lam, long long n, EwState* st, double s, float* p)
+{
+    __shared__ SolveOut out;
+    __shared__ unsigned long long scratch[2 * 4 + 1];
+    write_p(lam, n, enter_final(st, s, &out, scratch), p);
+    clear_level(st, 0);
+    clear_level(st, 1);
 }
 
 // ---- l_q quantisation (Section 4) -------------------------------------------------------------------
 enum { LQ_MAX = 0, LQ_TWO = 1, LQ_ONE = 2, LQ_POW = 3 };
 constexpr int LQ_WGS = 1024;
 
-// Per-workgroup part of |g|_q: max |g_i|, or the sum of g_i^2, |g_i| or |g_i|^q in double (fixed thread ->
-// element map and fixed reduction tree, so the norm is the same bits in every run).
-__global__ __launch_bounds__(256) void lq_norm_partial(const float* __restrict__ g, long long n, int mode, double q,
-                                                       double* __restrict__ partial)
+// One more element of |g|_q: max |g_i|, or the sum of g_i^2, |g_i| or |g_i|^q in double.
+// POW: any q but 1, 2 and infinity (pow takes so many registers that it gets kernels of its own).
+template <bool POW>
+__device__ inline double lq_add(double acc, float x, int mode, double q)
+{
+    const double a = (double)fabsf(x);
+    if (POW) return a > 0.0 ? acc + pow(a, q) : acc;
+    if (mode == LQ_MAX) return fmax(acc, a);
+    if (mode == LQ_TWO) return fma(a, a, acc);
+    return acc + a;
+}
+
+// Result in thread 0.
+template <int T>
+__device__ inline double lq_block_reduce(double acc, int mode, double* wpart /* LDS [T / 64] */)
+{
+    for (int o = 32; o > 0; o >>= 1) {
+        const double other = __shfl_down(acc, o);
+        acc = mode == LQ_MAX ? fmax(acc, other) : acc + other;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) wpart[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    double t = wpart[0];
+    if (threadIdx.x == 0)
+        for (int w = 1; w < T / 64; ++w) t = mode == LQ_MAX ? fmax(t, wpart[w]) : t + wpart[w];
+    return t;
+}
+
+template <bool POW>
+__device__ inline double lq_norm(double acc, int mode, double q)
+{
+    if (POW) return pow(acc, 1.0 / q);
+    return mode == LQ_TWO ? sqrt(acc) : acc;
+}
+
+// The norm: a part per workgroup, finished by the last one (fixed thread -> element map and fixed reduction tree, so the norm
+// is the same bits in every run).
+template <bool POW>
+__global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g, long long n, int mode, double q, double* partial,
+                                                    EwState* st, float* norm_out)
 {
     __shared__ double wpart[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     double acc = 0.0;
-    auto visit = [&](float x) {
-        const double a = (double)fabsf(x);
-        if (mode == LQ_MAX) acc = fmax(acc, a);
-        else if (mode == LQ_TWO) acc = fma(a, a, acc);
-        else if (mode == LQ_ONE) acc += a;
-        else if (a > 0.0) acc += pow(a, q);
-    };
+    auto visit = [&](float x) { acc = lq_add<POW>(acc, x, mode, q); };
     const bool vec = (((size_t)g) & 15) == 0;
     const long long n4 = vec ? n / 4 : 0;
     const long long stride = (long long)gridDim.x * 256;
@@ -887,41 +1229,47 @@ __global__ __launch_bounds__(256) void lq_norm_partial(const float* __restrict__
         for (int u = 0; u < 4; ++u) { visit(x[u].x); visit(x[u].y); visit(x[u].z); visit(x[u].w); }
     }
     for (long long i = n4 * 4 + (long long)blockIdx.x * 256 + tid; i < n; i += stride) visit(g[i]);
-    for (int o = 32; o > 0; o >>= 1) {
-        const double other = __shfl_down(acc, o);
-        acc = mode == LQ_MAX ? fmax(acc, other) : acc + other;
-    }
-    if (lane == 0) wpart[wave] = acc;
-    __syncthreads();
+    const double part = lq_block_reduce<256>(acc, mode, wpart);
     if (tid == 0) {
-        double t = wpart[0];
-        for (int w = 1; w < 4; ++w) t = mode == LQ_MAX ? fmax(t, wpart[w]) : t + wpart[w];
-        partial[blockIdx.x] = t;
+        __hip_atomic_store(&partial[blockIdx.x], part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the last workgroup to finish: |g|_q from the partial results, 1 / |g|_q as the sampler's ratio, the message's norm
+    if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
+    double t = 0.0;
+    for (int k = tid; k < (int)gridDim.x; k += 256) {
+        const double v = __hip_atomic_load(&partial[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        t = mode == LQ_MAX ? fmax(t, v) : t + v;
+    }
+    t = lq_block_reduce<256>(t, mode, wpart);
+    if (tid == 0) {
+        const double norm = lq_norm<POW>(t, mode, q);
+        st->ratio = norm > 0.0 ? 1.0 / norm : 0.0;               // p_i = min(1, |g_i| / |g|_q)
+        *norm_out = (float)norm;
     }
 }
 
-// |g|_q from the partial results (one workgroup), 1 / |g|_q as the sampler's ratio, and the message's norm.
-__global__ __launch_bounds__(256) void lq_norm_final(const double* __restrict__ partial, int n_partial, int mode, double q,
-                                                     EwState* st, float* norm_out)
+// The whole l_q encoder for n <= LOCAL_MAX.
+template <bool POW>
+__global__ __launch_bounds__(LOCAL_T) void lq_encode_local(const float* __restrict__ g, int n, int mode, double q,
+                                                           unsigned long long stream_id, unsigned long long seed,
+                                                           long long capacity, unsigned int* __restrict__ idx, float* p_out,
+                                                           float* norm_out, long long* count_out, int* flags)
 {
-    __shared__ double tree[256];
-    const int tid = threadIdx.x;
-    double t = 0.0;
-    for (int k = tid; k < n_partial; k += 256) t = mode == LQ_MAX ? fmax(t, partial[k]) : t + partial[k];
-    tree[tid] = t;
+    __shared__ double wpart[LOCAL_T / 64];
+    __shared__ double norm_sh;
+    float x[LOCAL_PER];
+    local_load(g, n, x);
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < LOCAL_PER; ++e)
+        if (e / 4 * LOCAL_T * 4 < n) acc = lq_add<POW>(acc, x[e], mode, q);
+    const double t = lq_block_reduce<LOCAL_T>(acc, mode, wpart);
+    if (threadIdx.x == 0) {
+        norm_sh = lq_norm<POW>(t, mode, q);
+        *norm_out = (float)norm_sh;
+    }
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (tid < off) tree[tid] = mode == LQ_MAX ? fmax(tree[tid], tree[tid + off]) : tree[tid] + tree[tid + off];
-        __syncthreads();
-    }
-    if (tid == 0) {
-        const double acc = tree[0];
-        const double norm = mode == LQ_MAX || mode == LQ_ONE ? acc : mode == LQ_TWO ? sqrt(acc) : pow(acc, 1.0 / q);
-        st->ratio = norm > 0.0 ? 1.0 / norm : 0.0;               // p_i = min(1, |g_i| / |g|_q)
-        st->n_s = 0ull; st->tail = norm; st->budget = 1.0; st->total_kept = 0ull;
-        for (int k = 0; k < 3; ++k) st->lvl[k].done = 1;
-        *norm_out = (float)norm;
-    }
+    local_message<true>(x, n, norm_sh > 0.0 ? 1.0 / norm_sh : 0.0, stream_id, seed, capacity, idx, nullptr, p_out, count_out, flags);
 }
 
 // The l_q encoder's pass over the gradient behind the norm: draws against the exact p, one group of segments per workgroup.
@@ -930,7 +1278,7 @@ __global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long
                                                unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int wsum[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double ratio = st->ratio;
     const int mine = sg.per_group / 4;
     const long long seg0 = (long long)blockIdx.x * sg.per_group + wave * mine;
@@ -984,20 +1332,22 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     return l;
 }
 
-// Enqueues the three histogram / solve levels; afterwards st->{n_s, tail, budget} are final.
-void enqueue_water_level(atomo_ctx* ctx, const float* x, int64_t n, double s, EwState* st, hipStream_t stream)
+// The state of the search lives outside the shared workspace: its histograms and tickets are handed from call to call zeroed
+// (the last kernel of a call clears what it used), which saves a clearing launch at the head of every call.
+int search_state(atomo_ctx* ctx, hipStream_t stream, EwState** st)
 {
-    // No workgroup may visit 2^16 elements or more (field widths of the packed histogram word).
-    const int64_t floor_wgs = (n + 49151) / 49152;
-    const int wgs = (int)std::max<int64_t>(std::min<int64_t>(HIST_WGS, (n + 1023) / 1024), floor_wgs);
-    const int wgs0 = (int)std::max<int64_t>(std::min<int64_t>(256, (n + 4095) / 4096), floor_wgs);
-    { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(st); }
-    { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist<0><<<wgs0, 1024, 0, stream>>>(x, n, st); }
-    { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_solve<0><<<1, 256, 0, stream>>>(st, s); }
-    { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist<1><<<wgs, 256, 0, stream>>>(x, n, st); }
-    { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_solve<1><<<1, 256, 0, stream>>>(st, s); }
-    { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist<2><<<wgs, 256, 0, stream>>>(x, n, st); }
-    { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_solve<2><<<1, 256, 0, stream>>>(st, s); }
+    if (!ctx->ew_state) {
+        ATOMO_HIP(ctx, hipMalloc(&ctx->ew_state, sizeof(EwState)));
+        ATOMO_HIP(ctx, hipMemsetAsync(ctx->ew_state, 0, sizeof(EwState), stream));
+    }
+    *st = (EwState*)ctx->ew_state;
+    return ATOMO_OK;
+}
+
+// Workgroups of level 0: none may visit 2^16 elements or more (field widths of the packed histogram word).
+int level0_workgroups(int64_t n)
+{
+    return (int)std::max<int64_t>(std::min<int64_t>(256, (n + 4095) / 4096), (n + 49151) / 49152);
 }
 
 }  // namespace
@@ -1012,10 +1362,15 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
                              const atomo_ew_msg* msg, float* p_out, const EwLayout& l, bool clear_first, hipStream_t stream)
 {
     const int64_t n = msg->n;
+    if (n <= LOCAL_MAX) {
+        ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
+        ew_encode_local<<<1, LOCAL_T, 0, stream>>>(g, (int)n, s, stream_id, seed, (long long)msg->capacity, msg->idx, msg->val,
+                                                   p_out, (long long*)msg->count, ctx->d_flags);
+        ATOMO_HIP(ctx, hipGetLastError());
+        return ATOMO_OK;
+    }
     const Segments& sg = l.sg;
-    // No workgroup may visit 2^16 elements or more (field widths of the packed histogram word).
-    const int64_t floor_wgs = (n + 49151) / 49152;
-    const int wgs0 = (int)std::max<int64_t>(std::min<int64_t>(256, (n + 4095) / 4096), floor_wgs);
+    const int wgs0 = level0_workgroups(n);
     const int wgs2 = (int)std::min<int64_t>(HIST_WGS, sg.n_groups);
     const unsigned quads = (unsigned)((sg.n_seg + 3) / 4), groups = (unsigned)sg.n_groups;
     const bool long_seg = l.steps == 16;
@@ -1033,8 +1388,8 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
     }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
-        if (long_seg) ew_settle<16><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg);
-        else ew_settle<4><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg);
+        if (long_seg) ew_settle<16><<<groups, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
+        else ew_settle<4><<<groups, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
         const auto write = long_seg ? ew_write<16, false> : ew_write<4, false>;
         write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg, (long long)msg->capacity, msg->idx, msg->val,
                                           (long long*)msg->count, ctx->d_flags);
@@ -1052,14 +1407,9 @@ int encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t seed, ui
     const int64_t n = msg->n;
     int rc = ensure_workspace(ctx, entrywise_workspace_bytes(n));
     if (rc != ATOMO_OK) return rc;
-    // The search state lives outside the shared workspace: its histograms are handed from call to call zeroed (the
-    // last kernel of a call clears them), which saves the clearing launch at the head of every call.
-    if (!ctx->ew_state) {
-        ATOMO_HIP(ctx, hipMalloc(&ctx->ew_state, sizeof(EwState)));
-        ATOMO_HIP(ctx, hipMemsetAsync(ctx->ew_state, 0, sizeof(EwState), stream));
-    }
     EwLayout l = ew_layout(ctx->ws, n);
-    l.st = (EwState*)ctx->ew_state;
+    rc = search_state(ctx, stream, &l.st);
+    if (rc != ATOMO_OK) return rc;
     return enqueue_encode_entrywise(ctx, g, s, seed, stream_id, msg, p_out, l, false, stream);
 }
 
@@ -1069,14 +1419,24 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
     const int64_t n = msg->n;
     int rc = ensure_workspace(ctx, entrywise_workspace_bytes(n));
     if (rc != ATOMO_OK) return rc;
-    const EwLayout l = ew_layout(ctx->ws, n);
+    EwLayout l = ew_layout(ctx->ws, n);
+    rc = search_state(ctx, stream, &l.st);
+    if (rc != ATOMO_OK) return rc;
     const int mode = std::isinf(q) ? LQ_MAX : q == 2.0 ? LQ_TWO : q == 1.0 ? LQ_ONE : LQ_POW;
-    const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
+    if (n <= LOCAL_MAX) {
+        ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
+        const auto encode = mode == LQ_POW ? lq_encode_local<true> : lq_encode_local<false>;
+        encode<<<1, LOCAL_T, 0, stream>>>(g, (int)n, mode, q, stream_id, seed, (long long)msg->capacity, msg->idx, p_out,
+                                                   msg->norm, (long long*)msg->count, ctx->d_flags);
+        ATOMO_HIP(ctx, hipGetLastError());
+        return ATOMO_OK;
+    }
     {
         ProfScope ps(ctx, ATOMO_K_EW_HIST, stream);              // the norm pass takes the place of the histograms
-        lq_norm_partial<<<wgs, 256, 0, stream>>>(g, n, mode, q, l.lq_partial);
+        const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
+        const auto pass = mode == LQ_POW ? lq_norm_pass<true> : lq_norm_pass<false>;
+        pass<<<wgs, 256, 0, stream>>>(g, n, mode, q, l.lq_partial, l.st, msg->norm);
     }
-    { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); lq_norm_final<<<1, 256, 0, stream>>>(l.lq_partial, wgs, mode, q, l.st, msg->norm); }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
         const unsigned groups = (unsigned)l.sg.n_groups;
@@ -1095,32 +1455,43 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
 int probabilities(atomo_ctx* ctx, const float* lambda, const int64_t* offsets, int n_seg, double s, float* p,
                   hipStream_t stream)
 {
-    std::vector<SmallSeg> small;
+    std::vector<char>& table = ctx->table_scratch;
+    table.clear();
     std::vector<int> large;
+    int n_local = 0;
     for (int k = 0; k < n_seg; ++k) {
         const int64_t len = offsets[k + 1] - offsets[k];
         if (len == 0) continue;
-        if (len <= ALG1_MAX) small.push_back(SmallSeg{(long long)offsets[k], (int)len, 0});
-        else large.push_back(k);
+        if (len <= LOCAL_MAX) {
+            const LocalSeg seg{(long long)offsets[k], (int)len, 0};
+            table.insert(table.end(), (const char*)&seg, (const char*)(&seg + 1));
+            ++n_local;
+        } else {
+            large.push_back(k);
+        }
     }
-    size_t need = align_up(small.size() * sizeof(SmallSeg), 256) + 256;
-    if (!large.empty()) need += align_up(sizeof(EwState), 256);
-    int rc = ensure_workspace(ctx, need);
-    if (rc != ATOMO_OK) return rc;
-    Carver carve(ctx->ws);
-    SmallSeg* d_small = carve.take<SmallSeg>(small.size());
-    EwState* st = large.empty() ? nullptr : carve.take<EwState>(1);
-    if (!small.empty()) {
-        rc = upload(ctx, d_small, small.data(), small.size() * sizeof(SmallSeg), stream);
+    void* d_segs = nullptr;
+    if (n_local) {
+        const int rc = resident_tables(ctx, ctx->prob_tables, table, stream, &d_segs);
         if (rc != ATOMO_OK) return rc;
-        prob_small<<<(unsigned)small.size(), 256, 0, stream>>>(lambda, d_small, s, p);
     }
-    for (int k : large) {
-        const int64_t len = offsets[k + 1] - offsets[k];
-        const float* x = lambda + offsets[k];
-        enqueue_water_level(ctx, x, len, s, st, stream);
-        const int wgs = (int)std::min<int64_t>(4096, (len + 255) / 256);
-        ew_write_p<<<wgs, 256, 0, stream>>>(x, len, st, p + offsets[k]);
+    EwState* st = nullptr;
+    if (!large.empty()) {
+        const int rc = search_state(ctx, stream, &st);
+        if (rc != ATOMO_OK) return rc;
+    }
+    for (size_t j = 0; j < std::max<size_t>(large.size(), n_local ? 1 : 0); ++j) {
+        const bool any = j < large.size();
+        const int64_t begin = any ? offsets[large[j]] : 0, len = any ? offsets[large[j] + 1] - begin : 0;
+        const float* x = lambda + begin;
+        const int beside = j == 0 ? n_local : 0;                 // the short segments ride along with the first long one
+        prob_first<<<(unsigned)(beside + (any ? level0_workgroups(len) : 0)), LOCAL_T, 0, stream>>>(
+            lambda, (const LocalSeg*)d_segs, beside, s, p, x, len, st);
+        if (!any) break;
+        const int wgs = (int)std::max<int64_t>(std::min<int64_t>(HIST_WGS, (len + 4095) / 4096), (len + 49151) / 49152);
+        ew_hist<1><<<wgs, 256, 0, stream>>>(x, len, st, s);
+        ew_hist<2><<<wgs, 256, 0, stream>>>(x, len, st, s);
+        prob_last<<<(int)std::min<int64_t>(1024, (len + 1023) / 1024), 256, 0, stream>>>(x, len, st, s, p + begin);
     }
     ATOMO_HIP(ctx, hipGetLastError());
     return ATOMO_OK;

@@ -57,3 +57,17 @@ def test_long_segments(n):
     m = binding.atomo_encode_lq(ctx(), dev(g), float("inf"), 1, 2).to_host()
     want = oracle.encode_lq(g, float("inf"), 1, 2)
     assert ctx().status()[0] == 0 and len(np.setxor1d(want["idx"], m["idx"])) <= 2
+
+
+def test_probabilities_on_both_sides_of_the_one_workgroup_limit():
+    """Segments of one workgroup beside two long ones, five different layouts in turn (more than the tables kept) and again."""
+    rng = np.random.default_rng(0)
+    layouts = [[5, 16_384, 16_385, 1, 70_003], [16_385], [16_384], [0, 4096, 0, 4097, 200_000], [1, 2, 3, 16_383, 40_001, 7]]
+    for lengths in layouts + layouts[:2]:
+        offsets = np.concatenate([[0], np.cumsum(lengths)])
+        lam = (rng.standard_normal(offsets[-1]) * np.exp(2 * rng.standard_normal(offsets[-1]))).astype(np.float32)
+        p = binding.atomo_probabilities(ctx(), dev(lam), offsets, 3.5).cpu().numpy()
+        for lo, hi in zip(offsets[:-1], offsets[1:]):
+            if hi > lo:
+                want = oracle.probabilities(lam[lo:hi].astype(np.float64), 3.5)
+                np.testing.assert_allclose(p[lo:hi], want, rtol=1e-6, atol=1e-12)
