@@ -15,7 +15,7 @@ struct ThinMat {
     int nchunks, chunk;              // the positions of the long side in partial Gram matrices of `chunk` each
     int capacity;
     double* part;                    // [nchunks][3][16 * 16]: the tiles (0, 0), (0, 1), (1, 1) of the partial sums
-    double* u;                       // [r][r] kept vectors of the shorter side, divided by their sigma (folded: times the weight
+    double* u;                       // [r + 8][r] kept vectors of the shorter side, divided by their sigma (folded: times the weight
                                      //   where the longer side is U)
     int* count;
     int* idx;

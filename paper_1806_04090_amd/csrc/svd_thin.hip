@@ -24,9 +24,11 @@ namespace {
 constexpr int GRAM_WAVES = 8;
 constexpr int GRAM_CHUNK = 128 * GRAM_WAVES;   // positions per workgroup: eight rounds of 16 per wave
 constexpr int MAX_CHUNKS = 128;
+constexpr int AHEAD = 4;                       // rounds in flight
 constexpr int PART = 3 * 256;                  // doubles of a partial Gram matrix
 
-// Bound: one read of the data; the matrix cores have three 16 x 16 x 4 products per four positions (one up to 16 vectors).
+// Bound: the matrix cores, with a 16 x 16 x 4 product per four positions up to 16 vectors, three from there on; vectors 16 .. 19
+// (the 18 columns of a 3 x 3 convolution) take two of 4 x 4 x 4 in four blocks, an eighth of the time of the two they replace.
 // 11.16 M elements of 18 columns: THIN_GRAM_MEASURED
 __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats, const Work* work)
 {
@@ -35,14 +37,16 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
     const ThinMat& m = mats[wk.mat];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
     const int r = m.r, p_end = min(m.M, (wk.a + 1) * m.chunk);
-    const bool two = r > 16;
+    const bool two = r > 16, narrow = two && r <= 20;
     // entry (vector i, position p) at i * by_vec + p * by_pos; a lane holds vectors l16 and 16 + l16 (clamped: zeroed below)
     const long long by_vec = m.tall ? 1 : m.ldg, by_pos = m.tall ? m.ldg : 1;
     const Global<const float> g0 = global(m.G) + (long long)min(l16, r - 1) * by_vec;
-    const Global<const float> g1 = global(m.G) + (long long)min(16 + l16, r - 1) * by_vec;
-    const float m0 = l16 < r ? 1.0f : 0.0f, m1 = 16 + l16 < r ? 1.0f : 0.0f;
+    const int second = 16 + (narrow ? l16 & 3 : l16);
+    const Global<const float> g1 = global(m.G) + (long long)min(second, r - 1) * by_vec;
+    const float m0 = l16 < r ? 1.0f : 0.0f, m1 = second < r ? 1.0f : 0.0f;
+    double cross = 0.0, corner = 0.0;                            // narrow: entries (4 (l16 / 4) + q, second) and (16 + q, second)
     doublex4 acc[3] = {doublex4{0, 0, 0, 0}, doublex4{0, 0, 0, 0}, doublex4{0, 0, 0, 0}};
-    // the four positions p0 + 4 q + s of a round, one per instruction; the next round's are on their way meanwhile
+    // the four positions p0 + 4 q + s of a round, one per instruction; those of the next rounds are on their way meanwhile
     struct Round { float a[4], b[4]; };
     auto fetch = [&](int p0, Round& x) {
         const int p = p0 + 4 * q;
@@ -70,36 +74,46 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
             acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, u, acc[0], 0, 0, 0);
             if (two) {
                 const double v = m1 != 0.0f ? (double)x.b[s] : 0.0;
-                acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, v, acc[1], 0, 0, 0);
-                acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc[2], 0, 0, 0);
+                if (narrow) {
+                    // block b: rows 4 b .. 4 b + 3 (lane l16 = 4 b + row, position q) by columns 16 .. 19
+                    cross = __builtin_amdgcn_mfma_f64_4x4x4f64(u, v, cross, 0, 0, 0);
+                    corner = __builtin_amdgcn_mfma_f64_4x4x4f64(v, v, corner, 0, 0, 0);
+                } else {
+                    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, v, acc[1], 0, 0, 0);
+                    acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc[2], 0, 0, 0);
+                }
             }
         }
     };
     constexpr int STEP = 16 * GRAM_WAVES;
-    Round x, y;
+    Round x[AHEAD];
     int p0 = wk.a * m.chunk + 16 * wave;
-    if (p0 < p_end) fetch(p0, x);
-    for (; p0 < p_end; p0 += 2 * STEP) {
-        if (p0 + STEP < p_end) fetch(p0 + STEP, y);
-        add(x);
-        if (p0 + STEP >= p_end) break;
-        if (p0 + 2 * STEP < p_end) fetch(p0 + 2 * STEP, x);
-        add(y);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+        if (p0 + u * STEP < p_end) fetch(p0 + u * STEP, x[u]);
+    for (; p0 < p_end; p0 += AHEAD * STEP) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (p0 + u * STEP >= p_end) break;
+            add(x[u]);
+            if (p0 + (u + AHEAD) * STEP < p_end) fetch(p0 + (u + AHEAD) * STEP, x[u]);
+        }
     }
     // the waves' sums in a fixed order: the upper half of them hands its own over, then all add up
-    auto at = [&](int t, int v) { return t * 256 + (4 * v + q) * 16 + l16; };
     const int tiles = two ? 3 : 1;
-    if (wave >= GRAM_WAVES / 2) {
-        for (int t = 0; t < tiles; ++t)
+    auto give = [&](double* to, bool add) {
+        auto put = [&](int e, double x) { to[e] = add ? to[e] + x : x; };
+        for (int t = 0; t < (narrow ? 1 : tiles); ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave - GRAM_WAVES / 2][at(t, v)] = acc[t][v];
-    }
+            for (int v = 0; v < 4; ++v) put(t * 256 + (4 * v + q) * 16 + l16, acc[t][v]);
+        if (narrow) {
+            put(256 + (4 * (l16 >> 2) + q) * 16 + (l16 & 3), cross);
+            if (l16 < 4) put(512 + q * 16 + l16, corner);
+        }
+    };
+    if (wave >= GRAM_WAVES / 2) give(red[wave - GRAM_WAVES / 2], false);
     __syncthreads();
-    if (wave < GRAM_WAVES / 2) {
-        for (int t = 0; t < tiles; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave][at(t, v)] += acc[t][v];
-    }
+    if (wave < GRAM_WAVES / 2) give(red[wave], true);
     __syncthreads();
     const Global<double> out = global(m.part) + (size_t)wk.a * PART;
     for (int e = tid; e < 256 * tiles; e += 64 * GRAM_WAVES) {
@@ -115,13 +129,13 @@ constexpr int ST = 512;                        // threads of a workgroup of thin
 constexpr int LD = THIN_R + 1;
 constexpr int MAX_SWEEPS = 15;
 
-// 1 / sqrt(x) of a positive normal number: the hardware's estimate and two of Newton's steps.
+// 1 / sqrt(x) of a positive normal number: the hardware's estimate (23 bits) and one step of third order, two dependent
+// operations shorter than two of Newton's.
 __device__ inline double inverse_root(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return y;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double h = fma(-x * y, y, 1.0);                        // x y^2 = 1 - h
+    return fma(y * h, fma(0.375, h, 0.5), y);
 }
 
 // Jacobi rotation of the pair with diagonal entries a, b and off-diagonal g: columns (x, y) become (c x - s y, s x + c y),
@@ -137,9 +151,9 @@ __device__ inline void rotation(double a, double b, double g, double& c, double&
     s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
 }
 
-// Bound: latency, one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other,
-// threads 0 .. 255 one 2 x 2 block each; threads 256 .. 511 rotate the vectors in place, two pairs of entries each.  A wave works
-// out all rotations of the round in its first 16 lanes and hands them around inside.
+// Bound: latency, one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
+// 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
+// rotations of the round for itself and hands them around inside.
 __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
 {
     __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];
@@ -148,31 +162,48 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     __shared__ int rank_of[THIN_R];
     const ThinMat& m = mats[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = m.r;
-    // C in both triangles: sums over the chunks
-    const bool two = r > 16;
-    for (int e0 = tid; e0 < (two ? PART : 256); e0 += ST) {
-        const Global<const double> in = global((const double*)m.part) + e0;
-        double sum = 0.0;
-        int c = 0;
-        for (; c + 32 <= m.nchunks; c += 32) {
-            double x[32];
+    // C in both triangles: sums over the chunks, of the entries i <= j that there are.  Up to 256 of them leave half of the
+    // threads for the second half of the chunks.
+    {
+        const int entries = r * (r + 1) / 2, parts = entries <= ST / 2 ? 2 : 1;
+        const int share = (m.nchunks + parts - 1) / parts;
+        for (int f = tid & (ST / parts - 1); f < entries; f += ST / parts) {
+            // f = j (j + 1) / 2 + i
+            int j = (int)((sqrtf(8.0f * (float)f + 1.0f) - 1.0f) * 0.5f);
+            j += (j + 1) * (j + 2) / 2 <= f;
+            j -= j * (j + 1) / 2 > f;
+            const int i = f - j * (j + 1) / 2;
+            const int e = j < 16 ? i * 16 + j : i < 16 ? 256 + i * 16 + j - 16 : 512 + (i - 16) * 16 + j - 16;
+            const Global<const double> in = global((const double*)m.part) + e;
+            const int part = tid / (ST / parts);
+            int c = part * share;
+            const int end = min(m.nchunks, c + share);
+            double sum = 0.0;
+            for (; c + 32 <= end; c += 32) {
+                double x[32];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) x[u] = in[(size_t)(c + u) * PART];
+                for (int u = 0; u < 32; ++u) x[u] = in[(size_t)(c + u) * PART];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) sum += x[u];
+                for (int u = 0; u < 32; ++u) sum += x[u];
+            }
+            for (; c < end; c += 8) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = in[(size_t)min(c + u, end - 1) * PART];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sum += c + u < end ? x[u] : 0.0;
+            }
+            A[part][i * LD + j] = sum;
         }
-        for (; c + 4 <= m.nchunks; c += 4) {
-            double x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = in[(size_t)(c + u) * PART];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sum += x[u];
+        __syncthreads();
+        for (int e = tid; e < r * THIN_R; e += ST) {
+            const int i = e >> 5, j = e & 31;
+            if (i <= j && j < r) {
+                const double sum = A[0][i * LD + j] + (parts == 2 ? A[1][i * LD + j] : 0.0);
+                A[0][i * LD + j] = sum;
+                A[0][j * LD + i] = sum;
+            }
         }
-        for (; c < m.nchunks; ++c) sum += in[(size_t)c * PART];
-        const int t = e0 >> 8, e = e0 & 255, i = (e >> 4) + (t == 2 ? 16 : 0), j = (e & 15) + (t > 0 ? 16 : 0);
-        // (a square tile holds both triangles, equal to the last bit: the products commute)
-        A[0][i * LD + j] = sum;
-        if (t == 1) A[0][j * LD + i] = sum;
     }
     for (int e = tid; e < THIN_R * THIN_R; e += ST) V[(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
     if (tid < 2) unfinished[tid] = 0;
@@ -186,11 +217,17 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         if (tid < n) A[0][r * LD + tid] = A[0][tid * LD + r] = 0.0;
         __syncthreads();
     }
-    const int ka = (tid & 255) >> 4, kb = tid & 15;
+    // half^2 blocks of A on the first waves, as many pairs of entries of V (rows ka and ka + half) on the next ones: four waves,
+    // one per SIMD, up to 22 vectors
+    const int waves = (half * half + 63) >> 6, role = wave / waves;         // 0: A, 1: V, above: no part in it
+    const int first_e = (wave - role * waves) << 6, item = first_e + lane;
+    const int ka = item / half, kb = item - ka * half;
+    const bool valid = item < half * half;
+    const int lane_a = min(ka, half - 1) - first_e % half;                  // lane whose pair kb is pair ka
+    const int src_a = lane_a < 0 ? lane_a + half : lane_a;
     const double floor = 1e-13 * trace;
     // round t pairs n1 with t and t + k with t - k (mod n1); a thread holds pairs ka and kb and moves them on by one per round
     auto first_of = [&](int k, int& p, int& q) {
-        k = min(k, half - 1);
         p = k == 0 ? n1 : k;
         q = k == 0 ? 0 : n1 - k;
     };
@@ -200,56 +237,49 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     };
     auto at = [](int i) { return (i << 5) + i; };                // i * LD
     static_assert(LD == 33, "row offsets by shift and add");
-    const int row_v = at(ka);
+    const int row_v = at(min(ka, half - 1)), row_w = row_v + at(half);
     int pa, qa, pb, qb;
-    first_of(ka, pa, qa);
+    first_of(min(ka, half - 1), pa, qa);
     first_of(kb, pb, qb);
     int cur = 0, sweeps = 0;
     bool open = n > 1 && trace > 0.0;
     while (open && sweeps < MAX_SWEEPS) {
         bool turned = false;
         for (int round = 0; round < n1; ++round) {
-            const double* old = A[cur];
-            double* now = A[cur ^ 1];
-            // everything that will be needed, on its way before the rotations
-            const int ra = at(pa), sa_ = at(qa), rb = at(pb), sb_ = at(qb);
-            const double dp = old[rb + pb], dq = old[sb_ + qb], g = old[rb + qb];
-            double b00 = 0.0, b01 = 0.0, b10 = 0.0, b11 = 0.0;
-            if (tid < 256) {
-                b00 = old[ra + pb];
-                b01 = old[ra + qb];
-                b10 = old[sa_ + pb];
-                b11 = old[sa_ + qb];
-            } else {
-                b00 = V[row_v + pb];                           // rows ka and ka + 16, pair kb
-                b01 = V[row_v + qb];
-                b10 = V[row_v + 16 * LD + pb];
-                b11 = V[row_v + 16 * LD + qb];
-            }
-            double cb, sb;
-            rotation(dp, dq, g, cb, sb);
-            // the sweep is the last one if all cosines it met were small (what it leaves is then their square), rows at the
-            // rounding of the largest aside
-            turned = turned || (g * g > 1e-12 * dp * dq && fmin(dp, dq) > floor);
-            const double c00 = cb * b00 - sb * b01, c01 = sb * b00 + cb * b01;
-            const double c10 = cb * b10 - sb * b11, c11 = sb * b10 + cb * b11;
-            if (tid < 256) {
-                const double ca = __shfl(cb, ka), sa = __shfl(sb, ka);      // (lane k holds pair k)
-                if (ka < half && kb < half) {
-                    const bool diagonal = ka == kb;
-                    now[ra + pb] = ca * c00 - sa * c10;
-                    now[ra + qb] = diagonal ? 0.0 : ca * c01 - sa * c11;
-                    now[sa_ + pb] = diagonal ? 0.0 : sa * c00 + ca * c10;
-                    now[sa_ + qb] = sa * c01 + ca * c11;
+            if (role < 2) {
+                const double* old = A[cur];
+                double* now = A[cur ^ 1];
+                // everything that will be needed, on its way before the rotations
+                const int ra = at(pa), sa_ = at(qa), rb = at(pb), sb_ = at(qb);
+                const double dp = old[rb + pb], dq = old[sb_ + qb], g = old[rb + qb];
+                const double* from = role == 0 ? old : V;
+                const int up = role == 0 ? ra : row_v, down = role == 0 ? sa_ : row_w;
+                const double b00 = from[up + pb], b01 = from[up + qb], b10 = from[down + pb], b11 = from[down + qb];
+                double cb, sb;
+                rotation(dp, dq, g, cb, sb);
+                // the sweep is the last one if all cosines it met were small (what it leaves is then their square), rows at
+                // the rounding of the largest aside
+                turned = turned || (g * g > 1e-12 * dp * dq && fmin(dp, dq) > floor);
+                const double c00 = cb * b00 - sb * b01, c01 = sb * b00 + cb * b01;
+                const double c10 = cb * b10 - sb * b11, c11 = sb * b10 + cb * b11;
+                if (role == 0) {
+                    const double ca = __shfl(cb, src_a), sa = __shfl(sb, src_a);
+                    if (valid) {
+                        const bool diagonal = ka == kb;
+                        now[ra + pb] = ca * c00 - sa * c10;
+                        now[ra + qb] = diagonal ? 0.0 : ca * c01 - sa * c11;
+                        now[sa_ + pb] = diagonal ? 0.0 : sa * c00 + ca * c10;
+                        now[sa_ + qb] = sa * c01 + ca * c11;
+                    }
+                } else if (valid) {
+                    V[up + pb] = c00;
+                    V[up + qb] = c01;
+                    V[down + pb] = c10;
+                    V[down + qb] = c11;
                 }
-            } else if (kb < half) {
-                V[row_v + pb] = c00;
-                V[row_v + qb] = c01;
-                V[row_v + 16 * LD + pb] = c10;
-                V[row_v + 16 * LD + qb] = c11;
+                move_on(ka, pa, qa);
+                move_on(kb, pb, qb);
             }
-            move_on(ka, pa, qa);
-            move_on(kb, pb, qb);
             __syncthreads();
             cur ^= 1;
         }
@@ -319,82 +349,99 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
 }
 
 // ------------------------------------------------------------------------------------------------
-constexpr int LONG_POS = 1024;                 // positions per workgroup
-constexpr int LONG_GROUP = 4;
+constexpr int LONG_POS = 256;                  // positions per workgroup, one per thread
+constexpr int LONG_GROUP = 8;
 
-// Bound: one read of the data, four kept atoms per pass.  A thread owns one position of 256 at a time.  The r entries of a
-// position of a tall matrix lie side by side: they come through LDS, so that the loads are coalesced; those of a wide matrix come
-// from r coalesced rows.
-__global__ __launch_bounds__(256) void thin_long(const ThinMat* mats, const Work* work)
+// acc[k] += x * u[k][i], the u by scalar loads (the same for all lanes)
+template <int NK>
+__device__ inline void long_dots(const float* mine /* LDS, r entries */, const __attribute__((address_space(4))) double* u, int r,
+                                 double (&acc)[LONG_GROUP])
 {
-    __shared__ double us[LONG_GROUP][THIN_R];
-    __shared__ float xs[256 * (THIN_R + 1)];
+    for (int i = 0; i < r; ++i) {
+        const double d = (double)mine[i];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) acc[k] = fma(d, u[k * r + i], acc[k]);
+    }
+}
+
+// Bound: one read of the data.  The entries of a block of positions are fetched before anything is known about the kept atoms,
+// go through LDS (those of a position of a tall matrix lie side by side, and a thread owns a position) and are multiplied with up
+// to eight atoms per pass.
+__global__ __launch_bounds__(LONG_POS) void thin_long(const ThinMat* mats, const Work* work)
+{
+    __shared__ float xs[LONG_POS * (THIN_R + 1)];
     const Work wk = work[blockIdx.x];
     const ThinMat& m = mats[wk.mat];
-    const int kept = min(*m.count, m.capacity), r = m.r, tid = threadIdx.x;
+    const int r = m.r, tid = threadIdx.x;
     const bool tall = m.tall;
     const Global<const float> G = global(m.G);
-    const Global<float> out = global(tall ? m.U : m.V);
     const int ls = r | 1;                                        // stride of a position in LDS
     const int by_r = ((1 << 20) + r - 1) / r;
-    const bool dense = m.ldg == r;
+    const int first = wk.a * LONG_POS, here = min(LONG_POS, m.M - first);
+    if (tall) {
+        const Global<const float> block = G + (long long)first * m.ldg;
+        const int total = here * r;
+        // element e of the block: position e / r (by a multiplication that is exact below 2^13), entry e mod r
+        auto put = [&](int e, float x) {
+            const int p = (e * by_r) >> 20;
+            xs[p * ls + (e - p * r)] = x;
+        };
+        if (m.ldg == r && (((size_t)m.G) & 15) == 0) {           // (a block is a multiple of 16 bytes long)
+            typedef float floatx4 __attribute__((ext_vector_type(4)));
+            const Global<const floatx4> quads = (Global<const floatx4>)block;
+            floatx4 x[THIN_R / 4];
+#pragma unroll
+            for (int u = 0; u < THIN_R / 4; ++u)
+                if ((tid + LONG_POS * u) * 4 + 3 < total) x[u] = quads[tid + LONG_POS * u];
+#pragma unroll
+            for (int u = 0; u < THIN_R / 4; ++u) {
+                const int e = (tid + LONG_POS * u) * 4;
+                if (e + 3 < total) {
+                    put(e, x[u].x);
+                    put(e + 1, x[u].y);
+                    put(e + 2, x[u].z);
+                    put(e + 3, x[u].w);
+                }
+            }
+            if (tid < (total & 3)) put((total & ~3) + tid, block[(total & ~3) + tid]);
+        } else {
+            for (int e0 = tid; e0 < total; e0 += 8 * LONG_POS) {
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int e = min(e0 + LONG_POS * u, total - 1), p = (e * by_r) >> 20;
+                    x[u] = block[(long long)p * m.ldg + (e - p * r)];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) put(min(e0 + LONG_POS * u, total - 1), x[u]);
+            }
+        }
+    } else {
+        const Global<const float> g = G + first + min(tid, here - 1);
+        for (int i0 = 0; i0 < r; i0 += 16) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = g[min(i0 + u, r - 1) * m.ldg];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (i0 + u < r) xs[tid * ls + i0 + u] = x[u];
+        }
+    }
+    const int kept = min(*m.count, m.capacity);
+    __syncthreads();
+    if (tid >= here) return;
+    const Global<float> out = global(tall ? m.U : m.V) + first + tid;
+    const float* mine = xs + tid * ls;
     for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
         const int ns = min(LONG_GROUP, kept - s0);
-        __syncthreads();
-        if (tid < LONG_GROUP * THIN_R) {
-            const int k = tid / THIN_R, i = tid % THIN_R;
-            us[k][i] = k < ns && i < r ? global(m.u)[(s0 + k) * r + i] : 0.0;
-        }
-        for (int h = 0; h < LONG_POS / 256; ++h) {
-            const int first = wk.a * LONG_POS + 256 * h, here = min(256, m.M - first);
-            if (here <= 0) break;
-            __syncthreads();
-            double acc[LONG_GROUP] = {0.0, 0.0, 0.0, 0.0};
-            if (tall) {
-                const Global<const float> block = G + (long long)first * m.ldg;
-                // element e of the block of `here` positions: position e / r (by a multiplication that is exact below 2^13),
-                // entry e mod r; eight loads in flight
-                const int total = here * r;
-                for (int e0 = tid; e0 < total; e0 += 8 * 256) {
-                    float x[8];
-                    int to[8];
+        const __attribute__((address_space(4))) double* u = (const __attribute__((address_space(4))) double*)(m.u + s0 * r);
+        double acc[LONG_GROUP] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if (ns <= 2) long_dots<2>(mine, u, r, acc);              // (a vector past the kept ones is read but not used)
+        else if (ns <= 4) long_dots<4>(mine, u, r, acc);
+        else long_dots<8>(mine, u, r, acc);
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int e = min(e0 + 256 * u, total - 1), p = (e * by_r) >> 20;
-                        to[u] = p * ls + (e - p * r);
-                        x[u] = block[dense ? (long long)e : (long long)p * m.ldg + (e - p * r)];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) xs[to[u]] = x[u];
-                }
-                __syncthreads();
-                const float* mine = xs + min(tid, here - 1) * ls;
-                for (int i = 0; i < r; ++i) {
-                    const double d = (double)mine[i];
-#pragma unroll
-                    for (int k = 0; k < LONG_GROUP; ++k) acc[k] = fma(d, us[k][i], acc[k]);
-                }
-            } else {
-                const Global<const float> g = G + first + min(tid, here - 1);
-                __syncthreads();
-                for (int i0 = 0; i0 < r; i0 += 8) {
-                    float x[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) x[u] = g[min(i0 + u, r - 1) * m.ldg];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double d = i0 + u < r ? (double)x[u] : 0.0;
-#pragma unroll
-                        for (int k = 0; k < LONG_GROUP; ++k) acc[k] = fma(d, us[k][min(i0 + u, THIN_R - 1)], acc[k]);
-                    }
-                }
-            }
-            if (tid < here) {
-#pragma unroll
-                for (int k = 0; k < LONG_GROUP; ++k)
-                    if (k < ns) out[(size_t)(s0 + k) * m.M + first + tid] = (float)acc[k];
-            }
-        }
+        for (int k = 0; k < LONG_GROUP; ++k)
+            if (k < ns) out[(size_t)(s0 + k) * m.M] = (float)acc[k];
     }
 }
 
@@ -408,7 +455,7 @@ void plan_matrix(Carver& carve, ThinMat& m)
     m.chunk = (int)(GRAM_CHUNK * ((runs + MAX_CHUNKS - 1) / MAX_CHUNKS));
     m.nchunks = (int)(((long long)m.M + m.chunk - 1) / m.chunk);
     m.part = carve.take<double>((size_t)m.nchunks * PART);
-    m.u = carve.take<double>((size_t)m.r * m.r);
+    m.u = carve.take<double>((size_t)(m.r + LONG_GROUP) * m.r);          // (thin_long reads whole groups)
 }
 
 void plan_work(ThinPlan& plan)
