@@ -41,4 +41,69 @@ __device__ inline double reciprocal(double x)
     return fma(fma(-x, r, 1.0), r, r);
 }
 
+// ------------------------------------------------------------------------------------------------
+// wave helpers (64 lanes, no LDS)
+// ------------------------------------------------------------------------------------------------
+template <int CTRL>
+__device__ inline double dpp(double x)
+{
+    const unsigned a = (unsigned)__builtin_amdgcn_mov_dpp((int)lo32(x), CTRL, 0xf, 0xf, true);
+    const unsigned b = (unsigned)__builtin_amdgcn_mov_dpp((int)hi32(x), CTRL, 0xf, 0xf, true);
+    return mk64(a, b);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
+
+// lanes 0..31 of the result: a of the lane plus a of lane + 32; lanes 32..63: b of both
+__device__ inline double fold32(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
+    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
+}
+// the same between neighbouring rows of 16 lanes (even rows: a, odd rows: b)
+__device__ inline double fold16(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
+    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
+}
+__device__ inline double sum8(double x)      // over the 8 lanes of a group, in every lane
+{
+    x += dpp<DPP_XOR1>(x);
+    x += dpp<DPP_XOR2>(x);
+    x += dpp<DPP_HALF_MIRROR>(x);
+    return x;
+}
+// sum over the 64 lanes, the same bits in every lane
+__device__ inline double wave_sum(double x)
+{
+    x = sum8(x);
+    x += dpp<DPP_MIRROR>(x);
+    x = fold16(x, x);
+    return fold32(x, x);
+}
+
+// Step k: x = column k of the current matrix, v the Householder vector that maps x[k + 1 ..] to a multiple of the first
+// unit vector, p = A v, w = tau p - (tau^2 / 2)(v^T p) v, A <- A - v w^T - w v^T.
+// beta, the entry that remains, and v_{k+1} = alpha - beta; tau = 2 / v^T v.  (A column of zeros: the floor under the
+// root makes v a multiple of the first unit vector and the step a change of sign.  The trace is about 1.)
+__device__ inline void householder(double alpha, double sig2, double& beta, double& v0)
+{
+    beta = -copysign(root(fma(alpha, alpha, fmax(sig2, 1e-280))), alpha);
+    v0 = alpha - beta;
+}
+__device__ inline double householder_tau(double sig2, double v0) { return 2.0 * reciprocal(fma(v0, v0, sig2)); }
+
+// The search for eigenvalues of T (matrices scaled to a trace under 1), in cells of equal relative width.
+constexpr double OD2_MIN = 7.7e-34;          // 2^-110: keeps the Sturm recurrence going where T splits
+constexpr double FLOOR_REL = 1.4551915e-11;  // 2^-36: four times the squared fp32 floor of the encoder (ZERO_REL)
+constexpr int LAM_BITS = 27;                 // the search ends at this relative precision of lambda
+constexpr u64 LAM_MIN_BITS = 0x3CD0000000000000ull;   // 2^-50: anything below is zero (lambda_1 >= 2^-12 in this scale)
+constexpr u64 LAM_MAX_BITS = 0x3FF0000000000000ull;   // 1.0: the trace is below it
+constexpr int LAM_STEP_BITS = 52 - LAM_BITS;
+
+__device__ inline double bits_double(u64 b) { return __longlong_as_double((long long)b); }
+
+__device__ inline double cell_start(u64 cell) { return bits_double(LAM_MIN_BITS + (cell << LAM_STEP_BITS)); }
+
 }  // namespace atomo

@@ -31,59 +31,11 @@ enum { CLS_64 = 0, CLS_128, CLS_256, CLS_512, CLS_640, CLS_COUNT };
 constexpr int CLS_CHUNKS[CLS_COUNT] = {1, 2, 4, 8, 10};
 constexpr int CLS_WGS[CLS_COUNT] = {1, 1, 16, 16, 32};
 
-constexpr double OD2_MIN = 7.7e-34;          // 2^-110: keeps the Sturm recurrence going where T splits
-constexpr double FLOOR_REL = 1.4551915e-11;  // 2^-36: four times the squared fp32 floor of the encoder (ZERO_REL)
-constexpr int LAM_BITS = 27;                 // the search ends at this relative precision of lambda
-constexpr u64 LAM_MIN_BITS = 0x3CD0000000000000ull;   // 2^-50: anything below is zero (lambda_1 >= 2^-12 in this scale)
-constexpr u64 LAM_MAX_BITS = 0x3FF0000000000000ull;   // 1.0: the trace is below it
-constexpr int LAM_STEP_BITS = 52 - LAM_BITS;
-
-// ------------------------------------------------------------------------------------------------
-// wave helpers (64 lanes, no LDS)
-// ------------------------------------------------------------------------------------------------
-template <int CTRL>
-__device__ inline double dpp(double x)
-{
-    const unsigned a = (unsigned)__builtin_amdgcn_mov_dpp((int)lo32(x), CTRL, 0xf, 0xf, true);
-    const unsigned b = (unsigned)__builtin_amdgcn_mov_dpp((int)hi32(x), CTRL, 0xf, 0xf, true);
-    return mk64(a, b);
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
-
-// lanes 0..31 of the result: a of the lane plus a of lane + 32; lanes 32..63: b of both
-__device__ inline double fold32(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
-    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
-}
-// the same between neighbouring rows of 16 lanes (even rows: a, odd rows: b)
-__device__ inline double fold16(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
-    return mk64(l[0], h[0]) + mk64(l[1], h[1]);
-}
 __device__ inline double fold8(double a, double b, int lane)
 {
     const bool up = lane & 8;
     const double keep = up ? b : a, give = up ? a : b;
     return keep + dpp<DPP_ROR8>(give);
-}
-__device__ inline double sum8(double x)      // over the 8 lanes of a group, in every lane
-{
-    x += dpp<DPP_XOR1>(x);
-    x += dpp<DPP_XOR2>(x);
-    x += dpp<DPP_HALF_MIRROR>(x);
-    return x;
-}
-// sum over the 64 lanes, the same bits in every lane
-__device__ inline double wave_sum(double x)
-{
-    x = sum8(x);
-    x += dpp<DPP_MIRROR>(x);
-    x = fold16(x, x);
-    return fold32(x, x);
 }
 // K <= 8 sums over the 64 lanes at once: lane l receives sum number (l >> 5 & 1) | (l >> 4 & 1) << 1 | (l >> 3 & 1) << 2
 template <int K>
@@ -263,17 +215,6 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
 // ------------------------------------------------------------------------------------------------
 // Householder reduction C = H T H^T
 // ------------------------------------------------------------------------------------------------
-// Step k: x = column k of the current matrix, v the Householder vector that maps x[k + 1 ..] to a multiple of the first
-// unit vector, p = A v, w = tau p - (tau^2 / 2)(v^T p) v, A <- A - v w^T - w v^T.
-// beta, the entry that remains, and v_{k+1} = alpha - beta; tau = 2 / v^T v.  (A column of zeros: the floor under the
-// root makes v a multiple of the first unit vector and the step a change of sign.  The trace is about 1.)
-__device__ inline void householder(double alpha, double sig2, double& beta, double& v0)
-{
-    beta = -copysign(root(fma(alpha, alpha, fmax(sig2, 1e-280))), alpha);
-    v0 = alpha - beta;
-}
-__device__ inline double householder_tau(double sig2, double v0) { return 2.0 * reciprocal(fma(v0, v0, sig2)); }
-
 // Where the steps are kept.
 struct StepStore {
     Global<double> refl, tau, td, od;
@@ -779,15 +720,11 @@ __device__ inline int sturm_count(scalar_ptr t, int n, double z)
     return count;
 }
 
-__device__ inline double bits_double(u64 b) { return __longlong_as_double((long long)b); }
-
 // Eigenvalue number i (descending) in [2^-50, 1), searched on the bit pattern of the double, in cells of 2^25 patterns
 // (LAM_BITS relative bits): a first pass at 256 points for all eigenvalues of the workgroup, then `lanes` points per
 // eigenvalue and pass.  The cell that is found does not depend on how many points a pass has.
 // Work: matrix, first eigenvalue; 256 / lanes eigenvalues per workgroup.  Behind the n_eig of these: matrix, block of
 // reflectors (block_factor: wanted by the next kernels, and this one leaves the room).
-__device__ inline double cell_start(u64 cell) { return bits_double(LAM_MIN_BITS + (cell << LAM_STEP_BITS)); }
-
 __global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats, const Work* work, int n_eig, int lanes)
 {
     if ((int)blockIdx.x >= n_eig) {

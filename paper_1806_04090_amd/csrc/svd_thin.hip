@@ -151,15 +151,199 @@ __device__ inline void rotation(double a, double b, double g, double& c, double&
     s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
 }
 
-// Bound: latency, one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
+// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n to THIN_R) by one wave: diagonal d, off-diagonal
+// e; the vectors of the steps go to the rows of H, C is used up.  Lane l holds row l mod 32 and every other column.
+__device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d, double* e, double* tau, int n)
+{
+    const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
+    auto in_order = [] {                                         // (the wave's LDS operations are performed in program order)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int k = 0; k + 2 < n; ++k) {
+        const double x = C[i * LD + k], alpha = C[(k + 1) * LD + k], diagonal = C[k * LD + k];
+        const double sig2 = wave_sum(h == 0 && i > k + 1 ? x * x : 0.0);
+        double beta, v0;
+        householder(alpha, sig2, beta, v0);
+        const double t = householder_tau(sig2, v0);
+        const double v = i > k + 1 ? x : i == k + 1 ? v0 : 0.0;
+        if (h == 0) H[k * LD + i] = v;
+        in_order();
+        // columns k + 1 + h, k + 3 + h, ..
+        constexpr int U = THIN_R / 2;
+        double c[U], vj[U];
+        double part = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; u += 4) {
+            if (k + 1 + 2 * u >= n) break;
+#pragma unroll
+            for (int y = u; y < u + 4; ++y) {
+                const int j = min(k + 1 + h + 2 * y, THIN_R - 1);
+                c[y] = C[i * LD + j];
+                vj[y] = k + 1 + h + 2 * y < n ? H[k * LD + j] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u += 4) {
+            if (k + 1 + 2 * u >= n) break;
+#pragma unroll
+            for (int y = u; y < u + 4; ++y) part = fma(c[y], vj[y], part);
+        }
+        const double p = i > k ? t * fold32(part, part) : 0.0;
+        const double pv = wave_sum(h == 0 ? p * v : 0.0);
+        const double w = fma(-0.5 * t * pv, v, p);
+        if (h == 0) w_sh[i] = w;
+        in_order();
+#pragma unroll
+        for (int u = 0; u < U; u += 4) {
+            if (k + 1 + 2 * u >= n) break;
+            double wj[4];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) wj[y] = w_sh[min(k + 1 + h + 2 * (u + y), THIN_R - 1)];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int j = k + 1 + h + 2 * (u + y);
+                if (j < n && i > k) C[i * LD + j] = fma(-v, wj[y], fma(-w, vj[u + y], c[u + y]));
+            }
+        }
+        if (lane == 0) {
+            d[k] = diagonal;
+            e[k] = beta;
+            tau[k] = t;
+        }
+        in_order();
+    }
+    if (lane == 0) {
+        if (n > 1) {
+            d[n - 2] = C[(n - 2) * LD + n - 2];
+            e[n - 2] = C[(n - 1) * LD + n - 2];
+        }
+        d[n - 1] = C[(n - 1) * LD + n - 1];
+    }
+}
+
+// Eigenvalues of T below z (see svd_direct.hip): t holds (e_{i-1}^2, d_i), n_pad of them, a multiple of eight, in LDS.
+__device__ inline int sturm_below(const doublex2* t, int n_pad, double z)
+{
+    double p0 = 0.0, p1 = 1.0;
+    unsigned signs = 0;
+    for (int i = 0; i < n_pad; i += 8) {
+        doublex2 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = t[i + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double p2 = fma(x[u].y - z, p1, -(x[u].x * p0));
+            p0 = p1;
+            p1 = p2;
+            signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+        }
+        const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+        p0 = __builtin_amdgcn_ldexp(p0, -ex);
+        p1 = __builtin_amdgcn_ldexp(p1, -ex);
+    }
+    return __popc(signs ^ (signs >> 1));
+}
+
+// All eigenvalues of T, descending, by the ST threads of the workgroup (all call): a first pass at ST points, then 16 points per
+// eigenvalue and pass, until a cell is left.
+__device__ inline void eigenvalues(const doublex2* t, int n_pad, int n, int* below /* LDS [ST] */, double* lam)
+{
+    constexpr u64 CELLS = (LAM_MAX_BITS - LAM_MIN_BITS) >> LAM_STEP_BITS, SPAN = CELLS / ST;
+    constexpr int LANES = ST / THIN_R;
+    const int tid = threadIdx.x, lane = tid & 63;
+    below[tid] = sturm_below(t, n_pad, cell_start(SPAN * tid));
+    __syncthreads();
+    const int l = tid & (LANES - 1), base = lane & ~(LANES - 1), i = tid / LANES, asc = n - 1 - i;
+    if (i < n) {
+        int lo = 0, hi = ST;                                     // last point with at most asc eigenvalues below it
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (below[mid] <= asc) lo = mid; else hi = mid;
+        }
+        const bool zero = below[0] > asc;
+        u64 g0 = SPAN * lo, g1 = zero ? g0 : g0 + SPAN;
+        const u64 group = ((1ull << LANES) - 1) << base;
+        while (g1 - g0 > 1) {                                    // (the lanes of an eigenvalue agree)
+            const u64 z = g0 + (g1 - g0) * (unsigned)(l + 1) / (unsigned)(LANES + 1);
+            const int k = __popcll(__ballot(sturm_below(t, n_pad, cell_start(z)) <= asc) & group);
+            const u64 z_lo = __shfl(z, base + max(k - 1, 0)), z_hi = __shfl(z, base + min(k, LANES - 1));
+            if (k > 0) g0 = z_lo;
+            if (k < LANES) g1 = z_hi;
+        }
+        if (l == 0) lam[i] = zero ? 0.0 : bits_double(LAM_MIN_BITS + (g0 << LAM_STEP_BITS) + (1ull << (LAM_STEP_BITS - 1)));
+    }
+}
+
+// Eigenvectors of T for the eigenvalues next to lam, one per lane and half-wave, into the rows of Z (not normalised; 1 / length
+// in length_inv): twisted factorisations, lanes 0 .. 31 with the pivots from the top and lanes 32 .. 63 with those from the bottom,
+// joined where the two meet with the smallest pivot.  The Rayleigh quotient corrects lam; the third round starts within
+// 2^-24 of the gap to the next kept eigenvalue.
+__device__ inline void twisted_vectors(const double* d, const double* e, int n, int count, double lam, double* P0, double* P1,
+                                       double* Z, double* length_inv)
+{
+    const int lane = threadIdx.x & 63, a = lane & 31;
+    const bool bottom = lane >= 32, real = a < count;
+    double* P = (bottom ? P1 : P0) + a * LD;
+    double* z = Z + a * LD;
+    auto in_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto pivot = [](double x) { return fabs(x) < 1e-150 ? copysign(1e-150, x) : x; };
+    double len2 = 1.0;
+    for (int round = 0; round < 3; ++round) {
+        double x = 0.0;
+        for (int k = 0; k < n; ++k) {
+            const int i = bottom ? n - 1 - k : k;
+            const double off = k == 0 ? 0.0 : e[bottom ? i : i - 1];
+            x = pivot((d[i] - lam) - (k == 0 ? 0.0 : off * off * reciprocal(x)));
+            if (real) P[i] = x;
+        }
+        in_order();
+        int at = 0;
+        double least = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const double g = real ? P0[a * LD + i] + P1[a * LD + i] - (d[i] - lam) : 1.0;
+            if (i == 0 || fabs(g) < fabs(least)) { least = g; at = i; }
+        }
+        double y = 1.0, sum = 0.0;
+        if (real && !bottom) z[at] = 1.0;
+        for (int k = 1; k < n; ++k) {
+            const int i = bottom ? at + k : at - k;
+            if (real && i >= 0 && i < n) {
+                y = -e[bottom ? i - 1 : i] * reciprocal(P[i]) * y;
+                z[i] = y;
+                sum = fma(y, y, sum);
+            }
+        }
+        len2 = 1.0 + fold32(sum, sum);
+        lam += real ? least * reciprocal(len2) : 0.0;
+        in_order();
+    }
+    if (real && !bottom) length_inv[a] = inverse_root(len2);
+}
+
+// Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
+// the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
+// zeros aside; kept neighbours apart); otherwise the two-sided Jacobi iteration.  18 columns: THIN_SOLVE_MEASURED
+// Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.
 __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
 {
     __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];
+    __shared__ double P1[THIN_R * LD], Z[THIN_R * LD];           // direct: V holds the reflectors, A[1] the reduced matrix, then pivots
+    __shared__ doublex2 T[THIN_R];
+    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R], tlen[THIN_R];
+    __shared__ int below[ST];
     __shared__ int unfinished[2];
     __shared__ double lam[THIN_R];
     __shared__ int rank_of[THIN_R];
+    __shared__ u64 drawn;
+    __shared__ int accepted;
     const ThinMat& m = mats[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = m.r;
     // C in both triangles: sums over the chunks, of the entries i <= j that there are.  Up to 256 of them leave half of the
@@ -205,107 +389,23 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             }
         }
     }
-    for (int e = tid; e < THIN_R * THIN_R; e += ST) V[(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
     if (tid < 2) unfinished[tid] = 0;
     __syncthreads();
-    // tournament over n = r rounded up to even (an entry past r is a row of zeros and never rotates)
-    const int n = (r + 1) & ~1, half = n >> 1, n1 = n - 1;
     double trace = 0.0;
-    for (int i = 0; i < r; ++i) trace += A[0][i * LD + i];
-    if (r & 1) {                                                 // the row and column of zeros
-        __syncthreads();
-        if (tid < n) A[0][r * LD + tid] = A[0][tid * LD + r] = 0.0;
-        __syncthreads();
+    int zero_rows = 0;
+    for (int i = 0; i < r; ++i) {
+        const double x = A[0][i * LD + i];
+        trace += x;
+        zero_rows += x == 0.0;
     }
-    // half^2 blocks of A on the first waves, as many pairs of entries of V (rows ka and ka + half) on the next ones: four waves,
-    // one per SIMD, up to 22 vectors
-    const int waves = (half * half + 63) >> 6, role = wave / waves;         // 0: A, 1: V, above: no part in it
-    const int first_e = (wave - role * waves) << 6, item = first_e + lane;
-    const int ka = item / half, kb = item - ka * half;
-    const bool valid = item < half * half;
-    const int lane_a = min(ka, half - 1) - first_e % half;                  // lane whose pair kb is pair ka
-    const int src_a = lane_a < 0 ? lane_a + half : lane_a;
-    const double floor = 1e-13 * trace;
-    // round t pairs n1 with t and t + k with t - k (mod n1); a thread holds pairs ka and kb and moves them on by one per round
-    auto first_of = [&](int k, int& p, int& q) {
-        p = k == 0 ? n1 : k;
-        q = k == 0 ? 0 : n1 - k;
-    };
-    auto move_on = [&](int k, int& p, int& q) {
-        if (k != 0) p = p + 1 == n1 ? 0 : p + 1;
-        q = q + 1 == n1 ? 0 : q + 1;
-    };
-    auto at = [](int i) { return (i << 5) + i; };                // i * LD
-    static_assert(LD == 33, "row offsets by shift and add");
-    const int row_v = at(min(ka, half - 1)), row_w = row_v + at(half);
-    int pa, qa, pb, qb;
-    first_of(min(ka, half - 1), pa, qa);
-    first_of(kb, pb, qb);
-    int cur = 0, sweeps = 0;
-    bool open = n > 1 && trace > 0.0;
-    while (open && sweeps < MAX_SWEEPS) {
-        bool turned = false;
-        for (int round = 0; round < n1; ++round) {
-            if (role < 2) {
-                const double* old = A[cur];
-                double* now = A[cur ^ 1];
-                // everything that will be needed, on its way before the rotations
-                const int ra = at(pa), sa_ = at(qa), rb = at(pb), sb_ = at(qb);
-                const double dp = old[rb + pb], dq = old[sb_ + qb], g = old[rb + qb];
-                const double* from = role == 0 ? old : V;
-                const int up = role == 0 ? ra : row_v, down = role == 0 ? sa_ : row_w;
-                const double b00 = from[up + pb], b01 = from[up + qb], b10 = from[down + pb], b11 = from[down + qb];
-                double cb, sb;
-                rotation(dp, dq, g, cb, sb);
-                // the sweep is the last one if all cosines it met were small (what it leaves is then their square), rows at
-                // the rounding of the largest aside
-                turned = turned || (g * g > 1e-12 * dp * dq && fmin(dp, dq) > floor);
-                const double c00 = cb * b00 - sb * b01, c01 = sb * b00 + cb * b01;
-                const double c10 = cb * b10 - sb * b11, c11 = sb * b10 + cb * b11;
-                if (role == 0) {
-                    const double ca = __shfl(cb, src_a), sa = __shfl(sb, src_a);
-                    if (valid) {
-                        const bool diagonal = ka == kb;
-                        now[ra + pb] = ca * c00 - sa * c10;
-                        now[ra + qb] = diagonal ? 0.0 : ca * c01 - sa * c11;
-                        now[sa_ + pb] = diagonal ? 0.0 : sa * c00 + ca * c10;
-                        now[sa_ + qb] = sa * c01 + ca * c11;
-                    }
-                } else if (valid) {
-                    V[up + pb] = c00;
-                    V[up + qb] = c01;
-                    V[down + pb] = c10;
-                    V[down + qb] = c11;
-                }
-                move_on(ka, pa, qa);
-                move_on(kb, pb, qb);
-            }
-            __syncthreads();
-            cur ^= 1;
-        }
-        if (turned) unfinished[sweeps & 1] = 1;
-        __syncthreads();
-        open = unfinished[sweeps & 1] != 0;
-        ++sweeps;
-        if (tid == 0) unfinished[sweeps & 1] = 0;                // (written again only after the barriers of the next sweep)
-    }
-    if (tid < r) lam[tid] = A[cur][tid * LD + tid];
-    if (tid < THIN_R) rank_of[tid] = 0;                          // (not all of them are written if lam is not a number)
-    __syncthreads();
-    if (tid < r) {
-        int before = 0;
-        const double mine = lam[tid];
-        for (int j = 0; j < r; ++j) before += lam[j] > mine || (lam[j] == mine && j < tid);
-        rank_of[before] = tid;
-    }
-    __syncthreads();
-    // one wave: sigma, Algorithm 1 (the first index whose probability stays under 1, see block_algorithm1), the draw
-    if (wave == 0) {
+    // wave 0: sigma, Algorithm 1 (the first index whose probability stays under 1, see block_algorithm1), the draw
+    float sigma = 0.0f, p = 0.0f;
+    u64 mask = 0ull;
+    auto draw = [&] {
         const double l0 = lam[rank_of[0]];
-        const int src = lane < r ? rank_of[lane] : 0;
-        const double l = lam[src];
+        const double l = lam[lane < r ? rank_of[lane] : 0];
         const bool real = lane < r && l > (double)svd::ZERO_REL * l0;
-        const float sigma = real ? (float)sqrt(l) : 0.0f;
+        sigma = real ? (float)sqrt(l) : 0.0f;
         double tail = 0.0;                                       // sum of the sigmas from this one on, smallest first
         for (int j = r - 1; j >= 0; --j) {
             const float sj = __shfl(sigma, j);
@@ -314,17 +414,150 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         const u64 under = __ballot(lane < r && (double)sigma * (s - (double)lane) <= tail);
         const int ns = under ? __ffsll((unsigned long long)under) - 1 : r;
         const double tail_ns = ns < r ? __shfl(tail, ns) : 0.0;
-        const float p = lane < r ? alg1_probability(sigma, lane, ns, s, tail_ns) : 0.0f;
+        p = lane < r ? alg1_probability(sigma, lane, ns, s, tail_ns) : 0.0f;
         const u32x4 rnd = philox4x32_10((u64)(lane >> 2), m.stream_id, seed);
         const uint32_t word = (lane & 3) == 0 ? rnd.x : (lane & 3) == 1 ? rnd.y : (lane & 3) == 2 ? rnd.z : rnd.w;
-        const bool kept = lane < r && u01(word) < p;
-        const u64 mask = __ballot(kept);
+        mask = __ballot(lane < r && u01(word) < p);
+    };
+    bool direct = trace > 1e-280 && trace < 1e280;               // (false for NaN)
+    int expo = 0;
+    if (direct) {
+        // scaled by a power of four to a trace in [1/4, 1)
+        (void)frexp(trace, &expo);
+        expo += expo & 1;
+        for (int e = tid; e < THIN_R * THIN_R; e += ST) {
+            const int i = e >> 5, j = e & 31;
+            A[1][i * LD + j] = i < r && j < r ? ldexp(A[0][i * LD + j], -expo) : 0.0;
+        }
+        __syncthreads();
+        if (wave == 0) tridiagonal(A[1], V, tw, td, te, ttau, r);
+        __syncthreads();
+        const int n_pad = (r + 7) & ~7, pad = n_pad - r;
+        if (tid < n_pad) {
+            const int i = tid - pad;
+            const double off = i > 0 ? te[i - 1] : 0.0;
+            T[tid] = i < 0 ? doublex2{0.0, 2.0} : doublex2{i > 0 ? fmax(off * off, OD2_MIN) : 0.0, td[i]};
+        }
+        if (tid < THIN_R) rank_of[tid] = tid;
+        __syncthreads();
+        eigenvalues(T, n_pad, r, below, lam);
+        __syncthreads();
+        if (wave == 0) {
+            draw();
+            const double l = lane < r ? lam[lane] : 0.0, up = lane > 0 && lane < r ? lam[lane - 1] : 0.0;
+            // two kept neighbours closer than 2^-22 of themselves: their vectors are not separated
+            const bool close = lane > 0 && lane < r && ((mask >> lane) & (mask >> (lane - 1)) & 1ull) && up - l <= l * 2.384185791015625e-07;
+            const bool resolved = zero_rows >= r || lam[r - 1 - zero_rows] > FLOOR_REL * lam[0];
+            const bool ok = resolved && __ballot(close) == 0ull;
+            if (lane == 0) accepted = ok;
+        }
+        __syncthreads();
+        direct = accepted != 0;
+    }
+    bool open = false;
+    if (!direct) {
+        for (int e = tid; e < THIN_R * THIN_R; e += ST) V[(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+        __syncthreads();
+        // tournament over n = r rounded up to even (an entry past r is a row of zeros and never rotates)
+        const int n = (r + 1) & ~1, half = n >> 1, n1 = n - 1;
+        if (r & 1) {                                                 // the row and column of zeros
+            __syncthreads();
+            if (tid < n) A[0][r * LD + tid] = A[0][tid * LD + r] = 0.0;
+            __syncthreads();
+        }
+        // half^2 blocks of A on the first waves, as many pairs of entries of V (rows ka and ka + half) on the next ones: four waves,
+        // one per SIMD, up to 22 vectors
+        const int waves = (half * half + 63) >> 6, role = wave / waves;         // 0: A, 1: V, above: no part in it
+        const int first_e = (wave - role * waves) << 6, item = first_e + lane;
+        const int ka = item / half, kb = item - ka * half;
+        const bool valid = item < half * half;
+        const int lane_a = min(ka, half - 1) - first_e % half;                  // lane whose pair kb is pair ka
+        const int src_a = lane_a < 0 ? lane_a + half : lane_a;
+        const double floor = 1e-13 * trace;
+        // round t pairs n1 with t and t + k with t - k (mod n1); a thread holds pairs ka and kb and moves them on by one per round
+        auto first_of = [&](int k, int& p, int& q) {
+            p = k == 0 ? n1 : k;
+            q = k == 0 ? 0 : n1 - k;
+        };
+        auto move_on = [&](int k, int& p, int& q) {
+            if (k != 0) p = p + 1 == n1 ? 0 : p + 1;
+            q = q + 1 == n1 ? 0 : q + 1;
+        };
+        auto at = [](int i) { return (i << 5) + i; };                // i * LD
+        static_assert(LD == 33, "row offsets by shift and add");
+        const int row_v = at(min(ka, half - 1)), row_w = row_v + at(half);
+        int pa, qa, pb, qb;
+        first_of(min(ka, half - 1), pa, qa);
+        first_of(kb, pb, qb);
+        int cur = 0, sweeps = 0;
+        open = n > 1 && trace > 0.0;
+        while (open && sweeps < MAX_SWEEPS) {
+            bool turned = false;
+            for (int round = 0; round < n1; ++round) {
+                if (role < 2) {
+                    const double* old = A[cur];
+                    double* now = A[cur ^ 1];
+                    // everything that will be needed, on its way before the rotations
+                    const int ra = at(pa), sa_ = at(qa), rb = at(pb), sb_ = at(qb);
+                    const double dp = old[rb + pb], dq = old[sb_ + qb], g = old[rb + qb];
+                    const double* from = role == 0 ? old : V;
+                    const int up = role == 0 ? ra : row_v, down = role == 0 ? sa_ : row_w;
+                    const double b00 = from[up + pb], b01 = from[up + qb], b10 = from[down + pb], b11 = from[down + qb];
+                    double cb, sb;
+                    rotation(dp, dq, g, cb, sb);
+                    // the sweep is the last one if all cosines it met were small (what it leaves is then their square), rows at
+                    // the rounding of the largest aside
+                    turned = turned || (g * g > 1e-12 * dp * dq && fmin(dp, dq) > floor);
+                    const double c00 = cb * b00 - sb * b01, c01 = sb * b00 + cb * b01;
+                    const double c10 = cb * b10 - sb * b11, c11 = sb * b10 + cb * b11;
+                    if (role == 0) {
+                        const double ca = __shfl(cb, src_a), sa = __shfl(sb, src_a);
+                        if (valid) {
+                            const bool diagonal = ka == kb;
+                            now[ra + pb] = ca * c00 - sa * c10;
+                            now[ra + qb] = diagonal ? 0.0 : ca * c01 - sa * c11;
+                            now[sa_ + pb] = diagonal ? 0.0 : sa * c00 + ca * c10;
+                            now[sa_ + qb] = sa * c01 + ca * c11;
+                        }
+                    } else if (valid) {
+                        V[up + pb] = c00;
+                        V[up + qb] = c01;
+                        V[down + pb] = c10;
+                        V[down + qb] = c11;
+                    }
+                    move_on(ka, pa, qa);
+                    move_on(kb, pb, qb);
+                }
+                __syncthreads();
+                cur ^= 1;
+            }
+            if (turned) unfinished[sweeps & 1] = 1;
+            __syncthreads();
+            open = unfinished[sweeps & 1] != 0;
+            ++sweeps;
+            if (tid == 0) unfinished[sweeps & 1] = 0;                // (written again only after the barriers of the next sweep)
+        }
+        if (tid < r) lam[tid] = A[cur][tid * LD + tid];
+        if (tid < THIN_R) rank_of[tid] = 0;                          // (not all of them are written if lam is not a number)
+        __syncthreads();
+        if (tid < r) {
+            int before = 0;
+            const double mine = lam[tid];
+            for (int j = 0; j < r; ++j) before += lam[j] > mine || (lam[j] == mine && j < tid);
+            rank_of[before] = tid;
+        }
+        __syncthreads();
+        if (wave == 0) draw();
+    }
+    // header by wave 0, then the kept vectors, one wave each
+    if (wave == 0) {
         const int pos = __popcll(mask & ((1ull << lane) - 1));
         if (lane < r) {
-            if (m.sigma_out) m.sigma_out[lane] = sigma;
+            if (m.sigma_out) m.sigma_out[lane] = direct ? (float)ldexp((double)sigma, expo / 2) : sigma;
             if (m.p_out) m.p_out[lane] = p;
         }
         if (lane == 0) {
+            drawn = mask;
             *m.count = __popcll(mask);
             m.report[0] = 1;
             m.report[1] = 2;
@@ -332,18 +565,38 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             if (__popcll(mask) > m.capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
             if (open && !(trace != trace)) atomicMax(&flags[FLAG_NOCONV], 1);
         }
-        if (kept && pos < m.capacity) {
-            const float weight = sigma / p;
-            m.idx[pos] = lane;
-            if (m.w) m.w[pos] = weight;
-            const double fold = m.w ? 1.0 : (double)weight;      // folded message: the weight goes into U
-            float* out = m.tall ? m.V + (size_t)pos * r : m.U + (size_t)pos * r;
-            const double inv = reciprocal(sqrt(l));
-            for (int i = 0; i < r; ++i) {
-                const double x = V[i * LD + src];
-                global(out)[i] = (float)(m.tall ? x : x * fold);
-                global(m.u)[pos * r + i] = x * inv * (m.tall ? fold : 1.0);
+        if ((mask >> lane) & 1ull) {
+            const float scaled = direct ? (float)ldexp((double)sigma, expo / 2) : sigma;
+            tw[pos] = scaled / p;
+            if (pos < m.capacity) {
+                m.idx[pos] = lane;
+                if (m.w) m.w[pos] = scaled / p;
             }
+            below[pos] = lane;
+        }
+    }
+    __syncthreads();
+    const int count = min(__popcll(drawn), m.capacity);
+    if (direct && wave == 0)
+        twisted_vectors(td, te, r, count, (lane & 31) < count ? lam[below[lane & 31]] : 0.0, A[1], P1, Z, tlen);
+    __syncthreads();
+    for (int a = wave; a < count; a += ST / 64) {
+        const int i = lane & 31, src = rank_of[below[a]];
+        double x, inv = inverse_root(lam[src]);
+        if (direct) {
+            x = i < r ? Z[a * LD + i] * tlen[a] : 0.0;
+            for (int k = r - 3; k >= 0; --k) {                   // H z, the last step's reflection first
+                const double v = V[k * LD + i];
+                x = fma(-ttau[k] * wave_sum(lane < 32 ? v * x : 0.0), v, x);
+            }
+            inv = ldexp(inv, -(expo / 2));
+        } else {
+            x = i < r ? V[i * LD + src] : 0.0;
+        }
+        const double fold = m.w ? 1.0 : (double)tw[a];           // folded message: the weight goes into U
+        if (lane < r) {
+            global(m.tall ? m.V + (size_t)a * r : m.U + (size_t)a * r)[i] = (float)(m.tall ? x : x * fold);
+            global(m.u)[a * r + i] = x * inv * (m.tall ? fold : 1.0);
         }
     }
 }
