@@ -83,6 +83,11 @@ __device__ inline double wave_sum(double x)
     return fold32(x, x);
 }
 
+__device__ inline double lane_value(double x, int lane)
+{
+    return mk64((unsigned)__builtin_amdgcn_readlane((int)lo32(x), lane), (unsigned)__builtin_amdgcn_readlane((int)hi32(x), lane));
+}
+
 // Step k: x = column k of the current matrix, v the Householder vector that maps x[k + 1 ..] to a multiple of the first
 // unit vector, p = A v, w = tau p - (tau^2 / 2)(v^T p) v, A <- A - v w^T - w v^T.
 // beta, the entry that remains, and v_{k+1} = alpha - beta; tau = 2 / v^T v.  (A column of zeros: the floor under the

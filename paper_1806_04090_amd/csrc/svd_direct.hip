@@ -51,11 +51,6 @@ __device__ inline double wave_sums(const double (&v)[K], int lane)
 }
 __device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2; }
 
-__device__ inline double lane_value(double x, int lane)
-{
-    return mk64((unsigned)__builtin_amdgcn_readlane((int)lo32(x), lane), (unsigned)__builtin_amdgcn_readlane((int)hi32(x), lane));
-}
-
 // ------------------------------------------------------------------------------------------------
 // Gram matrix: partial sums of one 64 x 64 tile over one chunk of columns of A
 // ------------------------------------------------------------------------------------------------

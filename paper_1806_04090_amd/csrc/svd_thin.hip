@@ -161,19 +161,21 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    auto half_sum = [](double y) {                               // over the 32 lanes of a half, the same bits in each
+        y = sum8(y);
+        y += dpp<DPP_MIRROR>(y);
+        return fold16(y, y);
+    };
+    double x = C[i * LD];                                        // column k of the current matrix, in both halves
     for (int k = 0; k + 2 < n; ++k) {
-        const double x = C[i * LD + k], alpha = C[(k + 1) * LD + k], diagonal = C[k * LD + k];
-        const double sig2 = wave_sum(h == 0 && i > k + 1 ? x * x : 0.0);
-        double beta, v0;
-        householder(alpha, sig2, beta, v0);
-        const double t = householder_tau(sig2, v0);
-        const double v = i > k + 1 ? x : i == k + 1 ? v0 : 0.0;
-        if (h == 0) H[k * LD + i] = v;
+        const double alpha = lane_value(x, k + 1), diagonal = lane_value(x, k);
+        // v is the column but for its entry k + 1, alpha - beta for alpha: the product with the column is under way before
+        // beta is known, and beta times column k + 1 comes off it afterwards
+        if (h == 0) w_sh[i] = x;
         in_order();
         // columns k + 1 + h, k + 3 + h, ..
         constexpr int U = THIN_R / 2;
         double c[U], vj[U];
-        double part = 0.0;
 #pragma unroll
         for (int u = 0; u < U; u += 4) {
             if (k + 1 + 2 * u >= n) break;
@@ -181,17 +183,32 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
             for (int y = u; y < u + 4; ++y) {
                 const int j = min(k + 1 + h + 2 * y, THIN_R - 1);
                 c[y] = C[i * LD + j];
-                vj[y] = k + 1 + h + 2 * y < n ? H[k * LD + j] : 0.0;
+                vj[y] = k + 1 + h + 2 * y < n ? w_sh[j] : 0.0;
             }
         }
+        const double sig2 = half_sum(i > k + 1 ? x * x : 0.0);
+        double even = 0.0, odd = 0.0;
 #pragma unroll
         for (int u = 0; u < U; u += 4) {
             if (k + 1 + 2 * u >= n) break;
 #pragma unroll
-            for (int y = u; y < u + 4; ++y) part = fma(c[y], vj[y], part);
+            for (int y = u; y < u + 4; y += 2) {
+                even = fma(c[y], vj[y], even);
+                odd = fma(c[y + 1], vj[y + 1], odd);
+            }
         }
+        double beta, v0;
+        householder(alpha, sig2, beta, v0);
+        const double t = householder_tau(sig2, v0);
+        const double v = i > k + 1 ? x : i == k + 1 ? v0 : 0.0;
+        if (h == 0) {
+            H[k * LD + i] = v;
+            even = fma(-beta, c[0], even);
+            vj[0] = v0;
+        }
+        const double part = even + odd;
         const double p = i > k ? t * fold32(part, part) : 0.0;
-        const double pv = wave_sum(h == 0 ? p * v : 0.0);
+        const double pv = half_sum(p * v);
         const double w = fma(-0.5 * t * pv, v, p);
         if (h == 0) w_sh[i] = w;
         in_order();
@@ -204,9 +221,12 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
                 const int j = k + 1 + h + 2 * (u + y);
-                if (j < n && i > k) C[i * LD + j] = fma(-v, wj[y], fma(-w, vj[u + y], c[u + y]));
+                const double next = fma(-v, wj[y], fma(-w, vj[u + y], c[u + y]));
+                if (j < n && i > k) C[i * LD + j] = next;
+                if (u + y == 0) x = next;                        // lower half: column k + 1
             }
         }
+        x = fold32(h == 0 ? x : 0.0, h == 0 ? x : 0.0);
         if (lane == 0) {
             d[k] = diagonal;
             e[k] = beta;
@@ -276,54 +296,82 @@ __device__ inline void eigenvalues(const doublex2* t, int n_pad, int n, int* bel
     }
 }
 
-// Eigenvectors of T for the eigenvalues next to lam, one per lane and half-wave, into the rows of Z (not normalised; 1 / length
-// in length_inv): twisted factorisations, lanes 0 .. 31 with the pivots from the top and lanes 32 .. 63 with those from the bottom,
-// joined where the two meet with the smallest pivot.  The Rayleigh quotient corrects lam; the third round starts within
-// 2^-24 of the gap to the next kept eigenvalue.
-__device__ inline void twisted_vectors(const double* d, const double* e, int n, int count, double lam, double* P0, double* P1,
-                                       double* Z, double* length_inv)
+template <int CTRL>
+__device__ inline double dpp_or_one(double x)
 {
-    const int lane = threadIdx.x & 63, a = lane & 31;
-    const bool bottom = lane >= 32, real = a < count;
-    double* P = (bottom ? P1 : P0) + a * LD;
-    double* z = Z + a * LD;
-    auto in_order = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    auto pivot = [](double x) { return fabs(x) < 1e-150 ? copysign(1e-150, x) : x; };
-    double len2 = 1.0;
+    return mk64((unsigned)__builtin_amdgcn_update_dpp(0, (int)lo32(x), CTRL, 0xF, 0xF, false),
+                (unsigned)__builtin_amdgcn_update_dpp(0x3FF00000, (int)hi32(x), CTRL, 0xF, 0xF, false));
+}
+
+// Unit eigenvector of T for the eigenvalue next to lam, by a wave: entry lane mod 32 in either half.  A twisted factorisation: the
+// lower half of the lanes works out the pivots from the top, the upper half those from the bottom, as quotients of the
+// characteristic polynomials (every lane runs through the recurrence and keeps its own step); the two are joined where they
+// meet with the smallest pivot, and the entries are products of quotients from there, by scans.  The Rayleigh quotient
+// corrects lam; the third round starts within 2^-24 of the gap to the next kept eigenvalue.
+// t: as for sturm_below (n entries after the padding), e: off-diagonal.
+__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam)
+{
+    const int lane = threadIdx.x & 63, i = lane & 31;
+    const bool bottom = lane >= 32;
+    const double di = t[min(i, n - 1)].y;
+    const double ei = i < n - 1 ? e[i] : 0.0, eb = i > 0 && i < n ? e[i - 1] : 0.0;
+    double z = 0.0, len2 = 1.0;
     for (int round = 0; round < 3; ++round) {
-        double x = 0.0;
-        for (int k = 0; k < n; ++k) {
-            const int i = bottom ? n - 1 - k : k;
-            const double off = k == 0 ? 0.0 : e[bottom ? i : i - 1];
-            x = pivot((d[i] - lam) - (k == 0 ? 0.0 : off * off * reciprocal(x)));
-            if (real) P[i] = x;
-        }
-        in_order();
-        int at = 0;
-        double least = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const double g = real ? P0[a * LD + i] + P1[a * LD + i] - (d[i] - lam) : 1.0;
-            if (i == 0 || fabs(g) < fabs(least)) { least = g; at = i; }
-        }
-        double y = 1.0, sum = 0.0;
-        if (real && !bottom) z[at] = 1.0;
-        for (int k = 1; k < n; ++k) {
-            const int i = bottom ? at + k : at - k;
-            if (real && i >= 0 && i < n) {
-                y = -e[bottom ? i - 1 : i] * reciprocal(P[i]) * y;
-                z[i] = y;
-                sum = fma(y, y, sum);
+        double p0 = 0.0, p1 = 1.0, num = 1.0, den = 1.0;
+        for (int k0 = 0; k0 < n; k0 += 8) {
+            double d[8], off[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = min(k0 + u, n - 1);
+                d[u] = t[bottom ? n - 1 - k : k].y;
+                off[u] = k0 + u == 0 ? 0.0 : t[bottom ? n - k : k].x;
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const double p2 = fma(d[u] - lam, p1, -(off[u] * p0));
+                if (k0 + u == (bottom ? n - 1 - i : i)) { num = p2; den = p1; }
+                p0 = p1;
+                p1 = p2;
+            }
+            const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+            p0 = __builtin_amdgcn_ldexp(p0, -ex);
+            p1 = __builtin_amdgcn_ldexp(p1, -ex);
         }
-        len2 = 1.0 + fold32(sum, sum);
-        lam += real ? least * reciprocal(len2) : 0.0;
-        in_order();
+        auto away_from_zero = [](double x) { return fabs(x) < 1e-290 ? copysign(1e-290, x) : x; };
+        den = away_from_zero(den);
+        num = away_from_zero(num);
+        const double pivot = num * reciprocal(den);
+        const double g = fold32(pivot, pivot) - (di - lam);
+        // the smallest |g| of the entries there are, with its place in the lowest bits
+        u64 least = i < n ? (((u64)__double_as_longlong(fabs(g))) & ~31ull) | (unsigned)i : ~0ull;
+        auto smaller = [&](u64 o) { least = o < least ? o : least; };
+        smaller((u64)__double_as_longlong(dpp<DPP_XOR1>(__longlong_as_double((long long)least))));
+        smaller((u64)__double_as_longlong(dpp<DPP_XOR2>(__longlong_as_double((long long)least))));
+        smaller((u64)__double_as_longlong(dpp<DPP_HALF_MIRROR>(__longlong_as_double((long long)least))));
+        smaller((u64)__double_as_longlong(dpp<DPP_MIRROR>(__longlong_as_double((long long)least))));
+        const double least_d = __longlong_as_double((long long)least);
+        smaller((u64)__double_as_longlong(lane_value(least_d, 0)));
+        smaller((u64)__double_as_longlong(lane_value(least_d, 16)));
+        const int at = __builtin_amdgcn_readfirstlane((int)(least & 31ull));
+        const double g_at = lane_value(g, at);
+        // z_i = -(e_i / pivot_i) z_{i+1} above, -(e_{i-1} / pivot_i) z_{i-1} below
+        const bool mine = bottom ? i > at && i < n : i < at;
+        double f = mine ? -(bottom ? eb : ei) * (den * reciprocal(num)) : 1.0;
+        auto step = [&](double shl, double shr) { f *= bottom ? shr : shl; };
+        step(dpp_or_one<0x101>(f), dpp_or_one<0x111>(f));
+        step(dpp_or_one<0x102>(f), dpp_or_one<0x112>(f));
+        step(dpp_or_one<0x104>(f), dpp_or_one<0x114>(f));
+        step(dpp_or_one<0x108>(f), dpp_or_one<0x118>(f));
+        const double row1 = lane_value(f, 16), row2 = lane_value(f, 47);
+        f *= lane < 16 ? row1 : lane >= 48 ? row2 : 1.0;
+        const double own = mine ? f : !bottom && i == at ? 1.0 : 0.0;
+        z = fold32(own, own);
+        double sum = sum8(z * z);
+        sum += dpp<DPP_MIRROR>(sum);
+        len2 = fold16(sum, sum);
+        lam += g_at * reciprocal(len2);
     }
-    if (real && !bottom) length_inv[a] = inverse_root(len2);
+    return z * inverse_root(len2);
 }
 
 // Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
@@ -334,10 +382,9 @@ __device__ inline void twisted_vectors(const double* d, const double* e, int n, 
 // rotations of the round for itself and hands them around inside.
 __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
 {
-    __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];
-    __shared__ double P1[THIN_R * LD], Z[THIN_R * LD];           // direct: V holds the reflectors, A[1] the reduced matrix, then pivots
+    __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
     __shared__ doublex2 T[THIN_R];
-    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R], tlen[THIN_R];
+    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R];
     __shared__ int below[ST];
     __shared__ int unfinished[2];
     __shared__ double lam[THIN_R];
@@ -577,14 +624,11 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     }
     __syncthreads();
     const int count = min(__popcll(drawn), m.capacity);
-    if (direct && wave == 0)
-        twisted_vectors(td, te, r, count, (lane & 31) < count ? lam[below[lane & 31]] : 0.0, A[1], P1, Z, tlen);
-    __syncthreads();
     for (int a = wave; a < count; a += ST / 64) {
         const int i = lane & 31, src = rank_of[below[a]];
         double x, inv = inverse_root(lam[src]);
         if (direct) {
-            x = i < r ? Z[a * LD + i] * tlen[a] : 0.0;
+            x = twisted_vector(T + (((r + 7) & ~7) - r), te, r, lam[src]);
             for (int k = r - 3; k >= 0; --k) {                   // H z, the last step's reflection first
                 const double v = V[k * LD + i];
                 x = fma(-ttau[k] * wave_sum(lane < 32 ? v * x : 0.0), v, x);
