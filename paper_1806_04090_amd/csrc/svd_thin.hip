@@ -127,6 +127,7 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
 // ------------------------------------------------------------------------------------------------
 constexpr int ST = 512;                        // threads of a workgroup of thin_solve
 constexpr int LD = THIN_R + 1;
+constexpr int OVERRUN = 8;                     // a row is read in groups of eight columns
 constexpr int MAX_SWEEPS = 15;
 
 // 1 / sqrt(x) of a positive normal number: the hardware's estimate (23 bits) and one step of third order, two dependent
@@ -151,7 +152,8 @@ __device__ inline void rotation(double a, double b, double g, double& c, double&
     s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
 }
 
-// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n to THIN_R) by one wave: diagonal d, off-diagonal
+// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n on, OVERRUN entries past the last row too, and in
+// w_sh) by one wave: diagonal d, off-diagonal
 // e; the vectors of the steps go to the rows of H, C is used up.  Lane l holds row l mod 32 and every other column.
 __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d, double* e, double* tau, int n)
 {
@@ -176,14 +178,15 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
         // columns k + 1 + h, k + 3 + h, ..
         constexpr int U = THIN_R / 2;
         double c[U], vj[U];
+        double* row = C + i * LD + k + 1 + h;
+        const double* column = w_sh + k + 1 + h;
 #pragma unroll
         for (int u = 0; u < U; u += 4) {
             if (k + 1 + 2 * u >= n) break;
 #pragma unroll
             for (int y = u; y < u + 4; ++y) {
-                const int j = min(k + 1 + h + 2 * y, THIN_R - 1);
-                c[y] = C[i * LD + j];
-                vj[y] = k + 1 + h + 2 * y < n ? w_sh[j] : 0.0;
+                c[y] = row[2 * y];
+                vj[y] = column[2 * y];
             }
         }
         const double sig2 = half_sum(i > k + 1 ? x * x : 0.0);
@@ -217,12 +220,11 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
             if (k + 1 + 2 * u >= n) break;
             double wj[4];
 #pragma unroll
-            for (int y = 0; y < 4; ++y) wj[y] = w_sh[min(k + 1 + h + 2 * (u + y), THIN_R - 1)];
+            for (int y = 0; y < 4; ++y) wj[y] = column[2 * (u + y)];
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
-                const int j = k + 1 + h + 2 * (u + y);
                 const double next = fma(-v, wj[y], fma(-w, vj[u + y], c[u + y]));
-                if (j < n && i > k) C[i * LD + j] = next;
+                if (i > k && k + 1 + h + 2 * (u + y) < n) row[2 * (u + y)] = next;
                 if (u + y == 0) x = next;                        // lower half: column k + 1
             }
         }
@@ -382,9 +384,9 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
 // rotations of the round for itself and hands them around inside.
 __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
 {
-    __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
+    __shared__ double A[2][THIN_R * LD + OVERRUN], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
     __shared__ doublex2 T[THIN_R];
-    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R];
+    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R + OVERRUN];
     __shared__ int below[ST];
     __shared__ int unfinished[2];
     __shared__ double lam[THIN_R];
@@ -472,10 +474,11 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         // scaled by a power of four to a trace in [1/4, 1)
         (void)frexp(trace, &expo);
         expo += expo & 1;
-        for (int e = tid; e < THIN_R * THIN_R; e += ST) {
-            const int i = e >> 5, j = e & 31;
-            A[1][i * LD + j] = i < r && j < r ? ldexp(A[0][i * LD + j], -expo) : 0.0;
+        for (int e = tid; e < THIN_R * LD + OVERRUN; e += ST) {
+            const int i = e / LD, j = e - i * LD;
+            A[1][e] = i < r && j < r ? ldexp(A[0][e], -expo) : 0.0;
         }
+        if (tid < OVERRUN) tw[THIN_R + tid] = 0.0;
         __syncthreads();
         if (wave == 0) tridiagonal(A[1], V, tw, td, te, ttau, r);
         __syncthreads();
