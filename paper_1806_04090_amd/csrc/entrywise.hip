@@ -1205,11 +1205,11 @@ __device__ inline double lq_norm(double acc, int mode, double q)
     return mode == LQ_TWO ? sqrt(acc) : acc;
 }
 
-// The norm: a part per workgroup, finished by the last one (fixed thread -> element map and fixed reduction tree, so the norm
-// is the same bits in every run).
+// The norm: a part per workgroup, added up by every workgroup of the pass behind it (fixed thread -> element map and fixed
+// reduction tree, so the norm is the same bits in every run).
 template <bool POW>
-__global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g, long long n, int mode, double q, double* partial,
-                                                    EwState* st, float* norm_out)
+__global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g, long long n, int mode, double q,
+                                                    double* __restrict__ partial)
 {
     __shared__ double wpart[4];
     const int tid = threadIdx.x;
@@ -1230,22 +1230,7 @@ __global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g,
     }
     for (long long i = n4 * 4 + (long long)blockIdx.x * 256 + tid; i < n; i += stride) visit(g[i]);
     const double part = lq_block_reduce<256>(acc, mode, wpart);
-    if (tid == 0) {
-        __hip_atomic_store(&partial[blockIdx.x], part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // the last workgroup to finish: |g|_q from the partial results, 1 / |g|_q as the sampler's ratio, the message's norm
-    if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
-    double t = 0.0;
-    for (int k = tid; k < (int)gridDim.x; k += 256) {
-        const double v = __hip_atomic_load(&partial[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        t = mode == LQ_MAX ? fmax(t, v) : t + v;
-    }
-    t = lq_block_reduce<256>(t, mode, wpart);
-    if (tid == 0) {
-        const double norm = lq_norm<POW>(t, mode, q);
-        st->ratio = norm > 0.0 ? 1.0 / norm : 0.0;               // p_i = min(1, |g_i| / |g|_q)
-        *norm_out = (float)norm;
-    }
+    if (tid == 0) partial[blockIdx.x] = part;
 }
 
 // The whole l_q encoder for n <= LOCAL_MAX.
@@ -1273,13 +1258,27 @@ __global__ __launch_bounds__(LOCAL_T) void lq_encode_local(const float* __restri
 }
 
 // The l_q encoder's pass over the gradient behind the norm: draws against the exact p, one group of segments per workgroup.
-template <int STEPS>
-__global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long long n, const EwState* st,
-                                               unsigned long long stream_id, unsigned long long seed, Segments sg)
+template <int STEPS, bool POW>
+__global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long long n, EwState* st, const double* __restrict__ partial,
+                                               int parts, int mode, double q, float* norm_out, unsigned long long stream_id,
+                                               unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const double ratio = st->ratio;
+    __shared__ double wpart[4], ratio_sh;
+    double acc = 0.0;
+    for (int k = tid; k < parts; k += 256) acc = mode == LQ_MAX ? fmax(acc, partial[k]) : acc + partial[k];
+    acc = lq_block_reduce<256>(acc, mode, wpart);
+    if (tid == 0) {
+        const double norm = lq_norm<POW>(acc, mode, q);
+        ratio_sh = norm > 0.0 ? 1.0 / norm : 0.0;                // p_i = min(1, |g_i| / |g|_q)
+        if (blockIdx.x == 0) {
+            st->ratio = ratio_sh;
+            *norm_out = (float)norm;
+        }
+    }
+    __syncthreads();
+    const double ratio = ratio_sh;
     const int mine = sg.per_group / 4;
     const long long seg0 = (long long)blockIdx.x * sg.per_group + wave * mine;
     unsigned int total = 0u;                                     // wave-uniform
@@ -1431,18 +1430,19 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
         ATOMO_HIP(ctx, hipGetLastError());
         return ATOMO_OK;
     }
+    const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
     {
         ProfScope ps(ctx, ATOMO_K_EW_HIST, stream);              // the norm pass takes the place of the histograms
-        const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
         const auto pass = mode == LQ_POW ? lq_norm_pass<true> : lq_norm_pass<false>;
-        pass<<<wgs, 256, 0, stream>>>(g, n, mode, q, l.lq_partial, l.st, msg->norm);
+        pass<<<wgs, 256, 0, stream>>>(g, n, mode, q, l.lq_partial);
     }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
         const unsigned groups = (unsigned)l.sg.n_groups;
         const bool long_seg = l.steps == 16;
-        if (long_seg) lq_draw<16><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg);
-        else lq_draw<4><<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg);
+        const auto draw = long_seg ? (mode == LQ_POW ? lq_draw<16, true> : lq_draw<16, false>)
+                                   : (mode == LQ_POW ? lq_draw<4, true> : lq_draw<4, false>);
+        draw<<<groups, 256, 0, stream>>>(g, n, l.st, l.lq_partial, wgs, mode, q, msg->norm, stream_id, seed, l.sg);
         const auto write = long_seg ? ew_write<16, true> : ew_write<4, true>;
         write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg, (long long)msg->capacity, msg->idx, nullptr,
                                           (long long*)msg->count, ctx->d_flags);
