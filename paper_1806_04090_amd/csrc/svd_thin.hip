@@ -29,7 +29,7 @@ constexpr int PART = 3 * 256;                  // doubles of a partial Gram matr
 
 // Bound: the matrix cores, with a 16 x 16 x 4 product per four positions up to 16 vectors, three from there on; vectors 16 .. 19
 // (the 18 columns of a 3 x 3 convolution) take two of 4 x 4 x 4 in four blocks, an eighth of the time of the two they replace.
-// 11.16 M elements of 18 columns: THIN_GRAM_MEASURED
+// 11.16 M elements of 18 columns: 20 us (27 with three large products; 14 without any).
 __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats, const Work* work)
 {
     __shared__ double red[GRAM_WAVES / 2][PART];
@@ -310,14 +310,14 @@ __device__ inline double dpp_or_one(double x)
 // characteristic polynomials (every lane runs through the recurrence and keeps its own step); the two are joined where they
 // meet with the smallest pivot, and the entries are products of quotients from there, by scans.  The Rayleigh quotient
 // corrects lam; the third round starts within 2^-24 of the gap to the next kept eigenvalue.
-// t: as for sturm_below (n entries after the padding), e: off-diagonal.
-__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam)
+// t: as for sturm_below (n entries after the padding), e: off-diagonal.  residual: |T z - lam z| in the last round.
+__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam, double& residual)
 {
     const int lane = threadIdx.x & 63, i = lane & 31;
     const bool bottom = lane >= 32;
     const double di = t[min(i, n - 1)].y;
     const double ei = i < n - 1 ? e[i] : 0.0, eb = i > 0 && i < n ? e[i - 1] : 0.0;
-    double z = 0.0, len2 = 1.0;
+    double z = 0.0, len2 = 1.0, gamma = 0.0;
     for (int round = 0; round < 3; ++round) {
         double p0 = 0.0, p1 = 1.0, num = 1.0, den = 1.0;
         for (int k0 = 0; k0 < n; k0 += 8) {
@@ -372,13 +372,17 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
         sum += dpp<DPP_MIRROR>(sum);
         len2 = fold16(sum, sum);
         lam += g_at * reciprocal(len2);
+        gamma = fabs(g_at);
     }
-    return z * inverse_root(len2);
+    const double inv = inverse_root(len2);
+    residual = gamma * inv;
+    return z * inv;
 }
 
 // Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
 // the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
-// zeros aside; kept neighbours apart); otherwise the two-sided Jacobi iteration.  18 columns: THIN_SOLVE_MEASURED
+// zeros aside; kept neighbours apart; vectors with a small residual); otherwise the two-sided Jacobi iteration.  18
+// columns: 42 us, 31 of them without the sums of the largest matrices; Jacobi in eight sweeps 73.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.
@@ -499,7 +503,16 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             const bool close = lane > 0 && lane < r && ((mask >> lane) & (mask >> (lane - 1)) & 1ull) && up - l <= l * 2.384185791015625e-07;
             const bool resolved = zero_rows >= r || lam[r - 1 - zero_rows] > FLOOR_REL * lam[0];
             const bool ok = resolved && __ballot(close) == 0ull;
-            if (lane == 0) accepted = ok;
+            if (lane == 0) { accepted = ok; drawn = mask; }
+            if ((mask >> lane) & 1ull) below[__popcll(mask & ((1ull << lane) - 1))] = lane;
+        }
+        __syncthreads();
+        const int count = accepted ? min(__popcll(drawn), m.capacity) : 0;
+        for (int a = wave; a < count; a += ST / 64) {
+            double residual;
+            const double z = twisted_vector(T + pad, te, r, lam[below[a]], residual);
+            if (lane < THIN_R) A[1][a * LD + lane] = z;
+            if (lane == 0 && !(residual <= 1e-12 * lam[0])) accepted = 0;
         }
         __syncthreads();
         direct = accepted != 0;
@@ -631,7 +644,7 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         const int i = lane & 31, src = rank_of[below[a]];
         double x, inv = inverse_root(lam[src]);
         if (direct) {
-            x = twisted_vector(T + (((r + 7) & ~7) - r), te, r, lam[src]);
+            x = i < r ? A[1][a * LD + i] : 0.0;
             for (int k = r - 3; k >= 0; --k) {                   // H z, the last step's reflection first
                 const double v = V[k * LD + i];
                 x = fma(-ttau[k] * wave_sum(lane < 32 ? v * x : 0.0), v, x);
@@ -664,7 +677,8 @@ __device__ inline void long_dots(const float* mine /* LDS, r entries */, const _
     }
 }
 
-// Bound: one read of the data.  The entries of a block of positions are fetched before anything is known about the kept atoms,
+// Bound: one read of the data; 11.16 M elements of 18 columns in 16 us (34 with four dependent rounds of loads per workgroup and the
+// atoms in LDS).  The entries of a block of positions are fetched before anything is known about the kept atoms,
 // go through LDS (those of a position of a tall matrix lie side by side, and a thread owns a position) and are multiplied with up
 // to eight atoms per pass.
 __global__ __launch_bounds__(LONG_POS) void thin_long(const ThinMat* mats, const Work* work)

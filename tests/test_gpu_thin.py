@@ -1,0 +1,60 @@
+"""GPU parity of the encoder of thin matrices (at most 32 vectors on the shorter side): the sizes at the edges of its tiles and runs of
+positions, and the matrices that its direct solution hands to the Jacobi iteration."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1806_04090_amd import binding, inputs
+from gpu_common import ctx, dev, check_svd_message_against_matrix
+from test_gpu_svd import encode, full_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 8, 15, 16, 17, 18, 20, 21, 24, 31, 32])
+@pytest.mark.parametrize("positions", [33, 255, 1025, 9001])
+@pytest.mark.parametrize("tall", [False, True])
+def test_edges_of_tiles_and_runs(r, positions, tall):
+    rng = np.random.default_rng(r * 31 + positions)
+    m, n = (positions, r) if tall else (r, positions)
+    G = inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5, 0.25, 0.1][:r], 0.02)
+    msgs, per, status, _ = encode([G], 3.0, 5, stream_base=r, capacity=r)
+    assert status == 0
+    full_parity(G, 3.0, 5, r, msgs[0], *per[0])
+
+
+@pytest.mark.parametrize("r", [2, 5, 18, 22, 23, 32])
+@pytest.mark.parametrize("kind", ["rank", "equal", "zeros", "nothing", "close"])
+def test_spectra_that_the_direct_solution_may_not_take(r, kind):
+    rng = np.random.default_rng(r)
+    M = 700
+    G = rng.standard_normal((M, r))
+    if kind == "rank":                                           # half of the spectrum at rounding
+        G = rng.standard_normal((M, max(1, r // 2))) @ rng.standard_normal((max(1, r // 2), r))
+    elif kind == "equal":                                        # one singular value r times
+        G = np.linalg.qr(G)[0]
+    elif kind == "zeros":                                        # columns without a gradient
+        G[:, ::2] = 0
+    elif kind == "nothing":
+        G[:] = 0
+    elif kind == "close":                                        # neighbours a float's rounding apart
+        u, _, vt = np.linalg.svd(G, full_matrices=False)
+        G = u * (1.0 - 2e-8 * np.arange(r)) @ vt
+    G = G.astype(np.float32)
+    msgs, per, status, _ = encode([G], r / 2 + 1.0, 2, capacity=r)
+    assert status == 0
+    check_svd_message_against_matrix(G.astype(np.float64), msgs[0].to_host(), *per[0])
+
+
+def test_strided_and_unaligned():
+    rng = np.random.default_rng(7)
+    host = inputs.low_rank_plus_noise(rng, 2500, 18, [1.0, 0.4, 0.2], 0.01)
+    wide = torch.zeros(2500, 21, device="cuda")
+    wide[:, 1:19] = dev(host)
+    flat = torch.zeros(2500 * 18 + 1, device="cuda")
+    flat[1:] = dev(host).reshape(-1)
+    for G in (wide[:, 1:19], flat[1:].view(2500, 18)):
+        sigma, p = torch.zeros(18, device="cuda"), torch.zeros(18, device="cuda")
+        msgs = binding.atomo_encode_svd(ctx(), [G], 3.0, 9, 40, sigma_out=sigma, p_out=p)
+        assert ctx().status()[0] == 0
+        full_parity(host, 3.0, 9, 40, msgs[0], sigma.cpu().numpy(), p.cpu().numpy())
