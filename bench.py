@@ -8,9 +8,10 @@ of the 21 messages to dense gradients.  Inputs are resident in HBM before the ti
 
 Prints ONE JSON line.  `value` = gradient elements encoded+decoded per second.
 `roofline` prices the encode as a whole: contraction flops the algorithm executes on real data (no
-padding, measured sweep counts) over the GPU time of one encode, taken inside the timed region from two HIP
-events per step (one before the encode, one after it, on the stream the library launches on), against the
-fp32 matrix-core peak.  `roofline.by_kernel_event_pass` breaks the step down by kernel class from a second pass
+padding; the route and the sweep counts that each layer reports) over the GPU time of one encode, taken inside the
+timed region from two HIP events per step (one before the encode, one after it, on the stream the library launches
+on), against the matrix-core peak of the precision they run in (fp64 for layers that are solved directly, fp32 for
+those that iterate).  `roofline.by_kernel_event_pass` breaks the step down by kernel class from a second pass
 over the same K steps with events around every launch (slower than the timed pass: the events cost a few
 microseconds per launch and the two streams of the encoder overlap; for detail, not for `achieved`).
 `cpu_baseline` is the fp64 oracle, as it stands, timed on this machine's host cores.
@@ -35,6 +36,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA_TFLOPS = 157.3        # MI355X published dense fp32 matrix peak
 PEAK_FP32_VALU_TFLOPS = 157.3        # published vector fp32 peak (packed); 78.6 for the unpacked code built here
+PEAK_FP64_TFLOPS = 78.6              # published fp64 peak, vector and matrix
 PEAK_HBM_GBS = 8000.0
 
 
@@ -54,13 +56,22 @@ def block_rows(r):
     return rows + [0] * (nb & 1)
 
 
+def solved_directly(m, n, sweeps, refreshes):
+    """True for a layer that reports the route of the direct encode: one sweep, two passes over the data."""
+    return 32 < min(m, n) <= 640 and (sweeps, refreshes) == (1, 2)
+
+
 ROTATION_UNITS = 1.0 + 2.0 * 17.0 / 32.0   # vectors of 64 that one rotation of a Jacobi step updates, see executed_work
 
 
 def executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_update_tiles, n_elem, kept_atoms):
     """Arithmetic and bytes the algorithm executes on real data (no padding) per step, by kernel class.
 
-    Thin layers (r <= 32) are streaming passes over the data (svd_thin), priced by their bytes.
+    Thin layers (r <= 32) are two streaming passes over the data (svd_thin), priced by their bytes.
+    Layers that are solved directly (svd_direct), all in fp64: the upper-triangular tiles of A A^T on the matrix cores,
+    M r (r + 64); the reduction to tridiagonal form, which keeps both triangles, 2 r^3; and per kept atom its image
+    under the reflectors and its long vector, 2 r^2 + 2 M r.  The search for the eigenvalues is not counted.
+    The classes below are those of the layers that iterate.
     A sweep visits every pair (i, j) of the layer's 32-row blocks once, n_i + n_j real rows per pair.
     Data-space layers (32 < r <= 480), one launch of svd_rowgram per tick (svd_update): the row update, 2 x 64 x 64 x 64
     per 64 x 64 tile of [A | T] that was rotated, counted on the device (pairs found converged are left alone), and
@@ -82,12 +93,15 @@ def executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_upda
     svd_eig class is priced as a whole (vector-ALU rotations + the MFMA work its launches carry) against the
     157.3 TFLOP/s that is both the fp32 vector and the fp32 matrix peak.
     """
-    gram = gram_first = refresh = twosided = catchup = thin_bytes = 0.0
-    for (m, n), sw, rf in zip(shapes, sweeps, refreshes):
+    gram = gram_first = refresh = twosided = catchup = thin_bytes = direct_gram = direct = 0.0
+    for (m, n), sw, rf, kept in zip(shapes, sweeps, refreshes, kept_atoms):
         r, M, gs = layer_geometry(m, n)
         if r <= 32:
-            # thin layers: largest-entry pass, first Gram pass, one read + write per rotation, gather of the kept atoms
-            thin_bytes += 4.0 * M * r * (3 + 2 * sw)
+            thin_bytes += 2 * 4.0 * M * r                      # Gram matrix, long vectors of the kept atoms
+            continue
+        if solved_directly(m, n, sw, rf):
+            direct_gram += M * r * (r + 64.0)
+            direct += 2.0 * r ** 3 + kept * 2.0 * r * (r + M)
             continue
         rows = block_rows(r)
         nb2 = len(rows)
@@ -114,8 +128,19 @@ def executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_upda
         "svd_prepare": ("hbm", 12.0 * n_elem, PEAK_HBM_GBS, "GB/s"),
         "svd_finalize": ("hbm", 4.0 * n_elem, PEAK_HBM_GBS, "GB/s"),
         "svd_thin": ("hbm", thin_bytes, PEAK_HBM_GBS, "GB/s"),
+        "svd_direct": ("alu", direct_gram + direct, PEAK_FP64_TFLOPS, "TFLOP/s"),
+        "svd_direct_gram": ("mfma", direct_gram, PEAK_FP64_TFLOPS, "TFLOP/s"),     # the part of it on the matrix cores
         "decode_svd": ("hbm", decode_bytes, PEAK_HBM_GBS, "GB/s"),
     }
+
+
+def matrix_core_work(work, rotations):
+    """(contraction flops of one encode, the peak they are held against in TFLOP/s: that of the precision they run in,
+    or of the mixture)."""
+    fp32 = sum(work[k][1] for k in ("svd_gram", "svd_update", "svd_refresh")) + work["svd_eig"][1] - rotations
+    fp64 = work["svd_direct_gram"][1]
+    at_peak = fp32 / PEAK_FP32_MFMA_TFLOPS + fp64 / PEAK_FP64_TFLOPS
+    return fp32 + fp64, (fp32 + fp64) / at_peak if at_peak > 0 else PEAK_FP32_MFMA_TFLOPS
 
 
 def profiled_traffic_bytes(kernel):
@@ -141,11 +166,13 @@ def profiled_traffic_bytes(kernel):
     return None
 
 
-def dense_equivalent_flops(shapes, sweeps):
-    """The contraction count of textbook blocked one-sided Jacobi on the data, sweeps x (8 M r^2 + 4 r^3) per layer:
-    what the same number of sweeps would cost without the Gram-space reformulation.  These flops are not executed
-    by the library; the figure is context only and enters no roofline fraction."""
-    return sum(sw * (8.0 * max(m, n) * min(m, n) ** 2 + 4.0 * min(m, n) ** 3) for (m, n), sw in zip(shapes, sweeps))
+def dense_equivalent_flops(shapes, sweeps, refreshes):
+    """The contraction count of textbook blocked one-sided Jacobi on the data, sweeps x (8 M r^2 + 4 r^3) per layer
+    that iterates (none for those solved directly): what the same number of sweeps would cost without the Gram-space
+    reformulation.  These flops are not executed by the library; the figure is context only and enters no roofline
+    fraction."""
+    return sum(sw * (8.0 * max(m, n) * min(m, n) ** 2 + 4.0 * min(m, n) ** 3)
+               for (m, n), sw, rf in zip(shapes, sweeps, refreshes) if not solved_directly(m, n, sw, rf))
 
 
 def main():
@@ -264,7 +291,7 @@ def main():
     work = executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_update_tiles, n_elem, kept_atoms)
     rotations = jacobi_steps * 32 * ROTATION_UNITS * 64 * 6
     # contraction flops executed on the matrix cores in one encode (the vector-ALU rotations are reported beside them)
-    contraction = sum(work[k][1] for k in ("svd_gram", "svd_update", "svd_refresh")) + work["svd_eig"][1] - rotations
+    contraction, peak = matrix_core_work(work, rotations)
     by_kernel = {}
     for k, v in sorted(per_step_ms.items()):
         kb, ka, kp, ku = work[k]
@@ -272,17 +299,18 @@ def main():
         by_kernel[k] = {"ms": round(v, 4), "scopes": launches[k], "bound": kb, "achieved": round(rate, 3), "unit": ku,
                         "frac": round(rate / kp, 5)}
     achieved = contraction / (encode_ms * 1e-3) / 1e12
-    dense_equivalent = dense_equivalent_flops(shapes, sweeps)
+    dense_equivalent = dense_equivalent_flops(shapes, sweeps, refreshes)
     roofline = {
         "kernel": "atomo_encode_svd (all launches of one encode of the 21-layer set)",
-        "bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-        "frac": round(achieved / PEAK_FP32_MFMA_TFLOPS, 5),
+        "bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
+        "frac": round(achieved / peak, 5),
         "encode_gpu_ms": round(encode_ms, 4),
         "executed_contraction_flops_per_encode": contraction,
         "vector_alu_rotation_flops_per_encode": rotations,
         "traffic": profiled_traffic_bytes("encode"),
         "traffic_unit": "HBM-side bytes per encode, all launches (rocprofv3 --pmc FETCH_SIZE + WRITE_SIZE, scaled by a plain "
                         "copy of known size; read from the committed summary in profiles/, not measured by this run)",
+        "layers_solved_directly": sum(solved_directly(m, n, sw, rf) for (m, n), sw, rf in zip(shapes, sweeps, refreshes)),
         "jacobi_sweeps_per_layer": sweeps,
         "gram_refreshes_per_layer": refreshes,
         "eigen_solves_per_step": pair_visits, "jacobi_steps_per_step": jacobi_steps,
@@ -290,7 +318,8 @@ def main():
         "by_kernel_event_pass": by_kernel,
         "ms_per_step_event_pass": round(ms_per_step_profiled, 4),
         # what the same sweep counts would cost as textbook blocked one-sided Jacobi on the data,
-        # sweeps x (8 M r^2 + 4 r^3): flops this library does NOT execute (it sweeps on the r x r Gram matrix)
+        # sweeps x (8 M r^2 + 4 r^3): flops this library does NOT execute (it sweeps on the r x r Gram matrix); layers
+        # that were solved directly do not count
         "dense_equivalent_not_executed": {
             "flops_same_sweeps": dense_equivalent,
             "tflops_over_encode": round(dense_equivalent / (encode_ms * 1e-3) / 1e12, 3),
@@ -375,8 +404,8 @@ def aggregate_decode_leg(ctx, torch, binding, inputs, shapes, s, seed, workers=1
     torch.cuda.synchronize()
     enc16 = (time.perf_counter() - t0) / 3
     ctx.status()
-    sweeps16 = ctx.svd_sweeps(len(all_mats))
-    dense16 = dense_equivalent_flops(list(shapes) * workers, sweeps16)
+    sweeps16, refreshes16 = ctx.svd_sweeps(len(all_mats)), ctx.svd_refreshes(len(all_mats))
+    dense16 = dense_equivalent_flops(list(shapes) * workers, sweeps16, refreshes16)
     del all_mats
     msgs = [flat_msgs[w * len(shapes):(w + 1) * len(shapes)] for w in range(workers)]
     groups = [[msgs[w][j] for w in range(workers)] for j in range(len(shapes))]
@@ -420,7 +449,7 @@ def aggregate_decode_leg(ctx, torch, binding, inputs, shapes, s, seed, workers=1
 def section6_leg(ctx, torch, binding, inputs, s, seed, reps=20):
     """The same encode + decode on the layer sets in the reshape of Section 6 ([x*y/2, 2*k*k] per convolution):
     ResNet-18 (every matrix has at most 18 columns, all on the thin path) and VGG-11-BN (eight such matrices
-    plus two 512 x 512 fully connected layers, which take the Gram-space iteration).  Wall time per step, and
+    plus two 512 x 512 fully connected layers).  Wall time per step, and
     the GPU time of the thin kernels against the bytes they have to move (see executed_work)."""
     out = {}
     for name, shapes in (("resnet18", inputs.RESNET18_SECTION6_SHAPES), ("vgg11bn", inputs.VGG11BN_SECTION6_SHAPES)):
@@ -444,7 +473,6 @@ def section6_leg(ctx, torch, binding, inputs, s, seed, reps=20):
             step()
         torch.cuda.synchronize()
         dt = (time.perf_counter() - t0) / reps
-        sweeps = ctx.svd_sweeps(len(shapes))
         ctx.profile_enable(True)
         prof = {}
         for _ in range(reps):
@@ -453,7 +481,7 @@ def section6_leg(ctx, torch, binding, inputs, s, seed, reps=20):
                 if cnt:
                     prof[k] = prof.get(k, 0.0) + ms
         ctx.profile_enable(False)
-        thin_bytes = sum(4.0 * m * n * (3 + 2 * sw) for (m, n), sw in zip(shapes, sweeps) if min(m, n) <= 32)
+        thin_bytes = sum(2 * 4.0 * m * n for m, n in shapes if min(m, n) <= 32)
         thin_ms = prof.get("svd_thin", 0.0) / reps
         out[name] = {"elements": n_elem, "status": status, "us_per_step": round(dt * 1e6, 1),
                      "elements_per_s": n_elem / dt,
@@ -477,7 +505,8 @@ def single_layer_leg(ctx, torch, binding, inputs, reps=50):
     for _ in range(5):
         step()
         torch.cuda.synchronize()
-    status, sweeps = ctx.status()
+    status, _ = ctx.status()
+    sweeps = ctx.svd_sweeps(1)
     t0 = time.perf_counter()
     for _ in range(reps):
         step()
@@ -490,9 +519,9 @@ def single_layer_leg(ctx, torch, binding, inputs, reps=50):
         step()
         torch.cuda.synchronize()
         lat.append(time.perf_counter() - t1)
-    flops = sweeps * (8.0 * 576 * 64 * 64 + 4.0 * 64 ** 3)
+    flops = dense_equivalent_flops([(64, 576)], sweeps, ctx.svd_refreshes(1))
     return {"workload": "one 64 x 576 matrix, rank-4 signal 1, .5, .25, .125 + N(0, 0.01^2), s = 2, encode + decode",
-            "status": status, "jacobi_sweeps": sweeps, "kept_atoms": int(msgs[0].count.item()),
+            "status": status, "jacobi_sweeps": sweeps[0], "kept_atoms": int(msgs[0].count.item()),
             "us_per_step_back_to_back": round(dt * 1e6, 1), "us_per_step_waiting_each_time": round(1e6 * sorted(lat)[len(lat) // 2], 1),
             "elements_per_s": 64 * 576 / dt,
             "dense_equivalent_gflops_not_a_roofline": round(flops / dt / 1e9, 2)}
@@ -500,10 +529,8 @@ def single_layer_leg(ctx, torch, binding, inputs, reps=50):
 
 def batch64_leg(ctx, torch, binding, inputs, with_oracle, reps=3):
     """64 matrices 512 x 4608 (rank-16 signal, sigma ~ U(0.1, 1), + N(0, 0.01^2)), s = 4, encoded in one call and
-    decoded in one launch: the configuration that fills the chip.  Encode: contraction flops executed (Gram
-    matrices, rotation of the data, two-sided updates of C, accumulation of the rotations, the blocks the pair
-    problems bring up to date; real data, measured sweep and refresh counts) over the encode time, against the fp32
-    matrix-core peak.  Decode: 604 MB written once, against the HBM peak."""
+    decoded in one launch: the configuration that fills the chip.  Encode: contraction flops executed (see
+    executed_work) over the encode time, against the matrix-core peak of their precision.  Decode: 604 MB written once, against the HBM peak."""
     s, seed = 4.0, 0
     host = inputs.vgg_deep_conv_batch(0)
     shapes = [g.shape for g in host]
@@ -539,7 +566,7 @@ def batch64_leg(ctx, torch, binding, inputs, with_oracle, reps=3):
     pair_visits, jacobi_steps, row_update_tiles = ctx.last_counters()
     work = executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_update_tiles, n_elem, kept)
     rotations = jacobi_steps * 32 * ROTATION_UNITS * 64 * 6
-    contraction = sum(work[k][1] for k in ("svd_gram", "svd_update", "svd_refresh")) + work["svd_eig"][1] - rotations
+    contraction, peak = matrix_core_work(work, rotations)
     dec_bytes = work["decode_svd"][1]
     out = {"workload": "64 matrices 512 x 4608, rank-16 signal sigma ~ U(0.1, 1) + N(0, 0.01^2), s = 4, one encode call + "
                        "one decode launch", "elements": n_elem, "status": max(status, status2, key=abs),
@@ -548,10 +575,10 @@ def batch64_leg(ctx, torch, binding, inputs, with_oracle, reps=3):
            "jacobi_sweeps": [min(sweeps), max(sweeps)], "gram_refreshes": [min(refreshes), max(refreshes)],
            "kept_atoms": sum(kept),
            "encode_roofline": {"bound": "mfma", "achieved": round(contraction / (enc_ms * 1e-3) / 1e12, 2),
-                               "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                               "frac": round(contraction / (enc_ms * 1e-3) / 1e12 / PEAK_FP32_MFMA_TFLOPS, 4),
+                               "peak": round(peak, 1), "unit": "TFLOP/s",
+                               "frac": round(contraction / (enc_ms * 1e-3) / 1e12 / peak, 4),
                                "executed_contraction_flops": contraction, "vector_alu_rotation_flops": rotations,
-                               "dense_equivalent_not_executed_flops": dense_equivalent_flops(shapes, sweeps)},
+                               "dense_equivalent_not_executed_flops": dense_equivalent_flops(shapes, sweeps, refreshes)},
            "decode_roofline": {"bound": "hbm", "achieved": round(dec_bytes / (dec_ms * 1e-3) / 1e9, 1), "peak": PEAK_HBM_GBS,
                                "unit": "GB/s", "frac": round(dec_bytes / (dec_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
                                "algorithmic_bytes": dec_bytes}}
