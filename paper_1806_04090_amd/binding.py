@@ -159,7 +159,11 @@ def _f32_cuda(t: torch.Tensor, what: str) -> torch.Tensor:
 
 @dataclass
 class SvdMessage:
-    """Kept singular triplets of one matrix; buffers are device tensors owned by this object."""
+    """Kept singular triplets of one matrix; buffers are device tensors owned by this object.
+
+    The bytes of the C descriptor are kept from the first use on (a call takes hundreds of messages).  Assigning a field
+    drops them, and copies and pickles leave them out; a tensor that is given other memory in place (`resize_`, `set_`,
+    `.data`) has to be assigned again."""
     rows: int
     cols: int
     capacity: int
@@ -169,14 +173,16 @@ class SvdMessage:
     U: torch.Tensor       # float32 [capacity, rows]
     V: torch.Tensor       # float32 [capacity, cols]
 
+    def __setattr__(self, name, value):
+        self.__dict__.pop("_packed", None)
+        object.__setattr__(self, name, value)
+
+    def __getstate__(self):
+        return {k: v for k, v in self.__dict__.items() if k != "_packed"}
+
     def c_struct(self) -> atomo_svd_msg:
-        """The C descriptor, built once (the buffers of a message are not replaced after allocation)."""
-        c = self.__dict__.get("_c")
-        if c is None:
-            c = atomo_svd_msg(self.rows, self.cols, self.capacity, self.count.data_ptr(), self.idx.data_ptr(),
-                              None if self.w is None else self.w.data_ptr(), self.U.data_ptr(), self.V.data_ptr())
-            self.__dict__["_c"] = c
-        return c
+        return atomo_svd_msg(self.rows, self.cols, self.capacity, self.count.data_ptr(), self.idx.data_ptr(),
+                             None if self.w is None else self.w.data_ptr(), self.U.data_ptr(), self.V.data_ptr())
 
     def pack(self) -> bytes:
         """The bytes of the C descriptor, kept as `_packed`."""
@@ -200,12 +206,7 @@ class EntrywiseMessage:
     val: torch.Tensor     # float32 [capacity]
 
     def c_struct(self) -> atomo_ew_msg:
-        """The C descriptor, built once (the buffers of a message are not replaced after allocation)."""
-        c = self.__dict__.get("_c")
-        if c is None:
-            c = atomo_ew_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.val.data_ptr())
-            self.__dict__["_c"] = c
-        return c
+        return atomo_ew_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.val.data_ptr())
 
     def to_host(self) -> dict:
         k = min(int(self.count.item()), self.capacity)
@@ -223,12 +224,7 @@ class LqMessage:
     norm: torch.Tensor    # float32 [1]
 
     def c_struct(self) -> atomo_lq_msg:
-        """The C descriptor, built once (the buffers of a message are not replaced after allocation)."""
-        c = self.__dict__.get("_c")
-        if c is None:
-            c = atomo_lq_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.norm.data_ptr())
-            self.__dict__["_c"] = c
-        return c
+        return atomo_lq_msg(self.n, self.capacity, self.count.data_ptr(), self.idx.data_ptr(), self.norm.data_ptr())
 
     def to_host(self) -> dict:
         k = min(int(self.count.item()), self.capacity)
