@@ -9,7 +9,7 @@
 // Precision.  Squaring loses half of the digits, so everything between the data and sigma is in double precision:
 // products of two floats are exact there, lambda has an absolute error of about 1e-15 lambda_1, and sigma one of
 // 1e-10 sigma_1 at the fp32 floor 2e-6 sigma_1 of the encoder.  A matrix with singular values at or under that floor
-// (rank-deficient gradients), or with two kept atoms whose eigenvalues the search cannot tell apart, is left to the
+// (rank-deficient gradients), or with two kept atoms whose vectors are not separated (direct_vectors), is left to the
 // Jacobi iteration: DS_ACCEPT stays 0.
 #include <algorithm>
 #include <cmath>
@@ -768,7 +768,6 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
     __shared__ float key[MAX_R];
     __shared__ Alg1Scratch sc;
     __shared__ int ipart[256];
-    __shared__ int close;
     const DirectMat& m = mats[blockIdx.x];
     const int tid = threadIdx.x, r = m.r;
     const double l0 = m.lam[0];
@@ -778,33 +777,19 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
         const double l = m.lam[i];
         key[i] = l > floor ? (float)ldexp(sqrt(l), half) : 0.0f;
     }
-    if (tid == 0) close = 0;
     __syncthreads();
     const int ns = block_algorithm1(key, r, s, sc);
     const double tail_ns = sc.tail_ns;
     const int per = (r + 255) / 256;
     const int lo = min(r, tid * per), hi = min(r, lo + per);
     int kept_local = 0;
-    bool kept_before = false;
     for (int i = lo; i < hi; ++i) {
         const float p = alg1_probability(key[i], i, ns, s, tail_ns);
         const u32x4 rnd = philox4x32_10((u64)(i >> 2), m.stream_id, seed);
         const uint32_t word = (i & 3) == 0 ? rnd.x : (i & 3) == 1 ? rnd.y : (i & 3) == 2 ? rnd.z : rnd.w;
         if (m.sigma_out) m.sigma_out[i] = key[i];
         if (m.p_out) m.p_out[i] = p;
-        const bool kept = u01(word) < p;
-        kept_local += kept;
-        // two kept neighbours that the search left inside one interval: their vectors are not separated
-        if (kept) {
-            if (i == lo && i > 0) {
-                const float pb = alg1_probability(key[i - 1], i - 1, ns, s, tail_ns);
-                const u32x4 rb = philox4x32_10((u64)((i - 1) >> 2), m.stream_id, seed);
-                const int x = (i - 1) & 3;
-                kept_before = u01(x == 0 ? rb.x : x == 1 ? rb.y : x == 2 ? rb.z : rb.w) < pb;
-            }
-            if (kept_before && i > 0 && m.lam[i - 1] - m.lam[i] <= m.lam[i] * (4.0 / (double)(1 << LAM_BITS))) close = 1;
-        }
-        kept_before = kept;
+        kept_local += u01(word) < p;
     }
     ipart[tid] = kept_local;
     __syncthreads();
@@ -816,7 +801,7 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
         m.report[1] = 2;
         // all of the spectrum above the floor, but for rows of A that are zero themselves; a matrix of zeros has no atoms
         const bool resolved = zeros >= r || (zeros < r && m.lam[r - 1 - zeros] > FLOOR_REL * l0);
-        m.st[DS_ACCEPT] = resolved && !close && m.st[DS_FAIL] == 0;
+        m.st[DS_ACCEPT] = resolved && m.st[DS_FAIL] == 0;
         atomicMax(&flags[FLAG_MAX_SWEEPS], 1);
     }
     if (tid == 255) {
@@ -846,13 +831,14 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
 //
 // First the eigenvector of T for the eigenvalue next to lam, by a twisted factorisation: pivots from the top (wave 0) and
 // from the bottom (wave 1) as quotients of the characteristic polynomials of the leading and of the trailing blocks,
-// twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and a second round starts
-// from there.  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
+// twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and the next round starts
+// from there, until the residual is small enough (KEPT_APART).  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
 // vector and those columns of V.  Bound: latency, two chains of n steps and then N / 16 blocks with one barrier each, whose V comes
 // from memory: two blocks are on their way while one is worked on (64 KB each at 512 rows: with one, a block took 4 us), the
 // factors of all blocks are in LDS before the first.
 // Work: matrix, slot.
 constexpr int VEC_THREADS = VMAX / 2;
+constexpr int VEC_ROUNDS = 5;    // two as a rule; three to five for atoms that share a cluster with another kept one
 constexpr int FLD = RB + 1;      // row stride of a factor in LDS
 constexpr int VEC_LDS = VMAX * FLD * (int)sizeof(double);
 
@@ -878,7 +864,10 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
             fact[i / 8 * FLD + 2 * (i & 7) + 1] = x.y;
         }
     }
-    double lam = m.lam[m.idx[slot]];
+    const int kept = min(*m.count, m.capacity), at_lam = m.idx[slot];
+    const KeptApart apart(m.lam[at_lam], slot > 0 ? m.lam[m.idx[slot - 1]] : -1.0,
+                          slot + 1 < kept ? m.lam[m.idx[slot + 1]] : -1.0, 4.0 / (double)(1 << LAM_BITS));
+    double lam = m.lam[at_lam];
     const double good = 1e-14 * m.lam[0];
     // what wave 0 needs of T: its lane's entries
     constexpr int PER = VMAX / 64;
@@ -906,7 +895,7 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
     }
     if (tid == 0) T[1][0].x = 0.0;
     __syncthreads();
-    for (int round = 0; round < 3; ++round) {
+    for (int round = 0; round < VEC_ROUNDS; ++round) {
         if (wave < 2 || nw == 1) {
             // wave 0 the leading blocks, wave 1 the trailing ones (a workgroup of one wave: both)
             for (int dir = nw == 1 ? 0 : wave; dir < (nw == 1 ? 2 : wave + 1); ++dir) {
@@ -987,14 +976,19 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
             down_after = __shfl_down(down_after, 1);
             if (lane == 0) up_before = 1.0;
             if (lane == 63) down_after = 1.0;
-            double sq = 0.0, run = up_before;
+            double sq = 0.0, weight = 0.0, run = up_before;
+            auto add = [&](int u) {
+                const double z2 = run * run;
+                sq += z2;
+                weight = fma(z2, fabs(d[u]) + (fabs(e_up[u]) + fabs(e_dn[u])), weight);
+            };
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
                 const int i = i0 + u;
                 if (i < i1 && i >= at) {
                     run *= f[u];
                     X[i] = run;
-                    sq = fma(run, run, sq);
+                    add(u);
                 }
             }
             run = down_after;
@@ -1004,16 +998,19 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
                 if (i < i1 && i < at) {
                     run *= f[u];
                     X[i] = run;
-                    sq = fma(run, run, sq);
+                    add(u);
                 }
             }
             const double norm2 = wave_sum(sq), res = fabs(gamma) / sqrt(norm2);    // |T x - lam x| / |x|
+            weight = wave_sum(weight) / norm2;
             lam += gamma / norm2;                                // Rayleigh quotient
-            // over: the residual is small enough, or it never will be (the eigenvalue was not separated from its
-            // neighbour, or the factorisation broke down)
+            // over: the residual is small enough, or it never will be (the eigenvalue was not separated from that of
+            // another kept atom, or the factorisation broke down)
             if (lane == 0) {
+                const bool last = round == VEC_ROUNDS - 1;
                 red[0] = lam;
-                s_scale = res <= good || (round == 2 && res <= 100.0 * good) ? 1.0 / sqrt(norm2) : round == 2 ? -1.0 : 0.0;
+                s_scale = res <= (last ? 100.0 * good : good) && apart.vector(res, weight, lam) ? 1.0 / sqrt(norm2)
+                          : last || !apart.possible ? -1.0 : 0.0;
             }
         }
         __syncthreads();

@@ -310,8 +310,9 @@ __device__ inline double dpp_or_one(double x)
 // characteristic polynomials (every lane runs through the recurrence and keeps its own step); the two are joined where they
 // meet with the smallest pivot, and the entries are products of quotients from there, by scans.  The Rayleigh quotient
 // corrects lam; the third round starts within 2^-24 of the gap to the next kept eigenvalue.
-// t: as for sturm_below (n entries after the padding), e: off-diagonal.  residual: |T z - lam z| in the last round.
-__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam, double& residual)
+// t: as for sturm_below (n entries after the padding), e: off-diagonal.  residual: |T z - lam z| in the last round; lam: its
+// Rayleigh quotient; weight: the sum of |T_ij| z_i^2.
+__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double& lam, double& residual, double& weight)
 {
     const int lane = threadIdx.x & 63, i = lane & 31;
     const bool bottom = lane >= 32;
@@ -376,12 +377,16 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
     }
     const double inv = inverse_root(len2);
     residual = gamma * inv;
+    const double z2 = z * z * (inv * inv);
+    double sum = sum8(z2 * (fabs(di) + (fabs(ei) + fabs(eb))));
+    sum += dpp<DPP_MIRROR>(sum);
+    weight = fold16(sum, sum);
     return z * inv;
 }
 
 // Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
 // the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
-// zeros aside; kept neighbours apart; vectors with a small residual); otherwise the two-sided Jacobi iteration.  18
+// zeros aside; vectors with a small residual, kept ones apart); otherwise the two-sided Jacobi iteration.  18
 // columns: 42 us, 31 of them without the sums of the largest matrices; Jacobi in eight sweeps 73.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
@@ -498,21 +503,21 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         __syncthreads();
         if (wave == 0) {
             draw();
-            const double l = lane < r ? lam[lane] : 0.0, up = lane > 0 && lane < r ? lam[lane - 1] : 0.0;
-            // two kept neighbours closer than 2^-22 of themselves: their vectors are not separated
-            const bool close = lane > 0 && lane < r && ((mask >> lane) & (mask >> (lane - 1)) & 1ull) && up - l <= l * 2.384185791015625e-07;
             const bool resolved = zero_rows >= r || lam[r - 1 - zero_rows] > FLOOR_REL * lam[0];
-            const bool ok = resolved && __ballot(close) == 0ull;
-            if (lane == 0) { accepted = ok; drawn = mask; }
+            if (lane == 0) { accepted = resolved; drawn = mask; }
             if ((mask >> lane) & 1ull) below[__popcll(mask & ((1ull << lane) - 1))] = lane;
         }
         __syncthreads();
         const int count = accepted ? min(__popcll(drawn), m.capacity) : 0;
         for (int a = wave; a < count; a += ST / 64) {
-            double residual;
-            const double z = twisted_vector(T + pad, te, r, lam[below[a]], residual);
+            const double own = lam[below[a]];
+            // (2^-22: from a distance of that the three rounds end with vectors apart)
+            const KeptApart apart(own, a > 0 ? lam[below[a - 1]] : -1.0, a + 1 < count ? lam[below[a + 1]] : -1.0,
+                                  2.384185791015625e-07);
+            double residual, weight, rayleigh = own;
+            const double z = twisted_vector(T + pad, te, r, rayleigh, residual, weight);
             if (lane < THIN_R) A[1][a * LD + lane] = z;
-            if (lane == 0 && !(residual <= 1e-12 * lam[0])) accepted = 0;
+            if (lane == 0 && !(residual <= 1e-12 * lam[0] && apart.vector(residual, weight, rayleigh))) accepted = 0;
         }
         __syncthreads();
         direct = accepted != 0;

@@ -125,3 +125,25 @@ def test_a_training_loop_enqueues_the_direct_encode_alone_until_it_falls_short()
     check_svd_message_against_matrix(low.astype(np.float64), msgs[0].to_host(), *per[0])
     msgs, per, status, _ = encode([low], 3.0, 9, adaptive=1)
     assert status == 0 and route() != [DIRECT]
+
+
+def nearly_equal_tail(rng, m, n, tail):
+    """One dominant singular value over a tail of equal ones, which the rounding to fp32 pulls apart by about 1e-8."""
+    u, _ = np.linalg.qr(rng.standard_normal((m, min(m, n))))
+    v, _ = np.linalg.qr(rng.standard_normal((n, min(m, n))))
+    s = np.full(min(m, n), tail)
+    s[0] = 1.0
+    return ((u * s) @ v.T).astype(np.float32)
+
+
+@pytest.mark.parametrize("tail", [1e-2, 1e-3, 1e-4, 1e-5])
+@pytest.mark.parametrize("shape", [(60, 80), (120, 100), (300, 400), (560, 520)])
+def test_kept_vectors_of_a_nearly_equal_tail_are_orthogonal(shape, tail):
+    # neighbours that the search tells apart but a vector with a residual that is small against the largest eigenvalue
+    # does not: accepted, they had cosines of 0.1 and more
+    r = min(shape)
+    host = [nearly_equal_tail(np.random.default_rng(seed), *shape, tail) for seed in range(4)]
+    msgs, per, status, _ = encode(host, 32.0, 1, capacity=r)
+    assert status == 0
+    for G, msg, (sigma, p) in zip(host, msgs, per):
+        check_svd_message_against_matrix(G.astype(np.float64), msg.to_host(), sigma, p)

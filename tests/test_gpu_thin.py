@@ -58,3 +58,19 @@ def test_strided_and_unaligned():
         msgs = binding.atomo_encode_svd(ctx(), [G], 3.0, 9, 40, sigma_out=sigma, p_out=p)
         assert ctx().status()[0] == 0
         full_parity(host, 3.0, 9, 40, msgs[0], sigma.cpu().numpy(), p.cpu().numpy())
+
+
+@pytest.mark.parametrize("tail", [1e-2, 1e-3, 1e-4, 1e-5])
+@pytest.mark.parametrize("r", [6, 18, 32])
+def test_kept_vectors_of_a_nearly_equal_tail_are_orthogonal(r, tail):
+    host = []
+    for seed in range(8):
+        rng = np.random.default_rng(seed)
+        u, v = np.linalg.qr(rng.standard_normal((900, r)))[0], np.linalg.qr(rng.standard_normal((r, r)))[0]
+        s = tail * (1.0 + 10.0 ** rng.uniform(-8, -5, r))
+        s[0] = 1.0
+        host.append(((u * s) @ v.T).astype(np.float32))
+    msgs, per, status, _ = encode(host, 0.7 * r, 2, capacity=r)
+    assert status == 0
+    for G, msg, (sigma, p) in zip(host, msgs, per):
+        check_svd_message_against_matrix(G.astype(np.float64), msg.to_host(), sigma, p)
