@@ -29,7 +29,9 @@ struct SweepHint {
     uint64_t sig = 0;            // shapes of the call
     uint64_t seq = 0;            // order of the calls (0 = unused)
     int limit_gs = 0, limit_ds = 0;   // the sweep limits that call ran with
-    bool tried_direct = false, direct_only = false;   // the direct encode went first; and nothing was enqueued behind it
+    bool tried_direct = false;   // the direct encode went first,
+    bool direct_only = false;    // and the matrices of a size for it were left out of the iteration
+    bool iterated = false;       // the iteration was enqueued: `host` holds sweep counts of the matrices that it had
 };
 
 // Descriptor tables that the device holds, with what they were made from.  They hold addresses, sizes and stream ids, never

@@ -1304,7 +1304,10 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             if (!h.pending && h.sig == sig && h.host[2] == 1 && (!best || h.seq > best->seq)) best = &h;
         }
         if (best && try_direct && best->tried_direct && best->host[4] == 0) direct_only = true;
-        if (best && !best->direct_only) {
+        // (no history for a matrix that iterates now and was solved directly then)
+        const bool history = best && best->iterated && (direct_only || !best->tried_direct || best->host[4] > 0) &&
+                             (direct_only || !best->direct_only);
+        if (history) {
             const int g = best->host[0], d = best->host[1];
             if (!(g >= best->limit_gs && best->limit_gs < max_sweeps)) {
                 limit_gs = std::min(max_sweeps, std::max(1, g + adaptive));
@@ -1324,6 +1327,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         hint->limit_ds = limit_ds;
         hint->tried_direct = try_direct;
         hint->direct_only = direct_only;
+        hint->iterated = false;
     }
 
     if ((size_t)n_mats > ctx->report_cap) {                      // (hipFree waits for the device)
@@ -1415,6 +1419,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const bool any_direct = !plan.direct.mats.empty();
     bool iterate = false;                                        // is anything enqueued for the Jacobi iteration?
     for (int j = 0; j < n_mats; ++j) iterate = iterate || !plan.mats[j].skip;
+    if (hint) hint->iterated = iterate;
     // thin matrices: beside all others on a stream of their own, from the caller's point in time
     const bool any_thin = !plan.thin.mats.empty();
     const bool beside = any_thin && (any_direct || iterate);

@@ -147,3 +147,37 @@ def test_kept_vectors_of_a_nearly_equal_tail_are_orthogonal(shape, tail):
     assert status == 0
     for G, msg, (sigma, p) in zip(host, msgs, per):
         check_svd_message_against_matrix(G.astype(np.float64), msg.to_host(), sigma, p)
+
+
+@pytest.mark.parametrize("shapes", [[(660, 700)], [(200, 260), (660, 700), (300, 18)]])
+def test_the_sweep_budget_of_matrices_that_iterate_beside_solved_ones_is_kept(shapes):
+    # a budget in force shows in a gradient that needs more sweeps than it allows; from the third call on the
+    # launches of all sweeps were enqueued again
+    rng = np.random.default_rng(1)
+    easy = [inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5], 0.02) for m, n in shapes]
+    big = shapes.index((660, 700))
+    low = (rng.standard_normal((660, 300)) @ rng.standard_normal((300, 700))).astype(np.float32)
+    hard = [low if j == big else g for j, g in enumerate(easy)]
+    assert encode(easy, 3.0, 9)[2] == 0
+    used = ctx().svd_sweeps(len(shapes))[big]
+    assert encode(hard, 3.0, 9)[2] == 0 and ctx().svd_sweeps(len(shapes))[big] > used + 1
+    for _ in range(4):
+        assert encode(easy, 3.0, 9, adaptive=1)[2] == 0
+    assert encode(hard, 3.0, 9, adaptive=1)[2] == binding.ATOMO_ENOCONV
+    assert encode(hard, 3.0, 9, adaptive=1)[2] == 0
+
+
+def test_sweep_counts_of_calls_that_solved_a_matrix_directly_are_no_budget_for_its_iteration():
+    shapes = [(200, 260), (660, 700)]
+    rng = np.random.default_rng(2)
+    easy = [inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5], 0.02) for m, n in shapes]
+    quick = np.zeros(shapes[1], dtype=np.float32)
+    quick[:, :660] = np.diag(np.linspace(1, 2, 660))             # orthogonal rows: done in the first sweep
+    low = (rng.standard_normal((200, 120)) @ rng.standard_normal((120, 260))).astype(np.float32)
+    for _ in range(3):
+        assert encode([easy[0], quick], 3.0, 9, adaptive=1)[2] == 0
+    assert encode([low, quick], 3.0, 9, adaptive=1)[2] == binding.ATOMO_ENOCONV
+    assert encode([low, quick], 3.0, 9, adaptive=1)[2] == 0      # (now it iterates, with all sweeps)
+    for _ in range(2):
+        assert encode([easy[0], quick], 3.0, 9, adaptive=1)[2] == 0
+    assert encode([easy[0], quick], 40.0, 9, adaptive=1)[2] == 0     # a budget of many atoms: everything iterates
