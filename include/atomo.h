@@ -175,9 +175,11 @@ typedef struct atomo_svd_options {
                                      /* data, at a sweep boundary; the context also remembers after how many sweeps */
                                      /* the first of them asked for that, and a call enqueues those launches only  */
                                      /* from k sweeps before: a matrix that is ready sooner sweeps on until then.  */
-                                     /* A call whose predecessor had every matrix solved directly enqueues no      */
-                                     /* iteration: a matrix that would have needed it keeps the direct result and  */
-                                     /* is reported through ATOMO_ENOCONV; the call after it enqueues everything   */
+                                     /* A matrix that was solved directly in that earlier call gets no iteration   */
+                                     /* enqueued: one that would have needed it keeps the direct result and is     */
+                                     /* reported through ATOMO_ENOCONV, and the call after it enqueues both.  A    */
+                                     /* matrix that was not solved directly iterates without another attempt in    */
+                                     /* the next eight calls                                                       */
 } atomo_svd_options;
 
 /* -------- context ------------------------------------------------------------------------------ */

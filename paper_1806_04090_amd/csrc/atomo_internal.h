@@ -19,18 +19,24 @@ namespace atomo {
 // Device-side latched flags (int32 each).
 enum { FLAG_CAPACITY = 0, FLAG_NOCONV = 1, FLAG_MAX_SWEEPS = 2, FLAG_EIG_VISITS = 3, FLAG_EIG_INNER = 4, FLAG_DS_UPDATE_UNITS = 5, FLAG_COUNT = 8 };
 
-// What an SVD encode learnt about its own sweep counts, for the calls after it (atomo_svd_options.adaptive).
+// How an SVD encode goes about a matrix: Jacobi iteration; direct encode with the iteration behind it for what that leaves
+// over; direct encode alone.
+enum : uint8_t { ROUTE_ITERATE = 0, ROUTE_BOTH = 1, ROUTE_DIRECT = 2 };
+
+// What an SVD encode learnt about its matrices, for the calls after it (atomo_svd_options.adaptive).
+constexpr int HINT_MATS = 4;     // word of the first matrix
 struct SweepHint {
     int32_t* host = nullptr;     // pinned, device-visible: [0] most sweeps of a Gram-space matrix, [1] of a data-space one,
-                                 // [2] 1 once written, [3] see ask_from, [4] matrices that the direct encode left over
+                                 // [2] 1 once written, [3] see ask_from, [HINT_MATS + j] 1 if matrix j was solved directly
     int32_t* dev = nullptr;      // the same memory as the device addresses it
+    size_t cap = 0;              // words
     hipEvent_t done = nullptr;   // recorded after the kernel that writes `host`
     bool pending = false;        // the event has not been seen complete yet
     uint64_t sig = 0;            // shapes of the call
     uint64_t seq = 0;            // order of the calls (0 = unused)
     int limit_gs = 0, limit_ds = 0;   // the sweep limits that call ran with
-    bool tried_direct = false;   // the direct encode went first,
-    bool direct_only = false;    // and the matrices of a size for it were left out of the iteration
+    std::vector<uint8_t> route;  // ROUTE_* of every matrix
+    std::vector<uint8_t> passed; // calls in a row that have not tried to solve the matrix, which an earlier one could not
     bool iterated = false;       // the iteration was enqueued: `host` holds sweep counts of the matrices that it had
 };
 

@@ -933,19 +933,16 @@ __global__ __launch_bounds__(256) void svd_select(const SvdMat* mats, double s, 
 }
 
 // Most sweeps any Gram-space matrix and any data-space matrix of the call took, and the fewest sweeps after which a
-// Gram-space matrix asked for a refresh (0: none did), and how many matrices the direct encode left to the iteration,
+// Gram-space matrix asked for a refresh (0: none did), and which matrices were solved directly,
 // into pinned host memory that the next calls read without waiting (atomo_svd_options.adaptive).  One workgroup.
 __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
 {
     __shared__ int red[3][256];
-    __shared__ int open;
-    if (threadIdx.x == 0) open = 0;
-    __syncthreads();
     const int never = 1 << 30;
     int gs = 0, ds = 0, ask = never;
     for (int j = threadIdx.x; j < n_mats; j += 256) {
         const SvdMat& m = mats[j];
-        if (m.accepted && *m.accepted == 0) atomicAdd(&open, 1);
+        if (m.accepted) out[HINT_MATS + j] = *m.accepted;
         if (m.skip) continue;
         const int sw = m.report[0];
         if (m.gs) gs = max(gs, sw); else ds = max(ds, sw);
@@ -967,7 +964,6 @@ __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
         out[0] = red[0][0];
         out[1] = red[1][0];
         out[3] = red[2][0] == never ? 0 : red[2][0];
-        out[4] = open;
         out[2] = 1;
     }
 }
@@ -1040,10 +1036,10 @@ struct Plan {
 constexpr size_t SPLIT_TWO_SIDED = 4096;
 
 // Lays the workspace out (base == nullptr: sizes only).
-// try_direct: the matrices of a size for it go through the direct encode first (plan.direct); direct_only: and are left
-// out of everything else.
+// route: ROUTE_* of every matrix (only those that direct::eligible takes may have another than ROUTE_ITERATE); the direct
+// encode has plan.direct.
 void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, float* sigma_out, float* p_out,
-                uint64_t stream_base, const uint64_t* stream_ids, bool try_direct, bool direct_only, void* base, Plan& plan)
+                uint64_t stream_base, const uint64_t* stream_ids, const uint8_t* route, void* base, Plan& plan)
 {
     Carver carve(base);
     carve.take<char>(256);
@@ -1053,10 +1049,10 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
     size_t update_tiles = 0;
     for (int j = 0; j < n_mats; ++j) {
         const int r = mats[j].rows < mats[j].cols ? mats[j].rows : mats[j].cols;
-        if (try_direct && direct::eligible(r)) {
+        if (route[j] != ROUTE_ITERATE) {
             plan.direct_of[j] = (int)plan.direct.mats.size();
             plan.direct.mats.push_back(direct::DirectMat{});
-            if (direct_only) continue;
+            if (route[j] == ROUTE_DIRECT) continue;
         }
         const int nb = (r + BS - 1) / BS, nb2 = nb + (nb & 1);
         if (r > THIN_R && nb2 >= GS_MIN_BLOCKS) update_tiles += (size_t)(nb2 / 2) * (nb2 / 2 + nb2 * BS / PR);
@@ -1092,9 +1088,11 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
             d.capacity = msgs ? m.capacity : m.r;
             d.count = m.count; d.idx = m.idx; d.w = m.w; d.U = m.U; d.V = m.V;
             d.sigma_out = m.sigma_out; d.p_out = m.p_out; d.stream_id = m.stream_id;
+            d.index = j;
+            d.alone = route[j] == ROUTE_DIRECT;
             direct::plan_matrix(carve, d);
             m.accepted = d.st + direct::DS_ACCEPT;
-            if (direct_only) {
+            if (d.alone) {
                 m.skip = 1;
                 continue;
             }
@@ -1229,6 +1227,20 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
     plan.bytes = carve.off;
 }
 
+// Without history: the direct encode goes first (with the iteration behind it) for the matrices of a size for it.
+std::vector<uint8_t> first_routes(const atomo_mat* mats, int n_mats, bool try_direct)
+{
+    std::vector<uint8_t> route(n_mats);
+    for (int j = 0; j < n_mats; ++j)
+        route[j] = try_direct && direct::eligible(std::min(mats[j].rows, mats[j].cols)) ? ROUTE_BOTH : ROUTE_ITERATE;
+    return route;
+}
+
+// A matrix that the direct encode could not solve iterates without another attempt in so many calls.  The attempt costs a
+// fifth of the iteration (512 x 512 of rank 128: 0.9 of 4.7 ms), so it then adds a fortieth; a gradient that has become
+// solvable waits at most eight steps for it.
+constexpr uint8_t DIRECT_RETRY = 8;
+
 }  // namespace
 
 int svd_workspace_bytes(const atomo_mat* mats, int n_mats, size_t* bytes)
@@ -1238,7 +1250,7 @@ int svd_workspace_bytes(const atomo_mat* mats, int n_mats, size_t* bytes)
         if ((mats[j].rows < mats[j].cols ? mats[j].rows : mats[j].cols) > MAX_R) return ATOMO_EINVAL;
     }
     Plan plan;
-    build_plan(mats, n_mats, nullptr, nullptr, nullptr, 0, nullptr, true, false, nullptr, plan);
+    build_plan(mats, n_mats, nullptr, nullptr, nullptr, 0, nullptr, first_routes(mats, n_mats, true).data(), nullptr, plan);
     *bytes = plan.bytes;
     return ATOMO_OK;
 }
@@ -1268,8 +1280,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
                             !(opt && ((opt->max_sweeps > 0 && opt->max_sweeps < 16) || opt->stop_cosine > 0.0f ||
                                       opt->max_inner_sweeps > 0 || opt->inner_reduction > 0.0f || opt->full_period > 0 ||
                                       opt->block_order != 0));
-    // A training loop (`adaptive`) whose last finished call had every matrix settled directly enqueues no iteration.
-    bool direct_only = false;
+    std::vector<uint8_t> route = first_routes(mats, n_mats, try_direct), passed(n_mats, 0);
 
     // Sweep limits of this call.  With `adaptive`, what the most recent finished call with the same shapes needed plus
     // the margin; a call that used up a reduced limit tells nothing about what was needed and is followed by a full one.
@@ -1301,12 +1312,23 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
                 if (q == hipSuccess) h.pending = false;
                 else (void)hipGetLastError();                    // "not ready" is an answer, not an error to keep
             }
-            if (!h.pending && h.sig == sig && h.host[2] == 1 && (!best || h.seq > best->seq)) best = &h;
+            if (!h.pending && h.sig == sig && h.route.size() == (size_t)n_mats && h.host[2] == 1 && (!best || h.seq > best->seq)) best = &h;
         }
-        if (best && try_direct && best->tried_direct && best->host[4] == 0) direct_only = true;
-        // (no history for a matrix that iterates now and was solved directly then)
-        const bool history = best && best->iterated && (direct_only || !best->tried_direct || best->host[4] > 0) &&
-                             (direct_only || !best->direct_only);
+        // Routes: a matrix that was solved directly gets no iteration behind it, one that fell short of that gets it
+        // again, and one that left its iteration the work is not tried again for a while.
+        bool history = best && best->iterated;
+        for (int j = 0; best && j < n_mats; ++j) {
+            const uint8_t then = best->route[j];
+            const bool solved = then != ROUTE_ITERATE && best->host[HINT_MATS + j] != 0;
+            if (route[j] == ROUTE_BOTH) {
+                if (solved) route[j] = ROUTE_DIRECT;
+                else if (then == ROUTE_BOTH) passed[j] = 1;
+                else if (then == ROUTE_ITERATE && best->passed[j] > 0 && best->passed[j] < DIRECT_RETRY) passed[j] = best->passed[j] + 1;
+                if (passed[j] > 0) route[j] = ROUTE_ITERATE;
+            }
+            // (no sweep counts for a matrix that iterates now and did not then)
+            if (route[j] != ROUTE_DIRECT && (solved || then == ROUTE_DIRECT)) history = false;
+        }
         if (history) {
             const int g = best->host[0], d = best->host[1];
             if (!(g >= best->limit_gs && best->limit_gs < max_sweeps)) {
@@ -1315,18 +1337,25 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             }
             if (!(d >= best->limit_ds && best->limit_ds < max_sweeps)) limit_ds = std::min(max_sweeps, std::max(1, d + adaptive));
         }
-        if (!hint->host) {
-            ATOMO_HIP(ctx, hipHostMalloc((void**)&hint->host, 8 * sizeof(int32_t), hipHostMallocDefault));
+        hint->seq = 0;                                           // (nothing to learn from until the call is under way)
+        const size_t words = HINT_MATS + (size_t)n_mats;
+        if (words > hint->cap) {
+            if (hint->host) ATOMO_HIP(ctx, hipHostFree(hint->host));
+            hint->host = nullptr;
+            hint->cap = 0;
+            const size_t want = align_up(words, 256);
+            ATOMO_HIP(ctx, hipHostMalloc((void**)&hint->host, want * sizeof(int32_t), hipHostMallocDefault));
             ATOMO_HIP(ctx, hipHostGetDevicePointer((void**)&hint->dev, hint->host, 0));
-            ATOMO_HIP(ctx, hipEventCreateWithFlags(&hint->done, hipEventDisableTiming));
+            hint->cap = want;
         }
-        for (int k = 0; k < 8; ++k) hint->host[k] = 0;
+        if (!hint->done) ATOMO_HIP(ctx, hipEventCreateWithFlags(&hint->done, hipEventDisableTiming));
+        for (size_t k = 0; k < words; ++k) hint->host[k] = 0;
         hint->sig = sig;
         hint->seq = ++ctx->hint_seq;
         hint->limit_gs = limit_gs;
         hint->limit_ds = limit_ds;
-        hint->tried_direct = try_direct;
-        hint->direct_only = direct_only;
+        hint->route = route;
+        hint->passed = passed;
         hint->iterated = false;
     }
 
@@ -1344,7 +1373,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     // (laid out in the workspace there is, and again if it turns out too small)
     for (;;) {
         plan = Plan();
-        build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, try_direct, direct_only, ctx->ws, plan);
+        build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, route.data(), ctx->ws, plan);
         if (plan.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL; // (the work items address the workspace in 32 bits of 16-byte units)
         if (ctx->ws && plan.bytes <= ctx->ws_bytes) break;
         if ((rc = ensure_workspace(ctx, plan.bytes)) != ATOMO_OK) return rc;
@@ -1443,7 +1472,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             ctx->direct_lds = true;
         }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, stream);
-        direct::launch(plan.direct, dt, s, seed, direct_only, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, stream);
+        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, stream);
     }
     if (!iterate) {
         if (beside) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join_thin, 0));

@@ -50,6 +50,8 @@ struct DirectMat {
     float* inv;                      // [capacity] 1 / sigma of the kept atom
     unsigned long long stream_id;
     int* report;                     // [2] sweeps (1: solved directly) and passes over the data
+    int index;                       // which matrix of the call this is
+    int alone;                       // 1: no iteration behind it, so it is reported if it is not accepted
 };
 
 struct DirectPlan {
@@ -73,10 +75,8 @@ struct DirectTables {
     int n_mats;
     const svd::Work *gram, *tiles, *tri, *eig, *vec, *lng;
 };
-// finish: the call enqueues nothing else for these matrices, so those that were not accepted are reported; hint_out
-// (may be null): where the counts for the next calls go.
-void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int finish, int* hint_out, int* d_flags,
-            hipStream_t stream);
+// hint_out (may be null, has to be if anything iterates): where the words for the next calls go.
+void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream);
 
 }  // namespace direct
 }  // namespace atomo

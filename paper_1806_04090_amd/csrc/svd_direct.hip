@@ -1107,29 +1107,20 @@ constexpr int LONG_GROUP = 4;
 
 // Bound: one read of the data (4 atoms at a time).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
 // positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The last workgroup reports.
-__global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_items, int n_mats, int finish,
-                                                   int* hint_out, int* flags)
+__global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_items, int n_mats, int* hint_out,
+                                                   int* flags)
 {
     __shared__ double us[LONG_GROUP][MAX_R];
     __shared__ double red[8][LONG_GROUP][LONG_COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if ((int)blockIdx.x >= n_items) {
-        __shared__ int left;
-        if (tid == 0) left = 0;
-        __syncthreads();
-        int open = 0;
-        for (int j = tid; j < n_mats; j += 512) open += mats[j].st[DS_ACCEPT] == 0;
-        if (open) atomicAdd(&left, open);
-        __syncthreads();
-        if (tid == 0 && finish) {
-            if (left) atomicMax(&flags[FLAG_NOCONV], 1);
-            if (hint_out) {
-                hint_out[0] = hint_out[1] = 1;
-                hint_out[3] = 0;
-                hint_out[4] = left;
-                hint_out[2] = 1;
-            }
+        for (int j = tid; j < n_mats; j += 512) {
+            const int accepted = mats[j].st[DS_ACCEPT];
+            if (!accepted && mats[j].alone) atomicMax(&flags[FLAG_NOCONV], 1);
+            if (hint_out) hint_out[HINT_MATS + mats[j].index] = accepted;
         }
+        __syncthreads();
+        if (tid == 0 && hint_out) hint_out[2] = 1;
         return;
     }
     const Work wk = work[blockIdx.x];
@@ -1302,8 +1293,7 @@ void plan_work(DirectPlan& plan)
         for (size_t k = 0; k < die[x].size(); ++k) plan.tri[8 * k + x] = die[x][k];
 }
 
-void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int finish, int* hint_out, int* d_flags,
-            hipStream_t stream)
+void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream)
 {
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
@@ -1313,7 +1303,7 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
     direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
-    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, (int)plan.lng.size(), t.n_mats, finish, hint_out, d_flags);
+    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, (int)plan.lng.size(), t.n_mats, hint_out, d_flags);
 }
 
 }  // namespace direct

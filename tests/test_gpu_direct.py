@@ -181,3 +181,32 @@ def test_sweep_counts_of_calls_that_solved_a_matrix_directly_are_no_budget_for_i
     for _ in range(2):
         assert encode([easy[0], quick], 3.0, 9, adaptive=1)[2] == 0
     assert encode([easy[0], quick], 40.0, 9, adaptive=1)[2] == 0     # a budget of many atoms: everything iterates
+
+
+def test_a_matrix_that_was_turned_down_iterates_without_another_attempt_and_is_tried_again_later():
+    shapes = [(200, 260), (300, 320), (96, 18), (70, 90)]
+    rng = np.random.default_rng(5)
+    easy = [inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5], 0.02) for m, n in shapes]
+    low = (rng.standard_normal((300, 90)) @ rng.standard_normal((90, 320))).astype(np.float32)
+    poor = [easy[0], low, easy[2], easy[3]]
+    want = [m.to_host() for m in encode(poor, 3.0, 9)[0]]
+    solved = lambda: [k == DIRECT for k in route(len(shapes))]
+    for _ in range(3):
+        msgs, _, status, _ = encode(poor, 3.0, 9, adaptive=1)
+        assert status == 0 and solved() == [True, False, True, True]
+        for a, m in zip(want, msgs):
+            b = m.to_host()
+            assert all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V"))
+    # a gradient of full rank in its place: iterates for a while (the others have no iteration behind them), then is solved
+    took = 0
+    while True:
+        msgs, per, status, _ = encode(easy, 3.0, 9, adaptive=1)
+        assert status == 0
+        full_parity(easy[1], 3.0, 9, 1, msgs[1], *per[1])
+        if all(solved()):
+            break
+        took += 1
+    assert 3 <= took <= 8
+    # a budget of many atoms in between: no attempt, no history from it, and none lost
+    assert encode(easy, 40.0, 9, adaptive=1)[2] == 0
+    assert encode(easy, 3.0, 9, adaptive=1)[2] == 0 and all(solved())
