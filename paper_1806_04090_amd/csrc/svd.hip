@@ -1466,13 +1466,31 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         if (beside) ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join_thin, s_thin));
     }
     // the hint comes from svd_pack, or from the direct encode if nothing iterates
+    hipEvent_t join_direct = nullptr;
     if (any_direct) {
         if (!ctx->direct_lds) {
             ATOMO_HIP(ctx, direct::allow_lds());
             ctx->direct_lds = true;
         }
-        ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, stream);
-        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, stream);
+        // Matrices with no iteration behind them are solved beside the iteration of the others, on a stream that has nothing
+        // else to do in this call (no stream of its own: a process has four hardware queues, and the caller's and three
+        // side streams fill them).  1024 x 2048 with the ResNet-18 layers: 6136 us per encode, 6709 in front of it.
+        bool apart = iterate;
+        for (const direct::DirectMat& d : plan.direct.mats) apart = apart && d.alone;
+        hipStream_t s_direct = stream;
+        if (apart) {
+            if ((rc = ensure_side_streams(ctx)) != ATOMO_OK) return rc;
+            if (plan.rowgram[0].empty()) { s_direct = ctx->side; join_direct = ctx->ev_join; }
+            else if (plan.rowgram[1].empty()) { s_direct = ctx->side2; join_direct = ctx->ev_join2; }
+            else if (!any_thin) { s_direct = ctx->side_thin; join_direct = ctx->ev_join_thin; }
+        }
+        if (join_direct) {
+            ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
+            ATOMO_HIP(ctx, hipStreamWaitEvent(s_direct, ctx->ev_fork, 0));
+        }
+        ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, s_direct);
+        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct);
+        if (join_direct) ATOMO_HIP(ctx, hipEventRecord(join_direct, s_direct));
     }
     if (!iterate) {
         if (beside) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join_thin, 0));
@@ -1603,6 +1621,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     }
     if (use_side[0]) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join, 0));
     if (use_side[1]) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join2, 0));
+    if (join_direct) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, join_direct, 0));
     {
         ProfScope ps(ctx, ATOMO_K_SVD_FINALIZE, stream);
         svd_select<<<(unsigned)n_mats, 256, 0, stream>>>(d_mats, s, (unsigned long long)seed, ctx->d_flags);

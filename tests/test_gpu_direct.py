@@ -210,3 +210,24 @@ def test_a_matrix_that_was_turned_down_iterates_without_another_attempt_and_is_t
     # a budget of many atoms in between: no attempt, no history from it, and none lost
     assert encode(easy, 40.0, 9, adaptive=1)[2] == 0
     assert encode(easy, 3.0, 9, adaptive=1)[2] == 0 and all(solved())
+
+
+@pytest.mark.parametrize("shapes", [[(660, 700), (200, 260), (512, 600)],                        # no data-space matrix iterates
+                                    [(660, 700), (300, 400), (200, 260), (300, 18)],             # large ones do
+                                    [(660, 700), (300, 400), (96, 130), (200, 260), (300, 18)],  # and small ones: no free stream
+                                    [(300, 400), (96, 130), (200, 260)]])
+def test_matrices_solved_beside_the_iteration_of_others_give_the_same_bits(shapes):
+    rng = np.random.default_rng(6)
+    host = [inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5], 0.02) for m, n in shapes]
+    for j, (m, n) in enumerate(shapes):
+        if (m, n) in ((300, 400), (96, 130)):                    # low rank: they iterate
+            host[j] = (rng.standard_normal((m, 40)) @ rng.standard_normal((40, n))).astype(np.float32)
+    want, per_want, status, _ = encode(host, 3.0, 9)
+    assert status == 0
+    want = [m.to_host() for m in want]
+    for _ in range(5):
+        msgs, per, status, _ = encode(host, 3.0, 9, adaptive=1)
+        assert status == 0
+        for a, m, x, y in zip(want, msgs, per_want, per):
+            b = m.to_host()
+            assert all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")) and np.array_equal(x, y)
