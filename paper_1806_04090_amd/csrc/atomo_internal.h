@@ -9,6 +9,7 @@
 
 #include "../../include/atomo.h"
 #include "../../include/atomo_bench.h"
+#include "../../include/atomo_debug.h"
 
 namespace atomo {
 
@@ -84,6 +85,8 @@ struct atomo_ctx {
     int hint_next = 0;
     uint64_t hint_seq = 0;
     bool direct_lds = false;       // direct::allow_lds has been called for this context's device
+    bool direct_spread = false;            // atomo_debug_direct_groups
+    long long direct_start_ticks = -1;     // (negative: the library's own bound)
     size_t rowgram_lds = 0;        // dynamic LDS that svd_rowgram has been allowed on this context's device
     atomo::TableCache svd_tables, dec_tables, prob_tables;   // of the SVD encoder, the SVD decoder and atomo_probabilities
     std::vector<char> table_scratch;     // where a call puts its tables together

@@ -328,6 +328,14 @@ int atomo_last_counters(const atomo_ctx* ctx, int32_t* pair_visits, int32_t* jac
     return ATOMO_OK;
 }
 
+int atomo_debug_direct_groups(atomo_ctx* ctx, int spread, int64_t start_ticks)
+{
+    if (!ctx) return ATOMO_EINVAL;
+    ctx->direct_spread = spread != 0;
+    ctx->direct_start_ticks = start_ticks;
+    return ATOMO_OK;
+}
+
 const char* atomo_strerror(int status)
 {
     switch (status) {

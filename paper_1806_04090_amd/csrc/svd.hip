@@ -1373,6 +1373,8 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     // (laid out in the workspace there is, and again if it turns out too small)
     for (;;) {
         plan = Plan();
+        plan.direct.spread = ctx->direct_spread;
+        plan.direct.start_ticks = ctx->direct_start_ticks >= 0 ? ctx->direct_start_ticks : direct::START_TICKS;
         build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, route.data(), ctx->ws, plan);
         if (plan.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL; // (the work items address the workspace in 32 bits of 16-byte units)
         if (ctx->ws && plan.bytes <= ctx->ws_bytes) break;
@@ -1426,6 +1428,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     place(plan.direct.gram, dt.gram);
     place(plan.direct.tiles, dt.tiles);
     place(plan.direct.tri, dt.tri);
+    place(plan.direct.groups, dt.groups);
     place(plan.direct.eig, dt.eig);
     place(plan.direct.vec, dt.vec);
     place(plan.direct.lng, dt.lng);

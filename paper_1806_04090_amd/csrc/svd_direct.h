@@ -9,12 +9,13 @@ namespace direct {
 constexpr int MAX_R = 640;           // vectors on the shorter side that the reduction holds in registers
 constexpr int TILE = 64;
 constexpr double MAX_BUDGET = 32.0;  // above this many expected atoms the vectors cost more than the Jacobi iteration
+constexpr long long START_TICKS = 2000000;   // 20 ms of the 100 MHz clock: how long a workgroup waits for its group to start
 
 // State words of a matrix (device, int32).
 enum {
     DS_ACCEPT = 0,       // 1: the message is in place and the Jacobi iteration leaves the matrix alone
     DS_EXP = 1,          // the Gram matrix was multiplied by 2^-DS_EXP (even) before the reduction
-    DS_FAIL = 2,         // 1: a wait of the reduction hit its bound
+    DS_FAIL = 2,         // 1: a wait of the reduction hit its bound (direct_tridiagonal_alone then does it again)
     DS_ZERO_ROWS = 3,    // rows of A that are exactly zero
     DS_WORDS = 8
 };
@@ -37,8 +38,8 @@ struct DirectMat {
     double* fact;                    // [N / 16][16][16] triangular factors of the blocks of 16 reflectors
     double* lam;                     // [r] eigenvalues, descending, scaled
     double* u;                       // [capacity][r] kept vectors of the shorter side
-    unsigned long long* xch;         // exchange slots of the reduction, see tri_group
-    int* xid;                        // [64] which die every workgroup of the matrix's group runs on, plus one
+    unsigned long long* xch;         // exchange slots of the reduction, see Tri
+    unsigned long long* gate;        // [1] the workgroups of the matrix's group that have started, see Gate
     int* st;                         // [DS_WORDS]
     int* count;
     int* idx;
@@ -56,24 +57,27 @@ struct DirectMat {
 
 struct DirectPlan {
     std::vector<DirectMat> mats;
-    std::vector<svd::Work> gram, tiles, tri, eig, vec, lng;
+    std::vector<svd::Work> gram, tiles, tri, groups, eig, vec, lng;
+    bool spread = false;             // deal the workgroups of a group over all dies (for tests)
+    long long start_ticks = START_TICKS;
     int eig_lanes = 64;              // lanes per eigenvalue in the search
     size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
     int max_nt = 1;
-    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
+    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + groups.size() + eig.size() + vec.size() + lng.size(); }
 };
 
 // Lets the kernels have more LDS than a launch gets by default; once per device.
 hipError_t allow_lds();
-// Lays out one matrix (base of `carve` null: sizes only) and appends its work; false if the matrix is not for this path.
+// true if a matrix of r vectors on the shorter side is of a size for this path
 bool eligible(int r);
+// Lays out one matrix (base of `carve` null: sizes only).
 void plan_matrix(Carver& carve, DirectMat& m);
 void plan_work(DirectPlan& plan);
 
 struct DirectTables {
     const DirectMat* mats;
     int n_mats;
-    const svd::Work *gram, *tiles, *tri, *eig, *vec, *lng;
+    const svd::Work *gram, *tiles, *tri, *groups, *eig, *vec, *lng;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.
 void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream);

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
     }
     if (ti == 0 && tj == 0) {
         if (tid < DS_WORDS) m.st[tid] = 0;
-        if (tid < 64) m.xid[tid] = 0;
+        if (tid == 0) *m.gate = 0;
         for (int i = tid; i < 4 * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
         if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
         if (tid == m.pad) m.td[tid].x = 0.0;
@@ -259,8 +259,52 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more.
 // The workgroups of a group sit on one die (blockIdx mod 8), whose L2 the exchange goes through: 0.77 us per step among 64
 // waves, against 5 us through memory; they check that with the die's number, and store through to memory if it is not so.
+// (On one die the stores have workgroup scope, which the memory model does not extend to other workgroups.  What carries them
+// over is the hardware: vector stores write through the L1 to the L2 that the whole die shares, and the readers' loads, of
+// agent scope, do not hit in an L1.  Agent scope on the stores would send them through to memory as well.)
+// Waits: nothing guarantees that a group is resident as a whole - other work on the GPU can hold the places that its last
+// workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, a group that does not
+// come together leaves as one (Gate), and direct_tridiagonal_alone reduces the matrix of a wait that was given up.
 // Bound: the chain of steps.  512 rows on 64 waves: 669 us, 1.3 us per step (955 before the
 // chain of a step was shortened).
+//
+// The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
+// waited too long, holds for all of them, for it is only set while some are missing, and who finds it set does not start.
+struct Gate {
+    static constexpr u64 OFF = 1ull << 63;
+    static __device__ inline int on_die(u64 word, int die) { return (int)(word >> (7 * die)) & 127; }
+    static __device__ inline int started(u64 word)
+    {
+        int sum = 0;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) sum += on_die(word, d);
+        return sum;
+    }
+    static __device__ inline int this_die() { return (int)__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 7; }
+    static __device__ inline void start(Global<u64> gate)
+    {
+        if (threadIdx.x == 0) __hip_atomic_fetch_add(gate, 1ull << (7 * this_die()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // True once all have started (one_die: all of them on this workgroup's die), false if the group does not start.
+    static __device__ inline bool pass(Global<u64> gate, int n_wgs, long long ticks, bool& one_die)
+    {
+        const int die = this_die();
+        const long long t0 = wall_clock64();
+        while (true) {
+            u64 word = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (word & OFF) return false;
+            if (started(word) == n_wgs) {
+                one_die = on_die(word, die) == n_wgs;
+                return true;
+            }
+            if (wall_clock64() - t0 >= ticks)                    // (a word that has changed meanwhile is looked at again)
+                (void)__hip_atomic_compare_exchange_strong(gate, &word, word | OFF, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_s_sleep(4);
+        }
+    }
+};
+
 template <int C, int R, int QW>
 struct Tri {
     static constexpr int CN = 64 * C, W = 64 * QW, OWN = (C + 3) / 4;
@@ -432,10 +476,9 @@ struct Tri {
     }
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
-    static constexpr long long SPIN_START = 200000000ll;         // 2 s of the 100 MHz clock for all workgroups to have started
 
     // false: a wait hit its bound
-    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs, double2* lds)
+    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs, long long start_ticks, double2* lds)
     {
         const StepStore store(mm);
         const int N = store.N;
@@ -448,9 +491,7 @@ struct Tri {
         q = w >> 6;
         off = CN - N;
         slots = global(mm.xch);
-        // which die: every workgroup says so, all wait for all
-        const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 15u) + 1;
-        if (threadIdx.x == 0) __hip_atomic_store(global(mm.xid) + member, xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        Gate::start(global(mm.gate));
         int expo, zeros;
         const double scale = scale_of<C>(mm, off, lane, expo, zeros);
 #pragma unroll
@@ -470,18 +511,7 @@ struct Tri {
             x[c] = j >= 0 ? scale * global(mm.C)[(size_t)mm.pad * N + j] : 0.0;
             v[c] = wv[c] = 0.0;
         }
-        {
-            const long long t0 = wall_clock64();
-            while (true) {
-                const int id = lane < n_wgs ? __hip_atomic_load(global(mm.xid) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : xcc;
-                if (__all(id != 0)) {
-                    local = __all(id == xcc);
-                    break;
-                }
-                if (wall_clock64() - t0 > SPIN_START) return false;
-                __builtin_amdgcn_s_sleep(4);
-            }
-        }
+        if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return false;
         phases<0>(k, store);
         update<C - 1, R - 1>();
         // what is left: the last 2 x 2 block
@@ -609,7 +639,7 @@ __device__ inline void tri_small(const DirectMat& m, double* lds)
 }
 
 // work: matrix (below 0: nothing), member of the group, workgroups of the group.
-__global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work)
+__global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work, long long start_ticks)
 {
     __shared__ double2 lds[2 * MAX_R];
     const Work wk = work[blockIdx.x];
@@ -619,11 +649,66 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
     switch (m.cls) {
         case CLS_64: tri_small<1>(m, (double*)lds); break;
         case CLS_128: tri_small<2>(m, (double*)lds); break;
-        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b, lds); } break;
-        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b, lds); } break;
-        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b, lds); } break;
+        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
     }
     if (!ok && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
+}
+
+// The reduction of a matrix whose group gave a wait up, by one workgroup that waits for nobody: the same steps on the matrix
+// in memory, of which nothing is needed afterwards.  A chain of two passes over what is left of it per step: tens of
+// milliseconds for 640 rows, and 2 us for the launch where there is nothing to do.
+__global__ __launch_bounds__(1024) void direct_tridiagonal_alone(const DirectMat* mats, const Work* groups)
+{
+    __shared__ double v[MAX_R], p[MAX_R];
+    const DirectMat& m = mats[groups[blockIdx.x].mat];
+    if (m.st[DS_FAIL] == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), N = m.nt * TILE;
+    const StepStore store(m);
+    const Global<double> A = global(m.C);
+    int expo, zeros;
+    const double scale = scale_of<MAX_R / 64>(m, MAX_R - N, lane, expo, zeros);
+    __syncthreads();
+    for (int e = tid; e < N * N; e += 1024) A[e] *= scale;
+    __syncthreads();
+    for (int k = m.pad; k < N - 2; ++k) {
+        const Global<const double> column = A + (size_t)k * N;
+        double sq = 0.0;
+        for (int i = lane; i < N; i += 64) sq = i > k + 1 ? fma(column[i], column[i], sq) : sq;
+        double beta, v0;
+        const double sig2 = wave_sum(sq);
+        householder(column[k + 1], sig2, beta, v0);
+        const double tau = householder_tau(sig2, v0);
+        if (wave == 0) {
+            for (int i = lane; i < N; i += 64) store.refl[(size_t)k * N + i] = v[i] = i > k + 1 ? column[i] : i == k + 1 ? v0 : 0.0;
+            if (lane == 0) store.put(k, tau, column[k], beta);
+        }
+        __syncthreads();
+        for (int i = k + 1 + wave; i < N; i += 16) {
+            double sum = 0.0;
+            for (int j = lane; j < N; j += 64) sum = j > k ? fma(A[(size_t)i * N + j], v[j], sum) : sum;
+            sum = wave_sum(sum);
+            if (lane == 0) p[i] = tau * sum;
+        }
+        __syncthreads();
+        double gamma = 0.0;
+        for (int i = lane; i < N; i += 64) gamma = i > k ? fma(v[i], p[i], gamma) : gamma;
+        gamma = wave_sum(gamma) * (0.5 * tau);
+        for (int i = k + 1 + wave; i < N; i += 16) {
+            const double vi = v[i], wi = fma(-gamma, vi, p[i]);
+            for (int j = lane; j < N; j += 64)
+                if (j > k) A[(size_t)i * N + j] = fma(-wi, v[j], fma(-vi, fma(-gamma, v[j], p[j]), A[(size_t)i * N + j]));
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        store.put(N - 2, 0.0, A[(size_t)(N - 2) * N + N - 2], A[(size_t)(N - 2) * N + N - 1]);
+        store.td[2 * N - 1] = A[(size_t)(N - 1) * N + N - 1];
+        m.st[DS_EXP] = expo;
+        m.st[DS_ZERO_ROWS] = zeros;
+        m.st[DS_FAIL] = 0;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -801,7 +886,7 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
         m.report[1] = 2;
         // all of the spectrum above the floor, but for rows of A that are zero themselves; a matrix of zeros has no atoms
         const bool resolved = zeros >= r || (zeros < r && m.lam[r - 1 - zeros] > FLOOR_REL * l0);
-        m.st[DS_ACCEPT] = resolved && m.st[DS_FAIL] == 0;
+        m.st[DS_ACCEPT] = resolved;
         atomicMax(&flags[FLAG_MAX_SWEEPS], 1);
     }
     if (tid == 255) {
@@ -1240,7 +1325,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.lam = carve.take<double>(m.r);
     m.u = carve.take<double>((size_t)m.capacity * m.r);
     m.xch = carve.take<u64>((size_t)4 * 64 * CLS_CHUNKS[m.cls]);
-    m.xid = carve.take<int>(64);
+    m.gate = carve.take<u64>(1);
     m.st = carve.take<int>(DS_WORDS);
     m.inv = carve.take<float>(m.capacity);
 }
@@ -1283,7 +1368,8 @@ void plan_work(DirectPlan& plan)
         int best = 0;
         for (int x = 1; x < 8; ++x)
             if (load[x] < load[best]) best = x;
-        for (int g = 0; g < wgs; ++g) die[best].push_back(Work{j, g, wgs, 0});
+        for (int g = 0; g < wgs; ++g) die[plan.spread ? (best + g) % 8 : best].push_back(Work{j, g, wgs, 0});
+        if (wgs > 1) plan.groups.push_back(Work{j, 0, 0, 0});
         load[best] += (long long)m.r * wgs;
     }
     size_t most = 0;
@@ -1298,7 +1384,8 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
     direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
-    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri);
+    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    if (!plan.groups.empty()) direct_tridiagonal_alone<<<grid(plan.groups), 1024, 0, stream>>>(t.mats, t.groups);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);

@@ -231,3 +231,34 @@ def test_matrices_solved_beside_the_iteration_of_others_give_the_same_bits(shape
         for a, m, x, y in zip(want, msgs, per_want, per):
             b = m.to_host()
             assert all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")) and np.array_equal(x, y)
+
+
+@pytest.fixture
+def groups():
+    yield ctx().debug_direct_groups
+    ctx().debug_direct_groups()
+
+
+@pytest.mark.parametrize("shape", [(129, 140), (200, 300), (256, 300), (300, 257), (512, 600), (530, 513), (640, 660)])
+def test_groups_over_several_dies_and_groups_that_do_not_come_together(groups, shape):
+    host = [inputs.low_rank_plus_noise(np.random.default_rng(seed), *shape, [1.0, 0.5, 0.2], 0.02) for seed in range(3)]
+    host[2][:, 5:9] = 0                                          # (a few rows or columns of zeros)
+    host[2][5:9] = 0
+    want, per_want, status, _ = encode(host, 4.0, 3)
+    assert status == 0 and route(3) == [DIRECT] * 3
+    want = [m.to_host() for m in want]
+    groups(spread=True)                                          # exchange through memory: the same sums
+    msgs, per, status, _ = encode(host, 4.0, 3)
+    assert status == 0 and route(3) == [DIRECT] * 3
+    for a, m in zip(want, msgs):
+        b = m.to_host()
+        assert all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V"))
+    for spread in (False, True):
+        groups(spread=spread, start_ticks=0)                     # every workgroup gives up: one reduces the matrix
+        msgs, per, status, _ = encode(host, 4.0, 3)
+        assert status == 0 and route(3) == [DIRECT] * 3
+        for j, (G, msg, (sigma, p)) in enumerate(zip(host, msgs, per)):
+            full_parity(G, 4.0, 3, j, msg, sigma, p)
+    groups()
+    msgs, _, status, _ = encode(host, 4.0, 3)
+    assert status == 0 and all(np.array_equal(a[k], m.to_host()[k]) for a, m in zip(want, msgs) for k in ("idx", "w", "U", "V"))
