@@ -176,8 +176,11 @@ typedef struct atomo_svd_options {
                                      /* the first of them asked for that, and a call enqueues those launches only  */
                                      /* from k sweeps before: a matrix that is ready sooner sweeps on until then.  */
                                      /* A matrix that was solved directly in that earlier call gets no iteration   */
-                                     /* enqueued: one that would have needed it keeps the direct result and is     */
-                                     /* reported through ATOMO_ENOCONV, and the call after it enqueues both.  A    */
+                                     /* enqueued.  One that would have needed it is reported through ATOMO_ENOCONV, */
+                                     /* and the call after it enqueues both; its message holds the direct result,  */
+                                     /* or, if a kept vector of that was not accepted, atoms of another exact      */
+                                     /* decomposition: the vectors of the shorter side, e_i (a_i / |a_i|)^T, drawn  */
+                                     /* with Algorithm 1 on their norms, so it is still an unbiased estimate.  A   */
                                      /* matrix that was not solved directly iterates without another attempt in    */
                                      /* the next eight calls                                                       */
 } atomo_svd_options;

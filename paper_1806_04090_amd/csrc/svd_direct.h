@@ -17,6 +17,7 @@ enum {
     DS_EXP = 1,          // the Gram matrix was multiplied by 2^-DS_EXP (even) before the reduction
     DS_FAIL = 2,         // 1: a wait of the reduction hit its bound (direct_tridiagonal_alone then does it again)
     DS_ZERO_ROWS = 3,    // rows of A that are exactly zero
+    DS_BROKEN = 4,       // 1: a kept vector was not accepted (DS_ACCEPT is 0 then)
     DS_WORDS = 8
 };
 
@@ -30,6 +31,7 @@ struct DirectMat {
     int capacity;
     double* part;                    // [nchunks][nt (nt + 1) / 2][64 * 64] partial Gram tiles
     double* C;                       // [N][N] Gram matrix, both triangles
+    double* diag;                    // [N] its diagonal: the squared norms of the rows of A
     double* refl;                    // [N][N] row k: the Householder vector of step k (entries from 64 (k / 64) on)
     double* tau;                     // [N]
     double2* td;                     // [N] tridiagonal matrix, scaled: squared coupling to the entry before (kept above

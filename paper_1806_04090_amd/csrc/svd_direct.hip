@@ -185,6 +185,7 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
     for (int p = 0; p < 16; ++p) {
         const int i = (tid >> 6) + 4 * p, j = tid & 63;
         C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
+        if (ti == tj && i == j) m.diag[ti * TILE + i] = sum[p];
         t[i][j] = sum[p];
     }
     if (ti != tj) {
@@ -1118,7 +1119,10 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
         }
     };
     const double scale = s_scale;
-    if (tid == 0 && !(scale > 0.0)) m.st[DS_ACCEPT] = 0;
+    if (tid == 0 && !(scale > 0.0)) {
+        m.st[DS_ACCEPT] = 0;
+        m.st[DS_BROKEN] = 1;
+    }
     double y0 = c0 >= pad && c0 < N ? X[c0 - pad] * scale : 0.0;
     double y1 = c0 + 1 >= pad && c0 < N ? X[c0 + 1 - pad] * scale : 0.0;
     const int last = (N - 3) / RB, first_block = pad / RB;
@@ -1191,27 +1195,117 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
 constexpr int LONG_COLS = 128;   // positions of the long side per workgroup
 constexpr int LONG_GROUP = 4;
 
-// Bound: one read of the data (4 atoms at a time).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
-// positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The last workgroup reports.
-__global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_items, int n_mats, int* hint_out,
-                                                   int* flags)
+// A message that needs no singular vectors, for a matrix with a kept vector that was not accepted and no iteration behind it:
+// the r vectors themselves are an atomic decomposition (A = sum_i |a_i| e_i (a_i / |a_i|)^T), exact, and what is drawn from it
+// by Algorithm 1 is an unbiased estimate of A.  Its atoms are sorted by their norms, as singular values are; they are not
+// orthogonal to each other.  256 threads of one workgroup.
+struct RowAtoms {
+    float key[1024];
+    int src[1024], count[256];
+    Alg1Scratch sc;
+    int row[MAX_R];
+    float weight[MAX_R];
+};
+static_assert(MAX_R <= 1024, "keys of one sort");
+__device__ inline void row_message(const DirectMat& m, double s, u64 seed, RowAtoms& x, int* flags)
 {
-    __shared__ double us[LONG_GROUP][MAX_R];
+    const int tid = threadIdx.x, r = m.r;
+    int P = 1;
+    while (P < r) P <<= 1;
+    __syncthreads();
+    for (int i = tid; i < P; i += 256) {
+        x.key[i] = i < r ? (float)sqrt(m.diag[m.pad + i]) : -1.0f;
+        x.src[i] = i;
+    }
+    __syncthreads();
+    block_sort_desc(x.key, x.src, P);
+    const int ns = block_algorithm1(x.key, r, s, x.sc);
+    const double tail_ns = x.sc.tail_ns;
+    const int per = (r + 255) / 256, lo = min(r, tid * per), hi = min(r, lo + per);
+    auto probability = [&](int i) { return alg1_probability(x.key[i], i, ns, s, tail_ns); };
+    auto drawn = [&](int i, float p) {
+        const u32x4 rnd = philox4x32_10((u64)(i >> 2), m.stream_id, seed);
+        return u01((i & 3) == 0 ? rnd.x : (i & 3) == 1 ? rnd.y : (i & 3) == 2 ? rnd.z : rnd.w) < p;
+    };
+    int mine = 0;
+    for (int i = lo; i < hi; ++i) {
+        const float p = probability(i);
+        if (m.sigma_out) m.sigma_out[i] = x.key[i];
+        if (m.p_out) m.p_out[i] = p;
+        mine += drawn(i, p);
+    }
+    x.count[tid] = mine;
+    __syncthreads();
+    int pos = 0, total = 0;
+    for (int t = 0; t < 256; ++t) {
+        pos += t < tid ? x.count[t] : 0;
+        total += x.count[t];
+    }
+    for (int i = lo; i < hi; ++i) {
+        const float p = probability(i);
+        if (!drawn(i, p)) continue;
+        if (pos < m.capacity) {
+            x.row[pos] = x.src[i];
+            x.weight[pos] = x.key[i] / p;
+            m.idx[pos] = i;
+            if (m.w) m.w[pos] = x.weight[pos];
+        }
+        ++pos;
+    }
+    if (tid == 0) {
+        *m.count = total;
+        if (total > m.capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
+    }
+    __syncthreads();
+    for (int k = 0; k < min(total, m.capacity); ++k) {
+        const int row = x.row[k];
+        const double inv = 1.0 / sqrt(m.diag[m.pad + row]);
+        const float in_u = m.w ? 1.0f : x.weight[k];             // folded message: the weight goes into U
+        float* const shorter = m.transposed ? m.V + (size_t)k * m.cols : m.U + (size_t)k * m.rows;
+        float* const longer = m.transposed ? m.U + (size_t)k * m.rows : m.V + (size_t)k * m.cols;
+        for (int i = tid; i < r; i += 256) shorter[i] = i == row ? (m.transposed ? 1.0f : in_u) : 0.0f;
+        for (int c = tid; c < m.M; c += 256) {
+            const float g = m.transposed ? m.G[(long long)c * m.ldg + row] : m.G[(long long)row * m.ldg + c];
+            longer[c] = (float)((double)g * inv) * (m.transposed ? in_u : 1.0f);
+        }
+    }
+}
+
+// Bound: one read of the data (4 atoms at a time).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
+// positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The first workgroup reports (the host
+// memory that it writes to is far away: it is not to start last), and makes the messages of row_message.
+__global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_mats, double s, u64 seed,
+                                                   int* hint_out, int* flags)
+{
+    __shared__ __attribute__((aligned(16))) double us[LONG_GROUP][MAX_R];
     __shared__ double red[8][LONG_GROUP][LONG_COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if ((int)blockIdx.x >= n_items) {
-        for (int j = tid; j < n_mats; j += 512) {
+    if (blockIdx.x == 0) {
+        static_assert(sizeof(RowAtoms) <= sizeof(us), "made in the place of the vectors");
+        __shared__ int broken;
+        if (tid >= 256) return;
+        if (tid == 0) {
+            broken = 0;
+            if (hint_out) hint_out[2] = 1;                       // (read after the call has finished)
+        }
+        __syncthreads();
+        for (int j = tid; j < n_mats; j += 256) {
             const int accepted = mats[j].st[DS_ACCEPT];
-            if (!accepted && mats[j].alone) atomicMax(&flags[FLAG_NOCONV], 1);
+            if (!accepted && mats[j].alone) {
+                atomicMax(&flags[FLAG_NOCONV], 1);
+                if (mats[j].st[DS_BROKEN]) broken = 1;
+            }
             if (hint_out) hint_out[HINT_MATS + mats[j].index] = accepted;
         }
         __syncthreads();
-        if (tid == 0 && hint_out) hint_out[2] = 1;
+        if (broken)
+            for (int j = 0; j < n_mats; ++j)
+                if (mats[j].alone && mats[j].st[DS_BROKEN]) row_message(mats[j], s, seed, *(RowAtoms*)us, flags);
         return;
     }
-    const Work wk = work[blockIdx.x];
+    const Work wk = work[blockIdx.x - 1];
     const DirectMat& m = mats[wk.mat];
-    const int kept = min(*m.count, m.capacity), r = m.r, p0 = wk.a * LONG_COLS;
+    const int kept = m.st[DS_BROKEN] ? 0 : min(*m.count, m.capacity), r = m.r, p0 = wk.a * LONG_COLS;
     const Global<const float> G = global(m.G);
     const Global<float> out = global(m.transposed ? m.U : m.V);
     for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
@@ -1318,6 +1412,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     const size_t N = (size_t)m.nt * TILE;
     m.part = carve.take<double>((size_t)m.nchunks * ntiles * TILE * TILE);
     m.C = carve.take<double>(N * N);
+    m.diag = carve.take<double>(N);
     m.refl = carve.take<double>(N * N);
     m.tau = carve.take<double>(N);
     m.td = carve.take<double2>(N);
@@ -1391,7 +1486,7 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
     direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
-    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, (int)plan.lng.size(), t.n_mats, hint_out, d_flags);
+    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, t.n_mats, s, (u64)seed, hint_out, d_flags);
 }
 
 }  // namespace direct

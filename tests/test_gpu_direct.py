@@ -262,3 +262,40 @@ def test_groups_over_several_dies_and_groups_that_do_not_come_together(groups, s
     groups()
     msgs, _, status, _ = encode(host, 4.0, 3)
     assert status == 0 and all(np.array_equal(a[k], m.to_host()[k]) for a, m in zip(want, msgs) for k in ("idx", "w", "U", "V"))
+
+
+@pytest.mark.parametrize("shape", [(40, 90), (300, 400), (310, 260), (600, 640)])
+@pytest.mark.parametrize("kind", ["equal", "tail"])
+@pytest.mark.parametrize("folded", [False, True])
+def test_a_matrix_that_falls_short_with_nothing_behind_it_still_has_an_unbiased_message(shape, kind, folded):
+    # vectors that were not accepted stayed in the message, several of them the same one
+    rng = np.random.default_rng(shape[0])
+    r = min(shape)
+    easy = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.5], 0.05)
+    G = np.zeros(shape, dtype=np.float32)
+    if kind == "equal":                                          # every singular value is 2
+        np.fill_diagonal(G, 2.0)
+    else:
+        G = nearly_equal_tail(rng, *shape, 1e-2)
+    c = binding.Context(0)
+    sigma, p = torch.zeros(r, device="cuda"), torch.zeros(r, device="cuda")
+    msg = [binding.alloc_svd_message(*shape, r, "cuda", folded=folded)]
+    for g, want in ((easy, 0), (easy, 0), (G, binding.ATOMO_ENOCONV)):
+        binding.atomo_encode_svd(c, [dev(g)], 20.0, 3, 8, msgs=msg, sigma_out=sigma, p_out=p, adaptive=1)
+        assert c.status()[0] == want
+    h = msg[0].to_host()
+    A = (G if shape[0] <= shape[1] else G.T).astype(np.float64)
+    norms = np.linalg.norm(A, axis=1)
+    p = p.cpu().numpy()
+    np.testing.assert_allclose(sigma.cpu().numpy(), np.sort(norms)[::-1], rtol=1e-6)
+    np.testing.assert_allclose(p, oracle.probabilities(np.sort(norms)[::-1], 20.0), rtol=1e-5)
+    assert np.array_equal(h["idx"], np.flatnonzero(oracle.bernoulli_mask(p, 3, 8))) and h["count"] > 5
+    dense = binding.atomo_decode(c, msg).cpu().numpy()
+    rows = dense if shape[0] <= shape[1] else dense.T
+    kept = np.flatnonzero(np.linalg.norm(rows, axis=1))          # whole vectors, each over its probability
+    assert kept.size == h["count"]
+    np.testing.assert_allclose(np.sort(np.linalg.norm(rows[kept], axis=1)), np.sort(sigma.cpu().numpy()[h["idx"]] / p[h["idx"]]), rtol=1e-5)
+    scale = np.linalg.norm(rows[kept], axis=1) / norms[kept]
+    assert np.abs(rows[kept] - A[kept] * scale[:, None]).max() <= 1e-5 * np.abs(rows).max()
+    binding.atomo_encode_svd(c, [dev(G)], 20.0, 3, 8, msgs=msg, adaptive=1)
+    assert c.status()[0] == 0                                    # the next call has the iteration
