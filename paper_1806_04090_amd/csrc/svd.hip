@@ -1428,7 +1428,6 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     place(plan.direct.gram, dt.gram);
     place(plan.direct.tiles, dt.tiles);
     place(plan.direct.tri, dt.tri);
-    place(plan.direct.groups, dt.groups);
     place(plan.direct.eig, dt.eig);
     place(plan.direct.vec, dt.vec);
     place(plan.direct.lng, dt.lng);

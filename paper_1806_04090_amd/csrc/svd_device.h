@@ -114,35 +114,27 @@ __device__ inline double cell_start(u64 cell) { return bits_double(LAM_MIN_BITS 
 // When the vectors of kept atoms are orthogonal.  Two vectors with residuals res of eigenvalues a distance `gap` apart have
 // a cosine of up to 2 res / gap, and their images on the other side one of about res / (sigma_i sigma_j) more, so a residual
 // that is small against the largest eigenvalue says nothing about atoms far below it.  What is asked for:
-//   - a residual under 1e-5 of both distances, and under 2e-5 together with the rounding of the factorisation (every entry
-//     of T to an ulp or two: `weight`, the sum of |T_ij| z_i^2, times 2^-52);
+//   - a residual, together with the rounding of the factorisation (every entry of T to an ulp or two: `weight`, the sum of
+//     |T_ij| z_i^2, times 2^-52), under 2e-5 of both distances;
 //   - a Rayleigh quotient that has stayed with its own eigenvalue: in a cluster two vectors can end at the same one;
 //   - eigenvalues further apart than what the search resolves (`cells` of the smaller).
 // Neighbours are those among the kept atoms: directions that the message does not hold may mix.  One dominant singular
 // value over a tail of equal ones, 1e-3 to 1e-5 of it, rounded to fp32, 6 x 900 to 300 x 400: with a bound on the residual alone
 // cosines up to 1; with these up to 8e-6 (the others are left over).  Noise spectra, neighbours of their bulk included: none left over.
 struct KeptApart {
-    double lam, gap, need;
+    double lam, gap, product;        // distance to the nearest neighbour; sigma_i sigma_j squared for the one before
     bool possible;
     // up, down: eigenvalues of the kept atoms before and after this one, negative if there is none
     __device__ inline KeptApart(double own, double up, double down, double cells) : lam(own)
     {
-        gap = need = 1e300;
-        if (up >= 0.0) {
-            gap = up - own;
-            need = fmin(gap, sqrt(up * own));
-        }
-        if (down >= 0.0) {
-            gap = fmin(gap, own - down);
-            need = fmin(need, gap);
-        }
-        need *= 1e-5;
+        gap = fmin(up >= 0.0 ? up - own : 1e300, down >= 0.0 ? own - down : 1e300);
+        product = up >= 0.0 ? up * own : 1e300;
         possible = (up < 0.0 || up - own > cells * own) && (down < 0.0 || own - down > cells * down);
     }
     __device__ inline bool vector(double residual, double weight, double rayleigh) const
     {
-        return possible && residual <= need && fma(weight, 2.220446049250313e-16, residual) <= 2.0 * need &&
-               fabs(rayleigh - lam) <= 0.25 * gap;
+        const double e = fma(weight, 2.220446049250313e-16, residual);
+        return possible && e <= 2e-5 * gap && e * e <= 4e-10 * product && fabs(rayleigh - lam) <= 0.25 * gap;
     }
 };
 

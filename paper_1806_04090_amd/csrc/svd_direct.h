@@ -15,9 +15,10 @@ constexpr long long START_TICKS = 2000000;   // 20 ms of the 100 MHz clock: how 
 enum {
     DS_ACCEPT = 0,       // 1: the message is in place and the Jacobi iteration leaves the matrix alone
     DS_EXP = 1,          // the Gram matrix was multiplied by 2^-DS_EXP (even) before the reduction
-    DS_FAIL = 2,         // 1: a wait of the reduction hit its bound (direct_tridiagonal_alone then does it again)
+    DS_FAIL = 2,         // 1: a wait of the reduction hit its bound (the matrix is not accepted)
     DS_ZERO_ROWS = 3,    // rows of A that are exactly zero
-    DS_BROKEN = 4,       // 1: a kept vector was not accepted (DS_ACCEPT is 0 then)
+    DS_BROKEN = 4,       // 1: the message is no decomposition of the matrix: a kept vector was not accepted, or DS_FAIL
+                         //    (DS_ACCEPT is 0 then)
     DS_WORDS = 8
 };
 
@@ -59,13 +60,13 @@ struct DirectMat {
 
 struct DirectPlan {
     std::vector<DirectMat> mats;
-    std::vector<svd::Work> gram, tiles, tri, groups, eig, vec, lng;
+    std::vector<svd::Work> gram, tiles, tri, eig, vec, lng;
     bool spread = false;             // deal the workgroups of a group over all dies (for tests)
     long long start_ticks = START_TICKS;
     int eig_lanes = 64;              // lanes per eigenvalue in the search
     size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
     int max_nt = 1;
-    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + groups.size() + eig.size() + vec.size() + lng.size(); }
+    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
 };
 
 // Lets the kernels have more LDS than a launch gets by default; once per device.
@@ -79,7 +80,7 @@ void plan_work(DirectPlan& plan);
 struct DirectTables {
     const DirectMat* mats;
     int n_mats;
-    const svd::Work *gram, *tiles, *tri, *groups, *eig, *vec, *lng;
+    const svd::Work *gram, *tiles, *tri, *eig, *vec, *lng;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.
 void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream);

@@ -185,11 +185,12 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
     for (int p = 0; p < 16; ++p) {
         const int i = (tid >> 6) + 4 * p, j = tid & 63;
         C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
-        if (ti == tj && i == j) m.diag[ti * TILE + i] = sum[p];
         t[i][j] = sum[p];
     }
-    if (ti != tj) {
-        __syncthreads();
+    __syncthreads();
+    if (ti == tj) {
+        if (tid < TILE) m.diag[ti * TILE + tid] = t[tid][tid];
+    } else {
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
             const int i = (tid >> 6) + 4 * p, j = tid & 63;
@@ -264,13 +265,14 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // over is the hardware: vector stores write through the L1 to the L2 that the whole die shares, and the readers' loads, of
 // agent scope, do not hit in an L1.  Agent scope on the stores would send them through to memory as well.)
 // Waits: nothing guarantees that a group is resident as a whole - other work on the GPU can hold the places that its last
-// workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, a group that does not
-// come together leaves as one (Gate), and direct_tridiagonal_alone reduces the matrix of a wait that was given up.
+// workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
+// not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
 // Bound: the chain of steps.  512 rows on 64 waves: 669 us, 1.3 us per step (955 before the
 // chain of a step was shortened).
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
-// waited too long, holds for all of them, for it is only set while some are missing, and who finds it set does not start.
+// waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
+// last to start then knows that no other has done or will do anything.
 struct Gate {
     static constexpr u64 OFF = 1ull << 63;
     static __device__ inline int on_die(u64 word, int die) { return (int)(word >> (7 * die)) & 127; }
@@ -282,12 +284,16 @@ struct Gate {
         return sum;
     }
     static __device__ inline int this_die() { return (int)__builtin_amdgcn_s_getreg(20 | (31 << 11)) & 7; }
-    static __device__ inline void start(Global<u64> gate, long long ticks)
+    // True in thread 0 of the last workgroup to start, if the group does not go on.  (No time to wait at all, ticks == 0: the
+    // group gives up however fast it is.)
+    static __device__ inline bool start(Global<u64> gate, int n_wgs, long long ticks)
     {
-        // (no time to wait at all: nobody is counted, so that the group gives up however fast it is)
-        if (threadIdx.x == 0 && ticks > 0) __hip_atomic_fetch_add(gate, 1ull << (7 * this_die()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x != 0) return false;
+        if (ticks == 0) __hip_atomic_fetch_or(gate, OFF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u64 before = __hip_atomic_fetch_add(gate, 1ull << (7 * this_die()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return (before & OFF) && started(before) == n_wgs - 1;
     }
-    // True once all have started (one_die: all of them on this workgroup's die), false if the group does not start.
+    // True once all have started (one_die: all of them on this workgroup's die), false if the group does not go on.
     static __device__ inline bool pass(Global<u64> gate, int n_wgs, long long ticks, bool& one_die)
     {
         const int die = this_die();
@@ -306,6 +312,10 @@ struct Gate {
         }
     }
 };
+
+// How a workgroup's part in a reduction ends: done; a wait of a step gave up; the group did not go on, and this workgroup was
+// the last of it to start, or not.
+enum TriEnd { TRI_DONE, TRI_FAILED, TRI_LAST, TRI_LEFT };
 
 template <int C, int R, int QW>
 struct Tri {
@@ -479,8 +489,7 @@ struct Tri {
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
 
-    // false: a wait hit its bound
-    __device__ inline bool run(const DirectMat& mm, int member, int n_wgs, long long start_ticks, double2* lds)
+    __device__ inline TriEnd run(const DirectMat& mm, int member, int n_wgs, long long start_ticks, double2* lds)
     {
         const StepStore store(mm);
         const int N = store.N;
@@ -493,7 +502,7 @@ struct Tri {
         q = w >> 6;
         off = CN - N;
         slots = global(mm.xch);
-        Gate::start(global(mm.gate), start_ticks);
+        const bool last = Gate::start(global(mm.gate), n_wgs, start_ticks);
         int expo, zeros;
         const double scale = scale_of<C>(mm, off, lane, expo, zeros);
 #pragma unroll
@@ -513,7 +522,7 @@ struct Tri {
             x[c] = j >= 0 ? scale * global(mm.C)[(size_t)mm.pad * N + j] : 0.0;
             v[c] = wv[c] = 0.0;
         }
-        if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return false;
+        if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
         phases<0>(k, store);
         update<C - 1, R - 1>();
         // what is left: the last 2 x 2 block
@@ -529,7 +538,7 @@ struct Tri {
             const double d = lane_value(a[R - 1][C - 1], 63);
             if (lane == 0) store.td[2 * N - 1] = d;
         }
-        return spin_limit != 0;
+        return spin_limit != 0 ? TRI_DONE : TRI_FAILED;
     }
 };
 
@@ -640,67 +649,73 @@ __device__ inline void tri_small(const DirectMat& m, double* lds)
     }
 }
 
-// work: matrix (below 0: nothing), member of the group, workgroups of the group.
-__global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work, long long start_ticks)
+// The reduction by one workgroup that waits for nobody: the same steps on the matrix in memory, which nothing needs
+// afterwards.  Two passes over what is left of it per step: 4 ms for 200
+// rows, 42 for 512, 83 for 640.
+__device__ inline void tri_alone(const DirectMat& m, double* lds)
 {
-    __shared__ double2 lds[2 * MAX_R];
-    const Work wk = work[blockIdx.x];
-    if (wk.mat < 0) return;
-    const DirectMat& m = mats[wk.mat];
-    bool ok = true;
-    switch (m.cls) {
-        case CLS_64: tri_small<1>(m, (double*)lds); break;
-        case CLS_128: tri_small<2>(m, (double*)lds); break;
-        case CLS_256: { Tri<4, 4, 1> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
-        case CLS_512: { Tri<8, 8, 1> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
-        default: { Tri<10, 5, 2> t; ok = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
-    }
-    if (!ok && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
-}
-
-// The reduction of a matrix whose group gave a wait up, by one workgroup that waits for nobody: the same steps on the matrix
-// in memory, of which nothing is needed afterwards.  A chain of two passes over what is left of it per step: 2 ms for 200
-// rows, 22 for 512, 41 for 640, and 2 us for the launch where there is nothing to do.
-__global__ __launch_bounds__(1024) void direct_tridiagonal_alone(const DirectMat* mats, const Work* groups)
-{
-    __shared__ double v[MAX_R], p[MAX_R];
-    const DirectMat& m = mats[groups[blockIdx.x].mat];
-    if (m.st[DS_FAIL] == 0) return;
+    constexpr int C = MAX_R / 64;
+    double *const v = lds, *const p = lds + MAX_R;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), N = m.nt * TILE;
     const StepStore store(m);
     const Global<double> A = global(m.C);
     int expo, zeros;
-    const double scale = scale_of<MAX_R / 64>(m, MAX_R - N, lane, expo, zeros);
+    const double scale = scale_of<C>(m, MAX_R - N, lane, expo, zeros);
+    auto load = [&](int i, double (&row)[C]) {                   // row i, lane l: columns l, l + 64, ..; zeros past the end
+#pragma unroll
+        for (int c = 0; c < C; ++c) row[c] = 64 * c < N ? A[(size_t)i * N + lane + 64 * c] : 0.0;
+    };
     __syncthreads();
-    for (int e = tid; e < N * N; e += 1024) A[e] *= scale;
+    for (int e = tid; e < N * N; e += 256) A[e] *= scale;
     __syncthreads();
     for (int k = m.pad; k < N - 2; ++k) {
-        const Global<const double> column = A + (size_t)k * N;
-        double sq = 0.0;
-        for (int i = lane; i < N; i += 64) sq = i > k + 1 ? fma(column[i], column[i], sq) : sq;
+        double x[C], sq = 0.0;
+        load(k, x);
+#pragma unroll
+        for (int c = 0; c < C; ++c) sq = lane + 64 * c > k + 1 ? fma(x[c], x[c], sq) : sq;
         double beta, v0;
         const double sig2 = wave_sum(sq);
-        householder(column[k + 1], sig2, beta, v0);
+        householder(A[(size_t)k * N + k + 1], sig2, beta, v0);
         const double tau = householder_tau(sig2, v0);
         if (wave == 0) {
-            for (int i = lane; i < N; i += 64) store.refl[(size_t)k * N + i] = v[i] = i > k + 1 ? column[i] : i == k + 1 ? v0 : 0.0;
-            if (lane == 0) store.put(k, tau, column[k], beta);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const int i = lane + 64 * c;
+                const double vi = i > k + 1 ? x[c] : i == k + 1 ? v0 : 0.0;
+                v[i] = vi;
+                if (i < N) store.refl[(size_t)k * N + i] = vi;
+            }
+            if (lane == 0) store.put(k, tau, A[(size_t)k * N + k], beta);
         }
         __syncthreads();
-        for (int i = k + 1 + wave; i < N; i += 16) {
-            double sum = 0.0;
-            for (int j = lane; j < N; j += 64) sum = j > k ? fma(A[(size_t)i * N + j], v[j], sum) : sum;
+#pragma unroll
+        for (int c = 0; c < C; ++c) x[c] = v[lane + 64 * c];     // (0 up to k)
+        for (int i = k + 1 + wave; i < N; i += 4) {
+            double row[C], sum = 0.0;
+            load(i, row);
+#pragma unroll
+            for (int c = 0; c < C; ++c) sum = fma(row[c], x[c], sum);
             sum = wave_sum(sum);
             if (lane == 0) p[i] = tau * sum;
         }
         __syncthreads();
-        double gamma = 0.0;
-        for (int i = lane; i < N; i += 64) gamma = i > k ? fma(v[i], p[i], gamma) : gamma;
+        double w[C], gamma = 0.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = lane + 64 * c;
+            w[c] = i > k && i < N ? p[i] : 0.0;
+            gamma = fma(x[c], w[c], gamma);
+        }
         gamma = wave_sum(gamma) * (0.5 * tau);
-        for (int i = k + 1 + wave; i < N; i += 16) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) w[c] = fma(-gamma, x[c], w[c]);
+        for (int i = k + 1 + wave; i < N; i += 4) {
             const double vi = v[i], wi = fma(-gamma, vi, p[i]);
-            for (int j = lane; j < N; j += 64)
-                if (j > k) A[(size_t)i * N + j] = fma(-wi, v[j], fma(-vi, fma(-gamma, v[j], p[j]), A[(size_t)i * N + j]));
+            double row[C];
+            load(i, row);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (lane + 64 * c > k && 64 * c < N) A[(size_t)i * N + lane + 64 * c] = fma(-wi, x[c], fma(-vi, w[c], row[c]));
         }
         __syncthreads();
     }
@@ -709,8 +724,26 @@ __global__ __launch_bounds__(1024) void direct_tridiagonal_alone(const DirectMat
         store.td[2 * N - 1] = A[(size_t)(N - 1) * N + N - 1];
         m.st[DS_EXP] = expo;
         m.st[DS_ZERO_ROWS] = zeros;
-        m.st[DS_FAIL] = 0;
     }
+}
+
+// work: matrix (below 0: nothing), member of the group, workgroups of the group.
+__global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work, long long start_ticks)
+{
+    __shared__ double2 lds[2 * MAX_R];
+    const Work wk = work[blockIdx.x];
+    if (wk.mat < 0) return;
+    const DirectMat& m = mats[wk.mat];
+    TriEnd end = TRI_DONE;
+    switch (m.cls) {
+        case CLS_64: tri_small<1>(m, (double*)lds); break;
+        case CLS_128: tri_small<2>(m, (double*)lds); break;
+        case CLS_256: { Tri<4, 4, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        case CLS_512: { Tri<8, 8, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        default: { Tri<10, 5, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+    }
+    if (end == TRI_LAST) tri_alone(m, (double*)lds);
+    if (end == TRI_FAILED && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -888,7 +921,8 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
         m.report[1] = 2;
         // all of the spectrum above the floor, but for rows of A that are zero themselves; a matrix of zeros has no atoms
         const bool resolved = zeros >= r || (zeros < r && m.lam[r - 1 - zeros] > FLOOR_REL * l0);
-        m.st[DS_ACCEPT] = resolved;
+        m.st[DS_ACCEPT] = resolved && m.st[DS_FAIL] == 0;
+        m.st[DS_BROKEN] = m.st[DS_FAIL];
         atomicMax(&flags[FLAG_MAX_SWEEPS], 1);
     }
     if (tid == 255) {
@@ -951,10 +985,17 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
             fact[i / 8 * FLD + 2 * (i & 7) + 1] = x.y;
         }
     }
-    const int kept = min(*m.count, m.capacity), at_lam = m.idx[slot];
-    const KeptApart apart(m.lam[at_lam], slot > 0 ? m.lam[m.idx[slot - 1]] : -1.0,
-                          slot + 1 < kept ? m.lam[m.idx[slot + 1]] : -1.0, 4.0 / (double)(1 << LAM_BITS));
-    double lam = m.lam[at_lam];
+    // its eigenvalue and those of the kept atoms beside it, all three on their way at once (an entry that is not there is
+    // not used, whatever it is)
+    double own[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int at = m.idx[min(max(slot + k - 1, 0), m.capacity - 1)];
+        own[k] = m.lam[min(max(at, 0), n - 1)];
+    }
+    double lam = own[1];
+    const KeptApart apart(lam, slot > 0 ? own[0] : -1.0, slot + 1 < min(*m.count, m.capacity) ? own[2] : -1.0,
+                          4.0 / (double)(1 << LAM_BITS));
     const double good = 1e-14 * m.lam[0];
     // what wave 0 needs of T: its lane's entries
     constexpr int PER = VMAX / 64;
@@ -1089,7 +1130,7 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
                 }
             }
             const double norm2 = wave_sum(sq), res = fabs(gamma) / sqrt(norm2);    // |T x - lam x| / |x|
-            weight = wave_sum(weight) / norm2;
+            weight = wave_sum(weight) * reciprocal(norm2);
             lam += gamma / norm2;                                // Rayleigh quotient
             // over: the residual is small enough, or it never will be (the eigenvalue was not separated from that of
             // another kept atom, or the factorisation broke down)
@@ -1465,7 +1506,6 @@ void plan_work(DirectPlan& plan)
         for (int x = 1; x < 8; ++x)
             if (load[x] < load[best]) best = x;
         for (int g = 0; g < wgs; ++g) die[plan.spread ? (best + g) % 8 : best].push_back(Work{j, g, wgs, 0});
-        if (wgs > 1) plan.groups.push_back(Work{j, 0, 0, 0});
         load[best] += (long long)m.r * wgs;
     }
     size_t most = 0;
@@ -1481,7 +1521,6 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
     direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
-    if (!plan.groups.empty()) direct_tridiagonal_alone<<<grid(plan.groups), 1024, 0, stream>>>(t.mats, t.groups);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
