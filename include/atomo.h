@@ -196,7 +196,9 @@ int atomo_create(atomo_ctx** out, int device);
 int atomo_destroy(atomo_ctx* ctx);
 
 /* Makes sure the workspace holds at least `bytes`; atomo_svd_workspace_bytes /
- * atomo_entrywise_workspace_bytes say how much a call will need (host-side arithmetic only). */
+ * atomo_entrywise_workspace_bytes say how much a call will need (host-side arithmetic only).  An SVD encode
+ * that cannot get that much does without the direct solution, which takes up to twice what the iteration does;
+ * atomo_reserve makes it try again. */
 int atomo_reserve(atomo_ctx* ctx, size_t bytes);
 int atomo_svd_workspace_bytes(const atomo_mat* mats /*host*/, int n_mats, size_t* bytes /*host*/);
 int atomo_entrywise_workspace_bytes(int64_t n, size_t* bytes /*host*/);

@@ -69,6 +69,7 @@ struct atomo_ctx {
     int device = 0;
     void* ws = nullptr;          // device workspace
     size_t ws_bytes = 0;
+    size_t ws_refused = SIZE_MAX;    // smallest workspace with the direct encode's part that could not be had (atomo_reserve forgets it)
     int32_t* d_flags = nullptr;  // [FLAG_COUNT] device
     int32_t* h_flags = nullptr;  // pinned readback buffer
     int last_hip = 0;

@@ -20,6 +20,7 @@ int ensure_workspace(atomo_ctx* ctx, size_t bytes)
     size_t want = align_up(bytes + bytes / 8, (size_t)1 << 20);
     hipError_t e = hipMalloc(&ctx->ws, want);
     if (e != hipSuccess) {
+        (void)hipGetLastError();              // (reported by the status alone: a later call is not to find it)
         ctx->last_hip = (int)e;
         ctx->ws = nullptr;
         return ATOMO_ENOMEM;
@@ -193,6 +194,7 @@ int atomo_reserve(atomo_ctx* ctx, size_t bytes)
     if (!ctx) return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
+    ctx->ws_refused = SIZE_MAX;
     return ensure_workspace(ctx, bytes);
 }
 

@@ -1019,6 +1019,7 @@ struct Plan {
     thin::ThinPlan thin;             // the matrices of at most THIN_R vectors
     bool own_update = false;         // the two-sided update runs as launches of its own (see SPLIT_TWO_SIDED)
     size_t bytes = 0;
+    size_t hot_bytes = 0;            // of them, what work items may point into (HOT_UNIT): all but the direct encode's
     size_t n_work() const
     {
         return prep.size() + rowgram[0].size() + rowgram[1].size() + fullgram.size() + tiles.size() + apply.size() +
@@ -1090,8 +1091,6 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
             d.sigma_out = m.sigma_out; d.p_out = m.p_out; d.stream_id = m.stream_id;
             d.index = j;
             d.alone = route[j] == ROUTE_DIRECT;
-            direct::plan_matrix(carve, d);
-            m.accepted = d.st + direct::DS_ACCEPT;
             if (d.alone) {
                 m.skip = 1;
                 continue;
@@ -1222,6 +1221,11 @@ void build_plan(const atomo_mat* mats, int n_mats, const atomo_svd_msg* msgs, fl
         std::stable_sort(list.begin(), list.end(), [&](const Work& a, const Work& b) {
             return plan.mats[a.mat].rows_alloc * (a.c >= 0 ? 2 : 1) > plan.mats[b.mat].rows_alloc * (b.c >= 0 ? 2 : 1);
         });
+    plan.hot_bytes = carve.off;
+    for (direct::DirectMat& d : plan.direct.mats) {
+        direct::plan_matrix(carve, d);
+        plan.mats[d.index].accepted = d.st + direct::DS_ACCEPT;
+    }
     direct::plan_work(plan.direct);
     thin::plan_work(plan.thin);
     plan.bytes = carve.off;
@@ -1370,15 +1374,29 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const uint64_t* stream_ids = opt ? opt->stream_ids : nullptr;
     Plan plan;
     int rc;
-    // (laid out in the workspace there is, and again if it turns out too small)
+    // (laid out in the workspace there is, and again if it turns out too small; where there is no memory for the direct
+    // encode, which takes up to twice what the iteration does, everything iterates)
     for (;;) {
         plan = Plan();
         plan.direct.spread = ctx->direct_spread;
         plan.direct.start_ticks = ctx->direct_start_ticks >= 0 ? ctx->direct_start_ticks : direct::START_TICKS;
         build_plan(mats, n_mats, msgs, sigma_out, p_out, stream_base, stream_ids, route.data(), ctx->ws, plan);
-        if (plan.bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL; // (the work items address the workspace in 32 bits of 16-byte units)
+        if (plan.hot_bytes >= (HOT_UNIT << 32)) return ATOMO_EINVAL; // (the work items address the workspace in 32 bits of 16-byte units)
         if (ctx->ws && plan.bytes <= ctx->ws_bytes) break;
-        if ((rc = ensure_workspace(ctx, plan.bytes)) != ATOMO_OK) return rc;
+        rc = plan.bytes >= ctx->ws_refused && !plan.direct.mats.empty() ? ATOMO_ENOMEM : ensure_workspace(ctx, plan.bytes);
+        if (rc == ATOMO_ENOMEM && !plan.direct.mats.empty()) {
+            ctx->ws_refused = std::min(ctx->ws_refused, plan.bytes);
+            std::fill(route.begin(), route.end(), ROUTE_ITERATE);
+            limit_gs = limit_ds = max_sweeps;
+            ask_from = 0;
+            if (hint) {
+                hint->route = route;
+                hint->passed.assign(n_mats, 0);
+                hint->limit_gs = hint->limit_ds = max_sweeps;
+            }
+            continue;
+        }
+        if (rc != ATOMO_OK) return rc;
     }
     for (int j = 0; j < n_mats; ++j) {
         plan.mats[j].report = ctx->d_report + 2 * j;

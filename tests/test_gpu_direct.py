@@ -299,3 +299,21 @@ def test_a_matrix_that_falls_short_with_nothing_behind_it_still_has_an_unbiased_
     assert np.abs(rows[kept] - A[kept] * scale[:, None]).max() <= 1e-5 * np.abs(rows).max()
     binding.atomo_encode_svd(c, [dev(G)], 20.0, 3, 8, msgs=msg, adaptive=1)
     assert c.status()[0] == 0                                    # the next call has the iteration
+
+
+def test_a_set_whose_iteration_fits_the_address_range_is_accepted_whatever_the_direct_encode_takes():
+    # work items of the iteration address 64 GiB of workspace; the direct encode's part (another 44 GB here) is not among that
+    n, shape = 2800, (640, 640)
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GB of free device memory")
+    c = binding.Context(0)
+    G = dev(inputs.low_rank_plus_noise(np.random.default_rng(0), 640, 640, [1.0, 0.5], 0.02))
+    msgs = [binding.alloc_svd_message(*shape, 8, "cuda") for _ in range(n)]
+    binding.atomo_encode_svd(c, [G] * n, 2.0, 1, msgs=msgs, stream_ids=[5 + j % 7 for j in range(n)])
+    assert c.status()[0] == 0
+    one = binding.Context(0)
+    for j in (0, 1, 1150, n - 1):
+        want = binding.atomo_encode_svd(one, [G], 2.0, 1, stream_ids=[5 + j % 7])[0].to_host()
+        got = msgs[j].to_host()
+        assert one.status()[0] == 0 and all(np.array_equal(want[k], got[k]) for k in ("idx", "w", "U", "V"))
+    c.close()
