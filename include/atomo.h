@@ -97,7 +97,7 @@ typedef struct atomo_ew_msg {
     int64_t n;                       /* length of the encoded gradient, 0 < n < 2^32                 */
     int64_t capacity;                /* room for this many pairs                                     */
     int64_t* count;                  /* [1]  number of pairs kept (may exceed capacity: see status)  */
-    uint32_t* idx;                   /* [capacity] kept coordinates, ascending                       */
+    uint32_t* idx;                   /* [capacity] kept coordinates, ascending: decoding searches them */
     float* val;                      /* [capacity] g_i / p_i                                         */
 } atomo_ew_msg;
 
@@ -204,7 +204,8 @@ int atomo_svd_workspace_bytes(const atomo_mat* mats /*host*/, int n_mats, size_t
 int atomo_entrywise_workspace_bytes(int64_t n, size_t* bytes /*host*/);
 
 /* Waits for `stream`, then reports and clears what the GPU latched since the last call:
- * ATOMO_OK, ATOMO_ECAPACITY, ATOMO_ENOCONV or ATOMO_EHIP.  If sweeps is not NULL it receives the
+ * ATOMO_OK, ATOMO_ECAPACITY, ATOMO_ENOCONV, ATOMO_EINVAL (an entry-wise or l_q message whose coordinates do not ascend
+ * was decoded: the output is not its sum) or ATOMO_EHIP.  If sweeps is not NULL it receives the
  * largest number of Jacobi sweeps any matrix of the last atomo_encode_svd took. */
 int atomo_status(atomo_ctx* ctx, void* stream, int32_t* sweeps /*host, optional*/);
 int atomo_last_hip_error(const atomo_ctx* ctx);
@@ -297,7 +298,8 @@ int atomo_encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uin
  *   kind = ATOMO_KIND_ENTRYWISE: msgs is a HOST array of n_msgs atomo_ew_msg with equal n;
  *                                out is the dense vector of n floats (ld is ignored).
  *   kind = ATOMO_KIND_LQ:        msgs is a HOST array of n_msgs atomo_lq_msg with equal n; out as above.
- * A message whose count exceeds its capacity contributes its first `capacity` atoms.
+ * A message whose count exceeds its capacity contributes its first `capacity` atoms.  The coordinates of
+ * an entry-wise or l_q message have to ascend, as encoders write them; others are reported by atomo_status.
  * The sum is formed in a fixed order (entry-wise and l_q messages one after the other, in the order
  * given), so the same messages decode to the same bits in every run.
  */

@@ -18,7 +18,7 @@ namespace atomo {
 // ---------------------------------------------------------------------------------------------
 
 // Device-side latched flags (int32 each).
-enum { FLAG_CAPACITY = 0, FLAG_NOCONV = 1, FLAG_MAX_SWEEPS = 2, FLAG_EIG_VISITS = 3, FLAG_EIG_INNER = 4, FLAG_DS_UPDATE_UNITS = 5, FLAG_COUNT = 8 };
+enum { FLAG_CAPACITY = 0, FLAG_NOCONV = 1, FLAG_MAX_SWEEPS = 2, FLAG_EIG_VISITS = 3, FLAG_EIG_INNER = 4, FLAG_DS_UPDATE_UNITS = 5, FLAG_ORDER = 6, FLAG_COUNT = 8 };
 
 // How an SVD encode goes about a matrix: Jacobi iteration; direct encode with the iteration behind it for what that leaves
 // over; direct encode alone.

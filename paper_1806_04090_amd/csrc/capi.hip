@@ -223,6 +223,7 @@ int atomo_status(atomo_ctx* ctx, void* stream, int32_t* sweeps)
     if (sweeps) *sweeps = ctx->h_flags[FLAG_MAX_SWEEPS];
     if (ctx->h_flags[FLAG_CAPACITY]) return ATOMO_ECAPACITY;
     if (ctx->h_flags[FLAG_NOCONV]) return ATOMO_ENOCONV;
+    if (ctx->h_flags[FLAG_ORDER]) return ATOMO_EINVAL;
     return ATOMO_OK;
 }
 

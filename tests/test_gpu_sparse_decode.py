@@ -59,3 +59,34 @@ def test_lq_messages(n, ks):
         want[idx] += np.where(neg, -1, 1).astype(np.float32) * (np.float32(0.25) * norm)
     got = binding.atomo_decode(ctx(), msgs, scale=0.25).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n,k", [(3, 2), (5000, 300), (70_001, 70_001), (20_000_003, 400_000)])
+@pytest.mark.parametrize("beside", [0, 3, 17])                          # messages in order that are decoded with it
+@pytest.mark.parametrize("lq", [False, True])
+def test_coordinates_that_do_not_ascend_are_reported(n, k, beside, lq):
+    rng = np.random.default_rng(n + beside)
+
+    def message(words):
+        m = (binding.alloc_lq_message if lq else binding.alloc_entrywise_message)(n, words.size, "cuda")
+        m.count.fill_(words.size)
+        if lq:                                                          # (the sign bit is no part of the coordinate)
+            words = words | ((rng.random(words.size) < 0.5).astype(np.uint32) << 31)
+            m.norm.fill_(1.0)
+        m.idx[:] = dev(words.astype(np.uint32).view(np.int32))
+        return m
+
+    good = np.sort(rng.choice(n, size=k, replace=False)).astype(np.uint32)
+    others = [message(good[: max(1, k // 50)]) for _ in range(beside)]
+    assert ctx().status()[0] == 0
+    binding.atomo_decode(ctx(), others + [message(good)])
+    assert ctx().status()[0] == 0
+    for where in (0, (k - 1) // 2, k - 2):
+        swapped = good.copy()
+        swapped[[where, where + 1]] = swapped[[where + 1, where]]
+        twice = good.copy()
+        twice[where + 1] = twice[where]
+        for bad in (swapped, twice, np.roll(good, k // 2)):
+            binding.atomo_decode(ctx(), others + [message(bad)])
+            assert ctx().status()[0] == binding.ATOMO_EINVAL
+    assert ctx().status()[0] == 0                                       # (reported once)
