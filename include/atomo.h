@@ -60,7 +60,7 @@ typedef enum atomo_status_code {
     ATOMO_ECAPACITY = -2,  /* (atomo_status only) more atoms were kept than a message could hold    */
     ATOMO_ENOCONV = -3,    /* (atomo_status only) the Jacobi SVD stopped at the sweep limit         */
     ATOMO_EHIP = -4,       /* a HIP runtime call failed; atomo_last_hip_error gives its code        */
-    ATOMO_ENOMEM = -5,     /* the workspace could not be allocated                                  */
+    ATOMO_ENOMEM = -5,     /* the workspace, or host memory for the plan of a call, could not be allocated */
     ATOMO_ETOOLARGE = -6   /* atomo_encode_entrywise_noalloc: n exceeds what its fixed scratch holds */
 } atomo_status_code;
 

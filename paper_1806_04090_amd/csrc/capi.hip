@@ -123,6 +123,17 @@ struct DeviceGuard {
     }
 };
 
+// The planners behind the entry points use the standard containers: no exception of theirs leaves the library.
+template <typename F>
+int guarded(F&& call)
+{
+    try {
+        return call();
+    } catch (...) {                           // (std::bad_alloc, std::length_error)
+        return ATOMO_ENOMEM;
+    }
+}
+
 bool bad_budget(double s) { return !(s > 0.0) || std::isnan(s) || std::isinf(s); }
 
 }  // namespace
@@ -201,7 +212,7 @@ int atomo_reserve(atomo_ctx* ctx, size_t bytes)
 int atomo_svd_workspace_bytes(const atomo_mat* mats, int n_mats, size_t* bytes)
 {
     if (!mats || n_mats <= 0 || !bytes) return ATOMO_EINVAL;
-    return svd_workspace_bytes(mats, n_mats, bytes);
+    return guarded([&] { return svd_workspace_bytes(mats, n_mats, bytes); });
 }
 
 int atomo_entrywise_workspace_bytes(int64_t n, size_t* bytes)
@@ -232,7 +243,7 @@ int atomo_svd_sweeps(atomo_ctx* ctx, void* stream, int32_t* sweeps, int32_t* ref
     if (!ctx || !sweeps || n_mats <= 0) return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return svd_sweeps(ctx, (hipStream_t)stream, sweeps, refreshes, n_mats);
+    return guarded([&] { return svd_sweeps(ctx, (hipStream_t)stream, sweeps, refreshes, n_mats); });
 }
 
 int atomo_profile_enable(atomo_ctx* ctx, int enable)
@@ -347,7 +358,7 @@ const char* atomo_strerror(int status)
         case ATOMO_ECAPACITY: return "a message kept more atoms than its capacity";
         case ATOMO_ENOCONV: return "Jacobi SVD reached the sweep limit";
         case ATOMO_EHIP: return "HIP runtime error";
-        case ATOMO_ENOMEM: return "out of device memory";
+        case ATOMO_ENOMEM: return "out of memory";
         case ATOMO_ETOOLARGE: return "input longer than the fixed scratch of the allocation-free entry point holds";
         default: return "unknown status";
     }
@@ -367,7 +378,7 @@ int atomo_probabilities(atomo_ctx* ctx, const float* lambda, const int64_t* offs
     if (!lambda || !p) return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return probabilities(ctx, lambda, offsets, n_seg, s, p, (hipStream_t)stream);
+    return guarded([&] { return probabilities(ctx, lambda, offsets, n_seg, s, p, (hipStream_t)stream); });
 }
 
 int atomo_encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint64_t seed, uint64_t stream_base,
@@ -389,7 +400,9 @@ int atomo_encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s
         return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return encode_svd(ctx, mats, n_mats, s, seed, stream_base, opt, msgs, sigma_out, p_out, (hipStream_t)stream);
+    return guarded([&] {
+        return encode_svd(ctx, mats, n_mats, s, seed, stream_base, opt, msgs, sigma_out, p_out, (hipStream_t)stream);
+    });
 }
 
 int atomo_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t seed, uint64_t stream_id,
@@ -400,7 +413,7 @@ int atomo_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t se
     if (!msg->count || !msg->idx || !msg->val) return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return encode_entrywise(ctx, g, s, seed, stream_id, msg, p_out, (hipStream_t)stream);
+    return guarded([&] { return encode_entrywise(ctx, g, s, seed, stream_id, msg, p_out, (hipStream_t)stream); });
 }
 
 int atomo_encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t stream_id,
@@ -411,7 +424,7 @@ int atomo_encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uin
     if (!msg->count || !msg->idx || !msg->norm) return ATOMO_EINVAL;
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return encode_lq(ctx, g, q, seed, stream_id, msg, p_out, (hipStream_t)stream);
+    return guarded([&] { return encode_lq(ctx, g, q, seed, stream_id, msg, p_out, (hipStream_t)stream); });
 }
 
 static int svd_batch(atomo_ctx* ctx, const atomo_svd_msg* msgs, const int32_t* first, int n_out, float scale,
@@ -432,7 +445,7 @@ static int svd_batch(atomo_ctx* ctx, const atomo_svd_msg* msgs, const int32_t* f
     }
     DeviceGuard guard(ctx);
     if (!guard.ok) return ATOMO_EHIP;
-    return decode_svd_batch(ctx, msgs, first, n_out, scale, outs, lds, accumulate, (hipStream_t)stream);
+    return guarded([&] { return decode_svd_batch(ctx, msgs, first, n_out, scale, outs, lds, accumulate, (hipStream_t)stream); });
 }
 
 int atomo_decode_svd_batch(atomo_ctx* ctx, const atomo_svd_msg* msgs, const int32_t* first, int n_out, float scale,
@@ -465,7 +478,7 @@ int atomo_decode(atomo_ctx* ctx, int kind, const void* msgs, int n_msgs, float s
         }
         DeviceGuard guard(ctx);
         if (!guard.ok) return ATOMO_EHIP;
-        return decode_entrywise(ctx, m, n_msgs, scale, out, (hipStream_t)stream);
+        return guarded([&] { return decode_entrywise(ctx, m, n_msgs, scale, out, (hipStream_t)stream); });
     }
     if (kind == ATOMO_KIND_LQ) {
         const atomo_lq_msg* m = (const atomo_lq_msg*)msgs;
@@ -475,7 +488,7 @@ int atomo_decode(atomo_ctx* ctx, int kind, const void* msgs, int n_msgs, float s
         }
         DeviceGuard guard(ctx);
         if (!guard.ok) return ATOMO_EHIP;
-        return decode_lq(ctx, m, n_msgs, scale, out, (hipStream_t)stream);
+        return guarded([&] { return decode_lq(ctx, m, n_msgs, scale, out, (hipStream_t)stream); });
     }
     return ATOMO_EINVAL;
 }

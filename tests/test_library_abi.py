@@ -3,6 +3,8 @@ declare, and the host-side argument validation answers without touching a GPU.""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -102,3 +104,24 @@ def test_struct_layouts_match_the_header(tmp_path):
         declared = [part.replace("*", " ").split()[-1] for stmt in body.split(";") if stmt.strip()
                     for part in stmt.split(",")]
         assert declared == [name for name, _ in st._fields_], st.__name__
+
+
+def test_a_call_that_runs_out_of_host_memory_returns_a_status():
+    # the planners allocate; nothing may be thrown through the C interface
+    code = f"""
+import ctypes as C, resource
+L = C.CDLL({binding.LIB_PATH!r})
+n = 2_000_000
+class Mat(C.Structure):
+    _fields_ = [("rows", C.c_int32), ("cols", C.c_int32), ("ld", C.c_int64), ("data", C.c_void_p)]
+mats = (Mat * n)()
+for j in range(n):
+    mats[j].rows, mats[j].cols = 64, 576
+size = C.c_size_t(0)
+used = [int(x.split()[1]) for x in open("/proc/self/status") if x.startswith("VmSize")][0] * 1024
+resource.setrlimit(resource.RLIMIT_AS, (used + (200 << 20), resource.RLIM_INFINITY))
+assert L.atomo_svd_workspace_bytes(mats, n, C.byref(size)) == {binding.ATOMO_ENOMEM}
+assert L.atomo_svd_workspace_bytes(mats, 10, C.byref(size)) == 0 and size.value > 0
+"""
+    done = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert done.returncode == 0, done.stderr
