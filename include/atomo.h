@@ -25,8 +25,8 @@
  *    Descriptor tables travel to the device through a ring of eight pinned
  *    staging buffers owned by the context: a call that needs a buffer whose
  *    previous copy (eight uploads ago) has not been executed yet waits for
- *    that copy, and for nothing else.  The SVD encoder and the SVD decoder
- *    each keep the four sets of tables used last on the device, and skip the
+ *    that copy, and for nothing else.  The SVD encoder, the SVD decoder and
+ *    atomo_probabilities each keep the four sets of tables used last on the device, and skip the
  *    upload when a call, on the same stream, describes exactly the buffers of
  *    one of them (a training loop, or one that takes a few sets of buffers in
  *    turn): the tables hold addresses and sizes, never data.
@@ -116,12 +116,12 @@ typedef struct atomo_lq_msg {
  * Matrices of 33 .. 640 vectors on the shorter side, with a budget s of at most 32 atoms, are first solved directly: the
  * Gram matrix in double precision, its eigenvalues, and singular vectors of the kept atoms only.  The Jacobi iteration
  * that the options below describe takes over for a matrix with singular values at or under twice the fp32 floor (3.8e-6 of the
- * largest; gradients of low rank, other than through rows that are zero) or with kept atoms whose singular values
- * agree to eight digits; for every other size and budget; and for every matrix of a call that sets stop_cosine,
- * max_inner_sweeps, inner_reduction, full_period or block_order, or a max_sweeps under the default. */
+ * largest; gradients of low rank, other than through rows that are zero) or with kept atoms whose vectors it cannot
+ * separate (singular values that agree to eight digits, fewer digits for values far below the largest); for every other
+ * size and budget; and for every matrix of a call that sets stop_cosine, max_inner_sweeps, inner_reduction, full_period or
+ * block_order, or a max_sweeps under the default. */
 typedef struct atomo_svd_options {
-    int32_t max_sweeps;              /* default 16 (0 = default).  Noise-dominated gradients take 8 to 10 sweeps   */
-                                     /* (6 or 7 with 481 or more vectors on the shorter side, see block_order),    */
+    int32_t max_sweeps;              /* default 16 (0 = default).  Noise-dominated gradients take 5 to 7 sweeps,   */
                                      /* exactly low-rank ones (rank 128 in 600 x 700) 12, singular values graded   */
                                      /* over two decades 11, three 14, five 16; a matrix half of whose rows are    */
                                      /* copies of the other half 16.  Every sweep allowed costs launches even when */
@@ -129,11 +129,9 @@ typedef struct atomo_svd_options {
                                      /* matrices).  Hitting the limit reports ATOMO_ENOCONV; the message is then   */
                                      /* still an exact decomposition of the input, with atoms that are not yet     */
                                      /* orthogonal to the tolerance.                                               */
-                                     /* Matrices with min(rows, cols) <= 32 (the [x*y/2, 2*k*k] reshape of Section */
-                                     /* 6) solve their whole r x r problem per pass over the data: they get        */
-                                     /* 1 + ceil(max_sweeps / 8) passes, at least 2 and at most 8 (three by        */
-                                     /* default; one or two rotate and the last confirms), and their               */
-                                     /* atomo_svd_sweeps count is the number of passes that rotated                */
+                                     /* No effect on matrices with min(rows, cols) <= 32 (the [x*y/2, 2*k*k]        */
+                                     /* reshape of Section 6): two passes over the data, the r x r problem solved  */
+                                     /* in double precision by one workgroup                                       */
     float   stop_cosine;             /* default 1e-4 (0 = default): stop after the first sweep whose largest */
                                      /* |<a_i,a_j>| / (|a_i||a_j|), measured before rotating, is below; matrices   */
                                      /* that iterate on their Gram matrix stop once the Gram matrix formed afresh  */
@@ -188,8 +186,8 @@ typedef struct atomo_svd_options {
 /* -------- context ------------------------------------------------------------------------------ */
 
 /* Creates a context on HIP device `device`.  *out is set on success.
- * A context owns one workspace and (for the SVD encoder) one helper stream that is forked from and joined
- * back into the caller's stream inside every call: calls that share a context must be issued from one host
+ * A context owns one workspace and (for the SVD encoder) three helper streams that are forked from and joined
+ * back into the caller's stream inside a call that uses them: calls that share a context must be issued from one host
  * thread at a time and onto one stream, or onto streams the caller has ordered among themselves; use one
  * context per concurrent stream. */
 int atomo_create(atomo_ctx** out, int device);
@@ -214,7 +212,7 @@ int atomo_last_hip_error(const atomo_ctx* ctx);
  * atomo_encode_svd took into sweeps[0 .. n_mats) (HOST) and, if refreshes is not NULL, how many
  * times the full Gram matrix of the matrix was formed from the data (matrices of 33 .. 480 rows
  * iterate directly on the data: 0 below 225 rows, from there on the number of whole-matrix
- * convergence checks near the end).  A matrix that was solved directly counts as one sweep and two passes over
+ * convergence checks near the end).  A matrix that was solved directly, or has at most 32 rows or columns, counts as one sweep and two passes over
  * the data (the Gram matrix, and the vectors of the longer side).  n_mats must match that call; the counts stay readable until the
  * next atomo_encode_svd on the context. */
 int atomo_svd_sweeps(atomo_ctx* ctx, void* stream, int32_t* sweeps /*host*/, int32_t* refreshes /*host, optional*/,

@@ -1,8 +1,14 @@
-// Spectral-ATOMO encoder (Section 5 of arXiv 1806.04090): batched blocked one-sided Jacobi SVD on
-// fp32 MFMA, followed by Algorithm 1 on the singular values, Philox Bernoulli sampling and packing
-// of the kept singular triplets.
+// Spectral-ATOMO encoder (Section 5 of arXiv 1806.04090): the host side of every SVD encode, and the kernels of the batched
+// blocked one-sided Jacobi SVD on fp32 MFMA, followed by Algorithm 1 on the singular values, Philox Bernoulli sampling and
+// packing of the kept singular triplets.
 //
-// Layout.  For a matrix G (rows x cols) let r = min(rows, cols) and M = max(rows, cols).  The r
+// Which matrix goes where (r = vectors on the shorter side): r <= 32 to svd_thin.hip; 33 .. 640 first to svd_direct.hip,
+// unless the budget is above 32 atoms or the caller says how the iteration is to run; the iteration of this file takes what the
+// direct encode does not accept, and all others.  With `adaptive` the route of a matrix follows what the call before did
+// with it (ROUTE_*).  Thin matrices, directly solved ones with nothing behind them, and the groups of the iteration run side by
+// side on the caller's stream and three streams of the context.
+//
+// Layout of the iteration.  For a matrix G (rows x cols) let r = min(rows, cols) and M = max(rows, cols).  The r
 // vectors of length M that get orthogonalised (the rows of G, or of G^T when rows > cols) are the
 // rows of a workspace matrix W = [A | T]: A (r x M) starts as those vectors (times a power of two
 // that brings the largest entry into [1, 2)), T (r x r) starts as the identity.  Every rotation is

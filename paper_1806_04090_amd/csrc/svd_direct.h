@@ -51,7 +51,7 @@ struct DirectMat {
     float* V;
     float* sigma_out;                // may be null
     float* p_out;                    // may be null
-    float* inv;                      // [capacity] 1 / sigma of the kept atom
+    float* weight;                   // [capacity] weight sigma / p of the kept atom (folded messages: it goes into U)
     unsigned long long stream_id;
     int* report;                     // [2] sweeps (1: solved directly) and passes over the data
     int index;                       // which matrix of the call this is

@@ -939,7 +939,7 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
                 const float weight = key[i] / p;
                 m.idx[pos] = i;
                 if (m.w) m.w[pos] = weight;
-                m.inv[pos] = weight;
+                m.weight[pos] = weight;
             }
             ++pos;
         }
@@ -1217,7 +1217,7 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
     double sq = 0.0;
     for (int w = 0; w < nw; ++w) sq += red[w];
     const double inv = 1.0 / sqrt(sq);
-    const float fold = m.w || m.transposed ? 1.0f : m.inv[slot];  // folded message: the weight goes into U
+    const float fold = m.w || m.transposed ? 1.0f : m.weight[slot];  // folded message: the weight goes into U
     const Global<float> out = global(m.transposed ? m.V + (size_t)slot * m.cols : m.U + (size_t)slot * m.rows);
     const Global<double> keep = global(m.u) + (size_t)slot * n;
     if (c0 >= pad && c0 < N) {
@@ -1417,7 +1417,7 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
             }
             const int i = m.idx[s0 + k];
             const double sigma = ldexp(sqrt(m.lam[i]), m.st[DS_EXP] / 2);
-            const float fold = m.w || !m.transposed ? 1.0f : m.inv[s0 + k];
+            const float fold = m.w || !m.transposed ? 1.0f : m.weight[s0 + k];
             out[(size_t)(s0 + k) * m.M + p0 + p] = (float)(sum / sigma) * fold;
         }
     }
@@ -1464,7 +1464,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.xch = carve.take<u64>((size_t)4 * 64 * CLS_CHUNKS[m.cls]);
     m.gate = carve.take<u64>(1);
     m.st = carve.take<int>(DS_WORDS);
-    m.inv = carve.take<float>(m.capacity);
+    m.weight = carve.take<float>(m.capacity);
 }
 
 void plan_work(DirectPlan& plan)

@@ -3,11 +3,12 @@
 //
 // Three launches and two passes over the data:
 //     thin_gram  : partial r x r Gram matrices of runs of positions, in double precision on the matrix cores
-//     thin_solve : one workgroup per matrix sums them, diagonalises the sum (two-sided Jacobi, all in LDS), takes the
-//                  singular values, runs Algorithm 1, draws the mask and writes the message but for the long vectors
+//     thin_solve : one workgroup per matrix sums them, takes the singular values of the sum (tridiagonal form and Sturm counts,
+//                  or, where that is not accepted, two-sided Jacobi, all in LDS), runs Algorithm 1, draws the mask and
+//                  writes the message but for the long vectors
 //     thin_long  : the long vectors of the kept atoms, A^T u / sigma
-// Products of two floats are exact in double precision: lambda has an absolute error of about 1e-15 lambda_1, and Jacobi's
-// vectors are orthogonal to rounding whatever the spectrum looks like.
+// Products of two floats are exact in double precision: lambda has an absolute error of about 1e-15 lambda_1.  The vectors of
+// the direct solution are orthogonal as KeptApart asks, Jacobi's to rounding whatever the spectrum looks like.
 #include <algorithm>
 #include <vector>
 
@@ -768,7 +769,7 @@ __global__ __launch_bounds__(LONG_POS) void thin_long(const ThinMat* mats, const
 
 void plan_matrix(Carver& carve, ThinMat& m)
 {
-    // chunks of 2048 positions, larger only to keep a matrix under 128 of them; from the shape alone, so that the sums do not
+    // chunks of GRAM_CHUNK positions, larger only to keep a matrix under 128 of them; from the shape alone, so that the sums do not
     // depend on what else is in the call
     const long long runs = ((long long)m.M + GRAM_CHUNK - 1) / GRAM_CHUNK;
     m.chunk = (int)(GRAM_CHUNK * ((runs + MAX_CHUNKS - 1) / MAX_CHUNKS));
