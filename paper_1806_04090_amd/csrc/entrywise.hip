@@ -397,8 +397,8 @@ __device__ inline bool last_workgroup(unsigned int* ticket, unsigned int self, u
     return last_sh != 0;
 }
 
-// ew_hist<0> whose last workgroup solves level 0 at once: one launch and one chain of dependent loads less than with
-// ew_solve<0> behind it.
+// Level 0: the histogram of all elements, and its last workgroup solves the level at once (one launch and one chain of
+// dependent loads less than with a kernel for it).
 __global__ __launch_bounds__(1024) void ew_hist0_solve0(const float* __restrict__ g, long long n, EwState* st, double s)
 {
     __shared__ unsigned long long acc[4 * NBUCKET];
