@@ -1417,15 +1417,18 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const size_t at_work = align_up(at_thin + plan.thin.mats.size() * sizeof(thin::ThinMat), 256);
     std::vector<char>& tables = ctx->table_scratch;
     tables.assign(at_work + plan.n_work() * sizeof(Work), 0);
-    memcpy(tables.data(), plan.mats.data(), plan.mats.size() * sizeof(SvdMat));
-    memcpy(tables.data() + at_direct, plan.direct.mats.data(), plan.direct.mats.size() * sizeof(direct::DirectMat));
-    memcpy(tables.data() + at_thin, plan.thin.mats.data(), plan.thin.mats.size() * sizeof(thin::ThinMat));
+    auto put = [&](size_t at, const auto& list) {                // (an empty list may have no address)
+        if (!list.empty()) memcpy(tables.data() + at, list.data(), list.size() * sizeof(list[0]));
+    };
+    put(0, plan.mats);
+    put(at_direct, plan.direct.mats);
+    put(at_thin, plan.thin.mats);
     struct Placed { const Work** where; size_t at; };
     std::vector<Placed> placed;
     size_t n_placed = 0;
     auto place = [&](const std::vector<Work>& list, const Work*& where) {
         placed.push_back(Placed{&where, n_placed});
-        memcpy(tables.data() + at_work + n_placed * sizeof(Work), list.data(), list.size() * sizeof(Work));
+        put(at_work + n_placed * sizeof(Work), list);
         n_placed += list.size();
     };
     const Work *w_prep, *w_rowgram[2], *w_fullgram, *w_tiles, *w_apply, *w_eig_gs, *w_eig_ds[2], *w_twosided, *w_strips, *w_ds_full,
