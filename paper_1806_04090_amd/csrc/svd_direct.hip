@@ -252,7 +252,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
     return ldexp(1.0, -e);
 }
 
-// Groups of 16 or 32 workgroups (matrices of more than 128 rows): every wave owns R rows of the matrix in registers (lane l:
+// Groups of 16 or 32 workgroups (matrices of more than 128 rows, until 128 are left): every wave owns R rows of the matrix in registers (lane l:
 // columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all waves
 // the same bits; one exchange per step: every wave publishes the entries of p of its rows, the owner of row k + 1
 // that row (column k + 1 of the matrix before the step), and every workgroup reads all of both, a quarter per wave.
@@ -267,8 +267,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // Waits: nothing guarantees that a group is resident as a whole - other work on the GPU can hold the places that its last
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
-// Bound: the chain of steps.  512 rows on 64 waves: 669 us, 1.3 us per step (955 before the
-// chain of a step was shortened).
+// Bound: the chain of steps.  384 steps of 512 rows on 64 waves: 535 us, 1.4 us each.
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
 // waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
@@ -313,6 +312,8 @@ struct Gate {
     }
 };
 
+constexpr int TAIL = 128, TS = TAIL / 16, TAIL_PHASE = 32;       // rows of TriTail; slots of 16; steps that run on the same slots
+
 // How a workgroup's part in a reduction ends: done; a wait of a step gave up; the group did not go on, and this workgroup was
 // the last of it to start, or not.
 enum TriEnd { TRI_DONE, TRI_FAILED, TRI_LAST, TRI_LEFT };
@@ -320,6 +321,7 @@ enum TriEnd { TRI_DONE, TRI_FAILED, TRI_LAST, TRI_LEFT };
 template <int C, int R, int QW>
 struct Tri {
     static constexpr int CN = 64 * C, W = 64 * QW, OWN = (C + 3) / 4;
+    static constexpr int LAST = C - TAIL / 64 - 1;               // the last chunk of columns that is reduced here
     double a[R][C];
     double x[C], v[C], wv[C];        // column k; the last step's vectors, which the rows have still to be updated with
     Global<u64> slots;
@@ -374,11 +376,10 @@ struct Tri {
     __device__ inline void phase(int& k, const StepStore& store)
     {
         constexpr int T0 = P / QW;                               // row slots before T0 are finished
-        constexpr int PN = P + 1 < C ? P + 1 : P;
-        const int k_end = P + 1 < C ? 64 * (P + 1) : CN - 2;
-        for (; k < k_end; ++k) {
+        constexpr int PN = P + 1;
+        for (; k < 64 * PN; ++k) {
             const int k1 = k + 1, l1 = k1 & 63;
-            const bool next_chunk = P + 1 < C && l1 == 0;        // row k + 1 is the first of chunk P + 1
+            const bool next_chunk = l1 == 0;                     // row k + 1 is the first of chunk P + 1
             double sq = 0.0;
 #pragma unroll
             for (int c = P; c < C; ++c) {
@@ -484,7 +485,7 @@ struct Tri {
     __device__ inline void phases(int& k, const StepStore& store)
     {
         phase<P>(k, store);
-        if constexpr (P + 1 < C) phases<P + 1>(k, store);
+        if constexpr (P < LAST) phases<P + 1>(k, store);
     }
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
@@ -524,130 +525,234 @@ struct Tri {
         }
         if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
         phases<0>(k, store);
-        update<C - 1, R - 1>();
-        // what is left: the last 2 x 2 block
-        if (w == 0) {
-            const double d = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63);
-            if (lane == 0) {
-                store.put(N - 2, 0.0, d, e);
-                mm.st[DS_EXP] = expo;
-                mm.st[DS_ZERO_ROWS] = zeros;
+        // what is left goes back to memory
+        constexpr int T0 = (LAST + 1) / QW;
+        update<LAST + 1, T0>();
+#pragma unroll
+        for (int t = T0; t < R; ++t) {
+            const Global<double> row = global(mm.C) + (size_t)(w + W * t - off) * N + lane - off;
+            if (W * t + w >= CN - TAIL) {
+#pragma unroll
+                for (int c = LAST + 1; c < C; ++c) row[64 * c] = a[t][c];
             }
         }
-        if (wl == 63 && q == (C - 1) % QW) {
-            const double d = lane_value(a[R - 1][C - 1], 63);
-            if (lane == 0) store.td[2 * N - 1] = d;
+        if (w == 0 && lane == 0) {
+            mm.st[DS_EXP] = expo;
+            mm.st[DS_ZERO_ROWS] = zeros;
         }
         return spin_limit != 0 ? TRI_DONE : TRI_FAILED;
     }
 };
 
-// Up to 128 rows: one workgroup, no exchange through memory.  Lane l holds rows l (and l + 64), wave w the columns w, w + 4, ..;
-// the products of the four waves are added up through LDS, one barrier per step.
-template <int C>
-__device__ inline void tri_small(const DirectMat& m, double* lds)
+// The last 128 rows of a reduction, which is all of a smaller matrix: one workgroup of 256 threads, no exchange through memory.
+// A thread holds rows 16 a + 4 wave + lane / 16 and columns 16 b + column_of(lane) of the trailing matrix, a, b < 8: the
+// columns are dealt to the lanes of a row of 16 such that the first lane has the one with the number of the thread's own
+// row, so what a vector holds at a row is a broadcast inside the row of lanes (row_newbcast) of what it holds at a column.  Every
+// thread works the vectors out at its columns for itself, all with the same bits: sums over the sixteen lanes go through
+// rotations, which give the same sum whatever column a row of lanes begins with.
+// One barrier per step.  What is handed over is (A y)_i, y the column below its first entry, and column k + 1 before the
+// step: the reflector v = y + v0 e_{k+1} is wanted only behind the barrier (A v = A y + v0 A e_{k+1}), so that the norm, the root
+// and the reciprocal run beside the products.
+// Bound: a step of 64 rows is a chain of about 250 instructions with one wave on every SIMD, 0.6 us; at 128 rows it is the issue of
+// 520, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix took 61 us with four waves that each owned columns and broadcast
+// through v_readlane, now 42; the last 128 rows of a group take 112 us and as many inside the group, but on one compute unit instead
+// of 16: 64 matrices of 512 rows 1744 -> 1472 + 112 us.
+constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROW_FIRST = 0x150;
+
+// over the 16 lanes of a row, in every lane, the same bits for every rotation of the values
+__device__ inline double ring_sum(double x)
 {
-    constexpr int CN = 64 * C, NC = 16 * C;                      // columns per wave
-    static_assert(10 * CN <= 4 * MAX_R, "the workgroup's LDS");
-    double(*part)[4][CN] = (double(*)[4][CN])lds;                // [2][4][CN] by step parity
-    double(*col)[CN] = (double(*)[CN])(lds + 8 * CN);            // [2][CN]
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const StepStore store(m);
-    const int N = store.N, off = CN - N;
-    int expo, zeros;
-    const double scale = scale_of<C>(m, off, lane, expo, zeros);
-    double a[NC][C], x[C];
-#pragma unroll
-    for (int t = 0; t < NC; ++t) {
-        const int j = w + 4 * t - off;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int i = lane + 64 * c - off;
-            a[t][c] = i >= 0 && j >= 0 ? scale * global(m.C)[(size_t)j * N + i] : 0.0;
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const int j = lane + 64 * c - off;
-        x[c] = j >= 0 ? scale * global(m.C)[(size_t)m.pad * N + j] : 0.0;
-    }
-    for (int k = off + m.pad; k < CN - 2; ++k) {
-        const int k1 = k + 1, l1 = k1 & 63, c1 = k1 >> 6;
-        const double alpha = lane_value(C > 1 && c1 ? x[C - 1] : x[0], l1);
-        double sq = 0.0;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const double y = lane + 64 * c > k1 ? x[c] : 0.0;
-            sq = fma(y, y, sq);
-        }
-        double beta, v0;
-        const double sig2 = wave_sum(sq);
-        householder(alpha, sig2, beta, v0);
-        double v[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int i = lane + 64 * c;
-            v[c] = i > k1 ? x[c] : i == k1 ? v0 : 0.0;
-        }
-        const double tau = householder_tau(sig2, v0);
-        if (w == (k & 3)) {
-            const int kk = k - off;
-            const double dk = lane_value(C > 1 && k >= 64 ? x[C - 1] : x[0], k & 63);
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (lane + 64 * c >= off) store.refl[(size_t)kk * N + lane + 64 * c - off] = v[c];
-            if (lane == 0) store.put(kk, tau, dk, beta);
-        }
-        double vj[NC], sum[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) sum[c] = 0.0;
-#pragma unroll
-        for (int t = 0; t < NC; ++t) {
-            vj[t] = lane_value(v[t / 16], w + 4 * (t & 15));
-#pragma unroll
-            for (int c = 0; c < C; ++c) sum[c] = fma(a[t][c], vj[t], sum[c]);
-        }
-        double(*pt)[CN] = part[k & 1];
-        double* cl = col[k & 1];
-#pragma unroll
-        for (int c = 0; c < C; ++c) pt[w][lane + 64 * c] = sum[c];
-        if (lane == l1) {
-#pragma unroll
-            for (int t = 0; t < NC; ++t) cl[w + 4 * t] = C > 1 && c1 ? a[t][C - 1] : a[t][0];
-        }
-        __syncthreads();
-        double p[C], gamma = 0.0;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int i = lane + 64 * c;
-            p[c] = (pt[0][i] + pt[1][i]) + (pt[2][i] + pt[3][i]);
-            p[c] = i > k ? p[c] : 0.0;
-            gamma = fma(v[c], p[c], gamma);
-        }
-        gamma = wave_sum(gamma) * tau * (0.5 * tau);
-        double wv[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) wv[c] = fma(-gamma, v[c], tau * p[c]);
-        const double wk1 = lane_value(C > 1 && c1 ? wv[C - 1] : wv[0], l1);
-#pragma unroll
-        for (int c = 0; c < C; ++c) x[c] = fma(-wv[c], v0, fma(-v[c], wk1, cl[lane + 64 * c]));
-#pragma unroll
-        for (int t = 0; t < NC; ++t) {
-            const double wj = lane_value(wv[t / 16], w + 4 * (t & 15));
-#pragma unroll
-            for (int c = 0; c < C; ++c) a[t][c] = fma(-wj, v[c], fma(-vj[t], wv[c], a[t][c]));
-        }
-    }
-    if (w == 3) {                                                // (the wave of the last column)
-        const double d2 = lane_value(x[C - 1], 62), e = lane_value(x[C - 1], 63), d1 = lane_value(a[NC - 1][C - 1], 63);
-        if (lane == 0) {
-            store.put(N - 2, 0.0, d2, e);
-            store.td[2 * N - 1] = d1;
-            m.st[DS_EXP] = expo;
-            m.st[DS_ZERO_ROWS] = zeros;
-        }
-    }
+    x += dpp<DPP_ROR8>(x);
+    x += dpp<DPP_ROR4>(x);
+    x += dpp<DPP_ROR2>(x);
+    x += dpp<DPP_ROR1>(x);
+    return x;
 }
+__device__ inline double fold_by(bool up, double a, double b, int which)
+{
+    const double keep = up ? b : a, give = up ? a : b;
+    return keep + (which == 8 ? dpp<DPP_ROR8>(give) : which == 4 ? dpp<DPP_HALF_MIRROR>(give) : dpp<DPP_XOR2>(give));
+}
+// K = 2, 4, 6 or 8 sums over the 16 lanes of a row at once: lane l receives sum number (l >> 3 & 1) | (l >> 2 & 1) << 1 |
+// (l >> 1 & 1) << 2 (of as many bits as K needs)
+template <int K>
+__device__ inline double row_sums(const double (&v)[K], int lane)
+{
+    constexpr int K1 = K / 2, K2 = (K1 + 1) / 2;
+    double a[K1], b[K2];
+#pragma unroll
+    for (int i = 0; i < K1; ++i) a[i] = fold_by(lane & 8, v[2 * i], v[2 * i + 1], 8);
+    if constexpr (K1 == 1) return sum8(a[0]);
+#pragma unroll
+    for (int i = 0; i < K2; ++i) b[i] = fold_by(lane & 4, a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i], 4);
+    double c = K2 == 1 ? b[0] + dpp<DPP_XOR2>(b[0]) : fold_by(lane & 2, b[0], b[K2 - 1], 2);
+    return c + dpp<DPP_XOR1>(c);
+}
+template <int K>
+__device__ inline int row_slot(int lane)
+{
+    return (lane >> 3 & 1) | (K > 2 ? (lane >> 2 & 1) << 1 : 0) | (K > 4 ? (lane >> 1 & 1) << 2 : 0);
+}
+
+struct TriTail {
+    double a[TS][TS];
+    double x[TS], v[TS], wv[TS];     // column k; the last step's vectors, which the matrix has still to be updated with
+    double2 (*shared)[TAIL];         // [2][TAIL] by step parity: A y and column k + 1
+    int lane, wave, col, row;        // column and row of slot 0
+    int off;                         // row i here is row i - off of the matrix
+
+    template <int S>
+    __device__ inline void steps(int& k, const StepStore& store)
+    {
+        constexpr int L = TS - S;
+        const int k_end = min(16 * S + TAIL_PHASE, TAIL - 2);
+        const bool pair = k < TAIL / 2 && off <= 0 && (store.N / 64 & 1) && store.N > TAIL;
+        for (; k < k_end; ++k) {
+            const int k1 = k + 1, s1 = k1 >> 4;                  // s1: S .. S + 2
+            double y[TS], sq = 0.0;
+#pragma unroll
+            for (int b = S; b < TS; ++b) {
+                y[b] = b > S + 2 || 16 * b + col > k1 ? x[b] : 0.0;
+                sq = fma(y[b], y[b], sq);
+            }
+            double sum[L];
+#pragma unroll
+            for (int t = 0; t < L; ++t) {
+                const double vr = dpp<DPP_ROW_FIRST>(v[S + t]), wr = dpp<DPP_ROW_FIRST>(wv[S + t]);
+                sum[t] = 0.0;
+#pragma unroll
+                for (int b = S; b < TS; ++b) {
+                    a[S + t][b] = fma(-wr, v[b], fma(-vr, wv[b], a[S + t][b]));
+                    sum[t] = fma(a[S + t][b], y[b], sum[t]);
+                }
+            }
+            double2* sh = shared[k & 1];
+            // column k + 1 of the matrix, from the threads that hold that row
+            if (wave == (k1 >> 2 & 3) && lane >> 4 == (k1 & 3)) {
+#pragma unroll
+                for (int t = 0; t < (L < 3 ? L : 3); ++t)
+                    if (s1 == S + t) {
+#pragma unroll
+                        for (int b = S; b < TS; ++b) sh[16 * b + col].y = a[S + t][b];
+                        asm volatile("" ::"n"(t));               // (merged, the branches would put `a` into memory)
+                    }
+            }
+            {
+                const double q = row_sums<L>(sum, lane);
+                const int t = row_slot<L>(lane);
+                if ((lane & (L > 4 ? 1 : L > 2 ? 3 : 7)) == 0 && t < L) sh[16 * (S + t) + row].x = q;
+            }
+            const double sig2 = ring_sum(sq);
+            const int from = (k1 - 4 * wave) & 15;               // the lane of row 0 that has column k + 1
+            const double x0 = lane_value(x[S], from), x1 = lane_value(x[S + 1], from), x2 = lane_value(x[S + 2 < TS ? S + 2 : S], from);
+            const double alpha = s1 == S ? x0 : s1 == S + 1 ? x1 : x2;
+            double beta, v0;
+            householder(alpha, sig2, beta, v0);
+            const double tau = householder_tau(sig2, v0);
+#pragma unroll
+            for (int b = S; b < TS; ++b) v[b] = b <= S + 2 && 16 * b + col == k1 ? v0 : y[b];
+            __syncthreads();
+            const double2 first = sh[k1];
+            double2 qc[TS];
+#pragma unroll
+            for (int b = S; b < TS; ++b) qc[b] = sh[16 * b + col];
+            // one wave keeps the step for the way back, with zeros in front (in the shadow of the loads)
+            if (wave == (k & 3)) {
+                const int kk = k - off, rg = lane >> 4, at = (k - 4 * wave) & 15;
+                const Global<double> r = store.refl + (size_t)kk * store.N - off + 16 * rg + col;
+#pragma unroll
+                for (int h = 0; h < TS / 4; ++h) {
+                    double part[4];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) part[b] = 4 * h + b < S ? 0.0 : v[max(4 * h + b, S)];
+                    const double even = rg & 1 ? part[1] : part[0], odd = rg & 1 ? part[3] : part[2];
+                    if (h > 0 || off <= 0) r[64 * h] = rg & 2 ? odd : even;
+                }
+                if (pair) r[-64] = 0.0;
+                const double d0 = lane_value(x[S], at), d1 = lane_value(x[S + 1], at);
+                if (lane == 0) store.put(kk, tau, k < 16 * (S + 1) ? d0 : d1, beta);
+            }
+            double p[TS], gamma = 0.0;
+#pragma unroll
+            for (int b = S; b < TS; ++b) {
+                p[b] = fma(v0, qc[b].y, qc[b].x);
+                if (b <= S + 1 && 16 * b + col <= k) p[b] = 0.0;
+                x[b] = qc[b].y;
+                gamma = fma(v[b], p[b], gamma);
+            }
+            gamma = ring_sum(gamma) * tau * (0.5 * tau);
+            const double wk1 = fma(-gamma, v0, tau * fma(v0, first.y, first.x));
+#pragma unroll
+            for (int b = S; b < TS; ++b) {
+                wv[b] = fma(-gamma, v[b], tau * p[b]);
+                x[b] = fma(-wv[b], v0, fma(-v[b], wk1, x[b]));
+            }
+        }
+    }
+
+    __device__ inline void run(const DirectMat& m, double* lds)
+    {
+        static_assert(TS == 8 && TAIL_PHASE == 32, "the phases below");
+        const StepStore store(m);
+        const int N = store.N;
+        shared = (double2(*)[TAIL])lds;
+        lane = threadIdx.x & 63;
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        row = 4 * wave + (lane >> 4);
+        col = (row + lane) & 15;
+        off = TAIL - N;
+        int k = off + m.pad;
+        double scale = 1.0;                                      // (larger matrices were scaled by their group)
+        if (off >= 0) {
+            int expo, zeros;
+            scale = scale_of<TAIL / 64>(m, off, lane, expo, zeros);
+            if (threadIdx.x == 0) {
+                m.st[DS_EXP] = expo;
+                m.st[DS_ZERO_ROWS] = zeros;
+            }
+        } else {
+            k = 0;
+        }
+        const Global<const double> C = global((const double*)m.C);
+        // (slots in front of a smaller matrix are never used: they read something of its first row)
+        const int from = off > 0 ? off : 0;
+#pragma unroll
+        for (int s = 0; s < TS; ++s) {
+            const Global<const double> r = C + (size_t)(max(16 * s, from) + row - off) * N + col - off;
+#pragma unroll
+            for (int b = 0; b < TS; ++b) a[s][b] = r[max(16 * b, from)];
+        }
+#pragma unroll
+        for (int b = 0; b < TS; ++b) x[b] = C[(size_t)(k - off) * N + max(16 * b, from) + col - off];
+#pragma unroll
+        for (int b = 0; b < TS; ++b) {
+#pragma unroll
+            for (int s = 0; s < TS; ++s) a[s][b] *= scale;
+            x[b] *= scale;
+            v[b] = wv[b] = 0.0;
+        }
+        if (off <= 0) {
+            steps<0>(k, store);
+            steps<2>(k, store);
+        }
+        steps<4>(k, store);
+        steps<6>(k, store);
+        // what is left: the last 2 x 2 block
+        if (row == 15) {
+            const double vr = dpp<DPP_ROW_FIRST>(v[TS - 1]), wr = dpp<DPP_ROW_FIRST>(wv[TS - 1]);
+            const double d1 = fma(-wr, v[TS - 1], fma(-vr, wv[TS - 1], a[TS - 1][TS - 1]));
+            if (col == 15) {
+                store.td[2 * N - 1] = d1;
+                store.od[N - 2] = x[TS - 1];
+                store.td[2 * N - 2] = fmax(x[TS - 1] * x[TS - 1], OD2_MIN);
+            }
+            if (col == 14) {
+                store.tau[N - 2] = 0.0;
+                store.td[2 * N - 3] = x[TS - 1];
+            }
+        }
+    }
+};
 
 // The reduction by one workgroup that waits for nobody: the same steps on the matrix in memory, which nothing needs
 // afterwards.  Two passes over what is left of it per step: 4 ms for 200
@@ -668,7 +773,7 @@ __device__ inline void tri_alone(const DirectMat& m, double* lds)
     __syncthreads();
     for (int e = tid; e < N * N; e += 256) A[e] *= scale;
     __syncthreads();
-    for (int k = m.pad; k < N - 2; ++k) {
+    for (int k = m.pad; k < N - TAIL; ++k) {
         double x[C], sq = 0.0;
         load(k, x);
 #pragma unroll
@@ -720,8 +825,6 @@ __device__ inline void tri_alone(const DirectMat& m, double* lds)
         __syncthreads();
     }
     if (tid == 0) {
-        store.put(N - 2, 0.0, A[(size_t)(N - 2) * N + N - 2], A[(size_t)(N - 2) * N + N - 1]);
-        store.td[2 * N - 1] = A[(size_t)(N - 1) * N + N - 1];
         m.st[DS_EXP] = expo;
         m.st[DS_ZERO_ROWS] = zeros;
     }
@@ -736,14 +839,20 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
     const DirectMat& m = mats[wk.mat];
     TriEnd end = TRI_DONE;
     switch (m.cls) {
-        case CLS_64: tri_small<1>(m, (double*)lds); break;
-        case CLS_128: tri_small<2>(m, (double*)lds); break;
         case CLS_256: { Tri<4, 4, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
         case CLS_512: { Tri<8, 8, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
         default: { Tri<10, 5, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
     }
     if (end == TRI_LAST) tri_alone(m, (double*)lds);
     if (end == TRI_FAILED && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
+}
+
+// One workgroup per matrix.
+__global__ __launch_bounds__(256, 1) void direct_tail(const DirectMat* mats)
+{
+    __shared__ double2 lds[2 * TAIL];
+    TriTail t;
+    t.run(mats[blockIdx.x], (double*)lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1502,6 +1611,7 @@ void plan_work(DirectPlan& plan)
     for (int j : order) {
         const DirectMat& m = plan.mats[j];
         const int wgs = CLS_WGS[m.cls];
+        if (m.r <= TAIL) continue;
         int best = 0;
         for (int x = 1; x < 8; ++x)
             if (load[x] < load[best]) best = x;
@@ -1520,7 +1630,8 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
     direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
-    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    if (!plan.tri.empty()) direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);

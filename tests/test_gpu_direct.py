@@ -34,6 +34,18 @@ def test_sizes_around_the_tiles(shape, tall):
     full_parity(G, 3.0, 5, 3, msgs[0], *per[0])
 
 
+@pytest.mark.parametrize("shape", [(34, 90), (47, 80), (48, 300), (49, 100), (79, 120), (80, 96), (81, 200), (95, 130), (96, 400),
+                                   (97, 150), (111, 160), (112, 300), (113, 140), (126, 180), (130, 300), (160, 200), (193, 240),
+                                   (321, 400), (384, 420), (385, 500)])
+def test_sizes_around_the_slots_of_one_workgroup(shape):
+    """Slots of 16 rows, steps on the same slots in runs of 32; behind a group the last rows of an even or odd number of chunks."""
+    rng = np.random.default_rng(shape[0] * 2003 + shape[1])
+    G = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.5, 0.25, 0.1], 0.01)
+    msgs, per, status, sweeps = encode([G], 3.0, 7, stream_base=2, capacity=min(shape))
+    assert status == 0 and route() == [DIRECT]
+    full_parity(G, 3.0, 7, 2, msgs[0], *per[0])
+
+
 def test_strided_folded_and_mixed_with_other_sizes_in_one_call():
     rng = np.random.default_rng(3)
     shapes = [(64, 27), (96, 200), (650, 660), (300, 140), (512, 700)]
