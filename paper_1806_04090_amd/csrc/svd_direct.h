@@ -27,7 +27,7 @@ struct DirectMat {
     long long ldg;
     int rows, cols, transposed, r, M;
     int nt, pad;                     // N = 64 nt >= r: the Gram matrix with `pad` zero rows and columns in front
-    int cls;                         // CLS_*: how the reduction splits the matrix (its last 128 rows are one workgroup's)
+    int cls;                         // CLS_*: how the reduction splits the matrix (its last rows are one workgroup's)
     int nchunks, kchunk;             // the columns of A in the Gram product: nchunks partial sums of kchunk each
     int capacity;
     double* part;                    // [nchunks][nt (nt + 1) / 2][64 * 64] partial Gram tiles

@@ -29,6 +29,7 @@ namespace {
 enum { CLS_64 = 0, CLS_128, CLS_256, CLS_512, CLS_640, CLS_COUNT };
 // columns / 64, workgroups of the group
 constexpr int CLS_CHUNKS[CLS_COUNT] = {1, 2, 4, 8, 10};
+constexpr int XCH = 5;            // vectors in the exchange slots of a group, see Tri
 constexpr int CLS_WGS[CLS_COUNT] = {1, 1, 16, 16, 32};
 
 __device__ inline double fold8(double a, double b, int lane)
@@ -49,6 +50,8 @@ __device__ inline double wave_sums(const double (&v)[K], int lane)
     for (int i = 0; i < K2; ++i) b[i] = fold16(a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i]);
     return sum8(fold8(b[0], K2 > 1 ? b[1] : b[0], lane));
 }
+// The value is worked out where this stands and not where it is used first (behind a wait, as a rule).
+__device__ inline void here(double& x) { asm volatile("" : "+v"(x)); }
 __device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2; }
 
 // ------------------------------------------------------------------------------------------------
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
     if (ti == 0 && tj == 0) {
         if (tid < DS_WORDS) m.st[tid] = 0;
         if (tid == 0) *m.gate = 0;
-        for (int i = tid; i < 4 * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
+        for (int i = tid; i < XCH * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
         if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
         if (tid == m.pad) m.td[tid].x = 0.0;
         // rows of the reflectors' blocks that are no step
@@ -252,13 +255,20 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
     return ldexp(1.0, -e);
 }
 
-// Groups of 16 or 32 workgroups (matrices of more than 128 rows, until 128 are left): every wave owns R rows of the matrix in registers (lane l:
-// columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all waves
-// the same bits; one exchange per step: every wave publishes the entries of p of its rows, the owner of row k + 1
-// that row (column k + 1 of the matrix before the step), and every workgroup reads all of both, a quarter per wave.
+// Groups of 16 or 32 workgroups (matrices of more than 128 rows, until 64 are left): every wave owns R rows of the matrix in
+// registers (lane l: columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all
+// waves the same bits; one exchange per step: every wave publishes the entries of A y of its rows (y: the column below its first entry;
+// A v = A y + v0 A e_{k+1}, so the reflector need not be known), the owner of row k + 1 that row, and every workgroup reads all of
+// both, a quarter per wave.
+// What everybody waits for is (A y)_i, so a step does nothing else before it: the product is taken with the matrix as it was before the
+// last step's update, whose share is a product with two sums of y (v_i (w y) + w_i (v y)).  The update itself, the reflector and the
+// row of the next step (handed over a step early, the readers add the update that it lacks) come behind it, while the entries
+// travel; the loads that look for them go out in the middle of that work (a load of 512 bytes by every wave takes 250 cycles, four of
+// them 460, whether the entries are there or not).
 // An entry is one 8-byte store whose two lowest mantissa bits carry the step number mod 4: a reader knows from the value
-// that it is the one of this step, no flag and no second round trip.  Two slots by step parity: a wave that publishes
-// step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more.
+// that it is the one of this step, no flag and no second round trip.  Two slots for A y by step parity: a wave that publishes
+// step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more; three for the
+// rows, which are written a step ahead.
 // The workgroups of a group sit on one die (blockIdx mod 8), whose L2 the exchange goes through: 0.77 us per step among 64
 // waves, against 5 us through memory; they check that with the die's number, and store through to memory if it is not so.
 // (On one die the stores have workgroup scope, which the memory model does not extend to other workgroups.  What carries them
@@ -267,7 +277,9 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // Waits: nothing guarantees that a group is resident as a whole - other work on the GPU can hold the places that its last
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
-// Bound: the chain of steps.  384 steps of 512 rows on 64 waves: 535 us, 1.4 us each.
+// Bound: the chain of steps.  448 steps of 512 rows: 1.5 us each at the beginning and 0.8 at the end on 64 waves, 515 us in all on 128
+// (1.4 us per step with the update, the norm and the root in front of the product).  Four groups per die, two waves on every
+// SIMD: the issue of the vectors that every wave works out for itself.
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
 // waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
@@ -312,7 +324,8 @@ struct Gate {
     }
 };
 
-constexpr int TAIL = 128, TS = TAIL / 16, TAIL_PHASE = 32;       // rows of TriTail; slots of 16; steps that run on the same slots
+constexpr int TAIL = 64;                                         // rows that a group leaves
+constexpr int ONE = 128, TS = ONE / 16, ONE_PHASE = 32;          // rows of TriOne; slots of 16; steps that run on the same slots
 
 // How a workgroup's part in a reduction ends: done; a wait of a step gave up; the group did not go on, and this workgroup was
 // the last of it to start, or not.
@@ -324,10 +337,13 @@ struct Tri {
     static constexpr int LAST = C - TAIL / 64 - 1;               // the last chunk of columns that is reduced here
     double a[R][C];
     double x[C], v[C], wv[C];        // column k; the last step's vectors, which the rows have still to be updated with
+    double vr[R];                    // v at the rows of the wave
+    double tau, diagonal, beta;      // the last step's
     Global<u64> slots;
     double2 (*shared)[CN];           // [2][CN] by step parity: p and column k + 1
-    int lane, wave, w, wl, q, off, k_first, spin_limit;
-    bool local;
+    int lane, wave, member, w, wl, q, off, k_first, spin_limit;
+    int third;                       // step mod 3
+    bool local;                      // the group sits on one die
 
     template <bool LOCAL>
     static __device__ inline void put(Global<u64> p, double value, u64 tag)
@@ -336,17 +352,23 @@ struct Tri {
         if (LOCAL) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         else __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // column k + 1 of the matrix, in row slot T of this wave
+    // a row of the matrix, in row slot T of this wave
     template <int P, int T>
     __device__ inline void put_row(Global<u64> slot, u64 tag) const
     {
-        if (local) {
+        if (__builtin_expect(local, 1)) {
 #pragma unroll
             for (int c = P; c < C; ++c) put<true>(slot + lane + 64 * c, a[T][c], tag);
         } else {
 #pragma unroll
             for (int c = P; c < C; ++c) put<false>(slot + lane + 64 * c, a[T][c], tag);
         }
+    }
+    template <int T>
+    __device__ inline void put_first(int row) const
+    {
+        if (w + W * T == row) put_row<0, T>(slots + (2 + 1) * CN, 1);
+        if constexpr (T + 1 < R) put_first<T + 1>(row);
     }
     // entry of row slot t of a vector whose chunks before P are finished (0 there)
     template <int P, int T>
@@ -361,14 +383,35 @@ struct Tri {
         }
     }
     template <int P, int T>
-    __device__ inline void update()
+    __device__ inline void entries(const double (&vec)[C], double (&at)[R]) const
     {
         if constexpr (T < R) {
-            const double vr = own<P, T>(v), wr = own<P, T>(wv);
-#pragma unroll
-            for (int c = P; c < C; ++c) a[T][c] = fma(-wr, v[c], fma(-vr, wv[c], a[T][c]));
-            update<P, T + 1>();
+            at[T] = own<P, T>(vec);
+            entries<P, T + 1>(vec, at);
         }
+    }
+    template <int P, int T0>
+    __device__ inline void update(const double (&wr)[R])
+    {
+#pragma unroll
+        for (int t = T0; t < R; ++t)
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                a[t][c] = fma(-wr[t], v[c], fma(-vr[t], wv[c], a[t][c]));
+                here(a[t][c]);
+            }
+    }
+
+    // step k - 1, every wave of the workgroup a part; with zeros in what is finished of its vector (that is read in pairs of chunks)
+    template <int P>
+    __device__ inline void keep(int k, const StepStore& store) const
+    {
+        const int kk = k - 1 - off;
+        const Global<double> row = store.refl + (size_t)kk * store.N + lane - off;
+#pragma unroll
+        for (int c = P > 1 ? P - 2 : 0; c < C; ++c)
+            if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[64 * c] = c < P ? 0.0 : v[c < P ? P : c];
+        if (wave == 3 && lane == 0) store.put(kk, tau, diagonal, beta);
     }
 
     // steps k of [64 P, 64 (P + 1)): chunks of columns before P are finished
@@ -380,83 +423,104 @@ struct Tri {
         for (; k < 64 * PN; ++k) {
             const int k1 = k + 1, l1 = k1 & 63;
             const bool next_chunk = l1 == 0;                     // row k + 1 is the first of chunk P + 1
-            double sq = 0.0;
-#pragma unroll
-            for (int c = P; c < C; ++c) {
-                const double y = c > PN || lane + 64 * c > k1 ? x[c] : 0.0;
-                sq = fma(y, y, sq);
-            }
-            const double sig2 = wave_sum(sq), alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
-            update<P, T0>();                                     // (fills the latency of the sum and of the root)
-            double beta, v0;
-            householder(alpha, sig2, beta, v0);
-#pragma unroll
-            for (int c = P; c < C; ++c) {
-                const int i = lane + 64 * c;
-                v[c] = c > PN || i > k1 ? x[c] : i == k1 ? v0 : 0.0;
-            }
             const unsigned step = (unsigned)(k - k_first + 1);   // (from 1: the cleared slots carry tag 0)
             const u64 tag = step & 3;
-            const Global<u64> slot_p = slots + (step & 1) * (2 * CN);
-            const Global<u64> slot_c = slot_p + CN;
-            // column k + 1 of the matrix, from the wave that owns that row
-            if (wl == l1) {
-                if (!next_chunk) {
-                    if (q == P % QW) put_row<P, P / QW>(slot_c, tag);
-                } else if (q == PN % QW) {
-                    put_row<P, PN / QW>(slot_c, tag);
-                }
+            const Global<u64> slot_p = slots + (step & 1) * CN, slot_c = slots + (2 + third) * CN;
+            third = third == 2 ? 0 : third + 1;
+            double y[C], vy = 0.0, wy = 0.0;
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                y[c] = c > PN || lane + 64 * c > k1 ? x[c] : 0.0;
+                vy = fma(v[c], y[c], vy);
+                wy = fma(wv[c], y[c], wy);
+            }
+            double wr[R], part[R - T0];
+            entries<P, T0>(wv, wr);
+#pragma unroll
+            for (int t = T0; t < R; ++t) {
+                double sum = fma(-wr[t], vy, -vr[t] * wy);
+#pragma unroll
+                for (int c = P; c < C; ++c) sum = fma(a[t][c], y[c], sum);
+                part[t - T0] = sum;
             }
             {
-                double part[R - T0];
-#pragma unroll
-                for (int t = T0; t < R; ++t) {
-                    double sum = a[t][P] * v[P];
-#pragma unroll
-                    for (int c = P + 1; c < C; ++c) sum = fma(a[t][c], v[c], sum);
-                    part[t - T0] = sum;
-                }
                 const double p = wave_sums<R - T0>(part, lane);
                 const int t = T0 + sum_slot(lane);
                 if ((lane & 7) == 0 && t < R) {
-                    if (local) put<true>(slot_p + w + W * t, p, tag);
+                    if (__builtin_expect(local, 1)) put<true>(slot_p + w + W * t, p, tag);
                     else put<false>(slot_p + w + W * t, p, tag);
                 }
             }
-            const double tau = householder_tau(sig2, v0);
-            if (w == (k & (W - 1))) {                            // one wave keeps the step for the way back
-                const int kk = k - off;
-                const Global<double> row = store.refl + (size_t)kk * store.N + lane - off;
-#pragma unroll
-                for (int c = P; c < C; ++c) row[64 * c] = v[c];
-                // (chunks are read in pairs: the finished half of one has to hold zeros)
-                if constexpr (P > 0) {
-                    if ((P - (off >> 6)) & 1) row[64 * (P - 1)] = 0.0;
+            // behind what the others wait for: the last step's reflector (one wave keeps it for the way back), the matrix, the row
+            // that the next step hands over
+            __builtin_amdgcn_sched_barrier(0);
+            if (__builtin_expect(member == (k - 1 & (W / 4 - 1)) && k > k_first, 0)) keep<P>(k, store);
+            update<P, T0>(wr);
+            if (__builtin_expect(wl == (k + 2 & 63), 0)) {
+                const Global<u64> slot = slots + (2 + third) * CN;
+                if (k + 2 < 64 * PN) {
+                    if (q == P % QW) put_row<P, P / QW>(slot, step + 1 & 3);
+                } else if (q == PN % QW) {
+                    put_row<P, PN / QW>(slot, step + 1 & 3);
                 }
-                const double dk = lane_value(x[P], k & 63);
-                if (lane == 0) store.put(kk, tau, dk, beta);
             }
-            // this wave's chunks of p and of the column (one of a finished chunk: any other), then the workgroup's
+            double sq = 0.0;
+#pragma unroll
+            for (int c = P; c < C; ++c) sq = fma(y[c], y[c], sq);
+            const double sig2 = wave_sum(sq), alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
+            __builtin_amdgcn_sched_barrier(0);
+            // this wave's chunks of p and of the column (one of a finished chunk: any other), then the workgroup's; they are on
+            // their way while the reflector is worked out
             constexpr int J0 = P / 4;
             int at[OWN - J0];
             u64 pu[OWN - J0], cu[OWN - J0];
 #pragma unroll
             for (int j = J0; j < OWN; ++j) at[j - J0] = lane + 64 * min(max(wave + 4 * j, P), C - 1);
-            int spins = 0;
-            while (true) {
+            auto look = [&]() {
 #pragma unroll
                 for (int j = 0; j < OWN - J0; ++j) {
                     pu[j] = __hip_atomic_load(slot_p + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     cu[j] = __hip_atomic_load(slot_c + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
+            };
+            look();
+            __builtin_amdgcn_sched_barrier(0);
+            double v0;
+            householder(alpha, sig2, beta, v0);
+            tau = householder_tau(sig2, v0);
+            diagonal = lane_value(x[P], k & 63);
+            double fresh[C];                                     // what the row of this step lacks of the last step's update
+            {
+                const double v1 = lane_value(next_chunk ? v[PN] : v[P], l1), w1 = lane_value(next_chunk ? wv[PN] : wv[P], l1);
+#pragma unroll
+                for (int c = P; c < C; ++c) {
+                    fresh[c] = fma(-w1, v[c], -v1 * wv[c]);
+                    here(fresh[c]);
+                }
+            }
+#pragma unroll
+            for (int c = P; c < C; ++c) {
+                v[c] = c <= PN && lane + 64 * c == k1 ? v0 : y[c];
+                here(v[c]);
+            }
+            here(tau);
+            entries<P, T0>(v, vr);
+            __builtin_amdgcn_sched_barrier(0);
+            auto ready = [&]() {
                 unsigned other = 0;
 #pragma unroll
                 for (int j = 0; j < OWN - J0; ++j) other |= ((unsigned)pu[j] ^ (unsigned)tag) | ((unsigned)cu[j] ^ (unsigned)tag);
-                if (__all((other & 3u) == 0u)) break;
-                if (++spins > spin_limit) {                      // (once: the steps after it wait for nothing)
-                    spin_limit = 0;
-                    break;
-                }
+                return __all((other & 3u) == 0u);
+            };
+            if (__builtin_expect(!ready(), 0)) {
+                int spins = 0;
+                do {
+                    if (++spins > spin_limit) {                  // (once: the steps after it wait for nothing)
+                        spin_limit = 0;
+                        break;
+                    }
+                    look();
+                } while (!ready());
             }
             double2* sh = shared[step & 1];
 #pragma unroll
@@ -468,8 +532,8 @@ struct Tri {
 #pragma unroll
             for (int c = P; c < C; ++c) {
                 const double2 pc = sh[lane + 64 * c];
-                p[c] = c <= PN && lane + 64 * c <= k ? 0.0 : pc.x;
-                x[c] = pc.y;
+                x[c] = pc.y + fresh[c];
+                p[c] = c <= PN && lane + 64 * c <= k ? 0.0 : fma(v0, x[c], pc.x);
                 gamma = fma(v[c], p[c], gamma);
             }
             gamma = wave_sum(gamma) * tau * (0.5 * tau);
@@ -490,8 +554,9 @@ struct Tri {
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
 
-    __device__ inline TriEnd run(const DirectMat& mm, int member, int n_wgs, long long start_ticks, double2* lds)
+    __device__ inline TriEnd run(const DirectMat& mm, int number, int n_wgs, long long start_ticks, double2* lds)
     {
+        member = number;
         const StepStore store(mm);
         const int N = store.N;
         spin_limit = SPIN_STEP;
@@ -524,10 +589,17 @@ struct Tri {
             v[c] = wv[c] = 0.0;
         }
         if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
+        third = 1;
+#pragma unroll
+        for (int t = 0; t < R; ++t) vr[t] = 0.0;
+        put_first<0>(k + 1);
         phases<0>(k, store);
         // what is left goes back to memory
         constexpr int T0 = (LAST + 1) / QW;
-        update<LAST + 1, T0>();
+        if (member == (k - 1 & (W / 4 - 1))) keep<LAST + 1>(k, store);
+        double wr[R];
+        entries<LAST + 1, T0>(wv, wr);
+        update<LAST + 1, T0>(wr);
 #pragma unroll
         for (int t = T0; t < R; ++t) {
             const Global<double> row = global(mm.C) + (size_t)(w + W * t - off) * N + lane - off;
@@ -544,7 +616,7 @@ struct Tri {
     }
 };
 
-// The last 128 rows of a reduction, which is all of a smaller matrix: one workgroup of 256 threads, no exchange through memory.
+// Up to 128 rows, or what a group leaves of a larger matrix: one workgroup of 256 threads, no exchange through memory.
 // A thread holds rows 16 a + 4 wave + lane / 16 and columns 16 b + column_of(lane) of the trailing matrix, a, b < 8: the
 // columns are dealt to the lanes of a row of 16 such that the first lane has the one with the number of the thread's own
 // row, so what a vector holds at a row is a broadcast inside the row of lanes (row_newbcast) of what it holds at a column.  Every
@@ -555,8 +627,7 @@ struct Tri {
 // and the reciprocal run beside the products.
 // Bound: a step of 64 rows is a chain of about 250 instructions with one wave on every SIMD, 0.6 us; at 128 rows it is the issue of
 // 520, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix took 61 us with four waves that each owned columns and broadcast
-// through v_readlane, now 42; the last 128 rows of a group take 112 us and as many inside the group, but on one compute unit instead
-// of 16: 64 matrices of 512 rows 1744 -> 1472 + 112 us.
+// through v_readlane, now 42.  What a group leaves is worked off by one compute unit instead of 16 or 32.
 constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROW_FIRST = 0x150;
 
 // over the 16 lanes of a row, in every lane, the same bits for every rotation of the values
@@ -594,19 +665,19 @@ __device__ inline int row_slot(int lane)
     return (lane >> 3 & 1) | (K > 2 ? (lane >> 2 & 1) << 1 : 0) | (K > 4 ? (lane >> 1 & 1) << 2 : 0);
 }
 
-struct TriTail {
+struct TriOne {
     double a[TS][TS];
     double x[TS], v[TS], wv[TS];     // column k; the last step's vectors, which the matrix has still to be updated with
-    double2 (*shared)[TAIL];         // [2][TAIL] by step parity: A y and column k + 1
+    double2 (*shared)[ONE];          // [2][ONE] by step parity: A y and column k + 1
     int lane, wave, col, row;        // column and row of slot 0
-    int off;                         // row i here is row i - off of the matrix
+    int off, first;                  // row i here is row i - off of the matrix; the first that is reduced here
 
     template <int S>
     __device__ inline void steps(int& k, const StepStore& store)
     {
         constexpr int L = TS - S;
-        const int k_end = min(16 * S + TAIL_PHASE, TAIL - 2);
-        const bool pair = k < TAIL / 2 && off <= 0 && (store.N / 64 & 1) && store.N > TAIL;
+        const int k_end = min(16 * S + ONE_PHASE, ONE - 2);
+        const bool pair = 16 * S < ONE / 2 ? off < 0 && (store.N / 64 & 1) : first > 0 && !(store.N / 64 & 1);
         for (; k < k_end; ++k) {
             const int k1 = k + 1, s1 = k1 >> 4;                  // s1: S .. S + 2
             double y[TS], sq = 0.0;
@@ -652,7 +723,7 @@ struct TriTail {
 #pragma unroll
             for (int b = S; b < TS; ++b) v[b] = b <= S + 2 && 16 * b + col == k1 ? v0 : y[b];
             __syncthreads();
-            const double2 first = sh[k1];
+            const double2 at_k1 = sh[k1];
             double2 qc[TS];
 #pragma unroll
             for (int b = S; b < TS; ++b) qc[b] = sh[16 * b + col];
@@ -666,9 +737,9 @@ struct TriTail {
 #pragma unroll
                     for (int b = 0; b < 4; ++b) part[b] = 4 * h + b < S ? 0.0 : v[max(4 * h + b, S)];
                     const double even = rg & 1 ? part[1] : part[0], odd = rg & 1 ? part[3] : part[2];
-                    if (h > 0 || off <= 0) r[64 * h] = rg & 2 ? odd : even;
+                    if (64 * h >= first) r[64 * h] = rg & 2 ? odd : even;
                 }
-                if (pair) r[-64] = 0.0;
+                if (pair) r[(16 * S < ONE / 2 ? 0 : 64) - 64] = 0.0;
                 const double d0 = lane_value(x[S], at), d1 = lane_value(x[S + 1], at);
                 if (lane == 0) store.put(kk, tau, k < 16 * (S + 1) ? d0 : d1, beta);
             }
@@ -681,7 +752,7 @@ struct TriTail {
                 gamma = fma(v[b], p[b], gamma);
             }
             gamma = ring_sum(gamma) * tau * (0.5 * tau);
-            const double wk1 = fma(-gamma, v0, tau * fma(v0, first.y, first.x));
+            const double wk1 = fma(-gamma, v0, tau * fma(v0, at_k1.y, at_k1.x));
 #pragma unroll
             for (int b = S; b < TS; ++b) {
                 wv[b] = fma(-gamma, v[b], tau * p[b]);
@@ -692,38 +763,36 @@ struct TriTail {
 
     __device__ inline void run(const DirectMat& m, double* lds)
     {
-        static_assert(TS == 8 && TAIL_PHASE == 32, "the phases below");
+        static_assert(TS == 8 && ONE_PHASE == 32, "the phases below");
         const StepStore store(m);
         const int N = store.N;
-        shared = (double2(*)[TAIL])lds;
+        shared = (double2(*)[ONE])lds;
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         row = 4 * wave + (lane >> 4);
         col = (row + lane) & 15;
-        off = TAIL - N;
-        int k = off + m.pad;
+        off = ONE - N;
+        first = N > ONE ? ONE - TAIL : off;
+        int k = N > ONE ? first : off + m.pad;
         double scale = 1.0;                                      // (larger matrices were scaled by their group)
         if (off >= 0) {
             int expo, zeros;
-            scale = scale_of<TAIL / 64>(m, off, lane, expo, zeros);
+            scale = scale_of<ONE / 64>(m, off, lane, expo, zeros);
             if (threadIdx.x == 0) {
                 m.st[DS_EXP] = expo;
                 m.st[DS_ZERO_ROWS] = zeros;
             }
-        } else {
-            k = 0;
         }
         const Global<const double> C = global((const double*)m.C);
-        // (slots in front of a smaller matrix are never used: they read something of its first row)
-        const int from = off > 0 ? off : 0;
+        // (slots in front of the first are never used: they read something of its row)
 #pragma unroll
         for (int s = 0; s < TS; ++s) {
-            const Global<const double> r = C + (size_t)(max(16 * s, from) + row - off) * N + col - off;
+            const Global<const double> r = C + (size_t)(max(16 * s, first) + row - off) * N + col - off;
 #pragma unroll
-            for (int b = 0; b < TS; ++b) a[s][b] = r[max(16 * b, from)];
+            for (int b = 0; b < TS; ++b) a[s][b] = r[max(16 * b, first)];
         }
 #pragma unroll
-        for (int b = 0; b < TS; ++b) x[b] = C[(size_t)(k - off) * N + max(16 * b, from) + col - off];
+        for (int b = 0; b < TS; ++b) x[b] = C[(size_t)(k - off) * N + max(16 * b, first) + col - off];
 #pragma unroll
         for (int b = 0; b < TS; ++b) {
 #pragma unroll
@@ -731,7 +800,7 @@ struct TriTail {
             x[b] *= scale;
             v[b] = wv[b] = 0.0;
         }
-        if (off <= 0) {
+        if (first == 0) {
             steps<0>(k, store);
             steps<2>(k, store);
         }
@@ -839,19 +908,25 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
     const DirectMat& m = mats[wk.mat];
     TriEnd end = TRI_DONE;
     switch (m.cls) {
+        case CLS_64:
+        case CLS_128: { TriOne t; t.run(m, (double*)lds); } break;
         case CLS_256: { Tri<4, 4, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
-        case CLS_512: { Tri<8, 8, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        case CLS_512:
+            if (wk.b == 32) { Tri<8, 4, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+            else { Tri<8, 8, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+            break;
         default: { Tri<10, 5, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
     }
     if (end == TRI_LAST) tri_alone(m, (double*)lds);
     if (end == TRI_FAILED && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
 }
 
-// One workgroup per matrix.
+// What the groups left; one workgroup per matrix.
 __global__ __launch_bounds__(256, 1) void direct_tail(const DirectMat* mats)
 {
-    __shared__ double2 lds[2 * TAIL];
-    TriTail t;
+    __shared__ double2 lds[2 * ONE];
+    if (mats[blockIdx.x].r <= ONE) return;
+    TriOne t;
     t.run(mats[blockIdx.x], (double*)lds);
 }
 
@@ -1570,7 +1645,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.fact = carve.take<double>(N * RB);
     m.lam = carve.take<double>(m.r);
     m.u = carve.take<double>((size_t)m.capacity * m.r);
-    m.xch = carve.take<u64>((size_t)4 * 64 * CLS_CHUNKS[m.cls]);
+    m.xch = carve.take<u64>((size_t)XCH * 64 * CLS_CHUNKS[m.cls]);
     m.gate = carve.take<u64>(1);
     m.st = carve.take<int>(DS_WORDS);
     m.weight = carve.take<float>(m.capacity);
@@ -1606,12 +1681,16 @@ void plan_work(DirectPlan& plan)
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
     // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].r > plan.mats[b].r; });
+    // Twice the workgroups for matrices of 257 to 512 rows, if every workgroup of the call has a compute unit to itself then: four of
+    // 512 rows and five of 256 480 -> 455 us for the first 384 steps; 64 of 512 rows, where it has not, 1395 -> 2297.
+    int total = 0;
+    for (const DirectMat& m : plan.mats) total += m.cls == CLS_512 ? 32 : CLS_WGS[m.cls];
+    const bool wide = total <= 256;
     std::vector<Work> die[8];
     long long load[8] = {0};
     for (int j : order) {
         const DirectMat& m = plan.mats[j];
-        const int wgs = CLS_WGS[m.cls];
-        if (m.r <= TAIL) continue;
+        const int wgs = m.cls == CLS_512 && wide ? 32 : CLS_WGS[m.cls];
         int best = 0;
         for (int x = 1; x < 8; ++x)
             if (load[x] < load[best]) best = x;
@@ -1630,8 +1709,8 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
     direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
-    if (!plan.tri.empty()) direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
-    direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
+    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
