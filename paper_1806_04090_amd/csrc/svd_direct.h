@@ -8,6 +8,7 @@ namespace direct {
 
 constexpr int MAX_R = 640;           // vectors on the shorter side that the reduction holds in registers
 constexpr int TILE = 64;
+constexpr size_t WIDE_MIN = 8192;    // work items of the Gram product from which on a wave takes a tile of its own (direct_gram_wide)
 constexpr double MAX_BUDGET = 32.0;  // above this many expected atoms the vectors cost more than the Jacobi iteration
 constexpr long long START_TICKS = 2000000;   // 20 ms of the 100 MHz clock: how long a workgroup waits for its group to start
 
@@ -29,6 +30,7 @@ struct DirectMat {
     int nt, pad;                     // N = 64 nt >= r: the Gram matrix with `pad` zero rows and columns in front
     int cls;                         // CLS_*: how the reduction splits the matrix (its last rows are one workgroup's)
     int nchunks, kchunk;             // the columns of A in the Gram product: nchunks partial sums of kchunk each
+    int first_tile;                  // its first word among the call's tickets
     int capacity;
     double* part;                    // [nchunks][nt (nt + 1) / 2][64 * 64] partial Gram tiles
     double* C;                       // [N][N] Gram matrix, both triangles
@@ -60,13 +62,14 @@ struct DirectMat {
 
 struct DirectPlan {
     std::vector<DirectMat> mats;
-    std::vector<svd::Work> gram, tiles, tri, eig, vec, lng;
+    std::vector<svd::Work> gram, tiles, gram_wide, tri, eig, vec, lng;
+    size_t n_tiles = 0;              // tickets: a word per tile of the Gram matrices, zero between launches
     bool spread = false;             // deal the workgroups of a group over all dies (for tests)
     long long start_ticks = START_TICKS;
     int eig_lanes = 64;              // lanes per eigenvalue in the search
     size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
     int max_nt = 1;
-    size_t n_work() const { return gram.size() + tiles.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
+    size_t n_work() const { return gram.size() + tiles.size() + gram_wide.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
 };
 
 // Lets the kernels have more LDS than a launch gets by default; once per device.
@@ -80,7 +83,8 @@ void plan_work(DirectPlan& plan);
 struct DirectTables {
     const DirectMat* mats;
     int n_mats;
-    const svd::Work *gram, *tiles, *tri, *eig, *vec, *lng;
+    const svd::Work *gram, *tiles, *gram_wide, *tri, *eig, *vec, *lng;
+    unsigned* tickets;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.
 void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream);

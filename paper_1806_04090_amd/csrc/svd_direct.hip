@@ -12,6 +12,7 @@
 // (rank-deficient gradients), or with two kept atoms whose vectors are not separated (direct_vectors), is left to the
 // Jacobi iteration: DS_ACCEPT stays 0.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <vector>
 
@@ -104,6 +105,20 @@ struct GramLoader {
     }
 };
 
+// What the kernels behind the Gram matrix need cleared; by the threads that finish its first tile.
+__device__ inline void clear_for_steps(const DirectMat& m, int tid, int n_threads)
+{
+    const int N = m.nt * TILE;
+    if (tid < DS_WORDS) m.st[tid] = 0;
+    if (tid == 0) *m.gate = 0;
+    for (int i = tid; i < XCH * 64 * CLS_CHUNKS[m.cls]; i += n_threads) m.xch[i] = 0;
+    if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
+    if (tid == m.pad) m.td[tid].x = 0.0;
+    // rows of the reflectors' blocks that are no step
+    for (int i = tid; i < (m.pad & 15) * N; i += n_threads) m.refl[(size_t)(m.pad & ~15) * N + i] = 0.0;
+    for (int i = tid; i < 2 * N; i += n_threads) m.refl[(size_t)(N - 2) * N + i] = 0.0;
+}
+
 // Bound: the double-precision matrix cores (2 x 64 cycles of v_mfma_f64_16x16x4 per 16 columns, sub-tile and wave; the
 // operand of four instructions is one 16-byte LDS read per lane).  A wave owns a 32 x 32 quarter of the tile.
 __global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const Work* work)
@@ -166,8 +181,7 @@ __global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const 
             for (int v = 0; v < 4; ++v) out[(qi + 16 * i + 4 * v + q) * TILE + qj + 16 * j + l16] = acc[i][j][v];
 }
 
-// Adds the partial tiles up in the order of the columns and writes both triangles; the first tile's workgroup also clears
-// what the reduction needs cleared.
+// Adds the partial tiles up in the order of the columns and writes both triangles.
 __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, const Work* work)
 {
     __shared__ double t[TILE][TILE + 1];
@@ -200,16 +214,141 @@ __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, co
             C[(size_t)(tj * TILE + i) * N + ti * TILE + j] = t[j][i];
         }
     }
-    if (ti == 0 && tj == 0) {
-        if (tid < DS_WORDS) m.st[tid] = 0;
-        if (tid == 0) *m.gate = 0;
-        for (int i = tid; i < XCH * 64 * CLS_CHUNKS[m.cls]; i += 256) m.xch[i] = 0;
-        if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
-        if (tid == m.pad) m.td[tid].x = 0.0;
-        // rows of the reflectors' blocks that are no step
-        for (int i = tid; i < (m.pad & 15) * N; i += 256) m.refl[(size_t)(m.pad & ~15) * N + i] = 0.0;
-        for (int i = tid; i < 2 * N; i += 256) m.refl[(size_t)(N - 2) * N + i] = 0.0;
+    if (ti == 0 && tj == 0) clear_for_steps(m, tid, 256);
+}
+
+// A partial tile is on its way to whoever adds them up, on any die: stores and loads of agent scope.
+__device__ inline void put_part(Global<double> p, double x)
+{
+    __hip_atomic_store((Global<u64>)p, (u64)__double_as_longlong(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double get_part(Global<const double> p)
+{
+    return __longlong_as_double((long long)__hip_atomic_load((Global<const u64>)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// True for the last of a tile's chunks to be finished, in the one thread that asks; everything that the chunk has
+// stored has to be out by then (vmcnt(0): a relaxed store of agent scope that is acknowledged is where every die's loads of
+// agent scope look).  The word is zero again when all have been.
+__device__ inline bool last_chunk(const DirectMat& m, unsigned* tickets, int tile)
+{
+    unsigned* t = tickets + m.first_tile + tile;
+    const bool last = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)m.nchunks - 1u;
+    if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
+__device__ inline void wait_for_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }    // vmcnt(0), the other counters as they are
+
+// The same sums, bit for bit, for calls of many tiles: a tile per wave, the data straight from the caches into registers, no barrier.
+// Bound: the matrix cores again, in whose 64 cycles the vector unit of the same SIMD does nothing: every other instruction comes on
+// top (measured: 66 cycles alone, 73 with one conversion from float beside it, 80 with two).  direct_gram has one conversion per
+// matrix instruction and more around it, this one 40 instructions per 64 of them, and leaves out the sub-tiles below the diagonal.
+// The last wave of a tile adds the partial tiles up beside the matrix instructions of the other wave on its SIMD.
+// 64 x (512 x 4608): 1325 us, of direct_gram and direct_gram_sum 1381 + 144; without the sums, which direct_gram_sum then takes 138 us
+// for, 1233.  Wide matrices (rows of A contiguous) whose chunks are whole 16s of columns.  A wave takes a tile of a chunk
+// of 576 columns 63 us or, two on a SIMD, twice that, so the call has to have many (WIDE_MIN).
+// (The same hand-over in place of direct_gram_sum behind direct_gram: 64 x 576 14.4 -> 16.9 us, the ResNet-18 layers 124 -> 139:
+// stores of agent scope write through.)
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool SAME>
+__device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, unsigned* tickets, int lane)
+{
+    const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
+    const size_t chunk_size = (size_t)ntiles * (TILE * TILE);
+    const Global<double> part = global(m.part) + (size_t)tile * (TILE * TILE);
+    const long long ld = m.ldg;
+    const int c0 = chunk * m.kchunk, cols = min(m.M - c0, m.kchunk);
+    const Global<const float> A = global(m.G) + (long long)(ti * TILE - m.pad) * ld + c0;
+    const Global<const float> B = global(m.G) + (long long)(tj * TILE - m.pad) * ld + c0;
+    const int l16 = lane & 15, q = lane >> 4;
+    const unsigned offset = 4u * ((unsigned)l16 * (unsigned)ld + 4u * q);
+    doublex4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    floatx4 a[4], b[4];
+    // lane (l16, q): columns c + 4 q .. c + 4 q + 3 of rows 16 i + l16
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = *(Global<const floatx4_any>)((Global<const char>)(A + 16 * i * ld + c) + offset);
+            if (!SAME) b[i] = *(Global<const floatx4_any>)((Global<const char>)(B + 16 * i * ld + c) + offset);
+        }
+    };
+    fetch(0);
+    for (int c = 0; c < cols; c += 16) {
+        double da[4][4], db[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                da[i][x] = (double)a[i][x];
+                db[i][x] = SAME ? da[i][x] : (double)b[i][x];
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(min(c + 16, cols - 16));
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = SAME ? i : 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[i][x], db[j][x], acc[i][j], 0, 0, 0);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = SAME ? i : 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) put_part(part + chunk * chunk_size + (16 * i + 4 * v + q) * TILE + 16 * j + l16, acc[i][j][v]);
+    wait_for_stores();
+    int last = 0;
+    if (lane == 0) last = last_chunk(m, tickets, tile);
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    // (all loads of a partial tile in flight at once, beside the matrix instructions of the other wave)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = SAME ? i : 0; j < 4; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int c = 0; c < m.nchunks; ++c) {
+        doublex4 t[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = SAME ? i : 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) t[i][j][v] = get_part((Global<const double>)part + c * chunk_size + (16 * i + 4 * v + q) * TILE + 16 * j + l16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = SAME ? i : 0; j < 4; ++j) acc[i][j] += t[i][j];
+    }
+    const int N = m.nt * TILE;
+    const Global<double> C = global(m.C);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = SAME ? i : 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * i + 4 * v + q, col = 16 * j + l16;
+                C[(size_t)(ti * TILE + row) * N + tj * TILE + col] = acc[i][j][v];
+                if (!SAME || i != j) C[(size_t)(tj * TILE + col) * N + ti * TILE + row] = acc[i][j][v];
+                if (SAME && i == j && row == col) m.diag[ti * TILE + row] = acc[i][j][v];
+            }
+    if (SAME && ti == 0) clear_for_steps(m, lane, 64);
+}
+
+__global__ __launch_bounds__(256, 2) void direct_gram_wide(const DirectMat* mats, const Work* work, int n, unsigned* tickets)
+{
+    const int item = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (item >= n) return;
+    const Work wk = work[item];
+    if (wk.mat < 0) return;
+    const DirectMat& m = mats[wk.mat];
+    const int lane = threadIdx.x & 63;
+    if (wk.a == wk.b) wide_tile<true>(m, wk.a, wk.b, wk.c, tickets, lane);
+    else wide_tile<false>(m, wk.a, wk.b, wk.c, tickets, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1654,7 +1793,11 @@ void plan_matrix(Carver& carve, DirectMat& m)
 void plan_work(DirectPlan& plan)
 {
     size_t eigenvalues = 0;
-    for (const DirectMat& m : plan.mats) eigenvalues += (size_t)m.r;
+    for (DirectMat& m : plan.mats) {
+        eigenvalues += (size_t)m.r;
+        m.first_tile = (int)plan.n_tiles;
+        plan.n_tiles += (size_t)m.nt * (m.nt + 1) / 2;
+    }
     // lanes per eigenvalue in the search: as many as one wave on every SIMD has (the search is bound by instruction issue:
     // with a few more than that, on some SIMDs two waves, it took twice as long)
     plan.eig_lanes = 64;
@@ -1679,6 +1822,26 @@ void plan_work(DirectPlan& plan)
     }
     plan.n_eig = plan.eig.size();
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
+    if (plan.gram.size() >= WIDE_MIN) {
+        // A die works on the tiles of one chunk of columns of one matrix at a time, whose rows they share; the cheaper tiles
+        // on the diagonal at the end, where an item more or less on a SIMD sets when the launch ends.
+        auto whole = [&](const Work& w) {
+            const DirectMat& m = plan.mats[w.mat];
+            return !m.transposed && m.M % 16 == 0 && (m.pad == 0 || w.a > 0) && m.ldg < 1 << 24;
+        };
+        std::vector<Work> wide[2];
+        for (const Work& w : plan.gram)
+            if (whole(w)) wide[w.a == w.b].push_back(w);
+        for (auto* list : {&plan.gram, &plan.tiles}) list->erase(std::remove_if(list->begin(), list->end(), whole), list->end());
+        for (auto& list : wide) {
+            std::stable_sort(list.begin(), list.end(), [](const Work& x, const Work& y) { return x.mat != y.mat ? x.mat < y.mat : x.c < y.c; });
+            std::vector<std::array<Work, 4>> fours((list.size() + 3) / 4);
+            for (auto& f : fours) f.fill(Work{-1, 0, 0, 0});
+            for (size_t k = 0; k < list.size(); ++k) fours[k / 4][k % 4] = list[k];
+            deal_to_dies(fours);
+            for (const auto& f : fours) plan.gram_wide.insert(plan.gram_wide.end(), f.begin(), f.end());
+        }
+    }
     // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].r > plan.mats[b].r; });
     // Twice the workgroups for matrices of 257 to 512 rows, if every workgroup of the call has a compute unit to itself then: four of
@@ -1707,8 +1870,12 @@ void plan_work(DirectPlan& plan)
 void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream)
 {
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
-    direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
-    direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
+    if (!plan.gram.empty()) {
+        direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
+        direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
+    }
+    if (!plan.gram_wide.empty())
+        direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size(), t.tickets);
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
     if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);

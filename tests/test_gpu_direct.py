@@ -122,6 +122,29 @@ def test_many_matrices_in_one_call_give_the_bits_of_calls_of_their_own():
     assert ctx().status()[0] == 0
 
 
+def test_calls_of_many_gram_tiles_give_the_bits_of_calls_of_their_own():
+    """From 8192 work items of the Gram product on, whole tiles of wide matrices are a wave's; tall, padded and odd ones beside them."""
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    shapes = [(512, 1152)] * 30 + [(1152, 512), (500, 1024), (512, 1001), (449, 1040), (64, 640)]
+    mats = []
+    for m, n in shapes:
+        wide = torch.randn(m, n + 3, generator=gen, device="cuda") * 0.01
+        wide[0] *= 40.0
+        mats.append(wide[:, 1:n + 1])                            # rows that start anywhere
+    total = sum(min(s) for s in shapes)
+    sigma = torch.zeros(total, device="cuda")
+    many = binding.atomo_encode_svd(ctx(), mats, 3.0, 4, 70, sigma_out=sigma)
+    assert ctx().status()[0] == 0 and route(len(shapes)) == [DIRECT] * len(shapes)
+    for j in (0, 13, 29, 30, 31, 32, 33, 34):
+        r, at = min(shapes[j]), sum(min(s) for s in shapes[:j])
+        own = torch.zeros(r, device="cuda")
+        one = binding.atomo_encode_svd(ctx(), [mats[j]], 3.0, 4, 70 + j, sigma_out=own)[0]
+        assert ctx().status()[0] == 0
+        assert torch.equal(own, sigma[at:at + r])
+        a, b = one.to_host(), many[j].to_host()
+        assert a["count"] == b["count"] and all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")), j
+
+
 def test_a_training_loop_enqueues_the_direct_encode_alone_until_it_falls_short():
     shape = (200, 260)
     rng = np.random.default_rng(0)
