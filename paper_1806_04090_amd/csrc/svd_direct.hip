@@ -1125,36 +1125,50 @@ __device__ inline void block_factor(const DirectMat& m, int b)
 // ------------------------------------------------------------------------------------------------
 // How many eigenvalues of T lie below z: sign changes of the characteristic polynomials of the leading blocks,
 // p_{i+1} = (d_i - z) p_i - e_{i-1}^2 p_{i-1} (no division; rescaled by a power of two every eight steps, the squared
-// off-diagonals are kept above 2^-110 so that eight steps stay inside the range).  T comes through scalar loads, four
-// entries (e_{i-1}^2, d_i) at a time; the padding in front, (0, 2), leaves the sign as it is.  Four instructions per step.
+// off-diagonals are kept above 2^-110 so that eight steps stay inside the range).  T comes through scalar loads, eight
+// entries (e_{i-1}^2, d_i) at a time, the next eight on their way while these are worked on (27 cycles per step, 38 when a step of
+// sixteen entries waits for its own); the padding in front, (0, 2), leaves the sign as it is.  Four instructions per step.
 typedef unsigned uintx16 __attribute__((ext_vector_type(16)));
 typedef const uintx16 __attribute__((address_space(4)))* scalar_ptr;   // read through the scalar cache, never written here
 
+__device__ inline void sturm_steps(const uintx16& a, const uintx16& b, double z, double& p0, double& p1, unsigned& signs)
+{
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const uintx16& w = u < 4 ? a : b;
+        const int x = 4 * (u & 3);
+        const double p2 = fma(mk64(w[x + 2], w[x + 3]) - z, p1, -(mk64(w[x], w[x + 1]) * p0));
+        p0 = p1;
+        p1 = p2;
+        signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+    }
+    // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
+    const unsigned e = max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u);
+    const double scale = mk64(0u, 0x7fd00000u - e);
+    p0 *= scale;
+    p1 *= scale;
+}
 __device__ inline int sturm_count(scalar_ptr t, int n, double z)
 {
     double p0 = 0.0, p1 = 1.0;
     int count = 0;
     unsigned signs = 0;
+    uintx16 a0 = t[0], a1 = t[1];
     for (int i = 0; i < n; i += 16) {
-        uintx16 e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) e[u] = t[i / 4 + u];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uintx16& w = e[2 * h + u / 4];
-                const int x = 4 * (u & 3);
-                const double p2 = fma(mk64(w[x + 2], w[x + 3]) - z, p1, -(mk64(w[x], w[x + 1]) * p0));
-                p0 = p1;
-                p1 = p2;
-                signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
-            }
-            const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-            p0 = __builtin_amdgcn_ldexp(p0, -ex);
-            p1 = __builtin_amdgcn_ldexp(p1, -ex);
-        }
+        // (a wait for scalar loads is one for all of them: the next go out behind it)
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(a0), "+s"(a1));
+        uintx16 b0 = t[i / 4 + 2], b1 = t[i / 4 + 3];
+        __builtin_amdgcn_sched_barrier(0);
+        sturm_steps(a0, a1, z, p0, p1, signs);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(b0), "+s"(b1));
+        const int next = i + 16 < n ? i / 4 + 4 : 0;
+        a0 = t[next];
+        a1 = t[next + 1];
+        __builtin_amdgcn_sched_barrier(0);
+        sturm_steps(b0, b1, z, p0, p1, signs);
         count += __popc((signs ^ (signs >> 1)) & 0xffffu);
+        __builtin_amdgcn_sched_barrier(0);
     }
     return count;
 }
@@ -1792,16 +1806,19 @@ void plan_matrix(Carver& carve, DirectMat& m)
 
 void plan_work(DirectPlan& plan)
 {
-    size_t eigenvalues = 0;
+    size_t steps = 0, longest = 0;                               // of the recurrence, one point for every eigenvalue; of one
     for (DirectMat& m : plan.mats) {
-        eigenvalues += (size_t)m.r;
+        steps += (size_t)m.r * m.nt;
+        longest = std::max(longest, (size_t)m.nt);
         m.first_tile = (int)plan.n_tiles;
         plan.n_tiles += (size_t)m.nt * (m.nt + 1) / 2;
     }
-    // lanes per eigenvalue in the search: as many as one wave on every SIMD has (the search is bound by instruction issue:
-    // with a few more than that, on some SIMDs two waves, it took twice as long)
-    plan.eig_lanes = 64;
-    while (plan.eig_lanes > 4 && eigenvalues * plan.eig_lanes > 1024 * 64) plan.eig_lanes /= 2;
+    // Lanes per eigenvalue in the search, which is bound by instruction issue: as many as one wave on every SIMD has, that is
+    // as keep all SIMDs busy for one recurrence of the largest matrix (the smaller ones share a SIMD; by the number of eigenvalues
+    // alone the ResNet-18 layers got 8 lanes and half of the SIMDs, nine passes instead of eight: 71 -> 67 us).  64 lanes would
+    // take as many passes as 32.
+    plan.eig_lanes = 32;
+    while (plan.eig_lanes > 4 && steps * plan.eig_lanes > 1024 * 64 * longest) plan.eig_lanes /= 2;
     std::vector<Work> factors;
     std::vector<int> order(plan.mats.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = (int)j;
