@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 namespace atomo {
 
@@ -50,6 +51,21 @@ __device__ inline double dpp(double x)
     const unsigned a = (unsigned)__builtin_amdgcn_mov_dpp((int)lo32(x), CTRL, 0xf, 0xf, true);
     const unsigned b = (unsigned)__builtin_amdgcn_mov_dpp((int)hi32(x), CTRL, 0xf, 0xf, true);
     return mk64(a, b);
+}
+// what lane L of the lane's row of 16 holds (both halves in one instruction: the only control that 64-bit moves have)
+template <int L>
+__device__ inline double row_lane(double x)
+{
+    return __longlong_as_double((long long)__builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + L, 0xf, 0xf, true));
+}
+// f(integral_constant 0) .. f(integral_constant 15)
+template <int L = 0, typename F>
+__device__ inline void for_lanes(F&& f)
+{
+    if constexpr (L < 16) {
+        f(std::integral_constant<int, L>());
+        for_lanes<L + 1>(f);
+    }
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
 

@@ -1291,37 +1291,162 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
 // from the bottom (wave 1) as quotients of the characteristic polynomials of the leading and of the trailing blocks,
 // twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and the next round starts
 // from there, until the residual is small enough (KEPT_APART).  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
-// vector and those columns of V.  Bound: latency, two chains of n steps and then N / 16 blocks with one barrier each, whose V comes
-// from memory: two blocks are on their way while one is worked on (64 KB each at 512 rows: with one, a block took 4 us), the
-// factors of all blocks are in LDS before the first.
+// vector and those columns of V; a wave joins in at the first block that reaches its columns.
+// Bound: latency.  One atom of 512 rows: two rounds of 512 steps 21 us, the vectors from them 8, N / 16 blocks with one barrier
+// each 28: the sums of 16 products over a wave and over the waves, the factor, V from memory (64 KB per block, two blocks
+// on their way while one is worked on).  The ResNet-18 layers 64 us, 64 matrices of 512 rows 143, 64 x 576 17.5; with loads of T and
+// of V that were waited for when they went out, and broadcasts through v_readlane, 90, 196 and 23.
 // Work: matrix, slot.
 constexpr int VEC_THREADS = VMAX / 2;
 constexpr int VEC_ROUNDS = 5;    // two as a rule; three to five for atoms that share a cluster with another kept one
 constexpr int FLD = RB + 1;      // row stride of a factor in LDS
 constexpr int VEC_LDS = VMAX * FLD * (int)sizeof(double);
 
-__global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat* mats, const Work* work)
-{
+// What a workgroup works out its eigenvector of T from.
+struct Twist {
+    // T from the top, padding in front, and from the bottom, padding behind (two steps' worth of eight: loads run ahead)
+    double2 T[2][VMAX + 16];
+    double E[VMAX + 1];                      // couplings of the r rows: E[i] between i - 1 and i, zero at both ends
     // characteristic polynomials of the leading blocks ([0], in units of index + 1) and of the trailing ones ([1]), every
     // pair of neighbours in one scale except where `B` holds the first of the pair in the scale of the second
+    double P[2][VMAX + 17], B[2][VMAX / 8 + 2];
+    double X[VMAX];                          // the vector
+    double lam, scale;                       // the Rayleigh quotient; what X is to be multiplied by, 0: another round, negative: not accepted
+
+    // P and B of one direction, by one lane: three instructions per step, eight entries of T on their way while eight are
+    // worked on (75 cycles per step when they were waited for, 48 now: the LDS traffic of one lane)
+    __device__ inline void polynomials(int dir, int n_pad, double lam)
+    {
+        const double2* t = T[dir];
+        double* out = P[dir];
+        double* bound = B[dir];
+        double p0 = 0.0, p1 = 1.0;
+        out[0] = 1.0;
+        auto eight = [&](const double2 (&e)[8], int i) {
+            double step[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                step[u] = fma(e[u].y - lam, p1, -(e[u].x * p0));
+                p0 = p1;
+                p1 = step[u];
+            }
+            // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
+            const unsigned x = max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u);
+            const double scale = mk64(0u, 0x7fd00000u - x);
+            p0 *= scale;
+            p1 *= scale;
+            step[7] = p1;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) out[i + 1 + u] = step[u];
+            bound[i >> 3] = p0;
+        };
+        double2 a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = t[u];
+        for (int i = 0; i < n_pad; i += 16) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) b[u] = t[i + 8 + u];
+            __builtin_amdgcn_sched_barrier(0);
+            eight(a, i);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[u] = t[i + 16 + u];
+            __builtin_amdgcn_sched_barrier(0);
+            eight(b, i + 8);
+        }
+    }
+
+    // The vector, by one wave: lane l the entries l per .. of it, per <= PER.
+    template <int PER>
+    __device__ inline void vector(int n, int skip, double lambda, double good, const KeptApart& apart, bool last, int lane)
+    {
+        // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet with the smallest pivot
+        const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
+        double d[PER], e_up[PER], e_dn[PER], top[PER], bot[PER], best = 1e300, gamma = 0.0;
+        int at = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int i = min(i0 + u, n - 1), s = skip + i, j = n - 1 - i;    // s, j: steps that made them
+            d[u] = T[0][s].y;
+            e_up[u] = E[i];
+            e_dn[u] = E[i + 1];
+            top[u] = P[0][s + 1] * reciprocal((s & 7) == 7 ? B[0][s >> 3] : P[0][s]);
+            bot[u] = P[1][j + 1] * reciprocal((j & 7) == 7 ? B[1][j >> 3] : P[1][j]);
+            const double g = top[u] + bot[u] - (d[u] - lambda);
+            if (i0 + u < i1 && fabs(g) < best) { best = fabs(g); gamma = g; at = i; }
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const double ob = __shfl_xor(best, o), og = __shfl_xor(gamma, o);
+            const int oa = __shfl_xor(at, o);
+            if (ob < best || (ob == best && oa < at)) { best = ob; gamma = og; at = oa; }
+        }
+        // entries from the twist outwards: products of -e_i / top_i downwards and of -e_{i-1} / bottom_i upwards,
+        // per lane over its own entries, then over the lanes
+        double f[PER], up = 1.0, down = 1.0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int i = i0 + u;
+            const bool before = i < at;
+            const double x = (before ? -e_dn[u] : -e_up[u]) * reciprocal(before ? top[u] : bot[u]);
+            f[u] = i < i1 && i != at ? x : 1.0;
+            down *= before ? f[u] : 1.0;
+            up *= before ? 1.0 : f[u];
+        }
+        double up_before = up, down_after = down;
+        for (int o = 1; o < 64; o <<= 1) {
+            const double x = __shfl_up(up_before, o), y = __shfl_down(down_after, o);
+            if (lane >= o) up_before *= x;
+            if (lane + o < 64) down_after *= y;
+        }
+        up_before = __shfl_up(up_before, 1);
+        down_after = __shfl_down(down_after, 1);
+        if (lane == 0) up_before = 1.0;
+        if (lane == 63) down_after = 1.0;
+        double x[PER], sq = 0.0, weight = 0.0, run = up_before;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (i0 + u >= at) run *= f[u];
+            x[u] = run;
+        }
+        run = down_after;
+#pragma unroll
+        for (int u = PER - 1; u >= 0; --u) {
+            if (i0 + u < at) {
+                run *= f[u];
+                x[u] = run;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const bool in = i0 + u < i1;
+            const double z2 = in ? x[u] * x[u] : 0.0;
+            if (in) X[i0 + u] = x[u];
+            sq += z2;
+            weight = fma(z2, fabs(d[u]) + (fabs(e_up[u]) + fabs(e_dn[u])), weight);
+        }
+        const double norm2 = wave_sum(sq), inv = reciprocal(norm2), size = root(norm2), res = fabs(gamma) * reciprocal(size);    // |T x - lam x| / |x|
+        weight = wave_sum(weight) * inv;
+        lambda = fma(gamma, inv, lambda);                        // Rayleigh quotient
+        // over: the residual is small enough, or it never will be (the eigenvalue was not separated from that of
+        // another kept atom, or the factorisation broke down)
+        if (lane == 0) {
+            lam = lambda;
+            scale = res <= (last ? 100.0 * good : good) && apart.vector(res, weight, lambda) ? reciprocal(size)
+                    : last || !apart.possible ? -1.0 : 0.0;
+        }
+    }
+};
+
+__global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat* mats, const Work* work)
+{
     extern __shared__ double fact[];
-    __shared__ double2 T[2][VMAX + 8];       // T from the top, padding in front, and from the bottom, padding behind
-    __shared__ double P[2][VMAX + 17], B[2][VMAX / 8 + 2], X[VMAX], part[2][VEC_THREADS / 64][RB], red[VEC_THREADS / 64];
-    __shared__ double s_scale;
+    __shared__ Twist tw;
+    __shared__ double part[2][VEC_THREADS / 64][RB], red[VEC_THREADS / 64];
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
     const int slot = wk.a, tid = threadIdx.x, lane = tid & 63, n = m.r, nthr = blockDim.x, nw = nthr >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (slot >= min(*m.count, m.capacity)) return;
     const int N = m.nt * TILE, pad = m.pad;
-    {
-        const Global<const doublex2> in = (Global<const doublex2>)global((const double*)m.fact);
-        for (int i = tid; i < N * RB / 2; i += nthr) {
-            const doublex2 x = in[i];
-            fact[i / 8 * FLD + 2 * (i & 7)] = x.x;
-            fact[i / 8 * FLD + 2 * (i & 7) + 1] = x.y;
-        }
-    }
     // its eigenvalue and those of the kept atoms beside it, all three on their way at once (an entry that is not there is
     // not used, whatever it is)
     double own[3];
@@ -1334,175 +1459,77 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
     const KeptApart apart(lam, slot > 0 ? own[0] : -1.0, slot + 1 < min(*m.count, m.capacity) ? own[2] : -1.0,
                           4.0 / (double)(1 << LAM_BITS));
     const double good = 1e-14 * m.lam[0];
-    // what wave 0 needs of T: its lane's entries
-    constexpr int PER = VMAX / 64;
-    const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
-    double d[PER], e_up[PER], e_dn[PER];                         // diagonal, coupling to the entry before, to the one after
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int i = i0 + u;
-        const bool in = wave == 0 && i < i1;
-        d[u] = in ? global((const double*)m.td)[2 * (pad + i) + 1] : 0.0;
-        e_up[u] = in && i > 0 ? global((const double*)m.od)[pad + i - 1] : 0.0;
-        e_dn[u] = in && i + 1 < n ? global((const double*)m.od)[pad + i] : 0.0;
-    }
     const int first = pad & ~15, n_pad = N - first;
     for (int i = tid; i < n_pad; i += nthr) {
         const doublex2 t = ((Global<const doublex2>)global((const double*)m.td))[first + i];
-        T[0][i] = make_double2(t.x, t.y);
-        T[1][n_pad - 1 - i].y = t.y;
-        T[1][n_pad - i].x = t.x;                                 // (the coupling to the entry before comes a step later)
+        tw.T[0][i] = make_double2(t.x, t.y);
+        tw.T[1][n_pad - 1 - i].y = t.y;
+        tw.T[1][n_pad - i].x = t.x;                              // (the coupling to the entry before comes a step later)
     }
-    if (tid < 8) {
-        T[0][n_pad + tid] = make_double2(0.0, 2.0);
-        if (tid > 0) T[1][n_pad + tid].x = 0.0;
-        T[1][n_pad + tid].y = 2.0;
+    for (int i = tid; i <= n; i += nthr) tw.E[i] = i > 0 && i < n ? global((const double*)m.od)[pad + i - 1] : 0.0;
+    if (tid < 16) {
+        tw.T[0][n_pad + tid] = make_double2(0.0, 2.0);
+        if (tid > 0) tw.T[1][n_pad + tid].x = 0.0;
+        tw.T[1][n_pad + tid].y = 2.0;
     }
-    if (tid == 0) T[1][0].x = 0.0;
+    if (tid == 0) tw.T[1][0].x = 0.0;
     __syncthreads();
-    for (int round = 0; round < VEC_ROUNDS; ++round) {
-        if (wave < 2 || nw == 1) {
-            // wave 0 the leading blocks, wave 1 the trailing ones (a workgroup of one wave: both)
-            for (int dir = nw == 1 ? 0 : wave; dir < (nw == 1 ? 2 : wave + 1); ++dir) {
-                const double2* t = T[dir];
-                double* out = P[dir];
-                double* bound = B[dir];
-                if (lane == 0) {
-                    double p0 = 0.0, p1 = 1.0;
-                    out[0] = 1.0;
-                    double2 next[8];
+    // the factors, wanted behind the rounds, by the waves that have nothing else to do
+    if (wave >= 2 || nw <= 2) {
+        const Global<const doublex2> in = (Global<const doublex2>)global((const double*)m.fact);
+        const int self = nw <= 2 ? tid : tid - 128, step = nw <= 2 ? nthr : nthr - 128;
+        for (int i0 = self; i0 < N * RB / 2; i0 += 8 * step) {
+            doublex2 x[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) next[u] = t[u];
-                    for (int i = 0; i < n_pad; i += 8) {
-                        double2 now[8];
-                        double step[8];
+            for (int u = 0; u < 8; ++u) x[u] = in[min(i0 + u * step, N * RB / 2 - 1)];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) now[u] = next[u];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) next[u] = t[i + 8 + u];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            step[u] = fma(now[u].y - lam, p1, -(now[u].x * p0));
-                            p0 = p1;
-                            p1 = step[u];
-                        }
-                        const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-                        p0 = __builtin_amdgcn_ldexp(p0, -ex);
-                        p1 = __builtin_amdgcn_ldexp(p1, -ex);
-                        step[7] = p1;
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) out[i + 1 + u] = step[u];
-                        bound[i >> 3] = p0;
-                    }
+            for (int u = 0; u < 8; ++u) {
+                const int i = i0 + u * step;
+                if (i < N * RB / 2) {
+                    fact[i / 8 * FLD + 2 * (i & 7)] = x[u].x;
+                    fact[i / 8 * FLD + 2 * (i & 7) + 1] = x[u].y;
                 }
             }
+        }
+    }
+    for (int round = 0; round < VEC_ROUNDS; ++round) {
+        // wave 0 the leading blocks, wave 1 the trailing ones (a workgroup of one wave: both)
+        if (lane == 0 && wave < 2) {
+            tw.polynomials(wave, n_pad, lam);
+            if (nw == 1) tw.polynomials(1, n_pad, lam);
         }
         __syncthreads();
         if (wave == 0) {
-            // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet with the smallest pivot
-            double top[PER], bot[PER], best = 1e300, gamma = 0.0;
-            int at = 0;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = i0 + u;
-                top[u] = bot[u] = 1.0;
-                if (i < i1) {
-                    const int s = pad - first + i, j = n - 1 - i;    // steps that made them
-                    top[u] = P[0][s + 1] * reciprocal((s & 7) == 7 ? B[0][s >> 3] : P[0][s]);
-                    bot[u] = P[1][j + 1] * reciprocal((j & 7) == 7 ? B[1][j >> 3] : P[1][j]);
-                    const double g = top[u] + bot[u] - (d[u] - lam);
-                    if (fabs(g) < best) { best = fabs(g); gamma = g; at = i; }
-                }
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const double ob = __shfl_xor(best, o), og = __shfl_xor(gamma, o);
-                const int oa = __shfl_xor(at, o);
-                if (ob < best || (ob == best && oa < at)) { best = ob; gamma = og; at = oa; }
-            }
-            // entries from the twist outwards: products of -e_i / top_i downwards and of -e_{i-1} / bottom_i upwards,
-            // per lane over its own entries, then over the lanes
-            double f[PER], up = 1.0, down = 1.0;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = i0 + u;
-                f[u] = 1.0;
-                if (i < i1) {
-                    f[u] = i < at ? -e_dn[u] * reciprocal(top[u]) : i > at ? -e_up[u] * reciprocal(bot[u]) : 1.0;
-                    if (i < at) down *= f[u]; else up *= f[u];
-                }
-            }
-            double up_before = up, down_after = down;
-            for (int o = 1; o < 64; o <<= 1) {
-                const double x = __shfl_up(up_before, o), y = __shfl_down(down_after, o);
-                if (lane >= o) up_before *= x;
-                if (lane + o < 64) down_after *= y;
-            }
-            up_before = __shfl_up(up_before, 1);
-            down_after = __shfl_down(down_after, 1);
-            if (lane == 0) up_before = 1.0;
-            if (lane == 63) down_after = 1.0;
-            double sq = 0.0, weight = 0.0, run = up_before;
-            auto add = [&](int u) {
-                const double z2 = run * run;
-                sq += z2;
-                weight = fma(z2, fabs(d[u]) + (fabs(e_up[u]) + fabs(e_dn[u])), weight);
-            };
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = i0 + u;
-                if (i < i1 && i >= at) {
-                    run *= f[u];
-                    X[i] = run;
-                    add(u);
-                }
-            }
-            run = down_after;
-#pragma unroll
-            for (int u = PER - 1; u >= 0; --u) {
-                const int i = i0 + u;
-                if (i < i1 && i < at) {
-                    run *= f[u];
-                    X[i] = run;
-                    add(u);
-                }
-            }
-            const double norm2 = wave_sum(sq), res = fabs(gamma) / sqrt(norm2);    // |T x - lam x| / |x|
-            weight = wave_sum(weight) * reciprocal(norm2);
-            lam += gamma / norm2;                                // Rayleigh quotient
-            // over: the residual is small enough, or it never will be (the eigenvalue was not separated from that of
-            // another kept atom, or the factorisation broke down)
-            if (lane == 0) {
-                const bool last = round == VEC_ROUNDS - 1;
-                red[0] = lam;
-                s_scale = res <= (last ? 100.0 * good : good) && apart.vector(res, weight, lam) ? 1.0 / sqrt(norm2)
-                          : last || !apart.possible ? -1.0 : 0.0;
-            }
+            const bool last = round == VEC_ROUNDS - 1;
+            const int skip = pad - first;
+            if (n <= 64) tw.vector<1>(n, skip, lam, good, apart, last, lane);
+            else if (n <= 128) tw.vector<2>(n, skip, lam, good, apart, last, lane);
+            else if (n <= 256) tw.vector<4>(n, skip, lam, good, apart, last, lane);
+            else if (n <= 512) tw.vector<8>(n, skip, lam, good, apart, last, lane);
+            else tw.vector<VMAX / 64>(n, skip, lam, good, apart, last, lane);
         }
         __syncthreads();
-        lam = red[0];
-        if (s_scale != 0.0) break;
+        lam = tw.lam;
+        if (tw.scale != 0.0) break;
         __syncthreads();
     }
     // back through H
     const int c0 = 2 * tid;                                      // this thread's entries: c0, c0 + 1
     struct Block { doublex2 v[RB]; };
+    // (no branch around the loads: behind one, the wait for an older block would be one for all of them)
     auto fetch = [&](int blk, Block& at) {
-        if (2 * wave + 1 >= blk * RB / 64) {                     // (uniform: the wave's 128 columns are not all finished)
-            const Global<const double> row = global((const double*)m.refl) + (size_t)max(blk, 0) * RB * N + min(c0, N - 2);
+        const Global<const char> row = (Global<const char>)(global((const double*)m.refl) + (size_t)max(blk, 0) * RB * N);
+        const unsigned offset = 8u * (unsigned)min(c0, N - 2);
 #pragma unroll
-            for (int j = 0; j < RB; ++j) at.v[j] = *(Global<const doublex2>)(row + (size_t)j * N);
-        } else {
-#pragma unroll
-            for (int j = 0; j < RB; ++j) at.v[j] = doublex2{0.0, 0.0};
-        }
+        for (int j = 0; j < RB; ++j) at.v[j] = *(Global<const doublex2>)(row + (size_t)j * N * 8 + offset);
     };
-    const double scale = s_scale;
+    const double scale = tw.scale;
     if (tid == 0 && !(scale > 0.0)) {
         m.st[DS_ACCEPT] = 0;
         m.st[DS_BROKEN] = 1;
     }
-    double y0 = c0 >= pad && c0 < N ? X[c0 - pad] * scale : 0.0;
-    double y1 = c0 + 1 >= pad && c0 < N ? X[c0 + 1 - pad] * scale : 0.0;
+    double y0 = c0 >= pad && c0 < N ? tw.X[c0 - pad] * scale : 0.0;
+    double y1 = c0 + 1 >= pad && c0 < N ? tw.X[c0 + 1 - pad] * scale : 0.0;
     const int last = (N - 3) / RB, first_block = pad / RB;
     auto apply = [&](int b, const Block& at) {
         double prod[RB];
@@ -1516,25 +1543,36 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
             pt[wave][8 + sum_slot(lane)] = hi;
         }
         __syncthreads();
-        double sum = 0.0;                                        // lane j: the product of vector j with y
+        double sum = 0.0;                                        // lane j of a row of 16: the product of vector j with y
 #pragma unroll
         for (int w = 0; w < VEC_THREADS / 64; ++w) sum += w < nw ? pt[w][lane & 15] : 0.0;
-        double t = 0.0;
-#pragma unroll
-        for (int j = 0; j < RB; ++j) t = fma(f[j], lane_value(sum, j), t);
-#pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const double tj = lane_value(t, j);
-            y0 = fma(-at.v[j].x, tj, y0);
-            y1 = fma(-at.v[j].y, tj, y1);
-        }
+        double t = 0.0, t_odd = 0.0;
+        for_lanes([&](auto j) {
+            constexpr int J = decltype(j)::value;
+            double& x = J & 1 ? t_odd : t;
+            x = fma(f[J], row_lane<J>(sum), x);
+        });
+        t += t_odd;
+        for_lanes([&](auto j) {
+            constexpr int J = decltype(j)::value;
+            const double tj = row_lane<J>(t);
+            y0 = fma(-at.v[J].x, tj, y0);
+            y1 = fma(-at.v[J].y, tj, y1);
+        });
         if (c0 >= N) y0 = y1 = 0.0;
     };
     {
+        // a wave joins in when its 128 columns are not all finished; the first two blocks from there are on their way by then
+        const int start = min(last, (2 * wave + 2) * 64 / RB - 1);
         Block a, c, e;
-        fetch(last, a);
-        fetch(last - 1, c);
-        for (int b = last;;) {
+        fetch(start, a);
+        fetch(start - 1, c);
+        int b = last;
+        for (; b > start; --b) {
+            if (lane < RB) part[b & 1][wave][lane] = 0.0;
+            __syncthreads();
+        }
+        for (;;) {
             fetch(b - 2, e);
             apply(b, a);
             if (--b < first_block) break;
