@@ -464,7 +464,7 @@ struct Gate {
 };
 
 constexpr int TAIL = 64;                                         // rows that a group leaves
-constexpr int ONE = 128, TS = ONE / 16, ONE_PHASE = 32;          // rows of TriOne; slots of 16; steps that run on the same slots
+constexpr int ONE = 128, TS = ONE / 16;                          // rows of TriOne; slots of 16
 
 // How a workgroup's part in a reduction ends: done; a wait of a step gave up; the group did not go on, and this workgroup was
 // the last of it to start, or not.
@@ -764,10 +764,11 @@ struct Tri {
 // One barrier per step.  What is handed over is (A y)_i, y the column below its first entry, and column k + 1 before the
 // step: the reflector v = y + v0 e_{k+1} is wanted only behind the barrier (A v = A y + v0 A e_{k+1}), so that the norm, the root
 // and the reciprocal run beside the products.
-// Bound: a step of 64 rows is a chain of about 250 instructions with one wave on every SIMD, 0.6 us; at 128 rows it is the issue of
-// 520, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix took 61 us with four waves that each owned columns and broadcast
-// through v_readlane, now 42.  What a group leaves is worked off by one compute unit instead of 16 or 32.
-constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROW_FIRST = 0x150;
+// Bound: a step of 64 rows is a chain of about 300 instructions with one wave on every SIMD, 0.55 us; at 128 rows it is the issue of
+// 550, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix took 61 us with four waves that each owned columns and broadcast
+// through v_readlane, now 39.5 (42.4 with steps in runs of 32 and two 32-bit moves per broadcast).  What a group leaves is worked
+// off by one compute unit instead of 16 or 32.
+constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124;
 
 // over the 16 lanes of a row, in every lane, the same bits for every rotation of the values
 __device__ inline double ring_sum(double x)
@@ -783,19 +784,19 @@ __device__ inline double fold_by(bool up, double a, double b, int which)
     const double keep = up ? b : a, give = up ? a : b;
     return keep + (which == 8 ? dpp<DPP_ROR8>(give) : which == 4 ? dpp<DPP_HALF_MIRROR>(give) : dpp<DPP_XOR2>(give));
 }
-// K = 2, 4, 6 or 8 sums over the 16 lanes of a row at once: lane l receives sum number (l >> 3 & 1) | (l >> 2 & 1) << 1 |
-// (l >> 1 & 1) << 2 (of as many bits as K needs)
+// K <= 8 sums over the 16 lanes of a row at once: lane l receives sum number (l >> 3 & 1) | (l >> 2 & 1) << 1 | (l >> 1 & 1) << 2,
+// of as many bits as K needs; there may be none of that number
 template <int K>
 __device__ inline double row_sums(const double (&v)[K], int lane)
 {
-    constexpr int K1 = K / 2, K2 = (K1 + 1) / 2;
+    constexpr int K1 = (K + 1) / 2, K2 = (K1 + 1) / 2;
     double a[K1], b[K2];
 #pragma unroll
-    for (int i = 0; i < K1; ++i) a[i] = fold_by(lane & 8, v[2 * i], v[2 * i + 1], 8);
-    if constexpr (K1 == 1) return sum8(a[0]);
+    for (int i = 0; i < K1; ++i) a[i] = 2 * i + 1 < K ? fold_by(lane & 8, v[2 * i], v[2 * i + 1 < K ? 2 * i + 1 : 0], 8) : v[2 * i] + dpp<DPP_ROR8>(v[2 * i]);
 #pragma unroll
-    for (int i = 0; i < K2; ++i) b[i] = fold_by(lane & 4, a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i], 4);
-    double c = K2 == 1 ? b[0] + dpp<DPP_XOR2>(b[0]) : fold_by(lane & 2, b[0], b[K2 - 1], 2);
+    for (int i = 0; i < K2; ++i)
+        b[i] = 2 * i + 1 < K1 ? fold_by(lane & 4, a[2 * i], a[2 * i + 1 < K1 ? 2 * i + 1 : 0], 4) : a[2 * i] + dpp<DPP_HALF_MIRROR>(a[2 * i]);
+    const double c = K2 == 1 ? b[0] + dpp<DPP_XOR2>(b[0]) : fold_by(lane & 2, b[0], b[K2 - 1], 2);
     return c + dpp<DPP_XOR1>(c);
 }
 template <int K>
@@ -807,69 +808,80 @@ __device__ inline int row_slot(int lane)
 struct TriOne {
     double a[TS][TS];
     double x[TS], v[TS], wv[TS];     // column k; the last step's vectors, which the matrix has still to be updated with
-    double2 (*shared)[ONE];          // [2][ONE] by step parity: A y and column k + 1
+    struct Step { double sum[ONE + 256], column[ONE]; };         // A y, and places for sums that are none; column k + 1
+    struct Kept { double tau, diagonal, beta; };
+    struct Scratch { Step step[2]; Kept kept[ONE]; };            // (by step parity)
+    Step* shared;                    // [2]
+    Kept* kept;
     int lane, wave, col, row;        // column and row of slot 0
     int off, first;                  // row i here is row i - off of the matrix; the first that is reduced here
 
     template <int S>
     __device__ inline void steps(int& k, const StepStore& store)
     {
-        constexpr int L = TS - S;
-        const int k_end = min(16 * S + ONE_PHASE, ONE - 2);
+        constexpr int L = TS - S, S1 = S + 1 < TS ? S + 1 : S;
+        const int k_end = min(16 * S + 16, ONE - 2);
         const bool pair = 16 * S < ONE / 2 ? off < 0 && (store.N / 64 & 1) : first > 0 && !(store.N / 64 & 1);
+        // where this lane's sum over a row goes (one that is none: to a place of its own)
+        const int t = row_slot<L>(lane);
+        const int sum_at = (lane & (L > 4 ? 1 : L > 2 ? 3 : L > 1 ? 7 : 15)) == 0 && t < L ? 16 * (S + t) + row : ONE + (int)threadIdx.x;
         for (; k < k_end; ++k) {
-            const int k1 = k + 1, s1 = k1 >> 4;                  // s1: S .. S + 2
-            double y[TS], sq = 0.0;
+            const int k1 = k + 1;
+            const bool next = S + 1 < TS && k1 == 16 * S1;       // row k + 1 is the first of slot S + 1
+            Step* sh = shared + (k & 1);
+            double sum[L], y[TS], sq = 0.0;
+            auto update = [&](int s) {
+                const double vr = row_lane<0>(v[s]), wr = row_lane<0>(wv[s]);
 #pragma unroll
-            for (int b = S; b < TS; ++b) {
-                y[b] = b > S + 2 || 16 * b + col > k1 ? x[b] : 0.0;
-                sq = fma(y[b], y[b], sq);
-            }
-            double sum[L];
+                for (int b = S; b < TS; ++b) a[s][b] = fma(-wr, v[b], fma(-vr, wv[b], a[s][b]));
+            };
+            // column k + 1 of the matrix, from the threads that hold that row
+            update(S);
+            if (S1 != S) update(S1);
+            if (wave == (k1 >> 2 & 3) && lane >> 4 == (k1 & 3)) {
+                if (!next) {
 #pragma unroll
-            for (int t = 0; t < L; ++t) {
-                const double vr = dpp<DPP_ROW_FIRST>(v[S + t]), wr = dpp<DPP_ROW_FIRST>(wv[S + t]);
-                sum[t] = 0.0;
+                    for (int b = S; b < TS; ++b) sh->column[16 * b + col] = a[S][b];
+                    asm volatile("" ::"n"(0));                   // (merged, the branches would put `a` into memory)
+                } else {
 #pragma unroll
-                for (int b = S; b < TS; ++b) {
-                    a[S + t][b] = fma(-wr, v[b], fma(-vr, wv[b], a[S + t][b]));
-                    sum[t] = fma(a[S + t][b], y[b], sum[t]);
+                    for (int b = S; b < TS; ++b) sh->column[16 * b + col] = a[S1][b];
+                    asm volatile("" ::"n"(1));
                 }
             }
-            double2* sh = shared[k & 1];
-            // column k + 1 of the matrix, from the threads that hold that row
-            if (wave == (k1 >> 2 & 3) && lane >> 4 == (k1 & 3)) {
 #pragma unroll
-                for (int t = 0; t < (L < 3 ? L : 3); ++t)
-                    if (s1 == S + t) {
-#pragma unroll
-                        for (int b = S; b < TS; ++b) sh[16 * b + col].y = a[S + t][b];
-                        asm volatile("" ::"n"(t));               // (merged, the branches would put `a` into memory)
-                    }
-            }
-            {
-                const double q = row_sums<L>(sum, lane);
-                const int t = row_slot<L>(lane);
-                if ((lane & (L > 4 ? 1 : L > 2 ? 3 : 7)) == 0 && t < L) sh[16 * (S + t) + row].x = q;
+            for (int b = S; b < TS; ++b) {
+                y[b] = b > S + 1 || 16 * b + col > k1 ? x[b] : 0.0;
+                sq = fma(y[b], y[b], sq);
             }
             const double sig2 = ring_sum(sq);
             const int from = (k1 - 4 * wave) & 15;               // the lane of row 0 that has column k + 1
-            const double x0 = lane_value(x[S], from), x1 = lane_value(x[S + 1], from), x2 = lane_value(x[S + 2 < TS ? S + 2 : S], from);
-            const double alpha = s1 == S ? x0 : s1 == S + 1 ? x1 : x2;
+            const double x0 = lane_value(x[S], from), x1 = lane_value(x[S1], from);
             double beta, v0;
-            householder(alpha, sig2, beta, v0);
+            householder(next ? x1 : x0, sig2, beta, v0);
             const double tau = householder_tau(sig2, v0);
 #pragma unroll
-            for (int b = S; b < TS; ++b) v[b] = b <= S + 2 && 16 * b + col == k1 ? v0 : y[b];
-            __syncthreads();
-            const double2 at_k1 = sh[k1];
-            double2 qc[TS];
+            for (int r = 0; r < L; ++r) {
+                if (S + r > S1) update(S + r);
+                sum[r] = 0.0;
 #pragma unroll
-            for (int b = S; b < TS; ++b) qc[b] = sh[16 * b + col];
-            // one wave keeps the step for the way back, with zeros in front (in the shadow of the loads)
+                for (int b = S; b < TS; ++b) sum[r] = fma(a[S + r][b], y[b], sum[r]);
+            }
+            sh->sum[sum_at] = row_sums<L>(sum, lane);
+#pragma unroll
+            for (int b = S; b < TS; ++b) v[b] = b <= S + 1 && 16 * b + col == k1 ? v0 : y[b];
+            __syncthreads();
+            const double q1 = sh->sum[k1], c1 = sh->column[k1];
+            double p[TS], c[TS];
+#pragma unroll
+            for (int b = S; b < TS; ++b) {
+                p[b] = sh->sum[16 * b + col];
+                c[b] = sh->column[16 * b + col];
+            }
+            // kept for the way back, with zeros in front (in the shadow of the loads, one wave the vector, one the rest)
             if (wave == (k & 3)) {
-                const int kk = k - off, rg = lane >> 4, at = (k - 4 * wave) & 15;
-                const Global<double> r = store.refl + (size_t)kk * store.N - off + 16 * rg + col;
+                const int rg = lane >> 4;
+                const Global<double> r = store.refl + (size_t)(k - off) * store.N - off + 16 * rg + col;
 #pragma unroll
                 for (int h = 0; h < TS / 4; ++h) {
                     double part[4];
@@ -879,33 +891,42 @@ struct TriOne {
                     if (64 * h >= first) r[64 * h] = rg & 2 ? odd : even;
                 }
                 if (pair) r[(16 * S < ONE / 2 ? 0 : 64) - 64] = 0.0;
-                const double d0 = lane_value(x[S], at), d1 = lane_value(x[S + 1], at);
-                if (lane == 0) store.put(kk, tau, k < 16 * (S + 1) ? d0 : d1, beta);
+            } else if (wave == (k + 2 & 3)) {
+                if (lane < 16 && col == (k & 15)) {
+                    kept[k].diagonal = x[S];
+                    kept[k].tau = tau;
+                    kept[k].beta = beta;
+                }
             }
-            double p[TS], gamma = 0.0;
+            double gamma = 0.0;
 #pragma unroll
             for (int b = S; b < TS; ++b) {
-                p[b] = fma(v0, qc[b].y, qc[b].x);
-                if (b <= S + 1 && 16 * b + col <= k) p[b] = 0.0;
-                x[b] = qc[b].y;
+                p[b] = fma(v0, c[b], p[b]);
+                if (b == S && 16 * b + col <= k) p[b] = 0.0;
                 gamma = fma(v[b], p[b], gamma);
             }
             gamma = ring_sum(gamma) * tau * (0.5 * tau);
-            const double wk1 = fma(-gamma, v0, tau * fma(v0, at_k1.y, at_k1.x));
+            const double wk1 = fma(-gamma, v0, tau * fma(v0, c1, q1));
 #pragma unroll
             for (int b = S; b < TS; ++b) {
                 wv[b] = fma(-gamma, v[b], tau * p[b]);
-                x[b] = fma(-wv[b], v0, fma(-v[b], wk1, x[b]));
+                x[b] = fma(-wv[b], v0, fma(-v[b], wk1, c[b]));
             }
         }
     }
-
-    __device__ inline void run(const DirectMat& m, double* lds)
+    template <int S>
+    __device__ inline void phases(int& k, const StepStore& store)
     {
-        static_assert(TS == 8 && ONE_PHASE == 32, "the phases below");
+        steps<S>(k, store);
+        if constexpr (S + 1 < TS) phases<S + 1>(k, store);
+    }
+
+    __device__ inline void run(const DirectMat& m, Scratch& lds)
+    {
         const StepStore store(m);
         const int N = store.N;
-        shared = (double2(*)[ONE])lds;
+        shared = lds.step;
+        kept = lds.kept;
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         row = 4 * wave + (lane >> 4);
@@ -939,15 +960,12 @@ struct TriOne {
             x[b] *= scale;
             v[b] = wv[b] = 0.0;
         }
-        if (first == 0) {
-            steps<0>(k, store);
-            steps<2>(k, store);
-        }
-        steps<4>(k, store);
-        steps<6>(k, store);
+        const int k_first = k;
+        if (first == 0) phases<0>(k, store);
+        else phases<TS / 2>(k, store);
         // what is left: the last 2 x 2 block
         if (row == 15) {
-            const double vr = dpp<DPP_ROW_FIRST>(v[TS - 1]), wr = dpp<DPP_ROW_FIRST>(wv[TS - 1]);
+            const double vr = row_lane<0>(v[TS - 1]), wr = row_lane<0>(wv[TS - 1]);
             const double d1 = fma(-wr, v[TS - 1], fma(-vr, wv[TS - 1], a[TS - 1][TS - 1]));
             if (col == 15) {
                 store.td[2 * N - 1] = d1;
@@ -958,6 +976,11 @@ struct TriOne {
                 store.tau[N - 2] = 0.0;
                 store.td[2 * N - 3] = x[TS - 1];
             }
+        }
+        __syncthreads();
+        if (k_first + (int)threadIdx.x < ONE - 2) {
+            const Kept& e = kept[k_first + threadIdx.x];
+            store.put(k_first + (int)threadIdx.x - off, e.tau, e.diagonal, e.beta);
         }
     }
 };
@@ -1042,13 +1065,14 @@ __device__ inline void tri_alone(const DirectMat& m, double* lds)
 __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* mats, const Work* work, long long start_ticks)
 {
     __shared__ double2 lds[2 * MAX_R];
+    static_assert(sizeof(lds) >= sizeof(TriOne::Scratch), "one workgroup's");
     const Work wk = work[blockIdx.x];
     if (wk.mat < 0) return;
     const DirectMat& m = mats[wk.mat];
     TriEnd end = TRI_DONE;
     switch (m.cls) {
         case CLS_64:
-        case CLS_128: { TriOne t; t.run(m, (double*)lds); } break;
+        case CLS_128: { TriOne t; t.run(m, *(TriOne::Scratch*)lds); } break;
         case CLS_256: { Tri<4, 4, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
         case CLS_512:
             if (wk.b == 32) { Tri<8, 4, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
@@ -1063,10 +1087,10 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
 // What the groups left; one workgroup per matrix.
 __global__ __launch_bounds__(256, 1) void direct_tail(const DirectMat* mats)
 {
-    __shared__ double2 lds[2 * ONE];
+    __shared__ TriOne::Scratch lds;
     if (mats[blockIdx.x].r <= ONE) return;
     TriOne t;
-    t.run(mats[blockIdx.x], (double*)lds);
+    t.run(mats[blockIdx.x], lds);
 }
 
 // ------------------------------------------------------------------------------------------------
