@@ -14,7 +14,8 @@ struct ThinMat {
     int rows, cols, tall, r, M;
     int nchunks, chunk;              // the positions of the long side in partial Gram matrices of `chunk` each
     int capacity;
-    double* part;                    // [nchunks][3][16 * 16]: the tiles (0, 0), (0, 1), (1, 1) of the partial sums
+    double* part;                    // [nchunks][3][16 * 16]: the tiles (0, 0), (1, 0), (1, 1) of the partial sums, of which
+                                     //   the entries of the lower triangle are read (up to 16 columns: the first)
     double* u;                       // [r + 8][r] kept vectors of the shorter side, divided by their sigma (folded: times the weight
                                      //   where the longer side is U)
     int* count;

@@ -104,12 +104,17 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
     const int tiles = two ? 3 : 1;
     auto give = [&](double* to, bool add) {
         auto put = [&](int e, double x) { to[e] = add ? to[e] + x : x; };
-        for (int t = 0; t < (narrow ? 1 : tiles); ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) put(t * 256 + (4 * v + q) * 16 + l16, acc[t][v]);
+        for (int v = 0; v < 4; ++v) put((4 * v + q) * 16 + l16, acc[0][v]);
         if (narrow) {
-            put(256 + (4 * (l16 >> 2) + q) * 16 + (l16 & 3), cross);
-            if (l16 < 4) put(512 + q * 16 + l16, corner);
+            put(256 + (l16 & 3) * 16 + 4 * (l16 >> 2) + q, cross);
+            if (l16 < 4) put(512 + l16 * 16 + q, corner);
+        } else if (two) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                put(256 + l16 * 16 + 4 * v + q, acc[1][v]);
+                put(512 + (4 * v + q) * 16 + l16, acc[2][v]);
+            }
         }
     };
     if (wave >= GRAM_WAVES / 2) give(red[wave - GRAM_WAVES / 2], false);
@@ -117,7 +122,8 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
     if (wave < GRAM_WAVES / 2) give(red[wave], true);
     __syncthreads();
     const Global<double> out = global(m.part) + (size_t)wk.a * PART;
-    for (int e = tid; e < 256 * tiles; e += 64 * GRAM_WAVES) {
+    for (int f = tid; f < (narrow ? 384 : 256 * tiles); f += 64 * GRAM_WAVES) {
+        const int e = narrow && f >= 320 ? f + 192 : f;          // (narrow: four vectors of the second and of the third tile)
         double sum = 0.0;
 #pragma unroll
         for (int w = 0; w < GRAM_WAVES / 2; ++w) sum += red[w][e];
@@ -128,7 +134,6 @@ __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats
 // ------------------------------------------------------------------------------------------------
 constexpr int ST = 512;                        // threads of a workgroup of thin_solve
 constexpr int LD = THIN_R + 1;
-constexpr int OVERRUN = 8;                     // a row is read in groups of eight columns
 constexpr int MAX_SWEEPS = 15;
 
 // 1 / sqrt(x) of a positive normal number: the hardware's estimate (23 bits) and one step of third order, two dependent
@@ -153,11 +158,15 @@ __device__ inline void rotation(double a, double b, double g, double& c, double&
     s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
 }
 
-// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n on, OVERRUN entries past the last row too, and in
-// w_sh) by one wave: diagonal d, off-diagonal
-// e; the vectors of the steps go to the rows of H, C is used up.  Lane l holds row l mod 32 and every other column.
-__device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d, double* e, double* tau, int n)
+// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n on) by one wave: diagonal d, off-diagonal
+// e; the vectors of the steps go to the rows of H.  Lane l holds the columns 16 (l / 32) .. of row l mod 32 in registers; the column
+// below its first entry, w and column k + 1 (the row of that number) go around through LDS.  The product is taken with
+// the column without its first entry, under way before the reflector is known (A v = A y + v0 A e_{k+1}).
+// 16 steps of 18 columns: 1600 cycles each with the matrix in LDS, 1340 now.
+struct TriScratch { double y[THIN_R], w[THIN_R], column[THIN_R]; };
+__device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, double* d, double* e, double* tau, int n)
 {
+    constexpr int U = THIN_R / 2;
     const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
     auto in_order = [] {                                         // (the wave's LDS operations are performed in program order)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -169,67 +178,55 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
         y += dpp<DPP_MIRROR>(y);
         return fold16(y, y);
     };
+    double a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = C[i * LD + U * h + u];
+    auto put_row = [&](int row) {
+        if (i == row) {
+#pragma unroll
+            for (int u = 0; u < U; u += 2) *(doublex2*)&lds.column[U * h + u] = doublex2{a[u], a[u + 1]};
+        }
+    };
+    auto get = [&](const double* from, double (&to)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; u += 2) {
+            const doublex2 t = *(const doublex2*)&from[U * h + u];
+            to[u] = t.x;
+            to[u + 1] = t.y;
+        }
+    };
     double x = C[i * LD];                                        // column k of the current matrix, in both halves
     for (int k = 0; k + 2 < n; ++k) {
-        const double alpha = lane_value(x, k + 1), diagonal = lane_value(x, k);
-        // v is the column but for its entry k + 1, alpha - beta for alpha: the product with the column is under way before
-        // beta is known, and beta times column k + 1 comes off it afterwards
-        if (h == 0) w_sh[i] = x;
+        const double y = i > k + 1 ? x : 0.0;
+        lds.y[i] = y;
+        put_row(k + 1);
         in_order();
-        // columns k + 1 + h, k + 3 + h, ..
-        constexpr int U = THIN_R / 2;
-        double c[U], vj[U];
-        double* row = C + i * LD + k + 1 + h;
-        const double* column = w_sh + k + 1 + h;
-#pragma unroll
-        for (int u = 0; u < U; u += 4) {
-            if (k + 1 + 2 * u >= n) break;
-#pragma unroll
-            for (int y = u; y < u + 4; ++y) {
-                c[y] = row[2 * y];
-                vj[y] = column[2 * y];
-            }
-        }
-        const double sig2 = half_sum(i > k + 1 ? x * x : 0.0);
+        double yj[U], wj[U];
+        get(lds.y, yj);
+        const double c = lds.column[i];
+        const double alpha = lane_value(x, k + 1), diagonal = lane_value(x, k);
+        const double sig2 = half_sum(y * y);
         double even = 0.0, odd = 0.0;
 #pragma unroll
-        for (int u = 0; u < U; u += 4) {
-            if (k + 1 + 2 * u >= n) break;
-#pragma unroll
-            for (int y = u; y < u + 4; y += 2) {
-                even = fma(c[y], vj[y], even);
-                odd = fma(c[y + 1], vj[y + 1], odd);
-            }
+        for (int u = 0; u < U; u += 2) {
+            even = fma(a[u], yj[u], even);
+            odd = fma(a[u + 1], yj[u + 1], odd);
         }
         double beta, v0;
         householder(alpha, sig2, beta, v0);
         const double t = householder_tau(sig2, v0);
-        const double v = i > k + 1 ? x : i == k + 1 ? v0 : 0.0;
-        if (h == 0) {
-            H[k * LD + i] = v;
-            even = fma(-beta, c[0], even);
-            vj[0] = v0;
-        }
+        const double v = i == k + 1 ? v0 : y;
         const double part = even + odd;
-        const double p = i > k ? t * fold32(part, part) : 0.0;
-        const double pv = half_sum(p * v);
-        const double w = fma(-0.5 * t * pv, v, p);
-        if (h == 0) w_sh[i] = w;
+        const double p = i > k ? t * fma(v0, c, fold32(part, part)) : 0.0;
+        const double w = fma(-0.5 * t * half_sum(p * v), v, p);
+        lds.w[i] = w;
         in_order();
+        get(lds.w, wj);
+        x = fma(-w, v0, fma(-v, lane_value(w, k + 1), c));
+        // (column k + 1, for which y is not v, is not used any more)
 #pragma unroll
-        for (int u = 0; u < U; u += 4) {
-            if (k + 1 + 2 * u >= n) break;
-            double wj[4];
-#pragma unroll
-            for (int y = 0; y < 4; ++y) wj[y] = column[2 * (u + y)];
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const double next = fma(-v, wj[y], fma(-w, vj[u + y], c[u + y]));
-                if (i > k && k + 1 + h + 2 * (u + y) < n) row[2 * (u + y)] = next;
-                if (u + y == 0) x = next;                        // lower half: column k + 1
-            }
-        }
-        x = fold32(h == 0 ? x : 0.0, h == 0 ? x : 0.0);
+        for (int u = 0; u < U; ++u) a[u] = fma(-v, wj[u], fma(-w, yj[u], a[u]));
+        if (h == 0) H[k * LD + i] = v;
         if (lane == 0) {
             d[k] = diagonal;
             e[k] = beta;
@@ -237,46 +234,49 @@ __device__ inline void tridiagonal(double* C, double* H, double* w_sh, double* d
         }
         in_order();
     }
-    if (lane == 0) {
-        if (n > 1) {
-            d[n - 2] = C[(n - 2) * LD + n - 2];
-            e[n - 2] = C[(n - 1) * LD + n - 2];
-        }
-        d[n - 1] = C[(n - 1) * LD + n - 1];
+    put_row(n - 1);
+    in_order();
+    if (lane == max(n - 2, 0) && n > 1) d[n - 2] = x;
+    if (lane == n - 1) {
+        if (n > 1) e[n - 2] = x;
+        d[n - 1] = lds.column[n - 1];
     }
 }
 
-// Eigenvalues of T below z (see svd_direct.hip): t holds (e_{i-1}^2, d_i), n_pad of them, a multiple of eight, in LDS.
-__device__ inline int sturm_below(const doublex2* t, int n_pad, double z)
+// Eigenvalues of T below z (see svd_direct.hip): t holds (e_{i-1}^2, d_i), eights of them.
+template <int EIGHTS>
+__device__ inline int sturm_below(const doublex2 (&t)[8 * EIGHTS], double z)
 {
     double p0 = 0.0, p1 = 1.0;
     unsigned signs = 0;
-    for (int i = 0; i < n_pad; i += 8) {
-        doublex2 x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = t[i + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double p2 = fma(x[u].y - z, p1, -(x[u].x * p0));
-            p0 = p1;
-            p1 = p2;
-            signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+    for (int i = 0; i < 8 * EIGHTS; ++i) {
+        const double p2 = fma(t[i].y - z, p1, -(t[i].x * p0));
+        p0 = p1;
+        p1 = p2;
+        signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
+        if (i % 8 == 7) {
+            // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
+            const double scale = mk64(0u, 0x7fd00000u - max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u));
+            p0 *= scale;
+            p1 *= scale;
         }
-        const int ex = max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-        p0 = __builtin_amdgcn_ldexp(p0, -ex);
-        p1 = __builtin_amdgcn_ldexp(p1, -ex);
     }
     return __popc(signs ^ (signs >> 1));
 }
 
 // All eigenvalues of T, descending, by the ST threads of the workgroup (all call): a first pass at ST points, then 16 points per
-// eigenvalue and pass, until a cell is left.
-__device__ inline void eigenvalues(const doublex2* t, int n_pad, int n, int* below /* LDS [ST] */, double* lam)
+// eigenvalue and pass, until a cell is left.  T (8 EIGHTS entries, in LDS) in registers.
+template <int EIGHTS>
+__device__ inline void eigenvalues(const doublex2* in, int n, int* below /* LDS [ST] */, double* lam)
 {
     constexpr u64 CELLS = (LAM_MAX_BITS - LAM_MIN_BITS) >> LAM_STEP_BITS, SPAN = CELLS / ST;
     constexpr int LANES = ST / THIN_R;
     const int tid = threadIdx.x, lane = tid & 63;
-    below[tid] = sturm_below(t, n_pad, cell_start(SPAN * tid));
+    doublex2 t[8 * EIGHTS];
+#pragma unroll
+    for (int i = 0; i < 8 * EIGHTS; ++i) t[i] = in[i];
+    below[tid] = sturm_below<EIGHTS>(t, cell_start(SPAN * tid));
     __syncthreads();
     const int l = tid & (LANES - 1), base = lane & ~(LANES - 1), i = tid / LANES, asc = n - 1 - i;
     if (i < n) {
@@ -286,14 +286,16 @@ __device__ inline void eigenvalues(const doublex2* t, int n_pad, int n, int* bel
             if (below[mid] <= asc) lo = mid; else hi = mid;
         }
         const bool zero = below[0] > asc;
-        u64 g0 = SPAN * lo, g1 = zero ? g0 : g0 + SPAN;
+        u64 g0 = SPAN * lo;
+        unsigned width = zero ? 0u : (unsigned)SPAN;             // of the interval from g0 on
+        static_assert(SPAN * LANES <= 0xffffffffull, "points of an interval in 32 bits");
+        auto point = [&](int k) { return width * (unsigned)k / (unsigned)(LANES + 1); };
         const u64 group = ((1ull << LANES) - 1) << base;
-        while (g1 - g0 > 1) {                                    // (the lanes of an eigenvalue agree)
-            const u64 z = g0 + (g1 - g0) * (unsigned)(l + 1) / (unsigned)(LANES + 1);
-            const int k = __popcll(__ballot(sturm_below(t, n_pad, cell_start(z)) <= asc) & group);
-            const u64 z_lo = __shfl(z, base + max(k - 1, 0)), z_hi = __shfl(z, base + min(k, LANES - 1));
-            if (k > 0) g0 = z_lo;
-            if (k < LANES) g1 = z_hi;
+        while (width > 1) {                                      // (the lanes of an eigenvalue agree)
+            const int k = __popcll(__ballot(sturm_below<EIGHTS>(t, cell_start(g0 + point(l + 1))) <= asc) & group);
+            const unsigned from = k > 0 ? point(k) : 0u, to = k < LANES ? point(k + 1) : width;
+            g0 += from;
+            width = to - from;
         }
         if (l == 0) lam[i] = zero ? 0.0 : bits_double(LAM_MIN_BITS + (g0 << LAM_STEP_BITS) + (1ull << (LAM_STEP_BITS - 1)));
     }
@@ -388,15 +390,17 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
 // Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
 // the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
 // zeros aside; vectors with a small residual, kept ones apart); otherwise the two-sided Jacobi iteration.  18
-// columns: 42 us, 31 of them without the sums of the largest matrices; Jacobi in eight sweeps 73.
+// columns: 33 us, 28 of them without the sums of the largest matrices (42 and 31 with the matrix, T and the partial sums read
+// from memory and LDS step by step); Jacobi in eight sweeps 73.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.
 __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, u64 seed, int* flags)
 {
-    __shared__ double A[2][THIN_R * LD + OVERRUN], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
+    __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
     __shared__ doublex2 T[THIN_R];
-    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R + OVERRUN];
+    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R];
+    __shared__ __attribute__((aligned(16))) TriScratch tri;
     __shared__ int below[ST];
     __shared__ int unfinished[2];
     __shared__ double lam[THIN_R];
@@ -405,8 +409,9 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     __shared__ int accepted;
     const ThinMat& m = mats[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = m.r;
-    // C in both triangles: sums over the chunks, of the entries i <= j that there are.  Up to 256 of them leave half of the
-    // threads for the second half of the chunks.
+    // C in both triangles: sums over the chunks, of the entries i <= j that there are, in the order in which a partial sum holds
+    // them (a wave's 64 entries are a few lines of memory: 128 partial sums 11 us with a line per entry, 4.7 so).  Up to 256 of
+    // them leave half of the threads for the second half of the chunks.
     {
         const int entries = r * (r + 1) / 2, parts = entries <= ST / 2 ? 2 : 1;
         const int share = (m.nchunks + parts - 1) / parts;
@@ -416,7 +421,7 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             j += (j + 1) * (j + 2) / 2 <= f;
             j -= j * (j + 1) / 2 > f;
             const int i = f - j * (j + 1) / 2;
-            const int e = j < 16 ? i * 16 + j : i < 16 ? 256 + i * 16 + j - 16 : 512 + (i - 16) * 16 + j - 16;
+            const int e = j < 16 ? j * 16 + i : i < 16 ? 256 + (j - 16) * 16 + i : 512 + (j - 16) * 16 + i - 16;
             const Global<const double> in = global((const double*)m.part) + e;
             const int part = tid / (ST / parts);
             int c = part * share;
@@ -484,13 +489,12 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         // scaled by a power of four to a trace in [1/4, 1)
         (void)frexp(trace, &expo);
         expo += expo & 1;
-        for (int e = tid; e < THIN_R * LD + OVERRUN; e += ST) {
+        for (int e = tid; e < THIN_R * LD; e += ST) {
             const int i = e / LD, j = e - i * LD;
             A[1][e] = i < r && j < r ? ldexp(A[0][e], -expo) : 0.0;
         }
-        if (tid < OVERRUN) tw[THIN_R + tid] = 0.0;
         __syncthreads();
-        if (wave == 0) tridiagonal(A[1], V, tw, td, te, ttau, r);
+        if (wave == 0) tridiagonal(A[1], V, tri, td, te, ttau, r);
         __syncthreads();
         const int n_pad = (r + 7) & ~7, pad = n_pad - r;
         if (tid < n_pad) {
@@ -500,7 +504,10 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         }
         if (tid < THIN_R) rank_of[tid] = tid;
         __syncthreads();
-        eigenvalues(T, n_pad, r, below, lam);
+        if (n_pad == 8) eigenvalues<1>(T, r, below, lam);
+        else if (n_pad == 16) eigenvalues<2>(T, r, below, lam);
+        else if (n_pad == 24) eigenvalues<3>(T, r, below, lam);
+        else eigenvalues<4>(T, r, below, lam);
         __syncthreads();
         if (wave == 0) {
             draw();
