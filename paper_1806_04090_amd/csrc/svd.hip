@@ -1482,14 +1482,19 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     bool iterate = false;                                        // is anything enqueued for the Jacobi iteration?
     for (int j = 0; j < n_mats; ++j) iterate = iterate || !plan.mats[j].skip;
     if (hint) hint->iterated = iterate;
-    // thin matrices: beside all others on a stream of their own, from the caller's point in time
+    // Thin matrices: beside all others on a stream of their own, from the caller's point in time; a few of them beside groups of
+    // workgroups (more than 128 rows) from the end of the Gram products.  A thin workgroup that is still on a compute unit when the
+    // groups are placed makes two of theirs share another one for the whole reduction (ResNet-18, two thin layers: 635
+    // us in two calls of three, 515 in the others and always so; 916 -> 868 us per call).  Behind the Gram products the groups are
+    // placed first, and at least 200 us are left, twice what 256 chunks take.
     const bool any_thin = !plan.thin.mats.empty();
     const bool beside = any_thin && (any_direct || iterate);
-    if (any_thin) {
+    const bool late = beside && !iterate && plan.direct.max_nt > 2 && plan.thin.gram.size() <= 256;
+    if (beside && (rc = ensure_side_streams(ctx)) != ATOMO_OK) return rc;
+    auto solve_thin = [&]() -> int {
         hipStream_t s_thin = stream;
         if (beside) {
-            if ((rc = ensure_side_streams(ctx)) != ATOMO_OK) return rc;
-            ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
+            if (!late) ATOMO_HIP(ctx, hipEventRecord(ctx->ev_fork, stream));
             ATOMO_HIP(ctx, hipStreamWaitEvent(ctx->side_thin, ctx->ev_fork, 0));
             s_thin = ctx->side_thin;
         }
@@ -1497,7 +1502,9 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         thin::launch(plan.thin, (const thin::ThinMat*)((char*)d_tables + at_thin), w_thin_gram, w_thin_long, s, seed, ctx->d_flags,
                      s_thin);
         if (beside) ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join_thin, s_thin));
-    }
+        return ATOMO_OK;
+    };
+    if (any_thin && !late && (rc = solve_thin()) != ATOMO_OK) return rc;
     // the hint comes from svd_pack, or from the direct encode if nothing iterates
     hipEvent_t join_direct = nullptr;
     if (any_direct) {
@@ -1522,9 +1529,11 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             ATOMO_HIP(ctx, hipStreamWaitEvent(s_direct, ctx->ev_fork, 0));
         }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, s_direct);
-        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct);
+        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct,
+                       late ? ctx->ev_fork : nullptr);
         if (join_direct) ATOMO_HIP(ctx, hipEventRecord(join_direct, s_direct));
     }
+    if (late && (rc = solve_thin()) != ATOMO_OK) return rc;
     if (!iterate) {
         if (beside) ATOMO_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_join_thin, 0));
         return record_hint();

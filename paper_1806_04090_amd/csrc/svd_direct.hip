@@ -1946,7 +1946,8 @@ void plan_work(DirectPlan& plan)
         for (size_t k = 0; k < die[x].size(); ++k) plan.tri[8 * k + x] = die[x][k];
 }
 
-void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream)
+void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
+            hipEvent_t gram_done)
 {
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     if (!plan.gram.empty()) {
@@ -1955,6 +1956,7 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     }
     if (!plan.gram_wide.empty())
         direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size(), t.tickets);
+    if (gram_done) (void)hipEventRecord(gram_done, stream);
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
     if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);

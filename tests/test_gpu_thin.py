@@ -74,3 +74,20 @@ def test_kept_vectors_of_a_nearly_equal_tail_are_orthogonal(r, tail):
     assert status == 0
     for G, msg, (sigma, p) in zip(host, msgs, per):
         check_svd_message_against_matrix(G.astype(np.float64), msg.to_host(), sigma, p)
+
+
+@pytest.mark.parametrize("thin", [[(64, 27)], [(131072, 6)] * 2, [(131072, 6)] * 2 + [(9, 1025)]])
+def test_beside_groups_the_bits_of_a_call_of_their_own(thin):
+    """Up to 256 chunks of positions start behind the Gram products of larger matrices, more at once."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    mats = []
+    for m, n in [(192, 256), (96, 200)] + thin:
+        mats.append(torch.randn(m, n, generator=gen, device="cuda") * 0.01)
+        mats[-1][0] *= 40.0
+    alone = [binding.atomo_encode_svd(ctx(), [G], 3.0, 4, 70 + j)[0].to_host() for j, G in enumerate(mats)]
+    for _ in range(4):                                           # (with the iteration enqueued, then without)
+        msgs = binding.atomo_encode_svd(ctx(), mats, 3.0, 4, 70, adaptive=1)
+        assert ctx().status()[0] == 0
+        for j, want in enumerate(alone):
+            got = msgs[j].to_host()
+            assert got["count"] == want["count"] and all(np.array_equal(got[k], want[k]) for k in ("idx", "w", "U", "V")), j
