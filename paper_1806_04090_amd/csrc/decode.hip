@@ -49,7 +49,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // v_mfma_f32_32x32x2f32, two atoms per instruction.  Wave w owns columns 64 w .. 64 w + 63 of the tile as
 // 2 x 2 blocks of 32 x 32.
 // The kept atoms of a batch of messages (`batch` x largest capacity <= ATOMS_MAX, chosen by the host) are first
-// listed in LDS (one round trip for all counts).  The operands then come through LDS in pieces of KP atoms: all
+// listed in LDS: by one wave, a message per lane, its place from a scan over the counts in registers, or, where it is
+// one message, by all threads (a thread per message that added the counts before its own up in LDS, a barrier more
+// and a second trip for the message behind it: the 131072 x 18 and the other layers of Section 6 23.5 us, now 17.5;
+// the update from 8 27.4, now 26.5).  The operands then come through LDS in pieces of KP atoms: all
 // 256 threads fetch the piece's slices of u (64 rows) and v (256 columns) with 16-byte loads that are all in
 // flight at once - every atom's u and v are contiguous rows of its message -, and the loads of the next piece
 // are issued before the products of the current one.  The weight is applied on the way into LDS.
@@ -60,8 +63,20 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int KP = 16;             // atoms per piece (8 and 24 measure the same; 32 leaves room for two workgroups per
                                    // compute unit instead of four and is a third slower)
 
+// sum over the lanes of the wave up to this one
+__device__ inline int inclusive_sum(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 to rows 1 and 3, 31 to rows 2 and 3
+    return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+}
+
+// (128 registers for four workgroups per compute unit; with the outputs in registers too, 63 of them would go to memory for three)
 template <bool TALL, bool ACCUMULATE>
-__global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, const DecMsg* msgs, const DecWork* work,
+__global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(const DecOut* outs, const DecMsg* msgs, const DecWork* work,
                                                         float scale, int batch)
 {
     constexpr int NCB = TALL ? 1 : 2;
@@ -73,8 +88,7 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
     __shared__ Global<const float> up[ATOMS_MAX];
     __shared__ Global<const float> vp[ATOMS_MAX];
     __shared__ Global<const float> wp[ATOMS_MAX];                // the atom's weight (nullptr: folded into u)
-    __shared__ int kept_of[ATOMS_MAX];
-    __shared__ int total_sh;
+    __shared__ int total_sh, span_sh;
     __shared__ __attribute__((aligned(16))) float Us[KP * US];
     __shared__ __attribute__((aligned(16))) float Vs[KP * VS];
     const DecWork wk = work[blockIdx.x];
@@ -162,29 +176,46 @@ __global__ __launch_bounds__(256) void decode_svd_tiles(const DecOut* outs, cons
         }
     };
 
+    // atoms [run, run + ATOMS_MAX) of the messages [first, first + nm) (several have no more than that together, by the host's choice
+    // of `batch`; one alone is taken in runs)
+    auto list = [&](int first, int nm, int run) {
+        auto put = [&](const DecMsg& m, int at, int k) {
+            up[at] = global(m.U) + (size_t)k * o.rows;
+            vp[at] = global(m.V) + (size_t)k * o.cols;
+            wp[at] = m.w ? global(m.w) + k : nullptr;            // folded messages carry the weight in U
+        };
+        if (nm == 1) {
+            const DecMsg m = msgs[first];
+            const int kept = min(*global(m.count), m.capacity), here = max(0, min(kept - run, ATOMS_MAX));
+            for (int k = tid; k < here; k += 256) put(m, k, run + k);
+            if (tid == 0) {
+                total_sh = here;
+                span_sh = kept;
+            }
+        } else if (wave == 0) {
+            int before = 0;
+            for (int q0 = 0; q0 < nm; q0 += 64) {                // (one round trip for all counts)
+                const bool there = q0 + lane < nm;
+                const DecMsg m = msgs[first + min(q0 + lane, nm - 1)];
+                const int kept = there ? min(*global(m.count), m.capacity) : 0;
+                const int upto = before + inclusive_sum(kept);
+                for (int k = 0, at = upto - kept; k < kept && at < ATOMS_MAX; ++k, ++at) put(m, at, k);
+                before = __builtin_amdgcn_readlane(upto, 63);
+            }
+            if (lane == 0) {
+                total_sh = min(before, ATOMS_MAX);
+                span_sh = 0;
+            }
+        }
+    };
+
     for (int first = o.first; first < o.last; first += batch) {
         const int nm = min(batch, o.last - first);
-        __syncthreads();                                         // the previous list is spent
-        for (int q = tid; q < nm; q += 256) kept_of[q] = min(*global(msgs[first + q].count), msgs[first + q].capacity);
-        __syncthreads();
-        // several messages: everything fits the list by the host's choice of `batch` (one run); a message of its
-        // own: runs of ATOMS_MAX atoms, `run` = first atom of the run
-        const int span = nm == 1 ? kept_of[0] : 1;
-        for (int run = 0; run < span; run += ATOMS_MAX) {
-            if (run > 0) __syncthreads();                        // the previous run is spent
-            for (int q = tid; q < nm; q += 256) {
-                int at = 0;
-                for (int e = 0; e < q; ++e) at += kept_of[e];
-                const DecMsg m = msgs[first + q];
-                const int kept = max(0, min(kept_of[q] - run, ATOMS_MAX - at));
-                for (int k = 0; k < kept; ++k) {
-                    up[at + k] = global(m.U) + (size_t)(run + k) * o.rows;
-                    vp[at + k] = global(m.V) + (size_t)(run + k) * o.cols;
-                    wp[at + k] = m.w ? global(m.w) + run + k : nullptr;    // folded messages carry the weight in U
-                }
-                if (q == nm - 1) total_sh = at + kept;
-            }
+        for (int run = 0, span = 1; run < span; run += ATOMS_MAX) {
+            if (run > 0 || first > o.first) __syncthreads();     // the previous list is spent
+            list(first, nm, run);
             __syncthreads();
+            span = span_sh;
             const int total = total_sh;
             if (total > 0) fetch(0, total);
             for (int k0 = 0; k0 < total; k0 += KP) {

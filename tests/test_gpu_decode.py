@@ -47,6 +47,20 @@ def test_svd_decode_many_messages_across_batches(rows, cols, capacity, ks):
     assert np.linalg.norm(out - want) <= 1e-5 * max(np.linalg.norm(want), 1e-30)
 
 
+@pytest.mark.parametrize("messages,capacity", [(2, 256), (16, 32), (17, 30), (63, 8), (64, 8), (65, 7), (129, 3), (512, 1)])
+def test_svd_decode_lists_of_messages(messages, capacity):
+    """A wave lists 64 messages at a time, one scan over their counts; some keep nothing, some all they can.  An entry of the result is a
+    sum of K products in float: its error is at most (K + 2) eps times the sum of their magnitudes."""
+    rng = np.random.default_rng(messages)
+    ks = [int(k) for k in rng.integers(0, capacity + 1, messages)]
+    ks[0], ks[-1] = 0, capacity
+    pairs = [make_msg(rng, 5, 36, k, capacity) for k in ks]
+    out = binding.atomo_decode(ctx(), [m for m, _ in pairs]).cpu().numpy()
+    want = oracle.decode_svd([h for _, h in pairs], 5, 36)
+    size = oracle.decode_svd([{key: np.abs(x) for key, x in h.items()} for _, h in pairs], 5, 36)
+    assert (np.abs(out - want) <= (sum(ks) + 2) * 2.0 ** -24 * size).all()
+
+
 def test_svd_decode_into_strided_output_and_batch():
     rng = np.random.default_rng(1)
     m1, h1 = make_msg(rng, 33, 50, 2, 4)
