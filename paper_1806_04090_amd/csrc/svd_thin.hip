@@ -25,12 +25,12 @@ namespace {
 constexpr int GRAM_WAVES = 8;
 constexpr int GRAM_CHUNK = 128 * GRAM_WAVES;   // positions per workgroup: eight rounds of 16 per wave
 constexpr int MAX_CHUNKS = 128;
-constexpr int AHEAD = 4;                       // rounds in flight
+constexpr int AHEAD = 3;                       // rounds in flight (80 registers: three workgroups per compute unit, two with 4: 20.5 us)
 constexpr int PART = 3 * 256;                  // doubles of a partial Gram matrix
 
 // Bound: the matrix cores, with a 16 x 16 x 4 product per four positions up to 16 vectors, three from there on; vectors 16 .. 19
 // (the 18 columns of a 3 x 3 convolution) take two of 4 x 4 x 4 in four blocks, an eighth of the time of the two they replace.
-// 11.16 M elements of 18 columns: 20 us (27 with three large products; 14 without any).
+// 11.16 M elements of 18 columns: 19 us (27 with three large products; 14 without any).
 __global__ __launch_bounds__(64 * GRAM_WAVES) void thin_gram(const ThinMat* mats, const Work* work)
 {
     __shared__ double red[GRAM_WAVES / 2][PART];
