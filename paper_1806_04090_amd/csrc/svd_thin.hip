@@ -690,13 +690,14 @@ __device__ inline void long_dots(const float* mine /* LDS, r entries */, const _
     }
 }
 
-// Bound: one read of the data; 11.16 M elements of 18 columns in 16 us (34 with four dependent rounds of loads per workgroup and the
+// Bound: one read of the data; 11.16 M elements of 18 columns in 14 us (15 with LDS for 32 columns whatever their number, which
+// leaves room for four workgroups per compute unit instead of eight; 34 with four dependent rounds of loads per workgroup and the
 // atoms in LDS).  The entries of a block of positions are fetched before anything is known about the kept atoms,
 // go through LDS (those of a position of a tall matrix lie side by side, and a thread owns a position) and are multiplied with up
 // to eight atoms per pass.
 __global__ __launch_bounds__(LONG_POS) void thin_long(const ThinMat* mats, const Work* work)
 {
-    __shared__ float xs[LONG_POS * (THIN_R + 1)];
+    extern __shared__ float xs[];                                // [LONG_POS][r | 1]
     const Work wk = work[blockIdx.x];
     const ThinMat& m = mats[wk.mat];
     const int r = m.r, tid = threadIdx.x;
@@ -799,7 +800,9 @@ void launch(const ThinPlan& plan, const ThinMat* d_mats, const Work* gram, const
 {
     thin_gram<<<(unsigned)plan.gram.size(), 64 * GRAM_WAVES, 0, stream>>>(d_mats, gram);
     thin_solve<<<(unsigned)plan.mats.size(), ST, 0, stream>>>(d_mats, s, (u64)seed, d_flags);
-    thin_long<<<(unsigned)plan.lng.size(), 256, 0, stream>>>(d_mats, lng);
+    int most = 0;
+    for (const ThinMat& m : plan.mats) most = std::max(most, m.r | 1);
+    thin_long<<<(unsigned)plan.lng.size(), LONG_POS, LONG_POS * most * sizeof(float), stream>>>(d_mats, lng);
 }
 
 }  // namespace thin
