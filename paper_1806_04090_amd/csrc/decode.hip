@@ -256,13 +256,15 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
 // the messages and writes its outputs once: one launch for a fill and a scatter per message, and the outputs of
 // several messages are not read back.  Inside a message the coordinates are distinct, so plain LDS read-add-writes
 // with a barrier between messages give the same bits in every run.
-// Bound: HBM write of the outputs.  11.17 M outputs, one message of 111,740 pairs: 11.4 us (before: 8.6 us fill + 4.1 us
-// scatter + 3 us upload of the descriptor); 16 messages 34 us (8.6 + 16 x 4.1); 268 M outputs 228 us (187 + 110).
+// Bound: HBM write of the outputs.  11.17 M outputs, one message of 111,740 pairs: 14.1 us, 11.4 without LDS
+// (decode_sparse_one; 8.6 us a fill + 4.1 us a scatter, as two launches); 16 messages 34 us (8.6 + 16 x 4.1); 268 M outputs 228 us (187 + 110).
 // The descriptors travel in the kernel's arguments (SPARSE_MSGS of them: half a kilobyte), nothing is uploaded.
 // ------------------------------------------------------------------------------------------------
 constexpr int SPARSE_TILE = 4096;      // outputs per workgroup: 16 KB of LDS, eight workgroups per compute unit
 constexpr int SPARSE_RESIDENT = 2048;  // workgroups the chip holds at once
 constexpr int SPARSE_MSGS = 16;        // messages per launch
+constexpr int64_t ONE_ANY = 1 << 22;   // outputs, and tiles, up to which one message decodes without LDS (see the dispatch)
+constexpr int ONE_TILES = 8192;
 
 struct SparseMsg {
     const long long* count;
@@ -302,6 +304,65 @@ __device__ inline long long lower_bound_group(const unsigned int* idx, long long
     return lo + below(lo + glane, glane < len);
 }
 
+// Share `number` of `shares` of a message's pairs: do their coordinates ascend?
+__device__ inline void check_order(const SparseMsg& m, int number, int shares, unsigned int mask, int* flags)
+{
+    const long long pairs = min(*m.count, m.capacity) - 1, share = (pairs + shares - 1) / shares;
+    const long long from = number * share, to = min(pairs, from + share);
+    bool disorder = false;
+    for (long long k0 = from + threadIdx.x; k0 < to; k0 += 256 * 8) {    // sixteen loads in flight
+        unsigned int a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const long long k = min(k0 + 256 * u, to - 1);
+            a[u] = m.idx[k] & mask;
+            b[u] = m.idx[k + 1] & mask;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) disorder |= a[u] >= b[u];
+    }
+    if (disorder) atomicMax(&flags[FLAG_ORDER], 1);
+}
+
+// One message: nothing is added up, so the outputs need not go through LDS.  Three waves write the zeros of the workgroup's tile,
+// from the start and without waiting for anything, while the fourth searches; the values follow behind the barrier (stores of
+// a workgroup to one place are performed in the order that the barrier gives them).  The searching wave has no stores of its own in
+// front of its loads, which would be waited for first.
+// Bound: the write of the outputs.  11.17 M outputs, 111,740 pairs: 14.1 -> 11.4 us (the stores waited for the search); one l_q
+// message of 3343 pairs 11.2 -> 9.3.
+template <bool LQ>
+__global__ __launch_bounds__(256) void decode_sparse_one(SparseMsg m, float scale, float* __restrict__ out, long long n, int checks,
+                                                         int* flags)
+{
+    __shared__ long long at_sh;
+    const unsigned int mask = LQ ? 0x7FFFFFFFu : 0xFFFFFFFFu;
+    if ((int)blockIdx.x < checks) {
+        check_order(m, blockIdx.x, checks, mask, flags);
+        return;
+    }
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const long long first = (long long)(blockIdx.x - checks) * SPARSE_TILE;
+    const int here = (int)min(n - first, (long long)SPARSE_TILE);
+    float* const o = out + first;
+    const long long kept = min(*m.count, m.capacity);
+    if (wave == 0) {
+        const long long at = lower_bound_group<64>(m.idx, kept, mask, (unsigned int)first);
+        if (tid == 0) at_sh = at;
+    } else {
+        const int quads = (((size_t)out) & 15) == 0 ? here / 4 : 0;
+        for (int k = tid - 64; k < quads; k += 192) *(float4*)(o + 4 * k) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int k = 4 * quads + tid - 64; k < here; k += 192) o[k] = 0.0f;
+    }
+    __syncthreads();
+    const float mag = LQ ? scale * *m.val : 0.0f;
+    for (long long k = at_sh + tid; k < kept; k += 256) {
+        const unsigned int w = m.idx[k];
+        const long long i = (long long)(w & mask) - first;
+        if (i >= here) break;                                    // ascending: nothing of this tile behind it
+        if (i >= 0) o[i] = LQ ? ((w >> 31) ? -mag : mag) : scale * m.val[k];
+    }
+}
+
 // A workgroup owns `run` consecutive tiles.  It searches for its part of every message once; from tile to tile it counts
 // how many of the pairs it had requested were used, and requests the next ones before it writes the tile.
 // G lanes look after one message: 64 for up to four messages, 16 for up to SPARSE_MSGS, so that the searches and the
@@ -322,22 +383,7 @@ __global__ __launch_bounds__(256) void decode_sparse(SparseMsgs msgs, float scal
     const int shift = (tid & 63) & ~(G - 1);
     const unsigned long long members = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
     if ((int)blockIdx.x < checks * msgs.n) {
-        const SparseMsg& m = msgs.m[blockIdx.x / checks];
-        const long long pairs = min(*m.count, m.capacity) - 1, share = (pairs + checks - 1) / checks;
-        const long long from = (blockIdx.x % checks) * share, to = min(pairs, from + share);
-        bool disorder = false;
-        for (long long k0 = from + tid; k0 < to; k0 += 256 * 8) {        // sixteen loads in flight
-            unsigned int a[8], b[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const long long k = min(k0 + 256 * u, to - 1);
-                a[u] = m.idx[k] & mask;
-                b[u] = m.idx[k + 1] & mask;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) disorder |= a[u] >= b[u];
-        }
-        if (disorder) atomicMax(&flags[FLAG_ORDER], 1);
+        check_order(msgs.m[blockIdx.x / checks], blockIdx.x % checks, checks, mask, flags);
         return;
     }
     const long long first = (long long)(blockIdx.x - checks * msgs.n) * run * SPARSE_TILE;
@@ -493,6 +539,11 @@ int decode_sparse_all(atomo_ctx* ctx, const MSG* msgs, int n_msgs, float scale, 
     // search, but the chip is full); from there on runs of tiles, so that a search serves several
     const int64_t tiles = (n + SPARSE_TILE - 1) / SPARSE_TILE;
     const int run = (int)std::max<int64_t>(1, tiles / SPARSE_RESIDENT / 4);
+    // One message's values go behind the zeros (decode_sparse_one) while the zeros are still in a cache: outputs that the L2s hold
+    // (16 MB: 1 M outputs 1.03 - 1.28 times faster from 0.1 to 50 % kept, 4 M 1.00 - 1.15), or the last level and few values
+    // (11.17 M with 0.1 % 12.2 -> 9.6 us, 1 % 12.9 -> 11.2, but 3 % 13.4 -> 14.3; 33.5 M with 1 % 28.8 -> 24.2, 6 % 33 -> 43).
+    // From there on a value costs a read and a write of its line: 67 M with 1 % 52 -> 72 us.
+    const bool alone = n_msgs == 1 && (n <= ONE_ANY || (tiles <= ONE_TILES && (int64_t)msgs[0].capacity <= n / 64));
     const unsigned wgs = (unsigned)((tiles + run - 1) / run);
     ProfScope ps(ctx, ATOMO_K_EW_DECODE, stream);
     for (int first = 0; first < n_msgs; first += SPARSE_MSGS) {
@@ -508,7 +559,8 @@ int decode_sparse_all(atomo_ctx* ctx, const MSG* msgs, int n_msgs, float scale, 
         // (16 rounds of loads for a workgroup, more from 2 M pairs on, where the tiles take longer than that)
         const int checks = (int)std::min<int64_t>(64, longest / 32768 + 1);
         const unsigned grid = wgs + (unsigned)(checks * part.n);
-        if (first > 0) decode_sparse<LQ, true, 16><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
+        if (alone) decode_sparse_one<LQ><<<grid, 256, 0, stream>>>(part.m[0], scale, out, n, checks, ctx->d_flags);
+        else if (first > 0) decode_sparse<LQ, true, 16><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
         else if (part.n > 4) decode_sparse<LQ, false, 16><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
         else decode_sparse<LQ, false, 64><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
     }

@@ -90,3 +90,35 @@ def test_coordinates_that_do_not_ascend_are_reported(n, k, beside, lq):
             binding.atomo_decode(ctx(), others + [message(bad)])
             assert ctx().status()[0] == binding.ATOMO_EINVAL
     assert ctx().status()[0] == 0                                       # (reported once)
+
+
+@pytest.mark.parametrize("n,k", [(1, 0), (1, 1), (4096, 0), (4097, 4097), (12_293, 300), (1 << 22, 1 << 21), ((1 << 22) + 1, 65_536),
+                                 ((1 << 22) + 1, 65_537), (8192 * 4096, 8192 * 64), (8192 * 4096 + 1, 8192 * 64)])
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("lq", [False, True])
+def test_one_message_on_both_sides_of_its_own_kernel(n, k, offset, lq):
+    """Values are stored over zeros that other waves have just stored: every output is compared, over what the buffer held before."""
+    gen = torch.Generator(device="cuda").manual_seed(n + k)
+    at = torch.unique(torch.randint(0, n, (k,), generator=gen, device="cuda")) if k < n else torch.arange(n, device="cuda")
+    if k:
+        at[0], at[-1] = 0, n - 1
+    kept = at.numel() if n > 1 else k
+    at = at[:kept]
+    out = torch.full((n + 2,), 9.0, device="cuda")
+    want = torch.full((n + 2,), 9.0, device="cuda")
+    want[offset:offset + n] = 0.0
+    if lq:
+        m = binding.alloc_lq_message(n, max(k, 1), "cuda")
+        neg = torch.rand(kept, generator=gen, device="cuda") < 0.5
+        m.idx[:kept] = torch.where(neg, at - (1 << 31), at).to(torch.int32)
+        m.norm.fill_(1.5)
+        want[offset + at] = torch.where(neg, -0.75, 0.75)
+    else:
+        m = binding.alloc_entrywise_message(n, max(k, 1), "cuda")
+        m.idx[:kept] = at.to(torch.int32)
+        m.val[:kept] = torch.randn(kept, generator=gen, device="cuda")
+        want[offset + at] = 0.5 * m.val[:kept]
+    m.count.fill_(kept)
+    binding.atomo_decode(ctx(), [m], scale=0.5, out=out[offset:offset + n])
+    assert torch.equal(out, want)
+    assert ctx().status()[0] == 0
