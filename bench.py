@@ -69,8 +69,9 @@ def executed_work(shapes, sweeps, refreshes, pair_visits, jacobi_steps, row_upda
 
     Thin layers (r <= 32) are two streaming passes over the data (svd_thin), priced by their bytes.
     Layers that are solved directly (svd_direct), all in fp64: the upper-triangular tiles of A A^T on the matrix cores,
-    M r (r + 64); the reduction to tridiagonal form, which keeps both triangles, 2 r^3; and per kept atom its image
-    under the reflectors and its long vector, 2 r^2 + 2 M r.  The search for the eigenvalues is not counted.
+    M r (r + 64) (calls of many tiles leave out what lies below the diagonal inside a tile on it); the reduction to
+    tridiagonal form, which keeps both triangles, 2 r^3; and per kept atom its image under the reflectors and its long
+    vector, 2 r^2 + 2 M r.  The search for the eigenvalues is not counted.
     The classes below are those of the layers that iterate.
     A sweep visits every pair (i, j) of the layer's 32-row blocks once, n_i + n_j real rows per pair.
     Data-space layers (32 < r <= 480), one launch of svd_rowgram per tick (svd_update): the row update, 2 x 64 x 64 x 64
