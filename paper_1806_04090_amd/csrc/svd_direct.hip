@@ -181,40 +181,53 @@ __global__ __launch_bounds__(256) void direct_gram(const DirectMat* mats, const 
             for (int v = 0; v < 4; ++v) out[(qi + 16 * i + 4 * v + q) * TILE + qj + 16 * j + l16] = acc[i][j][v];
 }
 
-// Adds the partial tiles up in the order of the columns and writes both triangles.
+// Adds the partial tiles up in the order of the columns and writes both triangles; a workgroup takes 16 rows of a tile.
+// Bound: HBM read where there are many tiles (the ResNet-18 layers 16 -> 14 us, 601 x 1237 and smaller ones 13.4 -> 7.9 against a
+// workgroup per tile and one partial tile at a time); with one tile the round trips for the partial sums, five at a time: 4.3 us
+// for the nine of 64 x 576 (7.5 by one workgroup).
+constexpr int SUM_ROWS = 16, SUM_AHEAD = 5;
 __global__ __launch_bounds__(256) void direct_gram_sum(const DirectMat* mats, const Work* work)
 {
-    __shared__ double t[TILE][TILE + 1];
+    __shared__ double t[SUM_ROWS][TILE + 1];
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
-    const int ti = wk.a, tj = wk.b, tid = threadIdx.x, N = m.nt * TILE;
+    const int ti = wk.a, tj = wk.b, row0 = SUM_ROWS * wk.c, tid = threadIdx.x, N = m.nt * TILE;
+    constexpr int PER = SUM_ROWS * TILE / 256;
     const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
-    const Global<const double> in = global((const double*)m.part) + (size_t)tile * (TILE * TILE);
+    const Global<const double> in = global((const double*)m.part) + (size_t)tile * (TILE * TILE) + row0 * TILE + tid;
     const Global<double> C = global(m.C);
-    double sum[16];
+    const size_t stride = (size_t)ntiles * (TILE * TILE);
+    double sum[PER];
 #pragma unroll
-    for (int p = 0; p < 16; ++p) sum[p] = 0.0;
-    for (int c = 0; c < m.nchunks; ++c) {
+    for (int p = 0; p < PER; ++p) sum[p] = 0.0;
+    for (int c = 0; c < m.nchunks; c += SUM_AHEAD) {
+        double x[SUM_AHEAD][PER];
 #pragma unroll
-        for (int p = 0; p < 16; ++p) sum[p] += in[(size_t)c * ntiles * (TILE * TILE) + tid + 256 * p];
+        for (int u = 0; u < SUM_AHEAD; ++u)
+#pragma unroll
+            for (int p = 0; p < PER; ++p) x[u][p] = in[(size_t)min(c + u, m.nchunks - 1) * stride + 256 * p];
+#pragma unroll
+        for (int u = 0; u < SUM_AHEAD; ++u)
+#pragma unroll
+            for (int p = 0; p < PER; ++p) sum[p] += c + u < m.nchunks ? x[u][p] : 0.0;
     }
 #pragma unroll
-    for (int p = 0; p < 16; ++p) {
+    for (int p = 0; p < PER; ++p) {
         const int i = (tid >> 6) + 4 * p, j = tid & 63;
-        C[(size_t)(ti * TILE + i) * N + tj * TILE + j] = sum[p];
+        C[(size_t)(ti * TILE + row0 + i) * N + tj * TILE + j] = sum[p];
         t[i][j] = sum[p];
     }
     __syncthreads();
     if (ti == tj) {
-        if (tid < TILE) m.diag[ti * TILE + tid] = t[tid][tid];
+        if (tid < SUM_ROWS) m.diag[ti * TILE + row0 + tid] = t[tid][row0 + tid];
     } else {
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const int i = (tid >> 6) + 4 * p, j = tid & 63;
-            C[(size_t)(tj * TILE + i) * N + ti * TILE + j] = t[j][i];
+        for (int p = 0; p < PER; ++p) {
+            const int i = tid / SUM_ROWS + 256 / SUM_ROWS * p, j = tid % SUM_ROWS;
+            C[(size_t)(tj * TILE + i) * N + ti * TILE + row0 + j] = t[j][i];
         }
     }
-    if (ti == 0 && tj == 0) clear_for_steps(m, tid, 256);
+    if (ti == 0 && tj == 0) clear_for_steps(m, tid + 256 * wk.c, 256 * (TILE / SUM_ROWS));
 }
 
 // A partial tile is on its way to whoever adds them up, on any die: stores and loads of agent scope.
@@ -1844,9 +1857,10 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.pad = m.nt * TILE - m.r;
     m.cls = class_of(m.r);
     const int ntiles = m.nt * (m.nt + 1) / 2;
-    // About 320 work items of the Gram product per matrix, none under 128 columns, at most 64 partial sums; from the shape
-    // alone, so that the sums do not depend on what else is in the call.
-    const int want = std::max(1, std::min({320 / ntiles, m.M / 128, 64}));
+    // About 320 work items of the Gram product per matrix, none under 128 columns, 64 in matrices of up to three tiles, which leave
+    // most of the chip idle (64 x 576: 11.0 -> 5.4 us), at most 64 partial sums; from the shape alone, so that the sums do not
+    // depend on what else is in the call.
+    const int want = std::max(1, std::min({320 / ntiles, m.M / (ntiles <= 3 ? 64 : 128), 64}));
     m.kchunk = (int)align_up((size_t)(m.M + want - 1) / want, GK);
     m.nchunks = (m.M + m.kchunk - 1) / m.kchunk;
     const size_t N = (size_t)m.nt * TILE;
@@ -1890,7 +1904,7 @@ void plan_work(DirectPlan& plan)
         const DirectMat& m = plan.mats[j];
         for (int ti = 0; ti < m.nt; ++ti)
             for (int tj = ti; tj < m.nt; ++tj) {
-                plan.tiles.push_back(Work{j, ti, tj, 0});
+                for (int q = 0; q < TILE / SUM_ROWS; ++q) plan.tiles.push_back(Work{j, ti, tj, q});
                 for (int c = 0; c < m.nchunks; ++c) plan.gram.push_back(Work{j, ti, tj, c});
             }
         for (int i = 0; i < m.r; i += 256 / plan.eig_lanes) plan.eig.push_back(Work{j, i, 0, 0});
