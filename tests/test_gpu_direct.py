@@ -352,3 +352,16 @@ def test_a_set_whose_iteration_fits_the_address_range_is_accepted_whatever_the_d
         got = msgs[j].to_host()
         assert one.status()[0] == 0 and all(np.array_equal(want[k], got[k]) for k in ("idx", "w", "U", "V"))
     c.close()
+
+
+@pytest.mark.parametrize("r", [33, 64, 128, 129])
+@pytest.mark.parametrize("M", [129, 320, 321, 385, 4099])
+@pytest.mark.parametrize("tall", [False, True])
+def test_sizes_around_the_partial_sums_of_a_gram_product(r, M, tall):
+    """Matrices of up to three tiles are cut into chunks of 64 columns, others of 128, and five partial tiles are added up at a time."""
+    rng = np.random.default_rng(r + M)
+    m, n = (M, r) if tall else (r, M)
+    G = inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5, 0.25, 0.1], 0.02)
+    msgs, per, status, _ = encode([G], 3.0, 5, stream_base=r, capacity=r)
+    assert status == 0
+    full_parity(G, 3.0, 5, r, msgs[0], *per[0])
