@@ -162,11 +162,13 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
             if (atom < KP && k0 + atom < total) rv[e] = load4(vp[k0 + atom], tile_c0 + 4 * part, o.cols);
         }
     };
-    auto stage = [&]() {
+    // the first `here` atoms of the piece are there; the others are zero whatever the scale is (infinity times a padding of zeros
+    // would be NaN, in every element of the tile)
+    auto stage = [&](int here) {
 #pragma unroll
         for (int e = 0; e < NU; ++e) {
             const int f = tid + 256 * e, atom = f / (UROWS / 4), part = f % (UROWS / 4);
-            const float w = scale * rw[e];
+            const float w = atom < here ? scale * rw[e] : 0.0f;
             if (atom < KP) *(float4*)&Us[atom * US + 4 * part] = make_float4(w * ru[e].x, w * ru[e].y, w * ru[e].z, w * ru[e].w);
         }
 #pragma unroll
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
             const int total = total_sh;
             if (total > 0) fetch(0, total);
             for (int k0 = 0; k0 < total; k0 += KP) {
-                stage();
+                stage(total - k0);
                 __syncthreads();
                 if (k0 + KP < total) fetch(k0 + KP, total);
                 const int pairs = (min(KP, total - k0) + 1) / 2;

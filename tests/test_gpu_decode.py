@@ -61,6 +61,21 @@ def test_svd_decode_lists_of_messages(messages, capacity):
     assert (np.abs(out - want) <= (sum(ks) + 2) * 2.0 ** -24 * size).all()
 
 
+@pytest.mark.parametrize("rows,cols", [(64, 256), (33, 300), (300, 18)])
+@pytest.mark.parametrize("k", [1, 2, 3, 16, 17, 33])
+@pytest.mark.parametrize("scale", [np.inf, -np.inf])
+def test_svd_decode_with_an_infinite_scale(rows, cols, k, scale):
+    """Atoms of positive entries: every element of the sum is infinite, for odd and even numbers of atoms alike."""
+    rng = np.random.default_rng(k)
+    m, _ = make_msg(rng, rows, cols, k, k + 1)
+    for part in (m.w, m.U, m.V):
+        part[:k] = part[:k].abs() + 0.5
+    out = binding.atomo_decode(ctx(), [m], scale=scale)
+    assert (out == scale).all()
+    binding.atomo_apply_svd_batch(ctx(), [[m]], scale, [out])
+    assert (out == scale).all()
+
+
 def test_svd_decode_into_strided_output_and_batch():
     rng = np.random.default_rng(1)
     m1, h1 = make_msg(rng, 33, 50, 2, 4)
