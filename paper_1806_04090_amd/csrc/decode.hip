@@ -189,7 +189,11 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
         if (nm == 1) {
             const DecMsg m = msgs[first];
             const int kept = min(*global(m.count), m.capacity), here = max(0, min(kept - run, ATOMS_MAX));
-            for (int k = tid; k < here; k += 256) put(m, k, run + k);
+            int mine = tid;
+            // (or the addresses below are worked out once in front of all batches, and six registers of every lane kept in scratch
+            // memory: 46.6 MiB written for the 42.6 of ResNet-18, 22.6 us for 16 workers, now 22.2.  The other form has registers left)
+            if (!ACCUMULATE) asm volatile("" : "+v"(mine));
+            for (int k = mine; k < here; k += 256) put(m, k, run + k);
             if (tid == 0) {
                 total_sh = here;
                 span_sh = kept;

@@ -3,9 +3,11 @@ declare, and the host-side argument validation answers without touching a GPU.""
 import ctypes as C
 import os
 import re
+import struct
 import subprocess
 import sys
 
+import msgpack
 import pytest
 
 from paper_1806_04090_amd import binding
@@ -125,3 +127,23 @@ assert L.atomo_svd_workspace_bytes(mats, 10, C.byref(size)) == 0 and size.value 
 """
     done = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
     assert done.returncode == 0, done.stderr
+
+
+def kernel_records():
+    """What the compiler notes about each kernel of the library (the metadata notes of the code objects in it)."""
+    data = open(binding.LIB_PATH, "rb").read()
+    found = {}
+    for note in re.finditer(rb"AMDGPU\0\0", data):
+        name_size, size, kind = struct.unpack("<III", data[note.start() - 12:note.start()])
+        if (name_size, kind) == (7, 32):
+            for record in msgpack.unpackb(data[note.end():note.end() + size])["amdhsa.kernels"]:
+                found[record[".name"]] = record
+    return found
+
+
+def test_the_decode_of_svd_messages_keeps_its_registers():
+    # registers of these kernels that go to scratch memory are written to HBM beside the outputs that bound them
+    tiles = {name: r for name, r in kernel_records().items() if "decode_svd_tiles" in name}
+    assert len(tiles) == 4
+    for name, r in tiles.items():
+        assert r[".private_segment_fixed_size"] == 0 and r[".vgpr_spill_count"] == 0, name
