@@ -239,9 +239,8 @@ __device__ inline double get_part(Global<const double> p)
 {
     return __longlong_as_double((long long)__hip_atomic_load((Global<const u64>)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
-// True for the last of a tile's chunks to be finished, in the one thread that asks; everything that the chunk has
-// stored has to be out by then (vmcnt(0): a relaxed store of agent scope that is acknowledged is where every die's loads of
-// agent scope look).  The word is zero again when all have been.
+// True for the last of a tile's chunks to be finished, in the one thread that asks, between wait_for_stores and loads_from_here.
+// The word is zero again when all have been.
 __device__ inline bool last_chunk(const DirectMat& m, unsigned* tickets, int tile)
 {
     unsigned* t = tickets + m.first_tile + tile;
@@ -249,7 +248,16 @@ __device__ inline bool last_chunk(const DirectMat& m, unsigned* tickets, int til
     if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return last;
 }
-__device__ inline void wait_for_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); }    // vmcnt(0), the other counters as they are
+// What the wave has put is where every die's loads of agent scope look, before anything that follows (vmcnt(0), the other counters
+// as they are: a relaxed store of agent scope that is acknowledged is there).  The fences cost no instruction: the compiler moves
+// neither the stores past the wait nor the wait's successors, nor loads, in front of it.
+__device__ inline void wait_for_stores()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+__device__ inline void loads_from_here() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront"); }
 
 // The same sums, bit for bit, for calls of many tiles: a tile per wave, the data straight from the caches into registers, no barrier.
 // Bound: the matrix cores again, in whose 64 cycles the vector unit of the same SIMD does nothing: every other instruction comes on
@@ -318,6 +326,7 @@ __device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, 
     int last = 0;
     if (lane == 0) last = last_chunk(m, tickets, tile);
     if (!__builtin_amdgcn_readfirstlane(last)) return;
+    loads_from_here();
     // (all loads of a partial tile in flight at once, beside the matrix instructions of the other wave)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
