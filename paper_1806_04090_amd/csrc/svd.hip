@@ -1416,9 +1416,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const size_t at_thin = align_up(at_direct + plan.direct.mats.size() * sizeof(direct::DirectMat), 256);
     const size_t at_work = align_up(at_thin + plan.thin.mats.size() * sizeof(thin::ThinMat), 256);
     std::vector<char>& tables = ctx->table_scratch;
-    // (and behind them the tickets of the direct encode: zeros that its kernels count in and leave zero)
-    const size_t at_tickets = align_up(at_work + plan.n_work() * sizeof(Work), 256);
-    tables.assign(at_tickets + plan.direct.n_tiles * sizeof(unsigned), 0);
+    tables.assign(at_work + plan.n_work() * sizeof(Work), 0);
     auto put = [&](size_t at, const auto& list) {                // (an empty list may have no address)
         if (!list.empty()) memcpy(tables.data() + at, list.data(), list.size() * sizeof(list[0]));
     };
@@ -1466,7 +1464,6 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     const SvdMat* d_mats = (const SvdMat*)d_tables;
     dt.mats = (const direct::DirectMat*)((char*)d_tables + at_direct);
     dt.n_mats = (int)plan.direct.mats.size();
-    dt.tickets = (unsigned*)((char*)d_tables + at_tickets);
     for (const Placed& x : placed) *x.where = (const Work*)((char*)d_tables + at_work) + x.at;
 
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };

@@ -30,7 +30,6 @@ struct DirectMat {
     int nt, pad;                     // N = 64 nt >= r: the Gram matrix with `pad` zero rows and columns in front
     int cls;                         // CLS_*: how the reduction splits the matrix (its last rows are one workgroup's)
     int nchunks, kchunk;             // the columns of A in the Gram product: nchunks partial sums of kchunk each
-    int first_tile;                  // its first word among the call's tickets
     int capacity;
     double* part;                    // [nchunks][nt (nt + 1) / 2][64 * 64] partial Gram tiles
     double* C;                       // [N][N] Gram matrix, both triangles
@@ -45,6 +44,7 @@ struct DirectMat {
     double* u;                       // [capacity][r] kept vectors of the shorter side
     unsigned long long* xch;         // exchange slots of the reduction, see Tri
     unsigned long long* gate;        // [1] the workgroups of the matrix's group that have started, see Gate
+    unsigned* tickets;               // [nt (nt + 1) / 2] chunks of a tile that are done, see direct_gram_wide
     int* st;                         // [DS_WORDS]
     int* count;
     int* idx;
@@ -63,7 +63,6 @@ struct DirectMat {
 struct DirectPlan {
     std::vector<DirectMat> mats;
     std::vector<svd::Work> gram, tiles, gram_wide, tri, eig, vec, lng;
-    size_t n_tiles = 0;              // tickets: a word per tile of the Gram matrices, zero between launches
     bool spread = false;             // deal the workgroups of a group over all dies (for tests)
     long long start_ticks = START_TICKS;
     int eig_lanes = 64;              // lanes per eigenvalue in the search
@@ -84,7 +83,6 @@ struct DirectTables {
     const DirectMat* mats;
     int n_mats;
     const svd::Work *gram, *tiles, *gram_wide, *tri, *eig, *vec, *lng;
-    unsigned* tickets;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.  gram_done (may be null) is recorded
 // behind the Gram products.

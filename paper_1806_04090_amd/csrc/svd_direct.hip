@@ -240,13 +240,9 @@ __device__ inline double get_part(Global<const double> p)
     return __longlong_as_double((long long)__hip_atomic_load((Global<const u64>)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 // True for the last of a tile's chunks to be finished, in the one thread that asks, between wait_for_stores and loads_from_here.
-// The word is zero again when all have been.
-__device__ inline bool last_chunk(const DirectMat& m, unsigned* tickets, int tile)
+__device__ inline bool last_chunk(const DirectMat& m, int tile)
 {
-    unsigned* t = tickets + m.first_tile + tile;
-    const bool last = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)m.nchunks - 1u;
-    if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return last;
+    return __hip_atomic_fetch_add(global(m.tickets) + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)m.nchunks - 1u;
 }
 // What the wave has put is where every die's loads of agent scope look, before anything that follows (vmcnt(0), the other counters
 // as they are: a relaxed store of agent scope that is acknowledged is there).  The fences cost no instruction: the compiler moves
@@ -271,7 +267,7 @@ __device__ inline void loads_from_here() { __builtin_amdgcn_fence(__ATOMIC_ACQUI
 // stores of agent scope write through.)
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <bool SAME>
-__device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, unsigned* tickets, int lane)
+__device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, int lane)
 {
     const int ntiles = m.nt * (m.nt + 1) / 2, tile = ti * m.nt - ti * (ti - 1) / 2 + (tj - ti);
     const size_t chunk_size = (size_t)ntiles * (TILE * TILE);
@@ -324,7 +320,7 @@ __device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, 
             for (int v = 0; v < 4; ++v) put_part(part + chunk * chunk_size + (16 * i + 4 * v + q) * TILE + 16 * j + l16, acc[i][j][v]);
     wait_for_stores();
     int last = 0;
-    if (lane == 0) last = last_chunk(m, tickets, tile);
+    if (lane == 0) last = last_chunk(m, tile);
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     loads_from_here();
     // (all loads of a partial tile in flight at once, beside the matrix instructions of the other wave)
@@ -361,7 +357,14 @@ __device__ inline void wide_tile(const DirectMat& m, int ti, int tj, int chunk, 
     if (SAME && ti == 0) clear_for_steps(m, lane, 64);
 }
 
-__global__ __launch_bounds__(256, 2) void direct_gram_wide(const DirectMat* mats, const Work* work, int n, unsigned* tickets)
+// In front of direct_gram_wide, a workgroup per matrix: its tickets in the workspace are what earlier calls left there.
+__global__ __launch_bounds__(64) void direct_clear_tickets(const DirectMat* mats)
+{
+    const DirectMat& m = mats[blockIdx.x];
+    for (int i = threadIdx.x; i < m.nt * (m.nt + 1) / 2; i += 64) m.tickets[i] = 0;
+}
+
+__global__ __launch_bounds__(256, 2) void direct_gram_wide(const DirectMat* mats, const Work* work, int n)
 {
     const int item = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (item >= n) return;
@@ -369,8 +372,8 @@ __global__ __launch_bounds__(256, 2) void direct_gram_wide(const DirectMat* mats
     if (wk.mat < 0) return;
     const DirectMat& m = mats[wk.mat];
     const int lane = threadIdx.x & 63;
-    if (wk.a == wk.b) wide_tile<true>(m, wk.a, wk.b, wk.c, tickets, lane);
-    else wide_tile<false>(m, wk.a, wk.b, wk.c, tickets, lane);
+    if (wk.a == wk.b) wide_tile<true>(m, wk.a, wk.b, wk.c, lane);
+    else wide_tile<false>(m, wk.a, wk.b, wk.c, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1885,6 +1888,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.u = carve.take<double>((size_t)m.capacity * m.r);
     m.xch = carve.take<u64>((size_t)XCH * 64 * CLS_CHUNKS[m.cls]);
     m.gate = carve.take<u64>(1);
+    m.tickets = carve.take<unsigned>(ntiles);
     m.st = carve.take<int>(DS_WORDS);
     m.weight = carve.take<float>(m.capacity);
 }
@@ -1892,11 +1896,9 @@ void plan_matrix(Carver& carve, DirectMat& m)
 void plan_work(DirectPlan& plan)
 {
     size_t steps = 0, longest = 0;                               // of the recurrence, one point for every eigenvalue; of one
-    for (DirectMat& m : plan.mats) {
+    for (const DirectMat& m : plan.mats) {
         steps += (size_t)m.r * m.nt;
         longest = std::max(longest, (size_t)m.nt);
-        m.first_tile = (int)plan.n_tiles;
-        plan.n_tiles += (size_t)m.nt * (m.nt + 1) / 2;
     }
     // Lanes per eigenvalue in the search, which is bound by instruction issue: as many as one wave on every SIMD has, that is
     // as keep all SIMDs busy for one recurrence of the largest matrix (the smaller ones share a SIMD; by the number of eigenvalues
@@ -1977,8 +1979,10 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
         direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
         direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
     }
-    if (!plan.gram_wide.empty())
-        direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size(), t.tickets);
+    if (!plan.gram_wide.empty()) {
+        direct_clear_tickets<<<(unsigned)t.n_mats, 64, 0, stream>>>(t.mats);
+        direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size());
+    }
     if (gram_done) (void)hipEventRecord(gram_done, stream);
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
     if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);

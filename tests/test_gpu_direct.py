@@ -145,6 +145,24 @@ def test_calls_of_many_gram_tiles_give_the_bits_of_calls_of_their_own():
         assert a["count"] == b["count"] and all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")), j
 
 
+def test_calls_of_many_gram_tiles_one_after_the_other():
+    """A training loop: the descriptors of the first call are found on the device by the others, which have other numbers in the same
+    buffers, and each call counts the parts of its Gram matrices from nothing."""
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    mats = [torch.empty(512, 1152, device="cuda") for _ in range(31)] + [torch.empty(200, 300, device="cuda")]
+    msgs = None
+    for step in range(4):
+        for g in mats:
+            g.copy_(torch.randn(g.shape, generator=gen, device="cuda") * 0.01)
+            g[step] *= 40.0
+        msgs = binding.atomo_encode_svd(ctx(), mats, 3.0, step, 70, msgs=msgs, adaptive=1)
+        assert ctx().status()[0] == 0 and route(len(mats)) == [DIRECT] * len(mats)
+        for j in (0, 17, 30, 31):
+            one = binding.atomo_encode_svd(ctx(), [mats[j]], 3.0, step, 70 + j)[0]
+            a, b = one.to_host(), msgs[j].to_host()
+            assert a["count"] == b["count"] and all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")), (step, j)
+
+
 def test_a_training_loop_enqueues_the_direct_encode_alone_until_it_falls_short():
     shape = (200, 260)
     rng = np.random.default_rng(0)
