@@ -1528,8 +1528,8 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             ATOMO_HIP(ctx, hipStreamWaitEvent(s_direct, ctx->ev_fork, 0));
         }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, s_direct);
-        direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct,
-                       late ? ctx->ev_fork : nullptr);
+        ATOMO_HIP(ctx, direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct,
+                                      late ? ctx->ev_fork : nullptr));
         if (join_direct) ATOMO_HIP(ctx, hipEventRecord(join_direct, s_direct));
     }
     if (late && (rc = solve_thin()) != ATOMO_OK) return rc;

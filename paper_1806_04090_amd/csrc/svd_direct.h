@@ -85,9 +85,9 @@ struct DirectTables {
     const svd::Work *gram, *tiles, *gram_wide, *tri, *eig, *vec, *lng;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.  gram_done (may be null) is recorded
-// behind the Gram products.
-void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
-            hipEvent_t gram_done = nullptr);
+// behind the Gram products; if that fails nothing else is enqueued.
+hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
+                  hipEvent_t gram_done = nullptr);
 
 }  // namespace direct
 }  // namespace atomo

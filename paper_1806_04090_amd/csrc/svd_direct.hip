@@ -1971,8 +1971,8 @@ void plan_work(DirectPlan& plan)
         for (size_t k = 0; k < die[x].size(); ++k) plan.tri[8 * k + x] = die[x][k];
 }
 
-void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
-            hipEvent_t gram_done)
+hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
+                  hipEvent_t gram_done)
 {
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
     if (!plan.gram.empty()) {
@@ -1983,7 +1983,10 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
         direct_clear_tickets<<<(unsigned)t.n_mats, 64, 0, stream>>>(t.mats);
         direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size());
     }
-    if (gram_done) (void)hipEventRecord(gram_done, stream);
+    if (gram_done) {
+        const hipError_t rc = hipEventRecord(gram_done, stream);
+        if (rc != hipSuccess) return rc;                         // (who waits for it would not wait for this call)
+    }
     direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
     if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
@@ -1991,6 +1994,7 @@ void launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t se
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
     direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
     direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, t.n_mats, s, (u64)seed, hint_out, d_flags);
+    return hipSuccess;
 }
 
 }  // namespace direct
