@@ -65,7 +65,7 @@ struct DirectPlan {
     std::vector<svd::Work> gram, tiles, gram_wide, tri, eig, vec, lng;
     bool spread = false;             // deal the workgroups of a group over all dies (for tests)
     long long start_ticks = START_TICKS;
-    int eig_lanes = 64;              // lanes per eigenvalue in the search
+    int eig_lanes = 32;              // lanes per eigenvalue in the search, at most 32
     size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
     int max_nt = 1;
     size_t n_work() const { return gram.size() + tiles.size() + gram_wide.size() + tri.size() + eig.size() + vec.size() + lng.size(); }

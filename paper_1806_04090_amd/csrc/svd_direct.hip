@@ -846,7 +846,7 @@ struct TriOne {
     {
         constexpr int L = TS - S, S1 = S + 1 < TS ? S + 1 : S;
         const int k_end = min(16 * S + 16, ONE - 2);
-        const bool pair = 16 * S < ONE / 2 ? off < 0 && (store.N / 64 & 1) : first > 0 && !(store.N / 64 & 1);
+        const bool pair = first > 0 && !(store.N / 64 & 1);
         // where this lane's sum over a row goes (one that is none: to a place of its own)
         const int t = row_slot<L>(lane);
         const int sum_at = (lane & (L > 4 ? 1 : L > 2 ? 3 : L > 1 ? 7 : 15)) == 0 && t < L ? 16 * (S + t) + row : ONE + (int)threadIdx.x;
@@ -915,7 +915,7 @@ struct TriOne {
                     const double even = rg & 1 ? part[1] : part[0], odd = rg & 1 ? part[3] : part[2];
                     if (64 * h >= first) r[64 * h] = rg & 2 ? odd : even;
                 }
-                if (pair) r[(16 * S < ONE / 2 ? 0 : 64) - 64] = 0.0;
+                if (pair) r[0] = 0.0;
             } else if (wave == (k + 2 & 3)) {
                 if (lane < 16 && col == (k & 15)) {
                     kept[k].diagonal = x[S];
@@ -1254,7 +1254,7 @@ __global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats,
     }
     const bool zero = below[0] > asc;
     u64 g0 = SPAN * lo, g1 = zero ? g0 : g0 + SPAN;
-    const u64 group = lanes == 64 ? ~0ull : ((1ull << lanes) - 1) << base;
+    const u64 group = ((1ull << lanes) - 1) << base;
     while (!__all(g1 - g0 <= 1)) {
         const u64 z = g0 + (g1 - g0) * (unsigned)(l + 1) / (unsigned)(lanes + 1);
         // points with at most asc eigenvalues below
