@@ -1481,14 +1481,17 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
         return ATOMO_OK;
     };
     if (hint) hint->iterated = iterate;
-    // Thin matrices: beside all others on a stream of their own, from the caller's point in time; a few of them beside groups of
-    // workgroups (more than 128 rows) from the end of the Gram products.  A thin workgroup that is still on a compute unit when the
-    // groups are placed makes two of theirs share another one for the whole reduction (ResNet-18, two thin layers: 635
-    // us in two calls of three, 515 in the others and always so; 916 -> 868 us per call).  Behind the Gram products the groups are
-    // placed first, and at least 200 us are left, twice what 256 chunks take.
+    // Thin matrices: beside all others on a stream of their own, from the caller's point in time; beside groups of workgroups (more
+    // than 128 rows) from the end of the Gram products.  A thin workgroup that is still on a compute unit when the groups are placed
+    // makes two of theirs share another one for the whole reduction (ResNet-18, two thin layers: 635 us in two calls of three, 515
+    // in the others and always so).  Behind the Gram products the groups are placed first.  From the start / behind the
+    // Gram products, us: the directly solved layers of ResNet-18 with its two thin ones 963 / 849, with 384 chunks of positions 983 / 856,
+    // 1024 988 / 899, 2048 1061 / 921; 512 x 4608 with 512 chunks 786 / 784, 8192 1114 / 979; 129 x 1200 with 2048 243 / 219, 8192
+    // 424 / 420; 40 of 512 x 1152 with 256 1875 / 1852.  In front of an iteration it goes either way (ResNet-18 with
+    // adaptive = 0 2500 / 2956, 512 x 4608 with 1024 chunks 2065 / 1942): from the start there.
     const bool any_thin = !plan.thin.mats.empty();
     const bool beside = any_thin && (any_direct || iterate);
-    const bool late = beside && !iterate && plan.direct.max_nt > 2 && plan.thin.gram.size() <= 256;
+    const bool late = beside && !iterate && plan.direct.max_nt > 2;
     if (beside && (rc = ensure_side_streams(ctx)) != ATOMO_OK) return rc;
     auto solve_thin = [&]() -> int {
         hipStream_t s_thin = stream;

@@ -78,7 +78,7 @@ def test_kept_vectors_of_a_nearly_equal_tail_are_orthogonal(r, tail):
 
 @pytest.mark.parametrize("thin", [[(64, 27)], [(131072, 6)] * 2, [(131072, 6)] * 2 + [(9, 1025)]])
 def test_beside_groups_the_bits_of_a_call_of_their_own(thin):
-    """Up to 256 chunks of positions start behind the Gram products of larger matrices, more at once."""
+    """Thin matrices start behind the Gram products of the matrices that groups reduce, or at once where something iterates."""
     gen = torch.Generator(device="cuda").manual_seed(3)
     mats = []
     for m, n in [(192, 256), (96, 200)] + thin:
