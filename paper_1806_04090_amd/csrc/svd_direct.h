@@ -8,7 +8,10 @@ namespace direct {
 
 constexpr int MAX_R = 640;           // vectors on the shorter side that the reduction holds in registers
 constexpr int TILE = 64;
-constexpr size_t WIDE_MIN = 8192;    // work items of the Gram product from which on a wave takes a tile of its own (direct_gram_wide)
+// a wave takes a tile of the Gram product of its own (direct_gram_wide) in calls with so many such work items, of chunks of so many
+// columns
+constexpr size_t WIDE_MIN = 8192;
+constexpr int WIDE_COLUMNS = 256;
 constexpr double MAX_BUDGET = 32.0;  // above this many expected atoms the vectors cost more than the Jacobi iteration
 constexpr long long START_TICKS = 2000000;   // 20 ms of the 100 MHz clock: how long a workgroup waits for its group to start
 

@@ -262,7 +262,8 @@ __device__ inline void loads_from_here() { __builtin_amdgcn_fence(__ATOMIC_ACQUI
 // The last wave of a tile adds the partial tiles up beside the matrix instructions of the other wave on its SIMD.
 // 64 x (512 x 4608): 1325 us, of direct_gram and direct_gram_sum 1381 + 144; without the sums, which direct_gram_sum then takes 138 us
 // for, 1233.  Wide matrices (rows of A contiguous) whose chunks are whole 16s of columns.  A wave takes a tile of a chunk
-// of 576 columns 63 us or, two on a SIMD, twice that, so the call has to have many (WIDE_MIN).
+// of 576 columns 63 us or, two on a SIMD, twice that, so the call has to have many (WIDE_MIN); and the partial tiles that go through
+// memory, 32 KB each way, cost as much for a chunk of few columns as for one of many (WIDE_COLUMNS).
 // (The same hand-over in place of direct_gram_sum behind direct_gram: 64 x 576 14.4 -> 16.9 us, the ResNet-18 layers 124 -> 139:
 // stores of agent scope write through.)
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -1926,13 +1927,19 @@ void plan_work(DirectPlan& plan)
     }
     plan.n_eig = plan.eig.size();
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
-    if (plan.gram.size() >= WIDE_MIN) {
+    // us per encode, by direct_gram / by direct_gram_wide: 512 x 4608 (chunks of 576 columns) with 4032 items 1133 / 1140, 6048
+    // 1578 / 1569, 8064 1789 / 1747, 17856 3514 / 3319; 512 x 2048 (256) with 6048 1306 / 1317, 8064 1428 / 1403, 17856 2719 / 2620;
+    // 384 x 4608 (320) with 5985 1005 / 1035, 8190 1158 / 1136; 256 x 16384 (512) with 6080 933 / 953, 8320 1154 / 1135.  But 192 x 8192
+    // (160) with 8112 586 / 712, 18096 1102 / 1144; 320 x 3072 (160) with 8100 826 / 870; 256 x 4096 (128) with 8320 659 / 766, 17920
+    // 1194 / 1254.  Nor beside long chunks, which are then a launch of their own: 30 of 512 x 4608 with 60 of 256 x 2304 (128) 2548 / 2738,
+    // with 60 of 512 x 1152 (160) 3954 / 4628; the layers of four ResNet-18 gradients 1326 / 1427, but those of 16 4288 / 4214.
+    auto whole = [&](const Work& w) {
+        const DirectMat& m = plan.mats[w.mat];
+        return m.kchunk >= WIDE_COLUMNS && !m.transposed && m.M % 16 == 0 && (m.pad == 0 || w.a > 0) && m.ldg < 1 << 24;
+    };
+    if ((size_t)std::count_if(plan.gram.begin(), plan.gram.end(), whole) >= WIDE_MIN) {
         // A die works on the tiles of one chunk of columns of one matrix at a time, whose rows they share; the cheaper tiles
         // on the diagonal at the end, where an item more or less on a SIMD sets when the launch ends.
-        auto whole = [&](const Work& w) {
-            const DirectMat& m = plan.mats[w.mat];
-            return !m.transposed && m.M % 16 == 0 && (m.pad == 0 || w.a > 0) && m.ldg < 1 << 24;
-        };
         std::vector<Work> wide[2];
         for (const Work& w : plan.gram)
             if (whole(w)) wide[w.a == w.b].push_back(w);

@@ -123,9 +123,10 @@ def test_many_matrices_in_one_call_give_the_bits_of_calls_of_their_own():
 
 
 def test_calls_of_many_gram_tiles_give_the_bits_of_calls_of_their_own():
-    """From 8192 work items of the Gram product on, whole tiles of wide matrices are a wave's; tall, padded and odd ones beside them."""
+    """From 8192 work items of the Gram product on, whole tiles of wide matrices in chunks of 256 columns and more are a wave's; tall, padded
+    and odd ones and shorter chunks beside them."""
     gen = torch.Generator(device="cuda").manual_seed(11)
-    shapes = [(512, 1152)] * 30 + [(1152, 512), (500, 1024), (512, 1001), (449, 1040), (64, 640)]
+    shapes = [(512, 2048)] * 30 + [(2048, 512), (500, 2048), (512, 2041), (449, 2064), (64, 640), (512, 1152)]
     mats = []
     for m, n in shapes:
         wide = torch.randn(m, n + 3, generator=gen, device="cuda") * 0.01
@@ -135,7 +136,7 @@ def test_calls_of_many_gram_tiles_give_the_bits_of_calls_of_their_own():
     sigma = torch.zeros(total, device="cuda")
     many = binding.atomo_encode_svd(ctx(), mats, 3.0, 4, 70, sigma_out=sigma)
     assert ctx().status()[0] == 0 and route(len(shapes)) == [DIRECT] * len(shapes)
-    for j in (0, 13, 29, 30, 31, 32, 33, 34):
+    for j in (0, 13, 29, 30, 31, 32, 33, 34, 35):
         r, at = min(shapes[j]), sum(min(s) for s in shapes[:j])
         own = torch.zeros(r, device="cuda")
         one = binding.atomo_encode_svd(ctx(), [mats[j]], 3.0, 4, 70 + j, sigma_out=own)[0]
@@ -149,7 +150,7 @@ def test_calls_of_many_gram_tiles_one_after_the_other():
     """A training loop: the descriptors of the first call are found on the device by the others, which have other numbers in the same
     buffers, and each call counts the parts of its Gram matrices from nothing."""
     gen = torch.Generator(device="cuda").manual_seed(12)
-    mats = [torch.empty(512, 1152, device="cuda") for _ in range(31)] + [torch.empty(200, 300, device="cuda")]
+    mats = [torch.empty(512, 2048, device="cuda") for _ in range(31)] + [torch.empty(200, 300, device="cuda")]
     msgs = None
     for step in range(4):
         for g in mats:
