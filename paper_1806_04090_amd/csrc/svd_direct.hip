@@ -1956,7 +1956,10 @@ void plan_work(DirectPlan& plan)
     // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].r > plan.mats[b].r; });
     // Twice the workgroups for matrices of 257 to 512 rows, if every workgroup of the call has a compute unit to itself then: four of
-    // 512 rows and five of 256 480 -> 455 us for the first 384 steps; 64 of 512 rows, where it has not, 1395 -> 2297.
+    // 512 rows and five of 256 480 -> 455 us for the first 384 steps; 64 of 512 rows, where it has not, 1395 -> 2297.  What else runs on
+    // the device is not known here: the encode of ResNet-18 takes 881 us alone (16 workgroups: 901), 3310 beside the same
+    // encode of another context (2985) and 3.9 ms, one call in ten 4.5 - 5.6, beside 8192^3 products in bf16 (3.0 - 3.8, 3.9).  In 60
+    // calls each beside these, fp32 products, long products and copies no group gave up its wait for its workgroups.
     int total = 0;
     for (const DirectMat& m : plan.mats) total += m.cls == CLS_512 ? 32 : CLS_WGS[m.cls];
     const bool wide = total <= 256;

@@ -391,7 +391,10 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
 // the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
 // zeros aside; vectors with a small residual, kept ones apart); otherwise the two-sided Jacobi iteration.  18
 // columns: 33 us, 28 of them without the sums of the largest matrices (42 and 31 with the matrix, T and the partial sums read
-// from memory and LDS step by step); Jacobi in eight sweeps 73.
+// from memory and LDS step by step); Jacobi in eight sweeps 73.  T takes 96 of its 158 registers for 18 columns, 128 for 32: two waves on
+// every SIMD do not fit beside a workgroup of the reduction of larger matrices (240 registers) any more, and where those fill
+// the chip it waits for the first of them to end.  That costs a call nothing: the directly solved layers of ResNet-18 with its two thin
+// ones 851 us, 852 with a form of 124 registers that fits; with 256 chunks of positions 853 and 857, with 100 small matrices 859 and 860.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.

@@ -164,6 +164,29 @@ def test_calls_of_many_gram_tiles_one_after_the_other():
             assert a["count"] == b["count"] and all(np.array_equal(a[k], b[k]) for k in ("idx", "w", "U", "V")), (step, j)
 
 
+def test_beside_the_work_of_another_stream():
+    """Groups find their places among other workgroups, or give up in bounded time and are reduced alone: a message either way."""
+    shapes = [(512, 700), (300, 400), (129, 260), (64, 100), (900, 18)]
+    host = [inputs.low_rank_plus_noise(np.random.default_rng(j), m, n, [1.0, 0.3], 0.02) for j, (m, n) in enumerate(shapes)]
+    mats = [dev(g) for g in host]
+    a, c = torch.ones(4096, 4096, device="cuda"), torch.empty(4096, 4096, device="cuda")
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    want = [m.to_host() for m in binding.atomo_encode_svd(ctx(), mats, 3.0, 6, 90)]
+    torch.cuda.synchronize()
+    for adaptive in (0, 1, 1, 1):
+        with torch.cuda.stream(two):
+            for _ in range(3):
+                torch.mm(a, a, out=c)
+        msgs = binding.atomo_encode_svd(ctx(), mats, 3.0, 6, 90, adaptive=adaptive, stream=one)
+        one.synchronize()
+        assert ctx().status(one)[0] == 0
+        for m, w in zip(msgs, want):
+            got = m.to_host()
+            assert got["count"] == w["count"] and np.array_equal(got["idx"], w["idx"])
+            np.testing.assert_allclose(got["w"], w["w"], rtol=1e-6)
+    torch.cuda.synchronize()
+
+
 def test_a_training_loop_enqueues_the_direct_encode_alone_until_it_falls_short():
     shape = (200, 260)
     rng = np.random.default_rng(0)
