@@ -260,8 +260,8 @@ __device__ inline void loads_from_here() { __builtin_amdgcn_fence(__ATOMIC_ACQUI
 // top (measured: 66 cycles alone, 73 with one conversion from float beside it, 80 with two).  direct_gram has one conversion per
 // matrix instruction and more around it, this one 40 instructions per 64 of them, and leaves out the sub-tiles below the diagonal.
 // The last wave of a tile adds the partial tiles up beside the matrix instructions of the other wave on its SIMD.
-// 64 x (512 x 4608): 1325 us, of direct_gram and direct_gram_sum 1381 + 144; without the sums, which direct_gram_sum then takes 138 us
-// for, 1233.  Wide matrices (rows of A contiguous) whose chunks are whole 16s of columns.  A wave takes a tile of a chunk
+// 64 x (512 x 4608), calls one after the other: 1331 us, of direct_gram and direct_gram_sum 1400 + 140; without the sums, which
+// direct_gram_sum then takes 138 us for, 1233.  Wide matrices (rows of A contiguous) whose chunks are whole 16s of columns.  A wave takes a tile of a chunk
 // of 576 columns 63 us or, two on a SIMD, twice that, so the call has to have many (WIDE_MIN); and the partial tiles that go through
 // memory, 32 KB each way, cost as much for a chunk of few columns as for one of many (WIDE_COLUMNS).
 // (The same hand-over in place of direct_gram_sum behind direct_gram: 64 x 576 14.4 -> 16.9 us, the ResNet-18 layers 124 -> 139:
