@@ -30,7 +30,7 @@ namespace {
 enum { CLS_64 = 0, CLS_128, CLS_256, CLS_512, CLS_640, CLS_COUNT };
 // columns / 64, workgroups of the group
 constexpr int CLS_CHUNKS[CLS_COUNT] = {1, 2, 4, 8, 10};
-constexpr int XCH = 5;            // vectors in the exchange slots of a group, see Tri
+constexpr int XCH = 6;            // vectors in the exchange slots of a group, see Tri
 constexpr int CLS_WGS[CLS_COUNT] = {1, 1, 16, 16, 32};
 
 __device__ inline double fold8(double a, double b, int lane)
@@ -51,6 +51,36 @@ __device__ inline double wave_sums(const double (&v)[K], int lane)
     for (int i = 0; i < K2; ++i) b[i] = fold16(a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i]);
     return sum8(fold8(b[0], K2 > 1 ? b[1] : b[0], lane));
 }
+// K <= 64 sums over the 64 lanes at once: lane l receives sum number reverse6(l) & (2^number_bits(K) - 1) (there may be none of it)
+template <int K, typename Fold, typename Add>
+__device__ inline void halve(const double (&in)[K], double (&out)[(K + 1) / 2], Fold fold, Add add)
+{
+#pragma unroll
+    for (int i = 0; i < K / 2; ++i) out[i] = fold(in[2 * i], in[2 * i + 1]);
+    if constexpr (K & 1) out[K / 2] = add(in[K - 1]);
+}
+template <int CTRL>
+__device__ inline double fold_dpp(bool up, double a, double b)
+{
+    const double keep = up ? b : a, give = up ? a : b;
+    return keep + dpp<CTRL>(give);
+}
+template <int K>
+__device__ inline double lane_sums(const double (&v)[K], int lane)
+{
+    constexpr int K1 = (K + 1) / 2, K2 = (K1 + 1) / 2, K3 = (K2 + 1) / 2, K4 = (K3 + 1) / 2, K5 = (K4 + 1) / 2;
+    static_assert(K5 <= 2, "a sum per lane");
+    double a[K1], b[K2], c[K3], d[K4], e[K5], f[1];
+    halve(v, a, [](double x, double y) { return fold32(x, y); }, [](double x) { return fold32(x, x); });
+    halve(a, b, [](double x, double y) { return fold16(x, y); }, [](double x) { return fold16(x, x); });
+    halve(b, c, [&](double x, double y) { return fold_dpp<DPP_ROR8>(lane & 8, x, y); }, [](double x) { return x + dpp<DPP_ROR8>(x); });
+    halve(c, d, [&](double x, double y) { return fold_dpp<DPP_HALF_MIRROR>(lane & 4, x, y); }, [](double x) { return x + dpp<DPP_HALF_MIRROR>(x); });
+    halve(d, e, [&](double x, double y) { return fold_dpp<DPP_XOR2>(lane & 2, x, y); }, [](double x) { return x + dpp<DPP_XOR2>(x); });
+    halve(e, f, [&](double x, double y) { return fold_dpp<DPP_XOR1>(lane & 1, x, y); }, [](double x) { return x + dpp<DPP_XOR1>(x); });
+    return f[0];
+}
+constexpr int number_bits(int k) { return k > 1 ? 1 + number_bits((k + 1) / 2) : 0; }
+__host__ __device__ constexpr int reverse6(int l) { return (l & 1) << 5 | (l & 2) << 3 | (l & 4) << 1 | (l & 8) >> 1 | (l & 16) >> 3 | (l & 32) >> 5; }
 // The value is worked out where this stands and not where it is used first (behind a wait, as a rule).
 __device__ inline void here(double& x) { asm volatile("" : "+v"(x)); }
 __device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2; }
@@ -429,11 +459,12 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // last step's update, whose share is a product with two sums of y (v_i (w y) + w_i (v y)).  The update itself, the reflector and the
 // row of the next step (handed over a step early, the readers add the update that it lacks) come behind it, while the entries
 // travel; the loads that look for them go out in the middle of that work (a load of 512 bytes by every wave takes 250 cycles, four of
-// them 460, whether the entries are there or not).
-// An entry is one 8-byte store whose two lowest mantissa bits carry the step number mod 4: a reader knows from the value
-// that it is the one of this step, no flag and no second round trip.  Two slots for A y by step parity: a wave that publishes
-// step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more; three for the
-// rows, which are written a step ahead.
+// them 460, whether the entries are there or not; a look that is too early costs a second one).  The ResNet-18 layers in 468 us with
+// the look there, 495 behind the reflector's vector, 575 in front of the update; two looks on their way at once 485.
+// An entry is one 8-byte store whose two lowest mantissa bits carry a tag that tells it from the one that lay there before: a reader
+// knows from the value that it is the one of this step, no flag and no second round trip.  Two slots for A y by step parity: a wave
+// that publishes step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more; four for
+// the rows, which are written a step ahead.
 // The workgroups of a group sit on one die (blockIdx mod 8), whose L2 the exchange goes through: 0.77 us per step among 64
 // waves, against 5 us through memory; they check that with the die's number, and store through to memory if it is not so.
 // (On one die the stores have workgroup scope, which the memory model does not extend to other workgroups.  What carries them
@@ -442,9 +473,12 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // Waits: nothing guarantees that a group is resident as a whole - other work on the GPU can hold the places that its last
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
-// Bound: the chain of steps.  448 steps of 512 rows: 1.5 us each at the beginning and 0.8 at the end on 64 waves, 515 us in all on 128
-// (1.4 us per step with the update, the norm and the root in front of the product).  Four groups per die, two waves on every
-// SIMD: the issue of the vectors that every wave works out for itself.
+// Bound: what a wave does for itself in a step, one wave on every SIMD: without the waits for the others a step takes as long.  448
+// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 468 us in all (517 with a chain of branches and
+// v_readlane for what a vector holds at the wave's rows, a reduction of its own for the norm, and the reflector behind the update; 800
+// of 3500 cycles).  Rows and columns split between the waves of a workgroup, two instead of eight entries of a vector per lane: 566, for
+// a second barrier and sums of sixteen rows.  Four groups per die, two waves on every SIMD: the issue of the vectors that every wave
+// works out for itself.
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
 // waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
@@ -501,62 +535,54 @@ struct Tri {
     static constexpr int CN = 64 * C, W = 64 * QW, OWN = (C + 3) / 4;
     static constexpr int LAST = C - TAIL / 64 - 1;               // the last chunk of columns that is reduced here
     double a[R][C];
-    double x[C], v[C], wv[C];        // column k; the last step's vectors, which the rows have still to be updated with
-    double vr[R];                    // v at the rows of the wave
+    // Column k; the last step's vectors, which the rows have still to be updated with.  [C]: their entries at the wave's rows, row
+    // slot t in lane t of every row of 16 lanes, from where they are broadcast.
+    double x[C + 1], v[C + 1], wv[C + 1];
     double tau, diagonal, beta;      // the last step's
     Global<u64> slots;
     double2 (*shared)[CN];           // [2][CN] by step parity: p and column k + 1
-    int lane, wave, member, w, wl, q, off, k_first, spin_limit;
-    int third;                       // step mod 3
+    int lane, wave, member, w, q, off, k_first, spin_limit;
+    int row_turn, keep_turn;         // the next steps at which this wave hands over a row, its workgroup keeps a vector
+    int row_number;                  // the row of this lane in the vectors' last part
     bool local;                      // the group sits on one die
 
-    template <bool LOCAL>
-    static __device__ inline void put(Global<u64> p, double value, u64 tag)
+    static __device__ inline u64 entry(double value, u64 tag) { return ((u64)__double_as_longlong(value) & ~3ull) | tag; }
+    static __device__ inline double value(u64 entry) { return __longlong_as_double((long long)(entry & ~3ull)); }
+    static __device__ inline Global<u64> at_byte(Global<u64> slot, unsigned byte) { return (Global<u64>)((Global<char>)slot + byte); }
+    __device__ inline void put(Global<u64> p, u64 entry) const
     {
-        const u64 x = ((u64)__double_as_longlong(value) & ~3ull) | tag;
-        if (LOCAL) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (__builtin_expect(!local, 0)) __hip_atomic_store(p, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // a row of the matrix, in row slot T of this wave
     template <int P, int T>
     __device__ inline void put_row(Global<u64> slot, u64 tag) const
     {
-        if (__builtin_expect(local, 1)) {
 #pragma unroll
-            for (int c = P; c < C; ++c) put<true>(slot + lane + 64 * c, a[T][c], tag);
-        } else {
-#pragma unroll
-            for (int c = P; c < C; ++c) put<false>(slot + lane + 64 * c, a[T][c], tag);
-        }
+        for (int c = P; c < C; ++c) put(slot + lane + 64 * c, entry(a[T][c], tag));
     }
     template <int T>
     __device__ inline void put_first(int row) const
     {
-        if (w + W * T == row) put_row<0, T>(slots + (2 + 1) * CN, 1);
+        if (w + W * T == row) put_row<0, T>(slot_c(1), 1);
         if constexpr (T + 1 < R) put_first<T + 1>(row);
     }
-    // entry of row slot t of a vector whose chunks before P are finished (0 there)
-    template <int P, int T>
-    __device__ inline double own(const double (&vec)[C]) const
-    {
-        if constexpr (QW == 1) {
-            return lane_value(vec[T], wl);
-        } else {
-            constexpr int c0 = 2 * T >= P ? 2 * T : 2 * T + 1;
-            if (q == 0) return 2 * T >= P ? lane_value(vec[c0], wl) : 0.0;
-            return lane_value(vec[2 * T + 1], wl);
-        }
-    }
-    template <int P, int T>
-    __device__ inline void entries(const double (&vec)[C], double (&at)[R]) const
+    // where the entries of A y and of the column of a step lie, and their tags (a cleared slot has tag 0; steps count from 1)
+    __device__ inline Global<u64> slot_p(unsigned step) const { return slots + (step & 1) * CN; }
+    __device__ inline Global<u64> slot_c(unsigned step) const { return slots + (2 + (step & 3)) * CN; }
+    static __device__ inline unsigned tag_p(unsigned step) { return step & 3; }
+    static __device__ inline unsigned tag_c(unsigned step) { return (step >> 2) + 1 & 3; }
+    // a vector's entries at the wave's rows
+    template <int T0, int T = T0>
+    static __device__ inline void entries(double vec, double (&at)[R])
     {
         if constexpr (T < R) {
-            at[T] = own<P, T>(vec);
-            entries<P, T + 1>(vec, at);
+            at[T] = row_lane<T>(vec);
+            entries<T0, T + 1>(vec, at);
         }
     }
     template <int P, int T0>
-    __device__ inline void update(const double (&wr)[R])
+    __device__ inline void update(const double (&wr)[R], const double (&vr)[R])
     {
 #pragma unroll
         for (int t = T0; t < R; ++t)
@@ -565,6 +591,14 @@ struct Tri {
                 a[t][c] = fma(-wr[t], v[c], fma(-vr[t], wv[c], a[t][c]));
                 here(a[t][c]);
             }
+    }
+    template <int P, int T0>
+    __device__ inline void update()
+    {
+        double wr[R], vr[R];
+        entries<T0>(wv[C], wr);
+        entries<T0>(v[C], vr);
+        update<P, T0>(wr, vr);
     }
 
     // step k - 1, every wave of the workgroup a part; with zeros in what is finished of its vector (that is read in pairs of chunks)
@@ -585,128 +619,132 @@ struct Tri {
     {
         constexpr int T0 = P / QW;                               // row slots before T0 are finished
         constexpr int PN = P + 1;
+        constexpr int K = R - T0 + 1;                            // sums of a step: the entries of A y, and y y
+        constexpr int J0 = P / 4, L = OWN - J0;
+        // this wave's chunks of p and of the column (one of a finished chunk: any other)
+        unsigned at[L];
+#pragma unroll
+        for (int j = 0; j < L; ++j) at[j] = 8u * (unsigned)(lane + 64 * min(max(wave + 4 * (j + J0), P), C - 1));
+        const int row_at = max(row_number, 64 * P);
+        // (a sum is in several lanes, the first of them hands it over)
+        const unsigned sum_at = 8u * (unsigned)(w + W * (T0 + reverse6(lane)));
+        const bool mine = reverse6(lane) < R - T0;
         for (; k < 64 * PN; ++k) {
-            const int k1 = k + 1, l1 = k1 & 63;
-            const bool next_chunk = l1 == 0;                     // row k + 1 is the first of chunk P + 1
-            const unsigned step = (unsigned)(k - k_first + 1);   // (from 1: the cleared slots carry tag 0)
-            const u64 tag = step & 3;
-            const Global<u64> slot_p = slots + (step & 1) * CN, slot_c = slots + (2 + third) * CN;
-            third = third == 2 ? 0 : third + 1;
-            double y[C], vy = 0.0, wy = 0.0;
+            const int k1 = k + 1;
+            const bool next_chunk = k1 == 64 * PN;               // row k + 1 is the first of chunk P + 1
+            const unsigned step = (unsigned)(k - k_first + 1);
+            u64 pu[L], cu[L];
+            auto look_p = [&]() {
+#pragma unroll
+                for (int j = 0; j < L; ++j) pu[j] = __hip_atomic_load(at_byte(slot_p(step), at[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            auto look_c = [&]() {
+#pragma unroll
+                for (int j = 0; j < L; ++j) cu[j] = __hip_atomic_load(at_byte(slot_c(step), at[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            double y[C + 1], sum[K], vy = 0.0, wy = 0.0, sq = 0.0;
 #pragma unroll
             for (int c = P; c < C; ++c) {
                 y[c] = c > PN || lane + 64 * c > k1 ? x[c] : 0.0;
                 vy = fma(v[c], y[c], vy);
                 wy = fma(wv[c], y[c], wy);
+                sq = fma(y[c], y[c], sq);
             }
-            double wr[R], part[R - T0];
-            entries<P, T0>(wv, wr);
+            double wr[R], vr[R];
+            entries<T0>(wv[C], wr);
+            entries<T0>(v[C], vr);
 #pragma unroll
             for (int t = T0; t < R; ++t) {
-                double sum = fma(-wr[t], vy, -vr[t] * wy);
+                double s = a[t][P] * y[P];
 #pragma unroll
-                for (int c = P; c < C; ++c) sum = fma(a[t][c], y[c], sum);
-                part[t - T0] = sum;
+                for (int c = PN; c < C; ++c) s = fma(a[t][c], y[c], s);
+                sum[t - T0] = fma(-wr[t], vy, fma(-vr[t], wy, s));
             }
-            {
-                const double p = wave_sums<R - T0>(part, lane);
-                const int t = T0 + sum_slot(lane);
-                if ((lane & 7) == 0 && t < R) {
-                    if (__builtin_expect(local, 1)) put<true>(slot_p + w + W * t, p, tag);
-                    else put<false>(slot_p + w + W * t, p, tag);
-                }
+            sum[K - 1] = sq;
+            const double sums = lane_sums<K>(sum, lane);
+            if (mine) put(at_byte(slot_p(step), sum_at), entry(sums, tag_p(step)));
+            // behind what the others wait for: the last step's vector (one workgroup keeps it for the way back), the reflector beside
+            // the matrix, the row that the next step hands over
+            __builtin_amdgcn_sched_barrier(0);
+            look_c();
+            if (__builtin_expect(k == keep_turn, 0)) {
+                keep<P>(k, store);
+                keep_turn += W / 4;
             }
-            // behind what the others wait for: the last step's reflector (one wave keeps it for the way back), the matrix, the row
-            // that the next step hands over
-            __builtin_amdgcn_sched_barrier(0);
-            if (__builtin_expect(member == (k - 1 & (W / 4 - 1)) && k > k_first, 0)) keep<P>(k, store);
-            update<P, T0>(wr);
-            if (__builtin_expect(wl == (k + 2 & 63), 0)) {
-                const Global<u64> slot = slots + (2 + third) * CN;
-                if (k + 2 < 64 * PN) {
-                    if (q == P % QW) put_row<P, P / QW>(slot, step + 1 & 3);
-                } else if (q == PN % QW) {
-                    put_row<P, PN / QW>(slot, step + 1 & 3);
-                }
-            }
-            double sq = 0.0;
-#pragma unroll
-            for (int c = P; c < C; ++c) sq = fma(y[c], y[c], sq);
-            const double sig2 = wave_sum(sq), alpha = lane_value(next_chunk ? x[PN] : x[P], l1);
-            __builtin_amdgcn_sched_barrier(0);
-            // this wave's chunks of p and of the column (one of a finished chunk: any other), then the workgroup's; they are on
-            // their way while the reflector is worked out
-            constexpr int J0 = P / 4;
-            int at[OWN - J0];
-            u64 pu[OWN - J0], cu[OWN - J0];
-#pragma unroll
-            for (int j = J0; j < OWN; ++j) at[j - J0] = lane + 64 * min(max(wave + 4 * j, P), C - 1);
-            auto look = [&]() {
-#pragma unroll
-                for (int j = 0; j < OWN - J0; ++j) {
-                    pu[j] = __hip_atomic_load(slot_p + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    cu[j] = __hip_atomic_load(slot_c + at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            };
-            look();
-            __builtin_amdgcn_sched_barrier(0);
+            const double sig2 = lane_value(sums, reverse6(K - 1)), alpha = lane_value(next_chunk ? x[PN] : x[P], k1 & 63);
             double v0;
             householder(alpha, sig2, beta, v0);
             tau = householder_tau(sig2, v0);
+            if constexpr (R <= 5) update<P, T0>(wr, vr);
+            else update<P, T0>();                                // (broadcast once more: no registers left to keep them)
+            here(v0);
+            here(tau);
+            if (__builtin_expect(k == row_turn, 0)) {
+                if (k + 2 < 64 * PN) {
+                    if (q == P % QW) put_row<P, P / QW>(slot_c(step + 1), tag_c(step + 1));
+                } else if (q == PN % QW) {
+                    put_row<P, PN / QW>(slot_c(step + 1), tag_c(step + 1));
+                }
+                row_turn += 64;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            look_p();
+            __builtin_amdgcn_sched_barrier(0);
             diagonal = lane_value(x[P], k & 63);
-            double fresh[C];                                     // what the row of this step lacks of the last step's update
+            double fresh[C + 1];                                 // what the row of this step lacks of the last step's update
             {
-                const double v1 = lane_value(next_chunk ? v[PN] : v[P], l1), w1 = lane_value(next_chunk ? wv[PN] : wv[P], l1);
+                const double v1 = lane_value(next_chunk ? v[PN] : v[P], k1 & 63), w1 = lane_value(next_chunk ? wv[PN] : wv[P], k1 & 63);
 #pragma unroll
-                for (int c = P; c < C; ++c) {
+                for (int c = P; c <= C; ++c) {
                     fresh[c] = fma(-w1, v[c], -v1 * wv[c]);
                     here(fresh[c]);
                 }
             }
+            y[C] = row_number > k1 ? x[C] : 0.0;
 #pragma unroll
-            for (int c = P; c < C; ++c) {
-                v[c] = c <= PN && lane + 64 * c == k1 ? v0 : y[c];
+            for (int c = P; c <= C; ++c) {
+                v[c] = c == C ? (row_number == k1 ? v0 : y[c]) : c <= PN && lane + 64 * c == k1 ? v0 : y[c];
                 here(v[c]);
             }
-            here(tau);
-            entries<P, T0>(v, vr);
             __builtin_amdgcn_sched_barrier(0);
             auto ready = [&]() {
                 unsigned other = 0;
 #pragma unroll
-                for (int j = 0; j < OWN - J0; ++j) other |= ((unsigned)pu[j] ^ (unsigned)tag) | ((unsigned)cu[j] ^ (unsigned)tag);
+                for (int j = 0; j < L; ++j) other |= ((unsigned)pu[j] ^ tag_p(step)) | ((unsigned)cu[j] ^ tag_c(step));
                 return __all((other & 3u) == 0u);
             };
             if (__builtin_expect(!ready(), 0)) {
-                int spins = 0;
-                do {
+                for (int spins = 0; !ready(); look_p(), look_c())
                     if (++spins > spin_limit) {                  // (once: the steps after it wait for nothing)
                         spin_limit = 0;
                         break;
                     }
-                    look();
-                } while (!ready());
             }
             double2* sh = shared[step & 1];
 #pragma unroll
-            for (int j = 0; j < OWN - J0; ++j)
-                sh[at[j]] = make_double2(__longlong_as_double((long long)(pu[j] & ~3ull)),
-                                         __longlong_as_double((long long)(cu[j] & ~3ull)));
+            for (int j = 0; j < L; ++j) sh[at[j] / 8] = make_double2(value(pu[j]), value(cu[j]));
             __syncthreads();
-            double p[C], gamma = 0.0;
+            double2 pc[C + 1];
 #pragma unroll
-            for (int c = P; c < C; ++c) {
-                const double2 pc = sh[lane + 64 * c];
-                x[c] = pc.y + fresh[c];
-                p[c] = c <= PN && lane + 64 * c <= k ? 0.0 : fma(v0, x[c], pc.x);
-                gamma = fma(v[c], p[c], gamma);
+            for (int c = P; c <= C; ++c) pc[c] = sh[c < C ? lane + 64 * c : row_at];
+            __builtin_amdgcn_sched_barrier(0);                   // (all of them are on their way at once)
+            double p[C + 1], gamma = 0.0;
+#pragma unroll
+            for (int c = P; c <= C; ++c) {
+                x[c] = pc[c].y + fresh[c];
+                p[c] = fma(v0, x[c], pc[c].x);
+                if (c == C) p[c] = row_number <= k ? 0.0 : p[c];
+                else if (c <= PN) p[c] = lane + 64 * c <= k ? 0.0 : p[c];
+                if (c < C) gamma = fma(v[c], p[c], gamma);
             }
+            const double pk1 = tau * lane_value(next_chunk ? p[PN] : p[P], k1 & 63);
             gamma = wave_sum(gamma) * tau * (0.5 * tau);
+            const double wk1 = fma(-gamma, v0, pk1);
 #pragma unroll
-            for (int c = P; c < C; ++c) wv[c] = fma(-gamma, v[c], tau * p[c]);
-            const double wk1 = lane_value(next_chunk ? wv[PN] : wv[P], l1);
-#pragma unroll
-            for (int c = P; c < C; ++c) x[c] = fma(-wv[c], v0, fma(-v[c], wk1, x[c]));
+            for (int c = P; c <= C; ++c) {
+                wv[c] = fma(-gamma, v[c], tau * p[c]);
+                x[c] = fma(-wv[c], v0, fma(-v[c], wk1, x[c]));
+            }
         }
     }
 
@@ -729,8 +767,8 @@ struct Tri {
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         w = member * 4 + wave;
-        wl = w & 63;
         q = w >> 6;
+        row_number = w + W * min(lane & 15, R - 1);
         off = CN - N;
         slots = global(mm.xch);
         const bool last = Gate::start(global(mm.gate), n_wgs, start_ticks);
@@ -747,24 +785,22 @@ struct Tri {
         }
         int k = off + mm.pad;
         k_first = k;
+        // (a wave has its rows of a chunk once, its workgroup every (W / 4)th vector from the first step's on)
+        row_turn = k + (w - (k + 2) & 63);
+        keep_turn = k + 1 + (member - k & (W / 4 - 1));
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const int j = lane + 64 * c - off;
+        for (int c = 0; c <= C; ++c) {
+            const int j = (c < C ? lane + 64 * c : row_number) - off;
             x[c] = j >= 0 ? scale * global(mm.C)[(size_t)mm.pad * N + j] : 0.0;
             v[c] = wv[c] = 0.0;
         }
         if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
-        third = 1;
-#pragma unroll
-        for (int t = 0; t < R; ++t) vr[t] = 0.0;
         put_first<0>(k + 1);
         phases<0>(k, store);
         // what is left goes back to memory
         constexpr int T0 = (LAST + 1) / QW;
-        if (member == (k - 1 & (W / 4 - 1))) keep<LAST + 1>(k, store);
-        double wr[R];
-        entries<LAST + 1, T0>(wv, wr);
-        update<LAST + 1, T0>(wr);
+        if (k == keep_turn) keep<LAST + 1>(k, store);
+        update<LAST + 1, T0>();
 #pragma unroll
         for (int t = T0; t < R; ++t) {
             const Global<double> row = global(mm.C) + (size_t)(w + W * t - off) * N + lane - off;
