@@ -67,6 +67,7 @@ __device__ inline void for_lanes(F&& f)
         for_lanes<L + 1>(f);
     }
 }
+constexpr int DPP_SHL1 = 0x101, DPP_SHL2 = 0x102, DPP_SHL4 = 0x104, DPP_SHL8 = 0x108;    // lane l: what lane l + n of its row has, or 0
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_ROR8 = 0x128;
 
 // lanes 0..31 of the result: a of the lane plus a of lane + 32; lanes 32..63: b of both
@@ -110,7 +111,7 @@ __device__ inline double lane_value(double x, int lane)
 // root makes v a multiple of the first unit vector and the step a change of sign.  The trace is about 1.)
 __device__ inline void householder(double alpha, double sig2, double& beta, double& v0)
 {
-    beta = -copysign(root(fma(alpha, alpha, fmax(sig2, 1e-280))), alpha);
+    beta = -copysign(root(fma(alpha, alpha, fmax(sig2, 1e-150))), alpha);
     v0 = alpha - beta;
 }
 __device__ inline double householder_tau(double sig2, double v0) { return 2.0 * reciprocal(fma(v0, v0, sig2)); }

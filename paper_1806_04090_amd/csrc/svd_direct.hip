@@ -51,7 +51,8 @@ __device__ inline double wave_sums(const double (&v)[K], int lane)
     for (int i = 0; i < K2; ++i) b[i] = fold16(a[2 * i], 2 * i + 1 < K1 ? a[2 * i + 1] : a[2 * i]);
     return sum8(fold8(b[0], K2 > 1 ? b[1] : b[0], lane));
 }
-// K <= 64 sums over the 64 lanes at once: lane l receives sum number reverse6(l) & (2^number_bits(K) - 1) (there may be none of it)
+// K <= 64 sums over the 64 lanes at once: lane l receives sum number reverse6(l), in as many of its bits as K needs
+// (there may be none of that number)
 template <int K, typename Fold, typename Add>
 __device__ inline void halve(const double (&in)[K], double (&out)[(K + 1) / 2], Fold fold, Add add)
 {
@@ -79,7 +80,6 @@ __device__ inline double lane_sums(const double (&v)[K], int lane)
     halve(e, f, [&](double x, double y) { return fold_dpp<DPP_XOR1>(lane & 1, x, y); }, [](double x) { return x + dpp<DPP_XOR1>(x); });
     return f[0];
 }
-constexpr int number_bits(int k) { return k > 1 ? 1 + number_bits((k + 1) / 2) : 0; }
 __host__ __device__ constexpr int reverse6(int l) { return (l & 1) << 5 | (l & 2) << 3 | (l & 4) << 1 | (l & 8) >> 1 | (l & 16) >> 3 | (l & 32) >> 5; }
 // The value is worked out where this stands and not where it is used first (behind a wait, as a rule).
 __device__ inline void here(double& x) { asm volatile("" : "+v"(x)); }
@@ -738,7 +738,7 @@ struct Tri {
                 if (c < C) gamma = fma(v[c], p[c], gamma);
             }
             const double pk1 = tau * lane_value(next_chunk ? p[PN] : p[P], k1 & 63);
-            gamma = wave_sum(gamma) * tau * (0.5 * tau);
+            gamma = wave_sum(gamma) * (tau * (0.5 * tau));
             const double wk1 = fma(-gamma, v0, pk1);
 #pragma unroll
             for (int c = P; c <= C; ++c) {
@@ -826,10 +826,12 @@ struct Tri {
 // One barrier per step.  What is handed over is (A y)_i, y the column below its first entry, and column k + 1 before the
 // step: the reflector v = y + v0 e_{k+1} is wanted only behind the barrier (A v = A y + v0 A e_{k+1}), so that the norm, the root
 // and the reciprocal run beside the products.
-// Bound: a step of 64 rows is a chain of about 300 instructions with one wave on every SIMD, 0.55 us; at 128 rows it is the issue of
-// 550, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix took 61 us with four waves that each owned columns and broadcast
-// through v_readlane, now 39.5 (42.4 with steps in runs of 32 and two 32-bit moves per broadcast).  What a group leaves is worked
-// off by one compute unit instead of 16 or 32.
+// All waves do the same in a step, but for the three numbers that one of them keeps: the column is handed over by the lanes that have
+// it, one of every row, and every row of lanes keeps the vector's entries at its rows.
+// Bound: a step of 64 rows is a chain of about 250 instructions with one wave on every SIMD, 0.53 us; at 128 rows it is the issue of
+// 500, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix takes 36.5 us (39.5 with a wave in turn that handed the column
+// over and one that kept the vector, and with loads for rows that are not there).  What a group leaves is worked off by one compute
+// unit instead of 16 or 32.
 constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124;
 
 // over the 16 lanes of a row, in every lane, the same bits for every rotation of the values
@@ -870,20 +872,22 @@ __device__ inline int row_slot(int lane)
 struct TriOne {
     double a[TS][TS];
     double x[TS], v[TS], wv[TS];     // column k; the last step's vectors, which the matrix has still to be updated with
-    struct Step { double sum[ONE + 256], column[ONE]; };         // A y, and places for sums that are none; column k + 1
+    struct Step { double2 at[ONE + 256]; };                      // A y and column k + 1, and places for sums that are none
     struct Kept { double tau, diagonal, beta; };
     struct Scratch { Step step[2]; Kept kept[ONE]; };            // (by step parity)
     Step* shared;                    // [2]
     Kept* kept;
     int lane, wave, col, row;        // column and row of slot 0
     int off, first;                  // row i here is row i - off of the matrix; the first that is reduced here
+    int k_first;                     // the first step
+    bool keeps;                      // this lane keeps an entry of every vector, that of row 16 (lane mod 16) + `row`
+    Global<double> kept_row;         // where its entry of the last step's belongs
 
     template <int S>
     __device__ inline void steps(int& k, const StepStore& store)
     {
         constexpr int L = TS - S, S1 = S + 1 < TS ? S + 1 : S;
         const int k_end = min(16 * S + 16, ONE - 2);
-        const bool pair = first > 0 && !(store.N / 64 & 1);
         // where this lane's sum over a row goes (one that is none: to a place of its own)
         const int t = row_slot<L>(lane);
         const int sum_at = (lane & (L > 4 ? 1 : L > 2 ? 3 : L > 1 ? 7 : 15)) == 0 && t < L ? 16 * (S + t) + row : ONE + (int)threadIdx.x;
@@ -891,25 +895,18 @@ struct TriOne {
             const int k1 = k + 1;
             const bool next = S + 1 < TS && k1 == 16 * S1;       // row k + 1 is the first of slot S + 1
             Step* sh = shared + (k & 1);
-            double sum[L], y[TS], sq = 0.0;
-            auto update = [&](int s) {
-                const double vr = row_lane<0>(v[s]), wr = row_lane<0>(wv[s]);
+            double sum[L], y[TS], vr[TS], wr[TS], sq = 0.0;
 #pragma unroll
-                for (int b = S; b < TS; ++b) a[s][b] = fma(-wr, v[b], fma(-vr, wv[b], a[s][b]));
-            };
-            // column k + 1 of the matrix, from the threads that hold that row
-            update(S);
-            if (S1 != S) update(S1);
-            if (wave == (k1 >> 2 & 3) && lane >> 4 == (k1 & 3)) {
-                if (!next) {
+            for (int s = S; s < TS; ++s) {
+                vr[s] = row_lane<0>(v[s]);
+                wr[s] = row_lane<0>(wv[s]);
 #pragma unroll
-                    for (int b = S; b < TS; ++b) sh->column[16 * b + col] = a[S][b];
-                    asm volatile("" ::"n"(0));                   // (merged, the branches would put `a` into memory)
-                } else {
+                for (int b = S; b < TS; ++b) a[s][b] = fma(-wr[s], v[b], fma(-vr[s], wv[b], a[s][b]));
+            }
+            // column k + 1 of the matrix: of every row the lane that has that column
+            if (col == (k1 & 15)) {
 #pragma unroll
-                    for (int b = S; b < TS; ++b) sh->column[16 * b + col] = a[S1][b];
-                    asm volatile("" ::"n"(1));
-                }
+                for (int s = S; s < TS; ++s) sh->at[16 * s + row].y = next ? a[s][S1] : a[s][S];
             }
 #pragma unroll
             for (int b = S; b < TS; ++b) {
@@ -918,63 +915,55 @@ struct TriOne {
             }
             const double sig2 = ring_sum(sq);
             const int from = (k1 - 4 * wave) & 15;               // the lane of row 0 that has column k + 1
-            const double x0 = lane_value(x[S], from), x1 = lane_value(x[S1], from);
-            double beta, v0;
-            householder(next ? x1 : x0, sig2, beta, v0);
-            const double tau = householder_tau(sig2, v0);
+            const double alpha = lane_value(next ? x[S1] : x[S], from);
+            double beta, v0, tau;
+            householder(alpha, sig2, beta, v0);
+            tau = householder_tau(sig2, v0);
 #pragma unroll
             for (int r = 0; r < L; ++r) {
-                if (S + r > S1) update(S + r);
                 sum[r] = 0.0;
 #pragma unroll
                 for (int b = S; b < TS; ++b) sum[r] = fma(a[S + r][b], y[b], sum[r]);
             }
-            sh->sum[sum_at] = row_sums<L>(sum, lane);
+            sh->at[sum_at].x = row_sums<L>(sum, lane);
+            // the last step's vector, for the way back
+            const double entry = kept_entry<S>(vr);
+            if (keeps && k > k_first) *kept_row = entry;
+            kept_row += k > k_first ? store.N : 0;
 #pragma unroll
             for (int b = S; b < TS; ++b) v[b] = b <= S + 1 && 16 * b + col == k1 ? v0 : y[b];
+            here(tau);
             __syncthreads();
-            const double q1 = sh->sum[k1], c1 = sh->column[k1];
-            double p[TS], c[TS];
+            double2 pc[TS];
+            const double q1 = sh->at[k1].x, c1 = sh->at[k1].y;
+#pragma unroll
+            for (int b = S; b < TS; ++b) pc[b] = sh->at[16 * b + col];
+            __builtin_amdgcn_sched_barrier(0);
+            if (wave == (k & 3) && lane < 16 && col == (k & 15)) kept[k] = Kept{tau, x[S], beta};
+            double p[TS], gamma = 0.0;
 #pragma unroll
             for (int b = S; b < TS; ++b) {
-                p[b] = sh->sum[16 * b + col];
-                c[b] = sh->column[16 * b + col];
-            }
-            // kept for the way back, with zeros in front (in the shadow of the loads, one wave the vector, one the rest)
-            if (wave == (k & 3)) {
-                const int rg = lane >> 4;
-                const Global<double> r = store.refl + (size_t)(k - off) * store.N - off + 16 * rg + col;
-#pragma unroll
-                for (int h = 0; h < TS / 4; ++h) {
-                    double part[4];
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) part[b] = 4 * h + b < S ? 0.0 : v[max(4 * h + b, S)];
-                    const double even = rg & 1 ? part[1] : part[0], odd = rg & 1 ? part[3] : part[2];
-                    if (64 * h >= first) r[64 * h] = rg & 2 ? odd : even;
-                }
-                if (pair) r[0] = 0.0;
-            } else if (wave == (k + 2 & 3)) {
-                if (lane < 16 && col == (k & 15)) {
-                    kept[k].diagonal = x[S];
-                    kept[k].tau = tau;
-                    kept[k].beta = beta;
-                }
-            }
-            double gamma = 0.0;
-#pragma unroll
-            for (int b = S; b < TS; ++b) {
-                p[b] = fma(v0, c[b], p[b]);
+                p[b] = fma(v0, pc[b].y, pc[b].x);
                 if (b == S && 16 * b + col <= k) p[b] = 0.0;
                 gamma = fma(v[b], p[b], gamma);
             }
-            gamma = ring_sum(gamma) * tau * (0.5 * tau);
+            gamma = ring_sum(gamma) * (tau * (0.5 * tau));
             const double wk1 = fma(-gamma, v0, tau * fma(v0, c1, q1));
 #pragma unroll
             for (int b = S; b < TS; ++b) {
                 wv[b] = fma(-gamma, v[b], tau * p[b]);
-                x[b] = fma(-wv[b], v0, fma(-v[b], wk1, c[b]));
+                x[b] = fma(-wv[b], v0, fma(-v[b], wk1, pc[b].y));
             }
         }
+    }
+    // entries at the thread's rows, that of row slot s in lane s of the row of lanes; zeros in what is finished
+    template <int S>
+    __device__ inline double kept_entry(const double (&vr)[TS]) const
+    {
+        double e = 0.0;
+#pragma unroll
+        for (int s = S; s < TS; ++s) e = (lane & 15) == s ? vr[s] : e;
+        return e;
     }
     template <int S>
     __device__ inline void phases(int& k, const StepStore& store)
@@ -996,6 +985,17 @@ struct TriOne {
         off = ONE - N;
         first = N > ONE ? ONE - TAIL : off;
         int k = N > ONE ? first : off + m.pad;
+        // (slots in front of the first are never used, and not loaded: 2 of 37 us for a matrix of 64 rows)
+        const Global<const double> C = global((const double*)m.C);
+        const bool whole = first == 0;
+#pragma unroll
+        for (int b = 0; b < TS; ++b) {
+            const int c = 16 * b + col - off;
+#pragma unroll
+            for (int s = 0; s < TS; ++s) a[s][b] = whole || (s >= TS / 2 && b >= TS / 2) ? C[(size_t)(16 * s + row - off) * N + c] : 0.0;
+            x[b] = whole || b >= TS / 2 ? C[(size_t)(k - off) * N + c] : 0.0;
+            v[b] = wv[b] = 0.0;
+        }
         double scale = 1.0;                                      // (larger matrices were scaled by their group)
         if (off >= 0) {
             int expo, zeros;
@@ -1005,26 +1005,26 @@ struct TriOne {
                 m.st[DS_ZERO_ROWS] = zeros;
             }
         }
-        const Global<const double> C = global((const double*)m.C);
-        // (slots in front of the first are never used: they read something of its row)
-#pragma unroll
-        for (int s = 0; s < TS; ++s) {
-            const Global<const double> r = C + (size_t)(max(16 * s, first) + row - off) * N + col - off;
-#pragma unroll
-            for (int b = 0; b < TS; ++b) a[s][b] = r[max(16 * b, first)];
-        }
-#pragma unroll
-        for (int b = 0; b < TS; ++b) x[b] = C[(size_t)(k - off) * N + max(16 * b, first) + col - off];
 #pragma unroll
         for (int b = 0; b < TS; ++b) {
 #pragma unroll
             for (int s = 0; s < TS; ++s) a[s][b] *= scale;
             x[b] *= scale;
-            v[b] = wv[b] = 0.0;
         }
-        const int k_first = k;
+        k_first = k;
+        // (with zeros in what is finished: a vector is read in pairs of 64 entries)
+        const bool pair = first > 0 && !(N / 64 & 1);
+        const int number = 16 * (lane & 15) + row;
+        keeps = (lane & 15) < TS && (pair || number >= first);
+        kept_row = store.refl + ((size_t)(k - off) * N + number) - off;
         if (first == 0) phases<0>(k, store);
         else phases<TS / 2>(k, store);
+        {
+            double vr[TS];
+            vr[TS - 1] = row_lane<0>(v[TS - 1]);                 // (by all lanes: one that is not active has nothing to give)
+            const double entry = kept_entry<TS - 1>(vr);
+            if (keeps) *kept_row = entry;
+        }
         // what is left: the last 2 x 2 block
         if (row == 15) {
             const double vr = row_lane<0>(v[TS - 1]), wr = row_lane<0>(wv[TS - 1]);
