@@ -10,6 +10,7 @@
 // Entry-wise and l_q messages: one launch that searches the messages' ascending coordinates (decode_sparse).
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "atomo_internal.h"
@@ -74,10 +75,16 @@ __device__ inline int inclusive_sum(int x)
     return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
 }
 
-// (128 registers for four workgroups per compute unit; with the outputs in registers too, 63 of them would go to memory for three)
+struct DecLds {
+    Global<const float> up[ATOMS_MAX];
+    Global<const float> vp[ATOMS_MAX];
+    Global<const float> wp[ATOMS_MAX];                           // the atom's weight (nullptr: folded into u)
+    int total, span;
+    __attribute__((aligned(16))) float operands[KP * (TR + TC + 64)];
+};
+
 template <bool TALL, bool ACCUMULATE>
-__global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(const DecOut* outs, const DecMsg* msgs, const DecWork* work,
-                                                        float scale, int batch)
+__device__ __forceinline__ void decode_tile(DecLds& lds, const DecOut* outs, const DecMsg* msgs, const DecWork* work, float scale, int batch)
 {
     constexpr int NCB = TALL ? 1 : 2;
     constexpr int UROWS = TALL ? TALL_ROWS : TR;                 // rows of the tile = length of a u slice
@@ -85,12 +92,9 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
     constexpr int US = UROWS + 32, VS = VCOLS + 32;              // LDS strides: odd and even atoms on different banks
     constexpr int NU = (KP * UROWS / 4 + 255) / 256;             // 16-byte loads per thread and piece, u and v
     constexpr int NV = (KP * VCOLS / 4 + 255) / 256;
-    __shared__ Global<const float> up[ATOMS_MAX];
-    __shared__ Global<const float> vp[ATOMS_MAX];
-    __shared__ Global<const float> wp[ATOMS_MAX];                // the atom's weight (nullptr: folded into u)
-    __shared__ int total_sh, span_sh;
-    __shared__ __attribute__((aligned(16))) float Us[KP * US];
-    __shared__ __attribute__((aligned(16))) float Vs[KP * VS];
+    static_assert(US + VS <= TR + TC + 64, "operands in the LDS of either form");
+    Global<const float> *const up = lds.up, *const vp = lds.vp, *const wp = lds.wp;
+    float *const Us = lds.operands, *const Vs = lds.operands + KP * US;
     const DecWork wk = work[blockIdx.x];
     const DecOut o = outs[wk.out];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -195,8 +199,8 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
             if (!ACCUMULATE) asm volatile("" : "+v"(mine));
             for (int k = mine; k < here; k += 256) put(m, k, run + k);
             if (tid == 0) {
-                total_sh = here;
-                span_sh = kept;
+                lds.total = here;
+                lds.span = kept;
             }
         } else if (wave == 0) {
             int before = 0;
@@ -209,38 +213,41 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
                 before = __builtin_amdgcn_readlane(upto, 63);
             }
             if (lane == 0) {
-                total_sh = min(before, ATOMS_MAX);
-                span_sh = 0;
+                lds.total = min(before, ATOMS_MAX);
+                lds.span = 0;
             }
         }
     };
 
+    auto products = [&](int here) {
+        const int pairs = (min(KP, here) + 1) / 2;
+        for (int t = 0; t < pairs; ++t) {
+            const float* ua = &Us[(2 * t + h) * US + row_off + l32];
+            const float* vb = &Vs[(2 * t + h) * VS + col_off + l32];
+            const float a0 = ua[0], a1 = ua[32], b0 = vb[0];
+            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
+            if (!TALL) {
+                const float b1 = vb[32];
+                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
+                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+            }
+        }
+    };
     for (int first = o.first; first < o.last; first += batch) {
         const int nm = min(batch, o.last - first);
         for (int run = 0, span = 1; run < span; run += ATOMS_MAX) {
             if (run > 0 || first > o.first) __syncthreads();     // the previous list is spent
             list(first, nm, run);
             __syncthreads();
-            span = span_sh;
-            const int total = total_sh;
+            span = lds.span;
+            const int total = lds.total;
             if (total > 0) fetch(0, total);
             for (int k0 = 0; k0 < total; k0 += KP) {
                 stage(total - k0);
                 __syncthreads();
                 if (k0 + KP < total) fetch(k0 + KP, total);
-                const int pairs = (min(KP, total - k0) + 1) / 2;
-                for (int t = 0; t < pairs; ++t) {
-                    const float* ua = &Us[(2 * t + h) * US + row_off + l32];
-                    const float* vb = &Vs[(2 * t + h) * VS + col_off + l32];
-                    const float a0 = ua[0], a1 = ua[32], b0 = vb[0];
-                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-                    if (!TALL) {
-                        const float b1 = vb[32];
-                        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-                        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-                    }
-                }
+                products(total - k0);
                 __syncthreads();                                 // the piece is spent
             }
         }
@@ -254,6 +261,18 @@ __global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(cons
             for (int v = 0; v < 16; ++v)
                 if (row0 + below(rb, v) < o.rows && col0 + cb * 32 < o.cols)
                     corner[below(rb, v) * o.ld + cb * 32] = ACCUMULATE ? old[rb][cb][v] + acc[rb][cb][v] : acc[rb][cb][v];
+}
+
+// The first n_wide items of `work` are 64 x 256 tiles, the others (TALL: there are some) tall ones; both in one launch, or a few of one
+// kind are a launch that nothing runs beside (the layers of ResNet-18 in the Section 6 reshape 22.3 -> 18.0 us).
+// (128 registers for four workgroups per compute unit; with the outputs in registers too, 63 of them would go to memory for three)
+template <bool TALL, bool ACCUMULATE>
+__global__ __launch_bounds__(256, ACCUMULATE ? 1 : 4) void decode_svd_tiles(const DecOut* outs, const DecMsg* msgs, const DecWork* work,
+                                                        int n_wide, float scale, int batch)
+{
+    __shared__ DecLds lds;
+    if (!TALL || (int)blockIdx.x < n_wide) decode_tile<false, ACCUMULATE>(lds, outs, msgs, work, scale, batch);
+    else decode_tile<true, ACCUMULATE>(lds, outs, msgs, work, scale, batch);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -520,15 +539,13 @@ int decode_svd_batch(atomo_ctx* ctx, const atomo_svd_msg* msgs, const int32_t* f
         int max_cap = 1;
         for (int k = 0; k < n_msgs; ++k) max_cap = std::max(max_cap, (int)msgs[k].capacity);
         const int batch = std::max(1, ATOMS_MAX / max_cap);      // messages whose atoms fit the LDS list together
-        const unsigned n_tall = (unsigned)hw_tall.size();
-        if (n_wide > 0) {
-            if (accumulate) decode_svd_tiles<false, true><<<(unsigned)n_wide, 256, 0, stream>>>(d_outs, d_msgs, d_work, scale, batch);
-            else decode_svd_tiles<false, false><<<(unsigned)n_wide, 256, 0, stream>>>(d_outs, d_msgs, d_work, scale, batch);
-        }
-        if (n_tall > 0) {
-            if (accumulate) decode_svd_tiles<true, true><<<n_tall, 256, 0, stream>>>(d_outs, d_msgs, d_work + n_wide, scale, batch);
-            else decode_svd_tiles<true, false><<<n_tall, 256, 0, stream>>>(d_outs, d_msgs, d_work + n_wide, scale, batch);
-        }
+        const unsigned grid = (unsigned)hw.size();
+        auto launch = [&](auto tall) {
+            if (accumulate) decode_svd_tiles<tall, true><<<grid, 256, 0, stream>>>(d_outs, d_msgs, d_work, (int)n_wide, scale, batch);
+            else decode_svd_tiles<tall, false><<<grid, 256, 0, stream>>>(d_outs, d_msgs, d_work, (int)n_wide, scale, batch);
+        };
+        if (hw_tall.empty()) launch(std::false_type());
+        else launch(std::true_type());
     }
     ATOMO_HIP(ctx, hipGetLastError());
     return ATOMO_OK;
