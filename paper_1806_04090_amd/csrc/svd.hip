@@ -1456,6 +1456,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     place(plan.direct.tiles, dt.tiles);
     place(plan.direct.gram_wide, dt.gram_wide);
     place(plan.direct.tri, dt.tri);
+    place(plan.direct.tri_half, dt.tri_half);
     place(plan.direct.eig, dt.eig);
     place(plan.direct.vec, dt.vec);
     place(plan.direct.lng, dt.lng);

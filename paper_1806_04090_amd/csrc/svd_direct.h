@@ -46,7 +46,8 @@ struct DirectMat {
     double* lam;                     // [r] eigenvalues, descending, scaled
     double* u;                       // [capacity][r] kept vectors of the shorter side
     unsigned long long* xch;         // exchange slots of the reduction, see Tri
-    unsigned long long* gate;        // [1] the workgroups of the matrix's group that have started, see Gate
+    double* half;                    // [3][384] where one group leaves the reduction to another: the column, and the last step's vectors
+    unsigned long long* gate;        // [2] the workgroups that have started, of the matrix's group and of one of eight, see Gate
     unsigned* tickets;               // [nt (nt + 1) / 2] chunks of a tile that are done, see direct_gram_wide
     int* st;                         // [DS_WORDS]
     int* count;
@@ -65,13 +66,14 @@ struct DirectMat {
 
 struct DirectPlan {
     std::vector<DirectMat> mats;
-    std::vector<svd::Work> gram, tiles, gram_wide, tri, eig, vec, lng;
+    std::vector<svd::Work> gram, tiles, gram_wide, tri, tri_half, eig, vec, lng;
     bool spread = false;             // deal the workgroups of a group over all dies (for tests)
     long long start_ticks = START_TICKS;
     int eig_lanes = 32;              // lanes per eigenvalue in the search, at most 32
+    bool few = false, half = false;  // reduction: direct_tridiagonal_few takes `tri`; behind direct_tridiagonal_half with `tri_half`
     size_t n_eig = 0;                // how many items of `eig` are searches; the others are blocks of reflectors
     int max_nt = 1;
-    size_t n_work() const { return gram.size() + tiles.size() + gram_wide.size() + tri.size() + eig.size() + vec.size() + lng.size(); }
+    size_t n_work() const { return gram.size() + tiles.size() + gram_wide.size() + tri.size() + tri_half.size() + eig.size() + vec.size() + lng.size(); }
 };
 
 // Lets the kernels have more LDS than a launch gets by default; once per device.
@@ -85,7 +87,7 @@ void plan_work(DirectPlan& plan);
 struct DirectTables {
     const DirectMat* mats;
     int n_mats;
-    const svd::Work *gram, *tiles, *gram_wide, *tri, *eig, *vec, *lng;
+    const svd::Work *gram, *tiles, *gram_wide, *tri, *tri_half, *eig, *vec, *lng;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.  gram_done (may be null) is recorded
 // behind the Gram products; if that fails nothing else is enqueued.

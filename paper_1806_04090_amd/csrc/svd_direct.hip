@@ -32,6 +32,12 @@ enum { CLS_64 = 0, CLS_128, CLS_256, CLS_512, CLS_640, CLS_COUNT };
 constexpr int CLS_CHUNKS[CLS_COUNT] = {1, 2, 4, 8, 10};
 constexpr int XCH = 6;            // vectors in the exchange slots of a group, see Tri
 constexpr int CLS_WGS[CLS_COUNT] = {1, 1, 16, 16, 32};
+constexpr int HALFWAY = 384, FEW_WGS = 8;    // rows that groups of so many workgroups take up, in calls of many, see direct_tridiagonal_few
+// of a vector in the exchange slots of a matrix: of its group, and of one of eight workgroups
+__host__ __device__ inline int slot_entries(int cls)
+{
+    return 64 * CLS_CHUNKS[cls] + (cls <= CLS_128 ? 0 : cls == CLS_256 ? 256 : HALFWAY);
+}
 
 __device__ inline double fold8(double a, double b, int lane)
 {
@@ -140,8 +146,8 @@ __device__ inline void clear_for_steps(const DirectMat& m, int tid, int n_thread
 {
     const int N = m.nt * TILE;
     if (tid < DS_WORDS) m.st[tid] = 0;
-    if (tid == 0) *m.gate = 0;
-    for (int i = tid; i < XCH * 64 * CLS_CHUNKS[m.cls]; i += n_threads) m.xch[i] = 0;
+    if (tid < 2) m.gate[tid] = 0;                                // (and the slots of both groups)
+    for (int i = tid; i < XCH * slot_entries(m.cls); i += n_threads) m.xch[i] = 0;
     if (tid < m.pad) m.td[tid] = make_double2(0.0, 2.0);
     if (tid == m.pad) m.td[tid].x = 0.0;
     // rows of the reflectors' blocks that are no step
@@ -450,7 +456,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
     return ldexp(1.0, -e);
 }
 
-// Groups of 16 or 32 workgroups (matrices of more than 128 rows, until 64 are left): every wave owns R rows of the matrix in
+// Groups of 8, 16 or 32 workgroups (matrices of more than 128 rows, until 64 are left): every wave owns R rows of the matrix in
 // registers (lane l: columns l, l + 64, ..), row r belonging to wave r mod W, and works the whole vectors x, v, w out for itself, all
 // waves the same bits; one exchange per step: every wave publishes the entries of A y of its rows (y: the column below its first entry;
 // A v = A y + v0 A e_{k+1}, so the reflector need not be known), the owner of row k + 1 that row, and every workgroup reads all of
@@ -478,7 +484,7 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // v_readlane for what a vector holds at the wave's rows, a reduction of its own for the norm, and the reflector behind the update; 800
 // of 3500 cycles).  Rows and columns split between the waves of a workgroup, two instead of eight entries of a vector per lane: 566, for
 // a second barrier and sums of sixteen rows.  Four groups per die, two waves on every SIMD: the issue of the vectors that every wave
-// works out for itself.
+// works out for itself (direct_tridiagonal_few).
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
 // waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
@@ -530,10 +536,16 @@ constexpr int ONE = 128, TS = ONE / 16;                          // rows of TriO
 // the last of it to start, or not.
 enum TriEnd { TRI_DONE, TRI_FAILED, TRI_LAST, TRI_LEFT };
 
-template <int C, int R, int QW>
+// A group of W waves for the last 64 C rows, until LEFT are left.  One of eight workgroups (FEW) may go on from what another has left:
+// the matrix without the last step's update, and the vectors that it needs for that, so that the sums stay the same.  Every matrix has
+// the same bits whatever the number of workgroups: a sum over a row is one wave's, in the order of the columns.
+template <int C, int R, int W, int LEFT = TAIL>
 struct Tri {
-    static constexpr int CN = 64 * C, W = 64 * QW, OWN = (C + 3) / 4;
-    static constexpr int LAST = C - TAIL / 64 - 1;               // the last chunk of columns that is reduced here
+    static constexpr int CN = 64 * C, OWN = (C + 3) / 4;
+    static constexpr int LAST = C - LEFT / 64 - 1;               // the last chunk of columns that is reduced here
+    static constexpr int TURN = W < 64 ? W : 64;                 // rows that the waves hand over in turn
+    static constexpr bool FEW = W == 4 * FEW_WGS;
+    static_assert(W * R == CN, "every row has a wave");
     double a[R][C];
     // Column k; the last step's vectors, which the rows have still to be updated with.  [C]: their entries at the wave's rows, row
     // slot t in lane t of every row of 16 lanes, from where they are broadcast.
@@ -541,7 +553,7 @@ struct Tri {
     double tau, diagonal, beta;      // the last step's
     Global<u64> slots;
     double2 (*shared)[CN];           // [2][CN] by step parity: p and column k + 1
-    int lane, wave, member, w, q, off, k_first, spin_limit;
+    int lane, wave, member, w, off, k_first, spin_limit;
     int row_turn, keep_turn;         // the next steps at which this wave hands over a row, its workgroup keeps a vector
     int row_number;                  // the row of this lane in the vectors' last part
     bool local;                      // the group sits on one die
@@ -560,6 +572,22 @@ struct Tri {
     {
 #pragma unroll
         for (int c = P; c < C; ++c) put(slot + lane + 64 * c, entry(a[T][c], tag));
+    }
+    // row `row` = k + 2 of this wave, k a step of phase P
+    template <int P, int T = 64 * P / W>
+    __device__ __forceinline__ void put_turn(int row, Global<u64> slot, u64 tag) const
+    {
+        if constexpr (W >= 64) {
+            constexpr int Q = W / 64;
+            if (row < 64 * (P + 1)) {
+                if (w >> 6 == P % Q) put_row<P, P / Q>(slot, tag);
+            } else if (w >> 6 == (P + 1) % Q) {
+                put_row<P, (P + 1) / Q>(slot, tag);
+            }
+        } else if constexpr (T <= 64 * (P + 1) / W && T < R) {   // (up to the first row of chunk P + 1)
+            if (w + W * T == row) put_row<P, T>(slot, tag);
+            else put_turn<P, T + 1>(row, slot, tag);
+        }
     }
     template <int T>
     __device__ inline void put_first(int row) const
@@ -593,7 +621,7 @@ struct Tri {
             }
     }
     template <int P, int T0>
-    __device__ inline void update()
+    __device__ __forceinline__ void update()
     {
         double wr[R], vr[R];
         entries<T0>(wv[C], wr);
@@ -603,21 +631,24 @@ struct Tri {
 
     // step k - 1, every wave of the workgroup a part; with zeros in what is finished of its vector (that is read in pairs of chunks)
     template <int P>
-    __device__ inline void keep(int k, const StepStore& store) const
+    __device__ __forceinline__ void keep(int k, const StepStore& store) const
     {
         const int kk = k - 1 - off;
         const Global<double> row = store.refl + (size_t)kk * store.N + lane - off;
 #pragma unroll
         for (int c = P > 1 ? P - 2 : 0; c < C; ++c)
             if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[64 * c] = c < P ? 0.0 : v[c < P ? P : c];
+        if constexpr (FEW && P <= 1) {                           // (the chunk in front, another group's)
+            if (off < 0 && wave == 3) row[-64] = 0.0;
+        }
         if (wave == 3 && lane == 0) store.put(kk, tau, diagonal, beta);
     }
 
     // steps k of [64 P, 64 (P + 1)): chunks of columns before P are finished
     template <int P>
-    __device__ inline void phase(int& k, const StepStore& store)
+    __device__ __forceinline__ void phase(int& k, const StepStore& store)
     {
-        constexpr int T0 = P / QW;                               // row slots before T0 are finished
+        constexpr int T0 = 64 * P / W;                           // row slots before T0 are finished
         constexpr int PN = P + 1;
         constexpr int K = R - T0 + 1;                            // sums of a step: the entries of A y, and y y
         constexpr int J0 = P / 4, L = OWN - J0;
@@ -680,12 +711,8 @@ struct Tri {
             here(v0);
             here(tau);
             if (__builtin_expect(k == row_turn, 0)) {
-                if (k + 2 < 64 * PN) {
-                    if (q == P % QW) put_row<P, P / QW>(slot_c(step + 1), tag_c(step + 1));
-                } else if (q == PN % QW) {
-                    put_row<P, PN / QW>(slot_c(step + 1), tag_c(step + 1));
-                }
-                row_turn += 64;
+                put_turn<P>(k + 2, slot_c(step + 1), tag_c(step + 1));
+                row_turn += TURN;
             }
             __builtin_amdgcn_sched_barrier(0);
             look_p();
@@ -749,7 +776,7 @@ struct Tri {
     }
 
     template <int P>
-    __device__ inline void phases(int& k, const StepStore& store)
+    __device__ __forceinline__ void phases(int& k, const StepStore& store)
     {
         phase<P>(k, store);
         if constexpr (P < LAST) phases<P + 1>(k, store);
@@ -757,7 +784,7 @@ struct Tri {
 
     static constexpr int SPIN_STEP = 1 << 20;                    // a quarter of a second and more: never seen
 
-    __device__ inline TriEnd run(const DirectMat& mm, int number, int n_wgs, long long start_ticks, double2* lds)
+    __device__ __forceinline__ TriEnd run(const DirectMat& mm, int number, int n_wgs, long long start_ticks, double2* lds)
     {
         member = number;
         const StepStore store(mm);
@@ -767,13 +794,13 @@ struct Tri {
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         w = member * 4 + wave;
-        q = w >> 6;
         row_number = w + W * min(lane & 15, R - 1);
         off = CN - N;
-        slots = global(mm.xch);
-        const bool last = Gate::start(global(mm.gate), n_wgs, start_ticks);
-        int expo, zeros;
-        const double scale = scale_of<C>(mm, off, lane, expo, zeros);
+        slots = global(mm.xch) + (FEW ? XCH * 64 * CLS_CHUNKS[mm.cls] : 0);
+        const bool last = Gate::start(global(mm.gate) + FEW, n_wgs, start_ticks);
+        int expo = 0, zeros = 0;
+        double scale = 1.0;                                      // (what another group has left is scaled)
+        if (!FEW || off >= 0) scale = scale_of<C>(mm, off, lane, expo, zeros);
 #pragma unroll
         for (int t = 0; t < R; ++t) {
             const int i = w + W * t - off;
@@ -783,33 +810,47 @@ struct Tri {
                 a[t][c] = i >= 0 && j >= 0 ? scale * global(mm.C)[(size_t)i * N + j] : 0.0;
             }
         }
-        int k = off + mm.pad;
+        int k = !FEW || off >= 0 ? off + mm.pad : 0;
         k_first = k;
         // (a wave has its rows of a chunk once, its workgroup every (W / 4)th vector from the first step's on)
-        row_turn = k + (w - (k + 2) & 63);
+        row_turn = k + (w - (k + 2) & (TURN - 1));
         keep_turn = k + 1 + (member - k & (W / 4 - 1));
+        const bool goes_on = FEW && off < 0;
+        const Global<const double> column = goes_on ? global((const double*)mm.half) : global((const double*)mm.C) + (size_t)mm.pad * N - off;
+        const Global<const double> last_v = goes_on ? column + CN : global((const double*)mm.C) + CN;
 #pragma unroll
         for (int c = 0; c <= C; ++c) {
-            const int j = (c < C ? lane + 64 * c : row_number) - off;
-            x[c] = j >= 0 ? scale * global(mm.C)[(size_t)mm.pad * N + j] : 0.0;
-            v[c] = wv[c] = 0.0;
+            const int i = c < C ? lane + 64 * c : row_number;
+            x[c] = i >= off ? scale * column[i] : 0.0;
+            v[c] = goes_on ? last_v[i] : 0.0;
+            wv[c] = goes_on ? last_v[CN + i] : 0.0;
         }
-        if (!Gate::pass(global(mm.gate), n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
+        if (!Gate::pass(global(mm.gate) + FEW, n_wgs, start_ticks, local)) return __syncthreads_or(last) ? TRI_LAST : TRI_LEFT;
         put_first<0>(k + 1);
         phases<0>(k, store);
         // what is left goes back to memory
-        constexpr int T0 = (LAST + 1) / QW;
+        constexpr int T0 = 64 * (LAST + 1) / W;
         if (k == keep_turn) keep<LAST + 1>(k, store);
-        update<LAST + 1, T0>();
+        if constexpr (LEFT == TAIL) {
+            update<LAST + 1, T0>();
+        } else if (w == 0) {
+#pragma unroll
+            for (int c = LAST + 1; c < C; ++c) {
+                const Global<double> at = global(mm.half) + lane + 64 * (c - LAST - 1);
+                at[0] = x[c];
+                at[LEFT] = v[c];
+                at[2 * LEFT] = wv[c];
+            }
+        }
 #pragma unroll
         for (int t = T0; t < R; ++t) {
             const Global<double> row = global(mm.C) + (size_t)(w + W * t - off) * N + lane - off;
-            if (W * t + w >= CN - TAIL) {
+            if (W * t + w >= CN - LEFT) {
 #pragma unroll
                 for (int c = LAST + 1; c < C; ++c) row[64 * c] = a[t][c];
             }
         }
-        if (w == 0 && lane == 0) {
+        if ((!FEW || off >= 0) && w == 0 && lane == 0) {
             mm.st[DS_EXP] = expo;
             mm.st[DS_ZERO_ROWS] = zeros;
         }
@@ -884,7 +925,7 @@ struct TriOne {
     Global<double> kept_row;         // where its entry of the last step's belongs
 
     template <int S>
-    __device__ inline void steps(int& k, const StepStore& store)
+    __device__ __forceinline__ void steps(int& k, const StepStore& store)
     {
         constexpr int L = TS - S, S1 = S + 1 < TS ? S + 1 : S;
         const int k_end = min(16 * S + 16, ONE - 2);
@@ -966,13 +1007,13 @@ struct TriOne {
         return e;
     }
     template <int S>
-    __device__ inline void phases(int& k, const StepStore& store)
+    __device__ __forceinline__ void phases(int& k, const StepStore& store)
     {
         steps<S>(k, store);
         if constexpr (S + 1 < TS) phases<S + 1>(k, store);
     }
 
-    __device__ inline void run(const DirectMat& m, Scratch& lds)
+    __device__ __forceinline__ void run(const DirectMat& m, Scratch& lds)
     {
         const StepStore store(m);
         const int N = store.N;
@@ -1048,25 +1089,35 @@ struct TriOne {
 };
 
 // The reduction by one workgroup that waits for nobody: the same steps on the matrix in memory, which nothing needs
-// afterwards.  Two passes over what is left of it per step: 4 ms for 200
-// rows, 42 for 512, 83 for 640.
-__device__ inline void tri_alone(const DirectMat& m, double* lds)
+// afterwards, from `have` rows on (all of them, if there are no more) until `left` are left.  Two passes over what is left of it per
+// step: 4 ms for 200 rows, 42 for 512, 83 for 640.
+__device__ __forceinline__ void tri_alone(const DirectMat& m, int have, int left, double* lds)
 {
     constexpr int C = MAX_R / 64;
     double *const v = lds, *const p = lds + MAX_R;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), N = m.nt * TILE;
     const StepStore store(m);
     const Global<double> A = global(m.C);
-    int expo, zeros;
-    const double scale = scale_of<C>(m, MAX_R - N, lane, expo, zeros);
+    const bool whole = have >= N;
+    int expo = 0, zeros = 0;
+    const double scale = whole ? scale_of<C>(m, MAX_R - N, lane, expo, zeros) : 1.0;
     auto load = [&](int i, double (&row)[C]) {                   // row i, lane l: columns l, l + 64, ..; zeros past the end
 #pragma unroll
         for (int c = 0; c < C; ++c) row[c] = 64 * c < N ? A[(size_t)i * N + lane + 64 * c] : 0.0;
     };
     __syncthreads();
-    for (int e = tid; e < N * N; e += 256) A[e] *= scale;
+    if (whole) {
+        for (int e = tid; e < N * N; e += 256) A[e] *= scale;
+    } else {                                                     // the update that the last step's vectors still owe
+        const Global<const double> last = global((const double*)m.half) + HALFWAY;
+        for (int e = tid; e < HALFWAY * HALFWAY; e += 256) {
+            const int i = e / HALFWAY, j = e % HALFWAY;
+            const Global<double> at = A + (size_t)(N - HALFWAY + i) * N + N - HALFWAY + j;
+            *at = fma(-last[HALFWAY + i], last[j], fma(-last[i], last[HALFWAY + j], *at));
+        }
+    }
     __syncthreads();
-    for (int k = m.pad; k < N - TAIL; ++k) {
+    for (int k = whole ? m.pad : N - have; k < N - left; ++k) {
         double x[C], sq = 0.0;
         load(k, x);
 #pragma unroll
@@ -1117,10 +1168,21 @@ __device__ inline void tri_alone(const DirectMat& m, double* lds)
         }
         __syncthreads();
     }
-    if (tid == 0) {
+    if (left == HALFWAY)
+        for (int i = tid; i < HALFWAY; i += 256) {
+            m.half[i] = A[(size_t)(N - HALFWAY) * N + N - HALFWAY + i];
+            m.half[HALFWAY + i] = m.half[2 * HALFWAY + i] = 0.0;
+        }
+    if (whole && tid == 0) {
         m.st[DS_EXP] = expo;
         m.st[DS_ZERO_ROWS] = zeros;
     }
+}
+
+__device__ __forceinline__ void tri_end(const DirectMat& m, TriEnd end, int have, int left, double2* lds)
+{
+    if (end == TRI_LAST) tri_alone(m, have, left, (double*)lds);
+    if (end == TRI_FAILED && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
 }
 
 // work: matrix (below 0: nothing), member of the group, workgroups of the group.
@@ -1135,15 +1197,51 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
     switch (m.cls) {
         case CLS_64:
         case CLS_128: { TriOne t; t.run(m, *(TriOne::Scratch*)lds); } break;
-        case CLS_256: { Tri<4, 4, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        case CLS_256: { Tri<4, 4, 64> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
         case CLS_512:
-            if (wk.b == 32) { Tri<8, 4, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
-            else { Tri<8, 8, 1> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+            if (wk.b == 32) { Tri<8, 4, 128> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+            else { Tri<8, 8, 64> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
             break;
-        default: { Tri<10, 5, 2> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
+        default: { Tri<10, 5, 128> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); } break;
     }
-    if (end == TRI_LAST) tri_alone(m, (double*)lds);
-    if (end == TRI_FAILED && (threadIdx.x & 63) == 0) m.st[DS_FAIL] = 1;
+    tri_end(m, end, MAX_R, TAIL, lds);
+}
+
+// For calls whose groups share compute units, where the issue of all the waves counts and not one step's chain: groups of eight
+// workgroups, twelve rows to a wave, for up to HALFWAY rows or for what direct_tridiagonal_half left of more.  Every wave works the
+// vectors out for itself, so half of the waves save half of that; and 64 groups have their places at once (75 MB of the 128 MB
+// of registers are matrix), where 32 of 512 rows have.  64 x (512 x 4608): 1510 -> 625 us for the first 128 steps, in two turns as
+// before, + 650 for the others.  Handing over at 320 rows 30 us more, at 256 (1062 + 298) 70.
+__global__ __launch_bounds__(256, 2) void direct_tridiagonal_few(const DirectMat* mats, const Work* work, long long start_ticks)
+{
+    __shared__ double2 lds[2 * MAX_R];
+    const Work wk = work[blockIdx.x];
+    if (wk.mat < 0) return;
+    const DirectMat& m = mats[wk.mat];
+    constexpr int W = 4 * FEW_WGS;
+    TriEnd end = TRI_DONE;
+    if (m.cls <= CLS_128) { TriOne t; t.run(m, *(TriOne::Scratch*)lds); }
+    else if (wk.b > FEW_WGS) {
+        if (m.cls == CLS_512) { Tri<8, 4, 128> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+        else { Tri<10, 5, 128> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+    }
+    else if (m.cls == CLS_256) { Tri<4, 256 / W, W> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+    else { Tri<HALFWAY / 64, HALFWAY / W, W> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+    tri_end(m, end, wk.b > FEW_WGS ? MAX_R : HALFWAY, TAIL, lds);
+}
+
+// The larger ones of such a call, down to HALFWAY rows.
+__global__ __launch_bounds__(256, 2) void direct_tridiagonal_half(const DirectMat* mats, const Work* work, long long start_ticks)
+{
+    __shared__ double2 lds[2 * MAX_R];
+    const Work wk = work[blockIdx.x];
+    if (wk.mat < 0) return;
+    const DirectMat& m = mats[wk.mat];
+    TriEnd end = TRI_DONE;
+    if (m.cls <= CLS_128) { TriOne t; t.run(m, *(TriOne::Scratch*)lds); }
+    else if (m.cls == CLS_512) { Tri<8, 8, 64, HALFWAY> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+    else { Tri<10, 5, 128, HALFWAY> t; end = t.run(m, wk.a, wk.b, start_ticks, lds); }
+    tri_end(m, end, MAX_R, HALFWAY, lds);
 }
 
 // What the groups left; one workgroup per matrix.
@@ -1983,8 +2081,9 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.fact = carve.take<double>(N * RB);
     m.lam = carve.take<double>(m.r);
     m.u = carve.take<double>((size_t)m.capacity * m.r);
-    m.xch = carve.take<u64>((size_t)XCH * 64 * CLS_CHUNKS[m.cls]);
-    m.gate = carve.take<u64>(1);
+    m.xch = carve.take<u64>((size_t)XCH * slot_entries(m.cls));
+    m.gate = carve.take<u64>(2);
+    m.half = carve.take<double>(m.nt * TILE > HALFWAY ? 3 * HALFWAY : 0);
     m.tickets = carve.take<unsigned>(ntiles);
     m.st = carve.take<int>(DS_WORDS);
     m.weight = carve.take<float>(m.capacity);
@@ -2049,32 +2148,57 @@ void plan_work(DirectPlan& plan)
             for (const auto& f : fours) plan.gram_wide.insert(plan.gram_wide.end(), f.begin(), f.end());
         }
     }
-    // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return plan.mats[a].r > plan.mats[b].r; });
     // Twice the workgroups for matrices of 257 to 512 rows, if every workgroup of the call has a compute unit to itself then: four of
     // 512 rows and five of 256 480 -> 455 us for the first 384 steps; 64 of 512 rows, where it has not, 1395 -> 2297.  What else runs on
     // the device is not known here: the encode of ResNet-18 takes 881 us alone (16 workgroups: 901), 3310 beside the same
     // encode of another context (2985) and 3.9 ms, one call in ten 4.5 - 5.6, beside 8192^3 products in bf16 (3.0 - 3.8, 3.9).  In 60
     // calls each beside these, fp32 products, long products and copies no group gave up its wait for its workgroups.
-    int total = 0;
-    for (const DirectMat& m : plan.mats) total += m.cls == CLS_512 ? 32 : CLS_WGS[m.cls];
-    const bool wide = total <= 256;
-    std::vector<Work> die[8];
-    long long load[8] = {0};
-    for (int j : order) {
-        const DirectMat& m = plan.mats[j];
-        const int wgs = m.cls == CLS_512 && wide ? 32 : CLS_WGS[m.cls];
-        int best = 0;
-        for (int x = 1; x < 8; ++x)
-            if (load[x] < load[best]) best = x;
-        for (int g = 0; g < wgs; ++g) die[plan.spread ? (best + g) % 8 : best].push_back(Work{j, g, wgs, 0});
-        load[best] += (long long)m.r * wgs;
+    auto large = [](const DirectMat& m) { return m.nt * TILE > HALFWAY; };
+    struct { int all = 0, large = 0; } most, usual, few;         // workgroups, by matrix: 32 or 16 for 257 to 512 rows; 32, or 8 up to HALFWAY
+    for (const DirectMat& m : plan.mats) {
+        const int n = CLS_WGS[m.cls], n_most = m.cls == CLS_512 ? 32 : n, n_few = large(m) ? n_most : std::min(n, FEW_WGS);
+        most.all += n_most, usual.all += n, few.all += n_few;
+        if (large(m)) usual.large += n, few.large += n_few;
     }
-    size_t most = 0;
-    for (const auto& l : die) most = std::max(most, l.size());
-    plan.tri.assign(8 * most, Work{-1, 0, 0, 0});
-    for (int x = 0; x < 8; ++x)
-        for (size_t k = 0; k < die[x].size(); ++k) plan.tri[8 * k + x] = die[x][k];
+    const bool wide = most.all <= 256;
+    // Where that is not so, groups of eight for up to HALFWAY rows if the larger ones have a compute unit per workgroup then, all 32 of
+    // them, or if there is no larger one and more than 256 workgroups otherwise: us per encode before / with them, n = 1024: 20 of 256
+    // rows 455 / 411, 64 of 256 804 / 640, 17 of 320 587 / 530; six of 512 and six of 256 786 / 735, eight of 512 with ten of 256 and ten of
+    // 128 817 / 761, six of 512 and 30 of 256 839 / 794.  Not beside more of the larger ones (eight of 512, 30 of 256, four of 600 and 16
+    // of 64 1058 / 1103), nor where every workgroup has its compute unit without (nine of 320 447 / 494).
+    // In two launches where the larger ones are more than have their places at once: 17 of 640 1950 / 1765, 28 of 512 and four of 640 1749 /
+    // 1546, 33 of 512 1721 / 1706, 48 of 512 1885 / 1875, 96 of 512 3453 / 3180; but ten of 512 811 / 951, 17 of 512 1143 / 1150, nine of 640
+    // 1312 / 1359.
+    const bool beside = !wide && few.large > 0 && few.large <= 256 && few.all <= 512;
+    plan.half = usual.large > 512;
+    plan.few = beside || plan.half || (!wide && few.large == 0 && usual.all > 256);
+    // Workgroup b runs on die b mod 8: every group goes to the die that has the least to do so far, longest chains first.
+    auto deal = [&](std::vector<Work>& list, auto&& workgroups) {
+        std::vector<Work> die[8];
+        long long load[8] = {0};
+        for (int j : order) {
+            const int wgs = workgroups(plan.mats[j]);
+            int best = 0;
+            for (int x = 1; x < 8; ++x)
+                if (load[x] < load[best]) best = x;
+            for (int g = 0; g < wgs; ++g) die[plan.spread ? (best + g) % 8 : best].push_back(Work{j, g, wgs, 0});
+            load[best] += (long long)plan.mats[j].r * wgs;
+        }
+        size_t most = 0;
+        for (const auto& l : die) most = std::max(most, l.size());
+        list.assign(8 * most, Work{-1, 0, 0, 0});
+        for (int x = 0; x < 8; ++x)
+            for (size_t k = 0; k < die[x].size(); ++k) list[8 * k + x] = die[x][k];
+    };
+    if (plan.half) {
+        deal(plan.tri_half, [&](const DirectMat& m) { return large(m) || m.cls <= CLS_128 ? CLS_WGS[m.cls] : 0; });
+        deal(plan.tri, [&](const DirectMat& m) { return m.cls <= CLS_128 ? 0 : FEW_WGS; });
+    } else if (plan.few) {
+        deal(plan.tri, [&](const DirectMat& m) { return large(m) ? 32 : std::min(CLS_WGS[m.cls], FEW_WGS); });
+    } else {
+        deal(plan.tri, [&](const DirectMat& m) { return m.cls == CLS_512 && wide ? 32 : CLS_WGS[m.cls]; });
+    }
 }
 
 hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
@@ -2093,7 +2217,9 @@ hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint6
         const hipError_t rc = hipEventRecord(gram_done, stream);
         if (rc != hipSuccess) return rc;                         // (who waits for it would not wait for this call)
     }
-    direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    if (plan.half) direct_tridiagonal_half<<<grid(plan.tri_half), 256, 0, stream>>>(t.mats, t.tri_half, plan.start_ticks);
+    if (plan.few) direct_tridiagonal_few<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
+    else direct_tridiagonal<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
     if (plan.max_nt * TILE > ONE) direct_tail<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats);
     direct_eigenvalues<<<grid(plan.eig), 256, 0, stream>>>(t.mats, t.eig, (int)plan.n_eig, plan.eig_lanes);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);

@@ -407,3 +407,41 @@ def test_sizes_around_the_partial_sums_of_a_gram_product(r, M, tall):
     msgs, per, status, _ = encode([G], 3.0, 5, stream_base=r, capacity=r)
     assert status == 0
     full_parity(G, 3.0, 5, r, msgs[0], *per[0])
+
+
+OF_EIGHT = {
+    "up to 384 rows": [(129, 140), (130, 300), (256, 300), (257, 258), (320, 400), (383, 390), (384, 500)] * 3,
+    "beside larger ones": [(385, 400), (512, 520), (640, 650)] + [(129, 131), (200, 260), (320, 330), (384, 390)] * 4 + [(64, 80), (128, 140)] * 3,
+    "behind larger groups": [(385, 390), (449, 460), (512, 520), (513, 520), (640, 650)] * 5 + [(250, 260), (384, 390), (100, 130), (40, 60)],
+}
+
+
+@pytest.mark.parametrize("kind", OF_EIGHT)
+def test_groups_of_eight_workgroups_give_the_bits_of_larger_ones(groups, kind):
+    shapes = OF_EIGHT[kind]
+    n = len(shapes)
+    first = {s: j for j, s in reversed(list(enumerate(shapes)))}
+    host = [inputs.low_rank_plus_noise(np.random.default_rng(j % 2), *s, [1.0, 0.5, 0.2], 0.02) for j, s in enumerate(shapes)]
+    host[1][5:9] = 0                                             # (a few rows of zeros)
+    mats = [dev(g) for g in host]
+
+    def check(msgs, wanted):
+        assert ctx().status()[0] == 0 and route(n) == [DIRECT] * n
+        for j, want in wanted.items():
+            got = msgs[j].to_host()
+            assert got["count"] == want["count"] and all(np.array_equal(got[k], want[k]) for k in ("idx", "w", "U", "V")), shapes[j]
+
+    own = {}
+    for j in sorted(set(first.values()) | {1, n - 1}):
+        own[j] = binding.atomo_encode_svd(ctx(), [mats[j]], 3.0, 6, j)[0].to_host()
+    # (nothing that an earlier call left in the workspace counts)
+    binding.atomo_encode_svd(ctx(), [torch.full((640, 700), float("nan"), device="cuda")] * n, 3.0, 6, 0)
+    assert ctx().status()[0] != 0
+    check(binding.atomo_encode_svd(ctx(), mats, 3.0, 6, 0), own)
+    groups(spread=True)                                          # exchange through memory
+    check(binding.atomo_encode_svd(ctx(), mats, 3.0, 6, 0), own)
+    groups(start_ticks=0)                                        # every workgroup gives up: one reduces the matrix
+    msgs, per, status, _ = encode(host, 3.0, 6)
+    check(msgs, {})
+    for j in first.values():
+        full_parity(host[j], 3.0, 6, j, msgs[j], *per[j])
