@@ -56,6 +56,7 @@ struct EwState {
     double tail;                  // final: sum of the uncapped magnitudes
     double budget;                // final: s - n_s
     double ratio;                 // final: budget / tail, +inf if tail == 0
+    unsigned int n_open;          // records that ew_settle left to ew_write, see Segments::open
 };
 
 
@@ -348,7 +349,7 @@ __device__ inline void publish(EwState* st, int level, const SolveOut& r, double
 // itself: about two microseconds of loads from L2 and scans, where a last workgroup behind a ticket costs the writing kernel
 // five to seven (2728 workgroups).  All 256 threads call; out in LDS.
 
-// At the head of the pass that histograms level 2: true if there is something to do for it, with the path in *out.
+// At the head of a pass that histograms level 2: true if there is something to do for it, with the path in *out.
 __device__ inline bool enter_level2(EwState* st, double s, SolveOut* out, unsigned long long* scratch)
 {
     const SolveOut in = st->lvl[0];
@@ -465,6 +466,12 @@ constexpr unsigned int DROPPED = 0x2000u;    // entry-wise: settled, not kept
 constexpr int MAX_GROUP = 64;
 constexpr unsigned int DIRECT_MAX = 65536;
 
+// A record whose draw lies between the bounds that level 1 gives for its p.
+struct EwOpen {
+    unsigned int i;
+    float x;
+};
+
 struct Segments {
     unsigned int* count;          // [n_seg] records of a segment; in a group with an OVER among them: kept coordinates | OVER
     unsigned int* group_kept;     // [n_groups] kept coordinates of a group of per_group segments
@@ -472,6 +479,8 @@ struct Segments {
     long long n_seg, n_groups;
     int slot_bytes;               // per segment
     int per_group;
+    EwOpen* open;                 // [open_max] the first open records, in any order
+    unsigned int open_max;
 };
 
 // Entry-wise records: values first, then the words.
@@ -543,6 +552,12 @@ __device__ inline unsigned int listed_total(const unsigned long long (&ballots)[
 __device__ inline float upper_ratio(double ratio)
 {
     return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
+}
+// r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  (the product may be beyond 2^24): a ratio beyond the float range is bounded by the
+// largest float
+__device__ inline float lower_ratio(double ratio)
+{
+    return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 - 4.76837158203125e-07)) : 3.0e38f;
 }
 __device__ inline unsigned int candidate_bits(const bool (&in)[4])
 {
@@ -623,14 +638,14 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
 // After level 0 the water level tau = tail / (s - n_s) is known to lie inside one bucket [lo, hi] of the float bit pattern
 // (12.5 % wide), so p_i = min(1, |g_i| / tau) is bracketed for every element, and because rounding is monotone,
 // fl(|g_i| / hi) <= p_i <= fl(|g_i| / lo)  holds for the float32 p_i that the final ratio will give.  An element is dropped
-// here if u >= p_hi, marked as kept for sure if u < p_lo; what lies between (about 0.12 s elements) is settled by ew_settle
+// here if u >= p_hi, marked as kept for sure if u < p_lo; what lies between (about 0.12 s elements) is settled by ew_settle and ew_write
 // once the remaining levels have fixed tau exactly.  Every element of the chosen bucket has p_hi >= 1 and so a record: level
 // 1 is histogrammed here and level 2 from the records.
 // Bound by the Philox rounds (17 or 18 wide multiplications per four elements): everything per element that can be left to
 // the candidates, one element in fifty, is left to them, and a lane takes one candidate per turn, because four predicated
 // blocks, one per component, were a third of the pass.  2^28 elements, 1 % kept: 230 us, where drawing, keep bits, and
 // gathering the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us
-// (now 17 for level 2, 24 to settle, 20 to write).
+// (now 24 to settle, 20 to write).
 template <int STEPS>
 __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long long n, EwState* st, double s,
                                                unsigned long long stream_id, unsigned long long seed, Segments sg)
@@ -644,6 +659,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     load_steps(g, seg * STEPS * 64, n, whole, vec, xv);
     const SolveOut so = st->lvl[0];
     clear_level(st, 2);
+    if (blockIdx.x == 0 && tid == 0) st->n_open = 0u;
     const bool done = so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
@@ -658,9 +674,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
         ratio_lo = so.hi < inf ? 1.0 / so.hi : 0.0;              // 1 / hi <= ratio <= 1 / lo
         ratio_hi = so.lo > 0.0 ? 1.0 / so.lo : inf;
     }
-    const double down = 1.0 - 4.76837158203125e-07;              // 1 - 2^-21
-    // a ratio beyond the float range is bounded from below by the largest float and from above by infinity
-    const float r_lo = ratio_lo < 1.0e31 ? (float)(ratio_lo * 16777216.0 * down) : 3.0e38f;
+    const float r_lo = lower_ratio(ratio_lo);
     const float r_hi = upper_ratio(ratio_hi);
     const bool zeros = !(ratio_hi < 1.0e31);                     // 0 * infinity: zeros are taken out by hand
     const unsigned int bucket = done ? 0xFFFFFFFFu : so.prefix;
@@ -738,109 +752,159 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     }
 }
 
-// Solves level 1; level-2 histogram of the elements on the path that it chose, from the records (nothing to do if level 1
-// settled everything).
+// The uniform of an element
+__device__ inline float ew_uniform(unsigned int i, unsigned long long stream_id, unsigned long long seed)
+{
+    const u32x4 rnd = philox4x32_10((unsigned long long)(i >> 2), stream_id, seed);
+    return u01((i & 2) ? ((i & 1) ? rnd.w : rnd.z) : ((i & 1) ? rnd.y : rnd.x));
+}
+
+// Solves level 1 and settles the records of a group of segments as far as that goes; level-2 histogram of the elements on the path
+// that it chose.  The bucket is 2^-13 of the water level wide, so p is known to that, and of s kept elements about 2^-13 s have their
+// draw in between (more among subnormal numbers).  Those are listed for ew_write, which
+// solves level 2 at its head; the others are kept or dropped here: one pass over the records and one launch less than with a pass
+// for the histogram and another for the draws (11.7 million elements, 1 % kept: 3.8 + 4.4 -> 5.8 us; encode and decode of 20,000 elements
+// 25.7 -> 21.6 us, 300,000 26.7 -> 24.6, 11.7 million 53.7 -> 52.3).  Where segments have no slots for their candidates their elements
+// are drawn again: sure ones by single-precision bounds (60 million, 20 % kept: 548 -> 445 us; 200 million, 15 %: 1308 -> 1275).
+// Leaves the count of what is kept for sure.
 template <int STEPS>
-__global__ __launch_bounds__(256) void ew_level2(const float* __restrict__ g, long long n, EwState* st, double s, Segments sg)
+__global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, EwState* st, double s,
+                                                  unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
     __shared__ unsigned int cnt[1 << L2_BITS];
     __shared__ unsigned long long sig[1 << L2_BITS];
+    __shared__ unsigned int wsum[4];
     __shared__ Group gr;
     __shared__ SolveOut out;
     __shared__ unsigned long long scratch[2 * 4 + 1];
-    if (!enter_level2(st, s, &out, scratch)) return;
-    const unsigned int prefix = out.prefix;
-    const int tid = threadIdx.x;
-    for (int b = tid; b < (1 << L2_BITS); b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long first = (long long)blockIdx.x * sg.per_group;
+    load_group(sg, blockIdx.x, gr);
+    const SolveOut in = st->lvl[0];
+    double ratio_lo, ratio_hi;
+    bool search = false;
+    unsigned int prefix = 0u, on_path = 0u;
+    if (in.done) {
+        ratio_lo = ratio_hi = st->ratio;
+    } else {
+        solve_written<1, 256>(st, s, in, &out, scratch);
+        if (blockIdx.x == 0 && tid == 0) publish(st, 1, out, s);
+        search = out.done == 0;
+        prefix = out.prefix;
+        on_path = out.count;
+        if (search) {                                            // (the sums of the search are good to 2^-40)
+            const double lo = (double)__uint_as_float(prefix << L2_BITS), hi = (double)__uint_as_float((prefix + 1) << L2_BITS);
+            ratio_lo = hi < __longlong_as_double(0x7FF0000000000000LL) ? 1.0 / hi * (1.0 - 0x1p-30) : 0.0;
+            ratio_hi = lo > 0.0 ? 1.0 / lo * (1.0 + 0x1p-30) : __longlong_as_double(0x7FF0000000000000LL);
+        } else {
+            ratio_lo = ratio_hi = final_ratio(s, out.n_s, out.tail);
+        }
+    }
+    const bool through_lds = search && on_path > DIRECT_MAX;
+    if (through_lds)
+        for (int b = tid; b < (1 << L2_BITS); b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
+    __syncthreads();
     auto visit = [&](float x) {
         const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
         if ((key >> L2_BITS) == prefix) {
-            atomicAdd(&cnt[key & ((1 << L2_BITS) - 1)], 1u);
-            atomicAdd(&sig[key & ((1 << L2_BITS) - 1)], (unsigned long long)significand(key));
+            const unsigned int b = key & ((1 << L2_BITS) - 1);
+            atomicAdd(through_lds ? &cnt[b] : &st->cnt[2][b], 1u);
+            atomicAdd(through_lds ? &sig[b] : &st->sig[2][b], (unsigned long long)significand(key));
         }
     };
-    for (long long group = blockIdx.x; group < sg.n_groups; group += gridDim.x) {
-        load_group(sg, group, gr);
-        __syncthreads();
-        if (gr.over) {
-            const long long i0 = group * sg.per_group * STEPS * STEP;
-            const long long i1 = min(n, i0 + (long long)sg.per_group * STEPS * STEP);
-            for (long long i = i0 + tid; i < i1; i += 256) visit(g[i]);
-        } else {
-            for (unsigned int t = tid; t < gr.before[MAX_GROUP]; t += 256) {
-                const int k = segment_of(gr, sg.per_group, t);
-                visit(ew_slots(sg, group * sg.per_group + k).val[t - gr.before[k]]);
-            }
-        }
-        __syncthreads();
-    }
-    for (int b = tid; b < (1 << L2_BITS); b += 256) {
-        if (cnt[b]) {
-            atomicAdd(&st->cnt[2][b], cnt[b]);
-            atomicAdd(&st->sig[2][b], sig[b]);
-        }
-    }
-}
-
-// Settles the records of a group of segments with the final ratio: the draw of an open one is repeated, and what is not kept
-// is marked.  Leaves the kept count of the group.
-template <int STEPS>
-__global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, EwState* st, double s,
-                                                 unsigned long long stream_id, unsigned long long seed, Segments sg)
-{
-    __shared__ unsigned int wsum[4];
-    __shared__ Group gr;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    __shared__ SolveOut out;
-    __shared__ unsigned long long scratch[2 * 4 + 1];
-    const double ratio = enter_final(st, s, &out, scratch);
-    const long long first = (long long)blockIdx.x * sg.per_group;
-    load_group(sg, blockIdx.x, gr);
-    __syncthreads();
-    unsigned int kept = 0u;                                      // wave-uniform
+    // -1 dropped, 1 kept, 0 open and listed
+    auto settle = [&](unsigned int i, float x) {
+        const float u = ew_uniform(i, stream_id, seed);
+        if (!(u < ew_probability(x, ratio_hi))) return -1;
+        if (u < ew_probability(x, ratio_lo)) return 1;
+        const unsigned int at = atomicAdd(&st->n_open, 1u);
+        if (at < sg.open_max) sg.open[at] = EwOpen{i, x};
+        return 0;
+    };
+    unsigned int kept = 0u;                                      // this lane's
     if (gr.over) {
+        const bool vec = (((size_t)g) & 15) == 0;
+        const float r_lo = lower_ratio(ratio_lo), r_hi = upper_ratio(ratio_hi);
         for (int k = wave; k < sg.per_group && first + k < sg.n_seg; k += 4) {
-            const unsigned int c = draw_segment<STEPS>(g, n, first + k, stream_id, seed, ratio,
-                                                       [](unsigned int, unsigned int, float, float) {});
-            if (lane == 0) sg.count[first + k] = c | OVER;
-            kept += c;
-        }
-    } else {
-        for (unsigned int t0 = 0; t0 < gr.before[MAX_GROUP]; t0 += 256) {
-            const unsigned int t = t0 + tid;
-            bool keep = false;
-            if (t < gr.before[MAX_GROUP]) {
-                const int k = segment_of(gr, sg.per_group, t);
-                const Slots sl = ew_slots(sg, first + k);
-                const unsigned int r = t - gr.before[k], word = sl.word[r];
-                const float x = sl.val[r];
-                keep = (word & FLAG_BIT) != 0u;
-                if (!keep) {
-                    const unsigned int off = word & (FLAG_BIT - 1);
-                    const u32x4 rnd = philox4x32_10((unsigned long long)((first + k) * STEPS * 64 + (off >> 2)), stream_id, seed);
-                    const unsigned int bits = (off & 2) ? ((off & 1) ? rnd.w : rnd.z) : ((off & 1) ? rnd.y : rnd.x);
-                    keep = u01(bits) < ew_probability(x, ratio);
-                    if (!keep) sl.word[r] = (unsigned short)(word | DROPPED);
+            unsigned int sure = 0u;
+            const long long seg = first + k;
+            const bool whole = vec && (seg + 1) * STEPS * STEP <= n;
+            // (a ratio beyond the float range has no bounds in single precision)
+            const bool exact = !search && !(ratio_hi < 1.0e31);
+            if (exact) {
+                const unsigned int c = draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio_hi,
+                                                           [](unsigned int, unsigned int, float, float) {});
+                sure = lane == 0 ? c : 0u;
+            }
+            for (int j0 = exact ? STEPS : 0; j0 < STEPS; j0 += 4) {
+                float4 xv[4];
+                const long long q0 = (seg * STEPS + j0) * 64;
+                load_steps(g, q0, n, whole, vec, xv);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
+                    const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+                    const float us[4] = {(float)(rnd.x >> 8), (float)(rnd.y >> 8), (float)(rnd.z >> 8), (float)(rnd.w >> 8)};
+                    bool in[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool is_sure = us[e] < fminf(16777216.0f, fabsf(xs[e]) * r_lo) * (1.0f - 2.384185791015625e-07f);
+                        sure += is_sure ? 1u : 0u;
+                        in[e] = !is_sure && !(us[e] >= fabsf(xs[e]) * r_hi);
+                        if (search && (q0 + u * 64 + lane) * 4 + e < n) visit(xs[e]);
+                    }
+                    unsigned int left = candidate_bits(in);
+                    while (__ballot(left != 0u)) {
+                        if (left) {
+                            const int e = __builtin_ctz(left);
+                            left &= left - 1;
+                            sure += settle((unsigned int)(seg * STEPS * STEP) + (j0 + u) * STEP + lane * 4 + e, pick(xs, e)) > 0 ? 1u : 0u;
+                        }
+                    }
                 }
             }
-            kept += (unsigned int)__popcll(__ballot(keep));
+            kept += sure;
+            for (int o = 32; o > 0; o >>= 1) sure += __shfl_xor(sure, o);
+            if (lane == 0) sg.count[first + k] = sure | OVER;
+        }
+    } else {
+        for (unsigned int t = tid; t < gr.before[MAX_GROUP]; t += 256) {
+            const int k = segment_of(gr, sg.per_group, t);
+            const Slots sl = ew_slots(sg, first + k);
+            const unsigned int r = t - gr.before[k], word = sl.word[r];
+            const float x = sl.val[r];
+            if (search) visit(x);
+            if (word & FLAG_BIT) {
+                ++kept;
+            } else {
+                const int what = settle((unsigned int)((first + k) * STEPS * STEP) + word, x);
+                if (what != 0) sl.word[r] = (unsigned short)(word | (what > 0 ? FLAG_BIT : DROPPED));
+                kept += what > 0 ? 1u : 0u;
+            }
         }
     }
+    for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o);
     if (lane == 0) wsum[wave] = kept;
     __syncthreads();
-    if (tid == 0) {
-        unsigned int all = 0u;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) all += wsum[w];
-        sg.group_kept[blockIdx.x] = all;
+    if (tid == 0) sg.group_kept[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (through_lds) {
+        for (int b = tid; b < (1 << L2_BITS); b += 256) {
+            if (cnt[b]) {
+                atomicAdd(&st->cnt[2][b], cnt[b]);
+                atomicAdd(&st->sig[2][b], sig[b]);
+            }
+        }
     }
 }
 
 // The message from the settled records, one group of segments per workgroup, which adds up the counts of all groups before
 // its own by itself.  The last group also reports the total.
 // LQ: every record is kept, and the message's words are index and sign (bit 31) alone.
+// Entry-wise: solves level 2, and draws the records that ew_settle left open with the final ratio, those of the groups before from
+// the list.  More of them than the list holds, which takes a water level under 1e-40, where floats are further apart: every workgroup
+// draws the groups before its own again from the gradient (11.7 million elements 6 ms).
 template <int STEPS, bool LQ>
-__global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, long long n, EwState* st,
+__global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, long long n, EwState* st, double s,
                                                 unsigned long long stream_id, unsigned long long seed, Segments sg,
                                                 long long capacity, unsigned int* __restrict__ idx, float* __restrict__ val,
                                                 long long* count_out, int* flags)
@@ -849,11 +913,48 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
     __shared__ unsigned int wsum[2][4];
     __shared__ Group gr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const double ratio = st->ratio;
     const long long first = (long long)blockIdx.x * sg.per_group;
     unsigned long long part = 0ull;
     for (long long i = tid; i < (long long)blockIdx.x; i += 256) part += sg.group_kept[i];
     load_group(sg, blockIdx.x, gr);
+    double ratio;
+    __shared__ unsigned int more[MAX_GROUP];                     // kept elements of this group's segments that group_kept lacks
+    unsigned int n_open = 0u;
+    if constexpr (!LQ) {
+        __shared__ SolveOut out;
+        __shared__ unsigned long long scratch[2 * 4 + 1];
+        n_open = st->n_open;
+        if (tid < MAX_GROUP) more[tid] = 0u;
+        ratio = enter_final(st, s, &out, scratch);
+        __syncthreads();
+    } else {
+        ratio = st->ratio;
+    }
+    // kept by the draw with the final ratio
+    auto drawn = [&](unsigned int i, float x) { return ew_uniform(i, stream_id, seed) < ew_probability(x, ratio); };
+    const bool listed = n_open <= sg.open_max;
+    if constexpr (!LQ) {
+        if (listed) {
+            for (unsigned int t = tid; t < n_open; t += 256) {
+                const EwOpen e = sg.open[t];
+                const long long seg = e.i / (STEPS * STEP);
+                if (seg < first + sg.per_group && drawn(e.i, e.x)) {
+                    if (seg < first) ++part;
+                    else atomicAdd(&more[seg - first], 1u);
+                }
+            }
+        } else {                                                 // too many for the list: all that is kept, from the gradient
+            part = 0ull;
+            for (long long seg = wave; seg < min(first + (gr.over ? sg.per_group : 0), sg.n_seg); seg += 4) {
+                const unsigned int c = draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio,
+                                                           [](unsigned int, unsigned int, float, float) {});
+                if (lane == 0) {
+                    if (seg < first) part += c;
+                    else more[seg - first] = c;
+                }
+            }
+        }
+    }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_down(part, o);
     if (lane == 0) bsum[wave] = part;
     __syncthreads();
@@ -872,12 +973,18 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
     };
     if (gr.over) {
         for (int k = wave; k < sg.per_group && first + k < sg.n_seg; k += 4) {
-            const unsigned long long pos0 = base + gr.before[k];
+            unsigned long long pos0 = base + gr.before[k];
             const unsigned int i0 = (unsigned int)((first + k) * STEPS * STEP);
+            if constexpr (!LQ) {
+                if (!listed) pos0 = base;
+                for (int j = 0; j < k; ++j) pos0 += more[j];
+            }
             draw_segment<STEPS>(g, n, first + k, stream_id, seed, ratio,
                                 [&](unsigned int pos, unsigned int off, float x, float p) { put(pos0 + pos, i0 + off, x, p); });
         }
-        base += gr.before[MAX_GROUP];
+        if (LQ || listed) base += gr.before[MAX_GROUP];
+        if constexpr (!LQ)
+            for (int j = 0; j < sg.per_group; ++j) base += more[j];
     } else {
         for (unsigned int t0 = 0; t0 < gr.before[MAX_GROUP]; t0 += 256) {
             const unsigned int t = t0 + tid;
@@ -892,6 +999,7 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
                 x = LQ ? (word & FLAG_BIT ? -1.0f : 1.0f) : sl.val[r];
                 keep = LQ || !(word & DROPPED);
                 i = (unsigned int)((first + k) * STEPS * STEP) + (word & (FLAG_BIT - 1));
+                if (!LQ && keep && !(word & FLAG_BIT)) keep = drawn(i, x);
             }
             if (LQ) {
                 if (keep) put(base + t, i, x, 1.0f);
@@ -1323,6 +1431,8 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     l.lq_partial = carve.take<double>(LQ_WGS);
     l.sg.count = carve.take<unsigned int>((size_t)l.sg.n_seg);
     l.sg.group_kept = carve.take<unsigned int>((size_t)l.sg.n_groups);
+    l.sg.open_max = (unsigned)(n / 4096 + 512);                  // (twice of what is to be expected of a message of all elements)
+    l.sg.open = carve.take<EwOpen>(l.sg.open_max);
     size_t step_bytes = STEP_BYTES;
     if (limit) step_bytes = std::min<size_t>(step_bytes, (limit - carve.off - 256) / ((size_t)l.sg.n_seg * l.steps) & ~(size_t)7);
     l.sg.slot_bytes = (int)(step_bytes * l.steps);
@@ -1370,7 +1480,6 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
     }
     const Segments& sg = l.sg;
     const int wgs0 = level0_workgroups(n);
-    const int wgs2 = (int)std::min<int64_t>(HIST_WGS, sg.n_groups);
     const unsigned quads = (unsigned)((sg.n_seg + 3) / 4), groups = (unsigned)sg.n_groups;
     const bool long_seg = l.steps == 16;
     if (clear_first) { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(l.st); }
@@ -1381,16 +1490,11 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
         else ew_draw<4><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
     }
     {
-        ProfScope ps(ctx, ATOMO_K_EW_HIST, stream);
-        if (long_seg) ew_level2<16><<<wgs2, 256, 0, stream>>>(g, n, l.st, s, sg);
-        else ew_level2<4><<<wgs2, 256, 0, stream>>>(g, n, l.st, s, sg);
-    }
-    {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
         if (long_seg) ew_settle<16><<<groups, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
         else ew_settle<4><<<groups, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
         const auto write = long_seg ? ew_write<16, false> : ew_write<4, false>;
-        write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, sg, (long long)msg->capacity, msg->idx, msg->val,
+        write<<<groups, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg, (long long)msg->capacity, msg->idx, msg->val,
                                           (long long*)msg->count, ctx->d_flags);
         if (p_out) ew_write_p<<<(int)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(g, n, l.st, p_out);
     }
@@ -1444,7 +1548,7 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
                                    : (mode == LQ_POW ? lq_draw<4, true> : lq_draw<4, false>);
         draw<<<groups, 256, 0, stream>>>(g, n, l.st, l.lq_partial, wgs, mode, q, msg->norm, stream_id, seed, l.sg);
         const auto write = long_seg ? ew_write<16, true> : ew_write<4, true>;
-        write<<<groups, 256, 0, stream>>>(g, n, l.st, stream_id, seed, l.sg, (long long)msg->capacity, msg->idx, nullptr,
+        write<<<groups, 256, 0, stream>>>(g, n, l.st, 0.0, stream_id, seed, l.sg, (long long)msg->capacity, msg->idx, nullptr,
                                           (long long*)msg->count, ctx->d_flags);
         if (p_out) ew_write_p<<<(int)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(g, n, l.st, p_out);
     }

@@ -170,3 +170,33 @@ def test_largest_supported_length():
     assert abs(total - float(val.abs().double().sum())) <= 1e-9 * total
     del out, g
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kind", ["dense", "dense_here_and_there", "subnormal", "subnormal_dense", "last_bucket"])
+@pytest.mark.parametrize("n", [17_000, 300_001])
+def test_records_that_the_second_search_level_leaves_open(kind, n):
+    """Open records in segments with and without slots for all candidates; more of them than the list holds (all nonzero elements
+    where a bucket reaches down to zero); the water level in the last bucket of its level, at 1.12494 = 1.125 - 2^-14.02."""
+    rng = np.random.default_rng(n)
+    g = (rng.standard_normal(n) * 0.5).astype(np.float32)
+    s = 0.3 * n
+    if kind == "dense_here_and_there":
+        g[rng.random(n) < np.where(np.arange(n) // 5000 % 2, 0.0, 0.97)] = 0
+        s = 0.2 * n
+    elif kind.startswith("subnormal"):
+        g = (rng.integers(-200, 201, n) * 2.0 ** -149).astype(np.float32)
+        s = 0.4 * n
+        if kind == "subnormal":                                  # (slots for them all)
+            g[rng.random(n) < 0.95] = 0
+            s = n / 100
+    elif kind == "last_bucket":
+        g = rng.uniform(0.1, 1.0, n).astype(np.float32)
+        s = float(g.astype(np.float64).sum()) / 1.12494
+    if not kind.startswith("subnormal"):
+        parity(g, s, 5, 2, capacity=n)
+        return
+    msg, p, status = encode(g, s, 5, 2, capacity=n)
+    np.testing.assert_allclose(p, oracle.probabilities(g.astype(np.float64), s), rtol=1e-6, atol=1e-12)
+    h, ref = msg.to_host(), oracle.encode_entrywise(g, s, 5, 2, p32=p)
+    assert status == 0 and np.array_equal(h["idx"], ref["idx"])
+    np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6, atol=2.0 ** -149)        # (a value is rounded to a multiple of that)
