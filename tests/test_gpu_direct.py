@@ -445,3 +445,26 @@ def test_groups_of_eight_workgroups_give_the_bits_of_larger_ones(groups, kind):
     check(msgs, {})
     for j in first.values():
         full_parity(host[j], 3.0, 6, j, msgs[j], *per[j])
+
+
+@pytest.mark.parametrize("kind", ["pairs", "graded", "even", "one_octave"])
+@pytest.mark.parametrize("r", [64, 130, 300])
+def test_eigenvalues_that_are_close_to_each_other_or_far_apart(r, kind):
+    """Pairs 2e-7 apart, a factor 2^(1/20) from each to the next, even steps, all within one octave; by 32 points per eigenvalue and, in a
+    call of many, by 4.  The search ends at 2^-27 of lambda, a float is rounded by 6e-8."""
+    rng = np.random.default_rng(r)
+    j = np.arange(r)
+    sv = {"pairs": 2.0 ** (-(j // 2) / 24.0) * (1.0 - 2e-7 * (j % 2)), "graded": 2.0 ** (-j / 20.0), "even": 1.0 - j / (r + 1.0),
+          "one_octave": 1.0 - 0.5 * np.sort(rng.random(r))}[kind]
+    u, _ = np.linalg.qr(rng.standard_normal((r, r)))
+    v, _ = np.linalg.qr(rng.standard_normal((r + 40, r)))
+    G = dev(((u * sv) @ v.T).astype(np.float32))
+    want = np.linalg.svd(G.cpu().numpy().astype(np.float64), compute_uv=False)
+    got = []
+    for n in (1, 70 * 300 // r):
+        sigma = torch.zeros(n * r, device="cuda")
+        binding.atomo_encode_svd(ctx(), [G] * n, 0.25, 3, 0, sigma_out=sigma)
+        assert ctx().status()[0] == 0 and route(n)[0] == DIRECT
+        got.append(sigma[:r].cpu().numpy())
+        np.testing.assert_allclose(got[-1], want, rtol=1e-7, atol=1e-9 * want[0])
+    assert np.array_equal(*got)
