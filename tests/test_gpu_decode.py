@@ -111,3 +111,33 @@ def test_matrix_core_rate_probe_returns_a_plausible_figure():
     # the measurement helper of bench.py: between a tenth of and the whole published fp32 matrix-core peak
     rate = ctx().measure_mfma_fp32()
     assert 15.0 < rate < 160.0
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_svd_decode_of_tall_and_other_outputs_in_one_call(accumulate):
+    """Outputs of at most 32 columns have tiles of their own in the same launch: both kinds, their edges, unaligned rows, several
+    messages and none that keeps anything.  An entry is a sum of K products in float, and one more with what was there: its error is at
+    most (K + 4) eps times the sum of the magnitudes."""
+    rng = np.random.default_rng(5)
+    shapes = [(64, 576), (1, 1), (2049, 18), (300, 32), (300, 33), (4097, 2), (33, 31), (130, 1030), (5000, 17), (513, 27)]
+    scale = 0.375
+    groups, outs, starts = [], [], []
+    for j, (rows, cols) in enumerate(shapes):
+        groups.append([make_msg(rng, rows, cols, k, 6) for k in ([3], [0, 4, 1], [0])[j % 3]])
+        ld = cols + j % 4
+        start = rng.standard_normal((rows, ld)).astype(np.float32)
+        starts.append(start)
+        outs.append(dev(start)[:, :cols])
+    messages = [[m for m, _ in grp] for grp in groups]
+    if accumulate:
+        binding.atomo_apply_svd_batch(ctx(), messages, scale, outs)
+    else:
+        binding.atomo_decode_svd_batch(ctx(), messages, scale, outs=outs)
+    for (rows, cols), grp, out, start in zip(shapes, groups, outs, starts):
+        want = oracle.decode_svd([h for _, h in grp], rows, cols, scale=scale)
+        size = oracle.decode_svd([{key: np.abs(x) for key, x in h.items()} for _, h in grp], rows, cols, scale=scale)
+        if accumulate:
+            want = want + start[:, :cols]
+            size = size + np.abs(start[:, :cols])
+        terms = sum(h["w"].size for _, h in grp)
+        assert (np.abs(out.cpu().numpy() - want) <= (terms + 4) * 2.0 ** -23 * size).all(), (rows, cols)

@@ -468,3 +468,21 @@ def test_eigenvalues_that_are_close_to_each_other_or_far_apart(r, kind):
         got.append(sigma[:r].cpu().numpy())
         np.testing.assert_allclose(got[-1], want, rtol=1e-7, atol=1e-9 * want[0])
     assert np.array_equal(*got)
+
+
+@pytest.mark.parametrize("r", [33, 64, 255, 256, 257, 512, 513, 640])
+def test_selection_at_the_edges_of_a_thread_s_share(r):
+    """One, two and three values per thread, and the last thread's share cut off; budgets that keep nearly nothing and nearly everything
+    that has a singular value, equal ones and zeros among them."""
+    rng = np.random.default_rng(r)
+    G = inputs.low_rank_plus_noise(rng, r, r + 30, [1.0, 0.5, 0.25, 0.1], 0.02)
+    dead = G.copy()
+    dead[rng.choice(r, r - 24, replace=False)] = 0               # 24 singular values
+    for G, s in ((G, 0.01), (G, 5.0), (dead, 2.0), (dead, 24.0)):
+        msgs, per, status, _ = encode([G], s, 8, stream_base=1, capacity=r)
+        sigma, p = per[0]
+        assert status == 0
+        p_ref = oracle.probabilities(sigma.astype(np.float64), s)
+        np.testing.assert_allclose(p, p_ref, rtol=1e-5, atol=1e-12)
+        mask = oracle.bernoulli_mask(p, 8, 1)
+        assert np.array_equal(msgs[0].to_host()["idx"], np.flatnonzero(mask))
