@@ -645,7 +645,7 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
 // the candidates, one element in fifty, is left to them, and a lane takes one candidate per turn, because four predicated
 // blocks, one per component, were a third of the pass.  2^28 elements, 1 % kept: 230 us, where drawing, keep bits, and
 // gathering the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us
-// (now 24 to settle, 20 to write).
+// (2^30 elements: 67 to settle, 74 to write).
 template <int STEPS>
 __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long long n, EwState* st, double s,
                                                unsigned long long stream_id, unsigned long long seed, Segments sg)
