@@ -1917,7 +1917,7 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
 // Vectors of the longer side: A^T u / sigma, four kept atoms per pass over the data
 // ------------------------------------------------------------------------------------------------
 constexpr int LONG_COLS = 128;   // positions of the long side per workgroup
-constexpr int LONG_GROUP = 4;
+constexpr int LONG_GROUP = 8, LONG_PART = 4;   // atoms per pass over the data; per sum over the waves
 
 // A message that needs no singular vectors, for a matrix with a kept vector that was not accepted and no iteration behind it:
 // the r vectors themselves are an atomic decomposition (A = sum_i |a_i| e_i (a_i / |a_i|)^T), exact, and what is drawn from it
@@ -1995,14 +1995,15 @@ __device__ inline void row_message(const DirectMat& m, double s, u64 seed, RowAt
     }
 }
 
-// Bound: one read of the data (4 atoms at a time).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
+// Bound: one read of the data, 8 atoms at a time, in rows of 512 bytes (64 x (512 x 4608), 4 atoms on average: 4 at a time 187 us, now 157; the
+// ResNet-18 layers, some with more than four, 28.8 -> 21.7).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
 // positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The first workgroup reports (the host
 // memory that it writes to is far away: it is not to start last), and makes the messages of row_message.
 __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_mats, double s, u64 seed,
                                                    int* hint_out, int* flags)
 {
     __shared__ __attribute__((aligned(16))) double us[LONG_GROUP][MAX_R];
-    __shared__ double red[8][LONG_GROUP][LONG_COLS];
+    __shared__ double red[8][LONG_PART][LONG_COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x == 0) {
         static_assert(sizeof(RowAtoms) <= sizeof(us), "made in the place of the vectors");
@@ -2035,15 +2036,36 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
     for (int s0 = 0; s0 < kept; s0 += LONG_GROUP) {
         const int ns = min(LONG_GROUP, kept - s0);
         __syncthreads();
-        for (int i = tid; i < LONG_GROUP * r; i += 512) {
-            const int k = i / r, x = i - k * r;
-            us[k][x] = k < ns ? global(m.u)[(size_t)(s0 + k) * r + x] : 0.0;
-        }
-        __syncthreads();
-        if (!m.transposed) {
-            double acc[LONG_GROUP][2];
+        for (int x = tid; x < r; x += 512)
+            for (int k0 = 0; k0 < ns; k0 += LONG_PART) {
+                double v[LONG_PART];
 #pragma unroll
-            for (int k = 0; k < LONG_GROUP; ++k) acc[k][0] = acc[k][1] = 0.0;
+                for (int k = 0; k < LONG_PART; ++k) v[k] = global(m.u)[(size_t)(s0 + min(k0 + k, ns - 1)) * r + x];
+#pragma unroll
+                for (int k = 0; k < LONG_PART; ++k) us[k0 + k][x] = k0 + k < ns ? v[k] : 0.0;
+            }
+        __syncthreads();
+        // the sums of LONG_PART atoms from k0 on are in `red`
+        auto put = [&](int k0) {
+            __syncthreads();
+            const int k = k0 + tid / LONG_COLS, p = tid % LONG_COLS;
+            if (k < ns && p0 + p < m.M) {
+                double sum = red[0][k - k0][p];
+                if (!m.transposed) {
+#pragma unroll
+                    for (int q = 1; q < 8; ++q) sum += red[q][k - k0][p];
+                }
+                const int i = m.idx[s0 + k];
+                const double sigma = ldexp(sqrt(m.lam[i]), m.st[DS_EXP] / 2);
+                const float fold = m.w || !m.transposed ? 1.0f : m.weight[s0 + k];
+                out[(size_t)(s0 + k) * m.M + p0 + p] = (float)(sum / sigma) * fold;
+            }
+        };
+        auto wide = [&](auto number) {
+            constexpr int N = decltype(number)::value;
+            double acc[N][2];
+#pragma unroll
+            for (int k = 0; k < N; ++k) acc[k][0] = acc[k][1] = 0.0;
             const int ca = min(p0 + lane, m.M - 1), cb = min(p0 + 64 + lane, m.M - 1);
             for (int i0 = wave; i0 < r; i0 += 8 * 8) {
                 float ga[8], gb[8];
@@ -2058,7 +2080,7 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
                     const int i = i0 + 8 * u;
                     if (i < r) {
 #pragma unroll
-                        for (int k = 0; k < LONG_GROUP; ++k) {
+                        for (int k = 0; k < N; ++k) {
                             acc[k][0] = fma((double)ga[u], us[k][i], acc[k][0]);
                             acc[k][1] = fma((double)gb[u], us[k][i], acc[k][1]);
                         }
@@ -2066,42 +2088,42 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
                 }
             }
 #pragma unroll
-            for (int k = 0; k < LONG_GROUP; ++k) {
-                red[wave][k][lane] = acc[k][0];
-                red[wave][k][64 + lane] = acc[k][1];
+            for (int k0 = 0; k0 < N; k0 += LONG_PART) {
+                if (k0 > 0) __syncthreads();
+#pragma unroll
+                for (int k = 0; k < LONG_PART; ++k) {
+                    red[wave][k][lane] = acc[k0 + k][0];
+                    red[wave][k][64 + lane] = acc[k0 + k][1];
+                }
+                put(k0);
             }
+        };
+        if (!m.transposed) {
+            if (ns > LONG_PART) wide(std::integral_constant<int, LONG_GROUP>());
+            else wide(std::integral_constant<int, LONG_PART>());
         } else {
             // positions wave, wave + 8, ..: eight at a time, the lanes along the vector
-            for (int h = 0; h < LONG_COLS / 64; ++h) {
-                for (int k = 0; k < ns; ++k) {
-                    double acc[8];
+            for (int k0 = 0; k0 < ns; k0 += LONG_PART) {
+                if (k0 > 0) __syncthreads();
+                for (int h = 0; h < LONG_COLS / 64; ++h) {
+                    for (int k = k0; k < min(ns, k0 + LONG_PART); ++k) {
+                        double acc[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
-                    for (int i = lane; i < r; i += 64) {
-                        const double uu = us[k][i];
+                        for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+                        for (int i = lane; i < r; i += 64) {
+                            const double uu = us[k][i];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const int p = min(p0 + 64 * h + wave + 8 * u, m.M - 1);
-                            acc[u] = fma((double)G[(long long)p * m.ldg + i], uu, acc[u]);
+                            for (int u = 0; u < 8; ++u) {
+                                const int p = min(p0 + 64 * h + wave + 8 * u, m.M - 1);
+                                acc[u] = fma((double)G[(long long)p * m.ldg + i], uu, acc[u]);
+                            }
                         }
+                        const double sum = wave_sums<8>(acc, lane);
+                        if ((lane & 7) == 0) red[0][k - k0][64 * h + wave + 8 * sum_slot(lane)] = sum;
                     }
-                    const double sum = wave_sums<8>(acc, lane);
-                    if ((lane & 7) == 0) red[0][k][64 * h + wave + 8 * sum_slot(lane)] = sum;
                 }
+                put(k0);
             }
-        }
-        __syncthreads();
-        const int k = tid / LONG_COLS, p = tid % LONG_COLS;
-        if (k < ns && p0 + p < m.M) {
-            double sum = red[0][k][p];
-            if (!m.transposed) {
-#pragma unroll
-                for (int q = 1; q < 8; ++q) sum += red[q][k][p];
-            }
-            const int i = m.idx[s0 + k];
-            const double sigma = ldexp(sqrt(m.lam[i]), m.st[DS_EXP] / 2);
-            const float fold = m.w || !m.transposed ? 1.0f : m.weight[s0 + k];
-            out[(size_t)(s0 + k) * m.M + p0 + p] = (float)(sum / sigma) * fold;
         }
     }
 }

@@ -486,3 +486,13 @@ def test_selection_at_the_edges_of_a_thread_s_share(r):
         np.testing.assert_allclose(p, p_ref, rtol=1e-5, atol=1e-12)
         mask = oracle.bernoulli_mask(p, 8, 1)
         assert np.array_equal(msgs[0].to_host()["idx"], np.flatnonzero(mask))
+
+
+@pytest.mark.parametrize("shape", [(96, 400), (400, 96), (300, 700), (513, 521)])
+@pytest.mark.parametrize("s", [5.0, 8.0, 17.0])
+def test_messages_of_more_atoms_than_a_pass_over_the_data_takes(shape, s):
+    rng = np.random.default_rng(shape[0])
+    G = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.8, 0.6, 0.5, 0.4, 0.3, 0.25, 0.2], 0.01)
+    msgs, per, status, _ = encode([G], s, 11, stream_base=4, capacity=40)
+    assert status == 0 and msgs[0].to_host()["count"] > 2
+    full_parity(G, s, 11, 4, msgs[0], *per[0])
