@@ -553,11 +553,11 @@ __device__ inline float upper_ratio(double ratio)
 {
     return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
 }
-// r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  (the product may be beyond 2^24): a ratio beyond the float range is bounded by the
-// largest float
+// r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  (the product may be beyond 2^24): a ratio of 1e31 and more, which times 2^24 may be
+// beyond the float range, is bounded by that of 1e31
 __device__ inline float lower_ratio(double ratio)
 {
-    return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 - 4.76837158203125e-07)) : 3.0e38f;
+    return (float)(fmin(ratio, 1.0e31) * 16777216.0 * (1.0 - 4.76837158203125e-07));
 }
 __device__ inline unsigned int candidate_bits(const bool (&in)[4])
 {

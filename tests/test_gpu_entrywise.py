@@ -200,3 +200,20 @@ def test_records_that_the_second_search_level_leaves_open(kind, n):
     h, ref = msg.to_host(), oracle.encode_entrywise(g, s, 5, 2, p32=p)
     assert status == 0 and np.array_equal(h["idx"], ref["idx"])
     np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6, atol=2.0 ** -149)        # (a value is rounded to a multiple of that)
+
+
+@pytest.mark.parametrize("kind", ["slots", "dense"])                       # segments with and without slots for their candidates
+@pytest.mark.parametrize("level", [5.0e-32, 6.0e-32, 9.7e-32, 1.2e-31])
+def test_water_levels_where_the_scaled_ratio_leaves_the_float_range(level, kind):
+    # 2^24 / level against the largest float, 3.4e38: the single-precision bounds of p change their form at a level of 1e-31
+    n = 100_001 if kind == "slots" else 2_000_003
+    rng = np.random.default_rng(7)
+    g = rng.standard_normal(n)
+    if kind == "slots":                                                   # (behind the level's last bound every nonzero is a candidate)
+        g[rng.random(n) < 0.95] = 0
+    s = n / 100 if kind == "slots" else 0.3 * n
+    p = oracle.probabilities(g, s)
+    g = (g * (level * np.max(p[g != 0] / np.abs(g[g != 0])))).astype(np.float32)          # (an uncapped p is |g| / level)
+    p_gpu = parity(g, s, 21, 4)[2]
+    free = (p_gpu > 0) & (p_gpu < 1)
+    np.testing.assert_allclose(np.abs(g[free]) / p_gpu[free], level, rtol=1e-5)
