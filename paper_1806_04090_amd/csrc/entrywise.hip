@@ -553,11 +553,17 @@ __device__ inline float upper_ratio(double ratio)
 {
     return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
 }
-// r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  (the product may be beyond 2^24): a ratio of 1e31 and more, which times 2^24 may be
-// beyond the float range, is bounded by that of 1e31
+// r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  unless p is below the normal range (the product may be beyond 2^24): a ratio of 1e31
+// and more, which times 2^24 may be beyond the float range, is bounded by that of 1e31
 __device__ inline float lower_ratio(double ratio)
 {
     return (float)(fmin(ratio, 1.0e31) * 16777216.0 * (1.0 - 4.76837158203125e-07));
+}
+// u < p for sure, for the integer u 2^24: fl32(|x| r) (1 - 2^-22) is more.  Less than 2^-100, where p, less by 2^24, may be so far
+// below the normal range that it is rounded to zero, is not enough for the u = 0 that it would count for.
+__device__ inline bool surely_below(float u, float x, float r)
+{
+    return u < fmaf(fminf(16777216.0f, fabsf(x) * r), 1.0f - 2.384185791015625e-07f, -7.888609052210118e-31f);
 }
 __device__ inline unsigned int candidate_bits(const bool (&in)[4])
 {
@@ -665,7 +671,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
     // uniform (an integer below 2^24): with r_lo <= ratio (1 - 2^-22) and r_hi >= ratio (1 + 2^-22),
     // fl32(|g| r_lo) (1 - 2^-22) <= p <= fl32(|g| r_hi) (each rounding moves a value by at most 2^-24 of itself; where
-    // |g| r_hi 2^24 underflows, p is zero).  A bracket that is a little wide only sends a few more coordinates to ew_settle,
+    // |g| r_hi 2^24 underflows, p is zero, and where p is below the normal range see surely_below).  A bracket that is a little wide only sends a few more coordinates to ew_settle,
     // which decides with the exact formula.
     double ratio_lo, ratio_hi;
     if (done) {
@@ -715,7 +721,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                             const int e = __builtin_ctz(left);
                             left &= left - 1;
                             const float x = pick(xs, e), uf = pick(us, e);
-                            const bool sure = uf < fminf(16777216.0f, fabsf(x) * r_lo) * (1.0f - 2.384185791015625e-07f);
+                            const bool sure = surely_below(uf, x, r_lo);
                             if (pos < (unsigned int)sl.capacity) {
                                 sl.val[pos] = x;
                                 sl.word[pos] = (unsigned short)(((j0 + u) * STEP + lane * 4 + e) | (sure ? FLAG_BIT : 0u));
@@ -848,7 +854,7 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
                     bool in[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const bool is_sure = us[e] < fminf(16777216.0f, fabsf(xs[e]) * r_lo) * (1.0f - 2.384185791015625e-07f);
+                        const bool is_sure = surely_below(us[e], xs[e], r_lo);
                         sure += is_sure ? 1u : 0u;
                         in[e] = !is_sure && !(us[e] >= fabsf(xs[e]) * r_hi);
                         if (search && (q0 + u * 64 + lane) * 4 + e < n) visit(xs[e]);

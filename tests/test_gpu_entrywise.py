@@ -217,3 +217,19 @@ def test_water_levels_where_the_scaled_ratio_leaves_the_float_range(level, kind)
     p_gpu = parity(g, s, 21, 4)[2]
     free = (p_gpu > 0) & (p_gpu < 1)
     np.testing.assert_allclose(np.abs(g[free]) / p_gpu[free], level, rtol=1e-5)
+
+
+@pytest.mark.parametrize("kind", ["dense", "slots"])
+@pytest.mark.parametrize("x", [2.0 ** -149, 2.0 ** -143, 2.0 ** -142, 2.0 ** -137, 2.0 ** -101])
+def test_a_draw_of_zero_against_a_probability_below_the_normal_range(x, kind):
+    # element 227537 draws 0 and is kept if its p is more than 0 as a float: the smallest is 2^-149, p = x / level
+    n, at = 300_001, 227_537
+    assert oracle.uniforms(58, 2, n)[at] == 0
+    rng = np.random.default_rng(0)
+    g = (rng.standard_normal(n) * 50).astype(np.float32)
+    if kind == "slots":
+        g[rng.random(n) < 0.95] = 0
+    g[at] = x
+    _, h, p_gpu = parity(g, 0.3 * n if kind == "dense" else n / 100, 58, 2, capacity=n)
+    level = 132.7 if kind == "dense" else 202.9
+    assert (at in h["idx"]) == (x / level > 2.0 ** -150) == (p_gpu[at] > 0)
