@@ -548,10 +548,11 @@ __device__ inline unsigned int listed_total(const unsigned long long (&ballots)[
     return (unsigned int)(__popcll(ballots[0]) + __popcll(ballots[1]) + __popcll(ballots[2]) + __popcll(ballots[3]));
 }
 
-// r with  p <= fl32(|x| r) 2^-24  for the p = fl32(|x| ratio) of any x but 0 (the product may be NaN there); see ew_draw
+// r with  p <= fl32(|x| r) 2^-24  for the p = fl32(|x| ratio) of any x but 0 (the product may be NaN there); see ew_draw.  More than zero,
+// so that the product is zero only where p is, whatever the level is.
 __device__ inline float upper_ratio(double ratio)
 {
-    return ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
+    return ratio < 1.0e31 ? fmaxf((float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)), __int_as_float(1)) : __int_as_float(0x7f800000);
 }
 // r with  fl32(|x| r) (1 - 2^-22) 2^-24 <= p  unless p is below the normal range (the product may be beyond 2^24): a ratio of 1e31
 // and more, which times 2^24 may be beyond the float range, is bounded by that of 1e31
@@ -599,7 +600,7 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
     const bool vec = (((size_t)g) & 15) == 0;
     const int lane = threadIdx.x & 63;
     // u >= p is decided in single precision wherever p (1 + 2^-21) leaves no doubt; the rest gets the exact p
-    const float r_hi = ratio < 1.0e31 ? (float)(ratio * 16777216.0 * (1.0 + 4.76837158203125e-07)) : __int_as_float(0x7f800000);
+    const float r_hi = upper_ratio(ratio);
     const bool whole = vec && (seg + 1) * STEPS * STEP <= n;
     unsigned int fill = 0u;                                      // wave-uniform
     for (int j0 = 0; j0 < STEPS; j0 += 4) {

@@ -233,3 +233,15 @@ def test_a_draw_of_zero_against_a_probability_below_the_normal_range(x, kind):
     _, h, p_gpu = parity(g, 0.3 * n if kind == "dense" else n / 100, 58, 2, capacity=n)
     level = 132.7 if kind == "dense" else 202.9
     assert (at in h["idx"]) == (x / level > 2.0 ** -150) == (p_gpu[at] > 0)
+
+
+@pytest.mark.parametrize("n, seed, at", [(16_000, 1246, 10_044), (300_001, 58, 227_537)])
+def test_a_draw_of_zero_below_a_water_level_beyond_the_float_range(n, seed, at):
+    # a budget so small that 2^24 / level is zero as a float: the one element that draws 0 has p = 1e-19 to 1e-18 and is kept
+    # (with a value of the level, which no float holds)
+    assert list(np.flatnonzero(oracle.uniforms(seed, 2, n) == 0)) == [at]
+    g = (np.random.default_rng(n).uniform(0.5e38, 1e38, n)).astype(np.float32)
+    msg, p, status = encode(g, 1e-13, seed, 2, capacity=8)
+    np.testing.assert_allclose(p, oracle.probabilities(g.astype(np.float64), 1e-13), rtol=1e-6)
+    h = msg.to_host()
+    assert status == 0 and list(h["idx"]) == [at] and np.isinf(h["val"][0])
