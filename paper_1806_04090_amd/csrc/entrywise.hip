@@ -465,6 +465,8 @@ constexpr unsigned int FLAG_BIT = 0x1000u;   // entry-wise: kept for sure; l_q: 
 constexpr unsigned int DROPPED = 0x2000u;    // entry-wise: settled, not kept
 constexpr int MAX_GROUP = 64;
 constexpr unsigned int DIRECT_MAX = 65536;
+constexpr unsigned int COUNTED = 0x80000000u;   // in group_kept: the group's final count, by ew_write
+constexpr int SPIN_COUNTED = 1 << 14;        // loads of another workgroup's count, about ten milliseconds: never seen
 
 // A record whose draw lies between the bounds that level 1 gives for its p.
 struct EwOpen {
@@ -768,12 +770,13 @@ __device__ inline float ew_uniform(unsigned int i, unsigned long long stream_id,
 
 // Solves level 1 and settles the records of a group of segments as far as that goes; level-2 histogram of the elements on the path
 // that it chose.  The bucket is 2^-13 of the water level wide, so p is known to that, and of s kept elements about 2^-13 s have their
-// draw in between (more among subnormal numbers).  Those are listed for ew_write, which
-// solves level 2 at its head; the others are kept or dropped here: one pass over the records and one launch less than with a pass
+// draw in between.  Those are listed for ew_write, which solves level 2 at its head; the others are kept or dropped here: one pass over the records and one launch less than with a pass
 // for the histogram and another for the draws (11.7 million elements, 1 % kept: 3.8 + 4.4 -> 5.8 us; encode and decode of 20,000 elements
 // 25.7 -> 21.6 us, 300,000 26.7 -> 24.6, 11.7 million 53.7 -> 52.3).  Where segments have no slots for their candidates their elements
 // are drawn again: sure ones by single-precision bounds (60 million, 20 % kept: 548 -> 445 us; 200 million, 15 %: 1308 -> 1275).
 // Leaves the count of what is kept for sure.
+// Below the normal range the bucket is wider, 2^-139, and where the list would not hold what lies in between (levels up to about
+// 6e-39) nothing is settled here.
 template <int STEPS>
 __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, EwState* st, double s,
                                                   unsigned long long stream_id, unsigned long long seed, Segments sg)
@@ -790,6 +793,7 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     const SolveOut in = st->lvl[0];
     double ratio_lo, ratio_hi;
     bool search = false;
+    bool listed = true;
     unsigned int prefix = 0u, on_path = 0u;
     if (in.done) {
         ratio_lo = ratio_hi = st->ratio;
@@ -803,6 +807,8 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
             const double lo = (double)__uint_as_float(prefix << L2_BITS), hi = (double)__uint_as_float((prefix + 1) << L2_BITS);
             ratio_lo = hi < __longlong_as_double(0x7FF0000000000000LL) ? 1.0 / hi * (1.0 - 0x1p-30) : 0.0;
             ratio_hi = lo > 0.0 ? 1.0 / lo * (1.0 + 0x1p-30) : __longlong_as_double(0x7FF0000000000000LL);
+            // (about so many draws lie between the bounds, half of the list at most unless the level is below the normal range)
+            listed = (s - (double)out.n_above) * (1.0 - ratio_lo / ratio_hi) <= (double)sg.open_max;
         } else {
             ratio_lo = ratio_hi = final_ratio(s, out.n_s, out.tail);
         }
@@ -829,7 +835,18 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
         return 0;
     };
     unsigned int kept = 0u;                                      // this lane's
-    if (gr.over) {
+    if (!listed) {
+        if (gr.over) {
+            const long long i1 = min(n, (first + sg.per_group) * STEPS * STEP);
+            for (long long i = first * STEPS * STEP + tid; i < i1; i += 256) visit(g[i]);
+        } else {
+            for (unsigned int t = tid; t < gr.before[MAX_GROUP]; t += 256) {
+                const int k = segment_of(gr, sg.per_group, t);
+                visit(ew_slots(sg, first + k).val[t - gr.before[k]]);
+            }
+        }
+        if (blockIdx.x == 0 && tid == 0) st->n_open = ~0u;
+    } else if (gr.over) {
         const bool vec = (((size_t)g) & 15) == 0;
         const float r_lo = lower_ratio(ratio_lo), r_hi = upper_ratio(ratio_hi);
         for (int k = wave; k < sg.per_group && first + k < sg.n_seg; k += 4) {
@@ -908,8 +925,10 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
 // its own by itself.  The last group also reports the total.
 // LQ: every record is kept, and the message's words are index and sign (bit 31) alone.
 // Entry-wise: solves level 2, and draws the records that ew_settle left open with the final ratio, those of the groups before from
-// the list.  More of them than the list holds, which takes a water level under 1e-40, where floats are further apart: every workgroup
-// draws the groups before its own again from the gradient (11.7 million elements 6 ms).
+// the list.  Without one, or with more of them than it holds, every workgroup draws its group from the gradient, hands the count over
+// and waits for those of the groups before, which count theirs before they wait for anybody.  A count that does not come (nothing
+// guarantees that workgroups start in order) is made here, so the wait has a bound.  Multiples of 2^-149 up to 200, 40 % kept: 16 million
+// 286 us, 268 million 3.6 ms (normal ones 188 us and 1.7 ms; with every workgroup drawing all groups before its own 12.8 and 209 ms).
 template <int STEPS, bool LQ>
 __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, long long n, EwState* st, double s,
                                                 unsigned long long stream_id, unsigned long long seed, Segments sg,
@@ -950,14 +969,36 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
                     else atomicAdd(&more[seg - first], 1u);
                 }
             }
-        } else {                                                 // too many for the list: all that is kept, from the gradient
+        } else {
+            auto draw = [&](long long seg) {
+                return draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio, [](unsigned int, unsigned int, float, float) {});
+            };
+            for (long long seg = first + wave; seg < min(first + sg.per_group, sg.n_seg); seg += 4) {
+                const unsigned int c = draw(seg);
+                if (lane == 0) more[seg - first] = c;
+            }
+            __syncthreads();
+            if (wave == 0) {
+                unsigned int own = more[lane];
+                for (int o = 32; o > 0; o >>= 1) own += __shfl_xor(own, o);
+                if (lane == 0) __hip_atomic_store(&sg.group_kept[blockIdx.x], own | COUNTED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             part = 0ull;
-            for (long long seg = wave; seg < min(first + (gr.over ? sg.per_group : 0), sg.n_seg); seg += 4) {
-                const unsigned int c = draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio,
-                                                           [](unsigned int, unsigned int, float, float) {});
-                if (lane == 0) {
-                    if (seg < first) part += c;
-                    else more[seg - first] = c;
+            for (unsigned int i0 = wave * 64; i0 < blockIdx.x; i0 += 256) {
+                const unsigned int i = min(i0 + lane, blockIdx.x);         // (the own group: counted)
+                unsigned int c = 0u;
+                unsigned long long missing = ~0ull;
+                for (int spins = 0; missing && spins < SPIN_COUNTED; ++spins) {
+                    c = __hip_atomic_load(&sg.group_kept[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    missing = __ballot(!(c & COUNTED) && i < blockIdx.x);
+                }
+                if ((c & COUNTED) && i < blockIdx.x) part += c & ~COUNTED;
+                for (; missing; missing &= missing - 1) {
+                    const long long from = (long long)(i0 + __builtin_ctzll(missing)) * sg.per_group;
+                    for (long long seg = from; seg < from + sg.per_group; ++seg) {
+                        const unsigned int c = draw(seg);
+                        if (lane == 0) part += c;
+                    }
                 }
             }
         }

@@ -172,11 +172,11 @@ def test_largest_supported_length():
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("kind", ["dense", "dense_here_and_there", "subnormal", "subnormal_dense", "last_bucket"])
-@pytest.mark.parametrize("n", [17_000, 300_001])
+@pytest.mark.parametrize("kind", ["dense", "dense_here_and_there", "subnormal", "subnormal_dense", "subnormal_wide", "last_bucket"])
+@pytest.mark.parametrize("n", [17_000, 300_001, 4_200_003])
 def test_records_that_the_second_search_level_leaves_open(kind, n):
     """Open records in segments with and without slots for all candidates; more of them than the list holds (all nonzero elements
-    where a bucket reaches down to zero); the water level in the last bucket of its level, at 1.12494 = 1.125 - 2^-14.02."""
+    where a bucket reaches down to zero, one draw in 170 at a level of 2.4e-40); the water level in the last bucket of its level, at 1.12494 = 1.125 - 2^-14.02."""
     rng = np.random.default_rng(n)
     g = (rng.standard_normal(n) * 0.5).astype(np.float32)
     s = 0.3 * n
@@ -189,6 +189,8 @@ def test_records_that_the_second_search_level_leaves_open(kind, n):
         if kind == "subnormal":                                  # (slots for them all)
             g[rng.random(n) < 0.95] = 0
             s = n / 100
+        elif kind == "subnormal_wide":
+            g, s = rng.uniform(0.0, 4.0e-40, n).astype(np.float32), 0.7 * n
     elif kind == "last_bucket":
         g = rng.uniform(0.1, 1.0, n).astype(np.float32)
         s = float(g.astype(np.float64).sum()) / 1.12494
@@ -245,3 +247,29 @@ def test_a_draw_of_zero_below_a_water_level_beyond_the_float_range(n, seed, at):
     np.testing.assert_allclose(p, oracle.probabilities(g.astype(np.float64), 1e-13), rtol=1e-6)
     h = msg.to_host()
     assert status == 0 and list(h["idx"]) == [at] and np.isinf(h["val"][0])
+
+
+@pytest.mark.parametrize("kind", ["multiples", "wide"])
+def test_a_subnormal_gradient_takes_about_as_long_as_another(kind):
+    # one more pass over the gradient, where each workgroup once drew all groups before its own: 12.8 ms instead of 0.2
+    n, times = 16_000_001, []
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    normal = torch.randn(n, generator=gen, device="cuda")
+    if kind == "multiples":
+        small, s = torch.randint(-200, 201, (n,), generator=gen, device="cuda").float() * 2.0 ** -149, 0.4 * n
+    else:
+        small, s = torch.rand(n, generator=gen, device="cuda") * 4.0e-40, 0.7 * n
+    msg = binding.alloc_entrywise_message(n, n, "cuda")
+    for g in (normal, small):
+        took = []
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            binding.atomo_encode_entrywise(ctx(), g, s, 5, 2, msg=msg)
+            end.record()
+            end.synchronize()
+            took.append(start.elapsed_time(end))
+        times.append(min(took))
+    assert ctx().status()[0] == 0
+    assert times[1] < 6 * times[0], times
