@@ -546,6 +546,10 @@ struct Tri {
     static constexpr int TURN = W < 64 ? W : 64;                 // rows that the waves hand over in turn
     static constexpr bool FEW = W == 4 * FEW_WGS;
     static_assert(W * R == CN, "every row has a wave");
+    // Row slots whose entries of the last step's vectors are broadcast at a time.  Beside 8 x 8 or 12 x 6 entries of the matrix there are
+    // no registers for those of all slots (all at once: 12 and 84 bytes per lane in scratch memory; 64 x (512 x 4608) 3197 -> 3152 us
+    // without, one or two slots at a time the same).
+    static constexpr int GROUP = R <= 5 ? R : 4;
     double a[R][C];
     // Column k; the last step's vectors, which the rows have still to be updated with.  [C]: their entries at the wave's rows, row
     // slot t in lane t of every row of 16 lanes, from where they are broadcast.
@@ -600,33 +604,49 @@ struct Tri {
     __device__ inline Global<u64> slot_c(unsigned step) const { return slots + (2 + (step & 3)) * CN; }
     static __device__ inline unsigned tag_p(unsigned step) { return step & 3; }
     static __device__ inline unsigned tag_c(unsigned step) { return (step >> 2) + 1 & 3; }
-    // a vector's entries at the wave's rows
-    template <int T0, int T = T0>
-    static __device__ inline void entries(double vec, double (&at)[R])
+    // the last step's vectors at row slot T; of the slots from T0 on, GROUP are under way at a time
+    template <int T0, int T>
+    __device__ __forceinline__ void entries(double& wr, double& vr)
+    {
+        if (GROUP < R && (T - T0) % GROUP == 0) {
+            here(wv[C]);
+            here(v[C]);
+        }
+        wr = row_lane<T>(wv[C]);
+        vr = row_lane<T>(v[C]);
+    }
+    // the entries of A y at the wave's rows
+    template <int P, int T0, int T = T0, int K>
+    __device__ __forceinline__ void products(const double (&y)[C + 1], double vy, double wy, double (&sum)[K], double (&wr)[R], double (&vr)[R])
     {
         if constexpr (T < R) {
-            at[T] = row_lane<T>(vec);
-            entries<T0, T + 1>(vec, at);
+            entries<T0, T>(wr[T], vr[T]);
+            double s = a[T][P] * y[P];
+#pragma unroll
+            for (int c = P + 1; c < C; ++c) s = fma(a[T][c], y[c], s);
+            sum[T - T0] = fma(-wr[T], vy, fma(-vr[T], wy, s));
+            if (GROUP < R) here(sum[T - T0]);
+            products<P, T0, T + 1>(y, vy, wy, sum, wr, vr);
         }
     }
-    template <int P, int T0>
-    __device__ inline void update(const double (&wr)[R], const double (&vr)[R])
+    template <int P>
+    __device__ __forceinline__ void update_row(double (&row)[C], double wr, double vr) const
     {
 #pragma unroll
-        for (int t = T0; t < R; ++t)
-#pragma unroll
-            for (int c = P; c < C; ++c) {
-                a[t][c] = fma(-wr[t], v[c], fma(-vr[t], wv[c], a[t][c]));
-                here(a[t][c]);
-            }
+        for (int c = P; c < C; ++c) {
+            row[c] = fma(-wr, v[c], fma(-vr, wv[c], row[c]));
+            here(row[c]);
+        }
     }
-    template <int P, int T0>
+    template <int P, int T0, int T = T0>
     __device__ __forceinline__ void update()
     {
-        double wr[R], vr[R];
-        entries<T0>(wv[C], wr);
-        entries<T0>(v[C], vr);
-        update<P, T0>(wr, vr);
+        if constexpr (T < R) {
+            double wr, vr;
+            entries<T0, T>(wr, vr);
+            update_row<P>(a[T], wr, vr);
+            update<P, T0, T + 1>();
+        }
     }
 
     // step k - 1, every wave of the workgroup a part; with zeros in what is finished of its vector (that is read in pairs of chunks)
@@ -634,12 +654,13 @@ struct Tri {
     __device__ __forceinline__ void keep(int k, const StepStore& store) const
     {
         const int kk = k - 1 - off;
-        const Global<double> row = store.refl + (size_t)kk * store.N + lane - off;
+        const Global<double> row = store.refl + (size_t)kk * store.N - off + (FEW ? 0 : lane);
+        const unsigned at = FEW ? lane : 0;                      // (no address to keep in registers)
 #pragma unroll
         for (int c = P > 1 ? P - 2 : 0; c < C; ++c)
-            if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[64 * c] = c < P ? 0.0 : v[c < P ? P : c];
+            if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[at + 64u * c] = c < P ? 0.0 : v[c < P ? P : c];
         if constexpr (FEW && P <= 1) {                           // (the chunk in front, another group's)
-            if (off < 0 && wave == 3) row[-64] = 0.0;
+            if (off < 0 && wave == 3) (row - 64)[at] = 0.0;
         }
         if (wave == 3 && lane == 0) store.put(kk, tau, diagonal, beta);
     }
@@ -682,15 +703,7 @@ struct Tri {
                 sq = fma(y[c], y[c], sq);
             }
             double wr[R], vr[R];
-            entries<T0>(wv[C], wr);
-            entries<T0>(v[C], vr);
-#pragma unroll
-            for (int t = T0; t < R; ++t) {
-                double s = a[t][P] * y[P];
-#pragma unroll
-                for (int c = PN; c < C; ++c) s = fma(a[t][c], y[c], s);
-                sum[t - T0] = fma(-wr[t], vy, fma(-vr[t], wy, s));
-            }
+            products<P, T0>(y, vy, wy, sum, wr, vr);
             sum[K - 1] = sq;
             const double sums = lane_sums<K>(sum, lane);
             if (mine) put(at_byte(slot_p(step), sum_at), entry(sums, tag_p(step)));
@@ -706,8 +719,12 @@ struct Tri {
             double v0;
             householder(alpha, sig2, beta, v0);
             tau = householder_tau(sig2, v0);
-            if constexpr (R <= 5) update<P, T0>(wr, vr);
-            else update<P, T0>();                                // (broadcast once more: no registers left to keep them)
+            if constexpr (GROUP < R) {                           // (broadcast once more: no registers left to keep them)
+                update<P, T0>();
+            } else {
+#pragma unroll
+                for (int t = T0; t < R; ++t) update_row<P>(a[t], wr[t], vr[t]);
+            }
             here(v0);
             here(tau);
             if (__builtin_expect(k == row_turn, 0)) {

@@ -147,3 +147,11 @@ def test_the_decode_of_svd_messages_keeps_its_registers():
     assert len(tiles) == 4
     for name, r in tiles.items():
         assert r[".private_segment_fixed_size"] == 0 and r[".vgpr_spill_count"] == 0, name
+
+
+def test_the_reduction_to_tridiagonal_form_keeps_its_registers():
+    # the matrix lies in registers there; scratch memory of one class of sizes would be set up by every launch
+    steps = {name: r for name, r in kernel_records().items() if "direct_tridiagonal" in name or "direct_tail" in name}
+    assert len(steps) == 4
+    for name, r in steps.items():
+        assert r[".private_segment_fixed_size"] == 0 and r[".vgpr_spill_count"] == 0, name
