@@ -24,6 +24,10 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
+# decode.hip: the loop of the products, 80 bytes, starts on a cache line of instructions wherever the code in front of it ends.  (An
+# update of 9.75 million parameters from 8 messages: 26.5 us where it starts 12 bytes into one, 26.1 so.)
+HIPCC_FLAGS_OF = {"decode.hip": ["-falign-loops=64"]}
+
 
 def _hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
@@ -52,7 +56,7 @@ def build(verbose: bool = False, host_ubsan: bool = False) -> str:
 
     def compile_one(src: str) -> str:
         obj = os.path.join(obj_dir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *HIPCC_FLAGS, *HIPCC_FLAGS_OF.get(src, []), *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
