@@ -24,9 +24,10 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
-# decode.hip: the loop of the products, 80 bytes, starts on a cache line of instructions wherever the code in front of it ends.  (An
-# update of 9.75 million parameters from 8 messages: 26.5 us where it starts 12 bytes into one, 26.1 so.)
-HIPCC_FLAGS_OF = {"decode.hip": ["-falign-loops=64"]}
+# Loops start on a cache line of instructions wherever the code in front of them ends.  decode.hip: the products, 80 bytes (an update of
+# 9.75 million parameters from 8 messages: 26.5 us where they start 12 bytes into a line, 26.1 so).  svd_direct.hip: a step of the
+# reduction (encode of the ResNet-18 layers 773 us where the compiler put them, 767 so; three of 300 x 1024 368 / 362, three of 512 667 / 661).
+HIPCC_FLAGS_OF = {"decode.hip": ["-falign-loops=64"], "svd_direct.hip": ["-falign-loops=64"]}
 
 
 def _hipcc() -> str:

@@ -546,10 +546,11 @@ struct Tri {
     static constexpr int TURN = W < 64 ? W : 64;                 // rows that the waves hand over in turn
     static constexpr bool FEW = W == 4 * FEW_WGS;
     static_assert(W * R == CN, "every row has a wave");
-    // Row slots whose entries of the last step's vectors are broadcast at a time.  Beside 8 x 8 or 12 x 6 entries of the matrix there are
-    // no registers for those of all slots (all at once: 12 and 84 bytes per lane in scratch memory; 64 x (512 x 4608) 3197 -> 3152 us
-    // without, one or two slots at a time the same).
-    static constexpr int GROUP = R <= 5 ? R : 4;
+    // A phase whose part of the matrix, 12 x 6 entries per lane, leaves no registers for the last step's vectors at the rows of all slots,
+    // nor for the address of a kept vector (up to 84 bytes per lane in scratch memory; 64 x (512 x 4608) 3197 -> 3152 us without).
+    // Four slots at a time where that is not needed lengthen the step: us per encode, n = 1024, in phases of up to 64 entries too / not:
+    // 17 of 320 rows 515 / 509, 20 of 256 398 / 392, ten of 512 808 / 796.
+    static constexpr bool tight(int p) { return (R - 64 * p / W) * (C - p) > 64; }
     double a[R][C];
     // Column k; the last step's vectors, which the rows have still to be updated with.  [C]: their entries at the wave's rows, row
     // slot t in lane t of every row of 16 lanes, from where they are broadcast.
@@ -604,11 +605,11 @@ struct Tri {
     __device__ inline Global<u64> slot_c(unsigned step) const { return slots + (2 + (step & 3)) * CN; }
     static __device__ inline unsigned tag_p(unsigned step) { return step & 3; }
     static __device__ inline unsigned tag_c(unsigned step) { return (step >> 2) + 1 & 3; }
-    // the last step's vectors at row slot T; of the slots from T0 on, GROUP are under way at a time
-    template <int T0, int T>
+    // the last step's vectors at row slot T; tight: of the slots from T0 on, four are under way at a time
+    template <int P, int T0, int T>
     __device__ __forceinline__ void entries(double& wr, double& vr)
     {
-        if (GROUP < R && (T - T0) % GROUP == 0) {
+        if (tight(P) && (T - T0) % 4 == 0) {
             here(wv[C]);
             here(v[C]);
         }
@@ -620,12 +621,12 @@ struct Tri {
     __device__ __forceinline__ void products(const double (&y)[C + 1], double vy, double wy, double (&sum)[K], double (&wr)[R], double (&vr)[R])
     {
         if constexpr (T < R) {
-            entries<T0, T>(wr[T], vr[T]);
+            entries<P, T0, T>(wr[T], vr[T]);
             double s = a[T][P] * y[P];
 #pragma unroll
             for (int c = P + 1; c < C; ++c) s = fma(a[T][c], y[c], s);
             sum[T - T0] = fma(-wr[T], vy, fma(-vr[T], wy, s));
-            if (GROUP < R) here(sum[T - T0]);
+            if (tight(P)) here(sum[T - T0]);
             products<P, T0, T + 1>(y, vy, wy, sum, wr, vr);
         }
     }
@@ -643,7 +644,7 @@ struct Tri {
     {
         if constexpr (T < R) {
             double wr, vr;
-            entries<T0, T>(wr, vr);
+            entries<P, T0, T>(wr, vr);
             update_row<P>(a[T], wr, vr);
             update<P, T0, T + 1>();
         }
@@ -654,8 +655,9 @@ struct Tri {
     __device__ __forceinline__ void keep(int k, const StepStore& store) const
     {
         const int kk = k - 1 - off;
-        const Global<double> row = store.refl + (size_t)kk * store.N - off + (FEW ? 0 : lane);
-        const unsigned at = FEW ? lane : 0;                      // (no address to keep in registers)
+        constexpr bool APART = FEW && tight(P);
+        const Global<double> row = store.refl + (size_t)kk * store.N - off + (APART ? 0 : lane);
+        const unsigned at = APART ? lane : 0;                    // (no address to keep in registers)
 #pragma unroll
         for (int c = P > 1 ? P - 2 : 0; c < C; ++c)
             if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[at + 64u * c] = c < P ? 0.0 : v[c < P ? P : c];
@@ -719,7 +721,7 @@ struct Tri {
             double v0;
             householder(alpha, sig2, beta, v0);
             tau = householder_tau(sig2, v0);
-            if constexpr (GROUP < R) {                           // (broadcast once more: no registers left to keep them)
+            if constexpr (R > 5) {                               // (broadcast once more: no registers left to keep them)
                 update<P, T0>();
             } else {
 #pragma unroll
