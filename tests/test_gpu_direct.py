@@ -494,5 +494,8 @@ def test_messages_of_more_atoms_than_a_pass_over_the_data_takes(shape, s):
     rng = np.random.default_rng(shape[0])
     G = inputs.low_rank_plus_noise(rng, *shape, [1.0, 0.8, 0.6, 0.5, 0.4, 0.3, 0.25, 0.2], 0.01)
     msgs, per, status, _ = encode([G], s, 11, stream_base=4, capacity=40)
-    assert status == 0 and msgs[0].to_host()["count"] > 2
+    assert status == 0 and route() == [DIRECT]
+    count = msgs[0].to_host()["count"]
+    # eight atoms per pass, summed four at a time: a pass with a second sum, a second pass, a third; the last sum of fewer than four
+    assert {5.0: 4 < count <= 8, 8.0: 8 < count <= 16, 17.0: 16 < count <= 24}[s] and count % 4 != 0
     full_parity(G, s, 11, 4, msgs[0], *per[0])
