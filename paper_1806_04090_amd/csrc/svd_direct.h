@@ -1,4 +1,4 @@
-// Direct Spectral-ATOMO encode (svd_direct.hip): descriptors and launches shared with the host side in svd.hip.
+// Direct Spectral-ATOMO encode (svd_direct.hip, svd_direct_values.hip): descriptors and launches shared with the host side in svd.hip.
 #pragma once
 
 #include "svd_common.h"
@@ -8,6 +8,7 @@ namespace direct {
 
 constexpr int MAX_R = 640;           // vectors on the shorter side that the reduction holds in registers
 constexpr int TILE = 64;
+constexpr int RB = 16;               // reflectors per block of the way back through H
 // a wave takes a tile of the Gram product of its own (direct_gram_wide) in calls with so many such work items, of chunks of so many
 // columns
 constexpr size_t WIDE_MIN = 8192;
@@ -93,6 +94,8 @@ struct DirectTables {
 // behind the Gram products; if that fails nothing else is enqueued.
 hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
                   hipEvent_t gram_done = nullptr);
+// its part in svd_direct_values.hip
+void launch_eigenvalues(const DirectPlan& plan, const DirectTables& t, hipStream_t stream);
 
 }  // namespace direct
 }  // namespace atomo
