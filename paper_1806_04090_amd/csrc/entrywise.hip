@@ -674,8 +674,8 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
     // uniform (an integer below 2^24): with r_lo <= ratio (1 - 2^-22) and r_hi >= ratio (1 + 2^-22),
     // fl32(|g| r_lo) (1 - 2^-22) <= p <= fl32(|g| r_hi) (each rounding moves a value by at most 2^-24 of itself; where
-    // |g| r_hi 2^24 underflows, p is zero, and where p is below the normal range see surely_below).  A bracket that is a little wide only sends a few more coordinates to ew_settle,
-    // which decides with the exact formula.
+    // |g| r_hi 2^24 underflows, p is zero, and where p is below the normal range see surely_below).  A bracket that is a little wide
+    // only sends a few more coordinates to ew_settle, which decides with the exact formula.
     double ratio_lo, ratio_hi;
     if (done) {
         ratio_lo = ratio_hi = final_ratio(s, so.n_s, so.tail);
@@ -770,10 +770,11 @@ __device__ inline float ew_uniform(unsigned int i, unsigned long long stream_id,
 
 // Solves level 1 and settles the records of a group of segments as far as that goes; level-2 histogram of the elements on the path
 // that it chose.  The bucket is 2^-13 of the water level wide, so p is known to that, and of s kept elements about 2^-13 s have their
-// draw in between.  Those are listed for ew_write, which solves level 2 at its head; the others are kept or dropped here: one pass over the records and one launch less than with a pass
-// for the histogram and another for the draws (11.7 million elements, 1 % kept: 3.8 + 4.4 -> 5.8 us; encode and decode of 20,000 elements
-// 25.7 -> 21.6 us, 300,000 26.7 -> 24.6, 11.7 million 53.7 -> 52.3).  Where segments have no slots for their candidates their elements
-// are drawn again: sure ones by single-precision bounds (60 million, 20 % kept: 548 -> 445 us; 200 million, 15 %: 1308 -> 1275).
+// draw in between.  Those are listed for ew_write, which solves level 2 at its head; the others are kept or dropped here: one pass over
+// the records and one launch less than with a pass for the histogram and another for the draws (11.7 million elements, 1 % kept: 3.8 +
+// 4.4 -> 5.8 us; encode and decode of 20,000 elements 25.7 -> 21.6 us, 300,000 26.7 -> 24.6, 11.7 million 53.7 -> 52.3).  Where segments
+// have no slots for their candidates their elements are drawn again: sure ones by single-precision bounds (60 million, 20 % kept: 548 ->
+// 445 us; 200 million, 15 %: 1308 -> 1275).
 // Leaves the count of what is kept for sure.
 // Below the normal range the bucket is wider, 2^-139, and where the list would not hold what lies in between (levels up to about
 // 6e-39) nothing is settled here.

@@ -480,11 +480,11 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
 // Bound: what a wave does for itself in a step, one wave on every SIMD: without the waits for the others a step takes as long.  448
-// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 468 us in all (517 with a chain of branches and
-// v_readlane for what a vector holds at the wave's rows, a reduction of its own for the norm, and the reflector behind the update; 800
-// of 3500 cycles).  Rows and columns split between the waves of a workgroup, two instead of eight entries of a vector per lane: 566, for
-// a second barrier and sums of sixteen rows.  Four groups per die, two waves on every SIMD: the issue of the vectors that every wave
-// works out for itself (direct_tridiagonal_few).
+// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 446 us in all, 452 with the loop where the
+// compiler puts it (517 -> 468, on another card, without a chain of branches and v_readlane for what a vector holds at the wave's rows,
+// a reduction of its own for the norm, and the reflector behind the update; 800 of 3500 cycles).  Rows and columns split between the
+// waves of a workgroup, two instead of eight entries of a vector per lane: 566, for a second barrier and sums of sixteen rows.  Four
+// groups per die, two waves on every SIMD: the issue of the vectors that every wave works out for itself (direct_tridiagonal_few).
 //
 // The word that a group starts by: seven bits per die count the workgroups that have started on it; OFF, set by one that has
 // waited too long, holds for all of them: it is only set while some are missing, and who finds it set does not go on.  The
@@ -1229,8 +1229,8 @@ __global__ __launch_bounds__(256, 2) void direct_tridiagonal(const DirectMat* ma
 // For calls whose groups share compute units, where the issue of all the waves counts and not one step's chain: groups of eight
 // workgroups, twelve rows to a wave, for up to HALFWAY rows or for what direct_tridiagonal_half left of more.  Every wave works the
 // vectors out for itself, so half of the waves save half of that; and 64 groups have their places at once (75 MB of the 128 MB
-// of registers are matrix), where 32 of 512 rows have.  64 x (512 x 4608): 1510 -> 625 us for the first 128 steps, in two turns as
-// before, + 650 for the others.  Handing over at 320 rows 30 us more, at 256 (1062 + 298) 70.
+// of registers are matrix), where 32 of 512 rows have.  64 x (512 x 4608): 1510 -> 670 us for the first 128 steps, in two turns as
+// before, + 655 for the others (700 with registers in scratch memory).  Handing over at 320 rows 30 us more, at 256 70.
 __global__ __launch_bounds__(256, 2) void direct_tridiagonal_few(const DirectMat* mats, const Work* work, long long start_ticks)
 {
     __shared__ double2 lds[2 * MAX_R];
@@ -1722,10 +1722,10 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
 }
 
 // ------------------------------------------------------------------------------------------------
-// Vectors of the longer side: A^T u / sigma, four kept atoms per pass over the data
+// Vectors of the longer side: A^T u / sigma, eight kept atoms per turn, summed over the waves four at a time
 // ------------------------------------------------------------------------------------------------
 constexpr int LONG_COLS = 128;   // positions of the long side per workgroup
-constexpr int LONG_GROUP = 8, LONG_PART = 4;   // atoms per pass over the data; per sum over the waves
+constexpr int LONG_GROUP = 8, LONG_PART = 4;   // atoms per turn (a pass over a wide matrix); per sum over the waves
 
 // A message that needs no singular vectors, for a matrix with a kept vector that was not accepted and no iteration behind it:
 // the r vectors themselves are an atomic decomposition (A = sum_i |a_i| e_i (a_i / |a_i|)^T), exact, and what is drawn from it
@@ -1803,10 +1803,11 @@ __device__ inline void row_message(const DirectMat& m, double s, u64 seed, RowAt
     }
 }
 
-// Bound: one read of the data, 8 atoms at a time, in rows of 512 bytes (64 x (512 x 4608), 4 atoms on average: 4 at a time 187 us, now 157; the
-// ResNet-18 layers, some with more than four, 28.8 -> 21.7).  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128
-// positions are two loads of 256 bytes), or positions w, w + 8, .. of a tall one.  The first workgroup reports (the host
-// memory that it writes to is far away: it is not to start last), and makes the messages of row_message.
+// Bound: of a wide matrix the read of the data, once for eight atoms, in rows of 512 bytes (64 x (512 x 4608), 4 atoms on average: 4 at
+// a time 187 us, now 157; the ResNet-18 layers, some with more than four, 28.8 -> 20.9).  Of a tall one the read of its 128 positions,
+// once for every atom.  512 threads: wave w takes rows w, w + 8, .. of a wide matrix (its 128 positions are two loads of 256 bytes), or
+// positions w, w + 8, .. of a tall one.  The first workgroup reports (the host memory that it writes to is far away: it is not to start
+// last), and makes the messages of row_message.
 __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const Work* work, int n_mats, double s, u64 seed,
                                                    int* hint_out, int* flags)
 {
