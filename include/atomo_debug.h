@@ -17,6 +17,11 @@ extern "C" {
  * workgroup; negative: the library's own bound.  Results agree with the usual path to rounding. */
 int atomo_debug_direct_groups(atomo_ctx* ctx, int spread, int64_t start_ticks);
 
+/* Where the entry-wise encoder has no list of open draws (water levels below the normal range), its workgroups count what they keep
+ * and read the counts of those before them.  loads: how often a workgroup looks for a count before it makes it itself; 0: never;
+ * negative: the library's own bound.  Results are the same. */
+int atomo_debug_entrywise_counts(atomo_ctx* ctx, int loads);
+
 #ifdef __cplusplus
 }
 #endif

@@ -88,10 +88,11 @@ def lib() -> C.CDLL:
         L.atomo_svd_sweeps.argtypes = [vp, vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.c_int]
         L.atomo_last_counters.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
         L.atomo_debug_direct_groups.argtypes = [vp, C.c_int, C.c_int64]
+        L.atomo_debug_entrywise_counts.argtypes = [vp, C.c_int]
         L.atomo_measure_mfma_fp32.argtypes = [vp, C.POINTER(C.c_double), vp]
         L.atomo_profile_enable.argtypes = [vp, C.c_int]
         L.atomo_profile_read.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
-        for name in ("atomo_debug_direct_groups", "atomo_last_counters", "atomo_svd_sweeps", "atomo_profile_enable", "atomo_profile_read", "atomo_create", "atomo_destroy", "atomo_reserve", "atomo_svd_workspace_bytes",
+        for name in ("atomo_debug_direct_groups", "atomo_debug_entrywise_counts", "atomo_last_counters", "atomo_svd_sweeps", "atomo_profile_enable", "atomo_profile_read", "atomo_create", "atomo_destroy", "atomo_reserve", "atomo_svd_workspace_bytes",
                      "atomo_entrywise_workspace_bytes", "atomo_status", "atomo_last_hip_error", "atomo_probabilities",
                      "atomo_encode_svd", "atomo_encode_entrywise", "atomo_encode_entrywise_noalloc", "atomo_encode_lq", "atomo_decode",
                      "atomo_decode_svd_batch", "atomo_apply_svd_batch", "atomo_measure_mfma_fp32"):
@@ -335,6 +336,10 @@ class Context:
     def debug_direct_groups(self, spread: bool = False, start_ticks: int = -1):
         """See atomo_debug.h; the defaults are the library's own behaviour."""
         _check(lib().atomo_debug_direct_groups(self._h, 1 if spread else 0, start_ticks), "atomo_debug_direct_groups")
+
+    def debug_entrywise_counts(self, loads: int = -1):
+        """See atomo_debug.h; the default is the library's own behaviour."""
+        _check(lib().atomo_debug_entrywise_counts(self._h, loads), "atomo_debug_entrywise_counts")
 
     def svd_sweeps(self, n_mats: int, stream: Optional[torch.cuda.Stream] = None) -> List[int]:
         """Jacobi sweeps each matrix of the last atomo_encode_svd took (waits for the stream)."""

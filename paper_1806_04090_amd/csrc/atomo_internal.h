@@ -88,6 +88,7 @@ struct atomo_ctx {
     bool direct_lds = false;       // direct::allow_lds has been called for this context's device
     bool direct_spread = false;            // atomo_debug_direct_groups
     long long direct_start_ticks = -1;     // (negative: the library's own bound)
+    int ew_spins = -1;                     // atomo_debug_entrywise_counts (negative: the library's own bound)
     size_t rowgram_lds = 0;        // dynamic LDS that svd_rowgram has been allowed on this context's device
     atomo::TableCache svd_tables, dec_tables, prob_tables;   // of the SVD encoder, the SVD decoder and atomo_probabilities
     std::vector<char> table_scratch;     // where a call puts its tables together

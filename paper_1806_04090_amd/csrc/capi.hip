@@ -350,6 +350,13 @@ int atomo_debug_direct_groups(atomo_ctx* ctx, int spread, int64_t start_ticks)
     return ATOMO_OK;
 }
 
+int atomo_debug_entrywise_counts(atomo_ctx* ctx, int loads)
+{
+    if (!ctx) return ATOMO_EINVAL;
+    ctx->ew_spins = loads;
+    return ATOMO_OK;
+}
+
 const char* atomo_strerror(int status)
 {
     switch (status) {

@@ -466,7 +466,7 @@ constexpr unsigned int DROPPED = 0x2000u;    // entry-wise: settled, not kept
 constexpr int MAX_GROUP = 64;
 constexpr unsigned int DIRECT_MAX = 65536;
 constexpr unsigned int COUNTED = 0x80000000u;   // in group_kept: the group's final count, by ew_write
-constexpr int SPIN_COUNTED = 1 << 14;        // loads of another workgroup's count, about ten milliseconds: never seen
+constexpr int SPIN_COUNTED = 1 << 14;        // Segments::spins, about ten milliseconds: never seen
 
 // A record whose draw lies between the bounds that level 1 gives for its p.
 struct EwOpen {
@@ -483,6 +483,7 @@ struct Segments {
     int per_group;
     EwOpen* open;                 // [open_max] the first open records, in any order
     unsigned int open_max;
+    int spins;                    // loads of another workgroup's count before it is made anew
 };
 
 // Entry-wise records: values first, then the words.
@@ -988,8 +989,8 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
             for (unsigned int i0 = wave * 64; i0 < blockIdx.x; i0 += 256) {
                 const unsigned int i = min(i0 + lane, blockIdx.x);         // (the own group: counted)
                 unsigned int c = 0u;
-                unsigned long long missing = ~0ull;
-                for (int spins = 0; missing && spins < SPIN_COUNTED; ++spins) {
+                unsigned long long missing = __ballot(i < blockIdx.x);
+                for (int spins = 0; missing && spins < sg.spins; ++spins) {
                     c = __hip_atomic_load(&sg.group_kept[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     missing = __ballot(!(c & COUNTED) && i < blockIdx.x);
                 }
@@ -1482,6 +1483,7 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     l.sg.group_kept = carve.take<unsigned int>((size_t)l.sg.n_groups);
     l.sg.open_max = (unsigned)(n / 4096 + 512);                  // (twice of what is to be expected of a message of all elements)
     l.sg.open = carve.take<EwOpen>(l.sg.open_max);
+    l.sg.spins = SPIN_COUNTED;
     size_t step_bytes = STEP_BYTES;
     if (limit) step_bytes = std::min<size_t>(step_bytes, (limit - carve.off - 256) / ((size_t)l.sg.n_seg * l.steps) & ~(size_t)7);
     l.sg.slot_bytes = (int)(step_bytes * l.steps);
@@ -1527,7 +1529,8 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
         ATOMO_HIP(ctx, hipGetLastError());
         return ATOMO_OK;
     }
-    const Segments& sg = l.sg;
+    Segments sg = l.sg;
+    if (ctx->ew_spins >= 0) sg.spins = ctx->ew_spins;
     const int wgs0 = level0_workgroups(n);
     const unsigned quads = (unsigned)((sg.n_seg + 3) / 4), groups = (unsigned)sg.n_groups;
     const bool long_seg = l.steps == 16;

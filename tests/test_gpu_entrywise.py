@@ -204,6 +204,26 @@ def test_records_that_the_second_search_level_leaves_open(kind, n):
     np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6, atol=2.0 ** -149)        # (a value is rounded to a multiple of that)
 
 
+@pytest.fixture
+def counts():
+    yield ctx().debug_entrywise_counts
+    ctx().debug_entrywise_counts()
+
+
+@pytest.mark.parametrize("n", [16_385, 70_000, 300_001])
+def test_counts_of_other_workgroups_that_do_not_come(counts, n):
+    # 5, 18 and 74 groups, the last of one segment (a wave looks for 64 counts at a time); looked for once, and not at all
+    g = (np.random.default_rng(n).integers(-200, 201, n) * 2.0 ** -149).astype(np.float32)
+    msg, p, status = encode(g, 0.4 * n, 5, 2, capacity=n)
+    h = msg.to_host()
+    assert status == 0 and np.array_equal(h["idx"], oracle.encode_entrywise(g, 0.4 * n, 5, 2, p32=p)["idx"])
+    for loads in (1, 0):
+        counts(loads)
+        msg, _, status = encode(g, 0.4 * n, 5, 2, capacity=n)
+        again = msg.to_host()
+        assert status == 0 and again["count"] == h["count"] and all(np.array_equal(again[k], h[k]) for k in ("idx", "val"))
+
+
 @pytest.mark.parametrize("kind", ["slots", "dense"])                       # segments with and without slots for their candidates
 @pytest.mark.parametrize("level", [5.0e-32, 6.0e-32, 9.7e-32, 1.2e-31])
 def test_water_levels_where_the_scaled_ratio_leaves_the_float_range(level, kind):
