@@ -36,7 +36,7 @@ int ensure_side_streams(atomo_ctx* ctx)
     if (!ctx->side_thin) ATOMO_HIP(ctx, hipStreamCreateWithFlags(&ctx->side_thin, hipStreamNonBlocking));
     hipEvent_t* events[] = {&ctx->ev_fork, &ctx->ev_join, &ctx->ev_join2, &ctx->ev_join_thin};
     for (hipEvent_t* e : events)
-        if (!*e) ATOMO_HIP(ctx, hipEventCreateWithFlags(e, hipEventDisableTiming));
+        if (!*e) ATOMO_HIP(ctx, hipEventCreateWithFlags(e, ON_DEVICE_EVENT));
     return ATOMO_OK;
 }
 

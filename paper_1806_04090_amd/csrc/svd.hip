@@ -954,6 +954,7 @@ __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
         if (m.gs) gs = max(gs, sw); else ds = max(ds, sw);
         if (m.gs) ask = min(ask, m.state[ST_FIRST_ASK] > 0 ? m.state[ST_FIRST_ASK] : never);
     }
+    __threadfence_system();                                      // (the host finds the words behind an event without a fence)
     red[0][threadIdx.x] = gs;
     red[1][threadIdx.x] = ds;
     red[2][threadIdx.x] = ask;
@@ -970,7 +971,9 @@ __device__ inline void sweep_hint(const SvdMat* mats, int n_mats, int* out)
         out[0] = red[0][0];
         out[1] = red[1][0];
         out[3] = red[2][0] == never ? 0 : red[2][0];
+        __threadfence_system();
         out[2] = 1;
+        __threadfence_system();
     }
 }
 
@@ -1358,7 +1361,7 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             ATOMO_HIP(ctx, hipHostGetDevicePointer((void**)&hint->dev, hint->host, 0));
             hint->cap = want;
         }
-        if (!hint->done) ATOMO_HIP(ctx, hipEventCreateWithFlags(&hint->done, hipEventDisableTiming));
+        if (!hint->done) ATOMO_HIP(ctx, hipEventCreateWithFlags(&hint->done, ON_DEVICE_EVENT));
         for (size_t k = 0; k < words; ++k) hint->host[k] = 0;
         hint->sig = sig;
         hint->seq = ++ctx->hint_seq;
@@ -1473,8 +1476,9 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
     for (int j = 0; j < n_mats; ++j) iterate = iterate || !plan.mats[j].skip;
     // (a call of thin matrices alone leaves nothing to learn: its words stay 0 and are not waited for; the event takes 6 us
     // of the stream: the ResNet-18 layers in the reshape of Section 6 91.8 -> 88.0)
+    // Where nothing iterates the words are those of the last kernel of the direct encode, whose completion is the event.
     auto record_hint = [&]() -> int {
-        if (hint && (iterate || any_direct)) {
+        if (hint && iterate) {
             ATOMO_HIP(ctx, hipEventRecord(hint->done, stream));
             hint->pending = true;
         }
@@ -1502,9 +1506,8 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             s_thin = ctx->side_thin;
         }
         ProfScope ps(ctx, ATOMO_K_SVD_THIN, s_thin);
-        thin::launch(plan.thin, (const thin::ThinMat*)((char*)d_tables + at_thin), w_thin_gram, w_thin_long, s, seed, ctx->d_flags,
-                     s_thin);
-        if (beside) ATOMO_HIP(ctx, hipEventRecord(ctx->ev_join_thin, s_thin));
+        ATOMO_HIP(ctx, thin::launch(plan.thin, (const thin::ThinMat*)((char*)d_tables + at_thin), w_thin_gram, w_thin_long, s, seed,
+                                    ctx->d_flags, s_thin, beside ? ctx->ev_join_thin : nullptr));
         return ATOMO_OK;
     };
     if (any_thin && !late && (rc = solve_thin()) != ATOMO_OK) return rc;
@@ -1532,8 +1535,10 @@ int encode_svd(atomo_ctx* ctx, const atomo_mat* mats, int n_mats, double s, uint
             ATOMO_HIP(ctx, hipStreamWaitEvent(s_direct, ctx->ev_fork, 0));
         }
         ProfScope ps(ctx, ATOMO_K_SVD_DIRECT, s_direct);
-        ATOMO_HIP(ctx, direct::launch(plan.direct, dt, s, seed, !iterate && hint ? hint->dev : nullptr, ctx->d_flags, s_direct,
-                                      late ? ctx->ev_fork : nullptr));
+        SweepHint* learns = iterate ? nullptr : hint;
+        ATOMO_HIP(ctx, direct::launch(plan.direct, dt, s, seed, learns ? learns->dev : nullptr, ctx->d_flags, s_direct,
+                                      late ? ctx->ev_fork : nullptr, learns ? learns->done : nullptr));
+        if (learns) learns->pending = true;
         if (join_direct) ATOMO_HIP(ctx, hipEventRecord(join_direct, s_direct));
     }
     if (late && (rc = solve_thin()) != ATOMO_OK) return rc;

@@ -91,9 +91,9 @@ struct DirectTables {
     const svd::Work *gram, *tiles, *gram_wide, *tri, *tri_half, *eig, *vec, *lng;
 };
 // hint_out (may be null, has to be if anything iterates): where the words for the next calls go.  gram_done (may be null) is recorded
-// behind the Gram products; if that fails nothing else is enqueued.
+// behind the Gram products; if that fails nothing else is enqueued.  done (may be null) is recorded behind the last kernel.
 hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
-                  hipEvent_t gram_done = nullptr);
+                  hipEvent_t gram_done, hipEvent_t done);
 // its part in svd_direct_values.hip
 void launch_eigenvalues(const DirectPlan& plan, const DirectTables& t, hipStream_t stream);
 

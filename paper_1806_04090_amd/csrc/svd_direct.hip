@@ -1818,10 +1818,7 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
         static_assert(sizeof(RowAtoms) <= sizeof(us), "made in the place of the vectors");
         __shared__ int broken;
         if (tid >= 256) return;
-        if (tid == 0) {
-            broken = 0;
-            if (hint_out) hint_out[2] = 1;                       // (read after the call has finished)
-        }
+        if (tid == 0) broken = 0;
         __syncthreads();
         for (int j = tid; j < n_mats; j += 256) {
             const int accepted = mats[j].st[DS_ACCEPT];
@@ -1831,7 +1828,12 @@ __global__ __launch_bounds__(512) void direct_long(const DirectMat* mats, const 
             }
             if (hint_out) hint_out[HINT_MATS + mats[j].index] = accepted;
         }
+        if (hint_out) __threadfence_system();                    // (the host finds the words behind an event without a fence)
         __syncthreads();
+        if (hint_out && tid == 0) {
+            hint_out[2] = 1;
+            __threadfence_system();
+        }
         if (broken)
             for (int j = 0; j < n_mats; ++j)
                 if (mats[j].alone && mats[j].st[DS_BROKEN]) row_message(mats[j], s, seed, *(RowAtoms*)us, flags);
@@ -2097,20 +2099,21 @@ void plan_work(DirectPlan& plan)
 }
 
 hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint64_t seed, int* hint_out, int* d_flags, hipStream_t stream,
-                  hipEvent_t gram_done)
+                  hipEvent_t gram_done, hipEvent_t done)
 {
     auto grid = [](const std::vector<Work>& list) { return (unsigned)list.size(); };
+    // (who waits for an event that was not recorded would not wait for this call)
+    const bool wide_last = !plan.gram_wide.empty();
     if (!plan.gram.empty()) {
         direct_gram<<<grid(plan.gram), 256, 0, stream>>>(t.mats, t.gram);
-        direct_gram_sum<<<grid(plan.tiles), 256, 0, stream>>>(t.mats, t.tiles);
+        const hipError_t rc = launch_recorded(wide_last ? nullptr : gram_done, direct_gram_sum, grid(plan.tiles), 256, 0, stream, t.mats, t.tiles);
+        if (rc != hipSuccess) return rc;
     }
-    if (!plan.gram_wide.empty()) {
+    if (wide_last) {
         direct_clear_tickets<<<(unsigned)t.n_mats, 64, 0, stream>>>(t.mats);
-        direct_gram_wide<<<(unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream>>>(t.mats, t.gram_wide, (int)plan.gram_wide.size());
-    }
-    if (gram_done) {
-        const hipError_t rc = hipEventRecord(gram_done, stream);
-        if (rc != hipSuccess) return rc;                         // (who waits for it would not wait for this call)
+        const hipError_t rc = launch_recorded(gram_done, direct_gram_wide, (unsigned)((plan.gram_wide.size() + 3) / 4), 256, 0, stream, t.mats,
+                                              t.gram_wide, (int)plan.gram_wide.size());
+        if (rc != hipSuccess) return rc;
     }
     if (plan.half) direct_tridiagonal_half<<<grid(plan.tri_half), 256, 0, stream>>>(t.mats, t.tri_half, plan.start_ticks);
     if (plan.few) direct_tridiagonal_few<<<grid(plan.tri), 256, 0, stream>>>(t.mats, t.tri, plan.start_ticks);
@@ -2120,8 +2123,7 @@ hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint6
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
     direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
-    direct_long<<<grid(plan.lng) + 1, 512, 0, stream>>>(t.mats, t.lng, t.n_mats, s, (u64)seed, hint_out, d_flags);
-    return hipSuccess;
+    return launch_recorded(done, direct_long, grid(plan.lng) + 1, 512, 0, stream, t.mats, t.lng, t.n_mats, s, (u64)seed, hint_out, d_flags);
 }
 
 }  // namespace direct

@@ -38,8 +38,9 @@ struct ThinPlan {
 // Lays one matrix out (base of `carve` null: sizes only); plan_work lists the work of all.
 void plan_matrix(Carver& carve, ThinMat& m);
 void plan_work(ThinPlan& plan);
-void launch(const ThinPlan& plan, const ThinMat* d_mats, const svd::Work* gram, const svd::Work* lng, double s, uint64_t seed,
-            int* d_flags, hipStream_t stream);
+// done (may be null) is recorded behind the last kernel
+hipError_t launch(const ThinPlan& plan, const ThinMat* d_mats, const svd::Work* gram, const svd::Work* lng, double s, uint64_t seed,
+                  int* d_flags, hipStream_t stream, hipEvent_t done);
 
 }  // namespace thin
 }  // namespace atomo

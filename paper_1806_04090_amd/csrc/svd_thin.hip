@@ -798,14 +798,14 @@ void plan_work(ThinPlan& plan)
     }
 }
 
-void launch(const ThinPlan& plan, const ThinMat* d_mats, const Work* gram, const Work* lng, double s, uint64_t seed, int* d_flags,
-            hipStream_t stream)
+hipError_t launch(const ThinPlan& plan, const ThinMat* d_mats, const Work* gram, const Work* lng, double s, uint64_t seed, int* d_flags,
+                  hipStream_t stream, hipEvent_t done)
 {
     thin_gram<<<(unsigned)plan.gram.size(), 64 * GRAM_WAVES, 0, stream>>>(d_mats, gram);
     thin_solve<<<(unsigned)plan.mats.size(), ST, 0, stream>>>(d_mats, s, (u64)seed, d_flags);
     int most = 0;
     for (const ThinMat& m : plan.mats) most = std::max(most, m.r | 1);
-    thin_long<<<(unsigned)plan.lng.size(), LONG_POS, LONG_POS * most * sizeof(float), stream>>>(d_mats, lng);
+    return launch_recorded(done, thin_long, (unsigned)plan.lng.size(), LONG_POS, LONG_POS * most * sizeof(float), stream, d_mats, lng);
 }
 
 }  // namespace thin

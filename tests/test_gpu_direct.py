@@ -499,3 +499,29 @@ def test_messages_of_more_atoms_than_a_pass_over_the_data_takes(shape, s):
     # eight atoms per pass, summed four at a time: a pass with a second sum, a second pass, a third; the last sum of fewer than four
     assert {5.0: 4 < count <= 8, 8.0: 8 < count <= 16, 17.0: 16 < count <= 24}[s] and count % 4 != 0
     full_parity(G, s, 11, 4, msgs[0], *per[0])
+
+
+def test_a_captured_call_replays_with_its_forks_and_joins():
+    """The events of a call that is captured are records of their own, not the completion of its kernels."""
+    rng = np.random.default_rng(77)
+    shapes = [(64, 27), (130, 700), (10, 512)]
+    mats, other = [[dev(inputs.low_rank_plus_noise(rng, m, n, [1.0, 0.5, 0.25], 0.01)) for m, n in shapes] for _ in range(2)]
+    c, stream = binding.Context(0), torch.cuda.Stream()
+    buffers = [g.clone() for g in mats]
+    with torch.cuda.stream(stream):
+        msgs = binding.atomo_encode_svd(c, buffers, 3.0, 4, 9)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+            binding.atomo_encode_svd(c, buffers, 3.0, 4, 9, msgs=msgs)
+    for given in (other, mats, other):
+        want = binding.atomo_encode_svd(ctx(), given, 3.0, 4, 9)
+        for b, g in zip(buffers, given):
+            b.copy_(g)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(msgs, want):
+            got, ref = a.to_host(), b.to_host()
+            assert np.array_equal(got["idx"], ref["idx"]) and np.array_equal(got["w"], ref["w"])
+            assert np.array_equal(got["U"], ref["U"]) and np.array_equal(got["V"], ref["V"])
