@@ -45,6 +45,7 @@ struct DirectMat {
     double* od;                      // [N] couplings: od[k] between k and k + 1
     double* fact;                    // [N / 16][16][16] triangular factors of the blocks of 16 reflectors
     double* lam;                     // [r] eigenvalues, descending, scaled
+    double* fine;                    // [r] where in its cell of the search each of them is
     double* u;                       // [capacity][r] kept vectors of the shorter side
     unsigned long long* xch;         // exchange slots of the reduction, see Tri
     double* half;                    // [3][384] where one group leaves the reduction to another: the column, and the last step's vectors

@@ -1407,14 +1407,14 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
 // twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and the next round starts
 // from there, until the residual is small enough (KEPT_APART).  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
 // vector and those columns of V; a wave joins in at the first block that reaches its columns.
-// Bound: latency.  One atom of 512 rows: two rounds of 512 steps 21 us, the vectors from them 8, N / 16 blocks with one barrier
+// Bound: latency.  One atom of 512 rows: a round of 512 steps 10 us, the vector from it 4, N / 16 blocks with one barrier
 // each 28: the sums of 16 products over a wave and over the waves, the factor, V from memory (64 KB per block, two blocks
-// on their way while one is worked on).  The ResNet-18 layers 64 us, 64 matrices of 512 rows 143, 64 x 576 17.5; with loads of T and
-// of V that were waited for when they went out, and broadcasts through v_readlane, 90, 196 and 23.
+// on their way while one is worked on).  The ResNet-18 layers 53 us, 64 matrices of 512 rows 132, 64 x 576 13.7; from the middle of
+// the cell, with two rounds for every atom above the noise, 66, 148 and 17.0.
 // Work: matrix, slot.
 constexpr int VMAX = MAX_R;
 constexpr int VEC_THREADS = VMAX / 2;
-constexpr int VEC_ROUNDS = 5;    // two as a rule; three to five for atoms that share a cluster with another kept one
+constexpr int VEC_ROUNDS = 5;    // one as a rule; two to five for atoms that share a cluster with another kept one
 constexpr int FLD = RB + 1;      // row stride of a factor in LDS
 constexpr int VEC_LDS = VMAX * FLD * (int)sizeof(double);
 
@@ -1565,16 +1565,23 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
     const int N = m.nt * TILE, pad = m.pad;
     // its eigenvalue and those of the kept atoms beside it, all three on their way at once (an entry that is not there is
     // not used, whatever it is)
-    double own[3];
+    double own[3], beside[2], lam;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const int at = m.idx[min(max(slot + k - 1, 0), m.capacity - 1)];
-        own[k] = m.lam[min(max(at, 0), n - 1)];
+        const int at = min(max(m.idx[min(max(slot + k - 1, 0), m.capacity - 1)], 0), n - 1);
+        own[k] = m.lam[at];
+        if (k == 1) {
+            lam = m.fine[at];
+            beside[0] = at > 0 ? m.lam[at - 1] : 1e300;
+            beside[1] = at + 1 < n ? m.lam[at + 1] : -1e300;
+        }
     }
-    double lam = own[1];
-    const KeptApart apart(lam, slot > 0 ? own[0] : -1.0, slot + 1 < min(*m.count, m.capacity) ? own[2] : -1.0,
+    const KeptApart apart(own[1], slot > 0 ? own[0] : -1.0, slot + 1 < min(*m.count, m.capacity) ? own[2] : -1.0,
                           4.0 / (double)(1 << LAM_BITS));
+    // A residual of `good` is what the middle of a cell can have and a second round improves to the rounding.  The first round starts from a
+    // better value; it is the last where its residual turns the vector by less than half a unit of fp32, or where the middle would do.
     const double good = 1e-14 * m.lam[0];
+    const double at_once = fabs(lam - own[1]) <= good ? good : fmin(good, 1.5e-8 * fmin(beside[0] - own[1], own[1] - beside[1]));
     const int first = pad & ~15, n_pad = N - first;
     for (int i = tid; i < n_pad; i += nthr) {
         const doublex2 t = ((Global<const doublex2>)global((const double*)m.td))[first + i];
@@ -1618,11 +1625,12 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
         if (wave == 0) {
             const bool last = round == VEC_ROUNDS - 1;
             const int skip = pad - first;
-            if (n <= 64) tw.vector<1>(n, skip, lam, good, apart, last, lane);
-            else if (n <= 128) tw.vector<2>(n, skip, lam, good, apart, last, lane);
-            else if (n <= 256) tw.vector<4>(n, skip, lam, good, apart, last, lane);
-            else if (n <= 512) tw.vector<8>(n, skip, lam, good, apart, last, lane);
-            else tw.vector<VMAX / 64>(n, skip, lam, good, apart, last, lane);
+            const double small = round == 0 ? at_once : good;
+            if (n <= 64) tw.vector<1>(n, skip, lam, small, apart, last, lane);
+            else if (n <= 128) tw.vector<2>(n, skip, lam, small, apart, last, lane);
+            else if (n <= 256) tw.vector<4>(n, skip, lam, small, apart, last, lane);
+            else if (n <= 512) tw.vector<8>(n, skip, lam, small, apart, last, lane);
+            else tw.vector<VMAX / 64>(n, skip, lam, small, apart, last, lane);
         }
         __syncthreads();
         lam = tw.lam;
@@ -1977,6 +1985,7 @@ void plan_matrix(Carver& carve, DirectMat& m)
     m.od = carve.take<double>(N);
     m.fact = carve.take<double>(N * RB);
     m.lam = carve.take<double>(m.r);
+    m.fine = carve.take<double>(m.r);
     m.u = carve.take<double>((size_t)m.capacity * m.r);
     m.xch = carve.take<u64>((size_t)XCH * slot_entries(m.cls));
     m.gate = carve.take<u64>(2);

@@ -218,8 +218,18 @@ __global__ __launch_bounds__(256) void direct_eigenvalues(const DirectMat* mats,
         if (k < lanes) r1 = r_hi, f1 = v_hi, e1 = e_hi;
         uniform = near && (u64)(r1 - r0) * (unsigned)(lanes + 1) > width;        // (not there: eigenvalues too close to each other)
     }
-    const u64 g0 = start + r0;
-    if (l == 0) m.lam[i] = zero ? 0.0 : bits_double(LAM_MIN_BITS + (g0 << LAM_STEP_BITS) + (1ull << (LAM_STEP_BITS - 1)));
+    // The polynomial at the ends of the cell says where in it the eigenvalue is (direct_vectors starts from there), to about 2^-20 of
+    // the cell where others are far; lam itself stays the middle.
+    const u64 cell = LAM_MIN_BITS + ((start + r0) << LAM_STEP_BITS), middle = 1ull << (LAM_STEP_BITS - 1);
+    if (l == 0) {
+        u64 inside = middle;
+        if (r1 - r0 == 1u && (f0 < 0.0f) != (f1 < 0.0f)) {
+            const double there = (double)f0 / ((double)f0 - ldexp((double)f1, e1 - e0));
+            inside = min((u64)(there * (double)(1ull << LAM_STEP_BITS)), (1ull << LAM_STEP_BITS) - 1);
+        }
+        m.lam[i] = zero ? 0.0 : bits_double(cell + middle);
+        m.fine[i] = zero ? 0.0 : bits_double(cell + inside);
+    }
 }
 
 }  // namespace
