@@ -58,6 +58,19 @@ __device__ inline double row_lane(double x)
 {
     return __longlong_as_double((long long)__builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + L, 0xf, 0xf, true));
 }
+// acc +- (what lane L of the lane's row of 16 holds of b) * x in one instruction, rounded once.  b has to come out of `broadcasts`, which
+// stands between the instruction that writes it and the first of these (two wait states; the compiler does not know what is inside).
+__device__ inline void broadcasts(double& b) { asm("s_nop 1" : "+v"(b)); }
+template <int L>
+__device__ inline void add_lane_product(double& acc, double b, double x)
+{
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(b), "v"(x), "n"(L));
+}
+template <int L>
+__device__ inline void sub_lane_product(double& acc, double b, double x)
+{
+    asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(b), "v"(x), "n"(L));
+}
 // f(integral_constant 0) .. f(integral_constant 15)
 template <int L = 0, typename F>
 __device__ inline void for_lanes(F&& f)

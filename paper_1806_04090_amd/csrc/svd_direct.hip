@@ -1407,73 +1407,71 @@ __global__ __launch_bounds__(256) void direct_select(const DirectMat* mats, doub
 // twisted where the two meet with the smallest pivot; the Rayleigh quotient corrects lam, and the next round starts
 // from there, until the residual is small enough (KEPT_APART).  Then its image under H, a block of 16 reflectors at a time: a thread owns two neighbouring entries of the
 // vector and those columns of V; a wave joins in at the first block that reaches its columns.
-// Bound: latency.  One atom of 512 rows: a round of 512 steps 10 us, the vector from it 4, N / 16 blocks with one barrier
-// each 28: the sums of 16 products over a wave and over the waves, the factor, V from memory (64 KB per block, two blocks
-// on their way while one is worked on).  The ResNet-18 layers 53 us, 64 matrices of 512 rows 132, 64 x 576 13.7; from the middle of
-// the cell, with two rounds for every atom above the noise, 66, 148 and 17.0.
+// Bound: latency.  One atom of 512 rows: a round of 512 steps 8 us, the vector from it 4, N / 16 blocks with one barrier
+// each 27: the sums of 16 products over a wave and over the waves, the factor, V from memory (64 KB per block, two blocks
+// on their way while one is worked on).  The ResNet-18 layers 51 us, 64 matrices of 512 rows 77, 64 x 576 12.6; from the middle of
+// the cell, with two rounds for every atom above the noise, 66, 148 and 17.0; with one round and one workgroup per compute unit 53, 132 and 13.7.
 // Work: matrix, slot.
 constexpr int VMAX = MAX_R;
 constexpr int VEC_THREADS = VMAX / 2;
 constexpr int VEC_ROUNDS = 5;    // one as a rule; two to five for atoms that share a cluster with another kept one
 constexpr int FLD = RB + 1;      // row stride of a factor in LDS
-constexpr int VEC_LDS = VMAX * FLD * (int)sizeof(double);
 
+// What a round leaves.
+struct TwistVector {
+    double X[VMAX];                          // the vector
+    double lam, scale;                       // the Rayleigh quotient; what X is to be multiplied by, 0: another round, negative: not accepted
+};
 // What a workgroup works out its eigenvector of T from.
 struct Twist {
-    // T from the top, padding in front, and from the bottom, padding behind (two steps' worth of eight: loads run ahead)
+    // T from the top, padding in front, and from the bottom, padding behind (one turn of sixteen: loads run ahead)
     double2 T[2][VMAX + 16];
     double E[VMAX + 1];                      // couplings of the r rows: E[i] between i - 1 and i, zero at both ends
     // characteristic polynomials of the leading blocks ([0], in units of index + 1) and of the trailing ones ([1]), every
     // pair of neighbours in one scale except where `B` holds the first of the pair in the scale of the second
     double P[2][VMAX + 17], B[2][VMAX / 8 + 2];
-    double X[VMAX];                          // the vector
-    double lam, scale;                       // the Rayleigh quotient; what X is to be multiplied by, 0: another round, negative: not accepted
 
-    // P and B of one direction, by one lane: three instructions per step, eight entries of T on their way while eight are
-    // worked on (75 cycles per step when they were waited for, 48 now: the LDS traffic of one lane)
-    __device__ inline void polynomials(int dir, int n_pad, double lam)
+    // P and B of one direction, by the first row of 16 lanes, all with the same polynomials: lane j has entry j of sixteen of T, from where
+    // it is broadcast; the next sixteen are on their way.  Three instructions per step, broadcasts within the products
+    // (64 matrices of 512 rows 86 -> 77 us, the ResNet-18 layers 53.5 -> 51.2 against one lane that read every entry from LDS).
+    __device__ inline void polynomials(int dir, int n_pad, double lam, int lane)
     {
-        const double2* t = T[dir];
+        const double2* t = T[dir] + lane;
         double* out = P[dir];
         double* bound = B[dir];
         double p0 = 0.0, p1 = 1.0;
         out[0] = 1.0;
-        auto eight = [&](const double2 (&e)[8], int i) {
-            double step[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                step[u] = fma(e[u].y - lam, p1, -(e[u].x * p0));
-                p0 = p1;
-                p1 = step[u];
-            }
-            // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
-            const unsigned x = max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u);
-            const double scale = mk64(0u, 0x7fd00000u - x);
-            p0 *= scale;
-            p1 *= scale;
-            step[7] = p1;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) out[i + 1 + u] = step[u];
-            bound[i >> 3] = p0;
-        };
-        double2 a[8], b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = t[u];
+        double2 next = *t;
         for (int i = 0; i < n_pad; i += 16) {
+            double d = next.y - lam, e = next.x;
+            next = t[i + 16];
+            broadcasts(d);
+            broadcasts(e);
+            double step[16];
+            for_lanes([&](auto u) {
+                constexpr int U = decltype(u)::value;
+                double p2 = 0.0;
+                sub_lane_product<U>(p2, e, p0);
+                add_lane_product<U>(p2, d, p1);
+                step[U] = p1 = (p0 = p1, p2);
+                if constexpr (U % 8 == 7) {
+                    // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
+                    const unsigned x = max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u);
+                    const double scale = mk64(0u, 0x7fd00000u - x);
+                    p0 *= scale;
+                    p1 *= scale;
+                    step[U] = p1;
+                    bound[(i + U) >> 3] = p0;
+                }
+            });
 #pragma unroll
-            for (int u = 0; u < 8; ++u) b[u] = t[i + 8 + u];
-            __builtin_amdgcn_sched_barrier(0);
-            eight(a, i);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = t[i + 16 + u];
-            __builtin_amdgcn_sched_barrier(0);
-            eight(b, i + 8);
+            for (int u = 0; u < 16; ++u) out[i + 1 + u] = step[u];
         }
     }
 
     // The vector, by one wave: lane l the entries l per .. of it, per <= PER.
     template <int PER>
-    __device__ inline void vector(int n, int skip, double lambda, double good, const KeptApart& apart, bool last, int lane)
+    __device__ inline void vector(TwistVector& to, int n, int skip, double lambda, double good, const KeptApart& apart, bool last, int lane) const
     {
         // pivots: top = P_{i+1} / P_i, bottom likewise; where they meet with the smallest pivot
         const int per = (n + 63) / 64, i0 = min(n, lane * per), i1 = min(n, i0 + per);
@@ -1535,7 +1533,7 @@ struct Twist {
         for (int u = 0; u < PER; ++u) {
             const bool in = i0 + u < i1;
             const double z2 = in ? x[u] * x[u] : 0.0;
-            if (in) X[i0 + u] = x[u];
+            if (in) to.X[i0 + u] = x[u];
             sq += z2;
             weight = fma(z2, fabs(d[u]) + (fabs(e_up[u]) + fabs(e_dn[u])), weight);
         }
@@ -1545,17 +1543,24 @@ struct Twist {
         // over: the residual is small enough, or it never will be (the eigenvalue was not separated from that of
         // another kept atom, or the factorisation broke down)
         if (lane == 0) {
-            lam = lambda;
-            scale = res <= (last ? 100.0 * good : good) && apart.vector(res, weight, lambda) ? reciprocal(size)
+            to.lam = lambda;
+            to.scale = res <= (last ? 100.0 * good : good) && apart.vector(res, weight, lambda) ? reciprocal(size)
                     : last || !apart.possible ? -1.0 : 0.0;
         }
     }
 };
 
+// The factors take the place of T and its polynomials, which the rounds have done with by then: 512 rows are 76 KB, two workgroups on a
+// compute unit, for calls that have more atoms than compute units (64 matrices of 512 rows, 256 atoms on average, 132 -> 86 us; with the
+// factors beside T, asked for at the start, the ResNet-18 layers took 1 us less, 601 rows 1.5).
+constexpr int VEC_LDS_MAX = VMAX * FLD * (int)sizeof(double);
+static_assert(VEC_LDS_MAX >= (int)sizeof(Twist), "the larger of the two");
+inline size_t vec_lds(int max_nt) { return std::max((size_t)max_nt * TILE * FLD * sizeof(double), sizeof(Twist)); }
 __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat* mats, const Work* work)
 {
-    extern __shared__ double fact[];
-    __shared__ Twist tw;
+    extern __shared__ __attribute__((aligned(16))) double fact[];
+    Twist& tw = *(Twist*)fact;
+    __shared__ TwistVector tv;
     __shared__ double part[2][VEC_THREADS / 64][RB], red[VEC_THREADS / 64];
     const Work wk = work[blockIdx.x];
     const DirectMat& m = mats[wk.mat];
@@ -1597,44 +1602,26 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
     }
     if (tid == 0) tw.T[1][0].x = 0.0;
     __syncthreads();
-    // the factors, wanted behind the rounds, by the waves that have nothing else to do
-    if (wave >= 2 || nw <= 2) {
-        const Global<const doublex2> in = (Global<const doublex2>)global((const double*)m.fact);
-        const int self = nw <= 2 ? tid : tid - 128, step = nw <= 2 ? nthr : nthr - 128;
-        for (int i0 = self; i0 < N * RB / 2; i0 += 8 * step) {
-            doublex2 x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = in[min(i0 + u * step, N * RB / 2 - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * step;
-                if (i < N * RB / 2) {
-                    fact[i / 8 * FLD + 2 * (i & 7)] = x[u].x;
-                    fact[i / 8 * FLD + 2 * (i & 7) + 1] = x[u].y;
-                }
-            }
-        }
-    }
     for (int round = 0; round < VEC_ROUNDS; ++round) {
         // wave 0 the leading blocks, wave 1 the trailing ones (a workgroup of one wave: both)
-        if (lane == 0 && wave < 2) {
-            tw.polynomials(wave, n_pad, lam);
-            if (nw == 1) tw.polynomials(1, n_pad, lam);
+        if (lane < 16 && wave < 2) {
+            tw.polynomials(wave, n_pad, lam, lane);
+            if (nw == 1) tw.polynomials(1, n_pad, lam, lane);
         }
         __syncthreads();
         if (wave == 0) {
             const bool last = round == VEC_ROUNDS - 1;
             const int skip = pad - first;
             const double small = round == 0 ? at_once : good;
-            if (n <= 64) tw.vector<1>(n, skip, lam, small, apart, last, lane);
-            else if (n <= 128) tw.vector<2>(n, skip, lam, small, apart, last, lane);
-            else if (n <= 256) tw.vector<4>(n, skip, lam, small, apart, last, lane);
-            else if (n <= 512) tw.vector<8>(n, skip, lam, small, apart, last, lane);
-            else tw.vector<VMAX / 64>(n, skip, lam, small, apart, last, lane);
+            if (n <= 64) tw.vector<1>(tv, n, skip, lam, small, apart, last, lane);
+            else if (n <= 128) tw.vector<2>(tv, n, skip, lam, small, apart, last, lane);
+            else if (n <= 256) tw.vector<4>(tv, n, skip, lam, small, apart, last, lane);
+            else if (n <= 512) tw.vector<8>(tv, n, skip, lam, small, apart, last, lane);
+            else tw.vector<VMAX / 64>(tv, n, skip, lam, small, apart, last, lane);
         }
         __syncthreads();
-        lam = tw.lam;
-        if (tw.scale != 0.0) break;
+        lam = tv.lam;
+        if (tv.scale != 0.0) break;
         __syncthreads();
     }
     // back through H
@@ -1647,13 +1634,13 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
 #pragma unroll
         for (int j = 0; j < RB; ++j) at.v[j] = *(Global<const doublex2>)(row + (size_t)j * N * 8 + offset);
     };
-    const double scale = tw.scale;
+    const double scale = tv.scale;
     if (tid == 0 && !(scale > 0.0)) {
         m.st[DS_ACCEPT] = 0;
         m.st[DS_BROKEN] = 1;
     }
-    double y0 = c0 >= pad && c0 < N ? tw.X[c0 - pad] * scale : 0.0;
-    double y1 = c0 + 1 >= pad && c0 < N ? tw.X[c0 + 1 - pad] * scale : 0.0;
+    double y0 = c0 >= pad && c0 < N ? tv.X[c0 - pad] * scale : 0.0;
+    double y1 = c0 + 1 >= pad && c0 < N ? tv.X[c0 + 1 - pad] * scale : 0.0;
     const int last = (N - 3) / RB, first_block = pad / RB;
     auto apply = [&](int b, const Block& at) {
         double prod[RB];
@@ -1671,17 +1658,17 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
 #pragma unroll
         for (int w = 0; w < VEC_THREADS / 64; ++w) sum += w < nw ? pt[w][lane & 15] : 0.0;
         double t = 0.0, t_odd = 0.0;
+        broadcasts(sum);
         for_lanes([&](auto j) {
             constexpr int J = decltype(j)::value;
-            double& x = J & 1 ? t_odd : t;
-            x = fma(f[J], row_lane<J>(sum), x);
+            add_lane_product<J>(J & 1 ? t_odd : t, sum, f[J]);
         });
         t += t_odd;
+        broadcasts(t);
         for_lanes([&](auto j) {
             constexpr int J = decltype(j)::value;
-            const double tj = row_lane<J>(t);
-            y0 = fma(-at.v[J].x, tj, y0);
-            y1 = fma(-at.v[J].y, tj, y1);
+            sub_lane_product<J>(y0, t, at.v[J].x);
+            sub_lane_product<J>(y1, t, at.v[J].y);
         });
         if (c0 >= N) y0 = y1 = 0.0;
     };
@@ -1691,6 +1678,20 @@ __global__ __launch_bounds__(VEC_THREADS, 1) void direct_vectors(const DirectMat
         Block a, c, e;
         fetch(start, a);
         fetch(start - 1, c);
+        {
+            constexpr int PER = RB;                              // pairs of entries of the factors per thread: N RB / 2, N / 2 threads
+            const Global<const doublex2> in = (Global<const doublex2>)global((const double*)m.fact);
+            doublex2 x[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) x[u] = in[min(tid + u * nthr, N * RB / 2 - 1)];
+            __builtin_amdgcn_sched_barrier(0);                   // (all of them on their way at once, beside the blocks)
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = min(tid + u * nthr, N * RB / 2 - 1);
+                fact[i / 8 * FLD + 2 * (i & 7)] = x[u].x;
+                fact[i / 8 * FLD + 2 * (i & 7) + 1] = x[u].y;
+            }
+        }
         int b = last;
         for (; b > start; --b) {
             if (lane < RB) part[b & 1][wave][lane] = 0.0;
@@ -1958,7 +1959,7 @@ int class_of(int r)
 
 hipError_t allow_lds()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(direct_vectors), hipFuncAttributeMaxDynamicSharedMemorySize, VEC_LDS);
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(direct_vectors), hipFuncAttributeMaxDynamicSharedMemorySize, VEC_LDS_MAX);
 }
 
 bool eligible(int r) { return r > svd::THIN_R && r <= MAX_R; }
@@ -2026,6 +2027,8 @@ void plan_work(DirectPlan& plan)
         for (int k = 0; k < m.capacity; ++k) plan.vec.push_back(Work{j, k, 0, 0});
         for (int p = 0; p < (m.M + LONG_COLS - 1) / LONG_COLS; ++p) plan.lng.push_back(Work{j, p, 0, 0});
     }
+    // (the slots that are filled as a rule are the first of each matrix, and the workgroups of the others are done at once)
+    std::stable_sort(plan.vec.begin(), plan.vec.end(), [](const Work& a, const Work& b) { return a.a < b.a; });
     plan.n_eig = plan.eig.size();
     plan.eig.insert(plan.eig.end(), factors.begin(), factors.end());
     // us per encode, by direct_gram / by direct_gram_wide: 512 x 4608 (chunks of 576 columns) with 4032 items 1133 / 1140, 6048
@@ -2131,7 +2134,7 @@ hipError_t launch(const DirectPlan& plan, const DirectTables& t, double s, uint6
     launch_eigenvalues(plan, t, stream);
     direct_select<<<(unsigned)t.n_mats, 256, 0, stream>>>(t.mats, s, (u64)seed, d_flags);
     const unsigned vec_threads = (unsigned)align_up((size_t)32 * plan.max_nt, 64);
-    direct_vectors<<<grid(plan.vec), vec_threads, (size_t)plan.max_nt * TILE * FLD * sizeof(double), stream>>>(t.mats, t.vec);
+    direct_vectors<<<grid(plan.vec), vec_threads, vec_lds(plan.max_nt), stream>>>(t.mats, t.vec);
     return launch_recorded(done, direct_long, grid(plan.lng) + 1, 512, 0, stream, t.mats, t.lng, t.n_mats, s, (u64)seed, hint_out, d_flags);
 }
 
