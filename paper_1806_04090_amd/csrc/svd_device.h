@@ -58,9 +58,25 @@ __device__ inline double row_lane(double x)
 {
     return __longlong_as_double((long long)__builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + L, 0xf, 0xf, true));
 }
-// acc +- (what lane L of the lane's row of 16 holds of b) * x in one instruction, rounded once.  b has to come out of `broadcasts`, which
-// stands between the instruction that writes it and the first of these (two wait states; the compiler does not know what is inside).
-__device__ inline void broadcasts(double& b) { asm("s_nop 1" : "+v"(b)); }
+// ... in the fours of lanes of BANKS, and `other` in the rest
+template <int L, int BANKS>
+__device__ inline double row_lane(double other, double x)
+{
+    return __longlong_as_double((long long)__builtin_amdgcn_update_dpp(__double_as_longlong(other), __double_as_longlong(x), 0x150 + L, 0xf, BANKS, false));
+}
+// The value is worked out where this stands and not where it is used first (behind a wait, as a rule).
+__device__ inline void here(double& x) { asm volatile("" : "+v"(x)); }
+// acc +- (what lane L of the lane's row of 16 holds of b) * x in one instruction, rounded once.  b has to come out of `broadcasts`: between
+// the instruction that writes it and the first of these are two wait states, and the compiler does not know what is inside (the built
+// code is looked over in a test).
+__device__ inline void wait_for_broadcasts() { asm volatile("s_nop 1"); }
+template <typename... D>
+__device__ inline void broadcasts(D&... b)
+{
+    (here(b), ...);
+    wait_for_broadcasts();
+    (here(b), ...);
+}
 template <int L>
 __device__ inline void add_lane_product(double& acc, double b, double x)
 {

@@ -87,8 +87,6 @@ __device__ inline double lane_sums(const double (&v)[K], int lane)
     return f[0];
 }
 __host__ __device__ constexpr int reverse6(int l) { return (l & 1) << 5 | (l & 2) << 3 | (l & 4) << 1 | (l & 8) >> 1 | (l & 16) >> 3 | (l & 32) >> 5; }
-// The value is worked out where this stands and not where it is used first (behind a wait, as a rule).
-__device__ inline void here(double& x) { asm volatile("" : "+v"(x)); }
 __device__ inline int sum_slot(int lane) { return (lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2; }
 
 // ------------------------------------------------------------------------------------------------
@@ -465,7 +463,9 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // last step's update, whose share is a product with two sums of y (v_i (w y) + w_i (v y)).  The update itself, the reflector and the
 // row of the next step (handed over a step early, the readers add the update that it lacks) come behind it, while the entries
 // travel; the loads that look for them go out in the middle of that work (a load of 512 bytes by every wave takes 250 cycles, four of
-// them 460, whether the entries are there or not; a look that is too early costs a second one).  The ResNet-18 layers in 468 us with
+// them 460, whether the entries are there or not; a look that is too early costs a second one, at the entries of A y alone: the row has
+// been there for a step.  One step in three has one; with the row looked at again the ResNet-18 layers 467 us, 601 x 1237 and smaller ones 609,
+// without 452 and 594).  The ResNet-18 layers in 468 us with
 // the look there, 495 behind the reflector's vector, 575 in front of the update; two looks on their way at once 485.
 // An entry is one 8-byte store whose two lowest mantissa bits carry a tag that tells it from the one that lay there before: a reader
 // knows from the value that it is the one of this step, no flag and no second round trip.  Two slots for A y by step parity: a wave
@@ -480,8 +480,8 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
 // Bound: what a wave does for itself in a step, one wave on every SIMD: without the waits for the others a step takes as long.  448
-// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 446 us in all, 452 with the loop where the
-// compiler puts it (517 -> 468, on another card, without a chain of branches and v_readlane for what a vector holds at the wave's rows,
+// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 446 us in all (by one card; by another 467, and 452 with
+// the second look as it is), 452 with the loop where the compiler puts it (517 -> 468, on another card, without a chain of branches and v_readlane for what a vector holds at the wave's rows,
 // a reduction of its own for the norm, and the reflector behind the update; 800 of 3500 cycles).  Rows and columns split between the
 // waves of a workgroup, two instead of eight entries of a vector per lane: 566, for a second barrier and sums of sixteen rows.  Four
 // groups per die, two waves on every SIMD: the issue of the vectors that every wave works out for itself (direct_tridiagonal_few).
@@ -546,11 +546,9 @@ struct Tri {
     static constexpr int TURN = W < 64 ? W : 64;                 // rows that the waves hand over in turn
     static constexpr bool FEW = W == 4 * FEW_WGS;
     static_assert(W * R == CN, "every row has a wave");
-    // A phase whose part of the matrix, 12 x 6 entries per lane, leaves no registers for the last step's vectors at the rows of all slots,
-    // nor for the address of a kept vector (up to 84 bytes per lane in scratch memory; 64 x (512 x 4608) 3197 -> 3152 us without).
-    // Four slots at a time where that is not needed lengthen the step: us per encode, n = 1024, in phases of up to 64 entries too / not:
-    // 17 of 320 rows 515 / 509, 20 of 256 398 / 392, ten of 512 808 / 796.
-    static constexpr bool tight(int p) { return (R - 64 * p / W) * (C - p) > 64; }
+    // Measured, and not explained by the number of instructions where a wave has few rows: ResNet-18, four rows, 458 us with KEEP and 476
+    // without (the same look); 64 x (512 x 4608), eight and twelve rows, bound by issue, 639 + 627 and 617 + 602.
+    static constexpr bool KEEP = R <= 5;
     double a[R][C];
     // Column k; the last step's vectors, which the rows have still to be updated with.  [C]: their entries at the wave's rows, row
     // slot t in lane t of every row of 16 lanes, from where they are broadcast.
@@ -605,49 +603,59 @@ struct Tri {
     __device__ inline Global<u64> slot_c(unsigned step) const { return slots + (2 + (step & 3)) * CN; }
     static __device__ inline unsigned tag_p(unsigned step) { return step & 3; }
     static __device__ inline unsigned tag_c(unsigned step) { return (step >> 2) + 1 & 3; }
-    // the last step's vectors at row slot T; tight: of the slots from T0 on, four are under way at a time
-    template <int P, int T0, int T>
-    __device__ __forceinline__ void entries(double& wr, double& vr)
+    // f(integral_constant T) for the row slots from T0 on
+    template <int T0, typename F>
+    static __device__ __forceinline__ void for_slots(F&& f)
     {
-        if (tight(P) && (T - T0) % 4 == 0) {
-            here(wv[C]);
-            here(v[C]);
+        if constexpr (T0 < R) {
+            f(std::integral_constant<int, T0>());
+            for_slots<T0 + 1>(f);
         }
-        wr = row_lane<T>(wv[C]);
-        vr = row_lane<T>(v[C]);
     }
-    // the entries of A y at the wave's rows
-    template <int P, int T0, int T = T0, int K>
-    __device__ __forceinline__ void products(const double (&y)[C + 1], double vy, double wy, double (&sum)[K], double (&wr)[R], double (&vr)[R])
+    // The entries of A y at the wave's rows, and the update.  KEEP: what the last step's vectors are at those rows stays in registers from the
+    // one to the other.  Else it is broadcast inside the products; one right behind the product that it adds to would wait for that, and the
+    // compiler does not know: the two of an entry stand apart.
+    template <int P, int T0, int K>
+    __device__ __forceinline__ void products(const double (&y)[C + 1], double vy, double wy, double (&sum)[K], double (&wr)[R], double (&vr)[R]) const
     {
-        if constexpr (T < R) {
-            entries<P, T0, T>(wr[T], vr[T]);
+        for_slots<T0>([&](auto t) {
+            constexpr int T = decltype(t)::value;
             double s = a[T][P] * y[P];
 #pragma unroll
             for (int c = P + 1; c < C; ++c) s = fma(a[T][c], y[c], s);
-            sum[T - T0] = fma(-wr[T], vy, fma(-vr[T], wy, s));
-            if (tight(P)) here(sum[T - T0]);
-            products<P, T0, T + 1>(y, vy, wy, sum, wr, vr);
+            if constexpr (KEEP) {
+                wr[T] = row_lane<T>(wv[C]);
+                vr[T] = row_lane<T>(v[C]);
+                s = fma(-wr[T], vy, fma(-vr[T], wy, s));
+            }
+            sum[T - T0] = s;
+        });
+        if constexpr (!KEEP) {
+            for_slots<T0>([&](auto t) { sub_lane_product<decltype(t)::value>(sum[t - T0], v[C], wy); });
+            for_slots<T0>([&](auto t) { sub_lane_product<decltype(t)::value>(sum[t - T0], wv[C], vy); });
         }
     }
-    template <int P>
-    __device__ __forceinline__ void update_row(double (&row)[C], double wr, double vr) const
+    template <int P, int T0>
+    __device__ __forceinline__ void update(const double (&wr)[R], const double (&vr)[R])
     {
+        for_slots<T0>([&](auto t) {
+            constexpr int T = decltype(t)::value;
+            if constexpr (KEEP) {
 #pragma unroll
-        for (int c = P; c < C; ++c) {
-            row[c] = fma(-wr, v[c], fma(-vr, wv[c], row[c]));
-            here(row[c]);
-        }
-    }
-    template <int P, int T0, int T = T0>
-    __device__ __forceinline__ void update()
-    {
-        if constexpr (T < R) {
-            double wr, vr;
-            entries<P, T0, T>(wr, vr);
-            update_row<P>(a[T], wr, vr);
-            update<P, T0, T + 1>();
-        }
+                for (int c = P; c < C; ++c) {
+                    a[T][c] = fma(-wr[T], v[c], fma(-vr[T], wv[c], a[T][c]));
+                    here(a[T][c]);
+                }
+            } else {
+#pragma unroll
+                for (int c = P; c < C; ++c) sub_lane_product<T>(a[T][c], v[C], wv[c]);
+#pragma unroll
+                for (int c = P; c < C; ++c) {
+                    sub_lane_product<T>(a[T][c], wv[C], v[c]);
+                    here(a[T][c]);
+                }
+            }
+        });
     }
 
     // step k - 1, every wave of the workgroup a part; with zeros in what is finished of its vector (that is read in pairs of chunks)
@@ -655,14 +663,12 @@ struct Tri {
     __device__ __forceinline__ void keep(int k, const StepStore& store) const
     {
         const int kk = k - 1 - off;
-        constexpr bool APART = FEW && tight(P);
-        const Global<double> row = store.refl + (size_t)kk * store.N - off + (APART ? 0 : lane);
-        const unsigned at = APART ? lane : 0;                    // (no address to keep in registers)
+        const Global<double> row = store.refl + (size_t)kk * store.N - off + lane;
 #pragma unroll
         for (int c = P > 1 ? P - 2 : 0; c < C; ++c)
-            if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[at + 64u * c] = c < P ? 0.0 : v[c < P ? P : c];
+            if ((c & 3) == wave && (c >= P || 64 * c >= off)) row[64u * c] = c < P ? 0.0 : v[c < P ? P : c];
         if constexpr (FEW && P <= 1) {                           // (the chunk in front, another group's)
-            if (off < 0 && wave == 3) (row - 64)[at] = 0.0;
+            if (off < 0 && wave == 3) *(row - 64) = 0.0;
         }
         if (wave == 3 && lane == 0) store.put(kk, tau, diagonal, beta);
     }
@@ -696,7 +702,8 @@ struct Tri {
 #pragma unroll
                 for (int j = 0; j < L; ++j) cu[j] = __hip_atomic_load(at_byte(slot_c(step), at[j]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             };
-            double y[C + 1], sum[K], vy = 0.0, wy = 0.0, sq = 0.0;
+            double y[C + 1], sum[K], wr[R], vr[R], vy = 0.0, wy = 0.0, sq = 0.0;
+            if constexpr (!KEEP) broadcasts(v[C], wv[C]);
 #pragma unroll
             for (int c = P; c < C; ++c) {
                 y[c] = c > PN || lane + 64 * c > k1 ? x[c] : 0.0;
@@ -704,7 +711,6 @@ struct Tri {
                 wy = fma(wv[c], y[c], wy);
                 sq = fma(y[c], y[c], sq);
             }
-            double wr[R], vr[R];
             products<P, T0>(y, vy, wy, sum, wr, vr);
             sum[K - 1] = sq;
             const double sums = lane_sums<K>(sum, lane);
@@ -721,12 +727,7 @@ struct Tri {
             double v0;
             householder(alpha, sig2, beta, v0);
             tau = householder_tau(sig2, v0);
-            if constexpr (R > 5) {                               // (broadcast once more: no registers left to keep them)
-                update<P, T0>();
-            } else {
-#pragma unroll
-                for (int t = T0; t < R; ++t) update_row<P>(a[t], wr[t], vr[t]);
-            }
+            update<P, T0>(wr, vr);
             here(v0);
             here(tau);
             if (__builtin_expect(k == row_turn, 0)) {
@@ -760,6 +761,7 @@ struct Tri {
                 return __all((other & 3u) == 0u);
             };
             if (__builtin_expect(!ready(), 0)) {
+                look_p();                                        // (the row of this step is there already, as a rule)
                 for (int spins = 0; !ready(); look_p(), look_c())
                     if (++spins > spin_limit) {                  // (once: the steps after it wait for nothing)
                         spin_limit = 0;
@@ -851,7 +853,10 @@ struct Tri {
         constexpr int T0 = 64 * (LAST + 1) / W;
         if (k == keep_turn) keep<LAST + 1>(k, store);
         if constexpr (LEFT == TAIL) {
-            update<LAST + 1, T0>();
+            double wr[R], vr[R];
+            if constexpr (!KEEP) broadcasts(v[C], wv[C]);
+            else for_slots<T0>([&](auto t) { wr[t] = row_lane<decltype(t)::value>(wv[C]), vr[t] = row_lane<decltype(t)::value>(v[C]); });
+            update<LAST + 1, T0>(wr, vr);
         } else if (w == 0) {
 #pragma unroll
             for (int c = LAST + 1; c < C; ++c) {
@@ -889,7 +894,7 @@ struct Tri {
 // All waves do the same in a step, but for the three numbers that one of them keeps: the column is handed over by the lanes that have
 // it, one of every row, and every row of lanes keeps the vector's entries at its rows.
 // Bound: a step of 64 rows is a chain of about 250 instructions with one wave on every SIMD, 0.53 us; at 128 rows it is the issue of
-// 500, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix takes 36.5 us (39.5 with a wave in turn that handed the column
+// 500, 192 of them the fma of the matrix, 1.1 us.  A 64-row matrix takes 36.5 us (37.2 with a move for every broadcast; 39.5 with a wave in turn that handed the column
 // over and one that kept the vector, and with loads for rows that are not there).  What a group leaves is worked off by one compute
 // unit instead of 16 or 32.
 constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124;
@@ -940,7 +945,7 @@ struct TriOne {
     int lane, wave, col, row;        // column and row of slot 0
     int off, first;                  // row i here is row i - off of the matrix; the first that is reduced here
     int k_first;                     // the first step
-    bool keeps;                      // this lane keeps an entry of every vector, that of row 16 (lane mod 16) + `row`
+    bool keeps;                      // this lane keeps an entry of every vector, see kept_entry
     Global<double> kept_row;         // where its entry of the last step's belongs
 
     template <int S>
@@ -955,13 +960,24 @@ struct TriOne {
             const int k1 = k + 1;
             const bool next = S + 1 < TS && k1 == 16 * S1;       // row k + 1 is the first of slot S + 1
             Step* sh = shared + (k & 1);
-            double sum[L], y[TS], vr[TS], wr[TS], sq = 0.0;
+            double sum[L], y[TS], sq = 0.0;
 #pragma unroll
             for (int s = S; s < TS; ++s) {
-                vr[s] = row_lane<0>(v[s]);
-                wr[s] = row_lane<0>(wv[s]);
+                here(v[s]);
+                here(wv[s]);
+            }
+            wait_for_broadcasts();
 #pragma unroll
-                for (int b = S; b < TS; ++b) a[s][b] = fma(-wr[s], v[b], fma(-vr[s], wv[b], a[s][b]));
+            for (int s = S; s < TS; ++s) {
+                here(v[s]);
+                here(wv[s]);
+            }
+#pragma unroll
+            for (int s = S; s < TS; ++s) {
+#pragma unroll
+                for (int b = S; b < TS; ++b) sub_lane_product<0>(a[s][b], v[s], wv[b]);
+#pragma unroll
+                for (int b = S; b < TS; ++b) sub_lane_product<0>(a[s][b], wv[s], v[b]);
             }
             // column k + 1 of the matrix: of every row the lane that has that column
             if (col == (k1 & 15)) {
@@ -987,7 +1003,7 @@ struct TriOne {
             }
             sh->at[sum_at].x = row_sums<L>(sum, lane);
             // the last step's vector, for the way back
-            const double entry = kept_entry<S>(vr);
+            const double entry = kept_entry<S>();
             if (keeps && k > k_first) *kept_row = entry;
             kept_row += k > k_first ? store.N : 0;
 #pragma unroll
@@ -1016,14 +1032,22 @@ struct TriOne {
             }
         }
     }
-    // entries at the thread's rows, that of row slot s in lane s of the row of lanes; zeros in what is finished
-    template <int S>
-    __device__ inline double kept_entry(const double (&vr)[TS]) const
+    // entries of v at the thread's rows: that of row slot 4 h + b in lane 4 b + h of the row of lanes, where a broadcast can be let in by
+    // fours of lanes; zeros in what is finished
+    template <int S, int H, int B = 0>
+    __device__ __forceinline__ void let_in(double& e) const
     {
-        double e = 0.0;
-#pragma unroll
-        for (int s = S; s < TS; ++s) e = (lane & 15) == s ? vr[s] : e;
-        return e;
+        if constexpr (4 * H + B >= S) e = row_lane<0, 1 << B>(e, v[4 * H + B]);
+        if constexpr (B < 3) let_in<S, H, B + 1>(e);
+    }
+    template <int S>
+    __device__ inline double kept_entry() const
+    {
+        static_assert(TS == 8, "two fours of slots");
+        double low = 0.0, high = 0.0;
+        if constexpr (S < 4) let_in<S, 0>(low);
+        let_in<S, 1>(high);
+        return lane & 1 ? high : low;
     }
     template <int S>
     __device__ __forceinline__ void phases(int& k, const StepStore& store)
@@ -1074,15 +1098,13 @@ struct TriOne {
         k_first = k;
         // (with zeros in what is finished: a vector is read in pairs of 64 entries)
         const bool pair = first > 0 && !(N / 64 & 1);
-        const int number = 16 * (lane & 15) + row;
-        keeps = (lane & 15) < TS && (pair || number >= first);
+        const int number = 16 * (4 * (lane & 3) + (lane >> 2 & 3)) + row;
+        keeps = (lane & 3) < TS / 4 && (pair || number >= first);
         kept_row = store.refl + ((size_t)(k - off) * N + number) - off;
         if (first == 0) phases<0>(k, store);
         else phases<TS / 2>(k, store);
         {
-            double vr[TS];
-            vr[TS - 1] = row_lane<0>(v[TS - 1]);                 // (by all lanes: one that is not active has nothing to give)
-            const double entry = kept_entry<TS - 1>(vr);
+            const double entry = kept_entry<TS - 1>();           // (by all lanes: one that is not active has nothing to give)
             if (keeps) *kept_row = entry;
         }
         // what is left: the last 2 x 2 block
@@ -1445,8 +1467,7 @@ struct Twist {
         for (int i = 0; i < n_pad; i += 16) {
             double d = next.y - lam, e = next.x;
             next = t[i + 16];
-            broadcasts(d);
-            broadcasts(e);
+            broadcasts(d, e);
             double step[16];
             for_lanes([&](auto u) {
                 constexpr int U = decltype(u)::value;

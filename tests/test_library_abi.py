@@ -155,3 +155,59 @@ def test_the_reduction_to_tridiagonal_form_keeps_its_registers():
     assert len(steps) == 4
     for name, r in steps.items():
         assert r[".private_segment_fixed_size"] == 0 and r[".vgpr_spill_count"] == 0, name
+
+
+def test_products_with_a_broadcast_operand_wait_for_it(tmp_path):
+    """v_fmac_f64 with row_newbcast comes from inline assembly (svd_device.h), for which the compiler keeps no wait states: two have to lie
+    between the vector instruction that writes the broadcast operand and the product, on every path to it."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no disassembler")
+    data = open(binding.LIB_PATH, "rb").read()
+    products = 0
+
+    def registers(operand):
+        m = re.match(r"-?v(?:\[(\d+):(\d+)\]|(\d+))", operand)
+        return set() if not m else {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+
+    for at in (m.start() for m in re.finditer(rb"\x7fELF\x02", data)):
+        if struct.unpack_from("<H", data, at + 18)[0] != 224:    # EM_AMDGPU
+            continue
+        obj = tmp_path / "code.o"
+        obj.write_bytes(data[at:])
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True, text=True).stdout
+        if "v_fmac_f64_dpp" not in text:
+            continue
+        code, where = [], {}
+        for line in text.split("\n"):
+            m = re.match(r"\s+(\S+)(.*?)// ([0-9A-F]+):", line)
+            if m:
+                where[int(m[3], 16)] = len(code)
+                code.append((m[1], m[2].strip(), int(m[3], 16)))
+        sources = {}
+        for i, (op, args, addr) in enumerate(code):
+            if op.startswith(("s_branch", "s_cbranch")):
+                offset = int(args.split()[0])
+                target = addr + 4 + 4 * (offset - 65536 if offset >= 32768 else offset)
+                sources.setdefault(target, []).append(i)
+
+        def writers(i, states):
+            """vector instructions in front of instruction i with fewer than `states` wait states between"""
+            before = list(sources.get(code[i][2], []))
+            if i > 0 and code[i - 1][0] not in ("s_branch", "s_endpgm"):
+                before.append(i - 1)
+            for j in before:
+                op, args, _ = code[j]
+                if op.startswith("v_"):
+                    yield j
+                left = states - (int(args) + 1 if op == "s_nop" else 1)
+                if left > 0:
+                    yield from writers(j, left)
+
+        for i, (op, args, addr) in enumerate(code):
+            if op == "v_fmac_f64_dpp":
+                products += 1
+                operand = registers(args.split(",")[1].strip())
+                for j in writers(i, 2):
+                    assert not operand & registers(code[j][1].split(",")[0].strip()), (hex(addr), code[j], args)
+    assert products > 100
