@@ -158,16 +158,19 @@ __device__ inline void rotation(double a, double b, double g, double& c, double&
     s = none ? 0.0 : copysign(0.5, h) * g * inv * ic;
 }
 
-// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n on) by one wave: diagonal d, off-diagonal
-// e; the vectors of the steps go to the rows of H.  Lane l holds the columns 16 (l / 32) .. of row l mod 32 in registers; the column
-// below its first entry, w and column k + 1 (the row of that number) go around through LDS.  The product is taken with
-// the column without its first entry, under way before the reflector is known (A v = A y + v0 A e_{k+1}).
-// 16 steps of 18 columns: 1600 cycles each with the matrix in LDS, 1340 now.
-struct TriScratch { double y[THIN_R], w[THIN_R], column[THIN_R]; };
+// Householder reduction of the n x n matrix C (LDS, both triangles, zeros from n on), n <= 2 U, by one wave: diagonal d, off-diagonal
+// e; the vectors of the steps go to the rows of H.  Lane l belongs to row 2 (l mod 16) + (l / 16 mod 2) and holds its columns 2 u + l / 32, u < U,
+// in registers.  The column below its first entry and w are operands that are broadcast inside the products: of a vector, every row of
+// 16 lanes gets the entries of its columns, which some row of lanes has in this order.  Column k + 1 (the row of that number) goes around
+// through LDS, beside the products.  The product is taken with the column without its first entry, under way before the reflector is known
+// (A v = A y + v0 A e_{k+1}), and the update by a step stands beside the sums of the next.
+// Bound: a chain of about 180 instructions.  18 columns: 1230 cycles per step; 1340 with all sixteen columns per lane, through LDS or not.
+struct TriScratch { double column[THIN_R]; };
+__device__ inline int tri_lane(int row) { return (row & 1) << 4 | row >> 1; }
+template <int U>
 __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, double* d, double* e, double* tau, int n)
 {
-    constexpr int U = THIN_R / 2;
-    const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
+    const int lane = threadIdx.x & 63, h = lane >> 5, i = 2 * (lane & 15) + (lane >> 4 & 1);
     auto in_order = [] {                                         // (the wave's LDS operations are performed in program order)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -178,54 +181,56 @@ __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, 
         y += dpp<DPP_MIRROR>(y);
         return fold16(y, y);
     };
+    auto columns = [](auto&& f) { for_lanes([&](auto u) { if constexpr (decltype(u)::value < U) f(u); }); };
     double a[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = C[i * LD + U * h + u];
-    auto put_row = [&](int row) {
+    for (int u = 0; u < U; ++u) a[u] = C[i * LD + 2 * u + h];
+    static_assert(U % 2 == 0, "written in pairs");
+    auto put_row = [&](int row) {                                // (for lane l of either half: the entry of its own row)
         if (i == row) {
 #pragma unroll
-            for (int u = 0; u < U; u += 2) *(doublex2*)&lds.column[U * h + u] = doublex2{a[u], a[u + 1]};
+            for (int u = 0; u < U; u += 2) *(doublex2*)&lds.column[16 * h + u] = doublex2{a[u], a[u + 1]};
         }
     };
-    auto get = [&](const double* from, double (&to)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; u += 2) {
-            const doublex2 t = *(const doublex2*)&from[U * h + u];
-            to[u] = t.x;
-            to[u + 1] = t.y;
-        }
+    // of a vector that both halves of the lanes have: the entry of column 2 j + h in lane j of the row of lanes
+    auto spread = [&](double y) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo32(y), lo32(y), false, false);
+        const auto g = __builtin_amdgcn_permlane16_swap(hi32(y), hi32(y), false, false);
+        return mk64(h ? l[1] : l[0], h ? g[1] : g[0]);
     };
+    if (h == 0) lds.column[lane] = 0.0;                          // (what no column is written to)
     double x = C[i * LD];                                        // column k of the current matrix, in both halves
+    double v = 0.0, w = 0.0, yj = 0.0, wj = 0.0;                 // the last step's, which the matrix has still to be updated with
+    auto update = [&] {
+        broadcasts(yj, wj);
+        columns([&](auto u) { sub_lane_product<decltype(u)::value>(a[u], yj, w); });
+        columns([&](auto u) { sub_lane_product<decltype(u)::value>(a[u], wj, v); });
+    };
     for (int k = 0; k + 2 < n; ++k) {
         const double y = i > k + 1 ? x : 0.0;
-        lds.y[i] = y;
+        const double alpha = lane_value(x, tri_lane(k + 1)), diagonal = lane_value(x, tri_lane(k));
+        const double sig2 = half_sum(y * y);
+        // (column k + 1, for which y is not v, is not used any more)
+        update();
         put_row(k + 1);
         in_order();
-        double yj[U], wj[U];
-        get(lds.y, yj);
-        const double c = lds.column[i];
-        const double alpha = lane_value(x, k + 1), diagonal = lane_value(x, k);
-        const double sig2 = half_sum(y * y);
+        const double c = lds.column[lane & 31];
+        yj = spread(y);
+        broadcasts(yj);
         double even = 0.0, odd = 0.0;
-#pragma unroll
-        for (int u = 0; u < U; u += 2) {
-            even = fma(a[u], yj[u], even);
-            odd = fma(a[u + 1], yj[u + 1], odd);
-        }
+        columns([&](auto u) {
+            constexpr int J = decltype(u)::value;
+            add_lane_product<J>(J & 1 ? odd : even, yj, a[J]);
+        });
         double beta, v0;
         householder(alpha, sig2, beta, v0);
         const double t = householder_tau(sig2, v0);
-        const double v = i == k + 1 ? v0 : y;
+        v = i == k + 1 ? v0 : y;
         const double part = even + odd;
         const double p = i > k ? t * fma(v0, c, fold32(part, part)) : 0.0;
-        const double w = fma(-0.5 * t * half_sum(p * v), v, p);
-        lds.w[i] = w;
-        in_order();
-        get(lds.w, wj);
-        x = fma(-w, v0, fma(-v, lane_value(w, k + 1), c));
-        // (column k + 1, for which y is not v, is not used any more)
-#pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = fma(-v, wj[u], fma(-w, yj[u], a[u]));
+        w = fma(-0.5 * t * half_sum(p * v), v, p);
+        wj = spread(w);
+        x = fma(-w, v0, fma(-v, lane_value(w, tri_lane(k + 1)), c));
         if (h == 0) H[k * LD + i] = v;
         if (lane == 0) {
             d[k] = diagonal;
@@ -234,21 +239,24 @@ __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, 
         }
         in_order();
     }
+    update();
     put_row(n - 1);
     in_order();
-    if (lane == max(n - 2, 0) && n > 1) d[n - 2] = x;
-    if (lane == n - 1) {
+    if (h == 0 && n > 1 && i == n - 2) d[n - 2] = x;
+    if (h == 0 && i == n - 1) {
         if (n > 1) e[n - 2] = x;
-        d[n - 1] = lds.column[n - 1];
+        d[n - 1] = lds.column[tri_lane(n - 1)];
     }
 }
 
-// Eigenvalues of T below z (see svd_direct.hip): t holds (e_{i-1}^2, d_i), eights of them.
+// Eigenvalues of T below z (see svd_direct_values.hip): t holds (e_{i-1}^2, d_i), eights of them; and the last polynomial, value * 2^expo up to
+// a factor that is the same for every z.
 template <int EIGHTS>
-__device__ inline int sturm_below(const doublex2 (&t)[8 * EIGHTS], double z)
+__device__ inline int sturm_below(const doublex2 (&t)[8 * EIGHTS], double z, float& value, int& expo)
 {
     double p0 = 0.0, p1 = 1.0;
     unsigned signs = 0;
+    expo = 0;
 #pragma unroll
     for (int i = 0; i < 8 * EIGHTS; ++i) {
         const double p2 = fma(t[i].y - z, p1, -(t[i].x * p0));
@@ -257,47 +265,87 @@ __device__ inline int sturm_below(const doublex2 (&t)[8 * EIGHTS], double z)
         signs = __builtin_amdgcn_alignbit(signs, hi32(p1), 31);
         if (i % 8 == 7) {
             // the larger of the two to [0.5, 1): 2^(1022 - E), E its exponent as it is stored
-            const double scale = mk64(0u, 0x7fd00000u - max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u));
+            const unsigned e = max(hi32(p0) & 0x7ff00000u, hi32(p1) & 0x7ff00000u);
+            const double scale = mk64(0u, 0x7fd00000u - e);
             p0 *= scale;
             p1 *= scale;
+            expo += (int)(e >> 20);
         }
     }
+    value = (float)p1;
     return __popc(signs ^ (signs >> 1));
 }
 
+// What the first pass of the search leaves.
+struct FirstPass { int below[ST], expo[ST]; float value[ST]; };
+
 // All eigenvalues of T, descending, by the ST threads of the workgroup (all call): a first pass at ST points, then 16 points per
-// eigenvalue and pass, until a cell is left.  T (8 EIGHTS entries, in LDS) in registers.
+// eigenvalue and pass, until a cell is left: evenly spaced, or, once the interval is narrow, around where the polynomial is expected to be
+// zero (see svd_direct_values.hip).  fine: where in its cell an eigenvalue is.  T (8 EIGHTS entries, in LDS) in registers.
+// 18 columns: 10.8 thousand cycles, two waves on a SIMD; 11.2 with evenly spaced points and a binary search of the first pass, and without `fine`.
 template <int EIGHTS>
-__device__ inline void eigenvalues(const doublex2* in, int n, int* below /* LDS [ST] */, double* lam)
+__device__ inline void eigenvalues(const doublex2* in, int n, FirstPass& first, double* lam, double* fine)
 {
     constexpr u64 CELLS = (LAM_MAX_BITS - LAM_MIN_BITS) >> LAM_STEP_BITS, SPAN = CELLS / ST;
-    constexpr int LANES = ST / THIN_R;
+    constexpr int LANES = ST / THIN_R, HALF = LANES / 2;
     const int tid = threadIdx.x, lane = tid & 63;
     doublex2 t[8 * EIGHTS];
 #pragma unroll
     for (int i = 0; i < 8 * EIGHTS; ++i) t[i] = in[i];
-    below[tid] = sturm_below<EIGHTS>(t, cell_start(SPAN * tid));
+    float value;
+    int expo;
+    first.below[tid] = sturm_below<EIGHTS>(t, cell_start(SPAN * tid), value, expo);
+    first.value[tid] = value;
+    first.expo[tid] = expo;
     __syncthreads();
     const int l = tid & (LANES - 1), base = lane & ~(LANES - 1), i = tid / LANES, asc = n - 1 - i;
     if (i < n) {
-        int lo = 0, hi = ST;                                     // last point with at most asc eigenvalues below it
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (below[mid] <= asc) lo = mid; else hi = mid;
-        }
-        const bool zero = below[0] > asc;
+        const u64 group = ((1ull << LANES) - 1) << base;
+        // last point with at most asc eigenvalues below it: of sixteen runs of 32, of sixteen pairs, of the two
+        static_assert(ST == 2 * LANES * LANES, "three steps");
+        auto held = [&](int at) { return __popcll(__ballot(first.below[at] <= asc) & group); };
+        const int run = max(held(2 * LANES * l) - 1, 0) * 2 * LANES, pair = run + max(held(run + 2 * l) - 1, 0) * 2;
+        const int lo = pair + (first.below[pair + 1] <= asc ? 1 : 0);
+        const bool zero = first.below[0] > asc;
+        const int hi = min(lo + 1, ST - 1);
         u64 g0 = SPAN * lo;
         unsigned width = zero ? 0u : (unsigned)SPAN;             // of the interval from g0 on
+        // the polynomial at its ends, of the same sign as long as it is not known
+        float f0 = first.value[lo], f1 = hi > lo ? first.value[hi] : f0;
+        int e0 = first.expo[lo], e1 = first.expo[hi];
         static_assert(SPAN * LANES <= 0xffffffffull, "points of an interval in 32 bits");
-        auto point = [&](int k) { return width * (unsigned)k / (unsigned)(LANES + 1); };
-        const u64 group = ((1ull << LANES) - 1) << base;
+        const int shift = 2 + 2 * (l < HALF ? l : LANES - 1 - l);
+        bool uniform = false;
         while (width > 1) {                                      // (the lanes of an eigenvalue agree)
-            const int k = __popcll(__ballot(sturm_below<EIGHTS>(t, cell_start(g0 + point(l + 1))) <= asc) & group);
-            const unsigned from = k > 0 ? point(k) : 0u, to = k < LANES ? point(k + 1) : width;
+            unsigned point = width * (unsigned)(l + 1) / (unsigned)(LANES + 1);
+            const bool near = !uniform && (f0 < 0.0f) != (f1 < 0.0f) && (u64)width * (unsigned)n < 1ull << (LAM_BITS - 4);
+            if (near) {
+                const float there = f0 * __builtin_amdgcn_rcpf(f0 - ldexpf(f1, e1 - e0));
+                const unsigned at = min((unsigned)(there * (float)width), width - 1u), offset = width >> shift;
+                point = min(max(l < HALF ? at - min(offset, at) : at + max(offset, 1u), 1u), width - 1u);
+            }
+            const int k = __popcll(__ballot(sturm_below<EIGHTS>(t, cell_start(g0 + point), value, expo) <= asc) & group);
+            const int before = base + max(k - 1, 0), behind = base + min(k, LANES - 1);
+            const unsigned p_lo = __shfl(point, before), p_hi = __shfl(point, behind);
+            const float v_lo = __shfl(value, before), v_hi = __shfl(value, behind);
+            const int x_lo = __shfl(expo, before), x_hi = __shfl(expo, behind);
+            const unsigned from = k > 0 ? p_lo : 0u, to = k < LANES ? p_hi : width;
+            if (k > 0) f0 = v_lo, e0 = x_lo;
+            if (k < LANES) f1 = v_hi, e1 = x_hi;
+            uniform = near && (u64)(to - from) * (unsigned)(LANES + 1) > width;  // (not there: eigenvalues too close to each other)
             g0 += from;
             width = to - from;
         }
-        if (l == 0) lam[i] = zero ? 0.0 : bits_double(LAM_MIN_BITS + (g0 << LAM_STEP_BITS) + (1ull << (LAM_STEP_BITS - 1)));
+        if (l == 0) {
+            const u64 cell = LAM_MIN_BITS + (g0 << LAM_STEP_BITS), middle = 1ull << (LAM_STEP_BITS - 1);
+            u64 inside = middle;
+            if (width == 1u && (f0 < 0.0f) != (f1 < 0.0f)) {
+                const double there = (double)f0 / ((double)f0 - ldexp((double)f1, e1 - e0));
+                inside = min((u64)(there * (double)(1ull << LAM_STEP_BITS)), (1ull << LAM_STEP_BITS) - 1);
+            }
+            lam[i] = zero ? 0.0 : bits_double(cell + middle);
+            fine[i] = zero ? 0.0 : bits_double(cell + inside);
+        }
     }
 }
 
@@ -312,16 +360,17 @@ __device__ inline double dpp_or_one(double x)
 // lower half of the lanes works out the pivots from the top, the upper half those from the bottom, as quotients of the
 // characteristic polynomials (every lane runs through the recurrence and keeps its own step); the two are joined where they
 // meet with the smallest pivot, and the entries are products of quotients from there, by scans.  The Rayleigh quotient
-// corrects lam; the third round starts within 2^-24 of the gap to the next kept eigenvalue.
-// t: as for sturm_below (n entries after the padding), e: off-diagonal.  residual: |T z - lam z| in the last round; lam: its
-// Rayleigh quotient; weight: the sum of |T_ij| z_i^2.
-__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double& lam, double& residual, double& weight)
+// corrects lam, for up to three rounds; one is enough as a rule, from where the eigenvalue is in its cell: if its residual is under `close`,
+// which turns the vector by less than half a unit of fp32, and passes.  (Always three, from the middle of the cell: 15 thousand cycles.)
+// t: as for sturm_below (n entries after the padding), e: off-diagonal.  good: of the residual |T z - lam z|; accepted: it passes.
+__device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam, double close, double good, const KeptApart& apart,
+                                        bool& accepted)
 {
     const int lane = threadIdx.x & 63, i = lane & 31;
     const bool bottom = lane >= 32;
     const double di = t[min(i, n - 1)].y;
     const double ei = i < n - 1 ? e[i] : 0.0, eb = i > 0 && i < n ? e[i - 1] : 0.0;
-    double z = 0.0, len2 = 1.0, gamma = 0.0;
+    double z = 0.0, inv = 1.0;
     for (int round = 0; round < 3; ++round) {
         double p0 = 0.0, p1 = 1.0, num = 1.0, den = 1.0;
         for (int k0 = 0; k0 < n; k0 += 8) {
@@ -372,29 +421,31 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
         f *= lane < 16 ? row1 : lane >= 48 ? row2 : 1.0;
         const double own = mine ? f : !bottom && i == at ? 1.0 : 0.0;
         z = fold32(own, own);
-        double sum = sum8(z * z);
+        const double z2 = z * z;
+        double sum = sum8(z2), weighted = sum8(z2 * (fabs(di) + (fabs(ei) + fabs(eb))));
         sum += dpp<DPP_MIRROR>(sum);
-        len2 = fold16(sum, sum);
-        lam += g_at * reciprocal(len2);
-        gamma = fabs(g_at);
+        weighted += dpp<DPP_MIRROR>(weighted);
+        const double len2 = fold16(sum, sum);
+        weighted = fold16(weighted, weighted);
+        inv = inverse_root(len2);
+        lam += g_at * (inv * inv);
+        const double residual = fabs(g_at) * inv;
+        accepted = residual <= good && apart.vector(residual, weighted * (inv * inv), lam);
+        if (accepted && residual <= close) break;
     }
-    const double inv = inverse_root(len2);
-    residual = gamma * inv;
-    const double z2 = z * z * (inv * inv);
-    double sum = sum8(z2 * (fabs(di) + (fabs(ei) + fabs(eb))));
-    sum += dpp<DPP_MIRROR>(sum);
-    weight = fold16(sum, sum);
     return z * inv;
 }
 
 // Two ways to the spectrum.  The direct one, as for larger matrices (svd_direct.hip): tridiagonal form, Sturm counts, vectors of
 // the kept atoms only.  It is accepted under the same conditions (the spectrum resolved down to four times the floor, rows of
 // zeros aside; vectors with a small residual, kept ones apart); otherwise the two-sided Jacobi iteration.  18
-// columns: 33 us, 28 of them without the sums of the largest matrices (42 and 31 with the matrix, T and the partial sums read
-// from memory and LDS step by step); Jacobi in eight sweeps 73.  T takes 96 of its 158 registers for 18 columns, 128 for 32: two waves on
-// every SIMD do not fit beside a workgroup of the reduction of larger matrices (240 registers) any more, and where those fill
+// columns: 25 us; Jacobi in eight sweeps 73.  In thousands of cycles (2^16 positions): sums of the partial matrices 7, the reduction 20, eigenvalues 11,
+// draw 1.6, vectors 6.5, back through the reflectors 3.7.  Before, 33 us: the trace entry by entry (2.2), the draw with a sum over the sigmas one
+// after the other and its Philox rounds behind the spectrum (4.3), the header in front of the way back (2.4), always three rounds for a vector
+// (15), one reflector at a time (5.2), all of 32 columns in the reduction (21.5).  T takes 96 of its 224 registers for 18 columns, 128 for 32: two waves on
+// every SIMD do not fit beside a workgroup of the reduction of larger matrices (251 registers), and where those fill
 // the chip it waits for the first of them to end.  That costs a call nothing: the directly solved layers of ResNet-18 with its two thin
-// ones 851 us, 852 with a form of 124 registers that fits; with 256 chunks of positions 853 and 857, with 100 small matrices 859 and 860.
+// ones 851 us, 852 with a form of 124 registers that fitted; with 256 chunks of positions 853 and 857, with 100 small matrices 859 and 860.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.
@@ -402,11 +453,13 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
 {
     __shared__ double A[2][THIN_R * LD], V[THIN_R * LD];         // direct: A[1] the matrix that is reduced, V the reflectors
     __shared__ doublex2 T[THIN_R];
-    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R];
+    __shared__ double td[THIN_R], te[THIN_R], ttau[THIN_R], tw[THIN_R], pairs[THIN_R / 2];
     __shared__ __attribute__((aligned(16))) TriScratch tri;
-    __shared__ int below[ST];
+    __shared__ FirstPass first;
+    __shared__ int kept_at[THIN_R];
+    __shared__ float uniform[THIN_R];
     __shared__ int unfinished[2];
-    __shared__ double lam[THIN_R];
+    __shared__ double lam[THIN_R], fine[THIN_R];
     __shared__ int rank_of[THIN_R];
     __shared__ u64 drawn;
     __shared__ int accepted;
@@ -458,13 +511,8 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     }
     if (tid < 2) unfinished[tid] = 0;
     __syncthreads();
-    double trace = 0.0;
-    int zero_rows = 0;
-    for (int i = 0; i < r; ++i) {
-        const double x = A[0][i * LD + i];
-        trace += x;
-        zero_rows += x == 0.0;
-    }
+    const double own_norm = A[0][min(lane, r - 1) * (LD + 1)], trace = wave_sum(lane < r ? own_norm : 0.0);
+    const int zero_rows = __popcll(__ballot(lane < r && own_norm == 0.0));
     // wave 0: sigma, Algorithm 1 (the first index whose probability stays under 1, see block_algorithm1), the draw
     float sigma = 0.0f, p = 0.0f;
     u64 mask = 0ull;
@@ -473,18 +521,35 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         const double l = lam[lane < r ? rank_of[lane] : 0];
         const bool real = lane < r && l > (double)svd::ZERO_REL * l0;
         sigma = real ? (float)sqrt(l) : 0.0f;
-        double tail = 0.0;                                       // sum of the sigmas from this one on, smallest first
-        for (int j = r - 1; j >= 0; --j) {
-            const float sj = __shfl(sigma, j);
-            if (j >= lane) tail += (double)sj;
-        }
+        double tail = (double)sigma;                             // sum of the sigmas from this one on (exact: 47 bits)
+        tail += dpp<DPP_SHL1>(tail);
+        tail += dpp<DPP_SHL2>(tail);
+        tail += dpp<DPP_SHL4>(tail);
+        tail += dpp<DPP_SHL8>(tail);
+        static_assert(THIN_R == 32, "two rows of lanes");
+        tail += lane < 16 ? lane_value(tail, 16) : 0.0;
         const u64 under = __ballot(lane < r && (double)sigma * (s - (double)lane) <= tail);
         const int ns = under ? __ffsll((unsigned long long)under) - 1 : r;
         const double tail_ns = ns < r ? __shfl(tail, ns) : 0.0;
         p = lane < r ? alg1_probability(sigma, lane, ns, s, tail_ns) : 0.0f;
-        const u32x4 rnd = philox4x32_10((u64)(lane >> 2), m.stream_id, seed);
-        const uint32_t word = (lane & 3) == 0 ? rnd.x : (lane & 3) == 1 ? rnd.y : (lane & 3) == 2 ? rnd.z : rnd.w;
-        mask = __ballot(lane < r && u01(word) < p);
+        mask = __ballot(lane < r && uniform[min(lane, r - 1)] < p);
+    };
+    // ... of which nothing but the comparison needs the spectrum
+    auto uniforms = [&] {
+        if (lane < THIN_R) {
+            const u32x4 rnd = philox4x32_10((u64)(lane >> 2), m.stream_id, seed);
+            const uint32_t word = (lane & 3) == 0 ? rnd.x : (lane & 3) == 1 ? rnd.y : (lane & 3) == 2 ? rnd.z : rnd.w;
+            uniform[lane] = u01(word);
+        }
+    };
+    // wave 0: what the other waves have to know of the kept atoms; sigma in the scale of the data
+    auto list_kept = [&] {
+        const int pos = __popcll(mask & ((1ull << lane) - 1));
+        if ((mask >> lane) & 1ull) {
+            kept_at[pos] = lane;
+            tw[pos] = sigma / p;
+        }
+        if (lane == 0) drawn = mask;
     };
     bool direct = trace > 1e-280 && trace < 1e280;               // (false for NaN)
     int expo = 0;
@@ -497,7 +562,13 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             A[1][e] = i < r && j < r ? ldexp(A[0][e], -expo) : 0.0;
         }
         __syncthreads();
-        if (wave == 0) tridiagonal(A[1], V, tri, td, te, ttau, r);
+        if (wave == 0) {
+            if (r <= 8) tridiagonal<4>(A[1], V, tri, td, te, ttau, r);
+            else if (r <= 16) tridiagonal<8>(A[1], V, tri, td, te, ttau, r);
+            else if (r <= 20) tridiagonal<10>(A[1], V, tri, td, te, ttau, r);
+            else tridiagonal<16>(A[1], V, tri, td, te, ttau, r);
+        }
+        if (wave == 1) uniforms();
         __syncthreads();
         const int n_pad = (r + 7) & ~7, pad = n_pad - r;
         if (tid < n_pad) {
@@ -507,28 +578,37 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
         }
         if (tid < THIN_R) rank_of[tid] = tid;
         __syncthreads();
-        if (n_pad == 8) eigenvalues<1>(T, r, below, lam);
-        else if (n_pad == 16) eigenvalues<2>(T, r, below, lam);
-        else if (n_pad == 24) eigenvalues<3>(T, r, below, lam);
-        else eigenvalues<4>(T, r, below, lam);
+        if (n_pad == 8) eigenvalues<1>(T, r, first, lam, fine);
+        else if (n_pad == 16) eigenvalues<2>(T, r, first, lam, fine);
+        else if (n_pad == 24) eigenvalues<3>(T, r, first, lam, fine);
+        else eigenvalues<4>(T, r, first, lam, fine);
         __syncthreads();
         if (wave == 0) {
             draw();
             const bool resolved = zero_rows >= r || lam[r - 1 - zero_rows] > FLOOR_REL * lam[0];
-            if (lane == 0) { accepted = resolved; drawn = mask; }
-            if ((mask >> lane) & 1ull) below[__popcll(mask & ((1ull << lane) - 1))] = lane;
+            if (lane == 0) accepted = resolved;
+            sigma = (float)ldexp((double)sigma, expo / 2);
+            list_kept();
+        } else {
+            // products of the neighbouring reflectors that are applied together
+            for (int q = wave - 1; q < (r - 2) / 2; q += ST / 64 - 1) {
+                const int k = r - 3 - 2 * q;
+                const double product = wave_sum(lane < THIN_R ? V[k * LD + lane] * V[(k - 1) * LD + lane] : 0.0);
+                if (lane == 0) pairs[q] = product;
+            }
         }
         __syncthreads();
         const int count = accepted ? min(__popcll(drawn), m.capacity) : 0;
         for (int a = wave; a < count; a += ST / 64) {
-            const double own = lam[below[a]];
+            const int at = kept_at[a];
+            const double own = lam[at], gap = fmin(at > 0 ? lam[at - 1] - own : 1e300, at + 1 < r ? own - lam[at + 1] : 1e300);
             // (2^-22: from a distance of that the three rounds end with vectors apart)
-            const KeptApart apart(own, a > 0 ? lam[below[a - 1]] : -1.0, a + 1 < count ? lam[below[a + 1]] : -1.0,
+            const KeptApart apart(own, a > 0 ? lam[kept_at[a - 1]] : -1.0, a + 1 < count ? lam[kept_at[a + 1]] : -1.0,
                                   2.384185791015625e-07);
-            double residual, weight, rayleigh = own;
-            const double z = twisted_vector(T + pad, te, r, rayleigh, residual, weight);
+            bool good = false;
+            const double z = twisted_vector(T + pad, te, r, fine[at], 1.5e-8 * gap, 1e-12 * lam[0], apart, good);
             if (lane < THIN_R) A[1][a * LD + lane] = z;
-            if (lane == 0 && !(residual <= 1e-12 * lam[0] && apart.vector(residual, weight, rayleigh))) accepted = 0;
+            if (lane == 0 && !good) accepted = 0;
         }
         __syncthreads();
         direct = accepted != 0;
@@ -536,6 +616,7 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
     bool open = false;
     if (!direct) {
         for (int e = tid; e < THIN_R * THIN_R; e += ST) V[(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+        if (wave == 1) uniforms();
         __syncthreads();
         // tournament over n = r rounded up to even (an entry past r is a row of zeros and never rotates)
         const int n = (r + 1) & ~1, half = n >> 1, n1 = n - 1;
@@ -626,17 +707,19 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             rank_of[before] = tid;
         }
         __syncthreads();
-        if (wave == 0) draw();
+        if (wave == 0) {
+            draw();
+            list_kept();
+        }
+        __syncthreads();
     }
-    // header by wave 0, then the kept vectors, one wave each
+    // header by wave 0; the kept vectors, one wave each, from wave 1 on
     if (wave == 0) {
-        const int pos = __popcll(mask & ((1ull << lane) - 1));
         if (lane < r) {
-            if (m.sigma_out) m.sigma_out[lane] = direct ? (float)ldexp((double)sigma, expo / 2) : sigma;
+            if (m.sigma_out) m.sigma_out[lane] = sigma;
             if (m.p_out) m.p_out[lane] = p;
         }
         if (lane == 0) {
-            drawn = mask;
             *m.count = __popcll(mask);
             m.report[0] = 1;
             m.report[1] = 2;
@@ -644,27 +727,30 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             if (__popcll(mask) > m.capacity) atomicMax(&flags[FLAG_CAPACITY], 1);
             if (open && !(trace != trace)) atomicMax(&flags[FLAG_NOCONV], 1);
         }
-        if ((mask >> lane) & 1ull) {
-            const float scaled = direct ? (float)ldexp((double)sigma, expo / 2) : sigma;
-            tw[pos] = scaled / p;
-            if (pos < m.capacity) {
-                m.idx[pos] = lane;
-                if (m.w) m.w[pos] = scaled / p;
-            }
-            below[pos] = lane;
+        const int pos = __popcll(mask & ((1ull << lane) - 1));
+        if (((mask >> lane) & 1ull) && pos < m.capacity) {
+            m.idx[pos] = lane;
+            if (m.w) m.w[pos] = sigma / p;
         }
     }
-    __syncthreads();
     const int count = min(__popcll(drawn), m.capacity);
-    for (int a = wave; a < count; a += ST / 64) {
-        const int i = lane & 31, src = rank_of[below[a]];
+    for (int a = (wave + ST / 64 - 1) % (ST / 64); a < count; a += ST / 64) {
+        const int i = lane & 31, src = rank_of[kept_at[a]];
         double x, inv = inverse_root(lam[src]);
         if (direct) {
+            // H z, the last step's reflection first, two at a time: both products with z in one sum, one in each half of the lanes
             x = i < r ? A[1][a * LD + i] : 0.0;
-            for (int k = r - 3; k >= 0; --k) {                   // H z, the last step's reflection first
-                const double v = V[k * LD + i];
-                x = fma(-ttau[k] * wave_sum(lane < 32 ? v * x : 0.0), v, x);
+            int k = r - 3;
+            for (int q = 0; k > 0; k -= 2, ++q) {
+                const double v = V[k * LD + i], u = V[(k - 1) * LD + i];
+                double sum = sum8((lane < 32 ? v : u) * x);
+                sum += dpp<DPP_MIRROR>(sum);
+                sum = fold16(sum, sum);
+                const double tv = ttau[k] * lane_value(sum, 0);
+                const double tu = ttau[k - 1] * fma(-tv, pairs[q], lane_value(sum, 32));
+                x = fma(-tu, u, fma(-tv, v, x));
             }
+            if (k == 0) x = fma(-ttau[0] * wave_sum(lane < 32 ? V[i] * x : 0.0), V[i], x);
             inv = ldexp(inv, -(expo / 2));
         } else {
             x = i < r ? V[i * LD + src] : 0.0;

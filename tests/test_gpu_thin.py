@@ -91,3 +91,30 @@ def test_beside_groups_the_bits_of_a_call_of_their_own(thin):
         for j, want in enumerate(alone):
             got = msgs[j].to_host()
             assert got["count"] == want["count"] and all(np.array_equal(got[k], want[k]) for k in ("idx", "w", "U", "V")), j
+
+
+@pytest.mark.parametrize("shape", [(1000, 2), (300, 3), (500, 8), (9, 700), (2000, 16), (17, 400), (3000, 18), (1500, 20), (21, 900), (800, 31),
+                                   (2500, 32)])
+@pytest.mark.parametrize("apart", [0.1, 1e-3, 1e-5])
+def test_vectors_of_neighbours_near_and_far(shape, apart):
+    """Kept singular vectors against those of LAPACK, at the edges of the columns that a lane holds.  A vector of an eigenvalue found to a
+    fraction of its cell takes one round, a neighbour in the way up to three; either way it may turn by 1.5e-8 (the first round's bound) and by
+    the rounding of the Gram matrix (1e-14 of the largest eigenvalue over the distance to the next), and every entry is rounded to fp32."""
+    rng = np.random.default_rng(shape[0] + shape[1] + int(1e6 * apart))
+    r = min(shape)
+    values = [1.0, 0.8, 0.8 * (1.0 - apart), 0.5, 0.25][:r]
+    G = inputs.low_rank_plus_noise(rng, *shape, values, 1e-4)
+    msgs, per, status, _ = encode([G], 20.0 if r > 5 else float(r), 3, stream_base=1, capacity=r)
+    assert status == 0
+    host = msgs[0].to_host()
+    U, S, Vt = np.linalg.svd(np.asarray(G, dtype=np.float64), full_matrices=False)
+    kept = [k for k, i in enumerate(host["idx"]) if i < len(values)]
+    assert len(kept) == len(values)                              # (p = 1 for all of them)
+    for k in kept:
+        i = int(host["idx"][k])
+        u, v = host["U"][:, k].astype(np.float64), host["V"][:, k].astype(np.float64)
+        gap = np.min(np.abs(np.delete(S, i) ** 2 - S[i] ** 2))
+        sign = np.sign(u @ U[:, i])
+        bound = 1.5e-8 + 6e-8 + 1e-14 * S[0] ** 2 / gap
+        assert np.linalg.norm(sign * u - U[:, i]) < bound * (1.0 + S[0] / S[i])
+        assert np.linalg.norm(sign * v - Vt[i]) < bound * (1.0 + S[0] / S[i])
