@@ -33,6 +33,7 @@ namespace {
 constexpr int L0_BITS = 11, L1_BITS = 10, L2_BITS = 10;
 constexpr int NBUCKET = 1 << L0_BITS;        // the largest level
 constexpr int HIST_WGS = 1024;
+constexpr unsigned int DIRECT_MAX = 65536;   // elements that a pass adds to the next level's global histogram one by one
 
 // What a level leaves behind: either the final answer or the path to continue on.
 struct SolveOut {
@@ -44,6 +45,18 @@ struct SolveOut {
     double tail;                  // done: sum of the uncapped magnitudes
     double lo, hi;                // level 0: the edges of the chosen bucket; the water level lies in [lo, hi]
     unsigned int count;           // elements in the chosen bucket
+    double sum;                   // their sum
+};
+
+// A long gradient's water level is looked for among the values around one that a sample of the gradient predicts ("sampled levels").
+// Level 1 is then a histogram of the window of WINDOW_BINS of its buckets; each of the workgroups of the draws, DRAW_WGS at most, counts
+// and adds up what it finds below and above the window:
+constexpr int WINDOW_BINS = 2048;
+constexpr unsigned int NO_WINDOW = ~0u;
+constexpr int DRAW_WGS = 4096;
+struct Tally {
+    double below, inside;         // sums of the elements below the window and inside
+    unsigned int n_in, n_from;    // how many inside, how many inside or above
 };
 
 struct EwState {
@@ -57,6 +70,10 @@ struct EwState {
     double budget;                // final: s - n_s
     double ratio;                 // final: budget / tail, +inf if tail == 0
     unsigned int n_open;          // records that ew_settle left to ew_write, see Segments::open
+    unsigned int window;          // sampled levels: first bucket of level 1 (key >> 10), NO_WINDOW if the sample does not say
+    unsigned int dense;           // sampled levels: many elements are to be expected in the window
+    unsigned int redo;            // sampled levels: the water level is not in the window, level 0 has been formed of all elements
+    Tally tally[DRAW_WGS];
 };
 
 
@@ -90,6 +107,27 @@ __global__ __launch_bounds__(256) void ew_clear(EwState* st)
         for (int k = 0; k < 65; ++k) st->ticket[k] = 0u;
         for (int k = 0; k < 3; ++k) { st->lvl[k].done = 0; st->lvl[k].prefix = 0u; st->lvl[k].n_above = 0ull; st->lvl[k].sum_below = 0.0; }
         st->n_s = 0ull; st->tail = 0.0; st->budget = 0.0; st->ratio = 0.0;
+    }
+}
+
+// Adds the packed words (hist_body) of a workgroup's histogram to the global one.
+template <int LEVEL, int COPIES, int NB, int TPB>
+__device__ inline void flush_hist(const unsigned long long* acc, EwState* st)
+{
+#pragma unroll 1
+    for (int b = threadIdx.x; b < NB; b += TPB) {
+        unsigned int c = 0u;
+        unsigned long long sg = 0ull;
+#pragma unroll
+        for (int k = 0; k < COPIES; ++k) {
+            const unsigned long long w = acc[k * NB + b];
+            c += (unsigned int)(w >> 40);
+            sg += w & ((1ull << 40) - 1);
+        }
+        if (c) {
+            atomicAdd(&st->cnt[LEVEL][b], c);
+            atomicAdd(&st->sig[LEVEL][b], sg);
+        }
     }
 }
 
@@ -139,20 +177,7 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
     }
     for (long long i = n4 * 4 + (long long)self * TPB + threadIdx.x; i < n; i += stride) visit(g[i]);
     __syncthreads();
-    for (int b = threadIdx.x; b < NB; b += TPB) {
-        unsigned int c = 0u;
-        unsigned long long sg = 0ull;
-#pragma unroll
-        for (int k = 0; k < COPIES; ++k) {
-            const unsigned long long w = acc[k * NB + b];
-            c += (unsigned int)(w >> 40);
-            sg += w & ((1ull << 40) - 1);
-        }
-        if (c) {
-            atomicAdd(&st->cnt[LEVEL][b], c);
-            atomicAdd(&st->sig[LEVEL][b], sg);
-        }
-    }
+    flush_hist<LEVEL, COPIES, NB, TPB>(acc, st);
 }
 
 // Inclusive prefix sums over the lanes of a wave by DPP moves (a shuffle through LDS takes about ten times as long):
@@ -184,24 +209,21 @@ __device__ inline V wave_prefix(V v)
 __device__ inline double lane_before(double v) { return dpp_moved<0x138, 0xF>(v); }           // wave_shr:1
 
 // One level of the search, by the T threads of a workgroup (all must call).
-// read(b, cnt, sig) gives a bucket of the level's histogram; `prefix`, n_above0 and sum_below0 are the path chosen so far
-// (level 0: nothing).  The result goes to `out` (LDS or global, visible to the workgroup after the call's last barrier).
+// read(b, cnt, sig) gives a bucket of the level's histogram, of NB (`bins` of them in use); `first` is the number of the first one among
+// all of its level, n_above0 and sum_below0 the path chosen so far (level 0: nothing).  The result goes to `out` (LDS or global, visible to the workgroup after the call's last barrier).
 // scratch: LDS, (2 T / 64 + 1) x 8 bytes.
-template <int LEVEL, int T, typename READ>
-__device__ inline void solve_hist(READ read, double s, unsigned int prefix, unsigned long long n_above0, double sum_below0,
+template <int LEVEL, int T, int NB, typename READ>
+__device__ inline void solve_hist(READ read, double s, unsigned int first, int bins, unsigned long long n_above0, double sum_below0,
                                   SolveOut* out, unsigned long long* scratch)
 {
     unsigned int* cpart = (unsigned int*)scratch;
     double* spart = (double*)(scratch + T / 64);
     int& best = *(int*)(scratch + 2 * (T / 64));
-    constexpr int NB = LEVEL == 0 ? (1 << L0_BITS) : (1 << L1_BITS);
     constexpr int SHIFT = LEVEL == 0 ? 20 : LEVEL == 1 ? 10 : 0;
     constexpr int PER = NB / T;
     static_assert(PER >= 1, "one bucket per thread at least");
     const int tid = threadIdx.x;
-    auto bucket_key = [&](int b) -> unsigned int {
-        return ((LEVEL == 0 ? 0u : prefix << (LEVEL == 1 ? L1_BITS : L2_BITS)) | (unsigned int)b) << SHIFT;
-    };
+    auto bucket_key = [&](int b) -> unsigned int { return (first + (unsigned int)b) << SHIFT; };
     // exponent shared by every element on the chosen path (level 0: part of the bucket index)
     auto bucket_exp = [&](int b) -> unsigned int { return bucket_key(b) >> 23; };
     auto bucket_lo = [&](int b) -> double { return (double)__uint_as_float(bucket_key(b)); };
@@ -253,7 +275,7 @@ __device__ inline void solve_hist(READ read, double s, unsigned int prefix, unsi
         for (int e = 0; e < PER; ++e) {
             const int b = tid * PER + e;
             const double h = bucket_lo(b) * (s - (double)(n_above0 + at_or_above)) - (sum_below0 + below);
-            if (h <= 0.0) mine_best = b;
+            if (h <= 0.0 && b < bins) mine_best = b;
             at_or_above -= cnt_r[e];
             below += sum_r[e];
         }
@@ -294,37 +316,40 @@ __device__ inline void solve_hist(READ read, double s, unsigned int prefix, unsi
         }
         out->done = done ? 1 : 0;
         out->count = c;
+        out->sum = bucket_sum;
         out->n_s = n_s;
         out->tail = tail;
         out->n_above = n_above;
         out->sum_below = sum_below;
-        out->prefix = (LEVEL == 0 ? 0u : prefix << (LEVEL == 1 ? L1_BITS : L2_BITS)) | (unsigned int)bs;
+        out->prefix = first + (unsigned int)bs;
         out->lo = bucket_lo(bs);
         out->hi = bs + 1 < NB ? bucket_lo(bs + 1) : __longlong_as_double(0x7FF0000000000000LL);
     }
     __syncthreads();
 }
 
-// The same from a histogram in st->cnt / st->sig that other workgroups of the running kernel wrote (atomics): device-scope
+// Level 0 from a histogram in st->cnt / st->sig that other workgroups of the running kernel wrote (atomics): device-scope
 // atomic loads instead of plain ones.
-template <int LEVEL, int T>
-__device__ inline void solve_level(const EwState* st, double s, unsigned int prefix, unsigned long long n_above0,
-                                   double sum_below0, SolveOut* out, unsigned long long* scratch)
+__device__ inline void load_bucket0(const EwState* st, int b, unsigned int& cnt, unsigned long long& sig)
 {
-    solve_hist<LEVEL, T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
-        cnt = __hip_atomic_load(&st->cnt[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sig = __hip_atomic_load(&st->sig[LEVEL][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }, s, prefix, n_above0, sum_below0, out, scratch);
+    cnt = __hip_atomic_load(&st->cnt[0][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sig = __hip_atomic_load(&st->sig[0][b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int T>
+__device__ inline void solve_level0(const EwState* st, double s, SolveOut* out, unsigned long long* scratch)
+{
+    solve_hist<0, T, 1 << L0_BITS>([&](int b, unsigned int& cnt, unsigned long long& sig) { load_bucket0(st, b, cnt, sig); },
+                                   s, 0u, 1 << L0_BITS, 0ull, 0.0, out, scratch);
 }
 
-// The same from a histogram that an earlier kernel wrote.
+// Levels 1 and 2, below the bucket of the level before, from a histogram that an earlier kernel wrote.
 template <int LEVEL, int T>
 __device__ inline void solve_written(const EwState* st, double s, const SolveOut& in, SolveOut* out, unsigned long long* scratch)
 {
-    solve_hist<LEVEL, T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+    solve_hist<LEVEL, T, 1 << L1_BITS>([&](int b, unsigned int& cnt, unsigned long long& sig) {
         cnt = st->cnt[LEVEL][b];
         sig = st->sig[LEVEL][b];
-    }, s, in.prefix, in.n_above, in.sum_below, out, scratch);
+    }, s, in.prefix << L1_BITS, 1 << L1_BITS, in.n_above, in.sum_below, out, scratch);
 }
 
 // (s - n_s) / tail, or +inf when nothing is left uncapped
@@ -406,8 +431,157 @@ __global__ __launch_bounds__(1024) void ew_hist0_solve0(const float* __restrict_
     __shared__ SolveOut out;
     hist_body<0, 1024>(g, n, st, acc, 0u, blockIdx.x, gridDim.x);
     if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
-    solve_level<0, 1024>(st, s, 0u, 0ull, 0.0, &out, acc);            // (acc is spent: scratch)
+    solve_level0<1024>(st, s, &out, acc);                             // (acc is spent: scratch)
     if (threadIdx.x == 0) publish(st, 0, out, s);
+}
+
+// ---- sampled levels -----------------------------------------------------------------------------------
+// Level 0 only says around which values the water level lies, and 2^20 elements, 16384 pieces of 64 at places that a hash
+// chooses, say that well enough: the window of level 1 is the 2^21 values around the level that they give, 6 % and more to
+// either side.  So the whole gradient is read once for search and draws, where the histogram of level 0 reads it once by itself:
+// ew_draw counts and adds up what lies below and above the window, and whether the water level is inside is then an exact
+// test.  If it is not (the sample had no part in what counts), or the sample is too scattered to say, level 0 is formed of all elements
+// and the draws are made again: more work, the same message.
+constexpr int SAMPLE = 1 << 20, PIECE = 64;
+constexpr bool sampled_levels(int steps) { return steps == 16; }
+constexpr long long LONG_FROM = 1ll << 25;   // elements from which on segments have 16 steps
+
+// The water level of SAMPLE elements with the budget of their share; st->window.
+__global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, long long n, EwState* st, double s)
+{
+    __shared__ unsigned long long acc[4 * NBUCKET];
+    __shared__ SolveOut out;
+    __shared__ double vpart[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const unsigned int t = blockIdx.x * 1024 + tid, piece = t / (PIECE / 4);
+    const long long spacing = n / (SAMPLE / PIECE) / PIECE;      // in pieces
+    const unsigned int hash = (piece * 0x9E3779B1u) ^ ((piece * 0x85EBCA6Bu) >> 15);
+    const long long at = ((long long)piece * spacing + (long long)(((unsigned long long)hash * (unsigned long long)spacing) >> 32)) * PIECE
+                         + (t & (PIECE / 4 - 1)) * 4;
+    float4 x;
+    if ((((size_t)g) & 15) == 0) x = *(const float4*)(g + at);
+    else x = make_float4(g[at], g[at + 1], g[at + 2], g[at + 3]);
+    for (int b = tid; b < 4 * NBUCKET; b += 1024) acc[b] = 0ull;
+    __syncthreads();
+    const float xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
+        atomicAdd(&acc[(tid & 3) * NBUCKET + (key >> 20)], (1ull << 40) | (unsigned long long)significand(key));
+    }
+    __syncthreads();
+    flush_hist<0, 4, NBUCKET, 1024>(acc, st);
+    if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
+    const double share = s * ((double)SAMPLE / (double)n);
+    solve_level0<1024>(st, share, &out, acc);
+    const SolveOut r = out;
+    double tau;
+    if (r.done) {
+        tau = r.tail / (share - (double)r.n_s);
+    } else {                                                     // between the edges of the bucket
+        const double h_lo = r.lo * (share - (double)(r.n_above + r.count)) - r.sum_below;
+        const double h_hi = r.hi * (share - (double)r.n_above) - r.sum_below - r.sum;
+        tau = r.lo + (r.hi - r.lo) * (h_lo / (h_lo - h_hi));
+    }
+    // h is a sum of min(|x|, tau) over the sample, whose variance is at most that of the squares
+    double v = 0.0;
+    for (int b = tid; b < NBUCKET; b += 1024) {
+        unsigned int cnt;
+        unsigned long long sig;
+        load_bucket0(st, b, cnt, sig);
+        const double m = fmin(tau, (double)__uint_as_float((unsigned int)(b + 1) << 20));      // (beyond the last number: NaN, and tau)
+        v += (double)cnt * m * m;
+    }
+    v = wave_prefix(v);
+    if (lane == 63) vpart[tid >> 6] = v;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < 16; ++w) v = vpart[w] + (w == 1 ? vpart[0] : v);
+    const double above = r.done ? (double)r.n_s : (double)r.n_above + (double)r.count * ((r.hi - tau) / (r.hi - r.lo));
+    // (a window of 1024 buckets to either side is 2^-4 of the level at least; a NaN says no)
+    const bool sure = tau > 0x1p-100 && tau < 0x1p100 && 4.0 * sqrt(v) < 0x1p-4 * tau * (share - above);
+    const unsigned int key = sure ? __float_as_uint((float)tau) : 0u;
+    st->window = sure ? (key >> 10) - WINDOW_BINS / 2 : NO_WINDOW;
+    double near = 0.0;
+    for (unsigned int b = (key >> 20) - (sure ? 1u : 0u); b <= (key >> 20) + 1u; ++b) {
+        unsigned int cnt;
+        unsigned long long sig;
+        load_bucket0(st, (int)b, cnt, sig);
+        near += (double)cnt;
+    }
+    st->dense = near * ((double)n / SAMPLE) > (double)DIRECT_MAX;
+}
+
+__device__ inline double window_edge(unsigned int window) { return (double)__uint_as_float(window << 10); }
+
+struct WindowPath {
+    double n_above;               // elements above the window
+    double sum_below;             // sum of those below
+    bool holds;                   // the water level is inside
+};
+
+// The tallies of all workgroups, in an order that is always the same.  All 1024 threads call; scratch: LDS, 4 * 16 doubles.
+__device__ inline WindowPath window_path(const EwState* st, unsigned int tallies, unsigned int window, double s, double* scratch)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < DRAW_WGS; k += 1024) {
+        const Tally t = k + threadIdx.x < tallies ? st->tally[k + threadIdx.x] : Tally{0.0, 0.0, 0u, 0u};
+        v[0] += t.below; v[1] += t.inside; v[2] += (double)t.n_in; v[3] += (double)t.n_from;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = wave_prefix(v[k]);
+        if (lane == 63) scratch[k * 16 + wave] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = scratch[k * 16];
+        for (int w = 1; w < 16; ++w) v[k] += scratch[k * 16 + w];
+    }
+    const double lo = window_edge(window), hi = window_edge(window + WINDOW_BINS);
+    WindowPath p;
+    p.n_above = v[3] - v[2];
+    p.sum_below = v[0];
+    p.holds = lo * (s - v[3]) - v[0] <= 0.0 && hi * (s - p.n_above) - v[0] - v[1] > 0.0;
+    return p;
+}
+
+// Behind the draws: the path into the window, or level 0 of all elements if the water level is not there.  `members` workgroups of
+// level 0 on a grid of fewer.
+__global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, long long n, EwState* st, double s, unsigned int tallies,
+                                                   unsigned int members)
+{
+    __shared__ unsigned long long acc[4 * NBUCKET];
+    __shared__ SolveOut out;
+    const unsigned int window = st->window;
+    if (window != NO_WINDOW) {
+        const WindowPath p = window_path(st, tallies, window, s, (double*)acc);
+        if (p.holds) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                SolveOut& l = st->lvl[0];
+                l.done = 0;
+                l.n_above = (unsigned long long)p.n_above;
+                l.sum_below = p.sum_below;
+                st->redo = 0u;
+            }
+            return;
+        }
+    }
+    for (unsigned int self = blockIdx.x; self < members; self += gridDim.x) {
+        __syncthreads();
+        hist_body<0, 1024>(g, n, st, acc, 0u, self, members);
+    }
+    clear_level(st, 1);
+    if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
+    solve_level0<1024>(st, s, &out, acc);
+    if (threadIdx.x == 0) {
+        publish(st, 0, out, s);
+        st->window = out.prefix << L1_BITS;
+        st->redo = 1u;
+    }
 }
 
 // p = min(1, |x| (s - n_s) / tail) (eq. (p_i), KKT appendix); `ratio` = (s - n_s) / tail in double,
@@ -440,6 +614,15 @@ __global__ __launch_bounds__(256) void ew_write_p(const float* lam, long long n,
     write_p(lam, n, st->ratio, p);
 }
 
+// A load of what is not read again soon: a gradient of several hundred MB that takes its place in the caches drives out what other
+// kernels wrote there, and waits for it.
+__device__ inline float4 load_once(const float4* p)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 v = __builtin_nontemporal_load((const f4*)p);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ inline float4 load4(const float* g, long long q, long long n, bool vec)
 {
     const long long i = q * 4;
@@ -464,7 +647,6 @@ constexpr unsigned int OVER = 0x80000000u;   // segment with more candidates tha
 constexpr unsigned int FLAG_BIT = 0x1000u;   // entry-wise: kept for sure; l_q: negative
 constexpr unsigned int DROPPED = 0x2000u;    // entry-wise: settled, not kept
 constexpr int MAX_GROUP = 64;
-constexpr unsigned int DIRECT_MAX = 65536;
 constexpr unsigned int COUNTED = 0x80000000u;   // in group_kept: the group's final count, by ew_write
 constexpr int SPIN_COUNTED = 1 << 14;        // Segments::spins, about ten milliseconds: never seen
 
@@ -581,13 +763,14 @@ __device__ inline float pick(const float (&v)[4], int e)
     return (e & 2) ? high : low;
 }
 // Four steps' float4s of a wave, from float4 q0 + lane on.  `whole`: aligned and all inside the gradient (wave-uniform).
+template <bool ONCE = false>
 __device__ inline void load_steps(const float* __restrict__ g, long long q0, long long n, bool whole, bool vec, float4 (&x)[4])
 {
     const int lane = threadIdx.x & 63;
     if (whole) {
         const float4* p = (const float4*)g + q0 + lane;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = p[u * 64];
+        for (int u = 0; u < 4; ++u) x[u] = ONCE ? load_once(p + u * 64) : p[u * 64];
     } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u) x[u] = load4(g, q0 + u * 64 + lane, n, vec);
@@ -596,7 +779,7 @@ __device__ inline void load_steps(const float* __restrict__ g, long long q0, lon
 
 // Calls visit(position, offset in the segment, value, p) for every kept coordinate of a segment, drawn from the gradient
 // with the exact ratio; returns their number.  All lanes of the wave call.
-template <int STEPS, typename VISIT>
+template <int STEPS, bool ONCE = false, typename VISIT>
 __device__ inline unsigned int draw_segment(const float* __restrict__ g, long long n, long long seg,
                                             unsigned long long stream_id, unsigned long long seed, double ratio, VISIT visit)
 {
@@ -609,7 +792,7 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
     for (int j0 = 0; j0 < STEPS; j0 += 4) {
         float4 xv[4];
         const long long q0 = (seg * STEPS + j0) * 64;
-        load_steps(g, q0, n, whole, vec, xv);
+        load_steps<ONCE>(g, q0, n, whole, vec, xv);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
@@ -656,21 +839,34 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
 // blocks, one per component, were a third of the pass.  2^28 elements, 1 % kept: 230 us, where drawing, keep bits, and
 // gathering the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us
 // (2^30 elements: 67 to settle, 74 to write).
-template <int STEPS>
+//
+// AFTER says what is known of the level.  EXACT: the bucket of level 0.  SAMPLED: the window of a sample; this pass then adds up
+// what lies below it and counts what lies above.  REDO: the bucket again, if the window did not hold the level.
+enum After { EXACT, SAMPLED, REDO };
+template <int STEPS, After AFTER>
 __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long long n, EwState* st, double s,
                                                unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
-    __shared__ unsigned int l1cnt[1 << L1_BITS];
-    __shared__ unsigned long long l1sig[1 << L1_BITS];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const long long seg = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool vec = (((size_t)g) & 15) == 0, whole = vec && (seg + 1) * STEPS * STEP <= n;
+    constexpr int BINS = AFTER == SAMPLED ? WINDOW_BINS : 1 << L1_BITS;
+    __shared__ unsigned long long acc[BINS];                     // packed as in hist_body
+    // Candidates of each wave until there are 64 of them: value; the upper 20 bits of its draw and its offset in the segment
+    constexpr unsigned int QUEUE = 128;
+    __shared__ uint2 queue[4][QUEUE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (AFTER == REDO && !st->redo) return;
+    const bool vec = (((size_t)g) & 15) == 0;
+    const long long quads = (sg.n_seg + 3) / 4;
+    long long seg = (long long)blockIdx.x * 4 + wave;
+    bool whole = vec && (seg + 1) * STEPS * STEP <= n;
     float4 xv[4];                                                // (in flight while the search's result arrives)
-    load_steps(g, seg * STEPS * 64, n, whole, vec, xv);
+    load_steps<STEPS == 16>(g, seg * STEPS * 64, n, whole, vec, xv);
     const SolveOut so = st->lvl[0];
-    clear_level(st, 2);
+    if (AFTER == SAMPLED) clear_level(st, 0);
+    if (AFTER != REDO) clear_level(st, 2);
     if (blockIdx.x == 0 && tid == 0) st->n_open = 0u;
-    const bool done = so.done != 0;
+    const unsigned int window = AFTER == SAMPLED ? st->window : so.prefix << L1_BITS;
+    if (AFTER == SAMPLED && window == NO_WINDOW) return;
+    const bool done = AFTER != SAMPLED && so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
     // uniform (an integer below 2^24): with r_lo <= ratio (1 - 2^-22) and r_hi >= ratio (1 + 2^-22),
@@ -678,87 +874,146 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     // |g| r_hi 2^24 underflows, p is zero, and where p is below the normal range see surely_below).  A bracket that is a little wide
     // only sends a few more coordinates to ew_settle, which decides with the exact formula.
     double ratio_lo, ratio_hi;
-    if (done) {
+    if (AFTER == SAMPLED) {
+        ratio_lo = 1.0 / window_edge(window + WINDOW_BINS);
+        ratio_hi = 1.0 / window_edge(window);
+    } else if (done) {
         ratio_lo = ratio_hi = final_ratio(s, so.n_s, so.tail);
     } else {
         ratio_lo = so.hi < inf ? 1.0 / so.hi : 0.0;              // 1 / hi <= ratio <= 1 / lo
         ratio_hi = so.lo > 0.0 ? 1.0 / so.lo : inf;
     }
     const float r_lo = lower_ratio(ratio_lo);
-    const float r_hi = upper_ratio(ratio_hi);
-    const bool zeros = !(ratio_hi < 1.0e31);                     // 0 * infinity: zeros are taken out by hand
-    const unsigned int bucket = done ? 0xFFFFFFFFu : so.prefix;
+    // The 32 bits w of a draw: (float)w >= fl32(256 |g| r_hi + 512) leaves u 2^24 = w / 256, rounded down, at |g| r_hi or more.
+    const float r_word = upper_ratio(ratio_hi) * 256.0f;
+    const bool zeros = AFTER != SAMPLED && !(r_word < __int_as_float(0x7f800000)); // 0 * infinity: zeros are taken out by hand
     // Few elements in the bucket: straight into the global histogram, where they hardly ever meet.  Many: through LDS.
-    const bool through_lds = !done && so.count > DIRECT_MAX;
-    if (through_lds) {
-        for (int b = tid; b < (1 << L1_BITS); b += 256) { l1cnt[b] = 0u; l1sig[b] = 0ull; }
-        __syncthreads();
-    }
-
-    if (seg < sg.n_seg) {
-        const Slots sl = ew_slots(sg, seg);
-        unsigned int fill = 0u;                                  // wave-uniform
-        for (int j0 = 0; j0 < STEPS; j0 += 4) {
-            const long long q0 = (seg * STEPS + j0) * 64;
-            if (j0 > 0) load_steps(g, q0, n, whole, vec, xv);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
-                const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
-                const float us[4] = {(float)(rnd.x >> 8), (float)(rnd.y >> 8), (float)(rnd.z >> 8), (float)(rnd.w >> 8)};
-                bool in[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) in[e] = !(us[e] >= fabsf(xs[e]) * r_hi);     // (a NaN is a candidate)
-                if (zeros) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) in[e] = in[e] && xs[e] != 0.0f;
-                }
-                unsigned long long ballots[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
-                if (ballots[0] | ballots[1] | ballots[2] | ballots[3]) {
-                    // one candidate per lane and turn: a lane seldom has a second one
-                    unsigned int pos = fill + listed_before(ballots);
-                    unsigned int left = candidate_bits(in);
-                    do {
-                        if (left) {
-                            const int e = __builtin_ctz(left);
-                            left &= left - 1;
-                            const float x = pick(xs, e), uf = pick(us, e);
-                            const bool sure = surely_below(uf, x, r_lo);
-                            if (pos < (unsigned int)sl.capacity) {
-                                sl.val[pos] = x;
-                                sl.word[pos] = (unsigned short)(((j0 + u) * STEP + lane * 4 + e) | (sure ? FLAG_BIT : 0u));
-                            }
-                            ++pos;
-                            const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
-                            if ((key >> 20) == bucket) {
-                                const unsigned int b = (key >> 10) & ((1 << L1_BITS) - 1);
-                                if (through_lds) {
-                                    atomicAdd(&l1cnt[b], 1u);
-                                    atomicAdd(&l1sig[b], (unsigned long long)significand(key));
-                                } else {
-                                    atomicAdd(&st->cnt[1][b], 1u);
-                                    atomicAdd(&st->sig[1][b], (unsigned long long)significand(key));
-                                }
-                            }
+    const bool through_lds = AFTER == SAMPLED ? st->dense != 0u : !done && so.count > DIRECT_MAX;
+    const unsigned int first_key = window << 10;
+    double below = 0.0, inside = 0.0;                            // this lane's
+    unsigned int n_in = 0u, n_from = 0u;
+    for (long long quad = blockIdx.x; quad < quads; quad += AFTER == EXACT ? quads : gridDim.x) {
+        if (AFTER != EXACT && quad != blockIdx.x) {
+            if (through_lds) __syncthreads();
+            seg = quad * 4 + wave;
+            whole = vec && (seg + 1) * STEPS * STEP <= n;
+            load_steps<STEPS == 16>(g, seg * STEPS * 64, n, whole, vec, xv);
+        }
+        if (through_lds) {
+#pragma unroll 1                                                 // (its addresses would stay in registers through the draws)
+            for (int b = tid; b < BINS; b += 256) acc[b] = 0ull;
+            __syncthreads();
+        }
+        if (seg < sg.n_seg) {
+            const Slots sl = ew_slots(sg, seg);
+            unsigned int fill = 0u, waiting = 0u;                // records written, candidates in the queue (wave-uniform)
+            // the first `count` candidates of the queue, one per lane
+            auto records = [&](unsigned int count) {
+                __builtin_amdgcn_wave_barrier();
+                const uint2 c = queue[wave][lane];
+                const float x = __uint_as_float(c.x);
+                const unsigned int pos = fill + lane, key = c.x & 0x7FFFFFFFu;
+                if ((unsigned int)lane < count) {
+                    if (pos < (unsigned int)sl.capacity) {
+                        const bool sure = surely_below((float)((c.y >> 12 << 4) | 15u), x, r_lo);
+                        sl.val[pos] = x;
+                        sl.word[pos] = (unsigned short)((c.y & 0xFFFu) | (sure ? FLAG_BIT : 0u));
+                    }
+                    if (AFTER == SAMPLED && key >= first_key) ++n_from;
+                    const unsigned int b = (key >> 10) - window;
+                    if (b < (unsigned int)BINS && !done) {
+                        if (AFTER == SAMPLED) {
+                            ++n_in;
+                            inside += (double)fabsf(x);
                         }
-                    } while (__ballot(left != 0u));
-                    fill += listed_total(ballots);
+                        if (through_lds) {
+                            atomicAdd(&acc[b], (1ull << 40) | (unsigned long long)significand(key));
+                        } else {
+                            atomicAdd(&st->cnt[1][b], 1u);
+                            atomicAdd(&st->sig[1][b], (unsigned long long)significand(key));
+                        }
+                    }
+                }
+                fill += count;
+            };
+            for (int j0 = 0; j0 < STEPS; j0 += 4) {
+                const long long q0 = (seg * STEPS + j0) * 64;
+                if (j0 > 0) load_steps<STEPS == 16>(g, q0, n, whole, vec, xv);
+                if constexpr (AFTER == SAMPLED) {                // (a NaN is above; beside the draws the sums take twenty registers more)
+                    const float edge = __uint_as_float(first_key);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) below += (double)(fabsf(xs[e]) < edge ? fabsf(xs[e]) : 0.0f);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const u32x4 rnd = philox4x32_10((unsigned long long)((unsigned int)(q0 + u * 64) + lane), stream_id, seed);
+                    const float xs[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+                    const unsigned int rs[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+                    bool in[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) in[e] = !((float)rs[e] >= fmaf(fabsf(xs[e]), r_word, 512.0f));     // (a NaN is a candidate)
+                    if (zeros) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) in[e] = in[e] && xs[e] != 0.0f;
+                    }
+                    unsigned long long ballots[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ballots[e] = __ballot(in[e]);
+                    if (ballots[0] | ballots[1] | ballots[2] | ballots[3]) {
+                        // one candidate per lane and turn: a lane seldom has a second one
+                        unsigned int at = waiting + listed_before(ballots), left = candidate_bits(in);
+                        waiting += listed_total(ballots);
+                        const float rf[4] = {__uint_as_float(rs[0]), __uint_as_float(rs[1]), __uint_as_float(rs[2]), __uint_as_float(rs[3])};
+                        for (;;) {
+                            do {
+                                if (left && at < QUEUE) {
+                                    const int e = __builtin_ctz(left);
+                                    left &= left - 1;
+                                    queue[wave][at++] = make_uint2(__float_as_uint(pick(xs, e)),
+                                                                   (__float_as_uint(pick(rf, e)) >> 12 << 12) | (unsigned int)((j0 + u) * STEP + lane * 4 + e));
+                                }
+                            } while (__ballot(left != 0u && at < QUEUE));
+                            if (waiting < 64u) break;
+                            records(64u);
+                            __builtin_amdgcn_wave_barrier();
+                            queue[wave][lane] = queue[wave][64 + lane];
+                            waiting -= 64u;
+                            at -= 64u;
+                        }
+                    }
                 }
             }
+            records(waiting);
+            if (lane == 0) sg.count[seg] = fill <= (unsigned int)sl.capacity ? fill : OVER;
         }
-        if (lane == 0) sg.count[seg] = fill <= (unsigned int)sl.capacity ? fill : OVER;
+        if (through_lds) {
+            __syncthreads();
+            flush_hist<1, 1, BINS, 256>(acc, st);
+        }
     }
-    if (through_lds) {
-        __syncthreads();
-        for (int b = tid; b < (1 << L1_BITS); b += 256) {
-            const unsigned int cnt = l1cnt[b];
-            if (cnt) {
-                atomicAdd(&st->cnt[1][b], cnt);
-                atomicAdd(&st->sig[1][b], l1sig[b]);
-            }
+    if constexpr (AFTER == SAMPLED) {
+        __shared__ double sums[2][4];
+        __shared__ unsigned int counts[2][4];
+        below = wave_prefix(below);
+        inside = wave_prefix(inside);
+        n_in = wave_prefix(n_in);
+        n_from = wave_prefix(n_from);
+        if (lane == 63) {
+            sums[0][wave] = below;
+            sums[1][wave] = inside;
+            counts[0][wave] = n_in;
+            counts[1][wave] = n_from;
         }
+        __syncthreads();
+        if (tid == 0)
+            st->tally[blockIdx.x] = Tally{(sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]), (sums[1][0] + sums[1][1]) + (sums[1][2] + sums[1][3]),
+                                          counts[0][0] + counts[0][1] + counts[0][2] + counts[0][3],
+                                          counts[1][0] + counts[1][1] + counts[1][2] + counts[1][3]};
     }
 }
 
@@ -800,7 +1055,14 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     if (in.done) {
         ratio_lo = ratio_hi = st->ratio;
     } else {
-        solve_written<1, 256>(st, s, in, &out, scratch);
+        if constexpr (sampled_levels(STEPS)) {
+            solve_hist<1, 256, WINDOW_BINS>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+                cnt = st->cnt[1][b];
+                sig = st->sig[1][b];
+            }, s, st->window, st->redo ? 1 << L1_BITS : WINDOW_BINS, in.n_above, in.sum_below, &out, scratch);
+        } else {
+            solve_written<1, 256>(st, s, in, &out, scratch);
+        }
         if (blockIdx.x == 0 && tid == 0) publish(st, 1, out, s);
         search = out.done == 0;
         prefix = out.prefix;
@@ -1113,7 +1375,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
     for (int e = 0; e < LOCAL_PER; ++e)
         if (e < per && key[e] != ~0u) add(copy + (key[e] >> 20), key[e]);
     __syncthreads();
-    solve_hist<0, LOCAL_T>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+    solve_hist<0, LOCAL_T, 1 << L0_BITS>([&](int b, unsigned int& cnt, unsigned long long& sig) {
         const unsigned long long w = sc.hist[b];
         cnt = (unsigned int)(w >> 40);
         sig = w & ((1ull << 40) - 1);
@@ -1125,7 +1387,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
                 sig += v & ((1ull << 40) - 1);
             }
         }
-    }, s, 0u, 0ull, 0.0, &sc.out, sc.solve);
+    }, s, 0u, 1 << L0_BITS, 0ull, 0.0, &sc.out, sc.solve);
     auto read = [&](int b, unsigned int& cnt, unsigned long long& sig) {
         cnt = (unsigned int)(sc.hist[b] >> 40);
         sig = sc.hist[b] & ((1ull << 40) - 1);
@@ -1137,7 +1399,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
     for (int e = 0; e < LOCAL_PER; ++e)
         if (e < per && (key[e] >> 20) == in.prefix) add((key[e] >> 10) & ((1 << L1_BITS) - 1), key[e]);
     __syncthreads();
-    solve_hist<1, LOCAL_T>(read, s, in.prefix, in.n_above, in.sum_below, &sc.out, sc.solve);
+    solve_hist<1, LOCAL_T, 1 << L1_BITS>(read, s, in.prefix << L1_BITS, 1 << L1_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
     if (sc.out.done) return;
     in = sc.out;
     clear(1 << L2_BITS);
@@ -1145,7 +1407,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
     for (int e = 0; e < LOCAL_PER; ++e)
         if (e < per && (key[e] >> 10) == in.prefix) add(key[e] & ((1 << L2_BITS) - 1), key[e]);
     __syncthreads();
-    solve_hist<2, LOCAL_T>(read, s, in.prefix, in.n_above, in.sum_below, &sc.out, sc.solve);
+    solve_hist<2, LOCAL_T, 1 << L2_BITS>(read, s, in.prefix << L2_BITS, 1 << L2_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
 }
 
 __device__ inline unsigned int magnitude(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -1271,7 +1533,7 @@ __global__ __launch_bounds__(LOCAL_T) void prob_first(const float* lam, const Lo
         const unsigned int self = blockIdx.x - n_local, members = gridDim.x - n_local;
         hist_body<0, LOCAL_T>(lambda_long, n_long, st, sc.hist, 0u, self, members);
         if (!last_workgroup(st->ticket, self, members)) return;
-        solve_level<0, LOCAL_T>(st, s, 0u, 0ull, 0.0, &sc.out, sc.solve);
+        solve_level0<LOCAL_T>(st, s, &sc.out, sc.solve);
         if (tid == 0) publish(st, 0, sc.out, s);
         return;
     }
@@ -1326,6 +1588,11 @@ __global__ __launch_bounds__(256) void prob_last(const float* lam, long long n, 
 // ---- l_q quantisation (Section 4) -------------------------------------------------------------------
 enum { LQ_MAX = 0, LQ_TWO = 1, LQ_ONE = 2, LQ_POW = 3 };
 constexpr int LQ_WGS = 1024;
+// From here on both passes read the gradient with load_once.  Up to about 256 MB of gradient and output stay in the last cache from
+// pass to pass; beyond that a pass that takes part in it pays for what the decode before left there (norm + draws of 35 million
+// elements 26 + 31 us in the caches' way and 28 + 32 so, 50 million 46 + 37 and 37 + 40, 64 million 69 + 44 and 48 + 48, 120 million
+// 133 + 96 and 83 + 96).
+constexpr long long ONCE_FROM = 42'000'000;
 
 // One more element of |g|_q: max |g_i|, or the sum of g_i^2, |g_i| or |g_i|^q in double.
 // POW: any q but 1, 2 and infinity (pow takes so many registers that it gets kernels of its own).
@@ -1365,7 +1632,8 @@ __device__ inline double lq_norm(double acc, int mode, double q)
 
 // The norm: a part per workgroup, added up by every workgroup of the pass behind it (fixed thread -> element map and fixed
 // reduction tree, so the norm is the same bits in every run).
-template <bool POW>
+// ONCE: see ONCE_FROM.
+template <bool POW, bool ONCE>
 __global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g, long long n, int mode, double q,
                                                     double* __restrict__ partial)
 {
@@ -1381,7 +1649,7 @@ __global__ __launch_bounds__(256) void lq_norm_pass(const float* __restrict__ g,
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const long long qq = q0 + u * stride;
-            x[u] = qq < n4 ? ((const float4*)g)[qq] : make_float4(0.f, 0.f, 0.f, 0.f);
+            x[u] = qq >= n4 ? make_float4(0.f, 0.f, 0.f, 0.f) : ONCE ? load_once((const float4*)g + qq) : ((const float4*)g)[qq];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) { visit(x[u].x); visit(x[u].y); visit(x[u].z); visit(x[u].w); }
@@ -1416,7 +1684,7 @@ __global__ __launch_bounds__(LOCAL_T) void lq_encode_local(const float* __restri
 }
 
 // The l_q encoder's pass over the gradient behind the norm: draws against the exact p, one group of segments per workgroup.
-template <int STEPS, bool POW>
+template <int STEPS, bool POW, bool ONCE>
 __global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long long n, EwState* st, const double* __restrict__ partial,
                                                int parts, int mode, double q, float* norm_out, unsigned long long stream_id,
                                                unsigned long long seed, Segments sg)
@@ -1442,7 +1710,7 @@ __global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long
     unsigned int total = 0u;                                     // wave-uniform
     for (long long seg = seg0; seg < min(seg0 + mine, sg.n_seg); ++seg) {
         const Slots sl = lq_slots(sg, seg);
-        const unsigned int kept = draw_segment<STEPS>(g, n, seg, stream_id, seed, ratio,
+        const unsigned int kept = draw_segment<STEPS, ONCE>(g, n, seg, stream_id, seed, ratio,
             [&](unsigned int pos, unsigned int off, float x, float) {
                 if (pos < (unsigned int)sl.capacity) sl.word[pos] = (unsigned short)(off | (x < 0.0f ? FLAG_BIT : 0u));
             });
@@ -1470,7 +1738,7 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     EwLayout l;
     // Short segments until there are enough of them to fill the chip several times over (8192 waves run at once), then
     // long ones: a segment costs its counts and a chain of loads in every later kernel whatever its length.
-    l.steps = n < (1ll << 25) ? 4 : 16;
+    l.steps = n < LONG_FROM ? 4 : 16;
     const int64_t seg = (int64_t)l.steps * STEP;
     l.sg.n_seg = (n + seg - 1) / seg;
     // A workgroup that writes the message adds up the counts of all groups before its own: about a thousand at most.
@@ -1535,11 +1803,15 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
     const unsigned quads = (unsigned)((sg.n_seg + 3) / 4), groups = (unsigned)sg.n_groups;
     const bool long_seg = l.steps == 16;
     if (clear_first) { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(l.st); }
-    { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist0_solve0<<<wgs0, 1024, 0, stream>>>(g, n, l.st, s); }
-    {
-        ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
-        if (long_seg) ew_draw<16><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
-        else ew_draw<4><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg);
+    if (long_seg) {
+        const unsigned draws = std::min<unsigned>(quads, DRAW_WGS);
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE / 4096, 1024, 0, stream>>>(g, n, l.st, s); }
+        { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, SAMPLED><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, draws, (unsigned)wgs0); }
+        { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
+    } else {
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist0_solve0<<<wgs0, 1024, 0, stream>>>(g, n, l.st, s); }
+        { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<4, EXACT><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
     }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
@@ -1587,17 +1859,21 @@ int encode_lq(atomo_ctx* ctx, const float* g, double q, uint64_t seed, uint64_t 
         return ATOMO_OK;
     }
     const int wgs = (int)std::min<int64_t>(LQ_WGS, (n + 4095) / 4096);
+    const bool once = n >= ONCE_FROM;
+    static_assert(ONCE_FROM >= LONG_FROM, "segments of 16 steps");
     {
         ProfScope ps(ctx, ATOMO_K_EW_HIST, stream);              // the norm pass takes the place of the histograms
-        const auto pass = mode == LQ_POW ? lq_norm_pass<true> : lq_norm_pass<false>;
+        const auto pass = once ? (mode == LQ_POW ? lq_norm_pass<true, true> : lq_norm_pass<false, true>)
+                               : (mode == LQ_POW ? lq_norm_pass<true, false> : lq_norm_pass<false, false>);
         pass<<<wgs, 256, 0, stream>>>(g, n, mode, q, l.lq_partial);
     }
     {
         ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream);
         const unsigned groups = (unsigned)l.sg.n_groups;
         const bool long_seg = l.steps == 16;
-        const auto draw = long_seg ? (mode == LQ_POW ? lq_draw<16, true> : lq_draw<16, false>)
-                                   : (mode == LQ_POW ? lq_draw<4, true> : lq_draw<4, false>);
+        const auto draw = once ? (mode == LQ_POW ? lq_draw<16, true, true> : lq_draw<16, false, true>)
+                        : long_seg ? (mode == LQ_POW ? lq_draw<16, true, false> : lq_draw<16, false, false>)
+                                   : (mode == LQ_POW ? lq_draw<4, true, false> : lq_draw<4, false, false>);
         draw<<<groups, 256, 0, stream>>>(g, n, l.st, l.lq_partial, wgs, mode, q, msg->norm, stream_id, seed, l.sg);
         const auto write = long_seg ? ew_write<16, true> : ew_write<4, true>;
         write<<<groups, 256, 0, stream>>>(g, n, l.st, 0.0, stream_id, seed, l.sg, (long long)msg->capacity, msg->idx, nullptr,

@@ -293,3 +293,58 @@ def test_a_subnormal_gradient_takes_about_as_long_as_another(kind):
         times.append(min(took))
     assert ctx().status()[0] == 0
     assert times[1] < 6 * times[0], times
+
+
+def sampled(n):
+    """Mask of the elements that the sample of a long gradient reads: 64 at a hashed place of each of 16384 parts."""
+    piece, spacing = np.arange(16384, dtype=np.uint64), n // 16384 // 64
+    m32 = np.uint64(0xFFFFFFFF)
+    h = ((piece * np.uint64(0x9E3779B1)) & m32) ^ (((piece * np.uint64(0x85EBCA6B)) & m32) >> np.uint64(15))
+    at = (piece * np.uint64(spacing) + ((h * np.uint64(spacing)) >> np.uint64(32))) * np.uint64(64)
+    mask = np.zeros(n, dtype=bool)
+    mask[(at[:, None] + np.arange(64, dtype=np.uint64)).astype(np.int64)] = True
+    return mask
+
+
+@pytest.mark.parametrize("kind, extra", [("heavy", 0), ("heavy", 4099), ("all_alike", 3), ("many_near_the_level", 1), ("above_the_window", 2),
+                                         ("below_the_window", 5), ("scattered", 1), ("zeros", 7), ("subnormal", 0), ("everything", 0)])
+def test_long_gradients_whose_level_a_sample_predicts(kind, extra):
+    """From 2^25 elements on.  The level is where the sample says, with few values near it or so many that they go through LDS; it is not,
+    because the sample saw none of the large values or nothing but them; the sample cannot say."""
+    n = 2 ** 25 + extra
+    rng = np.random.default_rng(n)
+    g = rng.standard_normal(n, dtype=np.float32) * np.float32(1e-3)
+    s = n / 100
+    if kind == "heavy":
+        g[rng.integers(0, n, n // 1000)] *= 100
+    elif kind == "all_alike":                                    # (every p is 0.4, one value)
+        g = np.where(rng.random(n, dtype=np.float32) < 0.5, np.float32(0.7), np.float32(-0.7))
+        s = 0.4 * n
+    elif kind == "many_near_the_level":                          # (and no segment has slots for them)
+        s = 0.6 * n
+    elif kind == "above_the_window":
+        g[~sampled(n)] *= 3
+    elif kind == "below_the_window":
+        g[sampled(n)] *= 3
+    elif kind == "scattered":                                    # (a handful of values holds the budget)
+        g[rng.integers(0, n, 40)] = 50.0
+        s = 37.5
+    elif kind == "zeros":
+        g[:] = 0
+    elif kind == "subnormal":
+        g = (rng.integers(-200, 201, n) * 2.0 ** -149).astype(np.float32)
+        g[rng.random(n, dtype=np.float32) < 0.95] = 0
+    elif kind == "everything":
+        s = 2.0 * n
+    d = torch.zeros(n + 4, device="cuda")[extra & 3:][:n]        # (aligned to 4, 8 and 16 bytes)
+    d.copy_(torch.from_numpy(g))
+    p = torch.zeros(n, device="cuda")
+    msg = binding.alloc_entrywise_message(n, n, "cuda")
+    for _ in range(2):                                           # (the second call finds what the first one left)
+        binding.atomo_encode_entrywise(ctx(), d, s, 5, 2, msg=msg, p_out=p)
+    assert ctx().status()[0] == 0
+    p = p.cpu().numpy()
+    np.testing.assert_allclose(p, oracle.probabilities(g.astype(np.float64), s), rtol=1e-6, atol=1e-12)
+    h, ref = msg.to_host(), oracle.encode_entrywise(g, s, 5, 2, p32=p)
+    assert h["count"] == ref["idx"].size and np.array_equal(h["idx"], ref["idx"])
+    np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6, atol=2.0 ** -149)
