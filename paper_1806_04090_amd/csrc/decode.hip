@@ -290,6 +290,10 @@ constexpr int SPARSE_RESIDENT = 2048;  // workgroups the chip holds at once
 constexpr int SPARSE_MSGS = 16;        // messages per launch
 constexpr int64_t ONE_ANY = 1 << 22;   // outputs, and tiles, up to which one message decodes without LDS (see the dispatch)
 constexpr int ONE_TILES = 8192;
+// Outputs from here on (384 MB) go around the last cache, which could not hold them: what is written into it drives out what others wrote,
+// and the pass behind this one waits for the rest (2^28 outputs 230 -> 207 us and the search behind it 3 faster, 180 million 152 -> 140,
+// 100 million 75 -> 72; 70 million 47 -> 52).
+constexpr long long AROUND_FROM = 96'000'000;
 
 struct SparseMsg {
     const long long* count;
@@ -396,7 +400,8 @@ __global__ __launch_bounds__(256) void decode_sparse_one(SparseMsg m, float scal
 // A message whose coordinates do not ascend does not decode (the searches miss some of its pairs): the first `checks`
 // workgroups per message compare its neighbours, and latch what they find.  Beside the others, as workgroups of their own: with
 // a share of it in every workgroup, 11.17 M outputs took 1.1 us longer.
-template <bool LQ, bool ACCUMULATE, int G>
+// AROUND: see AROUND_FROM.
+template <bool LQ, bool ACCUMULATE, int G, bool AROUND = false>
 __global__ __launch_bounds__(256) void decode_sparse(SparseMsgs msgs, float scale, float* __restrict__ out, long long n, int run,
                                                      int checks, int* flags)
 {
@@ -482,8 +487,11 @@ __global__ __launch_bounds__(256) void decode_sparse(SparseMsgs msgs, float scal
         float* const o = out + i0;
         if (here == SPARSE_TILE && (((size_t)o) & 15) == 0) {
 #pragma unroll
-            for (int k = 0; k < SPARSE_TILE / 1024; ++k)
-                *(float4*)(o + 4 * (tid + 256 * k)) = *(const float4*)&tile[4 * (tid + 256 * k)];
+            for (int k = 0; k < SPARSE_TILE / 1024; ++k) {
+                const floatx4 x = *(const floatx4*)&tile[4 * (tid + 256 * k)];
+                if (AROUND) __builtin_nontemporal_store(x, (floatx4*)(o + 4 * (tid + 256 * k)));
+                else *(floatx4*)(o + 4 * (tid + 256 * k)) = x;
+            }
         } else {
             for (int k = tid; k < here; k += 256) o[k] = tile[k];
         }
@@ -585,6 +593,7 @@ int decode_sparse_all(atomo_ctx* ctx, const MSG* msgs, int n_msgs, float scale, 
         if (alone) decode_sparse_one<LQ><<<grid, 256, 0, stream>>>(part.m[0], scale, out, n, checks, ctx->d_flags);
         else if (first > 0) decode_sparse<LQ, true, 16><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
         else if (part.n > 4) decode_sparse<LQ, false, 16><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
+        else if (n >= AROUND_FROM) decode_sparse<LQ, false, 64, true><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
         else decode_sparse<LQ, false, 64><<<grid, 256, 0, stream>>>(part, scale, out, n, run, checks, ctx->d_flags);
     }
     ATOMO_HIP(ctx, hipGetLastError());
