@@ -17,7 +17,8 @@
 //
 // Sampling and packing.  Coordinate i is kept iff u_i < p_i (Philox stream, float32 compare) and is
 // stored as (i, g_i / p_i) in ascending i.  The encoder reads the gradient twice: once for the level-0 histogram, once to
-// draw every uniform against the bracket that level 0 leaves for p_i.  Whatever may be kept is written down in that pass as
+// draw every uniform against the bracket that level 0 leaves for p_i; a long one once, against a bracket that a sample of it
+// leaves ("sampled levels").  Whatever may be kept is written down in that pass as
 // a record (value and offset), and all that follows reads the records, a hundredth of the gradient: the third level of the
 // search, the settling of the few draws inside the bracket, the message.  The l_q encoder (Section 4), whose probabilities
 // need only a norm, draws against the exact p and has nothing to settle.
@@ -441,33 +442,42 @@ __global__ __launch_bounds__(1024) void ew_hist0_solve0(const float* __restrict_
 // either side.  So the whole gradient is read once for search and draws, where the histogram of level 0 reads it once by itself:
 // ew_draw counts and adds up what lies below and above the window, and whether the water level is inside is then an exact
 // test.  If it is not (the sample had no part in what counts), or the sample is too scattered to say, level 0 is formed of all elements
-// and the draws are made again: more work, the same message.
-constexpr int SAMPLE = 1 << 20, PIECE = 64;
+// and the draws are made again: more work, the same message.  Two launches more, 4.5 us each where there is nothing to do, and 12.5 for the
+// sample: encode of 34 million elements 85 -> 79 us, 50 million 117 -> 91, 2^28 520 -> 312; where the sample misleads, 2^28 take 750.
+constexpr int SAMPLE = 1 << 20, PIECE = 64, SAMPLE_WGS = 64;
 constexpr bool sampled_levels(int steps) { return steps == 16; }
 constexpr long long LONG_FROM = 1ll << 25;   // elements from which on segments have 16 steps
 
-// The water level of SAMPLE elements with the budget of their share; st->window.
+// The water level of SAMPLE elements with the budget of their share; st->window.  Few workgroups: each adds its hundreds of buckets that
+// are not empty to the global histogram one by one (256 of them 13.8 us, 64 of them 11.6).
 __global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, long long n, EwState* st, double s)
 {
     __shared__ unsigned long long acc[4 * NBUCKET];
     __shared__ SolveOut out;
     __shared__ double vpart[16];
     const int tid = threadIdx.x, lane = tid & 63;
-    const unsigned int t = blockIdx.x * 1024 + tid, piece = t / (PIECE / 4);
     const long long spacing = n / (SAMPLE / PIECE) / PIECE;      // in pieces
-    const unsigned int hash = (piece * 0x9E3779B1u) ^ ((piece * 0x85EBCA6Bu) >> 15);
-    const long long at = ((long long)piece * spacing + (long long)(((unsigned long long)hash * (unsigned long long)spacing) >> 32)) * PIECE
-                         + (t & (PIECE / 4 - 1)) * 4;
-    float4 x;
-    if ((((size_t)g) & 15) == 0) x = *(const float4*)(g + at);
-    else x = make_float4(g[at], g[at + 1], g[at + 2], g[at + 3]);
+    const bool vec = (((size_t)g) & 15) == 0;
+    constexpr int PER = SAMPLE / SAMPLE_WGS / 4096;
+    float4 x[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const unsigned int t = (u * SAMPLE_WGS + blockIdx.x) * 1024 + tid, piece = t / (PIECE / 4);
+        const unsigned int hash = (piece * 0x9E3779B1u) ^ ((piece * 0x85EBCA6Bu) >> 15);
+        const long long at = ((long long)piece * spacing + (long long)(((unsigned long long)hash * (unsigned long long)spacing) >> 32)) * PIECE
+                             + (t & (PIECE / 4 - 1)) * 4;
+        x[u] = vec ? *(const float4*)(g + at) : make_float4(g[at], g[at + 1], g[at + 2], g[at + 3]);
+    }
     for (int b = tid; b < 4 * NBUCKET; b += 1024) acc[b] = 0ull;
     __syncthreads();
-    const float xs[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
-        atomicAdd(&acc[(tid & 3) * NBUCKET + (key >> 20)], (1ull << 40) | (unsigned long long)significand(key));
+    for (int u = 0; u < PER; ++u) {
+        const float xs[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
+            atomicAdd(&acc[(tid & 3) * NBUCKET + (key >> 20)], (1ull << 40) | (unsigned long long)significand(key));
+        }
     }
     __syncthreads();
     flush_hist<0, 4, NBUCKET, 1024>(acc, st);
@@ -826,19 +836,20 @@ __device__ inline unsigned int draw_segment(const float* __restrict__ g, long lo
     return fill;
 }
 
-// Second pass of the entry-wise encoder over the gradient; the level-0 result is read from st->lvl[0] (the launch before
-// left it there).
+// The pass of the entry-wise encoder that draws; the level-0 result is read from st->lvl[0] (the launch before left it there), or the
+// window of a sample from st->window.
 // After level 0 the water level tau = tail / (s - n_s) is known to lie inside one bucket [lo, hi] of the float bit pattern
 // (12.5 % wide), so p_i = min(1, |g_i| / tau) is bracketed for every element, and because rounding is monotone,
 // fl(|g_i| / hi) <= p_i <= fl(|g_i| / lo)  holds for the float32 p_i that the final ratio will give.  An element is dropped
 // here if u >= p_hi, marked as kept for sure if u < p_lo; what lies between (about 0.12 s elements) is settled by ew_settle and ew_write
 // once the remaining levels have fixed tau exactly.  Every element of the chosen bucket has p_hi >= 1 and so a record: level
 // 1 is histogrammed here and level 2 from the records.
-// Bound by the Philox rounds (17 or 18 wide multiplications per four elements): everything per element that can be left to
-// the candidates, one element in fifty, is left to them, and a lane takes one candidate per turn, because four predicated
-// blocks, one per component, were a third of the pass.  2^28 elements, 1 % kept: 230 us, where drawing, keep bits, and
-// gathering the kept values from the gradient again took 388 + 103 + 141 us and level 2, which read the gradient too, 202 us
-// (2^30 elements: 67 to settle, 74 to write).
+// Bound by the Philox rounds (18 wide multiplications per four elements) and the read: everything per element that can be left to
+// the candidates, one element in fifty, is left to them.  In a long segment a wave queues its candidates until there are 64, one per lane,
+// for what they take (bounds, record, histogram): step by step, a handful of lanes goes through that for the others (2^28 elements, 1 %
+// kept: 256 -> 244 us; 10 % 310 -> 295; segments of four steps gain nothing).  2^28 elements: 240 us with the sums below the window (10 of
+// them), where the histogram of level 0 took 210 and the draws 231.  Read the caches' way the pass takes 300: the decode of the step before
+// left its output there.
 //
 // AFTER says what is known of the level.  EXACT: the bucket of level 0.  SAMPLED: the window of a sample; this pass then adds up
 // what lies below it and counts what lies above.  REDO: the bucket again, if the window did not hold the level.
@@ -850,7 +861,8 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     constexpr int BINS = AFTER == SAMPLED ? WINDOW_BINS : 1 << L1_BITS;
     __shared__ unsigned long long acc[BINS];                     // packed as in hist_body
     // Candidates of each wave until there are 64 of them: value; the upper 20 bits of its draw and its offset in the segment
-    constexpr unsigned int QUEUE = 128;
+    constexpr bool QUEUED = STEPS == 16;
+    constexpr unsigned int QUEUE = QUEUED ? 128 : 1;
     __shared__ uint2 queue[4][QUEUE];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (AFTER == REDO && !st->redo) return;
@@ -893,7 +905,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     double below = 0.0, inside = 0.0;                            // this lane's
     unsigned int n_in = 0u, n_from = 0u;
     for (long long quad = blockIdx.x; quad < quads; quad += AFTER == EXACT ? quads : gridDim.x) {
-        if (AFTER != EXACT && quad != blockIdx.x) {
+        if (AFTER != EXACT && quad != blockIdx.x) {              // (EXACT has a workgroup for every four segments)
             if (through_lds) __syncthreads();
             seg = quad * 4 + wave;
             whole = vec && (seg + 1) * STEPS * STEP <= n;
@@ -906,34 +918,35 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
         }
         if (seg < sg.n_seg) {
             const Slots sl = ew_slots(sg, seg);
-            unsigned int fill = 0u, waiting = 0u;                // records written, candidates in the queue (wave-uniform)
+            unsigned int fill = 0u, waiting = 0u;                // records written, candidates in the queue, or all if there is none (wave-uniform)
+            // a candidate's record, and its place in the search: its draw is u (the queue's is rounded up: less is kept for sure)
+            auto record = [&](unsigned int pos, float x, float u, unsigned int offset) {
+                const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
+                if (pos < (unsigned int)sl.capacity) {
+                    sl.val[pos] = x;
+                    sl.word[pos] = (unsigned short)(offset | (surely_below(u, x, r_lo) ? FLAG_BIT : 0u));
+                }
+                if (AFTER == SAMPLED && key >= first_key) ++n_from;
+                const unsigned int b = (key >> 10) - window;
+                if (b < (unsigned int)BINS && !done) {
+                    if (AFTER == SAMPLED) {
+                        ++n_in;
+                        inside += (double)fabsf(x);
+                    }
+                    if (through_lds) {
+                        atomicAdd(&acc[b], (1ull << 40) | (unsigned long long)significand(key));
+                    } else {
+                        atomicAdd(&st->cnt[1][b], 1u);
+                        atomicAdd(&st->sig[1][b], (unsigned long long)significand(key));
+                    }
+                }
+            };
             // the first `count` candidates of the queue, one per lane
             auto records = [&](unsigned int count) {
                 __builtin_amdgcn_wave_barrier();
                 const uint2 c = queue[wave][lane];
-                const float x = __uint_as_float(c.x);
-                const unsigned int pos = fill + lane, key = c.x & 0x7FFFFFFFu;
-                if ((unsigned int)lane < count) {
-                    if (pos < (unsigned int)sl.capacity) {
-                        const bool sure = surely_below((float)((c.y >> 12 << 4) | 15u), x, r_lo);
-                        sl.val[pos] = x;
-                        sl.word[pos] = (unsigned short)((c.y & 0xFFFu) | (sure ? FLAG_BIT : 0u));
-                    }
-                    if (AFTER == SAMPLED && key >= first_key) ++n_from;
-                    const unsigned int b = (key >> 10) - window;
-                    if (b < (unsigned int)BINS && !done) {
-                        if (AFTER == SAMPLED) {
-                            ++n_in;
-                            inside += (double)fabsf(x);
-                        }
-                        if (through_lds) {
-                            atomicAdd(&acc[b], (1ull << 40) | (unsigned long long)significand(key));
-                        } else {
-                            atomicAdd(&st->cnt[1][b], 1u);
-                            atomicAdd(&st->sig[1][b], (unsigned long long)significand(key));
-                        }
-                    }
-                }
+                if ((unsigned int)lane < count)
+                    record(fill + lane, __uint_as_float(c.x), (float)((c.y >> 12 << 4) | 15u), c.y & 0xFFFu);
                 fill += count;
             };
             for (int j0 = 0; j0 < STEPS; j0 += 4) {
@@ -971,14 +984,16 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                         const float rf[4] = {__uint_as_float(rs[0]), __uint_as_float(rs[1]), __uint_as_float(rs[2]), __uint_as_float(rs[3])};
                         for (;;) {
                             do {
-                                if (left && at < QUEUE) {
+                                if (left && (!QUEUED || at < QUEUE)) {
                                     const int e = __builtin_ctz(left);
                                     left &= left - 1;
-                                    queue[wave][at++] = make_uint2(__float_as_uint(pick(xs, e)),
-                                                                   (__float_as_uint(pick(rf, e)) >> 12 << 12) | (unsigned int)((j0 + u) * STEP + lane * 4 + e));
+                                    const float x = pick(xs, e);
+                                    const unsigned int w = __float_as_uint(pick(rf, e)), offset = (unsigned int)((j0 + u) * STEP + lane * 4 + e);
+                                    if (QUEUED) queue[wave][at++] = make_uint2(__float_as_uint(x), (w >> 12 << 12) | offset);
+                                    else record(at++, x, (float)(w >> 8), offset);
                                 }
-                            } while (__ballot(left != 0u && at < QUEUE));
-                            if (waiting < 64u) break;
+                            } while (__ballot(left != 0u && (!QUEUED || at < QUEUE)));
+                            if (!QUEUED || waiting < 64u) break;
                             records(64u);
                             __builtin_amdgcn_wave_barrier();
                             queue[wave][lane] = queue[wave][64 + lane];
@@ -988,7 +1003,8 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                     }
                 }
             }
-            records(waiting);
+            if (QUEUED) records(waiting);
+            else fill = waiting;
             if (lane == 0) sg.count[seg] = fill <= (unsigned int)sl.capacity ? fill : OVER;
         }
         if (through_lds) {
@@ -1772,10 +1788,14 @@ int search_state(atomo_ctx* ctx, hipStream_t stream, EwState** st)
     return ATOMO_OK;
 }
 
-// Workgroups of level 0: none may visit 2^16 elements or more (field widths of the packed histogram word).
+// Workgroups of level 0: none may visit 2^16 elements or more (field widths of the packed histogram word).  Each adds some hundred buckets
+// that are not empty to the global histogram, one by one, which takes longer than to read 32,768 elements instead of 4,096 (one million
+// elements on 245 workgroups 11.3 us, on 64 8.4; four million on 256 13.1, on 128 11.5); below 64 of them the chip is too empty for that
+// (60,000 on 15 6.5, on 4 7.6).
 int level0_workgroups(int64_t n)
 {
-    return (int)std::max<int64_t>(std::min<int64_t>(256, (n + 4095) / 4096), (n + 49151) / 49152);
+    const int64_t few = std::min<int64_t>(256, std::max<int64_t>(64, n / 32768));
+    return (int)std::max<int64_t>(std::min<int64_t>(few, (n + 4095) / 4096), (n + 49151) / 49152);
 }
 
 }  // namespace
@@ -1805,7 +1825,7 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
     if (clear_first) { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(l.st); }
     if (long_seg) {
         const unsigned draws = std::min<unsigned>(quads, DRAW_WGS);
-        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE / 4096, 1024, 0, stream>>>(g, n, l.st, s); }
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE_WGS, 1024, 0, stream>>>(g, n, l.st, s); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, SAMPLED><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, draws, (unsigned)wgs0); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
