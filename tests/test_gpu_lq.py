@@ -95,3 +95,46 @@ def test_capacity_overflow_is_latched():
     h = msg.to_host()
     mask = oracle.bernoulli_mask(p, 2, 0)
     assert h["count"] == int(mask.sum()) > 10 and np.array_equal(h["idx"], np.flatnonzero(mask)[:10])
+
+
+@pytest.mark.parametrize("q", [0.3, 1.5, 2.5, 4.0, 4.000001, 9.0])        # (a table up to 4, pow beyond)
+@pytest.mark.parametrize("n", [3000, 16_385, 2 ** 25 + 1])
+def test_powers_by_a_table(q, n):
+    """Numbers of all exponents, at the ends of [1, 2) and of its 512 parts, zeros and subnormal ones.  p is one product in double
+    precision, rounded to a float: it is off by half a unit of that, 2^-24, and the sum of the powers by no more than 2^-50."""
+    rng = np.random.default_rng(n)
+    g = np.exp2(rng.uniform(-149, 20, n)).astype(np.float32)
+    m = min(n, 3000) // 2
+    part = rng.integers(0, 513, m)
+    edge = (1.0 + part / 512.0).astype(np.float32)
+    g[:m] = np.where(rng.random(m) < 0.5, edge, np.nextafter(edge, np.float32(0.0))) * np.exp2(rng.integers(-100, 18, m)).astype(np.float32)
+    g[m:m + 40] = 0.0
+    g[m + 40:m + 80] = np.arange(1, 41) * 2.0 ** -149
+    g *= rng.choice([-1.0, 1.0], n).astype(np.float32)
+    capacity = n
+    if n > 2 ** 25:
+        msg = binding.alloc_lq_message(n, capacity, "cuda")
+        p = torch.zeros(n, device="cuda")
+        binding.atomo_encode_lq(ctx(), dev(g), q, 5, 3, msg=msg, p_out=p)
+        p_gpu = p.cpu().numpy()
+    else:
+        msg, h = parity(g, q, 5, 3, capacity=capacity)
+        p_gpu = encode(g, q, 5, 3, capacity)[1]
+    a = np.abs(g.astype(np.longdouble))
+    norm = (a[a > 0] ** np.longdouble(q)).sum() ** (1 / np.longdouble(q))
+    np.testing.assert_allclose(float(msg.norm.item()), float(norm), rtol=2.0 ** -24 * 1.001)
+    np.testing.assert_allclose(p_gpu, np.minimum(a / norm, 1).astype(np.float64), rtol=2.0 ** -24 * 1.001, atol=2.0 ** -150 * 1.001)
+    assert ctx().status()[0] == 0
+
+
+@pytest.mark.parametrize("q", [1.5, 4.5])
+@pytest.mark.parametrize("n", [300, 20_000])
+def test_a_power_of_infinity(q, n):
+    g = np.ones(n, dtype=np.float32)
+    g[n // 2] = -np.inf
+    msg = binding.atomo_encode_lq(ctx(), dev(g), q, 1, 0)
+    assert np.isinf(float(msg.norm.item()))
+    g[n // 2] = np.nan                                            # (left out of the sum)
+    msg = binding.atomo_encode_lq(ctx(), dev(g), q, 1, 0, msg=binding.alloc_lq_message(n, n, "cuda"))
+    np.testing.assert_allclose(float(msg.norm.item()), (n - 1) ** (1 / q), rtol=2.0 ** -24 * 1.001)
+    ctx().status()
