@@ -252,6 +252,27 @@ __device__ __forceinline__ void decode_tile(DecLds& lds, const DecOut* outs, con
             }
         }
     }
+    // A narrow tile without gaps is one piece of memory: through LDS, and out in rows of 16 bytes per lane, where a row of the products is 18
+    // lanes of 32 (the layers of ResNet-18 in the Section 6 reshape, 11.16 M outputs: 17.9 -> 16.5 us; with several tiles one after the
+    // other in a workgroup, and one list of atoms for them, 24)
+    if constexpr (TALL && !ACCUMULATE) {
+        if (o.ld == o.cols && o.cols * TALL_ROWS <= KP * (TR + TC + 64)) {
+            const int cols = o.cols;
+            if (l32 < cols) {
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) lds.operands[(row_off + 4 * h + below(rb, v)) * cols + l32] = acc[rb][0][v];
+            }
+            __syncthreads();
+            const int here = min(TALL_ROWS, o.rows - tile_r0) * cols;
+            const Global<float> to = global(o.out) + (long long)tile_r0 * cols;
+            const int quads = (((size_t)to) & 15) == 0 ? here / 4 : 0;
+            for (int k = tid; k < quads; k += 256) *(Global<floatx4>)(to + 4 * k) = *(const floatx4*)&lds.operands[4 * k];
+            for (int k = 4 * quads + tid; k < here; k += 256) to[k] = lds.operands[k];
+            return;
+        }
+    }
     const Global<float> corner = global(o.out) + (long long)row0 * o.ld + col0;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)

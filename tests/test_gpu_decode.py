@@ -141,3 +141,19 @@ def test_svd_decode_of_tall_and_other_outputs_in_one_call(accumulate):
             size = size + np.abs(start[:, :cols])
         terms = sum(h["w"].size for _, h in grp)
         assert (np.abs(out.cpu().numpy() - want) <= (terms + 4) * 2.0 ** -23 * size).all(), (rows, cols)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2])                    # (aligned to 16, 4 and 8 bytes)
+@pytest.mark.parametrize("rows,cols", [(65, 1), (256, 2), (257, 17), (511, 18), (700, 24), (700, 25), (300, 32)])
+def test_svd_decode_of_narrow_outputs_without_gaps(rows, cols, offset):
+    """Tiles of up to 24 columns leave through LDS as one piece of memory; what lies before and behind the output stays.  Tolerance as above."""
+    rng = np.random.default_rng(rows + cols)
+    for ks in ([3], [0], [2, 0, 17]):
+        pairs = [make_msg(rng, rows, cols, k, 20) for k in ks]
+        flat = torch.full((rows * cols + 16,), 7.5, device="cuda")
+        out = flat[offset:offset + rows * cols].view(rows, cols)
+        binding.atomo_decode_svd_batch(ctx(), [[m for m, _ in pairs]], 0.5, outs=[out])
+        want = oracle.decode_svd([h for _, h in pairs], rows, cols, scale=0.5)
+        size = oracle.decode_svd([{key: np.abs(x) for key, x in h.items()} for _, h in pairs], rows, cols, scale=0.5)
+        assert (np.abs(out.cpu().numpy() - want) <= (sum(ks) + 4) * 2.0 ** -23 * size).all()
+        assert bool((flat[:offset] == 7.5).all()) and bool((flat[offset + rows * cols:] == 7.5).all())
