@@ -212,6 +212,16 @@ inline void deal_to_dies(std::vector<T>& list)
     list.swap(dealt);
 }
 
+// What a lane loads from LDS behind this is what other lanes of its wave stored in front of it.  The wave's LDS operations are performed in
+// program order, so there is nothing to wait for, but without the fences the compiler may keep a lane's own value or move the load: the
+// barrier alone says nothing of memory.
+__device__ inline void lanes_in_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11): device + host inline so every kernel draws the same stream
 // ---------------------------------------------------------------------------------------------

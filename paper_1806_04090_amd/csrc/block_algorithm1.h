@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "atomo_internal.h"
+
 namespace atomo {
 
 constexpr int ALG1_MAX = 2048;
@@ -30,10 +32,7 @@ __device__ inline void block_sort_desc(float* key, int* src, int P)
             if (j >= 128 || across) {
                 __syncthreads();
             } else {
-                // same wave: nothing to wait for, but the compiler must keep the stages apart
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                lanes_in_order();                                // (same wave)
             }
             across = j >= 128;
             for (int q = tid; q < (P >> 1); q += 256) {

@@ -943,8 +943,9 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
             };
             // the first `count` candidates of the queue, one per lane
             auto records = [&](unsigned int count) {
-                __builtin_amdgcn_wave_barrier();
+                lanes_in_order();
                 const uint2 c = queue[wave][lane];
+                lanes_in_order();                                // (its place is free from here on)
                 if ((unsigned int)lane < count)
                     record(fill + lane, __uint_as_float(c.x), (float)((c.y >> 12 << 4) | 15u), c.y & 0xFFFu);
                 fill += count;
@@ -995,8 +996,8 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                             } while (__ballot(left != 0u && (!QUEUED || at < QUEUE)));
                             if (!QUEUED || waiting < 64u) break;
                             records(64u);
-                            __builtin_amdgcn_wave_barrier();
                             queue[wave][lane] = queue[wave][64 + lane];
+                            lanes_in_order();
                             waiting -= 64u;
                             at -= 64u;
                         }

@@ -171,11 +171,6 @@ template <int U>
 __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, double* d, double* e, double* tau, int n)
 {
     const int lane = threadIdx.x & 63, h = lane >> 5, i = 2 * (lane & 15) + (lane >> 4 & 1);
-    auto in_order = [] {                                         // (the wave's LDS operations are performed in program order)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     auto half_sum = [](double y) {                               // over the 32 lanes of a half, the same bits in each
         y = sum8(y);
         y += dpp<DPP_MIRROR>(y);
@@ -213,7 +208,7 @@ __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, 
         // (column k + 1, for which y is not v, is not used any more)
         update();
         put_row(k + 1);
-        in_order();
+        lanes_in_order();
         const double c = lds.column[lane & 31];
         yj = spread(y);
         broadcasts(yj);
@@ -237,11 +232,11 @@ __device__ inline void tridiagonal(const double* C, double* H, TriScratch& lds, 
             e[k] = beta;
             tau[k] = t;
         }
-        in_order();
+        lanes_in_order();
     }
     update();
     put_row(n - 1);
-    in_order();
+    lanes_in_order();
     if (h == 0 && n > 1 && i == n - 2) d[n - 2] = x;
     if (h == 0 && i == n - 1) {
         if (n > 1) e[n - 2] = x;

@@ -211,3 +211,17 @@ def test_products_with_a_broadcast_operand_wait_for_it(tmp_path):
                 for j in writers(i, 2):
                     assert not operand & registers(code[j][1].split(",")[0].strip()), (hex(addr), code[j], args)
     assert products > 100
+
+
+def test_lanes_that_exchange_values_through_lds_have_fences():
+    # the wave's barrier alone does not keep the compiler from reusing what a lane stored itself, nor from moving a load over it
+    csrc = os.path.join(ROOT, "paper_1806_04090_amd", "csrc")
+    found = []
+    for name in sorted(os.listdir(csrc)):
+        text = re.sub(r"//.*", "", open(os.path.join(csrc, name)).read())
+        for m in re.finditer(r"__builtin_amdgcn_wave_barrier", text):
+            around = [line.strip() for line in text[:m.start()].split("\n")[-2:-1] + text[m.end():].split("\n")[1:2]]
+            found.append((name, around))
+    assert found
+    for name, around in found:
+        assert ["RELEASE" in around[0], "ACQUIRE" in around[1]] == [True, True], (name, around)
