@@ -295,6 +295,40 @@ def test_a_subnormal_gradient_takes_about_as_long_as_another(kind):
     assert times[1] < 6 * times[0], times
 
 
+def encode_time(g, s, msg, seed=5):
+    """Least time of seven encodes, in milliseconds."""
+    took = []
+    for _ in range(7):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        binding.atomo_encode_entrywise(ctx(), g, s, seed, 2, msg=msg)
+        end.record()
+        end.synchronize()
+        took.append(start.elapsed_time(end))
+    return min(took)
+
+
+@pytest.mark.parametrize("n", [16_000_001, 2 ** 25 + 5])
+@pytest.mark.parametrize("down", [92, 94, 96, 98])
+def test_a_tiny_water_level_takes_about_as_long_as_another(n, down):
+    """Levels of 2^-96.6 to 2^-102.6, where 2^32 over the level does not fit a float but 2^24 over it does, zeros among the elements: the
+    same draws are kept, with values smaller by just that power, and no more elements are looked at (but a long gradient is read twice, as
+    one whose level no sample predicts)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    g = torch.randn(n, generator=gen, device="cuda") * 1e-3
+    g[torch.randint(0, n, (n // 1000,), generator=gen, device="cuda")] *= 100
+    g[torch.rand(n, generator=gen, device="cuda") < 0.5] = 0
+    small = g * 2.0 ** -down
+    msgs = [binding.alloc_entrywise_message(n, n, "cuda") for _ in range(2)]
+    times = [encode_time(x, 0.01 * n, m) for x, m in zip((g, small), msgs)]
+    assert ctx().status()[0] == 0
+    a, b = (m.to_host() for m in msgs)
+    assert a["count"] == b["count"] > 0.009 * n and np.array_equal(a["idx"], b["idx"])
+    assert np.array_equal(a["val"], b["val"].astype(np.float64) * 2.0 ** down)
+    assert times[1] < (1.5 if n < 2 ** 25 else 2.2) * times[0], times
+
+
 def sampled(n):
     """Mask of the elements that the sample of a long gradient reads: 64 at a hashed place of each of 16384 parts."""
     piece, spacing = np.arange(16384, dtype=np.uint64), n // 16384 // 64
