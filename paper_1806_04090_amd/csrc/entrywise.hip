@@ -74,7 +74,6 @@ struct EwState {
     unsigned int window;          // sampled levels: first bucket of level 1 (key >> 10), NO_WINDOW if the sample does not say
     unsigned int dense;           // sampled levels: many elements are to be expected in the window
     unsigned int redo;            // sampled levels: the water level is not in the window, level 0 has been formed of all elements
-    Tally tally[DRAW_WGS];
 };
 
 
@@ -531,13 +530,13 @@ struct WindowPath {
 };
 
 // The tallies of all workgroups, in an order that is always the same.  All 1024 threads call; scratch: LDS, 4 * 16 doubles.
-__device__ inline WindowPath window_path(const EwState* st, unsigned int tallies, unsigned int window, double s, double* scratch)
+__device__ inline WindowPath window_path(const Tally* tally, unsigned int tallies, unsigned int window, double s, double* scratch)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < DRAW_WGS; k += 1024) {
-        const Tally t = k + threadIdx.x < tallies ? st->tally[k + threadIdx.x] : Tally{0.0, 0.0, 0u, 0u};
+        const Tally t = k + threadIdx.x < tallies ? tally[k + threadIdx.x] : Tally{0.0, 0.0, 0u, 0u};
         v[0] += t.below; v[1] += t.inside; v[2] += (double)t.n_in; v[3] += (double)t.n_from;
     }
 #pragma unroll
@@ -561,14 +560,14 @@ __device__ inline WindowPath window_path(const EwState* st, unsigned int tallies
 
 // Behind the draws: the path into the window, or level 0 of all elements if the water level is not there.  `members` workgroups of
 // level 0 on a grid of fewer.
-__global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, long long n, EwState* st, double s, unsigned int tallies,
-                                                   unsigned int members)
+__global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, long long n, EwState* st, double s, const Tally* tally,
+                                                   unsigned int tallies, unsigned int members)
 {
     __shared__ unsigned long long acc[4 * NBUCKET];
     __shared__ SolveOut out;
     const unsigned int window = st->window;
     if (window != NO_WINDOW) {
-        const WindowPath p = window_path(st, tallies, window, s, (double*)acc);
+        const WindowPath p = window_path(tally, tallies, window, s, (double*)acc);
         if (p.holds) {
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 SolveOut& l = st->lvl[0];
@@ -674,6 +673,7 @@ struct Segments {
     int slot_bytes;               // per segment
     int per_group;
     EwOpen* open;                 // [open_max] the first open records, in any order
+    Tally* tally;                 // [DRAW_WGS] sampled levels
     unsigned int open_max;
     int spins;                    // loads of another workgroup's count before it is made anew
 };
@@ -1034,7 +1034,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
         }
         __syncthreads();
         if (tid == 0)
-            st->tally[blockIdx.x] = Tally{(sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]), (sums[1][0] + sums[1][1]) + (sums[1][2] + sums[1][3]),
+            sg.tally[blockIdx.x] = Tally{(sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]), (sums[1][0] + sums[1][1]) + (sums[1][2] + sums[1][3]),
                                           counts[0][0] + counts[0][1] + counts[0][2] + counts[0][3],
                                           counts[1][0] + counts[1][1] + counts[1][2] + counts[1][3]};
     }
@@ -1826,6 +1826,7 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     l.sg.group_kept = carve.take<unsigned int>((size_t)l.sg.n_groups);
     l.sg.open_max = (unsigned)(n / 4096 + 512);                  // (twice of what is to be expected of a message of all elements)
     l.sg.open = carve.take<EwOpen>(l.sg.open_max);
+    l.sg.tally = l.steps == 16 ? carve.take<Tally>(DRAW_WGS) : nullptr;
     l.sg.spins = SPIN_COUNTED;
     size_t step_bytes = STEP_BYTES;
     if (limit) step_bytes = std::min<size_t>(step_bytes, (limit - carve.off - 256) / ((size_t)l.sg.n_seg * l.steps) & ~(size_t)7);
@@ -1886,7 +1887,7 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
         const unsigned draws = std::min<unsigned>(quads, DRAW_WGS);
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE_WGS, 1024, 0, stream>>>(g, n, l.st, s); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, SAMPLED><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
-        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, draws, (unsigned)wgs0); }
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, sg.tally, draws, (unsigned)wgs0); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
     } else {
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist0_solve0<<<wgs0, 1024, 0, stream>>>(g, n, l.st, s); }

@@ -62,6 +62,15 @@ def test_workspace_queries_are_host_only():
     assert L.atomo_entrywise_workspace_bytes(1 << 32, C.byref(nbytes)) == binding.ATOMO_EINVAL
 
 
+def test_scratch_memory_of_a_short_gradient_is_for_its_records():
+    # 5 MiB of atomo_encode_entrywise_noalloc hold the state of a search and the records: what a long gradient alone needs is not in there
+    nbytes = C.c_size_t(0)
+    for n in (16_385, 1 << 20, 1 << 24):
+        assert binding.lib().atomo_entrywise_workspace_bytes(n, C.byref(nbytes)) == 0
+        steps = (n + 1023) // 1024 * 4
+        assert nbytes.value < 288 * steps + steps + 8 * (n // 4096 + 512) + 90_000, n     # records, counts, open draws, histograms and the rest
+
+
 def test_no_fallback_without_a_gpu():
     import torch
     if torch.cuda.is_available():
