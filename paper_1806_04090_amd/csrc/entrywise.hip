@@ -31,7 +31,7 @@ namespace atomo {
 
 namespace {
 
-constexpr int L0_BITS = 11, L1_BITS = 10, L2_BITS = 10;
+constexpr int KEY_BITS = 31, L0_BITS = 11, L1_BITS = 10, L2_BITS = 10;
 constexpr int NBUCKET = 1 << L0_BITS;        // the largest level
 constexpr int HIST_WGS = 1024;
 constexpr unsigned int DIRECT_MAX = 65536;   // elements that a pass adds to the next level's global histogram one by one
@@ -53,6 +53,8 @@ struct SolveOut {
 // Level 1 is then a histogram of the window of WINDOW_BINS of its buckets; each of the workgroups of the draws, DRAW_WGS at most, counts
 // and adds up what it finds below and above the window:
 constexpr int WINDOW_BINS = 2048;
+constexpr int MAX_SHIFT = 11;
+constexpr bool sampled_levels(int steps) { return steps == 16; }
 constexpr unsigned int NO_WINDOW = ~0u;
 constexpr int DRAW_WGS = 4096;
 struct Tally {
@@ -71,7 +73,8 @@ struct EwState {
     double budget;                // final: s - n_s
     double ratio;                 // final: budget / tail, +inf if tail == 0
     unsigned int n_open;          // records that ew_settle left to ew_write, see Segments::open
-    unsigned int window;          // sampled levels: first bucket of level 1 (key >> 10), NO_WINDOW if the sample does not say
+    unsigned int shift;           // sampled levels: key >> shift is the bucket of level 1, as many single keys those of level 2
+    unsigned int window;          // sampled levels: first bucket of level 1, NO_WINDOW if the sample does not say
     unsigned int dense;           // sampled levels: many elements are to be expected in the window
     unsigned int redo;            // sampled levels: the water level is not in the window, level 0 has been formed of all elements
 };
@@ -210,20 +213,20 @@ __device__ inline double lane_before(double v) { return dpp_moved<0x138, 0xF>(v)
 
 // One level of the search, by the T threads of a workgroup (all must call).
 // read(b, cnt, sig) gives a bucket of the level's histogram, of NB (`bins` of them in use); `first` is the number of the first one among
-// all of its level, n_above0 and sum_below0 the path chosen so far (level 0: nothing).  The result goes to `out` (LDS or global, visible to the workgroup after the call's last barrier).
+// all of its level, of 2^shift keys each, n_above0 and sum_below0 the path chosen so far (level 0: nothing).  The result goes to `out`
+// (LDS or global, visible to the workgroup after the call's last barrier).
 // scratch: LDS, (2 T / 64 + 1) x 8 bytes.
 template <int LEVEL, int T, int NB, typename READ>
-__device__ inline void solve_hist(READ read, double s, unsigned int first, int bins, unsigned long long n_above0, double sum_below0,
-                                  SolveOut* out, unsigned long long* scratch)
+__device__ inline void solve_hist(READ read, double s, unsigned int first, unsigned int shift, int bins, unsigned long long n_above0,
+                                  double sum_below0, SolveOut* out, unsigned long long* scratch)
 {
     unsigned int* cpart = (unsigned int*)scratch;
     double* spart = (double*)(scratch + T / 64);
     int& best = *(int*)(scratch + 2 * (T / 64));
-    constexpr int SHIFT = LEVEL == 0 ? 20 : LEVEL == 1 ? 10 : 0;
     constexpr int PER = NB / T;
     static_assert(PER >= 1, "one bucket per thread at least");
     const int tid = threadIdx.x;
-    auto bucket_key = [&](int b) -> unsigned int { return (first + (unsigned int)b) << SHIFT; };
+    auto bucket_key = [&](int b) -> unsigned int { return (first + (unsigned int)b) << shift; };
     // exponent shared by every element on the chosen path (level 0: part of the bucket index)
     auto bucket_exp = [&](int b) -> unsigned int { return bucket_key(b) >> 23; };
     auto bucket_lo = [&](int b) -> double { return (double)__uint_as_float(bucket_key(b)); };
@@ -339,17 +342,18 @@ template <int T>
 __device__ inline void solve_level0(const EwState* st, double s, SolveOut* out, unsigned long long* scratch)
 {
     solve_hist<0, T, 1 << L0_BITS>([&](int b, unsigned int& cnt, unsigned long long& sig) { load_bucket0(st, b, cnt, sig); },
-                                   s, 0u, 1 << L0_BITS, 0ull, 0.0, out, scratch);
+                                   s, 0u, KEY_BITS - L0_BITS, 1 << L0_BITS, 0ull, 0.0, out, scratch);
 }
 
-// Levels 1 and 2, below the bucket of the level before, from a histogram that an earlier kernel wrote.
-template <int LEVEL, int T>
-__device__ inline void solve_written(const EwState* st, double s, const SolveOut& in, SolveOut* out, unsigned long long* scratch)
+// Levels 1 and 2 from a histogram that an earlier kernel wrote: `bins` <= NB buckets of 2^shift keys, from bucket `first` on.
+template <int LEVEL, int T, int NB = 1 << L1_BITS>
+__device__ inline void solve_written(const EwState* st, double s, unsigned int first, unsigned int shift, int bins, const SolveOut& in,
+                                     SolveOut* out, unsigned long long* scratch)
 {
-    solve_hist<LEVEL, T, 1 << L1_BITS>([&](int b, unsigned int& cnt, unsigned long long& sig) {
+    solve_hist<LEVEL, T, NB>([&](int b, unsigned int& cnt, unsigned long long& sig) {
         cnt = st->cnt[LEVEL][b];
         sig = st->sig[LEVEL][b];
-    }, s, in.prefix << L1_BITS, 1 << L1_BITS, in.n_above, in.sum_below, out, scratch);
+    }, s, first, shift, bins, in.n_above, in.sum_below, out, scratch);
 }
 
 // (s - n_s) / tail, or +inf when nothing is left uncapped
@@ -379,18 +383,22 @@ __device__ inline bool enter_level2(EwState* st, double s, SolveOut* out, unsign
 {
     const SolveOut in = st->lvl[0];
     if (in.done) return false;
-    solve_written<1, 256>(st, s, in, out, scratch);
+    solve_written<1, 256>(st, s, in.prefix << L1_BITS, L2_BITS, 1 << L1_BITS, in, out, scratch);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(st, 1, *out, s);
     return !out->done;
 }
 
-// Behind it: the final ratio.
+// Behind it: the final ratio.  SAMPLED: level 1 may have had wider buckets, see EwState::shift.
+template <bool SAMPLED = false>
 __device__ inline double enter_final(EwState* st, double s, SolveOut* out, unsigned long long* scratch)
 {
     if (st->lvl[0].done) return st->ratio;
     const SolveOut in = st->lvl[1];
     if (in.done) return st->ratio;
-    solve_written<2, 256>(st, s, in, out, scratch);
+    if (SAMPLED && st->shift > L2_BITS)
+        solve_written<2, 256, 1 << MAX_SHIFT>(st, s, in.prefix << MAX_SHIFT, 0u, 1 << MAX_SHIFT, in, out, scratch);
+    else
+        solve_written<2, 256>(st, s, in.prefix << L2_BITS, 0u, 1 << L2_BITS, in, out, scratch);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(st, 2, *out, s);
     return final_ratio(s, out->n_s, out->tail);
 }
@@ -407,6 +415,7 @@ __device__ inline double enter_final(EwState* st, double s, SolveOut* out, unsig
 __device__ inline bool last_workgroup(unsigned int* ticket, unsigned int self, unsigned int members)
 {
     __shared__ int last_sh;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");       // (the compiler keeps them in front)
     __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0), other counters untouched
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -436,32 +445,42 @@ __global__ __launch_bounds__(1024) void ew_hist0_solve0(const float* __restrict_
 }
 
 // ---- sampled levels -----------------------------------------------------------------------------------
-// Level 0 only says around which values the water level lies, and 2^20 elements, 16384 pieces of 64 at places that a hash
-// chooses, say that well enough: the window of level 1 is the 2^21 values around the level that they give, 6 % and more to
+// Level 0 only says around which values the water level lies, and 2^20 elements, 32768 pieces of 32 at places that a hash
+// chooses, say that well enough: the window of level 1 is the 2^21 or 2^22 values around the level that they give, 6 to 25 % to
 // either side.  So the whole gradient is read once for search and draws, where the histogram of level 0 reads it once by itself:
 // ew_draw counts and adds up what lies below and above the window, and whether the water level is inside is then an exact
 // test.  If it is not (the sample had no part in what counts), or the sample is too scattered to say, level 0 is formed of all elements
-// and the draws are made again: more work, the same message.  Two launches more, 4.5 us each where there is nothing to do, and 12.5 for the
-// sample: encode of 34 million elements 85 -> 79 us, 50 million 117 -> 91, 2^28 520 -> 312; where the sample misleads, 2^28 take 750.
-constexpr int SAMPLE = 1 << 20, PIECE = 64, SAMPLE_WGS = 64;
-constexpr bool sampled_levels(int steps) { return steps == 16; }
+// and the draws are made again: more work, the same message.  Two launches more, 4.8 us each where there is nothing to do, and 11 for the
+// sample: encode of 34 million elements 82 -> 73 us, 67 million 168 -> 104, 2^28 529 -> 280; where the sample cannot say (40 elements hold
+// a tenth of the sum) 66 -> 82, 137 -> 155 and 458 -> 391.
+constexpr int SAMPLE = 1 << 20, PIECE = 32, SAMPLE_WGS = 64;
 constexpr long long LONG_FROM = 1ll << 25;   // elements from which on segments have 16 steps
 
-// The water level of SAMPLE elements with the budget of their share; st->window.  Few workgroups: each adds its hundreds of buckets that
-// are not empty to the global histogram one by one (256 of them 13.8 us, 64 of them 11.6).
-__global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, long long n, EwState* st, double s)
+__device__ inline double window_edge(unsigned int bucket, unsigned int shift) { return (double)__uint_as_float(bucket << shift); }
+
+// Where the level is by SAMPLE elements with the budget of their share; st->window.  Few workgroups: each adds its hundreds of buckets that
+// are not empty to the global histogram one by one.
+// How far off that may be is taken from what the workgroups find each for itself, h(level) of its own pieces, every SAMPLE_WGS-th of the
+// gradient: neighbours of a gradient may be alike (rows of an embedding of which one in a hundred is not zero), and then the pieces are the
+// sample and not their elements.  The window is the wider one, or none, where three deviations ask for it.  With 16384 pieces of 64 taken for
+// 2^20 independent elements rows of 64, three in a hundred not zero, gave a level outside the window in one call of four (34 million
+// elements 175 us, otherwise 75; now 75).  Pieces of 16 are two cache lines for one and 1 us more, with deviations 0.7 times as large.
+// own: [SAMPLE_WGS][NBUCKET / 2], of a workgroup and a pair of buckets the sum of the workgroup's elements below (float) and the number of
+// the others.
+__global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, long long n, EwState* st, double s, unsigned long long* own)
 {
     __shared__ unsigned long long acc[4 * NBUCKET];
     __shared__ SolveOut out;
-    __shared__ double vpart[16];
-    const int tid = threadIdx.x, lane = tid & 63;
+    __shared__ double spart[16];
+    __shared__ unsigned int cpart[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long spacing = n / (SAMPLE / PIECE) / PIECE;      // in pieces
     const bool vec = (((size_t)g) & 15) == 0;
     constexpr int PER = SAMPLE / SAMPLE_WGS / 4096;
     float4 x[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const unsigned int t = (u * SAMPLE_WGS + blockIdx.x) * 1024 + tid, piece = t / (PIECE / 4);
+        const unsigned int t = u * 1024 + tid, piece = t / (PIECE / 4) * SAMPLE_WGS + blockIdx.x;
         const unsigned int hash = (piece * 0x9E3779B1u) ^ ((piece * 0x85EBCA6Bu) >> 15);
         const long long at = ((long long)piece * spacing + (long long)(((unsigned long long)hash * (unsigned long long)spacing) >> 32)) * PIECE
                              + (t & (PIECE / 4 - 1)) * 4;
@@ -475,14 +494,47 @@ __global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, l
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const unsigned int key = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
-            atomicAdd(&acc[(tid & 3) * NBUCKET + (key >> 20)], (1ull << 40) | (unsigned long long)significand(key));
+            if (key) atomicAdd(&acc[(tid & 3) * NBUCKET + (key >> 20)], (1ull << 40) | (unsigned long long)significand(key));
         }
     }
     __syncthreads();
-    flush_hist<0, 4, NBUCKET, 1024>(acc, st);
+    // a pair of buckets per thread: to the global histogram, and the workgroup's own sums
+    static_assert(NBUCKET == 2048, "a pair per thread");
+    unsigned int c = 0u;
+    double v = 0.0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int b = 2 * tid + e;
+        unsigned long long w = 0ull;                             // (16384 elements: the fields of the packed word hold them)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w += acc[k * NBUCKET + b];
+        const unsigned long long sig = w & ((1ull << 40) - 1);
+        if (w) {
+            atomicAdd(&st->cnt[0][b], (unsigned int)(w >> 40));
+            atomicAdd(&st->sig[0][b], sig);
+        }
+        c += (unsigned int)(w >> 40);
+        v += sig_value(sig, (unsigned int)b >> 3);
+    }
+    const unsigned int c_scan = wave_prefix(c);
+    const double v_scan = wave_prefix(v);
+    if (lane == 63) {
+        cpart[wave] = c_scan;
+        spart[wave] = v_scan;
+    }
+    __syncthreads();
+    unsigned int from = c - c_scan;
+    double below = lane_before(v_scan);
+    for (int w = 0; w < 16; ++w) {
+        from += w < wave ? 0u : cpart[w];
+        below += w < wave ? spart[w] : 0.0;
+    }
+    __hip_atomic_store(&own[blockIdx.x * (NBUCKET / 2) + tid], (unsigned long long)from << 32 | __float_as_uint((float)below), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
     if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
     const double share = s * ((double)SAMPLE / (double)n);
     solve_level0<1024>(st, share, &out, acc);
+    if (wave != 0) return;
     const SolveOut r = out;
     double tau;
     if (r.done) {
@@ -492,36 +544,38 @@ __global__ __launch_bounds__(1024) void ew_sample(const float* __restrict__ g, l
         const double h_hi = r.hi * (share - (double)r.n_above) - r.sum_below - r.sum;
         tau = r.lo + (r.hi - r.lo) * (h_lo / (h_lo - h_hi));
     }
-    // h is a sum of min(|x|, tau) over the sample, whose variance is at most that of the squares
-    double v = 0.0;
-    for (int b = tid; b < NBUCKET; b += 1024) {
-        unsigned int cnt;
-        unsigned long long sig;
-        load_bucket0(st, b, cnt, sig);
-        const double m = fmin(tau, (double)__uint_as_float((unsigned int)(b + 1) << 20));      // (beyond the last number: NaN, and tau)
-        v += (double)cnt * m * m;
-    }
-    v = wave_prefix(v);
-    if (lane == 63) vpart[tid >> 6] = v;
-    __syncthreads();
-    if (tid != 0) return;
-    for (int w = 1; w < 16; ++w) v = vpart[w] + (w == 1 ? vpart[0] : v);
+    const bool in_range = tau > 0x1p-94 && tau < 0x1p100;       // (not NaN)
+    const unsigned int key = in_range ? __float_as_uint((float)tau) : 0u;
+    static_assert(MAX_SHIFT == L2_BITS + 1, "a window reaches over one or two buckets of level 0 to either side");
+    unsigned int near = 0u;
+    unsigned long long sig;
+    if (in_range && lane < 5) load_bucket0(st, (int)(key >> 20) + lane - 2, near, sig);
+    // sum of min(|x|, level) over each workgroup's elements (those of the pair of buckets count as the level); their variance
+    static_assert(SAMPLE_WGS == 64, "one per lane");
+    const unsigned long long o = __hip_atomic_load(&own[lane * (NBUCKET / 2) + r.prefix / 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double h = (double)__uint_as_float((unsigned int)o) + tau * (double)(unsigned int)(o >> 32);
+    auto total = [](double v) {
+        const unsigned long long u = (unsigned long long)__double_as_longlong(wave_prefix(v));
+        return __longlong_as_double((long long)((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(u >> 32), 63) << 32 |
+                                                (unsigned int)__builtin_amdgcn_readlane((int)u, 63)));
+    };
+    const double apart = h - total(h) / SAMPLE_WGS, variance = total(apart * apart) * ((double)SAMPLE_WGS / (SAMPLE_WGS - 1));
     const double above = r.done ? (double)r.n_s : (double)r.n_above + (double)r.count * ((r.hi - tau) / (r.hi - r.lo));
-    // (a window of 1024 buckets to either side is 2^-4 of the level at least, and 2^32 over its values a float; a NaN says no)
-    const bool sure = tau > 0x1p-94 && tau < 0x1p100 && 4.0 * sqrt(v) < 0x1p-4 * tau * (share - above);
-    const unsigned int key = sure ? __float_as_uint((float)tau) : 0u;
-    st->window = sure ? (key >> 10) - WINDOW_BINS / 2 : NO_WINDOW;
-    double near = 0.0;
-    for (unsigned int b = (key >> 20) - (sure ? 1u : 0u); b <= (key >> 20) + 1u; ++b) {
-        unsigned int cnt;
-        unsigned long long sig;
-        load_bucket0(st, (int)b, cnt, sig);
-        near += (double)cnt;
+    // the window is 2^-4 to 2^-3 of the level to either side, with the wider buckets twice that; 2^32 over its values is a float
+    const double off = 3.0 * sqrt(variance);
+    auto holds = [&](unsigned int shift) {
+        const unsigned int first = (key >> shift) - WINDOW_BINS / 2;
+        return off < fmin(tau - window_edge(first, shift), window_edge(first + WINDOW_BINS, shift) - tau) * (share - above);
+    };
+    const bool narrow = in_range && holds(L2_BITS);
+    near = wave_prefix(narrow && (lane == 0 || lane == 4) ? 0u : near);
+    if (lane == 63) {
+        const unsigned int shift = narrow ? L2_BITS : MAX_SHIFT;
+        st->window = in_range && holds(shift) ? (key >> shift) - WINDOW_BINS / 2 : NO_WINDOW;
+        st->shift = shift;
+        st->dense = (double)near * ((double)n / SAMPLE) > (double)DIRECT_MAX;
     }
-    st->dense = near * ((double)n / SAMPLE) > (double)DIRECT_MAX;
 }
-
-__device__ inline double window_edge(unsigned int window) { return (double)__uint_as_float(window << 10); }
 
 struct WindowPath {
     double n_above;               // elements above the window
@@ -530,7 +584,7 @@ struct WindowPath {
 };
 
 // The tallies of all workgroups, in an order that is always the same.  All 1024 threads call; scratch: LDS, 4 * 16 doubles.
-__device__ inline WindowPath window_path(const Tally* tally, unsigned int tallies, unsigned int window, double s, double* scratch)
+__device__ inline WindowPath window_path(const Tally* tally, unsigned int tallies, unsigned int window, unsigned int shift, double s, double* scratch)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -550,7 +604,7 @@ __device__ inline WindowPath window_path(const Tally* tally, unsigned int tallie
         v[k] = scratch[k * 16];
         for (int w = 1; w < 16; ++w) v[k] += scratch[k * 16 + w];
     }
-    const double lo = window_edge(window), hi = window_edge(window + WINDOW_BINS);
+    const double lo = window_edge(window, shift), hi = window_edge(window + WINDOW_BINS, shift);
     WindowPath p;
     p.n_above = v[3] - v[2];
     p.sum_below = v[0];
@@ -567,7 +621,7 @@ __global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, 
     __shared__ SolveOut out;
     const unsigned int window = st->window;
     if (window != NO_WINDOW) {
-        const WindowPath p = window_path(tally, tallies, window, s, (double*)acc);
+        const WindowPath p = window_path(tally, tallies, window, st->shift, s, (double*)acc);
         if (p.holds) {
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 SolveOut& l = st->lvl[0];
@@ -589,6 +643,7 @@ __global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, 
     if (threadIdx.x == 0) {
         publish(st, 0, out, s);
         st->window = out.prefix << L1_BITS;
+        st->shift = L2_BITS;
         st->redo = 1u;
     }
 }
@@ -876,7 +931,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     if (AFTER == SAMPLED) clear_level(st, 0);
     if (AFTER != REDO) clear_level(st, 2);
     if (blockIdx.x == 0 && tid == 0) st->n_open = 0u;
-    const unsigned int window = AFTER == SAMPLED ? st->window : so.prefix << L1_BITS;
+    const unsigned int window = AFTER == SAMPLED ? st->window : so.prefix << L1_BITS, shift = AFTER == SAMPLED ? st->shift : L2_BITS;
     if (AFTER == SAMPLED && window == NO_WINDOW) return;
     const bool done = AFTER != SAMPLED && so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
@@ -887,8 +942,8 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     // only sends a few more coordinates to ew_settle, which decides with the exact formula.
     double ratio_lo, ratio_hi;
     if (AFTER == SAMPLED) {
-        ratio_lo = 1.0 / window_edge(window + WINDOW_BINS);
-        ratio_hi = 1.0 / window_edge(window);
+        ratio_lo = 1.0 / window_edge(window + WINDOW_BINS, shift);
+        ratio_hi = 1.0 / window_edge(window, shift);
     } else if (done) {
         ratio_lo = ratio_hi = final_ratio(s, so.n_s, so.tail);
     } else {
@@ -903,7 +958,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     const bool tiny_level = AFTER != SAMPLED && !(r_word < __int_as_float(0x7f800000));
     // Few elements in the bucket: straight into the global histogram, where they hardly ever meet.  Many: through LDS.
     const bool through_lds = AFTER == SAMPLED ? st->dense != 0u : !done && so.count > DIRECT_MAX;
-    const unsigned int first_key = window << 10;
+    const unsigned int first_key = window << shift;
     double below = 0.0, inside = 0.0;                            // this lane's
     unsigned int n_in = 0u, n_from = 0u;
     for (long long quad = blockIdx.x; quad < quads; quad += AFTER == EXACT ? quads : gridDim.x) {
@@ -929,7 +984,7 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
                     sl.word[pos] = (unsigned short)(offset | (surely_below(u, x, r_lo) ? FLAG_BIT : 0u));
                 }
                 if (AFTER == SAMPLED && key >= first_key) ++n_from;
-                const unsigned int b = (key >> 10) - window;
+                const unsigned int b = (key >> shift) - window;
                 if (b < (unsigned int)BINS && !done) {
                     if (AFTER == SAMPLED) {
                         ++n_in;
@@ -1061,8 +1116,10 @@ template <int STEPS>
 __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, long long n, EwState* st, double s,
                                                   unsigned long long stream_id, unsigned long long seed, Segments sg)
 {
-    __shared__ unsigned int cnt[1 << L2_BITS];
-    __shared__ unsigned long long sig[1 << L2_BITS];
+    constexpr bool SAMPLED_LEVELS = sampled_levels(STEPS);
+    constexpr int BINS = 1 << (SAMPLED_LEVELS ? MAX_SHIFT : L2_BITS);
+    __shared__ unsigned int cnt[BINS];
+    __shared__ unsigned long long sig[BINS];
     __shared__ unsigned int wsum[4];
     __shared__ Group gr;
     __shared__ SolveOut out;
@@ -1075,23 +1132,20 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     bool search = false;
     bool listed = true;
     unsigned int prefix = 0u, on_path = 0u;
+    const unsigned int shift = SAMPLED_LEVELS ? st->shift : L2_BITS;
     if (in.done) {
         ratio_lo = ratio_hi = st->ratio;
     } else {
-        if constexpr (sampled_levels(STEPS)) {
-            solve_hist<1, 256, WINDOW_BINS>([&](int b, unsigned int& cnt, unsigned long long& sig) {
-                cnt = st->cnt[1][b];
-                sig = st->sig[1][b];
-            }, s, st->window, st->redo ? 1 << L1_BITS : WINDOW_BINS, in.n_above, in.sum_below, &out, scratch);
-        } else {
-            solve_written<1, 256>(st, s, in, &out, scratch);
-        }
+        if constexpr (SAMPLED_LEVELS)
+            solve_written<1, 256, WINDOW_BINS>(st, s, st->window, shift, st->redo ? 1 << L1_BITS : WINDOW_BINS, in, &out, scratch);
+        else
+            solve_written<1, 256>(st, s, in.prefix << L1_BITS, shift, 1 << L1_BITS, in, &out, scratch);
         if (blockIdx.x == 0 && tid == 0) publish(st, 1, out, s);
         search = out.done == 0;
         prefix = out.prefix;
         on_path = out.count;
         if (search) {                                            // (the sums of the search are good to 2^-40)
-            const double lo = (double)__uint_as_float(prefix << L2_BITS), hi = (double)__uint_as_float((prefix + 1) << L2_BITS);
+            const double lo = (double)__uint_as_float(prefix << shift), hi = (double)__uint_as_float((prefix + 1) << shift);
             ratio_lo = hi < __longlong_as_double(0x7FF0000000000000LL) ? 1.0 / hi * (1.0 - 0x1p-30) : 0.0;
             ratio_hi = lo > 0.0 ? 1.0 / lo * (1.0 + 0x1p-30) : __longlong_as_double(0x7FF0000000000000LL);
             // (about so many draws lie between the bounds, half of the list at most unless the level is below the normal range)
@@ -1102,12 +1156,12 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     }
     const bool through_lds = search && on_path > DIRECT_MAX;
     if (through_lds)
-        for (int b = tid; b < (1 << L2_BITS); b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
+        for (int b = tid; b < BINS; b += 256) { cnt[b] = 0u; sig[b] = 0ull; }
     __syncthreads();
     auto visit = [&](float x) {
         const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
-        if ((key >> L2_BITS) == prefix) {
-            const unsigned int b = key & ((1 << L2_BITS) - 1);
+        if ((key >> shift) == prefix) {
+            const unsigned int b = key & ((1u << shift) - 1u);
             atomicAdd(through_lds ? &cnt[b] : &st->cnt[2][b], 1u);
             atomicAdd(through_lds ? &sig[b] : &st->sig[2][b], (unsigned long long)significand(key));
         }
@@ -1199,7 +1253,7 @@ __global__ __launch_bounds__(256) void ew_settle(const float* __restrict__ g, lo
     __syncthreads();
     if (tid == 0) sg.group_kept[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
     if (through_lds) {
-        for (int b = tid; b < (1 << L2_BITS); b += 256) {
+        for (int b = tid; b < BINS; b += 256) {
             if (cnt[b]) {
                 atomicAdd(&st->cnt[2][b], cnt[b]);
                 atomicAdd(&st->sig[2][b], sig[b]);
@@ -1238,7 +1292,7 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
         __shared__ unsigned long long scratch[2 * 4 + 1];
         n_open = st->n_open;
         if (tid < MAX_GROUP) more[tid] = 0u;
-        ratio = enter_final(st, s, &out, scratch);
+        ratio = enter_final<sampled_levels(STEPS)>(st, s, &out, scratch);
         __syncthreads();
     } else {
         ratio = st->ratio;
@@ -1367,6 +1421,13 @@ __global__ __launch_bounds__(256) void ew_write(const float* __restrict__ g, lon
     }
 }
 
+// The kernels of a gradient below 2^25 elements lie one behind the other: together they are 59 KB of instructions, and apart they drive one
+// another out of the 64 KB cache (11.17 million elements with their decode 51.6 us where others lay between, 50.3 so).
+template __global__ void ew_draw<4, EXACT>(const float* __restrict__, long long, EwState*, double, unsigned long long, unsigned long long, Segments);
+template __global__ void ew_settle<4>(const float* __restrict__, long long, EwState*, double, unsigned long long, unsigned long long, Segments);
+template __global__ void ew_write<4, false>(const float* __restrict__, long long, EwState*, double, unsigned long long, unsigned long long, Segments,
+                                            long long, unsigned int* __restrict__, float* __restrict__, long long*, int*);
+
 // ---- one workgroup for everything ----------------------------------------------------------------------
 // Up to LOCAL_MAX elements are held in the registers of one workgroup: the three levels of the search run in LDS one behind
 // the other, without a launch, a ticket or a global atomic between them.  9610 elements: 9.6 us in all (load 0.6, level 0 3.9,
@@ -1410,7 +1471,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
                 sig += v & ((1ull << 40) - 1);
             }
         }
-    }, s, 0u, 1 << L0_BITS, 0ull, 0.0, &sc.out, sc.solve);
+    }, s, 0u, KEY_BITS - L0_BITS, 1 << L0_BITS, 0ull, 0.0, &sc.out, sc.solve);
     auto read = [&](int b, unsigned int& cnt, unsigned long long& sig) {
         cnt = (unsigned int)(sc.hist[b] >> 40);
         sig = sc.hist[b] & ((1ull << 40) - 1);
@@ -1422,7 +1483,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
     for (int e = 0; e < LOCAL_PER; ++e)
         if (e < per && (key[e] >> 20) == in.prefix) add((key[e] >> 10) & ((1 << L1_BITS) - 1), key[e]);
     __syncthreads();
-    solve_hist<1, LOCAL_T, 1 << L1_BITS>(read, s, in.prefix << L1_BITS, 1 << L1_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
+    solve_hist<1, LOCAL_T, 1 << L1_BITS>(read, s, in.prefix << L1_BITS, L2_BITS, 1 << L1_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
     if (sc.out.done) return;
     in = sc.out;
     clear(1 << L2_BITS);
@@ -1430,7 +1491,7 @@ __device__ inline void local_water_level(const unsigned int (&key)[LOCAL_PER], i
     for (int e = 0; e < LOCAL_PER; ++e)
         if (e < per && (key[e] >> 10) == in.prefix) add(key[e] & ((1 << L2_BITS) - 1), key[e]);
     __syncthreads();
-    solve_hist<2, LOCAL_T, 1 << L2_BITS>(read, s, in.prefix << L2_BITS, 1 << L2_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
+    solve_hist<2, LOCAL_T, 1 << L2_BITS>(read, s, in.prefix << L2_BITS, 0u, 1 << L2_BITS, in.n_above, in.sum_below, &sc.out, sc.solve);
 }
 
 __device__ inline unsigned int magnitude(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
@@ -1800,6 +1861,7 @@ __global__ __launch_bounds__(256) void lq_draw(const float* __restrict__ g, long
 struct EwLayout {
     EwState* st;
     double* lq_partial;           // [LQ_WGS] per-workgroup parts of |g|_q
+    unsigned long long* own;      // [SAMPLE_WGS][NBUCKET / 2] sampled levels, see ew_sample
     Segments sg;
     int steps;                    // float4 steps per segment
     size_t bytes;
@@ -1826,7 +1888,8 @@ EwLayout ew_layout(void* base, int64_t n, size_t limit = 0)
     l.sg.group_kept = carve.take<unsigned int>((size_t)l.sg.n_groups);
     l.sg.open_max = (unsigned)(n / 4096 + 512);                  // (twice of what is to be expected of a message of all elements)
     l.sg.open = carve.take<EwOpen>(l.sg.open_max);
-    l.sg.tally = l.steps == 16 ? carve.take<Tally>(DRAW_WGS) : nullptr;
+    l.sg.tally = sampled_levels(l.steps) ? carve.take<Tally>(DRAW_WGS) : nullptr;
+    l.own = sampled_levels(l.steps) ? carve.take<unsigned long long>(SAMPLE_WGS * NBUCKET / 2) : nullptr;
     l.sg.spins = SPIN_COUNTED;
     size_t step_bytes = STEP_BYTES;
     if (limit) step_bytes = std::min<size_t>(step_bytes, (limit - carve.off - 256) / ((size_t)l.sg.n_seg * l.steps) & ~(size_t)7);
@@ -1885,7 +1948,7 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
     if (clear_first) { ProfScope ps(ctx, ATOMO_K_EW_SOLVE, stream); ew_clear<<<(3 * NBUCKET + 255) / 256, 256, 0, stream>>>(l.st); }
     if (long_seg) {
         const unsigned draws = std::min<unsigned>(quads, DRAW_WGS);
-        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE_WGS, 1024, 0, stream>>>(g, n, l.st, s); }
+        { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE_WGS, 1024, 0, stream>>>(g, n, l.st, s, l.own); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, SAMPLED><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, sg.tally, draws, (unsigned)wgs0); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
