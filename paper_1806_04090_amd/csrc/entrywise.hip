@@ -57,6 +57,7 @@ constexpr int MAX_SHIFT = 11;
 constexpr bool sampled_levels(int steps) { return steps == 16; }
 constexpr unsigned int NO_WINDOW = ~0u;
 constexpr int DRAW_WGS = 4096;
+constexpr int REDO_WGS = 1536;               // of the second draws: what the chip holds at once
 struct Tally {
     double below, inside;         // sums of the elements below the window and inside
     unsigned int n_in, n_from;    // how many inside, how many inside or above
@@ -92,8 +93,10 @@ __device__ inline unsigned int significand(unsigned int key)
     return e ? (mant | 0x800000u) : mant;
 }
 
-// Histograms: level 2 is cleared by the pass that forms level 1, levels 0 and 1 by the last kernel of a call (their readers
-// have run by then).
+// A call finds histograms of zeros.  Level 2, which ew_settle forms, is cleared by the draws in front of it (probabilities: by the pass that
+// forms level 1), levels 0 and 1 by the last kernel of a call (their readers have run by then).  Sampled levels: the first draws clear
+// level 0, which ew_confirm may form again, of all elements; where it does it clears level 1, all 2048 buckets of the window, of which the
+// draws behind it use 1024 (ew_settle looks at the others too).
 __device__ inline void clear_level(EwState* st, int level)
 {
     for (int i = blockIdx.x * 256 + threadIdx.x; i < NBUCKET; i += gridDim.x * 256) {
@@ -136,7 +139,8 @@ __device__ inline void flush_hist(const unsigned long long* acc, EwState* st)
 
 // Level-LEVEL histogram of the elements on the path `prefix`, by the TPB threads of workgroup `self` of `members` (all call):
 // accumulated in the LDS array acc (COPIES x NB packed words), then added to the global histogram.
-template <int LEVEL, int TPB>
+// ZEROS: zeros are counted (for the search they are not there; a test for each element costs more than they do where there are few).
+template <int LEVEL, int TPB, bool ZEROS = true>
 __device__ inline void hist_body(const float* __restrict__ g, long long n, EwState* st, unsigned long long* acc, unsigned int prefix,
                                  unsigned int self, unsigned int members)
 {
@@ -154,6 +158,7 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
     auto visit = [&](float x) {
         const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
         const unsigned long long word = (1ull << 40) | (unsigned long long)significand(key);
+        if (!ZEROS && key == 0u) return;
         if (LEVEL == 0) {
             atomicAdd(&acc[copy + (key >> SHIFT)], word);
         } else {
@@ -635,7 +640,7 @@ __global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, 
     }
     for (unsigned int self = blockIdx.x; self < members; self += gridDim.x) {
         __syncthreads();
-        hist_body<0, 1024>(g, n, st, acc, 0u, self, members);
+        hist_body<0, 1024, false>(g, n, st, acc, 0u, self, members);
     }
     clear_level(st, 1);
     if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
@@ -925,14 +930,17 @@ __global__ __launch_bounds__(256) void ew_draw(const float* __restrict__ g, long
     const long long quads = (sg.n_seg + 3) / 4;
     long long seg = (long long)blockIdx.x * 4 + wave;
     bool whole = vec && (seg + 1) * STEPS * STEP <= n;
+    if (AFTER == SAMPLED && st->window == NO_WINDOW) {           // (ahead of the loads: 11.7 us of them where it was not, now 5)
+        clear_level(st, 0);
+        return;                                                  // (the rest is for the next pass)
+    }
     float4 xv[4];                                                // (in flight while the search's result arrives)
     load_steps<STEPS == 16>(g, seg * STEPS * 64, n, whole, vec, xv);
     const SolveOut so = st->lvl[0];
     if (AFTER == SAMPLED) clear_level(st, 0);
-    if (AFTER != REDO) clear_level(st, 2);
+    clear_level(st, 2);
     if (blockIdx.x == 0 && tid == 0) st->n_open = 0u;
     const unsigned int window = AFTER == SAMPLED ? st->window : so.prefix << L1_BITS, shift = AFTER == SAMPLED ? st->shift : L2_BITS;
-    if (AFTER == SAMPLED && window == NO_WINDOW) return;
     const bool done = AFTER != SAMPLED && so.done != 0;
     const double inf = __longlong_as_double(0x7FF0000000000000LL);
     // Single-precision brackets of the p that the final ratio will give, p = fl32(|g| ratio), scaled by 2^24 like the
@@ -1951,7 +1959,7 @@ int enqueue_encode_entrywise(atomo_ctx* ctx, const float* g, double s, uint64_t 
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_sample<<<SAMPLE_WGS, 1024, 0, stream>>>(g, n, l.st, s, l.own); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, SAMPLED><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_confirm<<<256, 1024, 0, stream>>>(g, n, l.st, s, sg.tally, draws, (unsigned)wgs0); }
-        { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<draws, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
+        { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<16, REDO><<<std::min<unsigned>(draws, REDO_WGS), 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }
     } else {
         { ProfScope ps(ctx, ATOMO_K_EW_HIST, stream); ew_hist0_solve0<<<wgs0, 1024, 0, stream>>>(g, n, l.st, s); }
         { ProfScope ps(ctx, ATOMO_K_EW_SAMPLE, stream); ew_draw<4, EXACT><<<quads, 256, 0, stream>>>(g, n, l.st, s, stream_id, seed, sg); }

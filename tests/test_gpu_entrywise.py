@@ -352,9 +352,8 @@ def alike_neighbours(rng, n, length, active, noise):
     return g.ravel()[:n]
 
 
-@pytest.mark.parametrize("length, active, noise, keep, seed", [(64, 0.03, 0.0, 0.01, 0), (64, 0.03, 0.0, 0.01, 1), (64, 0.03, 0.0, 0.01, 2),
-                                                               (64, 0.02, 0.0, 0.001, 2), (64, 0.02, 1e-2, 0.01, 2), (512, 0.02, 1e-2, 0.01, 0),
-                                                               (512, 0.02, 0.0, 0.001, 0), (512, 0.1, 0.0, 0.01, 0)])
+@pytest.mark.parametrize("length, active, noise, keep, seed", [(64, 0.03, 0.0, 0.01, 0), (64, 0.02, 0.0, 0.001, 2), (64, 0.02, 1e-2, 0.01, 2),
+                                                               (512, 0.02, 0.0, 0.001, 0)])
 def test_a_long_gradient_whose_neighbours_are_alike_is_read_once(length, active, noise, keep, seed):
     """Inputs at which 16384 pieces of 64, taken for 2^20 independent elements, were sure of a level that is 6 to 12 % off, or would say
     that they cannot tell.  Those were read two and three times: 1.7 to 2.4 times as long."""
@@ -368,6 +367,20 @@ def test_a_long_gradient_whose_neighbours_are_alike_is_read_once(length, active,
     got = msg.to_host()
     assert h["count"] == got["count"] and np.array_equal(h["idx"], got["idx"]) and np.array_equal(h["val"], got["val"])
     assert time < 1.5 * time_plain, (time, time_plain)
+
+
+@pytest.mark.parametrize("length, active", [(64, 0.005), (64, 0.012)])
+def test_a_long_gradient_of_zeros_takes_no_longer_for_a_sample_that_cannot_say(length, active):
+    """Fewer elements that are not zero than the budget, or about as many: no sample finds a level, and level 0 is formed of all elements,
+    most of them in one bucket.  Twice the time of a gradient without zeros where those are counted, one by one; less without."""
+    n = 2 ** 25 + 1
+    g = alike_neighbours(np.random.default_rng(7), n, length, active, 0.0)
+    plain = np.random.default_rng(7).standard_normal(n, dtype=np.float32)
+    msg = binding.alloc_entrywise_message(n, n // 10, "cuda")
+    time_plain = encode_time(dev(plain), n / 100, msg)
+    time = encode_time(dev(g), n / 100, msg)
+    parity(g, n / 100, 5, 2, capacity=n // 10)
+    assert time < 1.6 * time_plain, (time, time_plain)
 
 
 @pytest.mark.parametrize("kind, extra", [("heavy", 0), ("heavy", 4099), ("all_alike", 3), ("many_near_the_level", 1), ("above_the_window", 2),
