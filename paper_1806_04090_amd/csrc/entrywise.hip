@@ -588,32 +588,38 @@ struct WindowPath {
     bool holds;                   // the water level is inside
 };
 
-// The tallies of all workgroups, in an order that is always the same.  All 1024 threads call; scratch: LDS, 4 * 16 doubles.
-__device__ inline WindowPath window_path(const Tally* tally, unsigned int tallies, unsigned int window, unsigned int shift, double s, double* scratch)
+// The tallies of all workgroups, in an order that is always the same.  All 1024 threads call; scratch: LDS, 5 * 16 doubles.
+// The sum below is that of its parts to multiples of 2^-52 of a bound, which add up without rounding, and that of the rest, which does not
+// count: rounded once (as one sum up to 2e-16 off; by level 0, of sums of buckets that are exact, up to 7e-17 for gradients of several kinds).
+__device__ inline WindowPath window_path(const Tally* tally, unsigned int tallies, unsigned int window, unsigned int shift, long long n, double s,
+                                         double* scratch)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    const double lo = window_edge(window, shift), hi = window_edge(window + WINDOW_BINS, shift);
+    const unsigned long long bound = (unsigned long long)__double_as_longlong(lo * (double)n);
+    const double unit = __longlong_as_double((long long)(((bound >> 52) + 2) << 52));          // more than twice the sum, a power of two
+    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < DRAW_WGS; k += 1024) {
         const Tally t = k + threadIdx.x < tallies ? tally[k + threadIdx.x] : Tally{0.0, 0.0, 0u, 0u};
-        v[0] += t.below; v[1] += t.inside; v[2] += (double)t.n_in; v[3] += (double)t.n_from;
+        const double part = (t.below + unit) - unit;
+        v[0] += part; v[1] += t.inside; v[2] += (double)t.n_in; v[3] += (double)t.n_from; v[4] += t.below - part;
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 5; ++k) {
         v[k] = wave_prefix(v[k]);
         if (lane == 63) scratch[k * 16 + wave] = v[k];
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 5; ++k) {
         v[k] = scratch[k * 16];
         for (int w = 1; w < 16; ++w) v[k] += scratch[k * 16 + w];
     }
-    const double lo = window_edge(window, shift), hi = window_edge(window + WINDOW_BINS, shift);
     WindowPath p;
     p.n_above = v[3] - v[2];
-    p.sum_below = v[0];
-    p.holds = lo * (s - v[3]) - v[0] <= 0.0 && hi * (s - p.n_above) - v[0] - v[1] > 0.0;
+    p.sum_below = v[0] + v[4];
+    p.holds = lo * (s - v[3]) - p.sum_below <= 0.0 && hi * (s - p.n_above) - p.sum_below - v[1] > 0.0;
     return p;
 }
 
@@ -626,7 +632,7 @@ __global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, 
     __shared__ SolveOut out;
     const unsigned int window = st->window;
     if (window != NO_WINDOW) {
-        const WindowPath p = window_path(tally, tallies, window, st->shift, s, (double*)acc);
+        const WindowPath p = window_path(tally, tallies, window, st->shift, n, s, (double*)acc);
         if (p.holds) {
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 SolveOut& l = st->lvl[0];

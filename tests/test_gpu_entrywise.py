@@ -329,6 +329,28 @@ def test_a_tiny_water_level_takes_about_as_long_as_another(n, down):
     assert times[1] < (1.5 if n < 2 ** 25 else 2.2) * times[0], times
 
 
+@pytest.mark.parametrize("seed", [1, 2])
+def test_the_sum_below_a_sampled_window_is_good_to_the_last_bit(seed):
+    """All elements lie below the level, from 1 down to 2^-30, and the budget is such that p of the largest one is rounded one way with their sum
+    rounded once and the other way with a sum that is one unit of 2^-53 larger (or smaller: the second budget).  Added up as one number
+    over the workgroups the sum of seed 1 is one unit too large, that of seed 2 one too small."""
+    n = 2 ** 25
+    g = np.exp2(np.random.default_rng(seed).uniform(-30, 0, n)).astype(np.float32)
+    at, total = int(np.argmax(g)), float(g.astype(np.longdouble).sum())
+    a = float(g[at])
+    for other in (np.nextafter(total, np.inf), np.nextafter(total, 0.0)):
+        p, s = np.float32(a * 1000.0 / total), 0.0
+        while not s:
+            p = np.nextafter(p, np.float32(1.0))
+            tie = (float(p) + float(np.nextafter(p, np.float32(1.0)))) / 2
+            tries = tie * total / a + np.arange(-8, 9) * np.spacing(1000.0)
+            rounded = [(tries / x * a).astype(np.float32) for x in (total, other)]
+            s = next(iter(tries[rounded[0] != rounded[1]]), 0.0)
+        want = np.float32(s / total * a)
+        _, p_gpu, status = encode(g, float(s), 5, 2, capacity=4000)
+        assert status == 0 and p_gpu[at] == want
+
+
 PIECE, PIECES = 32, 2 ** 15
 
 
