@@ -356,7 +356,7 @@ __device__ inline double dpp_or_one(double x)
 // characteristic polynomials (every lane runs through the recurrence and keeps its own step); the two are joined where they
 // meet with the smallest pivot, and the entries are products of quotients from there, by scans.  The Rayleigh quotient
 // corrects lam, for up to three rounds; one is enough as a rule, from where the eigenvalue is in its cell: if its residual is under `close`,
-// which turns the vector by less than half a unit of fp32, and passes.  (Always three, from the middle of the cell: 15 thousand cycles.)
+// which turns the vector by less than 1e-9, a sixtieth of a unit of fp32, and passes.  (Always three, from the middle of the cell: 15 thousand cycles.)
 // t: as for sturm_below (n entries after the padding), e: off-diagonal.  good: of the residual |T z - lam z|; accepted: it passes.
 __device__ inline double twisted_vector(const doublex2* t, const double* e, int n, double lam, double close, double good, const KeptApart& apart,
                                         bool& accepted)
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(ST) void thin_solve(const ThinMat* mats, double s, 
             const KeptApart apart(own, a > 0 ? lam[kept_at[a - 1]] : -1.0, a + 1 < count ? lam[kept_at[a + 1]] : -1.0,
                                   2.384185791015625e-07);
             bool good = false;
-            const double z = twisted_vector(T + pad, te, r, fine[at], 1.5e-8 * gap, 1e-12 * lam[0], apart, good);
+            const double z = twisted_vector(T + pad, te, r, fine[at], 1e-9 * gap, 1e-12 * lam[0], apart, good);
             if (lane < THIN_R) A[1][a * LD + lane] = z;
             if (lane == 0 && !good) accepted = 0;
         }

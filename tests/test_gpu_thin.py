@@ -98,7 +98,7 @@ def test_beside_groups_the_bits_of_a_call_of_their_own(thin):
 @pytest.mark.parametrize("apart", [0.1, 1e-3, 1e-5])
 def test_vectors_of_neighbours_near_and_far(shape, apart):
     """Kept singular vectors against those of LAPACK, at the edges of the columns that a lane holds.  A vector of an eigenvalue found to a
-    fraction of its cell takes one round, a neighbour in the way up to three; either way it may turn by 1.5e-8 (the first round's bound) and by
+    fraction of its cell takes one round, a neighbour in the way up to three; either way it may turn by 1e-9 (the first round's bound) and by
     the rounding of the Gram matrix (1e-14 of the largest eigenvalue over the distance to the next), and every entry is rounded to fp32."""
     rng = np.random.default_rng(shape[0] + shape[1] + int(1e6 * apart))
     r = min(shape)
@@ -115,6 +115,6 @@ def test_vectors_of_neighbours_near_and_far(shape, apart):
         u, v = host["U"][:, k].astype(np.float64), host["V"][:, k].astype(np.float64)
         gap = np.min(np.abs(np.delete(S, i) ** 2 - S[i] ** 2))
         sign = np.sign(u @ U[:, i])
-        bound = 1.5e-8 + 6e-8 + 1e-14 * S[0] ** 2 / gap
+        bound = 1e-9 + 6e-8 + 1e-14 * S[0] ** 2 / gap
         assert np.linalg.norm(sign * u - U[:, i]) < bound * (1.0 + S[0] / S[i])
         assert np.linalg.norm(sign * v - Vt[i]) < bound * (1.0 + S[0] / S[i])
