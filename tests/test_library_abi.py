@@ -166,19 +166,67 @@ def test_the_reduction_to_tridiagonal_form_keeps_its_registers():
         assert r[".private_segment_fixed_size"] == 0 and r[".vgpr_spill_count"] == 0, name
 
 
+TRANSCENDENTAL = ("v_rcp_", "v_rsq_", "v_sqrt_", "v_exp_", "v_log_", "v_sin_", "v_cos_")
+
+
+def registers(operand):
+    """Vector registers that an operand of a disassembled instruction names."""
+    m = re.match(r"-?\|?v(?:\[(\d+):(\d+)\]|(\d+))", operand)
+    return set() if not m else {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+
+
+def too_early(code):
+    """Of a list of (instruction, operands, address): the products with a broadcast operand, and what stands in front of each of them, on
+    some path, with fewer wait states between than it takes.  Two after a vector instruction that writes the broadcast operand, five
+    after one that writes EXEC, one after a transcendental one that writes any operand, 18 after a matrix instruction that does."""
+    sources = {}
+    for i, (op, args, addr) in enumerate(code):
+        if op.startswith(("s_branch", "s_cbranch")):
+            offset = int(args.split()[0])
+            sources.setdefault(addr + 4 + 4 * (offset - 65536 if offset >= 32768 else offset), []).append(i)
+
+    def in_front(i, states):
+        """(instruction, wait states between it and instruction i) for all with fewer than `states`"""
+        most, left = {}, [(i, 0)]
+        while left:
+            at, between = left.pop()
+            before = list(sources.get(code[at][2], []))
+            if at > 0 and code[at - 1][0] not in ("s_branch", "s_endpgm"):
+                before.append(at - 1)
+            for j in before:
+                if between < most.get(j, states):
+                    most[j] = between
+                    left.append((j, between + (int(code[j][1]) + 1 if code[j][0] == "s_nop" else 1)))
+        return most.items()
+
+    found, products = [], 0
+    for i, (op, args, addr) in enumerate(code):
+        if op != "v_fmac_f64_dpp":
+            continue
+        products += 1
+        operands = [registers(x.strip()) for x in args.split(" row_")[0].split(",")]
+        broadcast, all_of_them = operands[1], set().union(*operands)
+        for j, between in in_front(i, 18):
+            what, how = code[j][0], [x.strip() for x in code[j][1].split(",")]
+            if not what.startswith("v_"):
+                continue
+            written = registers(how[0])
+            if "_swap" in what:                                  # (v_swap, v_permlane16_swap, v_permlane32_swap)
+                written |= registers(how[1])
+            if (between < 2 and written & broadcast or between < 5 and (what.startswith("v_cmpx") or how[0].startswith("exec"))
+                    or between < 1 and what.startswith(TRANSCENDENTAL) and written & all_of_them
+                    or what.startswith(("v_mfma", "v_smfma")) and written & all_of_them):
+                found.append((hex(addr), op, args, code[j]))
+    return found, products
+
+
 def test_products_with_a_broadcast_operand_wait_for_it(tmp_path):
-    """v_fmac_f64 with row_newbcast comes from inline assembly (svd_device.h), for which the compiler keeps no wait states: two have to lie
-    between the vector instruction that writes the broadcast operand and the product, on every path to it."""
+    """v_fmac_f64 with row_newbcast comes from inline assembly (svd_device.h), for which the compiler keeps no wait states."""
     objdump = "/opt/rocm/llvm/bin/llvm-objdump"
     if not os.path.exists(objdump):
         pytest.skip("no disassembler")
     data = open(binding.LIB_PATH, "rb").read()
     products = 0
-
-    def registers(operand):
-        m = re.match(r"-?v(?:\[(\d+):(\d+)\]|(\d+))", operand)
-        return set() if not m else {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
-
     for at in (m.start() for m in re.finditer(rb"\x7fELF\x02", data)):
         if struct.unpack_from("<H", data, at + 18)[0] != 224:    # EM_AMDGPU
             continue
@@ -187,39 +235,43 @@ def test_products_with_a_broadcast_operand_wait_for_it(tmp_path):
         text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True, text=True).stdout
         if "v_fmac_f64_dpp" not in text:
             continue
-        code, where = [], {}
+        code = []
         for line in text.split("\n"):
             m = re.match(r"\s+(\S+)(.*?)// ([0-9A-F]+):", line)
             if m:
-                where[int(m[3], 16)] = len(code)
                 code.append((m[1], m[2].strip(), int(m[3], 16)))
-        sources = {}
-        for i, (op, args, addr) in enumerate(code):
-            if op.startswith(("s_branch", "s_cbranch")):
-                offset = int(args.split()[0])
-                target = addr + 4 + 4 * (offset - 65536 if offset >= 32768 else offset)
-                sources.setdefault(target, []).append(i)
-
-        def writers(i, states):
-            """vector instructions in front of instruction i with fewer than `states` wait states between"""
-            before = list(sources.get(code[i][2], []))
-            if i > 0 and code[i - 1][0] not in ("s_branch", "s_endpgm"):
-                before.append(i - 1)
-            for j in before:
-                op, args, _ = code[j]
-                if op.startswith("v_"):
-                    yield j
-                left = states - (int(args) + 1 if op == "s_nop" else 1)
-                if left > 0:
-                    yield from writers(j, left)
-
-        for i, (op, args, addr) in enumerate(code):
-            if op == "v_fmac_f64_dpp":
-                products += 1
-                operand = registers(args.split(",")[1].strip())
-                for j in writers(i, 2):
-                    assert not operand & registers(code[j][1].split(",")[0].strip()), (hex(addr), code[j], args)
+        found, here = too_early(code)
+        assert not found, found[:3]
+        products += here
     assert products > 100
+
+
+PRODUCT = "v[0:1], -v[2:3], v[4:5] row_newbcast:3 row_mask:0xf bank_mask:0xf"
+
+
+@pytest.mark.parametrize("wrong, before", [
+    (True, [("v_add_f64", "v[2:3], v[6:7], v[8:9]")]),
+    (True, [("v_mov_b32_e32", "v3, v9"), ("s_nop", "0")]),
+    (False, [("v_mov_b32_e32", "v3, v9"), ("s_nop", "1")]),
+    (False, [("v_mov_b32_e32", "v3, v9"), ("v_mov_b32_e32", "v10, v11"), ("v_mov_b32_e32", "v10, v11")]),
+    (False, [("v_add_f64", "v[4:5], v[6:7], v[8:9]")]),
+    (True, [("v_permlane16_swap_b32_e32", "v12, v3"), ("s_nop", "0")]),
+    (True, [("v_swap_b32", "v2, v12")]),
+    (False, [("v_permlane32_swap_b32_e32", "v12, v3"), ("s_nop", "1")]),
+    (True, [("v_cmpx_gt_u32_e64", "exec, v20, v21"), ("s_nop", "3")]),
+    (False, [("v_cmpx_gt_u32_e64", "exec, v20, v21"), ("s_nop", "4")]),
+    (True, [("v_rcp_f64_e32", "v[4:5], v[6:7]")]),
+    (False, [("v_rcp_f64_e32", "v[4:5], v[6:7]"), ("s_nop", "0")]),
+    (True, [("v_mfma_f64_16x16x4_f64", "v[0:7], v[8:9], v[10:11], v[0:7]"), ("s_nop", "15")]),
+    (True, [("v_mov_b32_e32", "v3, v9"), ("s_branch", "1"), ("v_mov_b32_e32", "v30, v31")]),    # (behind the branch: the product)
+    (False, [("v_mov_b32_e32", "v3, v9"), ("s_branch", "2"), ("v_mov_b32_e32", "v30, v31")]),   # (never reached from it)
+])
+def test_what_is_too_early_in_front_of_a_broadcast_is_found(wrong, before):
+    code = [("s_nop", "7", 0), ("s_nop", "7", 4)]
+    for op, args in before + [("v_fmac_f64_dpp", PRODUCT), ("s_endpgm", "")]:
+        code.append((op, args, 4 * len(code)))
+    found, products = too_early(code)
+    assert products == 1 and bool(found) == wrong
 
 
 def test_lanes_that_exchange_values_through_lds_have_fences():
