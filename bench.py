@@ -609,12 +609,20 @@ def batch64_leg(ctx, torch, binding, inputs, with_oracle, reps=3):
     return out
 
 
+SAMPLED_FROM = 1 << 25        # elements from which on the entry-wise encoder reads a gradient once, against a level that a sample predicts
+
+
+def entrywise_bytes(n, kept):
+    """Traffic of an entry-wise encode + decode: two reads of g (a global reduction precedes the draws; one where a sample does instead) and
+    one dense write, 4 B per element each, and 8 B out and 12 B in/out per kept pair."""
+    return (8.0 if n >= SAMPLED_FROM else 12.0) * n + 20.0 * kept
+
+
 def entrywise_leg(ctx, torch, binding, inputs, reps=40, sets=8):
     """The entry-wise path on the full flat gradient (11,173,962 elements, s = N/100), outside the timed
     steps of the headline metric: encode + decode, HBM-bound.  Eight input/message/output sets are rotated
     so that one repetition does not find the previous one's data in the last-level cache.  Algorithmic
-    traffic: two reads of g (a global reduction must precede sampling) and one dense write, 12 B per
-    element, plus 8 B out and 12 B in/out per kept pair."""
+    traffic: entrywise_bytes; the l_q encoder reads g twice at any length."""
     n = inputs.RESNET18_PARAMETERS
     g = torch.from_numpy(inputs.flat_heavy_tail(0))
     s = n / 100
@@ -647,7 +655,7 @@ def entrywise_leg(ctx, torch, binding, inputs, reps=40, sets=8):
             if cnt:
                 prof[name] = prof.get(name, 0.0) + ms
     ctx.profile_enable(False)
-    nbytes = 12.0 * n + 20.0 * kept
+    nbytes = entrywise_bytes(n, kept)
     # l_q quantisation of the same gradient (1-bit QSGD, TernGrad): norm pass instead of the histograms
     lq = {}
     for name, q in (("qsgd_1bit_q2", 2.0), ("terngrad_qinf", float("inf"))):
@@ -694,7 +702,7 @@ def entrywise_leg(ctx, torch, binding, inputs, reps=40, sets=8):
             torch.cuda.synchronize()
             dl = (time.perf_counter() - t0) / 5
             kl = int(ml.count.item())
-            bl = 12.0 * nl + 20.0 * kl
+            bl = entrywise_bytes(nl, kl)
             large = {"elements": nl, "kept": kl, "ms_per_step": round(dl * 1e3, 3), "elements_per_s": nl / dl,
                      "hbm_gbs": round(bl / dl / 1e9, 1), "hbm_frac": round(bl / dl / 1e9 / PEAK_HBM_GBS, 4)}
         del gl, ml, ol

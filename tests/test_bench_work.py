@@ -33,3 +33,13 @@ def test_a_layer_is_priced_by_the_route_it_reports(shape):
     assert flops == direct["svd_direct_gram"][1] and peak == pytest.approx(bench.PEAK_FP64_TFLOPS)
     flops, peak = bench.matrix_core_work(iterated, 0.0)
     assert flops > 0 and peak == pytest.approx(bench.PEAK_FP32_MFMA_TFLOPS)
+
+
+def test_a_long_gradient_is_priced_as_one_read():
+    # the encoder's own limit, as the source has it
+    import os
+    import re
+    source = open(os.path.join(os.path.dirname(bench.__file__), "paper_1806_04090_amd", "csrc", "entrywise.hip")).read()
+    assert bench.SAMPLED_FROM == 1 << int(re.search(r"constexpr long long LONG_FROM = 1ll << (\d+);", source)[1])
+    assert bench.entrywise_bytes(2 ** 25 - 1, 0) == 12 * (2 ** 25 - 1) and bench.entrywise_bytes(2 ** 25, 0) == 8 * 2 ** 25
+    assert bench.entrywise_bytes(2 ** 30, 10) == 8 * 2 ** 30 + 200
