@@ -138,3 +138,46 @@ def test_a_power_of_infinity(q, n):
     msg = binding.atomo_encode_lq(ctx(), dev(g), q, 1, 0, msg=binding.alloc_lq_message(n, n, "cuda"))
     np.testing.assert_allclose(float(msg.norm.item()), (n - 1) ** (1 / q), rtol=2.0 ** -24 * 1.001)
     ctx().status()
+
+
+def uniforms_on_the_device(n, stream, seed):
+    """The uniforms of a message, times 2^24: Philox4x32-10 in 64-bit integers."""
+    low = 0xFFFFFFFF
+    block = torch.arange((n + 3) // 4, device="cuda")
+    c = [block & low, block >> 32, torch.full_like(block, stream & low), torch.full_like(block, stream >> 32)]
+    k = [seed & low, seed >> 32]
+    for _ in range(10):
+        p0, p1 = c[0] * 0xD2511F53, c[2] * 0xCD9E8D57            # (modulo 2^64: the bits of the product)
+        c = [(p1 >> 32 & low) ^ c[1] ^ k[0], p1 & low, (p0 >> 32 & low) ^ c[3] ^ k[1], p0 & low]
+        k = [(k[0] + 0x9E3779B9) & low, (k[1] + 0xBB67AE85) & low]
+    return (torch.stack(c, 1).view(-1)[:n] >> 8).to(torch.float32)
+
+
+def test_uniforms_on_the_device_are_the_oracles():
+    u = uniforms_on_the_device(10_001, 3, 5 + (7 << 40)).cpu().numpy()
+    assert np.array_equal(u * np.float32(2.0 ** -24), oracle.uniforms(5 + (7 << 40), 3, 10_001))
+
+
+@pytest.mark.parametrize("q", [2.0, 1.5, INF, 4.5])                      # (sums of squares, a table, a maximum, pow)
+@pytest.mark.parametrize("n, offset", [(41_999_999, 0), (42_000_001, 0), (42_004_099, 1)])
+def test_gradients_read_around_the_last_cache(n, offset, q):
+    """From 42 million elements on both passes load past the cache.  Norm and p against torch in double precision: each is one rounding to
+    fp32 of a value good to 2^-50; what is kept is then the comparison of the oracle's uniforms with that p."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    g = torch.randn(n + 1, generator=gen, device="cuda")[offset:offset + n]
+    g *= torch.rand(n, generator=gen, device="cuda") ** 3
+    g[-5:] *= 50.0                                               # (the ragged end counts)
+    p = torch.zeros(n, device="cuda")
+    msg = binding.alloc_lq_message(n, n // 20, "cuda")
+    binding.atomo_encode_lq(ctx(), g, q, 5, 3, msg=msg, p_out=p)
+    assert ctx().status()[0] == 0
+    a = g.double().abs()
+    norm = a.max() if np.isinf(q) else (a ** q).sum() ** (1.0 / q)
+    assert abs(float(msg.norm) / float(norm) - 1.0) <= 2.0 ** -24 * 1.001
+    assert bool(((p.double() - (a / norm).clamp(max=1.0)).abs() <= 2.0 ** -24 * 1.001 * (a / norm) + 2.0 ** -150).all())
+    kept = torch.nonzero(uniforms_on_the_device(n, 3, 5) * 2.0 ** -24 < p).view(-1)
+    count = int(msg.count)
+    assert count == kept.numel() > 100
+    words = msg.idx[:count].long() & 0xFFFFFFFF
+    assert torch.equal(words & 0x7FFFFFFF, kept) and torch.equal(words >> 31 != 0, g[kept] < 0)

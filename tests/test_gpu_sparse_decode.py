@@ -122,3 +122,35 @@ def test_one_message_on_both_sides_of_its_own_kernel(n, k, offset, lq):
     binding.atomo_decode(ctx(), [m], scale=0.5, out=out[offset:offset + n])
     assert torch.equal(out, want)
     assert ctx().status()[0] == 0
+
+
+@pytest.mark.parametrize("lq", [False, True])
+@pytest.mark.parametrize("n", [96_000_000 - 1, 96_000_000 + 3])
+@pytest.mark.parametrize("messages, offset", [(1, 0), (3, 0), (3, 1), (5, 0)])
+def test_outputs_written_around_the_last_cache(n, messages, offset, lq):
+    """From 96 million outputs of one to four messages on.  Against a sum of the messages in their order, in fp32 on the device: the same bits."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(messages)
+    want, msgs = torch.zeros(n, device="cuda"), []
+    for j in range(messages):
+        idx = torch.randint(0, n, (200_000 * (j + 1),), generator=gen, device="cuda")
+        idx[:3] = torch.tensor([0, n - 1, n - 4], device="cuda")
+        idx = torch.unique(idx)
+        val = torch.randn(idx.numel(), generator=gen, device="cuda")
+        m = (binding.alloc_lq_message if lq else binding.alloc_entrywise_message)(n, idx.numel(), "cuda")
+        m.count.fill_(idx.numel())
+        if lq:
+            m.norm.fill_(0.5 + j)
+            m.idx.copy_((idx | (val < 0).long() << 31).to(torch.int32))
+            val = torch.where(val < 0, -1.0, 1.0) * (m.norm * 0.5)
+        else:
+            m.idx.copy_(idx.to(torch.int32))
+            m.val.copy_(val)
+            val = val * 0.5
+        want[idx] += val                                         # (every coordinate once per message)
+        msgs.append(m)
+    out = torch.full((n + 4,), 9.0, device="cuda")
+    binding.atomo_decode(ctx(), msgs, scale=0.5, out=out[offset:offset + n])
+    assert ctx().status()[0] == 0
+    assert torch.equal(out[offset:offset + n], want)
+    assert bool((out[:offset] == 9).all()) and bool((out[offset + n:] == 9).all())
