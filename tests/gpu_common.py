@@ -19,6 +19,19 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
+def uniforms_on_the_device(n, stream, seed):
+    """The uniforms of a message, times 2^24: Philox4x32-10 in 64-bit integers."""
+    low = 0xFFFFFFFF
+    block = torch.arange((n + 3) // 4, device="cuda")
+    c = [block & low, block >> 32, torch.full_like(block, stream & low), torch.full_like(block, stream >> 32)]
+    k = [seed & low, seed >> 32]
+    for _ in range(10):
+        p0, p1 = c[0] * 0xD2511F53, c[2] * 0xCD9E8D57            # (modulo 2^64: the bits of the product)
+        c = [(p1 >> 32 & low) ^ c[1] ^ k[0], p1 & low, (p0 >> 32 & low) ^ c[3] ^ k[1], p0 & low]
+        k = [(k[0] + 0x9E3779B9) & low, (k[1] + 0xBB67AE85) & low]
+    return (torch.stack(c, 1).view(-1)[:n] >> 8).to(torch.float32)
+
+
 def sigma_tolerance_ok(got, want):
     """|got - want| <= 1e-4 * max(want, 1e-3 * want_max): relative 1e-4, floored for tiny singular values."""
     want = np.asarray(want, dtype=np.float64)

@@ -5,7 +5,7 @@ import torch
 
 import oracle
 from paper_1806_04090_amd import binding, inputs
-from gpu_common import ctx, dev
+from gpu_common import ctx, dev, uniforms_on_the_device
 
 pytestmark = pytest.mark.gpu
 
@@ -447,3 +447,48 @@ def test_long_gradients_whose_level_a_sample_predicts(kind, extra):
     h, ref = msg.to_host(), oracle.encode_entrywise(g, s, 5, 2, p32=p)
     assert h["count"] == ref["idx"].size and np.array_equal(h["idx"], ref["idx"])
     np.testing.assert_allclose(h["val"], ref["val"], rtol=1e-6, atol=2.0 ** -149)
+
+
+@pytest.mark.parametrize("kind", ["plain", "apart", "scattered", "misleading", "many_near_the_level", "zeros"])
+@pytest.mark.parametrize("n", [2 ** 26 + 4099, 2 ** 28 + 3])
+def test_longer_gradients_than_one_round_of_the_draws(n, kind):
+    """From 2^26 elements on a workgroup of the draws takes several groups of segments, one after the other.  Against torch on the device: p
+    is min(1, |g| (s - n_s) / tail), one rounding to fp32 of a value in double precision, with the n_s and the tail that it leaves itself,
+    and what is kept is the comparison of the oracle's uniforms with it."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    g = torch.randn(n, generator=gen, device="cuda")
+    s = n / 100
+    if kind == "apart":                                          # (a window of wider buckets: rows that are alike)
+        rows = (torch.rand(n // 64 + 1, generator=gen, device="cuda") < 0.03).float() * torch.rand(n // 64 + 1, generator=gen, device="cuda")
+        g *= rows.repeat_interleave(64)[:n]
+        s = n / 500
+    elif kind == "scattered":                                    # (no window)
+        g[torch.randint(0, n, (3,), generator=gen, device="cuda")] = float(n)
+        s = 2.5
+    elif kind == "misleading":                                   # (the level is not in the window)
+        g[~torch.from_numpy(sampled(n)).cuda()] *= 3.0
+    elif kind == "many_near_the_level":
+        s = 0.6 * n
+    elif kind == "zeros":
+        g[torch.rand(n, generator=gen, device="cuda") < 0.995] = 0
+    p = torch.zeros(n, device="cuda")
+    msg = binding.alloc_entrywise_message(n, n if s > n / 10 else n // 50, "cuda")
+    for _ in range(2):                                           # (the second call finds what the first one left)
+        binding.atomo_encode_entrywise(ctx(), g, s, 5, 2, msg=msg, p_out=p)
+    assert ctx().status()[0] == 0
+    capped = p == 1.0
+    tail, n_s, most = 0.0, int(capped.sum()), 0.0
+    for part, c in zip(g.split(2 ** 26), capped.split(2 ** 26)):  # (in double precision a part at a time)
+        rest = torch.where(c, 0.0, part.abs()).double()
+        tail, most = tail + float(rest.sum()), max(most, float(rest.max()))
+    ratio = (s - n_s) / tail if tail > 0 else float("inf")
+    assert s >= n_s and (tail == 0 or most * ratio <= 1.0 + 2.0 ** -24)
+    for part, q in zip(g.split(2 ** 26), p.split(2 ** 26)):
+        want = torch.where(part == 0, 0.0, (part.double().abs() * ratio).clamp(max=1.0))
+        assert bool(((q.double() - want).abs() <= 2.0 ** -24 * 1.001 * want + 2.0 ** -149).all())
+    kept = torch.cat([torch.nonzero(u * 2.0 ** -24 < q).view(-1) + at * 2 ** 26 for at, (u, q) in
+                      enumerate(zip(uniforms_on_the_device(n, 2, 5).split(2 ** 26), p.split(2 ** 26)))])
+    assert int(msg.count) == kept.numel() > 0
+    assert torch.equal(msg.idx[:kept.numel()].long() & 0xFFFFFFFF, kept)
+    assert torch.equal(msg.val[:kept.numel()], g[kept] / p[kept])

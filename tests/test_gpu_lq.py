@@ -5,7 +5,7 @@ import torch
 
 import oracle
 from paper_1806_04090_amd import binding, inputs
-from gpu_common import ctx, dev
+from gpu_common import ctx, dev, uniforms_on_the_device
 
 pytestmark = pytest.mark.gpu
 
@@ -138,19 +138,6 @@ def test_a_power_of_infinity(q, n):
     msg = binding.atomo_encode_lq(ctx(), dev(g), q, 1, 0, msg=binding.alloc_lq_message(n, n, "cuda"))
     np.testing.assert_allclose(float(msg.norm.item()), (n - 1) ** (1 / q), rtol=2.0 ** -24 * 1.001)
     ctx().status()
-
-
-def uniforms_on_the_device(n, stream, seed):
-    """The uniforms of a message, times 2^24: Philox4x32-10 in 64-bit integers."""
-    low = 0xFFFFFFFF
-    block = torch.arange((n + 3) // 4, device="cuda")
-    c = [block & low, block >> 32, torch.full_like(block, stream & low), torch.full_like(block, stream >> 32)]
-    k = [seed & low, seed >> 32]
-    for _ in range(10):
-        p0, p1 = c[0] * 0xD2511F53, c[2] * 0xCD9E8D57            # (modulo 2^64: the bits of the product)
-        c = [(p1 >> 32 & low) ^ c[1] ^ k[0], p1 & low, (p0 >> 32 & low) ^ c[3] ^ k[1], p0 & low]
-        k = [(k[0] + 0x9E3779B9) & low, (k[1] + 0xBB67AE85) & low]
-    return (torch.stack(c, 1).view(-1)[:n] >> 8).to(torch.float32)
 
 
 def test_uniforms_on_the_device_are_the_oracles():
