@@ -29,6 +29,11 @@ enum : uint8_t { ROUTE_ITERATE = 0, ROUTE_BOTH = 1, ROUTE_DIRECT = 2 };
 // Events between streams of this device, and one that tells the host that a kernel has ended whose words for it are fenced: without
 // the flush to the host and to other devices that an event makes otherwise.  Between two kernels of a stream such an event takes
 // 1.1 us, with that flush 3.
+// HIP describes the flag for events that only take the time, whose inspection by the host need not synchronise with the work in front
+// of them.  What is relied on here is less than that and more: the host's words are fenced in the kernel that writes them
+// (__threadfence_system), and what a stream finds behind hipStreamWaitEvent rests on the release of device scope that every kernel
+// ends with and the acquire that the next one begins with, by which the kernels of one stream see each other's results on other dies too.
+// The latter is how the runtime works (ROCm 7, one device) and not a promise of the flag; it does not reach memory of other devices.
 constexpr unsigned ON_DEVICE_EVENT = hipEventDisableTiming | hipEventDisableSystemFence;
 
 // What an SVD encode learnt about its matrices, for the calls after it (atomo_svd_options.adaptive).

@@ -464,9 +464,9 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // row of the next step (handed over a step early, the readers add the update that it lacks) come behind it, while the entries
 // travel; the loads that look for them go out in the middle of that work (a load of 512 bytes by every wave takes 250 cycles, four of
 // them 460, whether the entries are there or not; a look that is too early costs a second one, at the entries of A y alone: the row has
-// been there for a step.  One step in three has one; with the row looked at again the ResNet-18 layers 467 us, 601 x 1237 and smaller ones 609,
-// without 452 and 594).  The ResNet-18 layers in 468 us with
-// the look there, 495 behind the reflector's vector, 575 in front of the update; two looks on their way at once 485.
+// been there for a step; one step in three has one).  The ResNet-18 layers, the figures of a sentence from one card each.  With the look there
+// 468 us, behind the reflector's vector 495, in front of the update 575, two looks on their way at once 485.  With the second look at the
+// entries alone 452, at the row too 467 (601 x 1237 and smaller ones 594 and 609).
 // An entry is one 8-byte store whose two lowest mantissa bits carry a tag that tells it from the one that lay there before: a reader
 // knows from the value that it is the one of this step, no flag and no second round trip.  Two slots for A y by step parity: a wave
 // that publishes step k + 1 has read all of step k, so when a wave has read all of step k + 1 nobody needs slot k any more; four for
@@ -480,9 +480,10 @@ __device__ inline double scale_of(const DirectMat& m, int off, int lane, int& ex
 // workgroups need, and partial groups of three calls can hold each other's.  So every wait has a bound, and a group that does
 // not come together leaves as one (Gate); the last of its workgroups to start reduces the matrix alone.
 // Bound: what a wave does for itself in a step, one wave on every SIMD: without the waits for the others a step takes as long.  448
-// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 446 us in all (by one card; by another 467, and 452 with
-// the second look as it is), 452 with the loop where the compiler puts it (517 -> 468, on another card, without a chain of branches and v_readlane for what a vector holds at the wave's rows,
-// a reduction of its own for the norm, and the reflector behind the update; 800 of 3500 cycles).  Rows and columns split between the
+// steps of 512 rows on 128 waves: 3000 cycles each at the beginning and 2000 at the end, 442 us in all in the profile of the ResNet-18 step.
+// What it was before, each pair from one card: 452 instead of 446 with the loop where the compiler puts it; 517 instead of 468 with a chain of
+// branches and v_readlane for what a vector holds at the wave's rows, a reduction of its own for the norm, and the reflector in front of the
+// update (800 of 3500 cycles).  Rows and columns split between the
 // waves of a workgroup, two instead of eight entries of a vector per lane: 566, for a second barrier and sums of sixteen rows.  Four
 // groups per die, two waves on every SIMD: the issue of the vectors that every wave works out for itself (direct_tridiagonal_few).
 //

@@ -439,8 +439,9 @@ __device__ inline double twisted_vector(const doublex2* t, const double* e, int 
 // after the other and its Philox rounds behind the spectrum (4.3), the header in front of the way back (2.4), always three rounds for a vector
 // (15), one reflector at a time (5.2), all of 32 columns in the reduction (21.5).  T takes 96 of its 224 registers for 18 columns, 128 for 32: two waves on
 // every SIMD do not fit beside a workgroup of the reduction of larger matrices (251 registers), and where those fill
-// the chip it waits for the first of them to end.  That costs a call nothing: the directly solved layers of ResNet-18 with its two thin
-// ones 851 us, 852 with a form of 124 registers that fitted; with 256 chunks of positions 853 and 857, with 100 small matrices 859 and 860.
+// the chip it waits for the first of them to end.  That costs a call nothing, measured with a form of 158 registers, which did not fit either:
+// the directly solved layers of ResNet-18 with its two thin ones 851 us, 852 with a form of 124 registers that fitted; with 256 chunks of
+// positions 853 and 857, with 100 small matrices 859 and 860.
 // Bound: latency.  Jacobi: one barrier per round of the tournament.  A is in two buffers: a round reads one and writes the other, one
 // 2 x 2 block per thread; other threads rotate the vectors in place, two pairs of entries each.  Every wave works out all
 // rotations of the round for itself and hands them around inside.
