@@ -492,3 +492,26 @@ def test_longer_gradients_than_one_round_of_the_draws(n, kind):
     assert int(msg.count) == kept.numel() > 0
     assert torch.equal(msg.idx[:kept.numel()].long() & 0xFFFFFFFF, kept)
     assert torch.equal(msg.val[:kept.numel()], g[kept] / p[kept])
+
+
+@pytest.mark.parametrize("kind, keep", [("normal", 0.01), ("normal", 0.3), ("normal", 0.7), ("normal", 1.0), ("two_values", 0.3), ("two_values", 0.7)])
+def test_long_and_short_segments_give_one_message(kind, keep):
+    """A gradient one element below 2^25, and the same with two zeros behind it, which takes the path of a sample: level, draws and so the message
+    are the same, and it takes no longer if its segments run over their slots (the whole gradient kept: 1.37 times as long where a segment
+    that had run over went on to queue its candidates)."""
+    n = 2 ** 25 - 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    g = torch.zeros(n + 2, device="cuda")
+    if kind == "normal":
+        g[:n].normal_(generator=gen)
+    else:
+        g[:n] = torch.where(torch.rand(n, generator=gen, device="cuda") < 0.5, 1.0, -1.25)
+    msgs = [binding.alloc_entrywise_message(n + k, n, "cuda") for k in (0, 2)]
+    times = [encode_time(g[:n + k], keep * n, m) for k, m in zip((0, 2), msgs)]
+    assert ctx().status()[0] == 0
+    count = int(msgs[0].count)
+    assert count == int(msgs[1].count) > 0
+    assert torch.equal(msgs[0].idx[:count], msgs[1].idx[:count]) and torch.equal(msgs[0].val[:count], msgs[1].val[:count])
+    if keep > 0.01:
+        assert times[1] < 1.2 * times[0], times
