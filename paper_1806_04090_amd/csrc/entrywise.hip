@@ -140,8 +140,8 @@ __device__ inline void flush_hist(const unsigned long long* acc, EwState* st)
 
 // Level-LEVEL histogram of the elements on the path `prefix`, by the TPB threads of workgroup `self` of `members` (all call):
 // accumulated in the LDS array acc (COPIES x NB packed words), then added to the global histogram.
-// ZEROS: zeros are counted (for the search they are not there; a test for each element costs more than they do where there are few).
-template <int LEVEL, int TPB, bool ZEROS = true>
+// Zeros may be counted or not: for the search they are not there.
+template <int LEVEL, int TPB>
 __device__ inline void hist_body(const float* __restrict__ g, long long n, EwState* st, unsigned long long* acc, unsigned int prefix,
                                  unsigned int self, unsigned int members)
 {
@@ -159,7 +159,6 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
     auto visit = [&](float x) {
         const unsigned int key = __float_as_uint(x) & 0x7FFFFFFFu;
         const unsigned long long word = (1ull << 40) | (unsigned long long)significand(key);
-        if (!ZEROS && key == 0u) return;
         if (LEVEL == 0) {
             atomicAdd(&acc[copy + (key >> SHIFT)], word);
         } else {
@@ -169,19 +168,38 @@ __device__ inline void hist_body(const float* __restrict__ g, long long n, EwSta
     };
 
     const bool vec = (((size_t)g) & 15) == 0;
-    const long long n4 = vec ? n / 4 : 0;
+    const long long n4 = n / 4;
     const long long stride = (long long)members * TPB;
-    // four loads in flight per thread: one at a time, the pass is a chain of memory latencies
+    // Four loads in flight per thread: one at a time, the pass is a chain of memory latencies.  Level 0: four neighbours of one bucket are
+    // one addition, and none if they are zeros: a gradient that is sparse or of few values queues in a few words of the LDS otherwise, the
+    // more so the fewer workgroups there are (encode of three million elements, one in 200 not zero, 36.8 -> 24.6 us, all of one magnitude
+    // 34.8 -> 23.4; with 256 workgroups instead of 91 and without this 30.7 and 26.6; normal ones 26.4 -> 26.6, with 256 27.6).
     for (long long q0 = (long long)self * TPB + threadIdx.x; q0 < n4; q0 += 4 * stride) {
         float4 x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const long long q = q0 + u * stride;
-            if (q < n4) x[u] = ((const float4*)g)[q];
+            if (q < n4) x[u] = vec ? ((const float4*)g)[q] : make_float4(g[4 * q], g[4 * q + 1], g[4 * q + 2], g[4 * q + 3]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (q0 + u * stride < n4) { visit(x[u].x); visit(x[u].y); visit(x[u].z); visit(x[u].w); }
+            if (q0 + u * stride >= n4) continue;
+            if (LEVEL == 0) {
+                const float xs[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+                unsigned int key[4], sum = 0u, some = 0u, apart = 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    key[e] = __float_as_uint(xs[e]) & 0x7FFFFFFFu;
+                    sum += significand(key[e]);
+                    some |= key[e];
+                    apart |= key[e] ^ key[0];
+                }
+                if (apart >> SHIFT == 0u) {
+                    if (some) atomicAdd(&acc[copy + (key[0] >> SHIFT)], (4ull << 40) | (unsigned long long)sum);
+                    continue;
+                }
+            }
+            visit(x[u].x); visit(x[u].y); visit(x[u].z); visit(x[u].w);
         }
     }
     for (long long i = n4 * 4 + (long long)self * TPB + threadIdx.x; i < n; i += stride) visit(g[i]);
@@ -650,7 +668,7 @@ __global__ __launch_bounds__(1024) void ew_confirm(const float* __restrict__ g, 
     }
     for (unsigned int self = blockIdx.x; self < members; self += gridDim.x) {
         __syncthreads();
-        hist_body<0, 1024, false>(g, n, st, acc, 0u, self, members);
+        hist_body<0, 1024>(g, n, st, acc, 0u, self, members);
     }
     clear_level(st, 1);
     if (!last_workgroup(st->ticket, blockIdx.x, gridDim.x)) return;
