@@ -274,6 +274,19 @@ __device__ __forceinline__ void decode_tile(DecLds& lds, const DecOut* outs, con
         }
     }
     const Global<float> corner = global(o.out) + (long long)row0 * o.ld + col0;
+    // A whole tall tile: no look at the row in front of every store, which is a branch each (600,000 rows, three atoms of each of four
+    // messages: 25 columns 24.8 -> 21.9 us, 24 columns with gaps 26.3 -> 23.0; 23.2 and 24.9 without the form above beside them)
+    if constexpr (TALL && !ACCUMULATE) {
+        if (tile_r0 + TALL_ROWS <= o.rows) {
+            if (l32 < o.cols) {
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) corner[below(rb, v) * o.ld] = acc[rb][0][v];
+            }
+            return;
+        }
+    }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll

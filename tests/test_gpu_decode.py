@@ -157,3 +157,37 @@ def test_svd_decode_of_narrow_outputs_without_gaps(rows, cols, offset):
         size = oracle.decode_svd([{key: np.abs(x) for key, x in h.items()} for _, h in pairs], rows, cols, scale=0.5)
         assert (np.abs(out.cpu().numpy() - want) <= (sum(ks) + 4) * 2.0 ** -23 * size).all()
         assert bool((flat[:offset] == 7.5).all()) and bool((flat[offset + rows * cols:] == 7.5).all())
+
+
+@pytest.mark.parametrize("rows,cols,gap", [(256, 25, 0), (512, 32, 0), (769, 31, 0), (255, 28, 0), (512, 18, 3), (600, 24, 1), (256, 1, 1), (1025, 32, 5)])
+def test_svd_decode_of_tall_tiles_that_are_not_one_piece_of_memory(rows, cols, gap):
+    """More than 24 columns, or gaps between the rows: whole tiles and the last one.  What lies between and behind the rows stays.  Tolerance as above."""
+    rng = np.random.default_rng(rows + cols)
+    for ks in ([3], [0], [2, 0, 17]):
+        pairs = [make_msg(rng, rows, cols, k, 20) for k in ks]
+        flat = torch.full((rows + 2, cols + gap), 7.5, device="cuda")
+        out = flat[1:rows + 1, :cols]
+        binding.atomo_decode_svd_batch(ctx(), [[m for m, _ in pairs]], 0.5, outs=[out])
+        want = oracle.decode_svd([h for _, h in pairs], rows, cols, scale=0.5)
+        size = oracle.decode_svd([{key: np.abs(x) for key, x in h.items()} for _, h in pairs], rows, cols, scale=0.5)
+        assert (np.abs(out.cpu().numpy() - want) <= (sum(ks) + 4) * 2.0 ** -23 * size).all()
+        assert bool((flat[0] == 7.5).all()) and bool((flat[rows + 1] == 7.5).all()) and bool((flat[:, cols:] == 7.5).all())
+
+
+def test_more_than_24_columns_take_no_longer_for_the_form_of_fewer():
+    # 600,000 rows: 25 columns took 1.14 times as long as 24 with the form for up to 24 in the same kernel, 0.97 times without it
+    rng, times = np.random.default_rng(3), []
+    for cols in (24, 25):
+        pairs = [make_msg(rng, 600_000, cols, 3, 3) for _ in range(4)]
+        out = torch.zeros(600_000, cols, device="cuda")
+        took = []
+        for _ in range(15):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                binding.atomo_decode_svd_batch(ctx(), [[m for m, _ in pairs]], 1.0, outs=[out])
+            end.record()
+            end.synchronize()
+            took.append(start.elapsed_time(end))
+        times.append(min(took))
+    assert times[1] < 1.09 * times[0], times
