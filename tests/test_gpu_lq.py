@@ -168,3 +168,12 @@ def test_gradients_read_around_the_last_cache(n, offset, q):
     assert count == kept.numel() > 100
     words = msg.idx[:count].long() & 0xFFFFFFFF
     assert torch.equal(words & 0x7FFFFFFF, kept) and torch.equal(words >> 31 != 0, g[kept] < 0)
+
+
+@pytest.mark.parametrize("q", [0.5, 1.5, 4.0])
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2049])                   # (a table of powers from 1025 elements on)
+def test_a_power_per_thread_and_more(n, q):
+    rng = np.random.default_rng(n)
+    g = (rng.standard_normal(n) * np.exp(rng.standard_normal(n))).astype(np.float32)
+    g[rng.random(n) < 0.5] = 0
+    parity(g, q, seed=3, stream=n)
